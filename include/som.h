@@ -347,7 +347,9 @@ int som_set_smoothing(som_ctx *ctx, int form);
  *                  ordered by their best block, and the split-fp16 pass runs over the remaining
  *                  (128 instances, block) pairs only.  Needs 6 bytes per element of extra device memory
  *                  and 4 bytes per instance and node block.
- *   SOM_FILTER_AUTO (default)  SOM_FILTER_TWO_LEVEL for maps of 1,024 nodes or more whose table of
+ *   SOM_FILTER_AUTO (default)  small searches run without any filter pass, all distances in fp64 on the
+ *                  matrix cores (some 1e9 multiply-adds in all; som_get_stats then reports zeros);
+ *                  beyond that SOM_FILTER_TWO_LEVEL for maps of 1,024 nodes or more whose table of
  *                  block minima (4 bytes x instances x nodes / 128) stays under 8 GiB, else
  *                  SOM_FILTER_SPLIT_F16.
  *   SOM_FILTER_FP32  fp32 matrix instructions on the operands as they are.

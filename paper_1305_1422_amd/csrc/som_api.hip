@@ -83,6 +83,10 @@ static void dev_free(T *&p) {
   p = nullptr;
 }
 
+// Dense data searched in double precision outright (bmu_direct.hip)?  Only where the caller left the choice of the
+// filter to the library.
+static bool direct_search(const som_ctx *c, int64_t n) { return c->filter == SOM_FILTER_AUTO && direct_search_pays(c, n); }
+
 // The dense filter runs on fp16 planes (one-level split pass or the two-level search).
 static bool uses_planes(const som_ctx *c) { return c->filter != SOM_FILTER_FP32; }
 
@@ -120,12 +124,28 @@ static void free_row_scratch(som_ctx *c) {
   c->csrd_on = 0;
 }
 
-// Scratch that scales with the number of instances; grown (never shrunk) on demand.
-static int ensure_rows(som_ctx *c, int64_t n, bool dense) {
-  const bool split = dense && uses_planes(c);
+// Records of the direct search.
+static int ensure_direct(som_ctx *c, int64_t n) {
+  const size_t need = direct_record_bytes(c, n);
+  if (need <= c->direct_cap) return SOM_OK;
+  (void)hipStreamSynchronize(c->stream);
+  if (c->direct_rec) (void)hipFree(c->direct_rec);
+  c->direct_rec = nullptr;
+  c->direct_cap = 0;
+  if (hipMalloc(&c->direct_rec, need) != hipSuccess)
+    return fail(c, SOM_ERR_ALLOC, "cannot allocate the records of %lld instances", (long long)n);
+  c->direct_cap = need;
+  return SOM_OK;
+}
+
+// Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
+// will run on them (false: the direct search, or an update alone).
+static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) {
+  const bool split = dense && filtered && uses_planes(c);
   // sized for the rows the scratch is (or will be) allocated for, so that it serves every n up to n_cap
   const bool coarse = split && two_level(c, n > c->n_cap ? n : c->n_cap);
-  const bool need_partial = (dense && (c->partial == nullptr || c->Wc == nullptr)) || c->collect_list == nullptr ||
+  const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && c->Wc == nullptr) ||
+                            (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
                             (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr));
   if (n <= c->n_cap && !need_partial) return SOM_OK;
@@ -152,11 +172,11 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense) {
     if (!dev_alloc(&c->partial, (size_t)c->max_chunks * c->dim))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate %lld x %d partial sums", (long long)c->max_chunks, c->dim);
   }
-  if (c->collect_list == nullptr) {
+  if (filtered && c->collect_list == nullptr) {
     if (!dev_alloc(&c->collect_list, (size_t)c->n_cap * kListCap))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate candidate lists for %lld instances", (long long)c->n_cap);
   }
-  if (dense && c->Wc == nullptr) {
+  if (dense && filtered && c->Wc == nullptr) {
     if (!dev_alloc(&c->Wc, (size_t)c->k * c->dim))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the centred code book (%d x %d)", c->k, c->dim);
   }
@@ -324,7 +344,24 @@ static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split,
   return SOM_OK;
 }
 
+// Small search: one or two kernels, no filter pass and no per-instance preparation.
+static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus) {
+  c->two_level_n = 0;
+  c->stats_none = 1;
+  StageTimer t(c, 0);
+  const float *mask = nullptr;
+  if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) {
+    SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->wn32, c->k));
+    SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
+    mask = c->wn32;
+  }
+  SOM_LAUNCH(c, launch_direct_search(c, X, n, W, mask, bmus));
+  return SOM_OK;
+}
+
 static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn) {
+  if (direct_search(c, n)) return bmu_search_direct(c, X, n, W, bmus);
+  c->stats_none = 0;
   int rc = ensure_candidates(c, n, true);
   if (!rc) rc = prepare_dense(c, X, n, W, have_xn);
   if (rc) return rc;
@@ -402,6 +439,7 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
                                  int64_t n, const float *W, int32_t *bmus) {
   int rc = ensure_candidates(c, n, true);
   if (rc) return rc;
+  c->stats_none = 0;
   ensure_rescan_copy(c);
   PlaneOperands swap(c);
   const bool coarse = two_level_ready(c, n);
@@ -435,6 +473,7 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus);
   int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn);
   if (rc) return rc;
+  c->stats_none = 0;
   ensure_rescan_copy(c);
   // registered rows whose frequent columns were split off: the sweeps walk the tail and start from the
   // matrix-core pass over the hot block; the exact kernels keep the caller's full rows
@@ -715,6 +754,7 @@ void som_destroy(som_ctx *c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   free_row_scratch(c);
+  if (c->direct_rec) (void)hipFree(c->direct_rec);
   dev_free(c->wn32); dev_free(c->wn64); dev_free(c->wmax_bits); dev_free(c->counts); dev_free(c->seg_off);
   dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->row_hash); dev_free(c->dedup_keys);
   dev_free(c->dedup_lowest); dev_free(c->cntT); dev_free(c->gx); dev_free(c->gy);
@@ -741,9 +781,10 @@ int som_bmus_dense(som_ctx *c, const float *data, int64_t n, const float *codebo
   if (!c) return SOM_ERR_INVALID_ARG;
   if (!data || !codebook || !bmus) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
-  if (!rc) rc = ensure_rows(c, n, true);
+  const bool direct = !rc && direct_search(c, n);
+  if (!rc) rc = direct ? ensure_direct(c, n) : ensure_rows(c, n, true);
   bool reg = false;
-  if (!rc && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
+  if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
   if (rc) return rc;
   return bmu_search_dense(c, data, n, codebook, bmus, reg);
 }
@@ -810,7 +851,7 @@ int som_update_dense(som_ctx *c, const float *data, int64_t n, const int32_t *bm
   if (!data || !codebook || !bmus) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
-  if (!rc) rc = ensure_rows(c, n, true);
+  if (!rc) rc = ensure_rows(c, n, true, false);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
   return update_dense(c, data, n, bmus, codebook);
@@ -834,9 +875,11 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   if (!data || !codebook || !bmus) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
-  if (!rc) rc = ensure_rows(c, n, true);
+  const bool direct = !rc && direct_search(c, n);
+  if (!rc && direct) rc = ensure_direct(c, n);
+  if (!rc) rc = ensure_rows(c, n, true, !direct);
   bool reg = false;
-  if (!rc && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
+  if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
   rc = bmu_search_dense(c, data, n, codebook, bmus, reg);
@@ -929,9 +972,10 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (!isfinite(radius0) || !isfinite(radiusN)) return fail(c, SOM_ERR_INVALID_ARG, "radius not finite");
   if (scale0 > 1.f || scaleN > 1.f) return fail(c, SOM_ERR_INVALID_ARG, "scale must be in (0, 1]");
   const bool dense = c->data_kind == 1;
-  int rc = ensure_rows(c, c->d_n, dense);
-  if (rc) return rc;
-  rc = registered_norms(c);
+  const bool direct = dense && direct_search(c, c->d_n);
+  int rc = direct ? ensure_direct(c, c->d_n) : SOM_OK;
+  if (!rc) rc = ensure_rows(c, c->d_n, dense, !direct);
+  if (!rc && !direct) rc = registered_norms(c);
   if (!rc && !dense) rc = registered_csr_dense(c);
   if (!rc && !dense && !c->csrd_on) rc = registered_hot(c);
   if (rc) return rc;
@@ -1125,6 +1169,11 @@ int som_debug_xcc_ids(int32_t *out, int n_blocks, void *hip_stream) {
 int som_get_stats(som_ctx *c, int64_t *out) {
   if (!c) return SOM_ERR_INVALID_ARG;
   if (!out) return fail(c, SOM_ERR_INVALID_ARG, "out is NULL");
+  if (c->stats_none) {
+    out[0] = out[1] = out[2] = 0;
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    return e == hipSuccess ? SOM_OK : dev_fail(c, e, "som_get_stats");
+  }
   int32_t h[3] = {0, 0, 0};
   hipError_t e = hipMemcpyAsync(h, c->list_counts, sizeof(h), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

@@ -182,6 +182,9 @@ struct som_ctx {
   int32_t *chunk_node;    // [n/kChunkRows + k]
   float *partial;         // [n/kChunkRows + k][dim]
   int64_t max_chunks;
+  void *direct_rec;       // records of the direct search (bmu_direct.hip), direct_cap bytes
+  size_t direct_cap;
+  int stats_none;         // the most recent search left nothing to the exact stage (direct search)
 
   // hot-column split of the registered sparse training set (csr_hot.hip); built on first use
   int hot_valid;          // 0: not examined yet; 1: examined (hot_on says whether the split is in use)
@@ -246,6 +249,11 @@ hipError_t launch_row_sqnorms(som_ctx *c, const float *A, int64_t nrows, int dim
                               float *out32, double *out64, unsigned *max_bits);
 hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n,
                                   float *out32);
+
+// bmu_direct.hip
+bool direct_search_pays(const som_ctx *c, int64_t n);
+size_t direct_record_bytes(const som_ctx *c, int64_t n);       // scratch it needs in c->direct_rec
+hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const float *W, const float *mask, int32_t *bmus);
 
 // bmu_dense.hip
 int bmu_dense_groups(const som_ctx *c, int64_t n);
