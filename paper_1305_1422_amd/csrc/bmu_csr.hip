@@ -466,8 +466,6 @@ hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_
 // Centred transposed 16-bit code book, node constants (wn32 = c_i), |w_i|^2 (wn64) and the largest |w'_i|^2
 // (wmax_bits), from mu and qstep: one pass over W.
 hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W) {
-  hipError_t e = launch_fill_zero_u32(c->stream, c->wmax_bits, 2);
-  if (e != hipSuccess) return e;
   const int tiles = c->kpad / kCtNodes;                       // kpad is a multiple of 512
   // enough workgroups for twelve per CU: a workgroup walks its slab one tile after the other and waits for
   // every tile's loads, so the memory system is kept busy by their number (two per CU: 2.3 TB/s)

@@ -414,9 +414,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
   }
 }
 
-// Merges the groups' records, a workgroup per instance.  An instance they leave open is decided by the plain
-// distances: of a group's best node alone where only that one is inside the limit, else of all nodes of the group
-// (trained maps hold exact copies of nodes side by side, so this is not rare).
+// Merges the groups' records: kWaves wavefronts per instance (four where there are few instances, else one).  An
+// instance they leave open is decided by the plain distances: of a group's best node alone where only that one is
+// inside the limit, else of all nodes of the group (trained maps hold exact copies of nodes side by side, so this is
+// not rare).
+template <int kWaves>
 __global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
                                                       int groups, int nodes_per_group, const float *__restrict__ X, int64_t n,
                                                       const float *__restrict__ W, int k, int dim,
@@ -424,7 +426,9 @@ __global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restri
   __shared__ double s_d2[4];
   __shared__ int s_id[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j = blockIdx.x;
+  const int part = wave % kWaves;
+  const int64_t j = (int64_t)blockIdx.x * (4 / kWaves) + wave / kWaves;
+  if (j >= n) return;                           // uniform over the workgroup, or (kWaves == 1) without barriers below
   DirectBest r = direct_none();
   for (int v = lane; v < groups; v += kWave) direct_merge(r, rec[(int64_t)v * n + j]);      // every wavefront all of them
   direct_row_merge(r);
@@ -436,8 +440,8 @@ __global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restri
   }
   const double limit = direct_limit(r, xn[j], dim);
   if (direct_decided(r, limit)) {
-    if (threadIdx.x == 0) bmus[j] = r.arg;
-    return;                                     // uniform
+    if (lane == 0 && part == 0) bmus[j] = r.arg;
+    return;                                     // uniform over the instance's wavefronts
   }
   double b = INFINITY;
   int a = 0x7fffffff;
@@ -446,16 +450,16 @@ __global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restri
     if (q.best > limit) continue;               // uniform; a NaN limit keeps every group
     int lo = v * nodes_per_group, hi = min(lo + nodes_per_group, k);
     if (q.second > limit && (unsigned)q.arg < (unsigned)k) { lo = q.arg; hi = lo + 1; }
-    const int quarter = ((hi - lo + 3) / 4 + 3) / 4 * 4;
-    direct_plain(X + j * dim, W, lo + wave * quarter, min(lo + (wave + 1) * quarter, hi), nullptr, dim, lane, b, a);
+    const int share = ((hi - lo + kWaves - 1) / kWaves + 3) / 4 * 4;
+    direct_plain(X + j * dim, W, lo + part * share, min(lo + (part + 1) * share, hi), nullptr, dim, lane, b, a);
   }
-  if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int v = 1; v < 4; ++v)
+  if (kWaves > 1) {
+    if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
+    __syncthreads();
+    for (int v = 0; v < kWaves; ++v)
       if (s_d2[v] < b || (s_d2[v] == b && s_id[v] < a)) { b = s_d2[v]; a = s_id[v]; }
-    bmus[j] = a == 0x7fffffff ? 0 : a;
   }
+  if (lane == 0 && part == 0) bmus[j] = a == 0x7fffffff ? 0 : a;
 }
 
 struct DirectPlan {
@@ -544,9 +548,14 @@ hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const flo
   else { if (p.nt == 4) SOM_DIRECT_HELD(4, 4, 4) else SOM_DIRECT_HELD(4, 4, 1) }
 #undef SOM_DIRECT_HELD
 #undef SOM_DIRECT
-  if (p.groups > 1)
-    hipLaunchKernelGGL(k_direct_merge, dim3((unsigned)n), dim3(256), 0, c->stream, rec, xn, p.groups, p.per_group * 16 * p.nt, X, n,
-                       W, c->k, c->dim, bmus);
+  if (p.groups > 1) {
+    if (n <= 4 * c->n_cu)
+      hipLaunchKernelGGL(k_direct_merge<4>, dim3((unsigned)n), dim3(256), 0, c->stream, rec, xn, p.groups,
+                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
+    else
+      hipLaunchKernelGGL(k_direct_merge<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, c->stream, rec, xn, p.groups,
+                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
+  }
   return hipGetLastError();
 }
 

@@ -264,8 +264,6 @@ hipError_t launch_split_hot_tail(som_ctx *c, const int64_t *indptr, const int32_
 }
 
 hipError_t launch_gather_hot_codebook(som_ctx *c, const float *W) {
-  hipError_t e = launch_fill_zero_u32(c->stream, c->hot_wmax_bits, 1);
-  if (e != hipSuccess) return e;
   const int blocks = c->k < c->n_cu * 4 ? c->k : c->n_cu * 4;
   hipLaunchKernelGGL(k_gather_hot_codebook, dim3(blocks), dim3(256), 0, c->stream, W, c->mu, c->hot_cols, c->k,
                      c->dim, c->hot_Wc, c->hot_wmax_bits);

@@ -295,8 +295,6 @@ hipError_t launch_sample_col_means(som_ctx *c, const float *A, int64_t nrows, in
 // Means of ALL rows of the code book (at most kMeanSlabs * kMeanRowsPerSlab of them) plus the
 // quantisation steps of its centred columns: c->mu, c->qstep, c->qstep_max_bits.
 hipError_t launch_codebook_means_and_steps(som_ctx *c, const float *W) {
-  hipError_t e = launch_fill_zero_u32(c->stream, c->qstep_max_bits, 1);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sample_col_sums, dim3((c->dim + kColBlock - 1) / kColBlock, kMeanSlabs), dim3(kColBlock), 0, c->stream, W,
                      (int64_t)c->k, (int64_t)1, c->dim, c->mu_partial, c->col_range);
   hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(64), 0, c->stream, c->mu_partial,
@@ -310,8 +308,6 @@ hipError_t launch_vec_sqnorm(som_ctx *c, const float *v, int dim, float *out) {
 }
 
 hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centered, bool want_wn64, bool x_centered) {
-  hipError_t e = launch_fill_zero_u32(c->stream, c->wmax_bits, 2);     // wmax_bits and wabs_bits are neighbours
-  if (e != hipSuccess) return e;
   float *wc = store_centered ? c->Wc : nullptr;
   unsigned *wabs = store_centered ? c->wmax_bits + 1 : nullptr;
   double *wn64 = want_wn64 ? c->wn64 : nullptr;

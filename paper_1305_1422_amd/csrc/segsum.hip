@@ -3,9 +3,10 @@
 //
 // The neighbourhood weight of an instance depends on it only through its BMU, so the update
 // needs S_b = sum of the instances whose BMU is b and C_b = their number.  Dense data:
-//   1. stable LSD radix sort of the instance ids by BMU (8-bit digits, ballot-based ranking),
-//      so every segment lists its instances in ascending order;
-//   2. segment offsets by binary search in the sorted keys, C_b = their differences;
+//   1. stable counting sort of the instance ids by BMU (counters of all nodes in LDS, ballot-based ranking),
+//      so every segment lists its instances in ascending order; C_b and the segment offsets fall out of it
+//      (maps whose counters do not fit LDS: LSD radix sort, offsets by binary search in the sorted keys);
+//   2. small sets skip the sort: a workgroup per node picks its instances out of the list of BMUs;
 //   3. every segment is cut into chunks of kChunkRows instances; one workgroup sums one chunk
 //      (fp64 registers, instances read as whole rows through the permutation);
 //   4. chunks of a node are added in order.
@@ -161,6 +162,365 @@ __global__ __launch_bounds__(64) void k_radix_scatter(const int32_t *__restrict_
       vals_out[before + rank] = val;
     }
   }
+}
+
+// ---------------------------------------------------------------- counting sort by node
+// The radix sort above needs three launches per digit and four more for the segments and chunks; with one counter
+// per node in LDS a single digit does.  A wavefront ranks its own consecutive keys, 64 at a time, in order, with
+// counters of its own (16 bits, so that several wavefronts' sets fit); the sets are then turned into exclusive
+// prefixes over the wavefronts.  Up to 2,048 keys per wavefront of one workgroup the rest is done there too
+// (k_group_one); beyond, a workgroup counts one tile of the keys (k_group_tiles), the tables are
+// summed over the tiles and scanned within blocks of 64 nodes (k_group_prefix), and k_group_place puts the ids in place.  Measured, everything up to the chunk table (us):
+// 20,011 keys, 2,700 nodes 37 -> 20; 100,000 keys, 2,500 nodes 71 -> 24; 1,000,000 keys, 10,000 nodes 144 -> 71.
+constexpr size_t kGroupLds = 160 * 1024 - 1024;      // the rest is for the scan's own words
+constexpr int kGroupKeysMax = 2048;                  // keys per wavefront, at most
+constexpr int kGroupOneKeys = 16384;                 // keys that one workgroup sorts faster than three launches do
+
+// Lanes whose key equals this lane's, among the valid ones: the ballots of all key bits are independent of each
+// other, and a lane collects the lanes that differ from it in any of them.
+__device__ __forceinline__ unsigned long long same_key_lanes(int key, bool valid, int bits) {
+  unsigned long long differ = 0;
+#pragma unroll
+  for (int b0 = 0; b0 < 20; b0 += 4) {
+    if (b0 >= bits) break;                            // uniform; the bits past the key's are equal everywhere
+#pragma unroll
+    for (int b = b0; b < b0 + 4; ++b) {
+      const unsigned bit = ((unsigned)key >> b) & 1u;
+      const unsigned long long bal = __ballot(bit);
+      const unsigned long long mine = 0ull - (unsigned long long)bit;
+      differ |= bal ^ mine;
+    }
+  }
+  return ~differ & __ballot(valid);
+}
+
+// Ranks the keys lo .. hi - 1 of this wavefront against its own counters; rank_out[j] = number of earlier keys of the
+// wavefront with the same value.
+__device__ __forceinline__ void group_rank_wave(const int32_t *__restrict__ keys, int64_t lo, int64_t hi, int k, int bits,
+                                                volatile uint16_t *cnt, int32_t *__restrict__ rank_out, int lane) {
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int next = lo + lane < hi ? keys[lo + lane] : 0;
+  for (int64_t j0 = lo; j0 < hi; j0 += 64) {
+    const bool valid = j0 + lane < hi;
+    const int key = valid ? clamp_node(next, k) : 0;
+    if (j0 + 64 + lane < hi) next = keys[j0 + 64 + lane];
+    const unsigned long long same = same_key_lanes(key, valid, bits);
+    const int rank = __popcll(same & below);
+    const int before = valid ? cnt[key] : 0;
+    if (valid && rank == 0) cnt[key] = (uint16_t)(before + __popcll(same));
+    if (valid) rank_out[j0 + lane] = before + rank;
+  }
+}
+
+// Exclusive scans over the nodes of their counts and of their chunk counts by a workgroup of kThreads, into LDS (seg,
+// chk: k + 1 entries each).  count(b) must be readable by every thread.
+template <int kThreads, typename Count>
+__device__ __forceinline__ void group_scan(Count count, int k, int chunk_rows, int *seg, int *chk, int (*s_wave)[2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (k + kThreads - 1) / kThreads;
+  const int b0 = min(tid * per, k), b1 = min(b0 + per, k);
+  int sum = 0, chunks = 0;
+  for (int b = b0; b < b1; ++b) {
+    const int v = count(b);
+    sum += v;
+    chunks += (v + chunk_rows - 1) / chunk_rows;
+  }
+  int inc = sum, cinc = chunks;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, 64), u = __shfl_up(cinc, o, 64);
+    if (lane >= o) { inc += t; cinc += u; }
+  }
+  if (lane == 63) { s_wave[wave][0] = inc; s_wave[wave][1] = cinc; }
+  __syncthreads();
+  int run = inc - sum, crun = cinc - chunks;
+  for (int w = 0; w < wave; ++w) { run += s_wave[w][0]; crun += s_wave[w][1]; }
+  for (int b = b0; b < b1; ++b) {
+    const int v = count(b);
+    seg[b] = run;
+    chk[b] = crun;
+    run += v;
+    crun += (v + chunk_rows - 1) / chunk_rows;
+  }
+  if (tid == kThreads - 1) { seg[k] = run; chk[k] = crun; }
+  __syncthreads();
+}
+
+// Writes the node of every chunk of 64 nodes b0 .. b0 + 63, a lane per node: the first chunks of a node by its lane,
+// the rest of a node with many by the whole wavefront.
+__device__ __forceinline__ void fill_chunk_nodes(int b, int first, int chunks, int32_t *__restrict__ chunk_node, int lane) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (u < chunks) chunk_node[first + u] = b;
+  unsigned long long more = __ballot(chunks > 4);
+  for (; more; more &= more - 1) {
+    const int q = __ffsll((long long)more) - 1;
+    const int f = __shfl(first, q, 64), n = __shfl(chunks, q, 64), bq = __shfl(b, q, 64);
+    for (int t = 4 + lane; t < n; t += 64) chunk_node[f + t] = bq;
+  }
+}
+
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void k_group_one(const int32_t *__restrict__ keys, int n, int k, int bits,
+                                                           int chunk_rows, int32_t *__restrict__ perm,
+                                                           int32_t *__restrict__ rank, int32_t *__restrict__ counts,
+                                                           int32_t *__restrict__ seg_off, int32_t *__restrict__ chunk_off,
+                                                           int32_t *__restrict__ chunk_node) {
+  extern __shared__ int s_dyn[];                      // seg [k + 1], chk [k + 1], counters [kWaves][k2]
+  __shared__ int s_wave[kWaves][2];
+  const int k2 = (k + 1) & ~1;
+  int *seg = s_dyn, *chk = seg + k + 1;
+  uint16_t *cnt = reinterpret_cast<uint16_t *>(chk + k + 1);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kThreads = 64 * kWaves;
+  for (int i = tid; i < kWaves * k2 / 2; i += kThreads) reinterpret_cast<uint32_t *>(cnt)[i] = 0u;
+  __syncthreads();
+  const int per = ((n + kWaves - 1) / kWaves + 63) / 64 * 64;
+  const int lo = min(wave * per, n), hi = min(lo + per, n);
+  group_rank_wave(keys, lo, hi, k, bits, cnt + wave * k2, rank, lane);
+  __syncthreads();
+  for (int b = tid; b < k; b += kThreads) {
+    int run = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int t = cnt[w * k2 + b];
+      cnt[w * k2 + b] = (uint16_t)run;
+      run += t;
+    }
+    counts[b] = run;
+  }
+  __syncthreads();                                    // (also makes counts visible to the workgroup)
+  group_scan<kThreads>([&](int b) { return counts[b]; }, k, chunk_rows, seg, chk, s_wave);
+  for (int b = tid; b <= k; b += kThreads) { seg_off[b] = seg[b]; chunk_off[b] = chk[b]; }
+  for (int b0 = 64 * wave; b0 < k; b0 += kThreads) {
+    const int b = b0 + lane;
+    fill_chunk_nodes(b, b < k ? chk[b] : 0, b < k ? chk[b + 1] - chk[b] : 0, chunk_node, lane);
+  }
+  for (int j = lo + lane; j < hi; j += 64) {
+    const int key = clamp_node(keys[j], k);
+    perm[seg[key] + cnt[wave * k2 + key] + rank[j]] = j;
+  }
+}
+
+// table[tile][node] = keys of the tile, rank[j] = position of key j among the equal ones of its tile.  kWaves of the
+// wavefronts rank; all of them clear and sum the counters.
+constexpr int kTileThreads = 1024;
+
+template <int kWaves>
+__global__ __launch_bounds__(kTileThreads) void k_group_tiles(const int32_t *__restrict__ keys, int64_t n, int k, int bits,
+                                                              int keys_per_wave, int32_t *__restrict__ table,
+                                                              int32_t *__restrict__ rank) {
+  extern __shared__ int s_dyn[];                      // counters [kWaves][k2]
+  const int k2 = (k + 1) & ~1;
+  uint16_t *cnt = reinterpret_cast<uint16_t *>(s_dyn);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int i = tid; i < kWaves * k2 / 2; i += kTileThreads) reinterpret_cast<uint32_t *>(cnt)[i] = 0u;
+  __syncthreads();
+  const int64_t tile0 = (int64_t)blockIdx.x * kWaves * keys_per_wave;
+  const int64_t tile1 = tile0 + kWaves * keys_per_wave < n ? tile0 + kWaves * keys_per_wave : n;
+  if (wave < kWaves) {
+    const int64_t lo = tile0 + wave * keys_per_wave;
+    if (lo < n) group_rank_wave(keys, lo, lo + keys_per_wave < n ? lo + keys_per_wave : n, k, bits, cnt + wave * k2, rank, lane);
+  }
+  __syncthreads();
+  for (int b = tid; b < k; b += kTileThreads) {
+    int run = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int t = cnt[w * k2 + b];
+      cnt[w * k2 + b] = (uint16_t)run;
+      run += t;
+    }
+    table[(int64_t)blockIdx.x * k + b] = run;
+  }
+  if (kWaves == 1) return;
+  __syncthreads();
+  for (int64_t j = tile0 + tid; j < tile1; j += kTileThreads)
+    rank[j] += cnt[(int)(j - tile0) / keys_per_wave * k2 + clamp_node(keys[j], k)];
+}
+
+// Exclusive prefixes of the table over the tiles, in place, and the totals; besides, the exclusive scans of the totals
+// and of the chunk counts within the workgroup's 64 nodes (local [2][k]) and their sums (sums [2][blocks]).  The four
+// wavefronts of a workgroup share the tiles.
+__global__ __launch_bounds__(256) void k_group_prefix(int32_t *__restrict__ table, int tiles, int k, int chunk_rows,
+                                                      int32_t *__restrict__ counts, int32_t *__restrict__ local,
+                                                      int32_t *__restrict__ sums) {
+  __shared__ int s_sum[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = blockIdx.x * 64 + lane;
+  const bool live = b < k;
+  const int per = (tiles + 3) / 4;
+  const int t0 = min(wave * per, tiles), t1 = min(t0 + per, tiles);
+  int32_t *col = table + (live ? b : 0);
+  int sum = 0;
+#pragma unroll 8
+  for (int t = t0; t < t1; ++t) sum += col[(int64_t)t * k];
+  s_sum[wave][lane] = sum;
+  __syncthreads();
+  int run = 0;
+  for (int w = 0; w < wave; ++w) run += s_sum[w][lane];
+  if (wave == 3) {
+    const int total = live ? run + sum : 0, chunks = (total + chunk_rows - 1) / chunk_rows;
+    int inc = total, cinc = chunks;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(inc, o, 64), u = __shfl_up(cinc, o, 64);
+      if (lane >= o) { inc += t; cinc += u; }
+    }
+    if (live) {
+      counts[b] = total;
+      local[b] = inc - total;
+      local[k + b] = cinc - chunks;
+    }
+    if (lane == 63) { sums[blockIdx.x] = inc; sums[gridDim.x + blockIdx.x] = cinc; }
+  }
+#pragma unroll 8
+  for (int t = t0; t < t1; ++t) {
+    const int v = col[(int64_t)t * k];
+    if (live) col[(int64_t)t * k] = run;
+    run += v;
+  }
+}
+
+// Every workgroup scans the sums of the 64-node blocks (at most kGroupMaxBlocks of them) for itself.
+constexpr int kGroupMaxBlocks = 1280;
+
+__global__ __launch_bounds__(1024) void k_group_place(const int32_t *__restrict__ keys, int64_t n, int k, int tile,
+                                                      int chunk_rows, const int32_t *__restrict__ table,
+                                                      const int32_t *__restrict__ rank, const int32_t *__restrict__ counts,
+                                                      const int32_t *__restrict__ local, const int32_t *__restrict__ sums,
+                                                      int32_t *__restrict__ perm, int32_t *__restrict__ seg_off,
+                                                      int32_t *__restrict__ chunk_off, int32_t *__restrict__ chunk_node) {
+  __shared__ int s_wave[16][2];
+  __shared__ int s_seg[kGroupMaxBlocks + 1], s_chk[kGroupMaxBlocks + 1];
+  const int blocks = (k + 63) / 64;
+  group_scan<1024>([&](int b) { return sums[b]; }, blocks, 1, s_seg, s_chk, s_wave);
+  __syncthreads();
+  group_scan<1024>([&](int b) { return sums[blocks + b]; }, blocks, 1, s_chk, s_chk, s_wave);
+  const int64_t at = (int64_t)blockIdx.x * 1024 + threadIdx.x, stride = (int64_t)gridDim.x * 1024;
+  const int lane = threadIdx.x & 63;
+  for (int64_t b0 = at - lane; b0 < k; b0 += stride) {
+    const int b = (int)b0 + lane;
+    int first = 0, chunks = 0;
+    if (b < k) {
+      first = local[k + b] + s_chk[b >> 6];
+      chunks = (counts[b] + chunk_rows - 1) / chunk_rows;
+      seg_off[b] = local[b] + s_seg[b >> 6];
+      chunk_off[b] = first;
+    }
+    fill_chunk_nodes(b, first, chunks, chunk_node, lane);
+  }
+  if (at == 0) { seg_off[k] = s_seg[blocks]; chunk_off[k] = s_chk[blocks]; }
+  for (int64_t j = at; j < n; j += stride) {
+    const int key = clamp_node(keys[j], k);
+    perm[local[key] + s_seg[key >> 6] + table[j / tile * k + key] + rank[j]] = (int32_t)j;
+  }
+}
+
+// Wavefronts whose counters fit LDS beside `extra` bytes per node; 0: not even one's.
+static int group_waves(int k, int extra) {
+  for (int w = 16; w >= 1; w /= 2)
+    if ((size_t)w * (size_t)((k + 1) & ~1) * 2 + (size_t)extra * ((size_t)k + 1) <= kGroupLds) return w;
+  return 0;
+}
+
+// Keys per wavefront of the tiled form: workgroups enough to spread over the chip, as long as the table stays at some
+// hundred thousand entries per pass.
+static int group_keys_per_wave(int k, int64_t n, int waves) {
+  int per = 256;
+  while (per < kGroupKeysMax && (n + (int64_t)per * waves - 1) / ((int64_t)per * waves) * k > 500000) per *= 2;
+  return per;
+}
+
+int64_t group_table_entries(int k, int64_t n) {
+  const int waves = group_waves(k, 0);
+  if (!waves || k > 64 * kGroupMaxBlocks) return 1;
+  // (a shorter list may be cut finer, but then its table has at most 500,000 entries and one more tile's)
+  const int64_t tile = (int64_t)waves * group_keys_per_wave(k, n, waves);
+  const int64_t most = (n + tile - 1) / tile * k;
+  return most > 500000 + k ? most : 500000 + k;
+}
+
+// ---------------------------------------------------------------- small sets: a workgroup per node
+// With few instances on few nodes the sort costs more than every node's looking through all BMUs: workgroup b
+// compacts the ids of its instances, in ascending order, and adds them up: kRowLanes rows at a time over the
+// columns of its column block, the row lanes' sums combined in order.  Bound by latency: 1,000 x 10 on 400 nodes
+// 5 us instead of 45 for sort, chunks and sums.
+constexpr int kGatherThreads = 512;
+constexpr int kGatherMax = 8192;          // instances (their ids fit 16 bits of LDS each; 16 per thread)
+
+__global__ __launch_bounds__(kGatherThreads) void k_gather_sums(const float *__restrict__ X, const int32_t *__restrict__ bmus,
+                                                                int n, int k, int dim, int col_lanes,
+                                                                int32_t *__restrict__ counts, float *__restrict__ S) {
+  constexpr int kWaves = kGatherThreads / 64, kPer = kGatherMax / kGatherThreads;
+  __shared__ uint16_t s_list[kGatherMax];
+  __shared__ int s_cnt[kWaves];
+  __shared__ double s_part[kGatherThreads];
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // wavefront w looks through the w-th stretch of the list, 64 instances at a time; all its loads are in flight at once
+  const int steps = (n + kGatherThreads - 1) / kGatherThreads;
+  const int lo = wave * steps * 64;
+  int key[kPer];
+#pragma unroll
+  for (int s = 0; s < kPer; ++s)
+    if (s < steps) {                          // uniform
+      const int j = lo + 64 * s + lane;
+      key[s] = j < n ? clamp_node(bmus[j], k) : -1;
+    }
+  unsigned mine = 0;                          // bit s: this lane's instance of step s belongs to the node
+  int found = 0;
+#pragma unroll
+  for (int s = 0; s < kPer; ++s)
+    if (s < steps) {
+      if (key[s] == b) mine |= 1u << s;
+      found += __popcll(__ballot(key[s] == b));
+    }
+  if (lane == 0) s_cnt[wave] = found;
+  __syncthreads();
+  int at = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const int t = s_cnt[w];
+    if (w < wave) at += t;
+    total += t;
+  }
+  if (found)
+    for (int s = 0; s < steps; ++s) {
+      const unsigned long long bal = __ballot((mine >> s) & 1u);
+      if ((mine >> s) & 1u) s_list[at + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(lo + 64 * s + lane);
+      at += __popcll(bal);
+    }
+  __syncthreads();
+  const int row_lanes = kGatherThreads / col_lanes;
+  const int cl = tid % col_lanes, rl = tid / col_lanes;
+  const int c = blockIdx.y * col_lanes + cl;
+  const bool live = c < dim;
+  const float *col = X + (live ? c : 0);
+  double sum = 0.0;
+  for (int r = rl; r < total; r += 8 * row_lanes) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = col[(int64_t)s_list[min(r + u * row_lanes, total - 1)] * dim];      // (no branch: all in flight)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += r + u * row_lanes < total ? (double)v[u] : 0.0;
+  }
+  s_part[tid] = sum;
+  __syncthreads();
+  if (rl == 0) {
+    double s = s_part[cl];
+    for (int r = 1; r < row_lanes; ++r) s += s_part[r * col_lanes + cl];
+    if (live) S[(int64_t)b * dim + c] = (float)s;
+  }
+  if (tid == 0 && blockIdx.y == 0) counts[b] = total;
+}
+
+// The nodes' looking through the list (8e6 comparisons take about as long as a launch) and the worst case, all rows
+// on one node (2^18 values: 20 us), draw the line.
+static bool gather_pays(const som_ctx *c, int64_t n) {
+  return n <= kGatherMax && n * (int64_t)c->k * ((c->dim + 255) / 256) <= 8000000 && n * (int64_t)c->dim <= 262144;
 }
 
 // ---------------------------------------------------------------- chunks
@@ -440,13 +800,63 @@ hipError_t launch_sort_keys(som_ctx *c, const int32_t *bmus, int64_t n, int key_
   return hipGetLastError();
 }
 
-// Stable permutation of instance ids by BMU, segment offsets and counts.
-// On return c->sort_val[0] holds the permutation (c->sort_key[0] the sorted BMUs).
-hipError_t launch_sort_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n) {
+template <int kWaves>
+static void launch_group_one(som_ctx *c, const int32_t *bmus, int64_t n, int bits, int chunk_rows) {
+  const size_t lds = (size_t)kWaves * ((c->k + 1) & ~1) * 2 + 8 * ((size_t)c->k + 1);
+  hipLaunchKernelGGL(k_group_one<kWaves>, dim3(1), dim3(64 * kWaves), lds, c->stream, bmus, (int)n, c->k, bits, chunk_rows,
+                     c->sort_val[0], c->sort_key[1], c->counts, c->seg_off, c->chunk_off, c->chunk_node);
+}
+
+template <int kWaves>
+static void launch_group_tiles(som_ctx *c, const int32_t *bmus, int64_t n, int bits, int per, unsigned tiles) {
+  hipLaunchKernelGGL(k_group_tiles<kWaves>, dim3(tiles), dim3(kTileThreads), (size_t)kWaves * ((c->k + 1) & ~1) * 2, c->stream,
+                     bmus, n, c->k, bits, per, c->group_table, c->sort_key[1]);
+}
+
+// Stable permutation of the instance ids by BMU (c->sort_val[0]), counts, segment offsets, chunk offsets and the
+// node of every chunk, for chunks of chunk_rows instances.
+static hipError_t launch_group_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n, int chunk_rows) {
+  int bits = 1;
+  while ((1ll << bits) < (long long)c->k) ++bits;
+  const int one = group_waves(c->k, 8), many = group_waves(c->k, 0);
+  if (one && n <= kGroupOneKeys && n <= (int64_t)one * kGroupKeysMax) {
+    switch (one) {
+      case 16: launch_group_one<16>(c, bmus, n, bits, chunk_rows); break;
+      case 8: launch_group_one<8>(c, bmus, n, bits, chunk_rows); break;
+      case 4: launch_group_one<4>(c, bmus, n, bits, chunk_rows); break;
+      case 2: launch_group_one<2>(c, bmus, n, bits, chunk_rows); break;
+      default: launch_group_one<1>(c, bmus, n, bits, chunk_rows);
+    }
+    return hipGetLastError();
+  }
+  if (many && c->k <= 64 * kGroupMaxBlocks) {
+    const int per = group_keys_per_wave(c->k, n, many);
+    const int tile = many * per;
+    const unsigned tiles = (unsigned)((n + tile - 1) / tile);
+    switch (many) {
+      case 16: launch_group_tiles<16>(c, bmus, n, bits, per, tiles); break;
+      case 8: launch_group_tiles<8>(c, bmus, n, bits, per, tiles); break;
+      case 4: launch_group_tiles<4>(c, bmus, n, bits, per, tiles); break;
+      case 2: launch_group_tiles<2>(c, bmus, n, bits, per, tiles); break;
+      default: launch_group_tiles<1>(c, bmus, n, bits, per, tiles);
+    }
+    const int nodeblocks = (c->k + 63) / 64;
+    int32_t *local = c->group_local, *sums = c->group_local + 2 * (size_t)c->k;
+    hipLaunchKernelGGL(k_group_prefix, dim3(nodeblocks), dim3(256), 0, c->stream, c->group_table, (int)tiles, c->k, chunk_rows,
+                       c->counts, local, sums);
+    int64_t blocks = ((n > c->k ? n : c->k) + 1023) / 1024;
+    if (blocks > 2 * (int64_t)c->n_cu) blocks = 2 * (int64_t)c->n_cu;
+    hipLaunchKernelGGL(k_group_place, dim3((unsigned)blocks), dim3(1024), 0, c->stream, bmus, n, c->k, tile, chunk_rows,
+                       c->group_table, c->sort_key[1], c->counts, local, sums, c->sort_val[0], c->seg_off, c->chunk_off,
+                       c->chunk_node);
+    return hipGetLastError();
+  }
   hipError_t e = launch_sort_keys(c, bmus, n, c->k);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_segment_bounds, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->sort_key[0], n, c->k,
                      c->seg_off, c->counts);
+  hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, c->counts, c->chunk_off, c->k, chunk_rows);
+  hipLaunchKernelGGL(k_fill_chunk_nodes, dim3(c->n_cu * 2), dim3(256), 0, c->stream, c->chunk_off, c->k, c->chunk_node);
   return hipGetLastError();
 }
 
@@ -455,11 +865,16 @@ hipError_t launch_scan_exclusive_i32(som_ctx *c, const int32_t *in, int32_t *out
   return hipGetLastError();
 }
 
-hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n) {
-  hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, c->counts, c->chunk_off, c->k,
-                     kChunkRows);
-  hipLaunchKernelGGL(k_fill_chunk_nodes, dim3(c->n_cu * 2), dim3(256), 0, c->stream, c->chunk_off, c->k,
-                     c->chunk_node);
+hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus) {
+  if (gather_pays(c, n)) {
+    int col_lanes = 16;
+    while (col_lanes < c->dim && col_lanes < 256) col_lanes *= 2;
+    hipLaunchKernelGGL(k_gather_sums, dim3(c->k, (c->dim + col_lanes - 1) / col_lanes), dim3(kGatherThreads), 0, c->stream, X,
+                       bmus, (int)n, c->k, c->dim, col_lanes, c->counts, c->S);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_group_by_bmu(c, bmus, n, kChunkRows);
+  if (e != hipSuccess) return e;
   int64_t max_chunks = n / kChunkRows + (n < c->k ? n : c->k);
   if (max_chunks < 1) max_chunks = 1;
   const bool vec4 = (c->dim % 4 == 0) && ((uintptr_t)X % 16 == 0);
@@ -489,12 +904,8 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
   int ysplit = (c->dim + 4095) / 4096;
   if (ysplit > 64) ysplit = 64;
   if (c->dim <= kCsrTile) {
-    hipError_t e = launch_sort_by_bmu(c, bmus, n);
+    hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, c->counts, c->chunk_off, c->k,
-                       kCsrChunkRows);
-    hipLaunchKernelGGL(k_fill_chunk_nodes, dim3(c->n_cu * 2), dim3(256), 0, c->stream, c->chunk_off, c->k,
-                       c->chunk_node);
     if (c->GxT) {          // matrix smoothing only reads the rows of chosen nodes
       hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, kCsrChunkRows, c->dim,
                          c->S);
@@ -512,12 +923,8 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
   // (worth the sort only with several instances per node: with 12,347 instances on 68,880 nodes it cost 0.09 ms
   // more than the plain scatter, with 100,000 on 2,500 it saves 0.14)
   if (c->hot_valid && c->hot_on && n >= 8 * (int64_t)c->k) {
-    hipError_t e = launch_sort_by_bmu(c, bmus, n);
+    hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, c->counts, c->chunk_off, c->k,
-                       kCsrChunkRows);
-    hipLaunchKernelGGL(k_fill_chunk_nodes, dim3(c->n_cu * 2), dim3(256), 0, c->stream, c->chunk_off, c->k,
-                       c->chunk_node);
     if (c->GxT) {
       hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, 0, c->dim, c->S);
     } else {

@@ -33,22 +33,6 @@ __device__ __forceinline__ double cooled(double v0, double vN, int n_epochs, int
   return kind == SOM_COOL_EXPONENTIAL ? v0 * pow(vN / v0, t) : v0 + (vN - v0) * t;
 }
 
-__global__ __launch_bounds__(256) void k_epoch_params(EpochParams *__restrict__ params, float *__restrict__ gx,
-                                                      float *__restrict__ gy, int rows, int cols, int hex,
-                                                      int epoch, int n_epochs, double r0, double rN, double s0,
-                                                      double sN, int cooling, int scale_cooling) {
-  const double radius = cooled(r0, rN, n_epochs, epoch, cooling);
-  const double inv = 1.0 / (8.0 * radius * radius);
-  if (threadIdx.x == 0) {
-    params->radius = radius;
-    params->scale = cooled(s0, sN, n_epochs, epoch, scale_cooling);
-    params->inv8r2 = inv;
-  }
-  for (int m = threadIdx.x; m <= 2 * cols; m += blockDim.x) gx[m] = (float)exp(-(double)m * (double)m * inv);
-  const double ya = hex ? 3.0 : 4.0;
-  for (int a = threadIdx.x; a < rows; a += blockDim.x) gy[a] = (float)exp(-ya * (double)a * (double)a * inv);
-}
-
 __global__ __launch_bounds__(256) void k_cool_schedule(int n_epochs, double r0, double rN, double s0, double sN,
                                                        int cooling, int scale_cooling,
                                                        double *__restrict__ radius_out,
@@ -72,6 +56,90 @@ __device__ __forceinline__ int row_offset(int yi, int yb, int toroid, int rows) 
   int a = yi > yb ? yi - yb : yb - yi;
   if (toroid && rows - a < a) a = rows - a;
   return a;
+}
+
+// ---------------------------------------------------------------- everything an epoch prepares from its radius alone
+// One launch at the head of an epoch: the cooled radius, the two Gaussian factor tables, the coefficient matrices of
+// the smoothing passes (or the weight table of a neighbourhood with compact support; see below for their layouts), and
+// the counters that the search of this epoch starts from.  (It was four launches of 2 to 5 us with next to no work.)
+struct EpochTables {
+  EpochParams *params;
+  float *gx, *gy;             // [2 cols + 1], [rows]
+  float *GxT, *GyT;           // or null
+  int xi_pad, e_pad;
+  float *H2;                  // or null
+  int rows, cols, hex, toroid, function, compact;
+  unsigned *zero;             // words to clear, or null
+  int zero_words;
+};
+
+constexpr int kSmoothTile = 16;
+
+__device__ __forceinline__ int direct_table_width(int cols, int toroid) {
+  return (toroid ? cols : 2 * cols - 1) + kSmoothTile;
+}
+
+__global__ __launch_bounds__(256) void k_epoch_tables(EpochTables t, int epoch, int n_epochs, double r0, double rN, double s0,
+                                                      double sN, int cooling, int scale_cooling) {
+  const double radius = cooled(r0, rN, n_epochs, epoch, cooling);
+  const double inv = 1.0 / (8.0 * radius * radius);
+  const double ya = t.hex ? 3.0 : 4.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    t.params->radius = radius;
+    t.params->scale = cooled(s0, sN, n_epochs, epoch, scale_cooling);
+    t.params->inv8r2 = inv;
+  }
+  auto gx = [&](int m) { return (float)exp(-(double)m * (double)m * inv); };
+  auto gy = [&](int a) { return (float)exp(-ya * (double)a * (double)a * inv); };
+  const int rows = t.rows, cols = t.cols, par = t.hex ? 2 : 1;
+  const int64_t n_gx = 2 * (int64_t)cols + 1, n_f = n_gx + rows;
+  const int64_t n_GxT = t.GxT ? (int64_t)par * par * cols * t.xi_pad : 0, n_GyT = t.GyT ? (int64_t)par * rows * t.e_pad : 0;
+  const int width = direct_table_width(cols, t.toroid);
+  const int64_t n_H2 = t.H2 ? (int64_t)(t.hex ? 3 : 1) * rows * width : 0;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t o = at; o < t.zero_words; o += stride) t.zero[o] = 0u;
+  for (int64_t o = at; o < n_f; o += stride) {
+    if (o < n_gx) t.gx[o] = gx((int)o);
+    else t.gy[o - n_gx] = gy((int)(o - n_gx));
+  }
+  for (int64_t o = at; o < n_GxT + n_GyT; o += stride) {
+    if (o < n_GxT) {
+      const int xi = (int)(o % t.xi_pad);
+      const int xb = (int)((o / t.xi_pad) % cols);
+      const int ps = (int)((o / ((int64_t)t.xi_pad * cols)) % par);
+      const int img = (int)(o / ((int64_t)t.xi_pad * cols * par));
+      t.GxT[o] = xi < cols ? gx(col_offset2(xi, xb, img, ps, t.hex, t.toroid, cols)) : 0.f;
+    } else {
+      const int64_t q = o - n_GxT;
+      const int e = (int)(q % t.e_pad);
+      const int yb = (int)((q / t.e_pad) % rows);
+      const int cls = (int)(q / ((int64_t)t.e_pad * rows));
+      const int yi = par * e + cls;
+      t.GyT[q] = yi < rows ? gy(row_offset(yi, yb, t.toroid, rows)) : 0.f;
+    }
+  }
+  const double reach = 4.0 * radius * radius;     // q = 4 d^2 <= 4 r^2: inside the radius
+  for (int64_t o = at; o < n_H2; o += stride) {
+    const int c = (int)(o % width);
+    const int a_raw = (int)((o / width) % rows);
+    const int cls = (int)(o / ((int64_t)width * rows));
+    const int dpar = t.hex ? cls - 1 : 0;
+    const int dx = t.toroid ? c % cols : c - (cols - 1);
+    long long m = 2ll * dx + dpar;
+    m = m < 0 ? -m : m;
+    long long a = a_raw;
+    if (t.toroid) {
+      if (2ll * cols - m < m) m = 2ll * cols - m;
+      if (rows - a < a) a = rows - a;
+    }
+    const double q = (double)(m * m + (t.hex ? 3 : 4) * a * a);
+    const bool inside = q <= reach;
+    float h;
+    if (t.function == SOM_NEIGHBORHOOD_BUBBLE) h = inside ? 1.f : 0.f;
+    else h = (t.compact && !inside) ? 0.f : (float)exp(-q * inv);
+    t.H2[o] = h;
+  }
 }
 
 // ---------------------------------------------------------------- count channel (fp64)
@@ -190,11 +258,34 @@ __global__ __launch_bounds__(256) void k_smooth_y_divide(const float *__restrict
 // The learning rate follows its own cooling kind if one was set (som_set_scale_cooling), else the radius' kind.
 static int scale_cooling_of(const som_ctx *c, int cooling) { return c->scale_cooling >= 0 ? c->scale_cooling : cooling; }
 
+static bool direct_neighbourhood(const som_ctx *c) { return c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact; }
+static bool small_smoothing(const som_ctx *c);
+
+// `search`: a BMU search follows; its counters are cleared on the way.
 hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0, double sN,
-                               int cooling) {
-  hipLaunchKernelGGL(k_epoch_params, dim3(1), dim3(256), 0, c->stream, c->params, c->gx, c->gy, c->rows, c->cols,
-                     c->grid_type == SOM_GRID_HEXAGONAL, epoch, n_epochs, r0, rN, s0, sN, cooling,
-                     scale_cooling_of(c, cooling));
+                               int cooling, bool search) {
+  EpochTables t;
+  t.params = c->params; t.gx = c->gx; t.gy = c->gy;
+  const bool direct = direct_neighbourhood(c), matrices = !direct && !small_smoothing(c);
+  t.GxT = matrices ? c->GxT : nullptr;
+  t.GyT = matrices ? c->GyT : nullptr;
+  t.xi_pad = c->xi_pad; t.e_pad = c->e_pad;
+  t.H2 = direct ? c->H2 : nullptr;
+  t.rows = c->rows; t.cols = c->cols;
+  t.hex = c->grid_type == SOM_GRID_HEXAGONAL; t.toroid = c->map_type == SOM_MAP_TOROID;
+  t.function = c->nb_function; t.compact = c->nb_compact;
+  t.zero = search ? reinterpret_cast<unsigned *>(c->list_counts) : nullptr;
+  t.zero_words = search ? kListWords : 0;
+  if (search) c->search_zeroed = 1;
+  const int64_t par = t.hex ? 2 : 1;
+  int64_t work = 2 * (int64_t)c->cols + 1 + c->rows;
+  if (t.GxT) work += par * par * c->cols * c->xi_pad + par * c->rows * c->e_pad;
+  if (t.H2) work += (int64_t)(t.hex ? 3 : 1) * c->rows * ((t.toroid ? c->cols : 2 * c->cols - 1) + kSmoothTile);
+  if (t.zero_words > work) work = t.zero_words;
+  int64_t blocks = (work + 255) / 256;
+  if (blocks > (int64_t)c->n_cu * 8) blocks = (int64_t)c->n_cu * 8;
+  hipLaunchKernelGGL(k_epoch_tables, dim3((unsigned)blocks), dim3(256), 0, c->stream, t, epoch, n_epochs, r0, rN, s0, sN,
+                     cooling, scale_cooling_of(c, cooling));
   return hipGetLastError();
 }
 
@@ -211,68 +302,102 @@ hipError_t launch_cool_schedule(som_ctx *c, int n_epochs, double r0, double rN, 
 // a wavefront needs for 16 neighbouring outputs and one source are contiguous (one scalar
 // load).  A lane owns one feature column, keeps 16 outputs in registers and streams over the
 // sources: 16 multiply-adds per loaded value, all operands but that value in scalar registers.
-//   GxT[image][source parity][xb][xi]  (xi padded to a multiple of 16 with zeros)
+// (k_epoch_tables writes them)
+//   GxT[image][source parity][xb][xi]  (xi padded to a multiple of 32 with zeros)
 //   GyT[class][yb][e], destination row yi = classes * e + class  (hex: classes = parities)
-constexpr int kSmoothTile = 16;
 constexpr int kSmoothUnroll = 8;    // source nodes whose loads are in flight together
 
-__global__ __launch_bounds__(256) void k_smooth_tables(const float *__restrict__ gx, const float *__restrict__ gy,
-                                                       int rows, int cols, int hex, int toroid, int xi_pad,
-                                                       int e_pad, float *__restrict__ GxT, float *__restrict__ GyT) {
-  const int par = hex ? 2 : 1;
-  const int64_t nx = (int64_t)par * par * cols * xi_pad;
-  const int64_t ny = (int64_t)par * rows * e_pad;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < nx + ny; o += stride) {
-    if (o < nx) {
-      const int xi = (int)(o % xi_pad);
-      const int xb = (int)((o / xi_pad) % cols);
-      const int ps = (int)((o / ((int64_t)xi_pad * cols)) % par);
-      const int img = (int)(o / ((int64_t)xi_pad * cols * par));
-      GxT[o] = xi < cols ? gx[col_offset2(xi, xb, img, ps, hex, toroid, cols)] : 0.f;
-    } else {
-      const int64_t q = o - nx;
-      const int e = (int)(q % e_pad);
-      const int yb = (int)((q / e_pad) % rows);
-      const int cls = (int)(q / ((int64_t)e_pad * rows));
-      const int yi = par * e + cls;
-      GyT[q] = yi < rows ? gy[row_offset(yi, yb, toroid, rows)] : 0.f;
+// Nodes that no instance chose contribute nothing to the sums.  Per map row the columns of the
+// nodes with C > 0 are listed in ascending order (hit_x, hit_n), so that the passes only touch what counts and the
+// rows of S that belong to empty nodes are never read; the count channel's pass along x is done on the way.  A
+// workgroup per map row.  cntT null: the lists alone.
+__global__ __launch_bounds__(256) void k_map_rows(const int32_t *__restrict__ counts, const float *__restrict__ gx, int rows,
+                                                  int cols, int hex, int toroid, int32_t *__restrict__ hit_x,
+                                                  int32_t *__restrict__ hit_n, double *__restrict__ cntT) {
+  __shared__ int s_x[kSmoothMatMax], s_c[kSmoothMatMax], s_n;
+  __shared__ float s_g[2 * kSmoothMatMax + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int y = blockIdx.x; y < rows; y += gridDim.x) {
+    if (tid < 64) {
+      int n = 0;
+      for (int x0 = 0; x0 < cols; x0 += 64) {
+        const int x = x0 + lane;
+        const int c = x < cols ? counts[(int64_t)y * cols + x] : 0;
+        const unsigned long long m = __ballot(c > 0);
+        const int at = n + __popcll(m & ((1ull << lane) - 1ull));
+        if (c > 0) {
+          hit_x[(int64_t)y * cols + at] = x;
+          if (cntT) { s_x[at] = x; s_c[at] = c; }
+        }
+        n += __popcll(m);
+      }
+      if (lane == 0) { hit_n[y] = n; s_n = n; }
+    } else if (cntT) {
+      for (int m = tid - 64; m <= 2 * cols; m += 192) s_g[m] = gx[m];
     }
+    if (!cntT) continue;                       // (cols is bounded by kSmoothMatMax with cntT only)
+    __syncthreads();
+    const int nh = s_n, k = rows * cols;
+    for (int o = tid; o < (hex ? 2 : 1) * cols; o += 256) {
+      const int p = o / cols, xi = o - p * cols;
+      double s = 0.0;
+      for (int t = 0; t < nh; ++t) s += (double)s_g[col_offset2(xi, s_x[t], p, y & 1, hex, toroid, cols)] * (double)s_c[t];
+      cntT[(int64_t)p * k + y * cols + xi] = s;
+    }
+    __syncthreads();
   }
 }
 
-// Nodes that no instance chose contribute nothing to the sums.  Per map row the columns of the
-// nodes with C > 0 are listed in ascending order (hit_x, hit_n), and the map rows that have any
-// (hit_rows, hit_rows[rows] = their number), so that both passes only touch what counts and the
-// rows of S that belong to empty nodes are never read.  One wavefront per map row.
-__global__ __launch_bounds__(64) void k_hit_lists(const int32_t *__restrict__ counts, int rows, int cols,
-                                                  int32_t *__restrict__ hit_x, int32_t *__restrict__ hit_n) {
-  const int lane = threadIdx.x;
-  for (int y = blockIdx.x; y < rows; y += gridDim.x) {
+// What else pass y needs, done by extra workgroups of the launch of pass x (grid.y beyond the map rows): the
+// neighbourhood masses D = pass y of the count channel, and the list of map rows that have chosen nodes (hit_rows,
+// hit_rows[rows] = their number).
+struct MassWork {
+  const double *cntT;
+  const float *gy;
+  double *massD;
+  const int32_t *hit_n;
+  int32_t *hit_rows;
+  int toroid;
+};
+
+__device__ __forceinline__ void mass_slice(const MassWork &mw, int rows, int cols, int hex, int block, int blocks) {
+  if (block == 0 && threadIdx.x < 64) {
+    const int lane = threadIdx.x;
     int n = 0;
-    for (int x0 = 0; x0 < cols; x0 += 64) {
-      const int x = x0 + lane;
-      const bool hit = x < cols && counts[y * cols + x] > 0;
+    for (int y0 = 0; y0 < rows; y0 += 64) {
+      const int y = y0 + lane;
+      const bool hit = y < rows && mw.hit_n[y] > 0;
       const unsigned long long m = __ballot(hit);
-      if (hit) hit_x[y * cols + n + __popcll(m & ((1ull << lane) - 1ull))] = x;
+      if (hit) mw.hit_rows[n + __popcll(m & ((1ull << lane) - 1ull))] = y;
       n += __popcll(m);
     }
-    if (lane == 0) hit_n[y] = n;
+    if (lane == 0) mw.hit_rows[rows] = n;
+  }
+  const int k = rows * cols;
+  for (int i = block * blockDim.x + threadIdx.x; i < k; i += blocks * blockDim.x) {
+    const int yi = i / cols, x = i - yi * cols;
+    const double *img = mw.cntT + (hex ? (int64_t)(yi & 1) * k : 0) + x;
+    // eight running sums: the loads of eight source rows are in flight together (a single chain of
+    // dependent fp64 additions is latency-bound)
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int yb = 0;
+    for (; yb + 8 <= rows; yb += 8)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        s[u] += (double)mw.gy[row_offset(yi, yb + u, mw.toroid, rows)] * img[(int64_t)(yb + u) * cols];
+    for (int u = 0; yb < rows; ++yb, ++u) s[u] += (double)mw.gy[row_offset(yi, yb, mw.toroid, rows)] * img[(int64_t)yb * cols];
+    mw.massD[i] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
   }
 }
 
-__global__ __launch_bounds__(64) void k_hit_rows(const int32_t *__restrict__ hit_n, int rows,
-                                                 int32_t *__restrict__ hit_rows) {
-  const int lane = threadIdx.x;
-  int n = 0;
-  for (int y0 = 0; y0 < rows; y0 += 64) {
-    const int y = y0 + lane;
-    const bool hit = y < rows && hit_n[y] > 0;
-    const unsigned long long m = __ballot(hit);
-    if (hit) hit_rows[n + __popcll(m & ((1ull << lane) - 1ull))] = y;
-    n += __popcll(m);
-  }
-  if (lane == 0) hit_rows[rows] = n;
+// Extra rows of grid.y that give every node a thread.
+static unsigned mass_rows(const som_ctx *c, dim3 grid, int threads) {
+  const int64_t per_row = (int64_t)grid.x * grid.z * threads;
+  return (unsigned)(((int64_t)c->k + per_row - 1) / per_row);
+}
+
+static MassWork mass_work(const som_ctx *c) {
+  return MassWork{c->cntT, c->gy, c->massD, c->hit_n, c->hit_rows, c->map_type == SOM_MAP_TOROID};
 }
 
 // Channel block and output tile of a workgroup.  Plain launch: channel block on grid.x, tile on
@@ -297,8 +422,13 @@ __global__ __launch_bounds__(256) void k_smooth_x_mat(const float *__restrict__ 
                                                       const float *__restrict__ GxT,
                                                       const int32_t *__restrict__ hit_x,
                                                       const int32_t *__restrict__ hit_n, int rows, int cols, int dim,
-                                                      int xi_pad) {
+                                                      int xi_pad, MassWork mw) {
   const int y = blockIdx.y;
+  if (y >= rows) {                   // uniform over the workgroup
+    mass_slice(mw, rows, cols, kHex, (y - rows) * gridDim.x * gridDim.z + blockIdx.z * gridDim.x + blockIdx.x,
+               (gridDim.y - rows) * gridDim.x * gridDim.z);
+    return;
+  }
   const int nh = hit_n[y];
   if (nh == 0) return;               // pass y skips this map row
   const int lane = threadIdx.x & 63;
@@ -420,7 +550,12 @@ __global__ __launch_bounds__(64 * kMfmaWaves) void k_smooth_mfma(const float *__
                                                      const int32_t *__restrict__ hit_n,
                                                      const int32_t *__restrict__ hit_rows,
                                                      const double *__restrict__ massD, int rows, int cols, int dim,
-                                                     int g_pad, int groups) {
+                                                     int g_pad, int groups, MassWork mw) {
+  if (!kPassY && (int)blockIdx.y >= rows) {          // uniform over the workgroup
+    mass_slice(mw, rows, cols, kHex, ((int)blockIdx.y - rows) * gridDim.x * gridDim.z + blockIdx.z * gridDim.x + blockIdx.x,
+               (gridDim.y - rows) * gridDim.x * gridDim.z);
+    return;
+  }
   constexpr int kM = 32 * MB;                        // outputs per workgroup
   constexpr int kCh = 32 * kMfmaWaves;               // channels per workgroup
   constexpr int kThreads = 64 * kMfmaWaves;
@@ -634,7 +769,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_smooth_mfma_split(const float *
                                                        const int32_t *__restrict__ hit_n,
                                                        const int32_t *__restrict__ hit_rows,
                                                        const double *__restrict__ massD, int rows, int cols,
-                                                       int dim, int g_pad, int groups) {
+                                                       int dim, int g_pad, int groups, MassWork mw) {
+  if (!kPassY && (int)blockIdx.y >= rows) {          // uniform over the workgroup
+    mass_slice(mw, rows, cols, kHex, ((int)blockIdx.y - rows) * gridDim.x * gridDim.z + blockIdx.z * gridDim.x + blockIdx.x,
+               (gridDim.y - rows) * gridDim.x * gridDim.z);
+    return;
+  }
   constexpr int kM = 32 * MB;                        // outputs per workgroup
   constexpr int kMp = (kM + 63) / 64 * 64;           // ... rounded up to whole wavefronts of staging tasks
   constexpr int kCh = 32 * kWaves;                   // channels per workgroup
@@ -821,8 +961,13 @@ static void launch_smooth_mfma(som_ctx *c, const float *In, float *Out, const fl
                                int lines, int parts, bool split) {
   int mb, groups;
   mfma_tiling(outputs, &mb, &groups);
-  const dim3 grid((unsigned)((c->dim + 32 * kMfmaWaves - 1) / (32 * kMfmaWaves)), (unsigned)lines, (unsigned)(parts * groups));
-  const dim3 split_grid((unsigned)((c->dim + 32 * kSplitWaves - 1) / (32 * kSplitWaves)), (unsigned)lines, (unsigned)(parts * groups));
+  dim3 grid((unsigned)((c->dim + 32 * kMfmaWaves - 1) / (32 * kMfmaWaves)), (unsigned)lines, (unsigned)(parts * groups));
+  dim3 split_grid((unsigned)((c->dim + 32 * kSplitWaves - 1) / (32 * kSplitWaves)), (unsigned)lines, (unsigned)(parts * groups));
+  if (!kPassY) {
+    grid.y += mass_rows(c, grid, 64 * kMfmaWaves);
+    split_grid.y += mass_rows(c, split_grid, 64 * kSplitWaves);
+  }
+  const MassWork mw = mass_work(c);
   // 16-byte loads of the source rows need rows that start and stay on 16-byte boundaries
   const bool vec4 = c->dim % 4 == 0 && c->dim >= 4 && (reinterpret_cast<uintptr_t>(In) & 15) == 0;
 #define SOM_SMOOTH_MFMA(B)                                                                                          \
@@ -830,13 +975,13 @@ static void launch_smooth_mfma(som_ctx *c, const float *In, float *Out, const fl
     if (split)                                                                                                      \
       hipLaunchKernelGGL((k_smooth_mfma_split<B, kPassY, kHex, kSplitWaves>), split_grid, dim3(64 * kSplitWaves), 0, \
                          c->stream, In, Out, Gt, c->hit_x, c->hit_n, c->hit_rows, c->massD, c->rows, c->cols, c->dim, \
-                         g_pad, groups);                                                                            \
+                         g_pad, groups, mw);                                                                        \
     else if (vec4)                                                                                                  \
       hipLaunchKernelGGL((k_smooth_mfma<B, kPassY, kHex, true>), grid, dim3(64 * kMfmaWaves), 0, c->stream, In, Out, \
-                         Gt, c->hit_x, c->hit_n, c->hit_rows, c->massD, c->rows, c->cols, c->dim, g_pad, groups);    \
+                         Gt, c->hit_x, c->hit_n, c->hit_rows, c->massD, c->rows, c->cols, c->dim, g_pad, groups, mw); \
     else                                                                                                            \
       hipLaunchKernelGGL((k_smooth_mfma<B, kPassY, kHex, false>), grid, dim3(64 * kMfmaWaves), 0, c->stream, In,     \
-                         Out, Gt, c->hit_x, c->hit_n, c->hit_rows, c->massD, c->rows, c->cols, c->dim, g_pad, groups); \
+                         Out, Gt, c->hit_x, c->hit_n, c->hit_rows, c->massD, c->rows, c->cols, c->dim, g_pad, groups, mw); \
   } while (0)
   switch (mb) {
     case 1: SOM_SMOOTH_MFMA(1); break;
@@ -862,73 +1007,10 @@ static void launch_smooth_mfma(som_ctx *c, const float *In, float *Out, const fl
 // contiguous: the same "lane owns a feature column, 16 outputs in registers, coefficients through
 // scalar loads" kernel as k_smooth_x_mat, now in one pass over all chosen source nodes whose row is
 // within reach, with the division at the end.  The count channel is summed in fp64 from the same table.
-__device__ __forceinline__ int direct_table_width(int cols, int toroid) {
-  return (toroid ? cols : 2 * cols - 1) + kSmoothTile;
-}
-
-__global__ __launch_bounds__(256) void k_direct_table(const EpochParams *__restrict__ params, int rows, int cols,
-                                                      int hex, int toroid, int function, int compact,
-                                                      float *__restrict__ H2) {
-  const int width = direct_table_width(cols, toroid);
-  const int classes = hex ? 3 : 1;
-  const double r = params->radius;
-  const double reach = 4.0 * r * r;               // q = 4 d^2 <= 4 r^2: inside the radius
-  const double inv = params->inv8r2;
-  const int64_t total = (int64_t)classes * rows * width;
-  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total; o += (int64_t)gridDim.x * blockDim.x) {
-    const int t = (int)(o % width);
-    const int a_raw = (int)((o / width) % rows);
-    const int cls = (int)(o / ((int64_t)width * rows));
-    const int dpar = hex ? cls - 1 : 0;
-    const int dx = toroid ? t % cols : t - (cols - 1);
-    long long m = 2ll * dx + dpar;
-    m = m < 0 ? -m : m;
-    long long a = a_raw;
-    if (toroid) {
-      if (2ll * cols - m < m) m = 2ll * cols - m;
-      if (rows - a < a) a = rows - a;
-    }
-    const double q = (double)(m * m + (hex ? 3 : 4) * a * a);
-    const bool inside = q <= reach;
-    float h;
-    if (function == SOM_NEIGHBORHOOD_BUBBLE) h = inside ? 1.f : 0.f;
-    else h = (compact && !inside) ? 0.f : (float)exp(-q * inv);
-    H2[o] = h;
-  }
-}
-
 __device__ __forceinline__ int direct_table_index(int xi, int xb, int cols, int toroid) {
   if (!toroid) return xi - xb + cols - 1;
   int d = xi - xb;
   return d < 0 ? d + cols : d;
-}
-
-__global__ __launch_bounds__(256) void k_count_direct(const int32_t *__restrict__ counts,
-                                                      const int32_t *__restrict__ hit_x,
-                                                      const int32_t *__restrict__ hit_n,
-                                                      const int32_t *__restrict__ hit_rows,
-                                                      const float *__restrict__ H2, int rows, int cols, int hex,
-                                                      int toroid, double *__restrict__ massD) {
-  const int k = rows * cols;
-  const int width = direct_table_width(cols, toroid);
-  const int nr = hit_rows[rows];
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < k; i += gridDim.x * blockDim.x) {
-    const int yi = i / cols, xi = i - yi * cols;
-    double s = 0.0;
-    for (int r = 0; r < nr; ++r) {
-      const int yb = hit_rows[r];
-      const int a = yi > yb ? yi - yb : yb - yi;
-      const int cls = hex ? (yi & 1) - (yb & 1) + 1 : 0;
-      const float *row = H2 + ((int64_t)cls * rows + a) * width;
-      const int32_t *hx = hit_x + (int64_t)yb * cols;
-      const int nh = hit_n[yb];
-      for (int t = 0; t < nh; ++t) {
-        const int xb = hx[t];
-        s += (double)row[direct_table_index(xi, xb, cols, toroid)] * (double)counts[yb * cols + xb];
-      }
-    }
-    massD[i] = s;
-  }
 }
 
 // Positions in the ascending list a[0..n) of the first entries that are >= v0, >= v1 and >= v2: every
@@ -949,24 +1031,31 @@ __device__ __forceinline__ void first_not_below3(const int32_t *__restrict__ a, 
   p2 = __builtin_amdgcn_readfirstlane(p2);
 }
 
-// grid = (ceil(dim/256), rows, ceil(cols/16)).  Source rows whose distance alone puts them out of
+// grid = (ceil(dim/64), rows, ceil(cols/16)).  A lane owns a feature channel, a workgroup 64 of them, and its four
+// wavefronts share the source rows (what the walk over the rows costs is a chain of dependent loads per row, so the
+// rows of one tile are walked in parallel; the partial sums are added in LDS: 70 -> 22 us on 45 x 60 nodes of
+// 100 channels at r = 12).  Source rows whose distance alone puts them out of
 // reach are skipped whole, and of the others only the source nodes whose column can be within reach of
 // one of the tile's 16 destination columns are visited: at row distance a that is |dx| <=
 // (sqrt(4 r^2 - (4 or 3) a^2) + 1) / 2, a stretch of the row's ascending hit list (two stretches
 // where it wraps round a toroid map).  The table holds zeros for everything
 // skipped, so the sums are the same; on a 336-column map at r = 30 the stretch is a seventh of the row.
+// The count channel is summed on the way, in fp64: lane l takes destination column l mod 16.
+constexpr int kDirectWaves = 4;
+
 template <bool kHex>
-__global__ __launch_bounds__(256) void k_smooth_direct(const float *__restrict__ S, float *__restrict__ W,
+__global__ __launch_bounds__(64 * kDirectWaves) void k_smooth_direct(const float *__restrict__ S, float *__restrict__ W,
                                                        const float *__restrict__ H2,
+                                                       const int32_t *__restrict__ counts,
                                                        const int32_t *__restrict__ hit_x,
                                                        const int32_t *__restrict__ hit_n,
-                                                       const int32_t *__restrict__ hit_rows,
-                                                       const double *__restrict__ massD,
                                                        const EpochParams *__restrict__ params, int rows, int cols,
                                                        int dim, int toroid, int bounded) {
+  __shared__ float s_acc[kDirectWaves][kSmoothTile][64];
+  __shared__ double s_mass[kDirectWaves][kSmoothTile];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c = blockIdx.x * 256 + wave * 64 + lane;
+  const int c = blockIdx.x * 64 + lane;
   const bool live = c < dim;
   const int yi = blockIdx.y;
   const int xi0 = blockIdx.z * kSmoothTile;
@@ -975,9 +1064,10 @@ __global__ __launch_bounds__(256) void k_smooth_direct(const float *__restrict__
   float acc[kSmoothTile];
 #pragma unroll
   for (int e = 0; e < kSmoothTile; ++e) acc[e] = 0.f;
-  const int nr = hit_rows[rows];
-  for (int r = 0; r < nr; ++r) {
-    const int yb = hit_rows[r];
+  double mass = 0.0;
+  for (int yb = wave; yb < rows; yb += kDirectWaves) {
+    const int nh = hit_n[yb];
+    if (nh == 0) continue;
     int a = yi > yb ? yi - yb : yb - yi;
     const int a_wrapped = (toroid && rows - a < a) ? rows - a : a;
     const double left = reach - (double)((kHex ? 3ll : 4ll) * a_wrapped * a_wrapped);
@@ -986,7 +1076,7 @@ __global__ __launch_bounds__(256) void k_smooth_direct(const float *__restrict__
     const float *trow = H2 + ((int64_t)cls * rows + a) * width;
     const float *src = S + (int64_t)yb * cols * dim + (live ? c : 0);
     const int32_t *hx = hit_x + (int64_t)yb * cols;
-    const int nh = hit_n[yb];
+    const int32_t *cnt = counts + (int64_t)yb * cols;
     // stretches [seg_lo[s], seg_hi[s]) of the hit list
     int seg_lo[2] = {0, 0}, seg_hi[2] = {nh, 0};
     if (bounded && nh >= 8) {
@@ -1012,86 +1102,160 @@ __global__ __launch_bounds__(256) void k_smooth_direct(const float *__restrict__
       for (int t = seg_lo[sgm]; t < t_end; t += kSmoothUnroll) {
         int xb[kSmoothUnroll];
         float s[kSmoothUnroll];
+        double n[kSmoothUnroll];
 #pragma unroll
         for (int u = 0; u < kSmoothUnroll; ++u) {
-          xb[u] = hx[min(t + u, t_end - 1)];
+          xb[u] = __builtin_amdgcn_readfirstlane(hx[min(t + u, t_end - 1)]);
           s[u] = (live && t + u < t_end) ? src[(int64_t)xb[u] * dim] : 0.f;
+          n[u] = t + u < t_end ? (double)cnt[xb[u]] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < kSmoothUnroll; ++u) {
           const float *g = trow + direct_table_index(xi0, xb[u], cols, toroid);
+          mass += (double)g[lane & (kSmoothTile - 1)] * n[u];
 #pragma unroll
           for (int e = 0; e < kSmoothTile; ++e) acc[e] = fmaf(g[e], s[u], acc[e]);
         }
       }
     }
   }
-  if (live) {
 #pragma unroll
-    for (int e = 0; e < kSmoothTile; ++e) {
-      const int xi = xi0 + e;
-      if (xi < cols) {
-        const int64_t i = (int64_t)yi * cols + xi;
-        const double D = massD[i];
-        if (D >= SOM_EPS_MASS) W[i * dim + c] = acc[e] / (float)D;
-      }
-    }
+  for (int e = 0; e < kSmoothTile; ++e) s_acc[wave][e][lane] = acc[e];
+  if (lane < kSmoothTile) s_mass[wave][lane] = mass;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kSmoothTile / kDirectWaves; ++q) {
+    const int e = wave + kDirectWaves * q;
+    const int xi = xi0 + e;
+    double D = 0.0;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kDirectWaves; ++w) { D += s_mass[w][e]; v += s_acc[w][e][lane]; }
+    if (live && xi < cols && D >= SOM_EPS_MASS) W[((int64_t)yi * cols + xi) * dim + c] = v / (float)D;
   }
 }
 
 static hipError_t launch_smooth_direct(som_ctx *c, float *W) {
   const int hex = c->grid_type == SOM_GRID_HEXAGONAL;
   const int toroid = c->map_type == SOM_MAP_TOROID;
-  const int width = (toroid ? c->cols : 2 * c->cols - 1) + kSmoothTile;
-  const int64_t entries = (int64_t)(hex ? 3 : 1) * c->rows * width;
-  int tb = (int)((entries + 255) / 256);
-  if (tb > c->n_cu * 8) tb = c->n_cu * 8;
-  hipLaunchKernelGGL(k_direct_table, dim3(tb), dim3(256), 0, c->stream, c->params, c->rows, c->cols, hex, toroid,
-                     c->nb_function, c->nb_compact, c->H2);
-  hipLaunchKernelGGL(k_hit_lists, dim3(c->rows < 1024 ? c->rows : 1024), dim3(64), 0, c->stream, c->counts, c->rows,
-                     c->cols, c->hit_x, c->hit_n);
-  hipLaunchKernelGGL(k_hit_rows, dim3(1), dim3(64), 0, c->stream, c->hit_n, c->rows, c->hit_rows);
-  int cb = (c->k + 255) / 256;
-  hipLaunchKernelGGL(k_count_direct, dim3(cb), dim3(256), 0, c->stream, c->counts, c->hit_x, c->hit_n, c->hit_rows,
-                     c->H2, c->rows, c->cols, hex, toroid, c->massD);
-  const dim3 grid((unsigned)((c->dim + 255) / 256), (unsigned)c->rows,
+  hipLaunchKernelGGL(k_map_rows, dim3(c->rows < 1024 ? c->rows : 1024), dim3(256), 0, c->stream, c->counts, c->gx, c->rows,
+                     c->cols, hex, toroid, c->hit_x, c->hit_n, (double *)nullptr);
+  const dim3 grid((unsigned)((c->dim + 63) / 64), (unsigned)c->rows,
                   (unsigned)((c->cols + kSmoothTile - 1) / kSmoothTile));
   const int bounded = c->nb_function == SOM_NEIGHBORHOOD_BUBBLE || c->nb_compact;
   if (hex)
-    hipLaunchKernelGGL(k_smooth_direct<true>, grid, dim3(256), 0, c->stream, c->S, W, c->H2, c->hit_x, c->hit_n,
-                       c->hit_rows, c->massD, c->params, c->rows, c->cols, c->dim, toroid, bounded);
+    hipLaunchKernelGGL(k_smooth_direct<true>, grid, dim3(64 * kDirectWaves), 0, c->stream, c->S, W, c->H2, c->counts, c->hit_x,
+                       c->hit_n, c->params, c->rows, c->cols, c->dim, toroid, bounded);
   else
-    hipLaunchKernelGGL(k_smooth_direct<false>, grid, dim3(256), 0, c->stream, c->S, W, c->H2, c->hit_x, c->hit_n,
-                       c->hit_rows, c->massD, c->params, c->rows, c->cols, c->dim, toroid, bounded);
+    hipLaunchKernelGGL(k_smooth_direct<false>, grid, dim3(64 * kDirectWaves), 0, c->stream, c->S, W, c->H2, c->counts, c->hit_x,
+                       c->hit_n, c->params, c->rows, c->cols, c->dim, toroid, bounded);
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- small maps: both passes in one launch
+// On a map of a few hundred nodes the seven launches of the general scheme (rows, masses, two passes, ..) have
+// nothing to do but wait for each other.  Here a workgroup takes one feature channel through both passes in LDS,
+// with the count channel in fp64 beside it (every workgroup repeats that one): 400 nodes x 10 channels 43 -> 7 us,
+// 1,073 hexagonal nodes x 33 channels 40 -> 13 us for the whole stage.
+constexpr int kSmallThreads = 1024;
+
+__global__ __launch_bounds__(kSmallThreads) void k_smooth_small(const float *__restrict__ S, float *__restrict__ W,
+                                                                const int32_t *__restrict__ counts,
+                                                                const float *__restrict__ gx, const float *__restrict__ gy,
+                                                                int rows, int cols, int dim, int hex, int toroid) {
+  extern __shared__ double s_cntT[];                  // [images][k], then the other arrays
+  const int k = rows * cols, images = hex ? 2 : 1;
+  double *s_c = s_cntT + images * k;                  // [k] counts
+  float *s_T = reinterpret_cast<float *>(s_c + k);    // [images][k]
+  float *s_S = s_T + images * k;                      // [k]
+  // the factors by signed offset, so that neighbouring sources read neighbouring entries:
+  // s_gx[2 (xi - xb) + parity difference + 2 cols], s_gy[yi - yb + rows]
+  float *s_gx = s_S + k;                              // [4 cols + 2]
+  float *s_gy = s_gx + 4 * cols + 2;                  // [2 rows]
+  const int c = blockIdx.x, tid = threadIdx.x;
+  for (int i = tid; i < k; i += kSmallThreads) {
+    const int n = counts[i];
+    const float v = S[(int64_t)i * dim + c];
+    s_c[i] = (double)n;
+    s_S[i] = n > 0 ? v : 0.f;                         // rows of nodes that nobody chose need not have been written
+  }
+  for (int t = tid; t <= 4 * cols; t += kSmallThreads) {
+    int m = t > 2 * cols ? t - 2 * cols : 2 * cols - t;
+    if (toroid && 2 * cols - m < m) m = 2 * cols - m;
+    s_gx[t] = gx[m];
+  }
+  for (int t = tid; t < 2 * rows; t += kSmallThreads) {
+    int a = t > rows ? t - rows : rows - t;
+    if (toroid && rows - a < a) a = rows - a;
+    s_gy[t] = gy[min(a, rows - 1)];
+  }
+  __syncthreads();
+  // (four terms at a time: a thread's chain of dependent LDS reads and additions is what these loops wait for)
+  for (int o = tid; o < images * k; o += kSmallThreads) {
+    const int p = o >= k, i = o - p * k;
+    const int y = i / cols, xi = i - y * cols;
+    const float *g = s_gx + 2 * xi + (hex ? p - (y & 1) : 0) + 2 * cols;
+    const float *row = s_S + y * cols;
+    const double *cnt = s_c + y * cols;
+    float acc = 0.f;
+    double mass = 0.0;
+#pragma unroll 4
+    for (int xb = 0; xb < cols; ++xb) {
+      const float f = g[-2 * xb];
+      acc = fmaf(f, row[xb], acc);
+      mass = fma((double)f, cnt[xb], mass);
+    }
+    s_T[o] = acc;
+    s_cntT[o] = mass;
+  }
+  __syncthreads();
+  for (int i = tid; i < k; i += kSmallThreads) {
+    const int yi = i / cols, x = i - yi * cols;
+    const float *g = s_gy + yi + rows;
+    const float *t = s_T + (hex ? (yi & 1) * k : 0) + x;
+    const double *m = s_cntT + (hex ? (yi & 1) * k : 0) + x;
+    float acc = 0.f;
+    double mass = 0.0;
+#pragma unroll 4
+    for (int yb = 0; yb < rows; ++yb) {
+      const float f = g[-yb];
+      acc = fmaf(f, t[yb * cols], acc);
+      mass = fma((double)f, m[yb * cols], mass);
+    }
+    if (mass >= SOM_EPS_MASS) W[(int64_t)i * dim + c] = acc / (float)mass;
+  }
+}
+
+// 1.2e5 multiply-adds per channel take a workgroup about 10 us, what the general scheme needs for its launches alone;
+// two channels per CU.  (A form asked for by som_set_smoothing is used as asked.)
+static bool small_smoothing(const som_ctx *c) {
+  const int64_t images = c->grid_type == SOM_GRID_HEXAGONAL ? 2 : 1;
+  return c->smooth_auto && (int64_t)c->k * (images * c->cols + c->rows) <= 120000 && c->dim <= 2 * c->n_cu;
+}
+
 hipError_t launch_smooth_and_divide(som_ctx *c, float *W) {
-  if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return launch_smooth_direct(c, W);
+  if (direct_neighbourhood(c)) return launch_smooth_direct(c, W);
   const int hex = c->grid_type == SOM_GRID_HEXAGONAL;
   const int toroid = c->map_type == SOM_MAP_TOROID;
   const int images = hex ? 2 : 1;
-  int cb = (images * c->k + 255) / 256;
-  hipLaunchKernelGGL(k_count_pass_x, dim3(cb), dim3(256), 0, c->stream, c->counts, c->gx, c->rows, c->cols, hex,
-                     toroid, c->cntT);
-  hipLaunchKernelGGL(k_count_pass_y, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->cntT, c->gy, c->rows,
-                     c->cols, hex, toroid, c->massD);
+  if (small_smoothing(c)) {
+    const size_t lds = (size_t)c->k * (images * 12 + 12) + 4 * (4 * (size_t)c->cols + 2 + 2 * c->rows);
+    hipLaunchKernelGGL(k_smooth_small, dim3(c->dim), dim3(kSmallThreads), lds, c->stream, c->S, W, c->counts, c->gx, c->gy,
+                       c->rows, c->cols, c->dim, hex, toroid);
+    return hipGetLastError();
+  }
   if (c->GxT) {           // sides small enough for coefficient matrices
     const int par = hex ? 2 : 1;
-    const int64_t entries = (int64_t)par * par * c->cols * c->xi_pad + (int64_t)par * c->rows * c->e_pad;
-    int tb = (int)((entries + 255) / 256);
-    if (tb > c->n_cu * 8) tb = c->n_cu * 8;
-    hipLaunchKernelGGL(k_smooth_tables, dim3(tb), dim3(256), 0, c->stream, c->gx, c->gy, c->rows, c->cols, hex, toroid,
-                       c->xi_pad, c->e_pad, c->GxT, c->GyT);
-    hipLaunchKernelGGL(k_hit_lists, dim3(c->rows < 1024 ? c->rows : 1024), dim3(64), 0, c->stream, c->counts, c->rows,
-                       c->cols, c->hit_x, c->hit_n);
-    hipLaunchKernelGGL(k_hit_rows, dim3(1), dim3(64), 0, c->stream, c->hit_n, c->rows, c->hit_rows);
+    hipLaunchKernelGGL(k_map_rows, dim3(c->rows), dim3(256), 0, c->stream, c->counts, c->gx, c->rows, c->cols, hex, toroid,
+                       c->hit_x, c->hit_n, c->cntT);
+    const MassWork mw = mass_work(c);
     const unsigned cb256 = (unsigned)((c->dim + 255) / 256);
     const unsigned xt = (unsigned)(images * ((c->cols + kSmoothTile - 1) / kSmoothTile));
     const unsigned yt = (unsigned)(par * (c->e_pad / kSmoothTile));
     const bool fold = cb256 >= 8;       // enough channel blocks to keep every XCD busy
     const unsigned cb8 = (cb256 + 7) / 8 * 8;
-    const dim3 gx = fold ? dim3(cb8 * xt, c->rows, 1) : dim3(cb256, c->rows, xt);
+    dim3 gx = fold ? dim3(cb8 * xt, c->rows, 1) : dim3(cb256, c->rows, xt);
+    gx.y += mass_rows(c, gx, 256);
     const dim3 gy = fold ? dim3(cb8 * yt, c->cols, 1) : dim3(cb256, c->cols, yt);
     // a pass runs on the matrix cores when its line is long enough to fill their 32-output blocks
     const bool mfma_x = c->smooth_mfma_min > 0 && c->cols >= c->smooth_mfma_min;
@@ -1102,20 +1266,24 @@ hipError_t launch_smooth_and_divide(som_ctx *c, float *W) {
     if (hex) {
       if (mfma_x) launch_smooth_mfma<false, true>(c, c->S, c->T, c->GxT, c->xi_pad, c->cols, c->rows, 2, split_x);
       else hipLaunchKernelGGL(k_smooth_x_mat<true>, gx, dim3(256), 0, c->stream, c->S, c->T, c->GxT,
-                              c->hit_x, c->hit_n, c->rows, c->cols, c->dim, c->xi_pad);
+                              c->hit_x, c->hit_n, c->rows, c->cols, c->dim, c->xi_pad, mw);
       if (mfma_y) launch_smooth_mfma<true, true>(c, c->T, W, c->GyT, c->e_pad, (c->rows + 1) / 2, c->cols, 2, split_y);
       else hipLaunchKernelGGL(k_smooth_y_mat<true>, gy, dim3(256), 0, c->stream, c->T, W, c->GyT,
                               c->hit_rows, c->massD, c->rows, c->cols, c->dim, c->e_pad);
     } else {
       if (mfma_x) launch_smooth_mfma<false, false>(c, c->S, c->T, c->GxT, c->xi_pad, c->cols, c->rows, 1, split_x);
       else hipLaunchKernelGGL(k_smooth_x_mat<false>, gx, dim3(256), 0, c->stream, c->S, c->T, c->GxT,
-                              c->hit_x, c->hit_n, c->rows, c->cols, c->dim, c->xi_pad);
+                              c->hit_x, c->hit_n, c->rows, c->cols, c->dim, c->xi_pad, mw);
       if (mfma_y) launch_smooth_mfma<true, false>(c, c->T, W, c->GyT, c->e_pad, c->rows, c->cols, 1, split_y);
       else hipLaunchKernelGGL(k_smooth_y_mat<false>, gy, dim3(256), 0, c->stream, c->T, W, c->GyT,
                               c->hit_rows, c->massD, c->rows, c->cols, c->dim, c->e_pad);
     }
     return hipGetLastError();
   }
+  hipLaunchKernelGGL(k_count_pass_x, dim3((images * c->k + 255) / 256), dim3(256), 0, c->stream, c->counts, c->gx, c->rows,
+                     c->cols, hex, toroid, c->cntT);
+  hipLaunchKernelGGL(k_count_pass_y, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->cntT, c->gy, c->rows,
+                     c->cols, hex, toroid, c->massD);
   const unsigned cblk = (unsigned)((c->dim + kSmoothCols - 1) / kSmoothCols);
   if (hex) {
     hipLaunchKernelGGL(k_smooth_x<true>, dim3(cblk, c->rows, 2), dim3(256), 0, c->stream, c->S, c->T, c->gx,

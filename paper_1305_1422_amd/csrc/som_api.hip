@@ -111,7 +111,7 @@ static void free_row_scratch(som_ctx *c) {
   dev_free(c->cand_n); dev_free(c->refine_list); dev_free(c->rescan_list);
   dev_free(c->collect_rows); dev_free(c->collect_thr); dev_free(c->collect_cnt); dev_free(c->collect_list);
   dev_free(c->sort_key[0]); dev_free(c->sort_key[1]); dev_free(c->sort_val[0]); dev_free(c->sort_val[1]);
-  dev_free(c->radix_hist); dev_free(c->chunk_node); dev_free(c->partial);
+  dev_free(c->radix_hist); dev_free(c->group_table); dev_free(c->chunk_node); dev_free(c->partial);
   dev_free(c->Xh); dev_free(c->xscale);
   dev_free(c->Xh1); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
   dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
@@ -160,7 +160,7 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
               dev_alloc(&c->sort_val[0], N) && dev_alloc(&c->sort_val[1], N) &&
               dev_alloc(&c->radix_hist, radix_table_entries(n));
     c->max_chunks = (int64_t)(N / kChunkRows) + c->k;
-    ok = ok && dev_alloc(&c->chunk_node, (size_t)c->max_chunks);
+    ok = ok && dev_alloc(&c->chunk_node, (size_t)c->max_chunks) && dev_alloc(&c->group_table, (size_t)group_table_entries(c->k, n));
     if (!ok) {
       free_row_scratch(c);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate scratch for %lld instances", (long long)n);
@@ -242,9 +242,9 @@ static int ensure_transposed(som_ctx *c) {
   if (c->Wt) return SOM_OK;
   const size_t words = ((size_t)c->dim * c->kpad + 1) / 2;      // int16 entries
   if (!(dev_alloc(&c->Wt, words) && dev_alloc(&c->col_range, (size_t)2 * 64 * c->dim) &&
-        dev_alloc(&c->qstep, (size_t)c->dim) && dev_alloc(&c->qstep_max_bits, 1) &&
+        dev_alloc(&c->qstep, (size_t)c->dim) &&
         dev_alloc(&c->ct_partial, (size_t)kCtMaxSlabs * c->k * 3))) {
-    dev_free(c->Wt); dev_free(c->col_range); dev_free(c->qstep); dev_free(c->qstep_max_bits); dev_free(c->ct_partial);
+    dev_free(c->Wt); dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial);
     return fail(c, SOM_ERR_ALLOC, "cannot allocate the transposed code book (%d x %d)", c->dim, c->kpad);
   }
   SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->Wt, (int64_t)words));
@@ -300,11 +300,20 @@ struct StageTimer {
 };
 
 // ---------------------------------------------------------------- stages
+// List lengths, work counters and maxima of a search start from zero: cleared by the epoch's first launch, or here.
+static int begin_search(som_ctx *c) {
+  if (!c->search_zeroed) SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
+  c->search_zeroed = 0;
+  return SOM_OK;
+}
+
 // Everything the filter pass needs besides the instances' own norms: centring vector (unless the
 // data are the registered set, whose vector is kept), centred code book and node constants, and
 // for the split-fp16 filter the fp16 planes of both operands.
 static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, bool have_xn) {
   StageTimer t(c, 5);
+  int rc = begin_search(c);
+  if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = two_level_ready(c, n);
   if (!have_xn) {
@@ -324,7 +333,6 @@ static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, 
   if (split)
     SOM_LAUNCH(c, launch_split_rows_f16(c, c->Wc, c->k, c->wmax_bits + 1, nullptr, c->Wh, c->wscale, 0,
                                         coarse ? c->Wh1 : nullptr));
-  SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
   return SOM_OK;
 }
 
@@ -407,9 +415,10 @@ static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices
   // centring vector of the sparse search: the mean of the code-book rows (changes every epoch);
   // it overwrites the one a registered dense training set may have cached
   if (c->data_kind == 1) { c->d_norms_valid = 0; c->d_split_valid = 0; }
+  rc = begin_search(c);
+  if (rc) return rc;
   SOM_LAUNCH(c, launch_codebook_means_and_steps(c, W));
   SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
-  SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
   return SOM_OK;
 }
 
@@ -446,11 +455,12 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
   c->two_level_n = coarse ? n : 0;
   {
     StageTimer t(c, 5);
+    rc = begin_search(c);
+    if (rc) return rc;
     SOM_LAUNCH(c, launch_center_codebook(c, W, true, true /* |w|^2 in fp64 for the sparse exact kernels */, true));
     if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
     SOM_LAUNCH(c, launch_split_rows_f16(c, c->Wc, c->k, c->wmax_bits + 1, nullptr, c->Wh, c->wscale, 0,
                                         coarse ? c->Wh1 : nullptr));
-    SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
   }
   {
     StageTimer t(c, 1);
@@ -506,8 +516,7 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
 static int update_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus, float *W) {
   {
     StageTimer t(c, 3);
-    SOM_LAUNCH(c, launch_sort_by_bmu(c, bmus, n));
-    SOM_LAUNCH(c, launch_accumulate_dense(c, X, n));
+    SOM_LAUNCH(c, launch_accumulate_dense(c, X, n, bmus));
   }
   StageTimer t(c, 4);
   SOM_LAUNCH(c, launch_smooth_and_divide(c, W));
@@ -566,10 +575,9 @@ static int registered_hot(som_ctx *c) {
     const size_t halves = (size_t)kHot * 2;
     if (!(dev_alloc(&c->hot_counts, (size_t)c->dim) && dev_alloc(&c->hot_rank, (size_t)c->dim) &&
           dev_alloc(&c->hot_cols, (size_t)kHot) && dev_alloc(&c->hot_Wc, (size_t)c->k * kHot) &&
-          dev_alloc(&c->hot_Wh, (size_t)c->k * halves) && dev_alloc(&c->hot_wscale, 1) &&
-          dev_alloc(&c->hot_wmax_bits, 1))) {
+          dev_alloc(&c->hot_Wh, (size_t)c->k * halves) && dev_alloc(&c->hot_wscale, 1))) {
       dev_free(c->hot_counts); dev_free(c->hot_rank); dev_free(c->hot_cols); dev_free(c->hot_Wc); dev_free(c->hot_Wh);
-      dev_free(c->hot_wscale); dev_free(c->hot_wmax_bits);
+      dev_free(c->hot_wscale);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the hot-column tables");
     }
   }
@@ -700,6 +708,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   c->scale_cooling = -1;
   c->hot_enabled = 1;
   c->csrd_enabled = 1;
+  c->smooth_auto = 1;
   c->smooth_mfma_min = kSmoothMfmaMin;
   c->smooth_split_min = kSmoothSplitMin;
 
@@ -714,8 +723,8 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
 
   const size_t K = (size_t)c->k;
   const size_t images = grid_type == SOM_GRID_HEXAGONAL ? 2 : 1;
-  bool ok = dev_alloc(&c->wn32, (K + 127) / 128 * 128) && dev_alloc(&c->wn64, K) && dev_alloc(&c->wmax_bits, 2) &&
-            dev_alloc(&c->counts, K + 1) && dev_alloc(&c->seg_off, K + 1) && dev_alloc(&c->chunk_off, K + 1) &&
+  bool ok = dev_alloc(&c->wn32, (K + 127) / 128 * 128) && dev_alloc(&c->wn64, K) &&
+            dev_alloc(&c->counts, K + 1) && dev_alloc(&c->group_local, 2 * (K + (K + 63) / 64)) && dev_alloc(&c->seg_off, K + 1) && dev_alloc(&c->chunk_off, K + 1) &&
             dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
             dev_alloc(&c->gy, (size_t)rows) && dev_alloc(&c->params, 1) && dev_alloc(&c->list_counts, kListWords) &&
             dev_alloc(&c->mu, (size_t)dim) && dev_alloc(&c->mu_partial, (size_t)64 * dim) &&
@@ -732,6 +741,9 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
     som_destroy(c);
     return fail(nullptr, SOM_ERR_ALLOC, "cannot allocate map scratch (%d nodes x %d)", c->k, dim);
   }
+  c->wmax_bits = reinterpret_cast<unsigned *>(c->list_counts) + kMaxWords;
+  c->qstep_max_bits = c->wmax_bits + 2;
+  c->hot_wmax_bits = c->wmax_bits + 3;
   hipError_t e = launch_fill_zero_u32(c->stream, c->list_counts, kListWords);
   if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->zero16, 16);
   if (e == hipSuccess && K % 128 != 0) {       // the tail of the node constants past k stays +inf for good
@@ -755,18 +767,18 @@ void som_destroy(som_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   free_row_scratch(c);
   if (c->direct_rec) (void)hipFree(c->direct_rec);
-  dev_free(c->wn32); dev_free(c->wn64); dev_free(c->wmax_bits); dev_free(c->counts); dev_free(c->seg_off);
+  dev_free(c->wn32); dev_free(c->wn64); dev_free(c->counts); dev_free(c->group_local); dev_free(c->seg_off);
   dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->row_hash); dev_free(c->dedup_keys);
   dev_free(c->dedup_lowest); dev_free(c->cntT); dev_free(c->gx); dev_free(c->gy);
   dev_free(c->params); dev_free(c->list_counts); dev_free(c->unit_work); dev_free(c->vq); dev_free(c->S); dev_free(c->T); dev_free(c->Wt); dev_free(c->Wt32);
-  dev_free(c->col_range); dev_free(c->qstep); dev_free(c->qstep_max_bits); dev_free(c->ct_partial); dev_free(c->H2);
+  dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial); dev_free(c->H2);
   dev_free(c->GxT); dev_free(c->GyT); dev_free(c->hit_x); dev_free(c->hit_n); dev_free(c->hit_rows);
   dev_free(c->mu); dev_free(c->mu_partial); dev_free(c->Wc); dev_free(c->zero16); dev_free(c->mu_norm2);
   dev_free(c->Wh); dev_free(c->Wh1); dev_free(c->wscale);
   free_hot(c);
   dev_free(c->csrd_mu); dev_free(c->csrd_mu_norm2); dev_free(c->csrd_xn);
   dev_free(c->hot_counts); dev_free(c->hot_rank); dev_free(c->hot_cols); dev_free(c->hot_Wc); dev_free(c->hot_Wh);
-  dev_free(c->hot_wscale); dev_free(c->hot_wmax_bits);
+  dev_free(c->hot_wscale);
   for (int s = 0; s < SOM_PROFILE_STAGES; ++s) {
     if (!c->prof_ev[s]) continue;
     for (int e = 0; e < 2 * kProfMax; ++e) (void)hipEventDestroy(c->prof_ev[s][e]);
@@ -853,7 +865,7 @@ int som_update_dense(som_ctx *c, const float *data, int64_t n, const int32_t *bm
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
   if (!rc) rc = ensure_rows(c, n, true, false);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
+  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, false));
   return update_dense(c, data, n, bmus, codebook);
 }
 
@@ -865,7 +877,7 @@ int som_update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, co
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
   if (!rc) rc = ensure_rows(c, n, false);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
+  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, false));
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
 }
 
@@ -881,7 +893,7 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   bool reg = false;
   if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
+  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
   rc = bmu_search_dense(c, data, n, codebook, bmus, reg);
   if (rc) return rc;
   return update_dense(c, data, n, bmus, codebook);
@@ -902,7 +914,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
     reg = true;
   }
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR));
+  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
   rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg);
   if (rc) return rc;
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
@@ -980,7 +992,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (!rc && !dense && !c->csrd_on) rc = registered_hot(c);
   if (rc) return rc;
   for (int e = 0; e < n_epochs; ++e) {
-    SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling));
+    SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, true));
     if (dense) {
       rc = bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true);
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
@@ -1061,6 +1073,7 @@ int som_validate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, 
   if (rc) return rc;
   int32_t *flag = c->list_counts + 3;
   int32_t bad = 0;
+  c->search_zeroed = 0;
   SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, flag, 1));
   SOM_LAUNCH(c, launch_validate_csr(c, indptr, indices, n, nnz, flag));
   SOM_LAUNCH(c, hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, c->stream));
@@ -1099,6 +1112,7 @@ int som_set_smoothing(som_ctx *c, int form) {
   if (!c) return SOM_ERR_INVALID_ARG;
   if (form != SOM_SMOOTH_AUTO && form != SOM_SMOOTH_VECTOR && form != SOM_SMOOTH_MATRIX && form != SOM_SMOOTH_MATRIX_SPLIT)
     return fail(c, SOM_ERR_INVALID_ARG, "unknown smoothing form %d", form);
+  c->smooth_auto = form == SOM_SMOOTH_AUTO;
   c->smooth_mfma_min = form == SOM_SMOOTH_AUTO ? kSmoothMfmaMin : (form == SOM_SMOOTH_VECTOR ? 0 : 1);
   c->smooth_split_min = form == SOM_SMOOTH_AUTO ? kSmoothSplitMin : (form == SOM_SMOOTH_MATRIX_SPLIT ? 1 : 0);
   return SOM_OK;

@@ -96,7 +96,7 @@ struct som_ctx {
   // per-map scratch (allocated in som_init)
   float *wn32;            // [k rounded up to 128] node constants c_i of the BMU filters, fp32; +inf past k
   double *wn64;           // [k] the same in fp64
-  unsigned *wmax_bits;    // [2] bit patterns of max_i |w'_i|^2 and of the largest |w'| element (non-negative floats order like uints)
+  unsigned *wmax_bits;    // [2] (words of list_counts, cleared with it) bit patterns of max_i |w'_i|^2 and of the largest |w'| element (non-negative floats order like uints)
   int32_t *counts;        // [k] instances per BMU
   int32_t *seg_off;       // [k+1] exclusive scan of counts
   int32_t *chunk_off;     // [k+1] exclusive scan of chunks per node
@@ -112,6 +112,7 @@ struct som_ctx {
   float *GxT, *GyT;       // the two filters as transposed coefficient matrices (maps with sides <= kSmoothMatMax)
   int xi_pad, e_pad;      // padded output extents of GxT / GyT (multiples of 32)
   int smooth_mfma_min;    // a smoothing pass over lines of at least this many nodes runs on the matrix cores (0: never)
+  int smooth_auto;        // the form of the smoothing passes is the library's choice (som_set_smoothing)
   int smooth_split_min;   // ... and from this many nodes on with bf16 operands in three parts (0: never)
   int32_t *hit_x, *hit_n; // [k] columns of the chosen nodes per map row, [rows] their number
   int32_t *hit_rows;      // [rows+1] map rows with chosen nodes, last entry = their number
@@ -132,7 +133,7 @@ struct som_ctx {
   float *col_range;       // [2][64][dim] slab minima and maxima of the code-book columns (with Wt)
   float *qstep;           // [dim] quantisation step of every column of Wt (with Wt)
   double *ct_partial;     // [kCtMaxSlabs][k][3] row sums per column slab of the fused centring / transpose pass (with Wt)
-  unsigned *qstep_max_bits;   // [1] bit pattern of the largest step
+  unsigned *qstep_max_bits;   // [1] (word of list_counts) bit pattern of the largest step
   float *Wc;              // [k][dim] centred code book w' = fl(w - mu) of the dense BMU search (lazily allocated)
   _Float16 *Wh;           // [k][ceil(dim/32)][64] centred code book as fp16 hi/lo planes (lazily allocated)
   _Float16 *Wh1;          // [k][ceil(dim/64)][64] its hi halves alone (two-level search)
@@ -179,11 +180,14 @@ struct som_ctx {
   int32_t *sort_key[2];   // [n] each
   int32_t *sort_val[2];   // [n] each
   int32_t *radix_hist;    // [bins * sort tiles], radix_table_entries(n_cap)
+  int32_t *group_table;   // [key tiles][k] counters of the counting sort, group_table_entries(k, n_cap)
+  int32_t *group_local;   // [2][k] and [2][ceil(k/64)]: scans of the counting sort within blocks of 64 nodes, block sums
   int32_t *chunk_node;    // [n/kChunkRows + k]
   float *partial;         // [n/kChunkRows + k][dim]
   int64_t max_chunks;
   void *direct_rec;       // records of the direct search (bmu_direct.hip), direct_cap bytes
   size_t direct_cap;
+  int search_zeroed;      // list_counts has been cleared for the next search (by k_epoch_tables)
   int stats_none;         // the most recent search left nothing to the exact stage (direct search)
 
   // hot-column split of the registered sparse training set (csr_hot.hip); built on first use
@@ -205,7 +209,7 @@ struct som_ctx {
   float *hot_Wc;          // [k][kHot] hot columns of the centred code book
   _Float16 *hot_Wh;       // [k][kHot/32][64] the same as planes
   float *hot_wscale;      // [1]
-  unsigned *hot_wmax_bits;    // [1]
+  unsigned *hot_wmax_bits;    // [1] (word of list_counts)
   float *hot_P;           // [ceil(k/128)][n][128] dot products of the hot parts divided by the instance scale
 
   // dense planes of the registered sparse training set (som_set_sparse_dense_filter); built on first use
@@ -303,6 +307,7 @@ constexpr int kListTickets = 8;    // entry counters of the list comparison behi
 constexpr int kListTicketStride = 1088;      // ... 4 KB + 256 B apart: another memory channel each
 constexpr int kListWords = kListCounts + kListTickets * kListTicketStride;
 constexpr int kUnitCounts = 4;     // first of the eight work-list lengths in it
+constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits
 enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3 };      // whose rounding bound the margin uses
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus,
                           bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */);
@@ -357,15 +362,15 @@ hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_
                                  bool hot = false);   // the rows are the tail of the registered set: sums start from hot_P
 
 // segsum.hip
-hipError_t launch_sort_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n);   // -> sort_val[0] = row ids
+int64_t group_table_entries(int k, int64_t n);       // entries of c->group_table for up to n instances
 hipError_t launch_sort_keys(som_ctx *c, const int32_t *keys, int64_t n, int key_range);   // the permutation alone
-hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n);   // -> S, counts
+hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus);   // -> S, counts
 hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
                                  const float *values, int64_t n, const int32_t *bmus);   // -> S, counts
 
 // smooth.hip
 hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0,
-                               double sN, int cooling);
+                               double sN, int cooling, bool search);
 hipError_t launch_cool_schedule(som_ctx *c, int n_epochs, double r0, double rN, double s0, double sN,
                                 int cooling, double *radius_out, double *scale_out);
 hipError_t launch_smooth_and_divide(som_ctx *c, float *W);

@@ -1,0 +1,47 @@
+"""Per-node sums and smoothing of the update alone, for given BMUs, through every way the instances are grouped by node
+(a workgroup per node, one workgroup's counting sort, the tiled one, maps whose counters leave room for one or two
+wavefronts only) and the one-launch smoothing of small maps, against the oracle: skewed, uniform and single-node
+assignments, sizes at the edges of the tiles."""
+import numpy as np
+import pytest
+
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("n,rows,cols,dim,grid,map_type", [
+    (1, 1, 1, 1, "square", "planar"), (63, 3, 5, 7, "hexagonal", "toroid"), (512, 20, 20, 10, "square", "planar"),
+    (513, 1, 70, 33, "hexagonal", "planar"), (8192, 9, 7, 32, "hexagonal", "toroid"), (8193, 9, 7, 5, "square", "toroid"),
+    (4097, 37, 29, 63, "hexagonal", "planar"), (3000, 12, 11, 300, "square", "toroid"),      # a workgroup per node
+    (16384, 21, 19, 40, "square", "planar"), (16385, 21, 19, 40, "hexagonal", "toroid"),      # one workgroup, tiles
+    (40001, 70, 70, 6, "square", "toroid"), (20000, 140, 150, 5, "hexagonal", "planar"),      # fewer counters per wavefront
+    (9000, 230, 231, 3, "square", "planar"),
+])
+@pytest.mark.parametrize("spread", ["skewed", "uniform", "one"])
+def test_update_for_given_bmus(oracle, n, rows, cols, dim, grid, map_type, spread):
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(6100 + n + dim)
+    k = rows * cols
+    X = rng.normal(0, 1, (n, dim)).astype(np.float32)
+    W = rng.random((k, dim)).astype(np.float32)
+    if spread == "uniform":
+        b = rng.integers(0, k, n)
+    elif spread == "skewed":
+        b = np.minimum(rng.integers(0, k, n), rng.integers(0, k, n) // 7)
+        b[rng.random(n) < 0.4] = k - 1
+    else:
+        b = np.full(n, k // 2)
+    b = b.astype(np.int32)
+    radius = max(1.0, min(rows, cols) / 4)
+    S, C = oracle.accumulate_dense(X, b, k)
+    new = []
+    for _ in range(2):
+        som = Som(rows, cols, dim, map_type, grid, codebook=torch.from_numpy(W))
+        som.update(P.to_dev(X), P.to_dev(b), radius)
+        new.append(som.codebook.cpu().numpy())
+        som.close()
+    assert np.array_equal(new[0], new[1])                    # the order of the additions is fixed
+    P.check_codebook(oracle, S, C, W, new[0], rows, cols, P.MAP[map_type], P.GRID[grid], radius)
