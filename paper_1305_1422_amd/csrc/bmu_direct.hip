@@ -23,6 +23,7 @@
 // Sharing out the work: a wavefront per 16 instances sweeps all nodes (many instances), the 8 wavefronts of a
 // workgroup share the nodes of 16 instances, or (few instances) the nodes are shared out over grid.y as well,
 // long rows over the four wavefronts of a workgroup besides, and a second kernel merges the groups.
+#include "row_load.hpp"
 #include "som_internal.hpp"
 
 #include <math.h>
@@ -30,7 +31,6 @@
 namespace som {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4d __attribute__((ext_vector_type(4)));
 
 constexpr int kDirectList = 64;       // nodes listed per open instance
 
@@ -129,42 +129,10 @@ __device__ __forceinline__ void direct_plain(const float *__restrict__ x, const 
   }
 }
 
-// This lane's four features c .. c + 3 of a row.  One 16-byte load on a 4-byte boundary, moved back where it would
-// reach past the row; direct_tail puts the features in place then (when they are used: what stands between a load
-// and its use has the compiler wait for everything in flight) and the zeros behind them.
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-template <bool kWide>
-__device__ __forceinline__ f32x4d direct_load(const float *__restrict__ row, int c, int dim) {
-  f32x4d v;
-  if (kWide) {
-    const f32x4u t = *reinterpret_cast<const f32x4u *>(row + min(c, dim - 4));
-    v = f32x4d{t[0], t[1], t[2], t[3]};
-  } else {                                       // rows of one to three features
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = row[min(c + e, dim - 1)];
-  }
-  return v;
-}
-
-template <bool kWide>
-__device__ __forceinline__ void direct_tail(f32x4d &v, int c, int dim) {
-  if (kWide) {
-    const int s = c - (dim - 4);                // how far the load was moved back, if at all
-    if (s > 0) {
-      const f32x4d t = (s & 1) ? f32x4d{v[1], v[2], v[3], 0.f} : v;
-      const f32x4d u = (s & 2) ? f32x4d{t[2], t[3], 0.f, 0.f} : t;
-      v = s >= 4 ? f32x4d{0.f, 0.f, 0.f, 0.f} : u;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = c + e < dim ? v[e] : 0.f;
-  }
-}
-
 // 16 features: lane group g holds features c0 + 4 g .. + 3 of its rows, matrix instruction e takes feature
 // c0 + 4 g + e from both operands.
 template <int NT>
-__device__ __forceinline__ void direct_step(const f32x4d &xs, const f32x4d (&ws)[NT], f64x4 (&acc)[NT], double (&wn)[NT]) {
+__device__ __forceinline__ void direct_step(const f32x4r &xs, const f32x4r (&ws)[NT], f64x4 (&acc)[NT], double (&wn)[NT]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const double xd = (double)xs[e];
@@ -212,13 +180,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
 
   // |x|^2 of instance l16, and the instances themselves if their rows are short
   constexpr int kHold = kSteps > 0 ? kSteps : 1;
-  f32x4d xs[kHold];
+  f32x4r xs[kHold];
   double xn = 0.0;
   if (kSteps > 0) {
 #pragma unroll
     for (int a = 0; a < kSteps; ++a) {
-      xs[a] = direct_load<kWide>(xr, 16 * a + 4 * g, dim);
-      direct_tail<kWide>(xs[a], 16 * a + 4 * g, dim);
+      xs[a] = row_load<kWide>(xr, 16 * a + 4 * g, dim);
+      row_tail<kWide>(xs[a], 16 * a + 4 * g, dim);
 #pragma unroll
       for (int e = 0; e < 4; ++e) xn = fma((double)xs[a][e], (double)xs[a][e], xn);
     }
@@ -259,14 +227,14 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
     }
   };
   auto sweep = [&](bool collect) {
-    f32x4d wv[2][kHold][NT];
+    f32x4r wv[2][kHold][NT];
     auto row_of = [&](int tile, int t) { return W + (int64_t)min(tile * 16 * NT + 16 * t + l16, k - 1) * dim; };
-    auto load_tile = [&](f32x4d (&dst)[kHold][NT], int tile) {
+    auto load_tile = [&](f32x4r (&dst)[kHold][NT], int tile) {
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float *wr = row_of(tile, t);
 #pragma unroll
-        for (int a = 0; a < kHold; ++a) dst[a][t] = direct_load<kWide>(wr, 16 * a + 4 * g, dim);
+        for (int a = 0; a < kHold; ++a) dst[a][t] = row_load<kWide>(wr, 16 * a + 4 * g, dim);
       }
     };
     if (kSteps > 0 && first < t1) load_tile(wv[0], first);
@@ -281,40 +249,40 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
         for (int a = 0; a < kSteps; ++a) {
           if (16 * a + 16 > dim)               // uniform
 #pragma unroll
-            for (int t = 0; t < NT; ++t) direct_tail<kWide>(wv[0][a][t], 16 * a + 4 * g, dim);
+            for (int t = 0; t < NT; ++t) row_tail<kWide>(wv[0][a][t], 16 * a + 4 * g, dim);
           direct_step<NT>(xs[a], wv[0][a], acc, wn);
         }
       } else {
-        f32x4d xa[2], wa[2][NT];
+        f32x4r xa[2], wa[2][NT];
         const float *wr[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) wr[t] = row_of(tile, t);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-          xa[b] = direct_load<kWide>(xr, c_lo + 16 * b + 4 * g, dim);
+          xa[b] = row_load<kWide>(xr, c_lo + 16 * b + 4 * g, dim);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) wa[b][t] = direct_load<kWide>(wr[t], c_lo + 16 * b + 4 * g, dim);
+          for (int t = 0; t < NT; ++t) wa[b][t] = row_load<kWide>(wr[t], c_lo + 16 * b + 4 * g, dim);
         }
         xn = 0.0;
         for (int c0 = c_lo; c0 < c_hi; c0 += 32) {
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
-            f32x4d x1 = xa[b], w1[NT];
+            f32x4r x1 = xa[b], w1[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) w1[t] = wa[b][t];
             const int c = c0 + 16 * b + 4 * g;
-            xa[b] = direct_load<kWide>(xr, c + 32, dim);
+            xa[b] = row_load<kWide>(xr, c + 32, dim);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) wa[b][t] = direct_load<kWide>(wr[t], c + 32, dim);
+            for (int t = 0; t < NT; ++t) wa[b][t] = row_load<kWide>(wr[t], c + 32, dim);
             if (c0 + 16 * b + 16 > dim) {        // uniform
-              direct_tail<kWide>(x1, c, dim);
+              row_tail<kWide>(x1, c, dim);
 #pragma unroll
-              for (int t = 0; t < NT; ++t) direct_tail<kWide>(w1[t], c, dim);
+              for (int t = 0; t < NT; ++t) row_tail<kWide>(w1[t], c, dim);
             }
             if (kSplit && c0 + 16 * b >= c_hi) {      // an odd number of steps: the next wavefront's features
-              x1 = f32x4d{0.f, 0.f, 0.f, 0.f};
+              x1 = f32x4r{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-              for (int t = 0; t < NT; ++t) w1[t] = f32x4d{0.f, 0.f, 0.f, 0.f};
+              for (int t = 0; t < NT; ++t) w1[t] = f32x4r{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) xn = fma((double)x1[e], (double)x1[e], xn);

@@ -27,6 +27,7 @@
 // Sparse scores |w|^2 - 2 x.w from an FMA chain of len terms, no centring: g = len,
 //   |s_fp32 - s_exact| <= u [ (2 g + 2) X Wm + 2 Wm^2 ].
 #include "margin.hpp"
+#include "row_load.hpp"
 
 namespace som {
 
@@ -739,37 +740,66 @@ hipError_t launch_refine_lists_csr(som_ctx *c, const int64_t *indptr, const int3
 // partial sum, the partial sums are added in index order by k_mean_of_partials: the result
 // does not depend on the schedule.  A node index outside [0, k) yields NaN.
 
-template <bool kCsr>
-__global__ __launch_bounds__(256) void k_bmu_distances(const float *__restrict__ X,
-                                                       const int64_t *__restrict__ indptr,
-                                                       const int32_t *__restrict__ indices,
-                                                       const float *__restrict__ values,
-                                                       const float *__restrict__ W, int64_t n, int k, int dim,
-                                                       const int32_t *__restrict__ bmus, float *__restrict__ dist,
-                                                       double *__restrict__ partial) {
-  __shared__ double wave_total[4];
+// Dense rows: memory-bound, one read of the instances (the nodes' rows come out of L2); a wavefront takes 1,024 features
+// of instance and node before it uses the first (100,000 x 1,000: 208 -> 82 us).
+// Sparse rows need |w|^2 of their nodes.  The nodes met are marked first (k_mark_nodes) and their norms taken once,
+// by a workgroup each (k_marked_norms): an instance's own wavefront reading its node's whole row took 321 us for 1,000
+// instances of a 50,000-column set on 321 nodes, the three launches take 35.
+constexpr int kDistThreads = 512;
+
+template <bool kCsr, bool kWide>
+__global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__restrict__ X,
+                                                                const int64_t *__restrict__ indptr,
+                                                                const int32_t *__restrict__ indices,
+                                                                const float *__restrict__ values,
+                                                                const float *__restrict__ W, const double *__restrict__ wn64,
+                                                                int64_t n, int k, int dim,
+                                                                const int32_t *__restrict__ bmus, float *__restrict__ dist,
+                                                                double *__restrict__ partial) {
+  constexpr int kWaves = kDistThreads / kWave;
+  __shared__ double wave_total[kWaves];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
   const int64_t per_block = (n + gridDim.x - 1) / gridDim.x;
   const int64_t j0 = (int64_t)blockIdx.x * per_block;
   const int64_t j1 = j0 + per_block < n ? j0 + per_block : n;
   double total = 0.0;
-  for (int64_t j = j0 + wave; j < j1; j += 4) {
+  for (int64_t j = j0 + wave; j < j1; j += kWaves) {
     const int b = bmus[j];
     double d = NAN;
     if ((unsigned)b < (unsigned)k) {
       const float *w = W + (int64_t)b * dim;
       double d2;
       if (kCsr) {
-        double wn = 0.0;
-        for (int c = lane; c < dim; c += kWave) wn += (double)w[c] * (double)w[c];
-        wn = wave_sum(wn);
         const int64_t rs = indptr[j];
         const int len = (int)(indptr[j + 1] - rs);
-        d2 = sqdist_csr_wave(indices + rs, values + rs, len, w, wn, csr_row_sqnorm_wave(values + rs, len, lane), dim,
+        d2 = sqdist_csr_wave(indices + rs, values + rs, len, w, wn64[b], csr_row_sqnorm_wave(values + rs, len, lane), dim,
                              lane);
       } else {
-        d2 = sqdist_dense_wave(X + j * dim, w, dim, lane);
+        const float *x = X + j * dim;
+        double s = 0.0;
+        for (int c0 = 0; c0 < dim; c0 += 4 * 4 * kWave) {
+          f32x4r xv[4], wv[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            xv[u] = row_load<kWide>(x, c0 + 4 * (lane + kWave * u), dim);
+            wv[u] = row_load<kWide>(w, c0 + 4 * (lane + kWave * u), dim);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int c = c0 + 4 * (lane + kWave * u);
+            if (c0 + 4 * kWave * (u + 1) > dim) {      // uniform
+              row_tail<kWide>(xv[u], c, dim);
+              row_tail<kWide>(wv[u], c, dim);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const double t = (double)xv[u][e] - (double)wv[u][e];
+              s += t * t;
+            }
+          }
+        }
+        d2 = wave_sum(s);
       }
       d = sqrt(d2);
     }
@@ -778,7 +808,39 @@ __global__ __launch_bounds__(256) void k_bmu_distances(const float *__restrict__
   }
   if (lane == 0) wave_total[wave] = total;
   __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = (wave_total[0] + wave_total[1]) + (wave_total[2] + wave_total[3]);
+  if (threadIdx.x == 0) {
+    double t = wave_total[0];
+    for (int w = 1; w < kWaves; ++w) t += wave_total[w];
+    partial[blockIdx.x] = t;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_mark_nodes(const int32_t *__restrict__ bmus, int64_t n, int k, int32_t mark,
+                                                    int32_t *__restrict__ flag) {
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (j < n && (unsigned)bmus[j] < (unsigned)k) flag[bmus[j]] = mark;
+}
+
+__global__ __launch_bounds__(256) void k_marked_norms(const float *__restrict__ W, int k, int dim, int32_t mark,
+                                                      const int32_t *__restrict__ flag, double *__restrict__ wn64) {
+  __shared__ double s_part[4];
+  for (int i = blockIdx.x; i < k; i += gridDim.x) {
+    if (flag[i] != mark) continue;               // uniform
+    const float *w = W + (int64_t)i * dim;
+    double s[4] = {0, 0, 0, 0};
+    for (int c0 = 0; c0 < dim; c0 += 8 * 256) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = w[min(c0 + 256 * u + (int)threadIdx.x, dim - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s[u & 3] += c0 + 256 * u + (int)threadIdx.x < dim ? (double)v[u] * (double)v[u] : 0.0;
+    }
+    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) wn64[i] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
+    __syncthreads();
+  }
 }
 
 __global__ __launch_bounds__(64) void k_mean_of_partials(const double *__restrict__ partial, int count, int64_t n,
@@ -789,28 +851,39 @@ __global__ __launch_bounds__(64) void k_mean_of_partials(const double *__restric
   if (threadIdx.x == 0) *out = n > 0 ? s / (double)n : 0.0;
 }
 
-hipError_t launch_bmu_distances_on(hipStream_t stream, const float *X, const int64_t *indptr, const int32_t *indices,
-                                   const float *values, int64_t n, const float *W, int k, int dim,
-                                   const int32_t *bmus, float *dist, double *qerror, double *partial) {
-  int blocks = (int)((n + 3) / 4);
+static int distance_blocks(int64_t n) {
+  int64_t blocks = (n + kDistThreads / kWave - 1) / (kDistThreads / kWave);
   if (blocks > kDistBlocks) blocks = kDistBlocks;
-  if (blocks < 1) blocks = 1;
-  if (X)
-    hipLaunchKernelGGL(k_bmu_distances<false>, dim3(blocks), dim3(256), 0, stream, X, nullptr, nullptr, nullptr, W,
-                       n, k, dim, bmus, dist, partial);
+  return blocks < 1 ? 1 : (int)blocks;
+}
+
+// Dense rows (no context needed).
+hipError_t launch_bmu_distances_on(hipStream_t stream, const float *X, int64_t n, const float *W, int k, int dim,
+                                   const int32_t *bmus, float *dist, double *qerror, double *partial) {
+  const int blocks = distance_blocks(n);
+  if (dim >= 4)
+    hipLaunchKernelGGL((k_bmu_distances<false, true>), dim3(blocks), dim3(kDistThreads), 0, stream, X, nullptr, nullptr,
+                       nullptr, W, nullptr, n, k, dim, bmus, dist, partial);
   else
-    hipLaunchKernelGGL(k_bmu_distances<true>, dim3(blocks), dim3(256), 0, stream, nullptr, indptr, indices, values,
-                       W, n, k, dim, bmus, dist, partial);
-  if (qerror)
-    hipLaunchKernelGGL(k_mean_of_partials, dim3(1), dim3(64), 0, stream, partial, blocks, n, qerror);
+    hipLaunchKernelGGL((k_bmu_distances<false, false>), dim3(blocks), dim3(kDistThreads), 0, stream, X, nullptr, nullptr,
+                       nullptr, W, nullptr, n, k, dim, bmus, dist, partial);
+  if (qerror) hipLaunchKernelGGL(k_mean_of_partials, dim3(1), dim3(64), 0, stream, partial, blocks, n, qerror);
   return hipGetLastError();
 }
 
 hipError_t launch_bmu_distances(som_ctx *c, const float *X, const int64_t *indptr, const int32_t *indices,
                                 const float *values, int64_t n, const float *W, const int32_t *bmus, float *dist,
                                 double *qerror) {
-  return launch_bmu_distances_on(c->stream, X, indptr, indices, values, n, W, c->k, c->dim, bmus, dist, qerror,
-                                 c->dist_partial);
+  if (X) return launch_bmu_distances_on(c->stream, X, n, W, c->k, c->dim, bmus, dist, qerror, c->dist_partial);
+  hipLaunchKernelGGL(k_mark_nodes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, bmus, n, c->k, c->dist_call,
+                     c->dist_flag);
+  hipLaunchKernelGGL(k_marked_norms, dim3(c->k < c->n_cu * 16 ? c->k : c->n_cu * 16), dim3(256), 0, c->stream, W, c->k, c->dim,
+                     c->dist_call, c->dist_flag, c->wn64);
+  const int blocks = distance_blocks(n);
+  hipLaunchKernelGGL((k_bmu_distances<true, false>), dim3(blocks), dim3(kDistThreads), 0, c->stream, nullptr, indptr, indices,
+                     values, W, c->wn64, n, c->k, c->dim, bmus, dist, c->dist_partial);
+  if (qerror) hipLaunchKernelGGL(k_mean_of_partials, dim3(1), dim3(64), 0, c->stream, c->dist_partial, blocks, n, qerror);
+  return hipGetLastError();
 }
 
 hipError_t launch_rescan_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,

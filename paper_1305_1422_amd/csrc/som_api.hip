@@ -90,6 +90,9 @@ static bool direct_search(const som_ctx *c, int64_t n) { return c->filter == SOM
 // The dense filter runs on fp16 planes (one-level split pass or the two-level search).
 static bool uses_planes(const som_ctx *c) { return c->filter != SOM_FILTER_FP32; }
 
+// The fp32 filter and long rows go through a centred copy of the code book.
+static bool needs_centred_copy(const som_ctx *c) { return !uses_planes(c) || c->dim > kPlaneMaxDim; }
+
 // Two-level search for n instances?  Asked for outright, or by default when the map has enough node
 // blocks for the coarse pass to leave most of them out; never when its table of block minima would
 // not be a modest share of the device memory.
@@ -144,7 +147,7 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
   const bool split = dense && filtered && uses_planes(c);
   // sized for the rows the scratch is (or will be) allocated for, so that it serves every n up to n_cap
   const bool coarse = split && two_level(c, n > c->n_cap ? n : c->n_cap);
-  const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && c->Wc == nullptr) ||
+  const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) ||
                             (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
                             (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr));
@@ -176,7 +179,7 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
     if (!dev_alloc(&c->collect_list, (size_t)c->n_cap * kListCap))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate candidate lists for %lld instances", (long long)c->n_cap);
   }
-  if (dense && filtered && c->Wc == nullptr) {
+  if (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) {
     if (!dev_alloc(&c->Wc, (size_t)c->k * c->dim))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the centred code book (%d x %d)", c->k, c->dim);
   }
@@ -321,18 +324,18 @@ static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, 
     c->d_split_valid = 0;
     c->csrd_valid = 0;          // the planes are about to hold other rows
     SOM_LAUNCH(c, launch_sample_col_means(c, X, n, c->dim, c->mu));
-    SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
-    SOM_LAUNCH(c, launch_row_sqnorms(c, X, n, c->dim, split ? c->mu : nullptr, c->xn32, nullptr, nullptr));
+    if (!split) {               // (the bound of centred instances has no term in |mu|)
+      SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
+      SOM_LAUNCH(c, launch_row_sqnorms(c, X, n, c->dim, nullptr, c->xn32, nullptr, nullptr));
+    }
   }
   if (split && !(have_xn && c->d_split_valid)) {
-    SOM_LAUNCH(c, launch_split_rows_f16(c, X, n, nullptr, c->mu, c->Xh, c->xscale, 0, coarse ? c->Xh1 : nullptr));
+    SOM_LAUNCH(c, launch_instance_planes(c, X, n, c->mu, c->Xh, c->xscale, coarse ? c->Xh1 : nullptr, c->xn32));
     c->d_split_valid = have_xn ? 1 : 0;
   }
-  SOM_LAUNCH(c, launch_center_codebook(c, W, true, false, split));
+  if (split) SOM_LAUNCH(c, launch_codebook_planes(c, W, false, coarse));
+  else SOM_LAUNCH(c, launch_center_codebook(c, W, true, false, false));
   if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
-  if (split)
-    SOM_LAUNCH(c, launch_split_rows_f16(c, c->Wc, c->k, c->wmax_bits + 1, nullptr, c->Wh, c->wscale, 0,
-                                        coarse ? c->Wh1 : nullptr));
   return SOM_OK;
 }
 
@@ -457,10 +460,8 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
     StageTimer t(c, 5);
     rc = begin_search(c);
     if (rc) return rc;
-    SOM_LAUNCH(c, launch_center_codebook(c, W, true, true /* |w|^2 in fp64 for the sparse exact kernels */, true));
+    SOM_LAUNCH(c, launch_codebook_planes(c, W, true /* |w|^2 in fp64 for the sparse exact kernels */, coarse));
     if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
-    SOM_LAUNCH(c, launch_split_rows_f16(c, c->Wc, c->k, c->wmax_bits + 1, nullptr, c->Wh, c->wscale, 0,
-                                        coarse ? c->Wh1 : nullptr));
   }
   {
     StageTimer t(c, 1);
@@ -539,10 +540,11 @@ static int registered_norms(som_ctx *c) {
   if (c->d_norms_valid) return SOM_OK;
   if (c->data_kind == 1) {
     SOM_LAUNCH(c, launch_sample_col_means(c, c->d_data, c->d_n, c->dim, c->mu));
-    SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
-    // the split-fp16 filter works on centred instances, and its margin on their norms
-    SOM_LAUNCH(c, launch_row_sqnorms(c, c->d_data, c->d_n, c->dim, uses_planes(c) ? c->mu : nullptr,
-                                     c->xn32, nullptr, nullptr));
+    c->d_split_valid = 0;      // the filters on planes get the norms of the centred rows with their planes
+    if (!uses_planes(c)) {
+      SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
+      SOM_LAUNCH(c, launch_row_sqnorms(c, c->d_data, c->d_n, c->dim, nullptr, c->xn32, nullptr, nullptr));
+    }
   } else {
     SOM_LAUNCH(c, launch_csr_row_sqnorms(c, c->d_indptr, c->d_values, c->d_n, c->xn32));
   }
@@ -656,10 +658,9 @@ static int registered_csr_dense(som_ctx *c) {
   for (int64_t r0 = 0; r0 < n && rcl == SOM_OK; r0 += batch) {
     const int64_t rows = n - r0 < batch ? n - r0 : batch;
     hipError_t e = launch_csr_densify(c, c->d_indptr, c->d_indices, c->d_values, r0, rows, dense);
-    if (e == hipSuccess) e = launch_row_sqnorms(c, dense, rows, c->dim, c->csrd_mu, c->csrd_xn + r0, nullptr, nullptr);
     if (e == hipSuccess)
-      e = launch_split_rows_f16(c, dense, rows, nullptr, c->csrd_mu, c->Xh + (size_t)r0 * row_halves, c->xscale + r0, 0,
-                                coarse ? c->Xh1 + (size_t)r0 * row_halves1 : nullptr);
+      e = launch_instance_planes(c, dense, rows, c->csrd_mu, c->Xh + (size_t)r0 * row_halves, c->xscale + r0,
+                                 coarse ? c->Xh1 + (size_t)r0 * row_halves1 : nullptr, c->csrd_xn + r0);
     if (e != hipSuccess) rcl = dev_fail(c, e, "dense planes of the sparse rows");
   }
   hipError_t es = hipStreamSynchronize(c->stream);     // the batch buffer is freed below
@@ -725,7 +726,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   const size_t images = grid_type == SOM_GRID_HEXAGONAL ? 2 : 1;
   bool ok = dev_alloc(&c->wn32, (K + 127) / 128 * 128) && dev_alloc(&c->wn64, K) &&
             dev_alloc(&c->counts, K + 1) && dev_alloc(&c->group_local, 2 * (K + (K + 63) / 64)) && dev_alloc(&c->seg_off, K + 1) && dev_alloc(&c->chunk_off, K + 1) &&
-            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
+            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->dist_flag, K) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
             dev_alloc(&c->gy, (size_t)rows) && dev_alloc(&c->params, 1) && dev_alloc(&c->list_counts, kListWords) &&
             dev_alloc(&c->mu, (size_t)dim) && dev_alloc(&c->mu_partial, (size_t)64 * dim) &&
             dev_alloc(&c->zero16, 16) && dev_alloc(&c->mu_norm2, 1) && dev_alloc(&c->wscale, 1) &&
@@ -746,6 +747,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   c->hot_wmax_bits = c->wmax_bits + 3;
   hipError_t e = launch_fill_zero_u32(c->stream, c->list_counts, kListWords);
   if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->zero16, 16);
+  if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->dist_flag, c->k);
   if (e == hipSuccess && K % 128 != 0) {       // the tail of the node constants past k stays +inf for good
     float inf[128];
     for (int i = 0; i < 128; ++i) inf[i] = INFINITY;
@@ -768,7 +770,7 @@ void som_destroy(som_ctx *c) {
   free_row_scratch(c);
   if (c->direct_rec) (void)hipFree(c->direct_rec);
   dev_free(c->wn32); dev_free(c->wn64); dev_free(c->counts); dev_free(c->group_local); dev_free(c->seg_off);
-  dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->row_hash); dev_free(c->dedup_keys);
+  dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->dist_flag); dev_free(c->row_hash); dev_free(c->dedup_keys);
   dev_free(c->dedup_lowest); dev_free(c->cntT); dev_free(c->gx); dev_free(c->gy);
   dev_free(c->params); dev_free(c->list_counts); dev_free(c->unit_work); dev_free(c->vq); dev_free(c->S); dev_free(c->T); dev_free(c->Wt); dev_free(c->Wt32);
   dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial); dev_free(c->H2);
@@ -837,6 +839,10 @@ int som_bmu_distances_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (!distances && !qerror) return fail(c, SOM_ERR_INVALID_ARG, "distances and qerror are both NULL");
   const int rc = check_csr(c, indptr, indices, values, n, nnz);
   if (rc) return rc;
+  if (++c->dist_call == 0x7fffffff) {           // call numbers start over: none of the marks left may match them
+    SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->dist_flag, c->k));
+    c->dist_call = 1;
+  }
   SOM_LAUNCH(c, launch_bmu_distances(c, nullptr, indptr, indices, values, n, codebook, bmus, distances, qerror));
   return SOM_OK;
 }
@@ -851,8 +857,7 @@ int som_bmu_distances_dense_static(const float *data, int64_t n, int dim, const 
   hipError_t e = hipSuccess;
   double *partial = static_scratch(&e);
   if (!partial) return dev_fail(nullptr, e, "address of the static scratch");
-  e = launch_bmu_distances_on((hipStream_t)hip_stream, data, nullptr, nullptr, nullptr, n, codebook, n_nodes, dim,
-                              bmus, distances, qerror, partial);
+  e = launch_bmu_distances_on((hipStream_t)hip_stream, data, n, codebook, n_nodes, dim, bmus, distances, qerror, partial);
   if (e != hipSuccess) return dev_fail(nullptr, e, "som_bmu_distances_dense_static");
   return SOM_OK;
 }

@@ -101,6 +101,8 @@ struct som_ctx {
   int32_t *seg_off;       // [k+1] exclusive scan of counts
   int32_t *chunk_off;     // [k+1] exclusive scan of chunks per node
   double *massD;          // [k] neighbourhood mass per node
+  int32_t *dist_flag;     // [k] call number of the last som_bmu_distances_csr that met the node
+  int32_t dist_call;
   double *dist_partial;   // [1024] per-workgroup sums of the distances to the BMUs
   uint64_t *row_hash;     // [k] hashes of the code-book rows (bubble neighbourhood only, lazily allocated)
   uint64_t *dedup_keys;   // [dedup_slots] open-addressing table of those hashes
@@ -289,6 +291,10 @@ hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, cons
                                  const float *mu /* subtracted first, or null */, _Float16 *out, float *scale_out,
                                  int dim = 0 /* row length; 0: the context's */,
                                  _Float16 *out_hi = nullptr /* the hi halves alone, rows padded to 64 columns */);
+constexpr int kPlaneMaxDim = 2048;       // rows up to this length are prepared in registers (no centred copy Wc of the code book)
+hipError_t launch_codebook_planes(som_ctx *c, const float *W, bool want_wn64, bool coarse);      // -> wn32, wmax_bits, Wh, wscale (wn64, Wh1)
+hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, const float *mu, _Float16 *out, float *scale_out,
+                                  _Float16 *out_hi, float *norm_out);
 hipError_t launch_probe_mfma_f16(hipStream_t stream, const uint16_t *A, const uint16_t *B, const float *C, float *D,
                                  int count);
 
@@ -325,10 +331,9 @@ hipError_t launch_rescan_csr(som_ctx *c, const int64_t *indptr, const int32_t *i
 
 // Workgroups of the distance kernel = partial sums it leaves (and the capacity of every buffer for them).
 constexpr int kDistBlocks = 1024;
-hipError_t launch_bmu_distances_on(hipStream_t stream, const float *X, const int64_t *indptr, const int32_t *indices,
-                                   const float *values, int64_t n, const float *W, int k, int dim,
+hipError_t launch_bmu_distances_on(hipStream_t stream, const float *X, int64_t n, const float *W, int k, int dim,
                                    const int32_t *bmus, float *dist, double *qerror,
-                                   double *partial /* [kDistBlocks] device scratch */);
+                                   double *partial /* [kDistBlocks] device scratch */);      // dense rows
 hipError_t launch_bmu_distances(som_ctx *c, const float *X, const int64_t *indptr, const int32_t *indices,
                                 const float *values, int64_t n, const float *W, const int32_t *bmus, float *dist,
                                 double *qerror);     // X != NULL: dense rows, else CSR

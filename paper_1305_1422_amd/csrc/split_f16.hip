@@ -14,6 +14,7 @@
 // shape of one LDS tile row of the filter kernel (bmu_dense_h.hip).  Padding columns are zero.
 // The coarse pass of the two-level search reads the hi halves alone: a second copy, rows padded to
 // whole chunks of 64 columns, 128 bytes per chunk again.
+#include "row_load.hpp"
 #include "som_internal.hpp"
 
 #include <math.h>
@@ -85,6 +86,189 @@ __global__ __launch_bounds__(256) void k_split_rows_f16(const float *__restrict_
       for (int c = padded + tl; c < padded_hi; c += kTeam) out_hi[r * (int64_t)padded_hi + c] = (_Float16)0.f;
     }
   }
+}
+
+// ---------------------------------------------------------------- rows of up to 2,048 features: held in registers
+// A wavefront keeps a whole row in registers (R groups of four features per lane, all loads in flight at once), so the
+// centred row's norm, its scale and its planes come from one read, where norms and planes used to read the instances
+// three times (100,000 x 1,000 unregistered instances, three planes: 115 + 350 us -> 185, 1 GB at 5.4 TB/s).  The centring vector
+// stays in registers over all rows of a wavefront.
+constexpr int kPlaneThreads = 1024;
+
+// c_i = |w'_i|^2 (the instances are centred too), optionally |w_i|^2 in fp64, the largest |w'_i|^2 and
+// the largest |w'| element, w' = fl(w - mu): fp64 sums in a fixed order per row.  One pair of atomics per workgroup of
+// sixteen wavefronts (an atomic on one address takes about 10 ns, whoever issues it; 2,500 x 1,000: 20 -> 9 us).
+template <int R>
+__global__ __launch_bounds__(kPlaneThreads) void k_node_stats(const float *__restrict__ W, int k, int dim,
+                                                              const float *__restrict__ mu, float *__restrict__ cn,
+                                                              unsigned *__restrict__ max_bits, double *__restrict__ wn64) {
+  __shared__ float s_max[2][kPlaneThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int stride = gridDim.x * (kPlaneThreads / 64);
+  const bool wide = dim >= 4;
+  f32x4r m[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int c = 4 * (lane + 64 * r);
+    m[r] = wide ? row_load<true>(mu, c, dim) : row_load<false>(mu, c, dim);
+    if (wide) row_tail<true>(m[r], c, dim); else row_tail<false>(m[r], c, dim);
+  }
+  float vmax = 0.f, amax = 0.f;
+  for (int i = blockIdx.x * (kPlaneThreads / 64) + wave; i < k; i += stride) {
+    const float *w = W + (int64_t)i * dim;
+    f32x4r x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = wide ? row_load<true>(w, 4 * (lane + 64 * r), dim) : row_load<false>(w, 4 * (lane + 64 * r), dim);
+    double s2 = 0.0, sw = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (wide) row_tail<true>(x[r], 4 * (lane + 64 * r), dim); else row_tail<false>(x[r], 4 * (lane + 64 * r), dim);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float t = x[r][e] - m[r][e];
+        amax = fmaxf(amax, fabsf(t));
+        s2 += (double)t * (double)t;
+        sw += (double)x[r][e] * (double)x[r][e];
+      }
+    }
+    s2 = wave_sum(s2);
+    if (wn64) sw = wave_sum(sw);
+    vmax = fmaxf(vmax, (float)s2);
+    if (lane == 0) {
+      cn[i] = (float)s2;
+      if (wn64) wn64[i] = sw;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+  if (lane == 0) { s_max[0][wave] = vmax; s_max[1][wave] = amax; }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    float v = 0.f;
+    for (int w = 0; w < kPlaneThreads / 64; ++w) v = fmaxf(v, s_max[threadIdx.x][w]);
+    if (v > 0.f) atomicMax(max_bits + threadIdx.x, __float_as_uint(v));
+  }
+}
+
+// The planes of a row, its scale and (instances) the squared norm of the centred row.  global_max_bits as in
+// k_split_rows_f16.  Bound by memory: it reads 4 and writes 4 to 6 bytes per element.
+template <int R>
+__global__ __launch_bounds__(256) void k_row_planes(const float *__restrict__ A, int64_t nrows, int dim, int nK,
+                                                    const unsigned *__restrict__ global_max_bits,
+                                                    const float *__restrict__ mu, _Float16 *__restrict__ out,
+                                                    float *__restrict__ scale_out, _Float16 *__restrict__ out_hi,
+                                                    float *__restrict__ norm_out) {
+  typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63;
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  const bool wide = dim >= 4;
+  const int padded = nK * 32, padded_hi = (nK + 1) / 2 * 64;
+  f32x4r m[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int c = 4 * (lane + 64 * r);
+    m[r] = wide ? row_load<true>(mu, c, dim) : row_load<false>(mu, c, dim);
+    if (wide) row_tail<true>(m[r], c, dim); else row_tail<false>(m[r], c, dim);
+  }
+  for (int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); j < nrows; j += stride) {
+    const float *a = A + j * dim;
+    f32x4r x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = wide ? row_load<true>(a, 4 * (lane + 64 * r), dim) : row_load<false>(a, 4 * (lane + 64 * r), dim);
+    float top = 0.f;
+    double s = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (wide) row_tail<true>(x[r], 4 * (lane + 64 * r), dim); else row_tail<false>(x[r], 4 * (lane + 64 * r), dim);
+      x[r] -= m[r];                              // fp32 difference, as the planes hold it
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        top = fmaxf(top, fabsf(x[r][e]));
+        s += (double)x[r][e] * (double)x[r][e];
+      }
+    }
+    if (global_max_bits) {
+      top = __uint_as_float(*global_max_bits);
+    } else {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, 64));
+    }
+    float inv;
+    const float scale = pow2_above(top, &inv);
+    if (norm_out) s = wave_sum(s);
+    if (lane == 0) {
+      if (!global_max_bits) scale_out[j] = scale;
+      else if (j == 0) *scale_out = scale;
+      if (norm_out) norm_out[j] = (float)s;
+    }
+    _Float16 *o = out + j * (int64_t)nK * 64;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = 4 * (lane + 64 * r);
+      f16x4 hi, lo;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = x[r][e] * inv;
+        hi[e] = (_Float16)v;
+        lo[e] = (_Float16)(v - (float)hi[e]);
+      }
+      if (c < padded) {
+        _Float16 *at = o + (c >> 5) * 64 + (c & 31);
+        *reinterpret_cast<f16x4 *>(at) = hi;
+        *reinterpret_cast<f16x4 *>(at + 32) = lo;
+      }
+      if (out_hi && c < padded_hi) *reinterpret_cast<f16x4 *>(out_hi + j * (int64_t)padded_hi + c) = hi;
+    }
+  }
+}
+
+static bool rows_fit_registers(const som_ctx *c) { return c->dim <= kPlaneMaxDim; }
+
+#define SOM_BY_ROW_GROUPS(dim, CALL)                                   \
+  do {                                                                 \
+    const int groups_ = ((dim) + 255) / 256;                           \
+    if (groups_ <= 1) { CALL(1); } else if (groups_ <= 2) { CALL(2); } \
+    else if (groups_ <= 4) { CALL(4); } else { CALL(8); }              \
+  } while (0)
+
+static hipError_t launch_row_planes(som_ctx *c, const float *A, int64_t nrows, const unsigned *global_max_bits, const float *mu,
+                                    _Float16 *out, float *scale_out, _Float16 *out_hi, float *norm_out) {
+  int64_t blocks = (nrows + 3) / 4;
+  const int64_t cap = (int64_t)c->n_cu * 16;
+  if (blocks > cap) blocks = cap;
+#define SOM_ROW_PLANES(R)                                                                                                \
+  hipLaunchKernelGGL(k_row_planes<R>, dim3((unsigned)blocks), dim3(256), 0, c->stream, A, nrows, c->dim, (c->dim + 31) / 32, \
+                     global_max_bits, mu, out, scale_out, out_hi, norm_out)
+  SOM_BY_ROW_GROUPS(c->dim, SOM_ROW_PLANES);
+#undef SOM_ROW_PLANES
+  return hipGetLastError();
+}
+
+// Centred code book for the filters that run on planes: node constants, maxima, planes and scale.
+hipError_t launch_codebook_planes(som_ctx *c, const float *W, bool want_wn64, bool coarse) {
+  _Float16 *hi = coarse ? c->Wh1 : nullptr;
+  if (!rows_fit_registers(c)) {
+    hipError_t e = launch_center_codebook(c, W, true, want_wn64, true);
+    if (e != hipSuccess) return e;
+    return launch_split_rows_f16(c, c->Wc, c->k, c->wmax_bits + 1, nullptr, c->Wh, c->wscale, 0, hi);
+  }
+  int blocks = (c->k + kPlaneThreads / 64 - 1) / (kPlaneThreads / 64);
+  if (blocks > c->n_cu) blocks = c->n_cu;
+#define SOM_NODE_STATS(R)                                                                                            \
+  hipLaunchKernelGGL(k_node_stats<R>, dim3(blocks), dim3(kPlaneThreads), 0, c->stream, W, c->k, c->dim, c->mu, c->wn32, \
+                     c->wmax_bits, want_wn64 ? c->wn64 : nullptr)
+  SOM_BY_ROW_GROUPS(c->dim, SOM_NODE_STATS);
+#undef SOM_NODE_STATS
+  return launch_row_planes(c, W, c->k, c->wmax_bits + 1, c->mu, c->Wh, c->wscale, hi, nullptr);
+}
+
+// Planes, scales and squared norms of centred instances.
+hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, const float *mu, _Float16 *out, float *scale_out,
+                                  _Float16 *out_hi, float *norm_out) {
+  if (rows_fit_registers(c)) return launch_row_planes(c, A, nrows, nullptr, mu, out, scale_out, out_hi, norm_out);
+  hipError_t e = launch_row_sqnorms(c, A, nrows, c->dim, mu, norm_out, nullptr, nullptr);
+  if (e != hipSuccess) return e;
+  return launch_split_rows_f16(c, A, nrows, nullptr, mu, out, scale_out, 0, out_hi);
 }
 
 hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, const unsigned *global_max_bits,
