@@ -342,9 +342,9 @@ int som_set_smoothing(som_ctx *ctx, int form);
  *                  fp32-grade scores at several times the fp32 matrix rate; needs 4 bytes per
  *                  element of extra device memory for instances and code book.
  *   SOM_FILTER_TWO_LEVEL  a coarse pass with ONE fp16 product per feature (the hi halves alone) finds, per
- *                  instance and block of 128 nodes, the smallest coarse score; the blocks that cannot
+ *                  instance and block of 128 neighbouring nodes, the smallest coarse score; the blocks that cannot
  *                  hold the BMU by the proven bound of those scores are dropped, the instances are
- *                  ordered by their best block, and the split-fp16 pass runs over the remaining
+ *                  ordered by the blocks they have left, and the split-fp16 pass runs over the remaining
  *                  (128 instances, block) pairs only.  Needs 6 bytes per element of extra device memory
  *                  and 4 bytes per instance and node block.
  *   SOM_FILTER_AUTO (default)  small searches run without any filter pass, all distances in fp64 on the
@@ -365,7 +365,8 @@ int som_set_filter(som_ctx *ctx, int filter);
  *   c_i = |w'_i|^2 + 2 mu . w'_i  (the sparse sweep multiplies with a 16-bit quantisation of w');
  *   mu_out [dim]    the centring vector mu that was used;
  *   margin_out [n]  fp64: the margin the exact stage applies to instance j - two scores of j whose
- *                   difference exceeds it are taken as decided - evaluated by the same device
+ *                   difference exceeds it are taken as decided (SOM_FILTER_TWO_LEVEL: its coarse pass,
+ *                   see som_debug_select_margins) - evaluated by the same device
  *                   function on the same inputs.  It is meant to cover the error of both scores.
  * All pointers are device pointers; scores must hold n * rows*cols floats.  A test compares the
  * scores with their exact values and checks that no error exceeds half the margin.
@@ -376,6 +377,15 @@ int som_debug_scores_dense(som_ctx *ctx, const float *data, int64_t n, const flo
 int som_debug_scores_csr(som_ctx *ctx, const int64_t *indptr, const int32_t *indices, const float *values,
                          int64_t n, int64_t nnz, const float *codebook, float *scores, float *mu_out,
                          double *margin_out);
+
+/*
+ * som_debug_select_margins - test hook: margin_out [n] (fp64, device) = the margins the block selection of the
+ * two-level search applies to the coarse scores of the n instances that the preceding som_debug_scores_dense
+ * wrote under SOM_FILTER_TWO_LEVEL.  Its margin_out bounds the errors of those scores for any rows; this one is
+ * made of what these rows lose to the rounding to 11 bits, and is smaller.
+ * Errors: NULL pointers, no such preceding call with this n -> SOM_ERR_INVALID_ARG.
+ */
+int som_debug_select_margins(som_ctx *ctx, int64_t n, double *margin_out);
 
 /*
  * som_debug_mfma_f16 - test hook (not an operation of the paper): `count` independent

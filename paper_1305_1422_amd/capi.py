@@ -31,7 +31,7 @@ EXPORTS = [
     "som_bmu_distances_dense", "som_bmu_distances_csr", "som_bmu_distances_dense_static",
     "som_cool_schedule", "som_umatrix", "som_get_stats", "som_two_level_stats",
     "som_profile_enable", "som_profile_read",
-    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_mfma_f16", "som_debug_xcc_ids",
+    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_mfma_f16", "som_debug_xcc_ids",
 ]
 PROFILE_STAGES = ("bmu_dense_filter", "bmu_csr_filter", "bmu_exact", "node_sums", "smooth_divide", "prepare_dense")
 
@@ -116,6 +116,8 @@ def load():
     L.som_set_filter.argtypes = [vp, i32]
     L.som_set_neighborhood.restype = i32
     L.som_set_neighborhood.argtypes = [vp, i32, i32]
+    L.som_debug_select_margins.restype = i32
+    L.som_debug_select_margins.argtypes = [vp, i64, vp]
     L.som_debug_scores_dense.restype = i32
     L.som_debug_scores_dense.argtypes = [vp, vp, i64, vp, vp, vp, vp]
     L.som_debug_scores_csr.restype = i32
@@ -364,6 +366,12 @@ def som_set_smoothing(ctx, form: int) -> None:
 
 def som_set_filter(ctx, filter: int) -> None:
     _check(ctx, load().som_set_filter(ctx, filter))
+
+
+def som_debug_select_margins(ctx, margin_out) -> None:
+    """Test hook: the margins of the block selection for the coarse scores of the preceding som_debug_scores_dense."""
+    import torch
+    _check(ctx, load().som_debug_select_margins(ctx, margin_out.shape[0], _ptr(margin_out, torch.float64, "margin_out")))
 
 
 def som_debug_scores_dense(ctx, data, codebook, scores, mu_out, margin_out) -> None:

@@ -50,14 +50,15 @@ __device__ __forceinline__ void load4_to_lds_c(const void *base, unsigned lane_o
 __device__ __forceinline__ f16x8 as_halves_c(f32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
 // kDump = false: block_min[node block of 128][instance] = smallest score of the pair.
-// kDump = true (test hook): every score to dump[instance * k + node].
+// kDump = true (test hook): every score to dump[instance * k + node]; the rows of Wh are nodes node_of[0], node_of[1], ...
 // wc: node constants c_i, readable for i < k_const (a multiple of 128 >= k, +inf past k).
 template <bool kDump>
 __global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(const float *__restrict__ Xh, const float *__restrict__ Wh,
                                                              const float *__restrict__ wc, int k_const,
                                                              const float *__restrict__ xscale,
                                                              const float *__restrict__ wscale, int64_t n, int k,
-                                                             int nK, int groups, float *__restrict__ out) {
+                                                             int nK, int groups, float *__restrict__ out,
+                                                             const int32_t *__restrict__ node_of) {
   __shared__ __attribute__((aligned(16))) float sW[2][kCTN * kCRow];
   __shared__ __attribute__((aligned(16))) float sX[2][kCTI * kCRow];
   __shared__ float sWn[2][kCTN];     // node constants of the node tiles in flight, by parity of the tile's ordinal
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(const float *__rest
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) {
               const int64_t inst = inst0 + wi * 64 + ni * 32 + l32;
-              if (node < k && inst < n) out[inst * k + node] = fmaf(factor[ni], acc[mi][ni][v], swn[nl]);
+              if (node < k && inst < n) out[inst * k + node_of[node]] = fmaf(factor[ni], acc[mi][ni][v], swn[nl]);
             }
           }
       } else {
@@ -284,10 +285,10 @@ hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump) {
   const float *Wh = reinterpret_cast<const float *>(c->Wh1);
   if (dump)
     hipLaunchKernelGGL((k_bmu_coarse<true>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, Xh, Wh, c->wn32,
-                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, dump);
+                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, dump, c->node_of);
   else
     hipLaunchKernelGGL((k_bmu_coarse<false>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, Xh, Wh, c->wn32,
-                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, c->coarse_min);
+                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, c->coarse_min, c->node_of);
   return hipGetLastError();
 }
 

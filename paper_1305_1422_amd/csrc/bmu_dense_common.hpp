@@ -55,14 +55,15 @@ __device__ __forceinline__ int mfma_row(int mi, int v, int lhi) { return mi * 32
 // Scores of one node block, s = c_i + factor * dot (factor = -2, times the operand scales where
 // the operands were scaled): push into the running lists (filter mode) or append the nodes under
 // the per-instance threshold to the collected lists (collect mode).  `tot` is cleared.  With `dump`
-// (filter mode, test hook) the scores of the first n_dump instances are also written out.
+// (filter mode, test hook) the scores of the first n_dump instances are also written out.  node_of: the nodes are
+// counted in another order than the map's.
 template <bool kCollect>
 __device__ __forceinline__ void consume_scores(f32x16 (&tot)[2][2], const float *__restrict__ swn, int node0, int k,
                                                int wm, int lhi, const float (&factor)[2], Top2 (&top)[2],
                                                const float (&lim)[2],
                                                const int64_t (&slot_of)[2], int32_t *__restrict__ cnt,
                                                int32_t *__restrict__ list, float *__restrict__ dump = nullptr,
-                                               int64_t n_dump = 0) {
+                                               int64_t n_dump = 0, const int32_t *__restrict__ node_of = nullptr) {
   if (!kCollect && dump) {
     // test hook: every score of the block goes to dump[instance][node] as well (tot is read, not cleared)
 #pragma unroll
@@ -89,7 +90,7 @@ __device__ __forceinline__ void consume_scores(f32x16 (&tot)[2][2], const float 
           const float s = fmaf(factor[ni], tot[mi][ni][v], wnv);
           if (s <= lim[ni] && node < k) {
             const int pos = atomicAdd(&cnt[slot_of[ni]], 1);
-            if (pos < kListCap) list[slot_of[ni] * kListCap + pos] = node;
+            if (pos < kListCap) list[slot_of[ni] * kListCap + pos] = node_of ? node_of[node] : node;
           }
           tot[mi][ni][v] = 0.f;
         }
@@ -134,11 +135,12 @@ __device__ __forceinline__ void consume_scores(f32x16 (&tot)[2][2], const float 
 // into kCand candidates plus the smallest dropped score, and store them.  TI = instances per
 // tile; mval/midx: LDS scratch of TI*4*3 floats and TI*4*2 ints that no wavefront reads any more.
 // With `rows` the tile is positions inst0 .. of that index list and the lists are stored under the
-// instances' own numbers.
+// instances' own numbers, with node_of the nodes under theirs.
 template <int TI>
 __device__ __forceinline__ void merge_and_store(const Top2 (&top)[2], float *mval, int *midx, int tid, int wm, int wi,
                                                 int l32, int lhi, int64_t inst0, int64_t n, int64_t group,
-                                                CandView out, const int32_t *__restrict__ rows = nullptr) {
+                                                CandView out, const int32_t *__restrict__ rows = nullptr,
+                                                const int32_t *__restrict__ node_of = nullptr) {
 #pragma unroll
   for (int ni = 0; ni < 2; ++ni) {
     const int il = wi * 64 + ni * 32 + l32;
@@ -182,7 +184,7 @@ __device__ __forceinline__ void merge_and_store(const Top2 (&top)[2], float *mva
 #pragma unroll
     for (int t = 0; t < kCand; ++t) {
       out.val[j * kCand + t] = v[t];
-      out.idx[j * kCand + t] = id[t];
+      out.idx[j * kCand + t] = node_of && id[t] >= 0 ? node_of[id[t]] : id[t];
     }
     out.over[j] = ov;
   }

@@ -80,7 +80,8 @@ __device__ __forceinline__ f16x8 as_halves(f32x4 v) { return __builtin_bit_cast(
 // same sets of candidate blocks), and the workgroups of tile t share out the tcnt[t] node blocks listed,
 // ascending, in tlist[t * blocks of the map ..] instead of all of them; candidates are stored under the
 // instances' own numbers.  Collect mode takes such lists too (for the tiles of ITS index list) when the
-// search ran in two levels: a node outside the blocks listed for an instance cannot be its BMU.
+// search ran in two levels: a node outside the blocks listed for an instance cannot be its BMU.  The two-level
+// search counts the nodes in an order of its own: row p of Wh and constant p are node node_of[p]'s.
 // `unit` numbers the (instance tile, node group) pairs; see the decoding below.
 template <int kMode>
 __device__ __forceinline__ void bmu_dense_h_unit(const float *__restrict__ Xh, const float *__restrict__ Wh,
@@ -90,7 +91,8 @@ __device__ __forceinline__ void bmu_dense_h_unit(const float *__restrict__ Xh, c
                                                  const int32_t *__restrict__ rows, const int32_t *__restrict__ n_slots,
                                                  const float *__restrict__ thr, int32_t *__restrict__ cnt,
                                                  int32_t *__restrict__ list, const int32_t *__restrict__ tcnt,
-                                                 const int32_t *__restrict__ tlist, const int64_t unit) {
+                                                 const int32_t *__restrict__ tlist, const int32_t *__restrict__ node_of,
+                                                 const int64_t unit) {
   constexpr bool kCollect = kMode == kHCollect;
   constexpr bool kDump = kMode == kHDump;
   constexpr bool kPartial = kMode == kHPartial;
@@ -346,12 +348,12 @@ __device__ __forceinline__ void bmu_dense_h_unit(const float *__restrict__ Xh, c
             const int node = nb * kTN + nl;
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) {
-              if (node < k && slot_of[ni] < n) dump[slot_of[ni] * k + node] = fmaf(factor[ni], tot[mi][ni][v], sWn[ord & 3][nl]);
+              if (node < k && slot_of[ni] < n) dump[slot_of[ni] * k + (node_of ? node_of[node] : node)] = fmaf(factor[ni], tot[mi][ni][v], sWn[ord & 3][nl]);
               tot[mi][ni][v] = 0.f;
             }
           }
       } else {
-        consume_scores<kCollect>(tot, sWn[ord & 3], nb * kTN, k, wm, lhi, factor, top, lim, slot_of, cnt, list);
+        consume_scores<kCollect>(tot, sWn[ord & 3], nb * kTN, k, wm, lhi, factor, top, lim, slot_of, cnt, list, nullptr, 0, node_of);
       }
     }
 
@@ -361,7 +363,7 @@ __device__ __forceinline__ void bmu_dense_h_unit(const float *__restrict__ Xh, c
   }
   if (kDump || kCollect || kPartial) return;
   merge_and_store<kHTI>(top, &sW[0][0], reinterpret_cast<int *>(&sX[0][0]), tid, wm, wi, l32, lhi, inst0, n, group,
-                        out, kFine ? rows : nullptr);
+                        out, kFine ? rows : nullptr, kFine ? node_of : nullptr);
 }
 
 // Filter, dump, partial and fine modes: one unit per workgroup.  Collect mode: the number
@@ -378,18 +380,19 @@ __global__ __launch_bounds__(128 * kHWI, 2) void k_bmu_dense_h(const float *__re
                                                         const int32_t *__restrict__ n_slots,
                                                         const float *__restrict__ thr, int32_t *__restrict__ cnt,
                                                         int32_t *__restrict__ list, const int32_t *__restrict__ tcnt,
-                                                        const int32_t *__restrict__ tlist) {
+                                                        const int32_t *__restrict__ tlist,
+                                                        const int32_t *__restrict__ node_of) {
   if (kMode == kHCollect) {
     const int64_t ntiles = ((int64_t)*n_slots + 64 * kHWI - 1) / (64 * kHWI);
     const int64_t units = (ntiles + 7) / 8 * 8 * groups;
     for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
       bmu_dense_h_unit<kMode>(Xh, Wh, wc, xscale, wscale, n, k, nK, flush_chunks, groups, out, dump, rows,
-                              n_slots, thr, cnt, list, tcnt, tlist, unit);
+                              n_slots, thr, cnt, list, tcnt, tlist, node_of, unit);
       __syncthreads();               // the next unit reuses the LDS stages
     }
   } else {
     bmu_dense_h_unit<kMode>(Xh, Wh, wc, xscale, wscale, n, k, nK, flush_chunks, groups, out, dump, rows,
-                            n_slots, thr, cnt, list, tcnt, tlist, (int64_t)blockIdx.x);
+                            n_slots, thr, cnt, list, tcnt, tlist, node_of, (int64_t)blockIdx.x);
   }
 }
 
@@ -431,7 +434,7 @@ int bmu_dense_h_fine_groups(const som_ctx *c, int64_t n) {
   return (int)want;
 }
 
-hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump) {
+hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump, bool ordered) {
   const int groups = bmu_dense_h_groups(c, n);
   const int64_t tiles = (n + 64 * kHWI - 1) / (64 * kHWI);
   const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
@@ -442,11 +445,11 @@ hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump) {
   if (dump)
     hipLaunchKernelGGL((k_bmu_dense_h<kHDump>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream, Xh, Wh,
                        c->wn32, c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, dump, nullptr, nullptr, nullptr,
-                       nullptr, nullptr, nullptr, nullptr);
+                       nullptr, nullptr, nullptr, nullptr, ordered ? c->node_of : nullptr);
   else
     hipLaunchKernelGGL((k_bmu_dense_h<kHFilter>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream, Xh, Wh,
                        c->wn32, c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, dump, nullptr, nullptr, nullptr,
-                       nullptr, nullptr, nullptr, nullptr);
+                       nullptr, nullptr, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -461,7 +464,7 @@ hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n) {
   hipLaunchKernelGGL((k_bmu_dense_h<kHFine>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream,
                      reinterpret_cast<const float *>(c->Xh), reinterpret_cast<const float *>(c->Wh), c->wn32,
                      c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, nullptr, c->sort_val[0],
-                     nullptr, nullptr, nullptr, nullptr, c->tile_cnt, c->tile_list);
+                     nullptr, nullptr, nullptr, nullptr, c->tile_cnt, c->tile_list, c->node_of);
   return hipGetLastError();
 }
 
@@ -475,7 +478,7 @@ hipError_t launch_hot_partial(som_ctx *c, int64_t n) {
   hipLaunchKernelGGL((k_bmu_dense_h<kHPartial>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream,
                      reinterpret_cast<const float *>(c->hot_Xh), reinterpret_cast<const float *>(c->hot_Wh), nullptr,
                      nullptr, c->hot_wscale, n, c->k, kHot / 32, split_flush_chunks(kHot), groups, out, c->hot_P,
-                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -497,7 +500,7 @@ hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists) {
                      reinterpret_cast<const float *>(c->Xh), reinterpret_cast<const float *>(c->Wh), c->wn32,
                      c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, nullptr, c->collect_rows, c->list_counts + 1,
                      c->collect_thr, c->collect_cnt, c->collect_list, lists ? c->ctile_cnt : nullptr,
-                     lists ? c->ctile_list : nullptr);
+                     lists ? c->ctile_list : nullptr, lists ? c->node_of : nullptr);
   return hipGetLastError();
 }
 

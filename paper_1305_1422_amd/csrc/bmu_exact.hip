@@ -625,7 +625,7 @@ static double split_roundings_for(int dim) {
 }
 
 MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool hot) {
-  MarginModel mm{2.0 * fp32_pass_roundings(c->dim) + 4.0, 0.0, nullptr, nullptr, 0, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr};
+  MarginModel mm{2.0 * fp32_pass_roundings(c->dim) + 4.0, 0.0, nullptr, nullptr, 0, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr};
   if (mode == kCertifyCsr) {
     mm.indptr = indptr;
     mm.row_q = c->row_q;
@@ -639,9 +639,9 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
     }
   }
   if (mode == kCertifyCoarse) {
-    // One fp16 product per feature pair on the hi halves alone (coarse pass of the two-level search).  An
-    // operand element v / scale is rounded to 11 significant bits, |dv| <= 2^-11 |v| + 2^-25 scale, so by
-    // Cauchy-Schwarz the dot product of the rounded rows is off by at most
+    // One fp16 product per feature pair on the hi halves alone (coarse pass of the two-level search), whatever the
+    // rows are.  An operand element v / scale is rounded to 11 significant bits, |dv| <= 2^-11 |v| + 2^-25 scale, so
+    // by Cauchy-Schwarz the dot product of the rounded rows is off by at most
     //   |dx| |w'| + |hi_x| |dw| <= (2 + 2^-11) 2^-11 X Wm + floor terms = (2^14 + 8) u X Wm + ...,
     // doubled by the factor -2 of the score.  Accumulation: one chain of ceil(dim / 16) matrix instructions
     // per score, never flushed, priced per instruction like the split pass (2.5 u of the running sum each,
@@ -653,6 +653,16 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
     mm.xscale = c->xscale;
     mm.wscale = c->wscale;
     mm.x_centered = 1;
+  }
+  if (mode == kCertifySelect) {
+    // The same pass, with the norms |dx| and |dw| that these rows really have (xlost, wlost_bits) in the place of
+    // their worst case: the roundings are spread evenly, so the norms are less than half of it, and the block
+    // selection keeps fewer blocks.
+    const double chain = 2.5 * (double)((c->dim + 15) / 16) + 9.0 + 2.0;
+    mm.coef_xw = 2.0 * chain * (1.0 + 0x1p-9) + 4.0 + 2.0;
+    mm.x_centered = 1;
+    mm.xlost = c->xlost;
+    mm.wlost_bits = c->wlost_bits;
   }
   if (mode == kCertifySplit) {
     // dot product: accumulation + 3 * 2^-22 of the split (= 12 u) ; both doubled by the factor -2;
@@ -740,14 +750,15 @@ hipError_t launch_refine_lists_csr(som_ctx *c, const int64_t *indptr, const int3
 // partial sum, the partial sums are added in index order by k_mean_of_partials: the result
 // does not depend on the schedule.  A node index outside [0, k) yields NaN.
 
-// Dense rows: memory-bound, one read of the instances (the nodes' rows come out of L2); a wavefront takes 1,024 features
-// of instance and node before it uses the first (100,000 x 1,000: 208 -> 82 us).
+// Dense rows: memory-bound, one read of the instances (the nodes' rows come out of L2); kLanes lanes share a row (16 up
+// to 64 features, 32 up to 128, else the wavefront) and take 4 kAhead features each of instance and node before they use
+// the first (100,000 x 1,000: 208 -> 82 us; 91,834 x 30: 25 -> 9).
 // Sparse rows need |w|^2 of their nodes.  The nodes met are marked first (k_mark_nodes) and their norms taken once,
 // by a workgroup each (k_marked_norms): an instance's own wavefront reading its node's whole row took 321 us for 1,000
 // instances of a 50,000-column set on 321 nodes, the three launches take 35.
 constexpr int kDistThreads = 512;
 
-template <bool kCsr, bool kWide>
+template <bool kCsr, bool kWide, int kLanes, int kAhead>
 __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__restrict__ X,
                                                                 const int64_t *__restrict__ indptr,
                                                                 const int32_t *__restrict__ indices,
@@ -756,15 +767,15 @@ __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__r
                                                                 int64_t n, int k, int dim,
                                                                 const int32_t *__restrict__ bmus, float *__restrict__ dist,
                                                                 double *__restrict__ partial) {
-  constexpr int kWaves = kDistThreads / kWave;
-  __shared__ double wave_total[kWaves];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  constexpr int kTeams = kDistThreads / kLanes;
+  __shared__ double team_total[kTeams];
+  const int lane = threadIdx.x % kLanes;
+  const int team = threadIdx.x / kLanes;
   const int64_t per_block = (n + gridDim.x - 1) / gridDim.x;
   const int64_t j0 = (int64_t)blockIdx.x * per_block;
   const int64_t j1 = j0 + per_block < n ? j0 + per_block : n;
   double total = 0.0;
-  for (int64_t j = j0 + wave; j < j1; j += kWaves) {
+  for (int64_t j = j0 + team; j < j1; j += kTeams) {
     const int b = bmus[j];
     double d = NAN;
     if ((unsigned)b < (unsigned)k) {
@@ -778,17 +789,17 @@ __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__r
       } else {
         const float *x = X + j * dim;
         double s = 0.0;
-        for (int c0 = 0; c0 < dim; c0 += 4 * 4 * kWave) {
-          f32x4r xv[4], wv[4];
+        for (int c0 = 0; c0 < dim; c0 += 4 * kAhead * kLanes) {
+          f32x4r xv[kAhead], wv[kAhead];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            xv[u] = row_load<kWide>(x, c0 + 4 * (lane + kWave * u), dim);
-            wv[u] = row_load<kWide>(w, c0 + 4 * (lane + kWave * u), dim);
+          for (int u = 0; u < kAhead; ++u) {
+            xv[u] = row_load<kWide>(x, c0 + 4 * (lane + kLanes * u), dim);
+            wv[u] = row_load<kWide>(w, c0 + 4 * (lane + kLanes * u), dim);
           }
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 4 * (lane + kWave * u);
-            if (c0 + 4 * kWave * (u + 1) > dim) {      // uniform
+          for (int u = 0; u < kAhead; ++u) {
+            const int c = c0 + 4 * (lane + kLanes * u);
+            if (c0 + 4 * kLanes * (u + 1) > dim) {      // uniform
               row_tail<kWide>(xv[u], c, dim);
               row_tail<kWide>(wv[u], c, dim);
             }
@@ -799,18 +810,18 @@ __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__r
             }
           }
         }
-        d2 = wave_sum(s);
+        d2 = team_sum<kLanes>(s);
       }
       d = sqrt(d2);
     }
     if (dist && lane == 0) dist[j] = (float)d;
     total += d;
   }
-  if (lane == 0) wave_total[wave] = total;
+  if (lane == 0) team_total[team] = total;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double t = wave_total[0];
-    for (int w = 1; w < kWaves; ++w) t += wave_total[w];
+    double t = team_total[0];
+    for (int w = 1; w < kTeams; ++w) t += team_total[w];
     partial[blockIdx.x] = t;
   }
 }
@@ -851,8 +862,9 @@ __global__ __launch_bounds__(64) void k_mean_of_partials(const double *__restric
   if (threadIdx.x == 0) *out = n > 0 ? s / (double)n : 0.0;
 }
 
-static int distance_blocks(int64_t n) {
-  int64_t blocks = (n + kDistThreads / kWave - 1) / (kDistThreads / kWave);
+static int distance_blocks(int64_t n, int lanes) {
+  const int teams = kDistThreads / lanes;
+  int64_t blocks = (n + teams - 1) / teams;
   if (blocks > kDistBlocks) blocks = kDistBlocks;
   return blocks < 1 ? 1 : (int)blocks;
 }
@@ -860,13 +872,17 @@ static int distance_blocks(int64_t n) {
 // Dense rows (no context needed).
 hipError_t launch_bmu_distances_on(hipStream_t stream, const float *X, int64_t n, const float *W, int k, int dim,
                                    const int32_t *bmus, float *dist, double *qerror, double *partial) {
-  const int blocks = distance_blocks(n);
-  if (dim >= 4)
-    hipLaunchKernelGGL((k_bmu_distances<false, true>), dim3(blocks), dim3(kDistThreads), 0, stream, X, nullptr, nullptr,
-                       nullptr, W, nullptr, n, k, dim, bmus, dist, partial);
-  else
-    hipLaunchKernelGGL((k_bmu_distances<false, false>), dim3(blocks), dim3(kDistThreads), 0, stream, X, nullptr, nullptr,
-                       nullptr, W, nullptr, n, k, dim, bmus, dist, partial);
+  const int blocks = distance_blocks(n, dim <= 64 ? 16 : dim <= 128 ? 32 : kWave);
+#define SOM_DISTANCES(WIDE, L, AHEAD)                                                                                  \
+  hipLaunchKernelGGL((k_bmu_distances<false, WIDE, L, AHEAD>), dim3(blocks), dim3(kDistThreads), 0, stream, X, nullptr, \
+                     nullptr, nullptr, W, nullptr, n, k, dim, bmus, dist, partial)
+  if (dim < 4) SOM_DISTANCES(false, 16, 1);
+  else if (dim <= 64) SOM_DISTANCES(true, 16, 1);
+  else if (dim <= 128) SOM_DISTANCES(true, 32, 1);
+  else if (dim <= 256) SOM_DISTANCES(true, 64, 1);
+  else if (dim <= 512) SOM_DISTANCES(true, 64, 2);
+  else SOM_DISTANCES(true, 64, 4);
+#undef SOM_DISTANCES
   if (qerror) hipLaunchKernelGGL(k_mean_of_partials, dim3(1), dim3(64), 0, stream, partial, blocks, n, qerror);
   return hipGetLastError();
 }
@@ -879,8 +895,8 @@ hipError_t launch_bmu_distances(som_ctx *c, const float *X, const int64_t *indpt
                      c->dist_flag);
   hipLaunchKernelGGL(k_marked_norms, dim3(c->k < c->n_cu * 16 ? c->k : c->n_cu * 16), dim3(256), 0, c->stream, W, c->k, c->dim,
                      c->dist_call, c->dist_flag, c->wn64);
-  const int blocks = distance_blocks(n);
-  hipLaunchKernelGGL((k_bmu_distances<true, false>), dim3(blocks), dim3(kDistThreads), 0, c->stream, nullptr, indptr, indices,
+  const int blocks = distance_blocks(n, kWave);
+  hipLaunchKernelGGL((k_bmu_distances<true, false, kWave, 1>), dim3(blocks), dim3(kDistThreads), 0, c->stream, nullptr, indptr, indices,
                      values, W, c->wn64, n, c->k, c->dim, bmus, dist, c->dist_partial);
   if (qerror) hipLaunchKernelGGL(k_mean_of_partials, dim3(1), dim3(64), 0, c->stream, c->dist_partial, blocks, n, qerror);
   return hipGetLastError();

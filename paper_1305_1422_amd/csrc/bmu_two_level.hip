@@ -11,17 +11,24 @@
 //      m[b][j] <= m_j + 2 e_j - a node of any other block has an exact score above that of the node
 //      that gave m_j, strictly, so it is not the BMU and does not tie with it.  The kernel writes that
 //      block set as a bit mask, and a sort key made of the size class of the set (1, 2, 3-4, 5-8, ...
-//      blocks; the widest class first) and its lowest block;
-//   3. the instances are put in the order of their keys (segsum.hip's radix sort).  A fine-pass tile
+//      blocks; the widest class first), its lowest block and the distance from there to its highest;
+//   3. the instances are put in the order of their keys (segsum.hip's grouping).  A fine-pass tile
 //      works on the union of its 128 instances' sets, so one instance with a wide set (one that lies
 //      between clusters, say) makes its whole tile expensive: the size class keeps such instances among
-//      themselves, and within a class the lowest block puts instances with nearly the same sets side
-//      by side (on a map that has begun to order itself the sets are runs of neighbouring blocks);
+//      themselves, and within a class the lowest and the highest block put instances with the same sets
+//      side by side (listed blocks per tile, lowest alone / both: sparse uniform rows on 50 x 50 nodes
+//      3.0 / 1.7, uniform noise on 74 x 95 7.3 / 6.0, a mixture on 100 x 100 2.1 / 1.9);
 //   4. k_tile_lists: the union of the masks over every 128 consecutive instances of that order, as an
 //      ascending list of blocks;
 //   5. fine pass (k_bmu_dense_h, fine mode): the split-fp16 filter over those (tile, block) pairs only.
 // Its candidates go through the exact stage like those of the one-level filter: the nodes it never saw
 // are out by the argument of step 2, whatever the exact stage decides about the others.
+// A block is a patch of the map, not 128 nodes of consecutive index: the planes hold the nodes in bands of about
+// kPatchRows rows, column by column within a band, so that a block is about 12 rows of 10 or 11 columns.  The
+// candidates of an instance lie in a neighbourhood of its BMU, which such patches cover with far fewer blocks than
+// strips of one or two map rows do (listed blocks per tile, strips / patches, both with the bound on e_j that the
+// residuals give: 1,000,000 x 128 on 100 x 100 nodes 5.3 / 2.1, 50,000 x 256 on 200 x 200 12.1 / 4.4; fine pass
+// there 950 -> 300 and 250 -> 90 us).
 // The price is steps 2-4 and the table m (4 bytes per instance and node block, written once and read
 // twice); when every block of every tile is listed (a code book of equal rows) the fine pass is the
 // whole one-level filter and the coarse pass is lost: a third more work in that worst case.
@@ -38,7 +45,7 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
                                                               const float *__restrict__ xn32,
                                                               const unsigned *__restrict__ wmax_bits,
                                                               const float *__restrict__ mu_norm2, MarginModel mm,
-                                                              int classes, int32_t *__restrict__ key,
+                                                              int classes, int spans, int32_t *__restrict__ key,
                                                               uint32_t *__restrict__ mask) {
   constexpr int kHold = 32;
   constexpr int kWordsAtOnce = 8;               // mask words combined per round: 256 blocks
@@ -69,7 +76,7 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
     t32 = (float)thr;                           // rounded up: no block inside the window is lost
     if ((double)t32 < thr) t32 = nextafterf(t32, INFINITY);
   }
-  int listed = 0, lowest = 0x7fffffff;          // kept by part 0
+  int listed = 0, lowest = 0x7fffffff, highest = 0;          // kept by part 0
   for (int w0 = 0; w0 < blocks; w0 += 32 * kWordsAtOnce) {
     uint32_t bits[kWordsAtOnce];
 #pragma unroll
@@ -102,6 +109,7 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
         for (int p = 0; p < kParts; ++p) all |= s_bits[p][w][lane];
         mask[(int64_t)((w0 >> 5) + w) * n + j] = all;
         if (all && lowest == 0x7fffffff) lowest = w0 + 32 * w + __ffs((int)all) - 1;
+        if (all) highest = w0 + 32 * w + 31 - __clz((int)all);
         listed += __popc(all);
       }
     }
@@ -110,7 +118,8 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
   if (part == 0 && live) {
     const int size_class = listed <= 1 ? 0 : 32 - __clz(listed - 1);      // ceil(log2(listed))
     // widest sets first: their tiles are the longest workgroups of the fine pass and should not start last
-    key[j] = (classes - 1 - size_class) * blocks + (lowest == 0x7fffffff ? 0 : lowest);
+    const int first = lowest == 0x7fffffff ? 0 : lowest;
+    key[j] = ((classes - 1 - size_class) * blocks + first) * spans + min(max(highest - first, 0), spans - 1);
   }
 }
 
@@ -121,8 +130,26 @@ static int size_classes(int blocks) {
   return classes;
 }
 
-// Keys of k_select_blocks are below this.
-int two_level_key_range(int blocks) { return size_classes(blocks) * blocks; }
+// The order of the nodes in the planes (see the head of this file): bands of rows, each column by column.
+__global__ __launch_bounds__(256) void k_patch_order(int rows, int cols, int bands, int32_t *__restrict__ node_of,
+                                                     int32_t *__restrict__ pos_of) {
+  const int p = blockIdx.x * 256 + threadIdx.x;
+  if (p >= rows * cols) return;
+  const int band = (int)((((int64_t)p / cols + 1) * bands - 1) / rows);      // the last one that starts at or before that row
+  const int r0 = (int)((int64_t)band * rows / bands), r1 = (int)((int64_t)(band + 1) * rows / bands);
+  const int in = p - r0 * cols, col = in / (r1 - r0), row = r0 + in % (r1 - r0);
+  const int node = row * cols + col;
+  node_of[p] = node;
+  pos_of[node] = p;
+}
+
+hipError_t launch_patch_order(som_ctx *c) {
+  int bands = (c->rows + kPatchRows / 2) / kPatchRows;
+  if (bands < 1) bands = 1;
+  hipLaunchKernelGGL(k_patch_order, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->rows, c->cols, bands, c->node_of,
+                     c->pos_of);
+  return hipGetLastError();
+}
 
 // One wavefront per tile of 128 consecutive entries of `rows`: OR of their masks, expanded to a list.
 // The masks are stored with stride n; `rows` has n entries, or *n_rows of them if n_rows is given.
@@ -152,15 +179,17 @@ __global__ __launch_bounds__(256) void k_tile_lists(const uint32_t *__restrict__
 }
 
 hipError_t launch_select_blocks(som_ctx *c, int64_t n) {
-  const int blocks = (c->k + 127) / 128;
+  const int blocks = (c->k + 127) / 128, classes = size_classes(blocks);
+  // as many steps of the span as keep the keys below k: the grouping by key has room for that many
+  const int spans = c->k / (classes * blocks) > blocks ? blocks : c->k / (classes * blocks) > 1 ? c->k / (classes * blocks) : 1;
   if (blocks <= 128)      // 32 blocks held per thread: all of them
     hipLaunchKernelGGL(k_select_blocks<4>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifyCoarse, nullptr),
-                       size_classes(blocks), c->coarse_key, c->coarse_mask);
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifySelect, nullptr),
+                       classes, spans, c->coarse_key, c->coarse_mask);
   else
     hipLaunchKernelGGL(k_select_blocks<8>, dim3((unsigned)((n + 63) / 64)), dim3(512), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifyCoarse, nullptr),
-                       size_classes(blocks), c->coarse_key, c->coarse_mask);
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifySelect, nullptr),
+                       classes, spans, c->coarse_key, c->coarse_mask);
   return hipGetLastError();
 }
 

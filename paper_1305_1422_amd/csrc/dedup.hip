@@ -73,7 +73,8 @@ __global__ __launch_bounds__(256) void k_dedup_mark(const float *__restrict__ W,
                                                     const uint64_t *__restrict__ hash,
                                                     const unsigned long long *__restrict__ keys,
                                                     const int32_t *__restrict__ lowest, int slots,
-                                                    float *__restrict__ node_const) {
+                                                    float *__restrict__ node_const,
+                                                    const int32_t *__restrict__ pos_of) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const int nwaves = gridDim.x * (blockDim.x / kWave);
@@ -92,11 +93,11 @@ __global__ __launch_bounds__(256) void k_dedup_mark(const float *__restrict__ W,
     const float *b = W + (int64_t)rep * dim;
     int differ = 0;
     for (int c = lane; c < dim; c += kWave) differ |= (__float_as_uint(a[c]) != __float_as_uint(b[c]));
-    if (!__any(differ) && lane == 0) node_const[i] = INFINITY;
+    if (!__any(differ) && lane == 0) node_const[pos_of ? pos_of[i] : i] = INFINITY;
   }
 }
 
-hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W) {
+hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W, const int32_t *pos_of) {
   const int waves_grid = (c->k + 3) / 4 < c->n_cu * 8 ? (c->k + 3) / 4 : c->n_cu * 8;
   const int slots = c->dedup_slots;
   unsigned long long *keys = reinterpret_cast<unsigned long long *>(c->dedup_keys);
@@ -105,7 +106,7 @@ hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W) {
   hipLaunchKernelGGL(k_dedup_insert, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->row_hash, c->k, keys,
                      c->dedup_lowest, slots);
   hipLaunchKernelGGL(k_dedup_mark, dim3(waves_grid), dim3(256), 0, c->stream, W, c->k, c->dim, c->row_hash, keys,
-                     c->dedup_lowest, slots, c->wn32);
+                     c->dedup_lowest, slots, c->wn32, pos_of);
   return hipGetLastError();
 }
 

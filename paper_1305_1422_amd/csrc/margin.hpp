@@ -25,6 +25,10 @@ struct MarginModel {
   const float *hot_xn;       // [n] |x_hot|^2
   const float *hot_xscale;   // [n]
   const float *hot_wscale;   // [1]
+  // coarse pass with the residuals of the rows at hand: what its operands, rounded to 11 bits, leave out: |x' - hi(x')| of every instance and the largest
+  // |w' - hi(w')| of the nodes; null in the other models
+  const float *xlost;            // [n]
+  const unsigned *wlost_bits;    // [1]
 };
 
 __device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j, double xnorm2, double wmax2,
@@ -47,6 +51,10 @@ __device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j,
   if (mm.coef_hot > 0.0) {
     const double xh = sqrt((double)mm.hot_xn[j] * (1.0 + 1.2e-7));
     bound += mm.coef_hot * xh * wm + sqrt((double)kHot) * ((double)mm.hot_xscale[j] * wm + (double)*mm.hot_wscale * xh);
+  }
+  if (mm.xlost) {            // x'.w' - hi(x').hi(w') = dx.w' + hi(x').dw, doubled by the score's factor -2
+    const double lx = (double)mm.xlost[j], lw = (double)__uint_as_float(*mm.wlost_bits);
+    absolute += 2.0 * (lx * wm + (xn + lx) * lw);
   }
   if (mm.xscale) bound += mm.coef_floor * ((double)mm.xscale[j] * wm + (double)*mm.wscale * xn);
   return 2.125 * (u * bound + absolute);          // both scores of a pair may err, plus slack for higher-order terms

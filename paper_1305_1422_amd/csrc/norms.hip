@@ -72,7 +72,8 @@ __global__ __launch_bounds__(256) void k_center_codebook(const float *__restrict
                                                          const float *__restrict__ mu, float *__restrict__ Wc,
                                                          float *__restrict__ cn, unsigned *__restrict__ max_bits,
                                                          double *__restrict__ wn64,
-                                                         unsigned *__restrict__ wabs_bits, int x_centered) {
+                                                         unsigned *__restrict__ wabs_bits, int x_centered,
+                                                         const int32_t *__restrict__ pos_of) {
   __shared__ double scratch[4][3];
   constexpr int kTeams = 256 / kTeam;
   const int tl = threadIdx.x % kTeam, team = threadIdx.x / kTeam;
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(256) void k_center_codebook(const float *__restrict
       sw = wave_sum(sw);
     }
     if (tl == 0) {
-      cn[i] = (float)(x_centered ? s2 : s2 + 2.0 * sm);      // instances centred too: |w'|^2 - 2 x'.w' ranks alike
+      cn[pos_of ? pos_of[i] : i] = (float)(x_centered ? s2 : s2 + 2.0 * sm);      // instances centred too: |w'|^2 - 2 x'.w' ranks alike
       vmax = fmaxf(vmax, (float)s2);
       if (wn64) wn64[i] = sw;
     }
@@ -307,7 +308,8 @@ hipError_t launch_vec_sqnorm(som_ctx *c, const float *v, int dim, float *out) {
   return hipGetLastError();
 }
 
-hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centered, bool want_wn64, bool x_centered) {
+hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centered, bool want_wn64, bool x_centered,
+                                  const int32_t *pos_of) {
   float *wc = store_centered ? c->Wc : nullptr;
   unsigned *wabs = store_centered ? c->wmax_bits + 1 : nullptr;
   double *wn64 = want_wn64 ? c->wn64 : nullptr;
@@ -315,11 +317,11 @@ hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centere
   if (c->dim <= 2048) {
     const int need = (c->k + 3) / 4;
     hipLaunchKernelGGL(k_center_codebook<64>, dim3(need < cap ? need : cap), dim3(256), 0, c->stream, W, c->k, c->dim,
-                       c->mu, wc, c->wn32, c->wmax_bits, wn64, wabs, x_centered ? 1 : 0);
+                       c->mu, wc, c->wn32, c->wmax_bits, wn64, wabs, x_centered ? 1 : 0, pos_of);
   } else {
     const int cap_long = c->n_cu * 8;       // long rows: more workgroups in flight, still few atomics
     hipLaunchKernelGGL(k_center_codebook<256>, dim3(c->k < cap_long ? c->k : cap_long), dim3(256), 0, c->stream, W, c->k, c->dim,
-                       c->mu, wc, c->wn32, c->wmax_bits, wn64, wabs, x_centered ? 1 : 0);
+                       c->mu, wc, c->wn32, c->wmax_bits, wn64, wabs, x_centered ? 1 : 0, pos_of);
   }
   return hipGetLastError();
 }

@@ -39,4 +39,12 @@ __device__ __forceinline__ void row_tail(f32x4r &v, int c, int dim) {
   }
 }
 
+// Sum over the kLanes lanes (a power of two) of this lane's team, in all of them.
+template <int kLanes, typename T>
+__device__ __forceinline__ T team_sum(T v) {
+#pragma unroll
+  for (int o = kLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
 }  // namespace som

@@ -778,7 +778,7 @@ __global__ __launch_bounds__(256) void k_scatter_csr(const int64_t *__restrict__
 
 // Stable permutation of the ids 0 .. n - 1 by integer keys in [0, key_range) (larger keys are clamped).
 // On return c->sort_val[0] holds the permutation, c->sort_key[0] the sorted keys.
-hipError_t launch_sort_keys(som_ctx *c, const int32_t *bmus, int64_t n, int key_range) {
+static hipError_t launch_sort_keys(som_ctx *c, const int32_t *bmus, int64_t n, int key_range) {
   const RadixPlan plan = radix_plan(n, key_range);
   const int bins = 1 << plan.digit_bits;
   const int32_t *kin = bmus;
@@ -858,6 +858,11 @@ static hipError_t launch_group_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n
   hipLaunchKernelGGL(k_scan_exclusive, dim3(1), dim3(1024), 0, c->stream, c->counts, c->chunk_off, c->k, chunk_rows);
   hipLaunchKernelGGL(k_fill_chunk_nodes, dim3(c->n_cu * 2), dim3(256), 0, c->stream, c->chunk_off, c->k, c->chunk_node);
   return hipGetLastError();
+}
+
+// Order of the instances by a key below k: the permutation alone (c->sort_val[0]; the tables of the grouping are scratch).
+hipError_t launch_order_by_key(som_ctx *c, const int32_t *keys, int64_t n) {
+  return launch_group_by_bmu(c, keys, n, 1 << 20);
 }
 
 hipError_t launch_scan_exclusive_i32(som_ctx *c, const int32_t *in, int32_t *out, int len) {

@@ -116,9 +116,10 @@ static void free_row_scratch(som_ctx *c) {
   dev_free(c->sort_key[0]); dev_free(c->sort_key[1]); dev_free(c->sort_val[0]); dev_free(c->sort_val[1]);
   dev_free(c->radix_hist); dev_free(c->group_table); dev_free(c->chunk_node); dev_free(c->partial);
   dev_free(c->Xh); dev_free(c->xscale);
-  dev_free(c->Xh1); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
+  dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
   dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
   c->two_level_n = 0;
+  c->debug_coarse_n = 0;
   c->n_cap = 0;
   c->cand_cap = 0;
   c->d_norms_valid = 0;
@@ -197,16 +198,20 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
   if (coarse) {
     const size_t row_halves = (size_t)((c->dim + 63) / 64) * 64;
     const size_t blocks = (size_t)(c->k + 127) / 128, tiles = ((size_t)c->n_cap + 127) / 128;
-    if (c->Wh1 == nullptr && !dev_alloc(&c->Wh1, (size_t)c->k * row_halves))
-      return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of the code book");
+    if (c->Wh1 == nullptr) {
+      dev_free(c->node_of); dev_free(c->pos_of);
+      if (!(dev_alloc(&c->node_of, (size_t)c->k) && dev_alloc(&c->pos_of, (size_t)c->k) && dev_alloc(&c->Wh1, (size_t)c->k * row_halves)))
+        return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of the code book");
+      SOM_LAUNCH(c, launch_patch_order(c));
+    }
     if (c->Xh1 == nullptr) {
       c->d_split_valid = 0;
       c->csrd_valid = 0;
-      if (!(dev_alloc(&c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc(&c->coarse_min, blocks * (size_t)c->n_cap) &&
+      if (!(dev_alloc(&c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc(&c->xlost, (size_t)c->n_cap) && dev_alloc(&c->coarse_min, blocks * (size_t)c->n_cap) &&
             dev_alloc(&c->coarse_key, (size_t)c->n_cap) && dev_alloc(&c->coarse_mask, (blocks + 31) / 32 * (size_t)c->n_cap) &&
             dev_alloc(&c->tile_cnt, tiles) && dev_alloc(&c->tile_list, tiles * blocks) &&
             dev_alloc(&c->ctile_cnt, tiles) && dev_alloc(&c->ctile_list, tiles * blocks))) {
-        dev_free(c->Xh1); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
+        dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
         dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
         return fail(c, SOM_ERR_ALLOC, "cannot allocate the two-level search's scratch for %lld instances", (long long)c->n_cap);
       }
@@ -330,12 +335,12 @@ static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, 
     }
   }
   if (split && !(have_xn && c->d_split_valid)) {
-    SOM_LAUNCH(c, launch_instance_planes(c, X, n, c->mu, c->Xh, c->xscale, coarse ? c->Xh1 : nullptr, c->xn32));
+    SOM_LAUNCH(c, launch_instance_planes(c, X, n, c->mu, 0, coarse, c->xn32));
     c->d_split_valid = have_xn ? 1 : 0;
   }
   if (split) SOM_LAUNCH(c, launch_codebook_planes(c, W, false, coarse));
   else SOM_LAUNCH(c, launch_center_codebook(c, W, true, false, false));
-  if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
+  if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W, coarse ? c->pos_of : nullptr));
   return SOM_OK;
 }
 
@@ -344,7 +349,7 @@ static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split,
   if (coarse) {
     SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr));
     SOM_LAUNCH(c, launch_select_blocks(c, n));
-    SOM_LAUNCH(c, launch_sort_keys(c, c->coarse_key, n, two_level_key_range((c->k + 127) / 128)));
+    SOM_LAUNCH(c, launch_order_by_key(c, c->coarse_key, n));
     SOM_LAUNCH(c, launch_tile_lists(c, n));
     SOM_LAUNCH(c, launch_bmu_dense_h_fine(c, n));
   } else if (split) {
@@ -461,7 +466,7 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
     rc = begin_search(c);
     if (rc) return rc;
     SOM_LAUNCH(c, launch_codebook_planes(c, W, true /* |w|^2 in fp64 for the sparse exact kernels */, coarse));
-    if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
+    if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W, coarse ? c->pos_of : nullptr));
   }
   {
     StageTimer t(c, 1);
@@ -653,14 +658,12 @@ static int registered_csr_dense(som_ctx *c) {
   float *dense = nullptr;
   if (!dev_alloc(&dense, (size_t)batch * c->dim)) return fail(c, SOM_ERR_ALLOC, "cannot allocate a batch of dense rows");
   const bool coarse = two_level_ready(c, n);
-  const size_t row_halves = (size_t)((c->dim + 31) / 32) * 64, row_halves1 = (size_t)((c->dim + 63) / 64) * 64;
   int rcl = SOM_OK;
   for (int64_t r0 = 0; r0 < n && rcl == SOM_OK; r0 += batch) {
     const int64_t rows = n - r0 < batch ? n - r0 : batch;
     hipError_t e = launch_csr_densify(c, c->d_indptr, c->d_indices, c->d_values, r0, rows, dense);
     if (e == hipSuccess)
-      e = launch_instance_planes(c, dense, rows, c->csrd_mu, c->Xh + (size_t)r0 * row_halves, c->xscale + r0,
-                                 coarse ? c->Xh1 + (size_t)r0 * row_halves1 : nullptr, c->csrd_xn + r0);
+      e = launch_instance_planes(c, dense, rows, c->csrd_mu, r0, coarse, c->csrd_xn + r0);
     if (e != hipSuccess) rcl = dev_fail(c, e, "dense planes of the sparse rows");
   }
   hipError_t es = hipStreamSynchronize(c->stream);     // the batch buffer is freed below
@@ -745,6 +748,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   c->wmax_bits = reinterpret_cast<unsigned *>(c->list_counts) + kMaxWords;
   c->qstep_max_bits = c->wmax_bits + 2;
   c->hot_wmax_bits = c->wmax_bits + 3;
+  c->wlost_bits = c->wmax_bits + 4;
   hipError_t e = launch_fill_zero_u32(c->stream, c->list_counts, kListWords);
   if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->zero16, 16);
   if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->dist_flag, c->k);
@@ -776,7 +780,7 @@ void som_destroy(som_ctx *c) {
   dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial); dev_free(c->H2);
   dev_free(c->GxT); dev_free(c->GyT); dev_free(c->hit_x); dev_free(c->hit_n); dev_free(c->hit_rows);
   dev_free(c->mu); dev_free(c->mu_partial); dev_free(c->Wc); dev_free(c->zero16); dev_free(c->mu_norm2);
-  dev_free(c->Wh); dev_free(c->Wh1); dev_free(c->wscale);
+  dev_free(c->Wh); dev_free(c->Wh1); dev_free(c->node_of); dev_free(c->pos_of); dev_free(c->wscale);
   free_hot(c);
   dev_free(c->csrd_mu); dev_free(c->csrd_mu_norm2); dev_free(c->csrd_xn);
   dev_free(c->hot_counts); dev_free(c->hot_rank); dev_free(c->hot_cols); dev_free(c->hot_Wc); dev_free(c->hot_Wh);
@@ -1148,11 +1152,20 @@ int som_debug_scores_dense(som_ctx *c, const float *data, int64_t n, const float
   if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = c->filter == SOM_FILTER_TWO_LEVEL && two_level_ready(c, n);    // asked for by name: its coarse scores
+  c->debug_coarse_n = coarse ? n : 0;
   if (coarse) SOM_LAUNCH(c, launch_bmu_coarse(c, n, scores));
-  else if (split) SOM_LAUNCH(c, launch_bmu_dense_h(c, n, scores));
+  else if (split) SOM_LAUNCH(c, launch_bmu_dense_h(c, n, scores, two_level_ready(c, n)));
   else SOM_LAUNCH(c, launch_bmu_dense(c, data, n, scores));
   SOM_LAUNCH(c, launch_margins(c, n, coarse ? kCertifyCoarse : split ? kCertifySplit : kCertifyFp32, nullptr, margin_out));
   SOM_LAUNCH(c, hipMemcpyAsync(mu_out, c->mu, (size_t)c->dim * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  return SOM_OK;
+}
+
+int som_debug_select_margins(som_ctx *c, int64_t n, double *margin_out) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  if (!margin_out) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  if (n < 1 || n != c->debug_coarse_n) return fail(c, SOM_ERR_INVALID_ARG, "no coarse scores of %lld instances", (long long)n);
+  SOM_LAUNCH(c, launch_margins(c, n, kCertifySelect, nullptr, margin_out));
   return SOM_OK;
 }
 

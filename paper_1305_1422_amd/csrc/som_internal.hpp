@@ -212,6 +212,10 @@ struct som_ctx {
   _Float16 *hot_Wh;       // [k][kHot/32][64] the same as planes
   float *hot_wscale;      // [1]
   unsigned *hot_wmax_bits;    // [1] (word of list_counts)
+  unsigned *wlost_bits;       // [1] (word of list_counts) largest |w' - hi(w')| of the two-level search's planes
+  float *xlost;               // [n_cap] |x' - hi(x')| of the instances, with Xh1
+  int64_t debug_coarse_n;     // instances of the last som_debug_scores_dense, if it ran the coarse pass
+  int32_t *node_of, *pos_of;  // [k] order of the nodes in the two-level search's planes, and its inverse
   float *hot_P;           // [ceil(k/128)][n][128] dot products of the hot parts divided by the instance scale
 
   // dense planes of the registered sparse training set (som_set_sparse_dense_filter); built on first use
@@ -250,7 +254,8 @@ hipError_t launch_sample_col_means(som_ctx *c, const float *A, int64_t nrows, in
 hipError_t launch_codebook_means_and_steps(som_ctx *c, const float *W);      // -> mu, qstep, qstep_max_bits
 hipError_t launch_vec_sqnorm(som_ctx *c, const float *v, int dim, float *out);
 hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centered, bool want_wn64,
-                                  bool x_centered);   // -> Wc, wn32 (= c_i; without the 2 mu.w' term if the instances are centred too), wmax_bits, wn64
+                                  bool x_centered,
+                                  const int32_t *pos_of = nullptr);   // -> Wc, wn32 (= c_i; without the 2 mu.w' term if the instances are centred too), wmax_bits, wn64
 hipError_t launch_row_sqnorms(som_ctx *c, const float *A, int64_t nrows, int dim, const float *mu,
                               float *out32, double *out64, unsigned *max_bits);
 hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n,
@@ -277,24 +282,26 @@ inline int split_flush_chunks(int dim) { return dim >= 256 ? 4 : 2; }
 constexpr int kTwoLevelMinBlocks = 8;
 constexpr int64_t kTwoLevelMaxTable = 8ll << 30;
 int bmu_dense_h_groups(const som_ctx *c, int64_t n);
-hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump);            // Xh, Wh -> candidates (or all scores)
+hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump, bool ordered = false /* dump: rows in the order node_of */);            // Xh, Wh -> candidates (or all scores)
 int bmu_dense_h_fine_groups(const som_ctx *c, int64_t n);
 hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump);              // bmu_coarse.hip: Xh1, Wh1 -> coarse_min (or all scores)
 hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n);                     // sort_val[0], tile_cnt, tile_list -> candidates
 // bmu_two_level.hip
 hipError_t launch_select_blocks(som_ctx *c, int64_t n);                        // coarse_min -> coarse_key, coarse_mask
-int two_level_key_range(int blocks);                                           // keys of coarse_key are below this
+constexpr int kPatchRows = 12;
+hipError_t launch_patch_order(som_ctx *c);                                     // -> node_of, pos_of
 hipError_t launch_tile_lists(som_ctx *c, int64_t n);                           // coarse_mask, sort_val[0] -> tile_cnt, tile_list
 hipError_t launch_collect_tile_lists(som_ctx *c, int64_t n);                   // coarse_mask, collect_rows -> ctile_cnt, ctile_list
 hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists = false);   // rows of collect_rows -> collect_list
 hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, const unsigned *global_max_bits,
                                  const float *mu /* subtracted first, or null */, _Float16 *out, float *scale_out,
                                  int dim = 0 /* row length; 0: the context's */,
-                                 _Float16 *out_hi = nullptr /* the hi halves alone, rows padded to 64 columns */);
+                                 _Float16 *out_hi = nullptr /* the hi halves alone, rows padded to 64 columns */,
+                                 const int32_t *src = nullptr, float *res_out = nullptr, unsigned *res_max = nullptr);
 constexpr int kPlaneMaxDim = 2048;       // rows up to this length are prepared in registers (no centred copy Wc of the code book)
 hipError_t launch_codebook_planes(som_ctx *c, const float *W, bool want_wn64, bool coarse);      // -> wn32, wmax_bits, Wh, wscale (wn64, Wh1)
-hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, const float *mu, _Float16 *out, float *scale_out,
-                                  _Float16 *out_hi, float *norm_out);
+hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, const float *mu, int64_t first, bool coarse,
+                                  float *norm_out);                              // -> Xh, xscale, norm_out (Xh1, xlost)
 hipError_t launch_probe_mfma_f16(hipStream_t stream, const uint16_t *A, const uint16_t *B, const float *C, float *D,
                                  int count);
 
@@ -308,13 +315,13 @@ struct UnitWork {
   int32_t *list;          // [slots][kListCap] candidate lists, seeded with the nodes of the complete ranges
 };
 constexpr size_t kRescanCopyMax = (size_t)16 << 30;      // bytes: no transposed copy for the full rescan beyond this
-constexpr int kListCounts = 16;    // words of lengths and flags at the head of som_ctx::list_counts
+constexpr int kListCounts = 32;    // words of lengths and flags at the head of som_ctx::list_counts
 constexpr int kListTickets = 8;    // entry counters of the list comparison behind them ...
 constexpr int kListTicketStride = 1088;      // ... 4 KB + 256 B apart: another memory channel each
 constexpr int kListWords = kListCounts + kListTickets * kListTicketStride;
 constexpr int kUnitCounts = 4;     // first of the eight work-list lengths in it
-constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits
-enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3 };      // whose rounding bound the margin uses
+constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits, wlost_bits
+enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4 };      // whose rounding bound the margin uses
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus,
                           bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */);
 hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr, double *out,
@@ -352,7 +359,7 @@ hipError_t launch_hot_partial(som_ctx *c, int64_t n);                // bmu_dens
 hipError_t launch_scan_exclusive_i32(som_ctx *c, const int32_t *in, int32_t *out, int len);   // segsum.hip
 
 // dedup.hip
-hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W);   // wn32[i] = +inf for rows equal to a lower-indexed row
+hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W, const int32_t *pos_of = nullptr);   // wn32[i] = +inf for rows equal to a lower-indexed row
 
 // bmu_csr.hip
 constexpr int kCtMaxSlabs = 64;            // column slabs of the fused centring / transpose pass
@@ -368,7 +375,7 @@ hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_
 
 // segsum.hip
 int64_t group_table_entries(int k, int64_t n);       // entries of c->group_table for up to n instances
-hipError_t launch_sort_keys(som_ctx *c, const int32_t *keys, int64_t n, int key_range);   // the permutation alone
+hipError_t launch_order_by_key(som_ctx *c, const int32_t *keys, int64_t n);   // -> sort_val[0]
 hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus);   // -> S, counts
 hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
                                  const float *values, int64_t n, const int32_t *bmus);   // -> S, counts

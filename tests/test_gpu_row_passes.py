@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-DIMS = [1, 2, 3, 4, 5, 31, 33, 63, 64, 255, 256, 257, 511, 513, 1023, 1025, 2047, 2048, 2049]
+DIMS = [1, 2, 3, 4, 5, 31, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 1023, 1025, 2047, 2048, 2049]
 
 
 @pytest.mark.parametrize("filter", ["split_f16", "two_level"])
@@ -28,7 +28,7 @@ def test_planes_of_any_row_length(oracle, filter, dim):
 
 
 @pytest.mark.parametrize("n", [1, 7, 2051, 9001])
-@pytest.mark.parametrize("dim", [1, 3, 4, 6, 1023, 1024, 1025, 2050])
+@pytest.mark.parametrize("dim", [1, 3, 4, 6, 64, 65, 128, 129, 256, 257, 513, 1023, 1024, 1025, 2050])
 def test_distances_of_any_row_length(n, dim):
     from paper_1305_1422_amd import Som
     rng = np.random.default_rng(6200 + n + dim)

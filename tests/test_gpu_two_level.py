@@ -155,3 +155,67 @@ def test_statistics_of_the_second_pass(oracle):
     som.bmus(P.to_dev(X))
     assert som.two_level_stats() == (pairs, pairs)
     som.close()
+
+
+@pytest.mark.parametrize("rows,cols,dim", [(1, 1500, 20), (1500, 1, 20), (5, 300, 33), (300, 5, 33), (13, 100, 64), (17, 77, 65),
+                                           (18, 64, 2100), (41, 29, 7)])
+def test_node_patches_of_any_map_shape(oracle, rows, cols, dim):
+    """The planes hold the nodes by bands of map rows: bands of one row, of all rows, of unequal heights, maps narrower
+    than a block, rows too long for registers; copies of nodes in different bands (the lowest index wins), also where a
+    bubble neighbourhood masks them."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(7000 + rows + dim)
+    k, n = rows * cols, 700
+    W, _ = _ordered_map(rng, rows, cols, dim, 9)
+    W += 0.02 * rng.random((k, dim)).astype(np.float32)
+    W[k - 1] = W[k // 2] = W[3]
+    X = (W[rng.integers(0, k, n)] + 0.03 * rng.standard_normal((n, dim))).astype(np.float32)
+    X[:3] = W[k - 1]
+    b, _ = _bmus(W, X, rows, cols)
+    P.check_bmus_dense(oracle, X, W, b)
+    assert np.all(b[:3] == 3)
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    som.set_neighborhood("bubble")
+    assert np.array_equal(som.bmus(P.to_dev(X)).cpu().numpy(), b)
+    csr = torch.from_numpy(X).to_sparse_csr()
+    dev = (csr.crow_indices().cuda(), csr.col_indices().to(torch.int32).cuda(), csr.values().cuda())
+    som.close()
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    from paper_1305_1422_amd import capi
+    capi.som_set_data_csr(som.ctx, *dev)
+    P.check_bmus_dense(oracle, X, W, som.bmus(dev).cpu().numpy())
+    som.close()
+
+
+@pytest.mark.parametrize("case", ["uniform", "offset_mixture", "heavy_tail", "tiny_and_huge_rows", "ragged_dim", "odd_dim",
+                                  "long_rows"])
+def test_selection_margin_covers_the_coarse_scores(case):
+    """The block selection's margin, made of the residuals of the rows at hand, against fp64 scores of the same centred
+    rows: no coarse score is off by more than half of it, and it stays below the bound for any rows."""
+    from paper_1305_1422_amd import Som, capi
+    from tests.test_gpu_filter_bound import _dense_case
+    rng = np.random.default_rng(7200)
+    rows, cols = 12, 25
+    if case == "long_rows":
+        x, w = rng.random((60, 2500)).astype(np.float32), rng.random((rows * cols, 2500)).astype(np.float32)
+    else:
+        x, w = _dense_case(case, rng, rows, cols)
+    n, dim = x.shape
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(w), filter="two_level")
+    scores = torch.empty((n, rows * cols), dtype=torch.float32, device="cuda")
+    mu = torch.empty(dim, dtype=torch.float32, device="cuda")
+    any_rows = torch.empty(n, dtype=torch.float64, device="cuda")
+    margin = torch.empty(n, dtype=torch.float64, device="cuda")
+    capi.som_debug_scores_dense(som.ctx, P.to_dev(x), som.codebook, scores, mu, any_rows)
+    capi.som_debug_select_margins(som.ctx, margin)
+    with pytest.raises(Exception):
+        capi.som_debug_select_margins(som.ctx, margin[:-1])
+    m = mu.cpu().numpy()
+    xc, wc = (x - m).astype(np.float32).astype(np.float64), (w - m).astype(np.float32).astype(np.float64)
+    exact = (wc ** 2).sum(1)[None, :] - 2.0 * xc @ wc.T
+    err = np.abs(scores.cpu().numpy().astype(np.float64) - exact).max(1)
+    margin, any_rows = margin.cpu().numpy(), any_rows.cpu().numpy()
+    som.close()
+    assert np.all(err <= 0.5 * margin), (err / margin).max()
+    assert np.all(margin <= any_rows)
+    print(f"{case}: worst error / half the margin {(2 * err / margin).max():.3f}, margin / bound for any rows {(margin / any_rows).mean():.3f}")
