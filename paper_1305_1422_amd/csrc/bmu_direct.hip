@@ -382,20 +382,24 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
   }
 }
 
-// Merges the groups' records: kWaves wavefronts per instance (four where there are few instances, else one).  An
+// Merges the groups' records: kWaves wavefronts per instance, the more the fewer instances there are.  An
 // instance they leave open is decided by the plain distances: of a group's best node alone where only that one is
 // inside the limit, else of all nodes of the group (trained maps hold exact copies of nodes side by side, so this is
-// not rare).
+// not rare).  What bounds it is the latency of one load after the other, so a lane holds a group's record (walked one
+// by one they were half of the time), and sixteen wavefronts take four nodes each of a group of 64 (64 instances, 2,500
+// nodes, 1,000 features, most instances open: 53 us with four wavefronts, 25 with sixteen).
 template <int kWaves>
-__global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
+__global__ __launch_bounds__(kWaves > 4 ? 64 * kWaves : 256) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
                                                       int groups, int nodes_per_group, const float *__restrict__ X, int64_t n,
                                                       const float *__restrict__ W, int k, int dim,
                                                       int32_t *__restrict__ bmus) {
-  __shared__ double s_d2[4];
-  __shared__ int s_id[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int kBlockWaves = kWaves > 4 ? kWaves : 4;
+  __shared__ double s_d2[kBlockWaves];
+  __shared__ int s_id[kBlockWaves];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = wave % kWaves;
-  const int64_t j = (int64_t)blockIdx.x * (4 / kWaves) + wave / kWaves;
+  const int64_t j = (int64_t)blockIdx.x * (kBlockWaves / kWaves) + wave / kWaves;
   if (j >= n) return;                           // uniform over the workgroup, or (kWaves == 1) without barriers below
   DirectBest r = direct_none();
   for (int v = lane; v < groups; v += kWave) direct_merge(r, rec[(int64_t)v * n + j]);      // every wavefront all of them
@@ -413,13 +417,20 @@ __global__ __launch_bounds__(256) void k_direct_merge(const DirectBest *__restri
   }
   double b = INFINITY;
   int a = 0x7fffffff;
-  for (int v = 0; v < groups; ++v) {
-    const DirectBest q = rec[(int64_t)v * n + j];
-    if (q.best > limit) continue;               // uniform; a NaN limit keeps every group
+  int turn = 0;                                 // single nodes go to the wavefronts in turn
+  for (int v0 = 0; v0 < groups; v0 += kWave) {
+    const int v = v0 + lane;
+    const DirectBest q = v < groups ? rec[(int64_t)v * n + j] : direct_none();
     int lo = v * nodes_per_group, hi = min(lo + nodes_per_group, k);
     if (q.second > limit && (unsigned)q.arg < (unsigned)k) { lo = q.arg; hi = lo + 1; }
-    const int share = ((hi - lo + kWaves - 1) / kWaves + 3) / 4 * 4;
-    direct_plain(X + j * dim, W, lo + part * share, min(lo + (part + 1) * share, hi), nullptr, dim, lane, b, a);
+    // (a NaN limit keeps every group)
+    for (unsigned long long kept = __ballot(v < groups && !(q.best > limit)); kept; kept &= kept - 1, ++turn) {
+      const int from = __ffsll((long long)kept) - 1;
+      const int glo = __builtin_amdgcn_readlane(lo, from), ghi = __builtin_amdgcn_readlane(hi, from);
+      const int share = ((ghi - glo + kWaves - 1) / kWaves + 3) / 4 * 4;
+      const int at = glo + (part + turn) % kWaves * share;
+      direct_plain(X + j * dim, W, at, min(at + share, ghi), nullptr, dim, lane, b, a);
+    }
   }
   if (kWaves > 1) {
     if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
@@ -517,7 +528,10 @@ hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const flo
 #undef SOM_DIRECT_HELD
 #undef SOM_DIRECT
   if (p.groups > 1) {
-    if (n <= 4 * c->n_cu)
+    if (n <= c->n_cu)          // a workgroup per CU
+      hipLaunchKernelGGL(k_direct_merge<16>, dim3((unsigned)n), dim3(1024), 0, c->stream, rec, xn, p.groups,
+                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
+    else if (n <= 4 * c->n_cu)
       hipLaunchKernelGGL(k_direct_merge<4>, dim3((unsigned)n), dim3(256), 0, c->stream, rec, xn, p.groups,
                          p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
     else

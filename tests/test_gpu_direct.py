@@ -27,6 +27,7 @@ def _bmus(W, X, rows, cols, **kw):
     (40, 9, 9, 15), (300, 20, 20, 16), (1000, 20, 20, 17), (700, 33, 31, 33), (65, 20, 13, 64),
     (4097, 37, 29, 49), (900, 17, 8, 65), (33, 40, 40, 130),                        # the nodes over the wavefronts / groups
     (7, 50, 50, 511), (64, 30, 30, 513), (3, 40, 50, 1000),                         # the features over the wavefronts
+    (256, 40, 50, 520), (257, 40, 50, 520), (1030, 30, 40, 100),                    # 16, 4, 1 wavefronts merge an instance
     (70000, 3, 7, 6), (66001, 10, 12, 18),                                          # a wavefront per 16 instances
 ])
 def test_matches_the_oracle(oracle, n, rows, cols, dim):
