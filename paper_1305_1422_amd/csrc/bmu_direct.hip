@@ -125,7 +125,7 @@ __device__ __forceinline__ void direct_plain(const float *__restrict__ x, const 
     direct_distance4_wave(x, W, id, dim, lane, d2);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (d2[u] < best || (d2[u] == best && id[u] < arg)) { best = d2[u]; arg = id[u]; }
+      if (nearer(d2[u], id[u], best, arg)) { best = d2[u]; arg = id[u]; }
   }
 }
 
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kWaves > 4 ? 64 * kWaves : 256) void k_direct_merge
     if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
     __syncthreads();
     for (int v = 0; v < kWaves; ++v)
-      if (s_d2[v] < b || (s_d2[v] == b && s_id[v] < a)) { b = s_d2[v]; a = s_id[v]; }
+      if (nearer(s_d2[v], s_id[v], b, a)) { b = s_d2[v]; a = s_id[v]; }
   }
   if (lane == 0 && part == 0) bmus[j] = a == 0x7fffffff ? 0 : a;
 }

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void k_refine_dense(const float *__restrict__ 
     for (int t = 0; t < cn; ++t) {
       const int i = cand_idx[j * kCand + t];
       const double d2 = sqdist_dense_wave(X + j * dim, W + (int64_t)i * dim, dim, lane);
-      if (d2 < best || (d2 == best && i < arg)) { best = d2; arg = i; }
+      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
     }
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
   }
@@ -309,12 +309,12 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
       sqdist_dense_wave4(X + j * dim, W, id, dim, lane, d2);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (d2[u] < best || (d2[u] == best && id[u] < arg)) { best = d2[u]; arg = id[u]; }
+        if (nearer(d2[u], id[u], best, arg)) { best = d2[u]; arg = id[u]; }
     }
     for (; t < cn; ++t) {
       const int i = min(max(lst[t], 0), k - 1);
       const double d2 = sqdist_dense_wave(X + j * dim, W + (int64_t)i * dim, dim, lane);
-      if (d2 < best || (d2 == best && i < arg)) { best = d2; arg = i; }
+      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
     }
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
   }
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256) void k_refine_csr(const int64_t *__restrict__ 
     for (int t = 0; t < cn; ++t) {
       const int i = cand_idx[j * kCand + t];
       const double d2 = sqdist_csr_wave(indices + s, values + s, len, W + (int64_t)i * dim, wn64[i], xn, dim, lane);
-      if (d2 < best || (d2 == best && i < arg)) { best = d2; arg = i; }
+      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
     }
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
   }
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_csr(const int64_t *__restr
     for (int t = 0; t < cn; ++t) {
       const int i = min(max(lst[t], 0), k - 1);
       const double d2 = sqdist_csr_wave(indices + s, values + s, len, W + (int64_t)i * dim, wn64[i], xn, dim, lane);
-      if (d2 < best || (d2 == best && i < arg)) { best = d2; arg = i; }
+      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
     }
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;
   }

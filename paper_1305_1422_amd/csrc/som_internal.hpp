@@ -395,6 +395,13 @@ hipError_t launch_fill_uniform(som_ctx *c, float *W, int64_t count, uint64_t see
 hipError_t launch_fill_zero_u32(hipStream_t s, void *p, int64_t count_u32);
 hipError_t launch_probe_xcc(hipStream_t stream, int32_t *out, int n_blocks);
 
+// Does node i at squared distance d2 take the place of node arg at `best`?  Nearer, or as near with a lower index; a
+// distance of +inf never does (a plain scan from best = +inf with a strict comparison, so that an instance at no finite
+// distance of any node gets node 0 whatever order the nodes come in).
+__device__ __forceinline__ bool nearer(double d2, int i, double best, int arg) {
+  return d2 < best || (d2 == best && best < INFINITY && i < arg);
+}
+
 // ---------------------------------------------------------------- device helpers
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

@@ -76,3 +76,27 @@ def test_non_finite_rows():
         assert np.all(b[[3, 5, 6]] == 0) and not np.isin(b[keep], [hit, (hit + 1) % len(W)]).any()
         same = keep[~np.isin(want[keep], [hit, (hit + 1) % len(W)])]
         assert np.array_equal(b[same], want[same])
+
+
+@pytest.mark.parametrize("filt", ["auto", "split_f16", "two_level", "fp32"])
+@pytest.mark.parametrize("n,rows,cols,dim", [(40, 12, 12, 20), (66000, 4, 5, 5), (20, 40, 40, 700), (64, 5, 8, 700)])
+def test_no_finite_distance_gives_node_0(oracle, filt, n, rows, cols, dim):
+    """An instance with an infinite component is at no finite distance of any node, whatever node 0 holds: a NaN or an
+    infinity of its own makes its distance a NaN while the others are at +inf.  The answer is node 0 all the same, by
+    every filter and by the direct search in one kernel (wavefronts that share the nodes or own an instance tile), with
+    shared features, and merged from groups."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(5400 + n)
+    X = rng.random((n, dim)).astype(np.float32)
+    X[3, 1], X[5, 0], X[6, 2] = np.inf, -np.inf, np.nan
+    for bad in (np.nan, np.inf):
+        W = rng.random((rows * cols, dim)).astype(np.float32)
+        W[0, :3] = bad
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter=filt)
+        b = som.bmus(P.to_dev(X)).cpu().numpy()
+        som.close()
+        m = min(n, 500)
+        assert np.array_equal(b[[3, 5, 6]], oracle.bmu_dense(X[[3, 5, 6]], W))
+        assert np.all(b[[3, 5, 6]] == 0)
+        keep = np.setdiff1d(np.arange(m), [3, 5, 6])
+        P.check_bmus_dense(oracle, X[keep], W, b[keep])

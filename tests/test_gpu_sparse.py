@@ -513,3 +513,30 @@ def test_full_scan_of_instances_with_hundreds_of_near_copies(oracle, copies, row
     assert rescanned >= 24, (refined, collected, rescanned)                 # the rows of 511 nonzeros and more, at least
     P.check_bmus_csr(oracle, csr, dim, W, b)
     assert b[6] == exact[0]                                                  # exact zero distance: no band, the lowest copy
+
+
+@pytest.mark.parametrize("registered", [False, True])
+@pytest.mark.parametrize("n,rows,cols,dim", [(40, 12, 12, 90), (900, 40, 30, 3000)])
+def test_no_finite_distance_gives_node_0(oracle, n, rows, cols, dim, registered):
+    """As for dense rows: where node 0 holds a NaN or an infinity and the instance an infinity, its distance is a NaN and
+    the other nodes are at +inf; none is finite, so the answer is node 0."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8400 + n)
+    indptr, indices, values = sparse_zipf_csr(n, dim, 8401, mean_len=20.0, max_len=60)
+    values = values.copy()
+    hit = [3, 5]
+    values[indptr[3]], values[indptr[6] - 1] = np.inf, -np.inf
+    csr = (indptr, indices, values)
+    for bad in (np.nan, np.inf):
+        W = rng.random((rows * cols, dim)).astype(np.float32)
+        W[0] = bad
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        dev = P.csr_to_dev(csr)
+        if registered:
+            capi.som_set_data_csr(som.ctx, *dev)
+        b = som.bmus(dev).cpu().numpy()
+        som.close()
+        assert np.all(oracle.bmu_csr(P.csr_take_rows(csr, hit), dim, W) == 0)
+        assert np.all(b[hit] == 0)
+        keep = np.setdiff1d(np.arange(n), hit)
+        P.check_bmus_csr(oracle, csr, dim, W, b, rows=keep)
