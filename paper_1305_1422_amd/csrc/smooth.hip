@@ -261,7 +261,7 @@ static int scale_cooling_of(const som_ctx *c, int cooling) { return c->scale_coo
 static bool direct_neighbourhood(const som_ctx *c) { return c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact; }
 static bool small_smoothing(const som_ctx *c);
 
-// `search`: a BMU search follows; its counters are cleared on the way.
+// `search`: a BMU search with a filter pass follows in the same call; its counters are cleared on the way.
 hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0, double sN,
                                int cooling, bool search) {
   EpochTables t;
@@ -276,7 +276,6 @@ hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, d
   t.function = c->nb_function; t.compact = c->nb_compact;
   t.zero = search ? reinterpret_cast<unsigned *>(c->list_counts) : nullptr;
   t.zero_words = search ? kListWords : 0;
-  if (search) c->search_zeroed = 1;
   const int64_t par = t.hex ? 2 : 1;
   int64_t work = 2 * (int64_t)c->cols + 1 + c->rows;
   if (t.GxT) work += par * par * c->cols * c->xi_pad + par * c->rows * c->e_pad;

@@ -308,19 +308,19 @@ struct StageTimer {
 };
 
 // ---------------------------------------------------------------- stages
-// List lengths, work counters and maxima of a search start from zero: cleared by the epoch's first launch, or here.
-static int begin_search(som_ctx *c) {
-  if (!c->search_zeroed) SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
-  c->search_zeroed = 0;
+// List lengths, work counters and maxima of a search start from zero.  `cleared`: the epoch's first launch, in the same
+// call, has seen to it (never an earlier call: what a call records into a graph must stand on its own).
+static int begin_search(som_ctx *c, bool cleared) {
+  if (!cleared) SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->list_counts, kListWords));
   return SOM_OK;
 }
 
 // Everything the filter pass needs besides the instances' own norms: centring vector (unless the
 // data are the registered set, whose vector is kept), centred code book and node constants, and
 // for the split-fp16 filter the fp16 planes of both operands.
-static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, bool have_xn) {
+static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, bool have_xn, bool cleared) {
   StageTimer t(c, 5);
-  int rc = begin_search(c);
+  int rc = begin_search(c, cleared);
   if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = two_level_ready(c, n);
@@ -375,11 +375,12 @@ static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float 
   return SOM_OK;
 }
 
-static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn) {
+static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn,
+                            bool cleared = false) {
   if (direct_search(c, n)) return bmu_search_direct(c, X, n, W, bmus);
   c->stats_none = 0;
   int rc = ensure_candidates(c, n, true);
-  if (!rc) rc = prepare_dense(c, X, n, W, have_xn);
+  if (!rc) rc = prepare_dense(c, X, n, W, have_xn, cleared);
   if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = two_level_ready(c, n);
@@ -405,7 +406,7 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
 // vector (mean of the code-book rows) with the quantisation steps, node constants, the transposed 16-bit
 // code book and the scaled values.
 static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
-                       int64_t nnz, const float *W, bool have_xn) {
+                       int64_t nnz, const float *W, bool have_xn, bool cleared) {
   if (nnz > c->vq_cap) {
     (void)hipStreamSynchronize(c->stream);
     dev_free(c->vq);
@@ -423,7 +424,7 @@ static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices
   // centring vector of the sparse search: the mean of the code-book rows (changes every epoch);
   // it overwrites the one a registered dense training set may have cached
   if (c->data_kind == 1) { c->d_norms_valid = 0; c->d_split_valid = 0; }
-  rc = begin_search(c);
+  rc = begin_search(c, cleared);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_codebook_means_and_steps(c, W));
   SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
@@ -453,7 +454,7 @@ struct PlaneOperands {
 static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split, bool coarse);
 
 static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
-                                 int64_t n, const float *W, int32_t *bmus) {
+                                 int64_t n, const float *W, int32_t *bmus, bool cleared) {
   int rc = ensure_candidates(c, n, true);
   if (rc) return rc;
   c->stats_none = 0;
@@ -463,7 +464,7 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
   c->two_level_n = coarse ? n : 0;
   {
     StageTimer t(c, 5);
-    rc = begin_search(c);
+    rc = begin_search(c, cleared);
     if (rc) return rc;
     SOM_LAUNCH(c, launch_codebook_planes(c, W, true /* |w|^2 in fp64 for the sparse exact kernels */, coarse));
     if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W, coarse ? c->pos_of : nullptr));
@@ -485,9 +486,9 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
 }
 
 static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
-                          int64_t n, int64_t nnz, const float *W, int32_t *bmus, bool have_xn) {
-  if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus);
-  int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn);
+                          int64_t n, int64_t nnz, const float *W, int32_t *bmus, bool have_xn, bool cleared = false) {
+  if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus, cleared);
+  int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn, cleared);
   if (rc) return rc;
   c->stats_none = 0;
   ensure_rescan_copy(c);
@@ -902,8 +903,8 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   bool reg = false;
   if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
-  rc = bmu_search_dense(c, data, n, codebook, bmus, reg);
+  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, !direct));
+  rc = bmu_search_dense(c, data, n, codebook, bmus, reg, true);
   if (rc) return rc;
   return update_dense(c, data, n, bmus, codebook);
 }
@@ -924,7 +925,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
   }
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
-  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg);
+  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true);
   if (rc) return rc;
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
 }
@@ -1001,12 +1002,13 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (!rc && !dense && !c->csrd_on) rc = registered_hot(c);
   if (rc) return rc;
   for (int e = 0; e < n_epochs; ++e) {
-    SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, true));
+    SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, !direct));
     if (dense) {
-      rc = bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true);
+      rc = bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true);
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
     } else {
-      rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true);
+      rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
+                          true);
       if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, bmus, codebook);
     }
     if (rc) return rc;
@@ -1082,7 +1084,6 @@ int som_validate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, 
   if (rc) return rc;
   int32_t *flag = c->list_counts + 3;
   int32_t bad = 0;
-  c->search_zeroed = 0;
   SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, flag, 1));
   SOM_LAUNCH(c, launch_validate_csr(c, indptr, indices, n, nnz, flag));
   SOM_LAUNCH(c, hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, c->stream));
@@ -1148,7 +1149,7 @@ int som_debug_scores_dense(som_ctx *c, const float *data, int64_t n, const float
   int rc = check_rows(c, n);
   if (!rc) rc = ensure_rows(c, n, true);
   if (!rc) rc = ensure_candidates(c, n, true);
-  if (!rc) rc = prepare_dense(c, data, n, codebook, false);
+  if (!rc) rc = prepare_dense(c, data, n, codebook, false, false);
   if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = c->filter == SOM_FILTER_TWO_LEVEL && two_level_ready(c, n);    // asked for by name: its coarse scores
@@ -1175,7 +1176,7 @@ int som_debug_scores_csr(som_ctx *c, const int64_t *indptr, const int32_t *indic
   if (!codebook || !scores || !mu_out || !margin_out) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_csr(c, indptr, indices, values, n, nnz);
   if (!rc) rc = ensure_rows(c, n, false);
-  if (!rc) rc = prepare_csr(c, indptr, indices, values, n, nnz, codebook, false);
+  if (!rc) rc = prepare_csr(c, indptr, indices, values, n, nnz, codebook, false, false);
   if (rc) return rc;
   rc = codebook_for_sweep(c, codebook);
   if (rc) return rc;

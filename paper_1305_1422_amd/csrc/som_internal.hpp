@@ -189,7 +189,6 @@ struct som_ctx {
   int64_t max_chunks;
   void *direct_rec;       // records of the direct search (bmu_direct.hip), direct_cap bytes
   size_t direct_cap;
-  int search_zeroed;      // list_counts has been cleared for the next search (by k_epoch_tables)
   int stats_none;         // the most recent search left nothing to the exact stage (direct search)
 
   // hot-column split of the registered sparse training set (csr_hot.hip); built on first use

@@ -1,0 +1,60 @@
+"""Calls recorded into a HIP graph: every call clears the counters and lists that its own search appends to, so that a
+recorded search does not build on what another call did, or was only recorded to do."""
+import numpy as np
+import pytest
+
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("filt", ["split_f16", "two_level", "fp32"])
+def test_filtered_search_beside_a_direct_epoch(oracle, filt):
+    """A map full of near-copies (every list of the exact stage is in use).  A small epoch, searched without a filter
+    pass, and a filtered search are recorded one after the other; an eager filtered search runs while the recorded epoch
+    has not, and between the replays."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9100)
+    rows, cols, dim, n = 24, 25, 40, 1500
+    means = rng.random((12, dim))
+    W = (means[rng.integers(0, 12, rows * cols)] + 1e-7 * rng.standard_normal((rows * cols, dim))).astype(np.float32)
+    X = (means[rng.integers(0, 12, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    small = rng.random((30, dim)).astype(np.float32)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        Xd, Sd, Wd = P.to_dev(X), P.to_dev(small), P.to_dev(W)
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        b_small = torch.empty(30, dtype=torch.int32, device="cuda")
+        b, b_eager = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+
+        def both():
+            som.codebook.copy_(Wd)
+            som.set_filter("auto")
+            som.train_epoch(Sd, 1.0, bmus=b_small)
+            som.codebook.copy_(Wd)
+            som.set_filter(filt)
+            som.bmus(Xd, b)
+
+        both()                                    # allocates what the recorded calls need
+        want_small, want = b_small.cpu().numpy(), b.cpu().numpy()
+        stats = som.stats()
+        assert stats[1] > 0                       # the lists are in use
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            both()
+        som.bmus(Xd, b_eager)
+        assert np.array_equal(b_eager.cpu().numpy(), want) and som.stats() == stats
+        for _ in range(4):
+            b.fill_(-1)
+            b_small.fill_(-1)
+            graph.replay()
+            assert np.array_equal(b.cpu().numpy(), want) and np.array_equal(b_small.cpu().numpy(), want_small)
+            assert som.stats() == stats
+            som.bmus(Xd, b_eager)
+            assert np.array_equal(b_eager.cpu().numpy(), want)
+        stream.synchronize()
+        som.close()
+    P.check_bmus_dense(oracle, X, W, want)
