@@ -82,50 +82,55 @@ __device__ __forceinline__ bool direct_decided(const DirectBest &r, double limit
   return r.arg != 0x7fffffff && r.second > limit;          // false on NaNs
 }
 
-// Plain distances of four rows by a wavefront, every one with the same order of additions; 256 features of all
-// five rows are loaded before the first is used.
-__device__ __forceinline__ void direct_distance4_wave(const float *__restrict__ x, const float *__restrict__ W,
-                                                      const int (&id)[4], int dim, int lane, double (&d2)[4]) {
-#pragma unroll
-  for (int u = 0; u < 4; ++u) d2[u] = 0.0;
-  for (int c0 = 0; c0 < dim; c0 += 4 * kWave) {
-    float xv[4], wv[4][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = min(c0 + q * kWave + lane, dim - 1);
-      xv[q] = x[c];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) wv[u][q] = W[(int64_t)id[u] * dim + c];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool on = c0 + q * kWave + lane < dim;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double d = on ? (double)xv[q] - (double)wv[u][q] : 0.0;
-        d2[u] += d * d;
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) d2[u] = wave_sum(d2[u]);
-}
-
-// Adds the nodes lo .. hi - 1, or those listed, to a wavefront's running plain minimum.
-__device__ __forceinline__ void direct_plain(const float *__restrict__ x, const float *__restrict__ W, int lo, int hi,
-                                             const int *list, int dim, int lane, double &best, int &arg) {
-  for (int i = lo; i < hi; i += 4) {
+// Adds the nodes node(lo) .. node(hi - 1) to the lanes' running plain minima.  A node is taken by a team of lanes, four
+// features a lane (rows of up to 4 features: a lane per node; beyond 128: the wavefront), four nodes per team at once,
+// so that a short row leaves no lanes idle (1,000,000 x 10 on 100 nodes, 20 copies of 5 rows: 3,670 -> 910 us); the additions of a node come in the same order whichever team has it.
+template <bool kWide, typename Node>
+__device__ __forceinline__ void direct_plain(const float *__restrict__ x, const float *__restrict__ W, int lo, int hi, Node node,
+                                             int dim, int lane, double &best, int &arg) {
+  int team = 1;
+  while (team < kWave && 4 * team < dim) team *= 2;            // uniform
+  const int teams = kWave / team, own = lane / team, part = 4 * (lane & (team - 1));
+  for (int i = lo; i < hi; i += 4 * teams) {
     int id[4];
     double d2[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int at = min(i + u, hi - 1);
-      id[u] = list ? __builtin_amdgcn_readfirstlane(list[at]) : at;
+      id[u] = node(min(i + u * teams + own, hi - 1));
+      d2[u] = 0.0;
     }
-    direct_distance4_wave(x, W, id, dim, lane, d2);
+    for (int c0 = 0; c0 < dim; c0 += 4 * team) {
+      const int c = c0 + part;
+      f32x4r xv = row_load<kWide>(x, c, dim), wv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) wv[u] = row_load<kWide>(W + (int64_t)id[u] * dim, c, dim);
+      row_tail<kWide>(xv, c, dim);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        row_tail<kWide>(wv[u], c, dim);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double d = (double)xv[e] - (double)wv[u][e];
+          d2[u] += d * d;
+        }
+      }
+    }
+    for (int o = team / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) d2[u] += __shfl_xor(d2[u], o, kWave);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (nearer(d2[u], id[u], best, arg)) { best = d2[u]; arg = id[u]; }
+  }
+}
+
+// The minima of 64 lanes as one, in all of them.
+__device__ __forceinline__ void direct_plain_merge(double &best, int &arg) {
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const double b = __shfl_xor(best, o, kWave);
+    const int a = __shfl_xor(arg, o, kWave);
+    if (nearer(b, a, best, arg)) { best = b; arg = a; }
   }
 }
 
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const double s = fma(-2.0, acc[v], w2);
-        second[v] = fmin(second[v], fmax(best[v], s));      // (a NaN score makes the instance an open one)
+        second[v] = fmin(second[v], fmax(best[v], s));      // (a NaN score is passed over, as its distance would be)
         arg[v] = s < best[v] ? node : arg[v];
         best[v] = fmin(best[v], s);
       }
@@ -376,69 +381,93 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
     const int cnt = __builtin_amdgcn_readfirstlane(s_cnt[team][q]);
     double b = INFINITY;
     int a = 0x7fffffff;
-    if (cnt <= kDirectList) direct_plain(X + (j0 + q) * dim, W, 0, cnt, &s_list[team][q][0], dim, lane, b, a);
-    else direct_plain(X + (j0 + q) * dim, W, 0, k, nullptr, dim, lane, b, a);
+    const int *listed = &s_list[team][q][0];
+    if (cnt <= kDirectList) direct_plain<kWide>(X + (j0 + q) * dim, W, 0, cnt, [&](int p) { return listed[p]; }, dim, lane, b, a);
+    else direct_plain<kWide>(X + (j0 + q) * dim, W, 0, k, [](int p) { return p; }, dim, lane, b, a);
+    direct_plain_merge(b, a);
     if (lane == 0) bmus[j0 + q] = a == 0x7fffffff ? 0 : a;
   }
 }
 
-// Merges the groups' records: kWaves wavefronts per instance, the more the fewer instances there are.  An
-// instance they leave open is decided by the plain distances: of a group's best node alone where only that one is
-// inside the limit, else of all nodes of the group (trained maps hold exact copies of nodes side by side, so this is
-// not rare).  What bounds it is the latency of one load after the other, so a lane holds a group's record (walked one
-// by one they were half of the time), and sixteen wavefronts take four nodes each of a group of 64 (64 instances, 2,500
-// nodes, 1,000 features, most instances open: 53 us with four wavefronts, 25 with sixteen).
-template <int kWaves>
-__global__ __launch_bounds__(kWaves > 4 ? 64 * kWaves : 256) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
-                                                      int groups, int nodes_per_group, const float *__restrict__ X, int64_t n,
-                                                      const float *__restrict__ W, int k, int dim,
-                                                      int32_t *__restrict__ bmus) {
-  constexpr int kBlockWaves = kWaves > 4 ? kWaves : 4;
-  __shared__ double s_d2[kBlockWaves];
-  __shared__ int s_id[kBlockWaves];
+// Merges the groups' records.  A wavefront per instance merges them, a lane per record; the instances they leave open are
+// then decided one after the other by the whole workgroup, by plain distances: of a group's best node alone where only
+// that one is inside the limit, else of all nodes of the group.  What bounds that is the latency of one load after the
+// other, so the nodes of all groups in question are shared out evenly over the sixteen wavefronts, and a workgroup
+// takes no more instances than two workgroups per CU leave it (per_block <= 16).  Measured, search and merge, a wavefront
+// per open instance from 1,024 instances on and 64 nodes one after the other / as it is now: 5,000 x 20 on a trained map
+// of 2,500 nodes 162 / 52 us, 1,500 x 20 on 2,500 nodes of which each has 19 exact copies 677 / 93.
+constexpr int kMergeWaves = 16;
+
+template <bool kWide>
+__global__ __launch_bounds__(64 * kMergeWaves) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
+                                                                   int groups, int nodes_per_group, int per_block,
+                                                                   const float *__restrict__ X, int64_t n,
+                                                                   const float *__restrict__ W, int k, int dim,
+                                                                   int32_t *__restrict__ bmus) {
+  __shared__ double s_limit[kMergeWaves], s_d2[kMergeWaves];
+  __shared__ int s_open[kMergeWaves], s_id[kMergeWaves], s_one[kWave], s_first[kWave];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int part = wave % kWaves;
-  const int64_t j = (int64_t)blockIdx.x * (kBlockWaves / kWaves) + wave / kWaves;
-  if (j >= n) return;                           // uniform over the workgroup, or (kWaves == 1) without barriers below
-  DirectBest r = direct_none();
-  for (int v = lane; v < groups; v += kWave) direct_merge(r, rec[(int64_t)v * n + j]);      // every wavefront all of them
-  direct_row_merge(r);
+  const int64_t j0 = (int64_t)blockIdx.x * per_block;
+  if (wave < per_block && j0 + wave < n) {
+    const int64_t j = j0 + wave;
+    DirectBest r = direct_none();
+    for (int v = lane; v < groups; v += kWave) direct_merge(r, rec[(int64_t)v * n + j]);
+    direct_row_merge(r);
 #pragma unroll
-  for (int o = 16; o <= 32; o <<= 1) {
-    const DirectBest b{__shfl_xor(r.best, o, kWave), __shfl_xor(r.second, o, kWave), __shfl_xor(r.wmax, o, kWave),
-                       __shfl_xor(r.arg, o, kWave)};
-    direct_merge(r, b);
-  }
-  const double limit = direct_limit(r, xn[j], dim);
-  if (direct_decided(r, limit)) {
-    if (lane == 0 && part == 0) bmus[j] = r.arg;
-    return;                                     // uniform over the instance's wavefronts
-  }
-  double b = INFINITY;
-  int a = 0x7fffffff;
-  int turn = 0;                                 // single nodes go to the wavefronts in turn
-  for (int v0 = 0; v0 < groups; v0 += kWave) {
-    const int v = v0 + lane;
-    const DirectBest q = v < groups ? rec[(int64_t)v * n + j] : direct_none();
-    int lo = v * nodes_per_group, hi = min(lo + nodes_per_group, k);
-    if (q.second > limit && (unsigned)q.arg < (unsigned)k) { lo = q.arg; hi = lo + 1; }
-    // (a NaN limit keeps every group)
-    for (unsigned long long kept = __ballot(v < groups && !(q.best > limit)); kept; kept &= kept - 1, ++turn) {
-      const int from = __ffsll((long long)kept) - 1;
-      const int glo = __builtin_amdgcn_readlane(lo, from), ghi = __builtin_amdgcn_readlane(hi, from);
-      const int share = ((ghi - glo + kWaves - 1) / kWaves + 3) / 4 * 4;
-      const int at = glo + (part + turn) % kWaves * share;
-      direct_plain(X + j * dim, W, at, min(at + share, ghi), nullptr, dim, lane, b, a);
+    for (int o = 16; o <= 32; o <<= 1) {
+      const DirectBest b{__shfl_xor(r.best, o, kWave), __shfl_xor(r.second, o, kWave), __shfl_xor(r.wmax, o, kWave),
+                         __shfl_xor(r.arg, o, kWave)};
+      direct_merge(r, b);
     }
+    const double limit = direct_limit(r, xn[j], dim);
+    const bool decided = direct_decided(r, limit);
+    if (lane == 0) {
+      s_open[wave] = !decided;
+      s_limit[wave] = limit;
+      if (decided) bmus[j] = r.arg;
+    }
+  } else if (lane == 0) {
+    s_open[wave] = 0;
   }
-  if (kWaves > 1) {
+  __syncthreads();
+  for (int q = 0; q < per_block; ++q) {
+    if (!s_open[q]) continue;                   // uniform
+    const int64_t j = j0 + q;
+    const double limit = s_limit[q];
+    double b = INFINITY;
+    int a = 0x7fffffff;
+    for (int v0 = 0; v0 < groups; v0 += kWave) {
+      const int v = v0 + lane;
+      const DirectBest r = v < groups ? rec[(int64_t)v * n + j] : direct_none();
+      const bool kept = v < groups && !(r.best > limit);            // (a NaN limit keeps every group)
+      const bool one = kept && r.second > limit && (unsigned)r.arg < (unsigned)k;
+      const unsigned long long ones = __ballot(one), whole = __ballot(kept && !one), below = (1ull << lane) - 1ull;
+      if (wave == 0) {
+        if (one) s_one[__popcll(ones & below)] = r.arg;
+        else if (kept) s_first[__popcll(whole & below)] = v * nodes_per_group;
+      }
+      __syncthreads();
+      const int singles = __popcll(ones), total = singles + __popcll(whole) * nodes_per_group;
+      const int share = (total + kMergeWaves - 1) / kMergeWaves, at = wave * share;
+      direct_plain<kWide>(X + j * dim, W, at, min(at + share, total), [&](int p) {
+        if (p < singles) return s_one[p];
+        const int g = (p - singles) / nodes_per_group;
+        return min(s_first[g] + (p - singles) - g * nodes_per_group, k - 1);       // (the last group may be short)
+      }, dim, lane, b, a);
+      __syncthreads();
+    }
+    direct_plain_merge(b, a);
     if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
     __syncthreads();
-    for (int v = 0; v < kWaves; ++v)
-      if (nearer(s_d2[v], s_id[v], b, a)) { b = s_d2[v]; a = s_id[v]; }
+    if (wave == 0) {
+      b = lane < kMergeWaves ? s_d2[lane] : INFINITY;
+      a = lane < kMergeWaves ? s_id[lane] : 0x7fffffff;
+      direct_plain_merge(b, a);
+      if (lane == 0) bmus[j] = a == 0x7fffffff ? 0 : a;
+    }
+    __syncthreads();
   }
-  if (lane == 0 && part == 0) bmus[j] = a == 0x7fffffff ? 0 : a;
 }
 
 struct DirectPlan {
@@ -528,15 +557,15 @@ hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const flo
 #undef SOM_DIRECT_HELD
 #undef SOM_DIRECT
   if (p.groups > 1) {
-    if (n <= c->n_cu)          // a workgroup per CU
-      hipLaunchKernelGGL(k_direct_merge<16>, dim3((unsigned)n), dim3(1024), 0, c->stream, rec, xn, p.groups,
-                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
-    else if (n <= 4 * c->n_cu)
-      hipLaunchKernelGGL(k_direct_merge<4>, dim3((unsigned)n), dim3(256), 0, c->stream, rec, xn, p.groups,
-                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
+    int64_t per_block = (n + 2 * (int64_t)c->n_cu - 1) / (2 * (int64_t)c->n_cu);
+    if (per_block > kMergeWaves) per_block = kMergeWaves;
+    const dim3 grid((unsigned)((n + per_block - 1) / per_block));
+    if (c->dim >= 4)
+      hipLaunchKernelGGL(k_direct_merge<true>, grid, dim3(64 * kMergeWaves), 0, c->stream, rec, xn, p.groups,
+                         p.per_group * 16 * p.nt, (int)per_block, X, n, W, c->k, c->dim, bmus);
     else
-      hipLaunchKernelGGL(k_direct_merge<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, c->stream, rec, xn, p.groups,
-                         p.per_group * 16 * p.nt, X, n, W, c->k, c->dim, bmus);
+      hipLaunchKernelGGL(k_direct_merge<false>, grid, dim3(64 * kMergeWaves), 0, c->stream, rec, xn, p.groups,
+                         p.per_group * 16 * p.nt, (int)per_block, X, n, W, c->k, c->dim, bmus);
   }
   return hipGetLastError();
 }

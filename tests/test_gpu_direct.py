@@ -27,8 +27,11 @@ def _bmus(W, X, rows, cols, **kw):
     (40, 9, 9, 15), (300, 20, 20, 16), (1000, 20, 20, 17), (700, 33, 31, 33), (65, 20, 13, 64),
     (4097, 37, 29, 49), (900, 17, 8, 65), (33, 40, 40, 130),                        # the nodes over the wavefronts / groups
     (7, 50, 50, 511), (64, 30, 30, 513), (3, 40, 50, 1000),                         # the features over the wavefronts
-    (256, 40, 50, 520), (257, 40, 50, 520), (1030, 30, 40, 100),                    # 16, 4, 1 wavefronts merge an instance
-    (70000, 3, 7, 6), (66001, 10, 12, 18),                                          # a wavefront per 16 instances
+    (512, 40, 50, 520), (513, 40, 50, 520), (1537, 30, 40, 100), (4200, 40, 25, 100), (8200, 100, 25, 20),   # 1 .. 16 instances merged by a workgroup
+    (11000, 20, 20, 64), (12001, 31, 31, 33),                                       # ... in tiles of 64 nodes
+    (64, 5, 8, 700), (8000, 5, 8, 200), (20000, 10, 10, 64),                        # one group of nodes: no merge
+    (3, 250, 250, 3), (9, 70, 300, 2),                                              # groups, rows shorter than a load
+    (70000, 3, 7, 6), (66001, 10, 12, 18), (66000, 4, 4, 9), (66000, 6, 10, 80),    # a wavefront per 16 instances
 ])
 def test_matches_the_oracle(oracle, n, rows, cols, dim):
     rng = np.random.default_rng(5100 + n + dim)
@@ -49,7 +52,8 @@ def test_matches_the_oracle(oracle, n, rows, cols, dim):
         assert b[0] == 1 and b[n // 2] == k // 2
 
 
-@pytest.mark.parametrize("n,dim,bubble", [(50, 40, False), (50, 600, False), (70000, 4, False), (50, 40, True)])
+@pytest.mark.parametrize("n,dim,bubble", [(50, 40, False), (50, 600, False), (70000, 4, False), (50, 40, True), (1200, 200, False),
+                                          (1200, 200, True), (3000, 13, False), (800, 1000, False)])
 def test_more_copies_than_a_list_holds(oracle, n, dim, bubble):
     rng = np.random.default_rng(5200 + dim)
     rows, cols = 20, 15
