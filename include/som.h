@@ -348,7 +348,9 @@ int som_set_smoothing(som_ctx *ctx, int form);
  *                  (128 instances, block) pairs only.  Needs 6 bytes per element of extra device memory
  *                  and 4 bytes per instance and node block.
  *   SOM_FILTER_AUTO (default)  small searches run without any filter pass, all distances in fp64 on the
- *                  matrix cores (some 1e9 multiply-adds in all; som_get_stats then reports zeros);
+ *                  matrix cores, wherever that is estimated to take less time than a filtered search (from
+ *                  400 nodes on up to some 1e9 to 1e10 multiply-adds in all, on smaller maps of few features
+ *                  up to any number of instances; som_get_stats then reports zeros);
  *                  beyond that SOM_FILTER_TWO_LEVEL for maps of 1,024 nodes or more whose table of
  *                  block minima (4 bytes x instances x nodes / 128) stays under 8 GiB, else
  *                  SOM_FILTER_SPLIT_F16.

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const double s = fma(-2.0, acc[v], w2);
-        second[v] = fmin(second[v], fmax(best[v], s));      // (a NaN score is passed over, as its distance would be)
+        second[v] = fmin(second[v], fmax(best[v], s));      // (a NaN score is no candidate; behind a finite one it leaves the instance open)
         arg[v] = s < best[v] ? node : arg[v];
         best[v] = fmin(best[v], s);
       }
@@ -514,14 +514,48 @@ static DirectPlan direct_plan(const som_ctx *c, int64_t n) {
   return p;
 }
 
-// Where the direct search wins.  It works off about 1.8e13 (padded) multiply-adds a second behind one launch; the
-// filtered search starts at 35 us more (60 with the second level, from 1,024 nodes on), takes 0.02 ns per code-book
-// entry for its planes and norms, and 0.4 ns per instance besides its matrix work, which is small at these sizes.  Measured, direct against filtered: 64 x 2,500
-// x 1,000 23 / 210 us, 4,000 x 1,024 x 256 58 / 122, 20,000 x 400 x 64 78 / 83, 1,000,000 x 100 x 10 227 / 476.
-bool direct_search_pays(const som_ctx *c, int64_t n) {
-  const double work = (double)n * (double)c->k * (double)((c->dim + 15) / 16 * 16);
-  return work <= 1.8e13 * ((c->k < 128 * kTwoLevelMinBlocks ? 35e-6 : 60e-6) + 0.4e-9 * (double)n +
-                         0.02e-9 * (double)c->k * (double)c->dim);
+// Where the direct search wins: estimates of both searches in microseconds, fitted to timings over maps of 100 to 40,000
+// nodes, rows of 10 to 1,000 features and 64 to 4,000,000 instances (unordered and trained code books, and such of
+// which every row has 19 copies).
+// Direct, in (16 x 16 x 16)-steps per SIMD, by the ways of sharing out: 0.2 a step, and besides what a wavefront waits
+// for between its tiles.  Where groups are merged, 1.45 times that, for the plain distances of open instances there: a
+// trained map leaves up to a third of them open (1,500 x 100 on 2,500 nodes: unordered 39, trained 60, all rows copied
+// 263 against 124 / 167 / 164 filtered).  The second sweep of the other forms needs no such allowance, since the
+// filtered search's exact stage grows by as much on such maps (12,000 x 64 on 400 nodes: 50 / 49 / 96 against
+// 62 / 92 / 123).
+static double direct_search_us(const som_ctx *c, int64_t n) {
+  const DirectPlan p = direct_plan(c, n);
+  const double nt16 = (double)((n + 15) / 16), steps = (double)((c->dim + 15) / 16), cu = (double)c->n_cu;
+  const double row = (double)p.nt * steps;               // steps of a tile of nodes with 16 instances
+  if (p.share == 1)                                      // (and the instances' rows, read once)
+    return 4.0 + nt16 / cu * 0.256 * (0.21 * p.tiles * row + 0.5 + 0.8 * fmin(steps, 4.0));
+  if (p.share == 8)
+    return 6.0 + fmax(nt16 / cu, 1.0) * (0.44 * ((p.tiles + 7) / 8) * row + (p.nt == 1 ? 1.7 : c->dim <= 64 ? 2.0 * steps : 0.0));
+  if (p.share == 4)                                      // whole turns of four tiles
+    return (p.groups > 1 ? 1.45 : 1.0) * (11.0 + (p.groups > 1 ? 0.26 : 0.36) * nt16 * ((p.tiles + 3) / 4 * 4) * row / (4.0 * cu));
+  return 1.45 * (14.0 + 0.21 * nt16 * p.tiles * row / (4.0 * cu));
+}
+
+// Filtered, on an unordered code book (a trained one costs up to half as much again): launches, the code book's planes,
+// per instance the exact stage and the matrix work; instances that are not registered bring their own planes.
+static double filtered_search_us(const som_ctx *c, int64_t n, bool registered) {
+  const double k = (double)c->k, dim = (double)c->dim;
+  const bool two_level = (c->k + 127) / 128 >= kTwoLevelMinBlocks;
+  double fixed = (two_level ? 84.0 : 40.0 + 0.004 * k) + 0.02 * dim + 2e-5 * k * dim;
+  double each = two_level ? 0.3e-6 * k + 0.5e-8 * k * dim : 0.04e-3 + 0.6e-6 * k + 0.6e-8 * k * dim;
+  if (!registered) {
+    fixed += 9.0;
+    each += 0.08e-3 + 1.5e-6 * dim;
+  }
+  return fixed + each * (double)n;
+}
+
+// The line lies where the two meet on an unordered code book, and 15 % beyond, since most maps are ordered ones.
+// Direct / filtered on both sides of it, registered, unordered: 12,000 x 64 on 400 nodes 50 / 48, 20,000 x 64 77 / 55;
+// 70,000 x 64 on 100 nodes 51 / 53, 150,000 x 64 105 / 65, 1,000,000 x 64 648 / 198; 400,000 x 16 on 400 nodes 174 / 182,
+// 1,000,000 x 16 413 / 318; 12,000 x 20 on 2,500 nodes 67 / 116, 35,000 x 20 195 / 156.
+bool direct_search_pays(const som_ctx *c, int64_t n, bool registered) {
+  return direct_search_us(c, n) <= 1.15 * filtered_search_us(c, n, registered);
 }
 
 size_t direct_record_bytes(const som_ctx *c, int64_t n) {

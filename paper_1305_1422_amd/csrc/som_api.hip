@@ -84,8 +84,10 @@ static void dev_free(T *&p) {
 }
 
 // Dense data searched in double precision outright (bmu_direct.hip)?  Only where the caller left the choice of the
-// filter to the library.
-static bool direct_search(const som_ctx *c, int64_t n) { return c->filter == SOM_FILTER_AUTO && direct_search_pays(c, n); }
+// filter to the library.  `registered`: the filtered search would find the instances' planes ready.
+static bool direct_search(const som_ctx *c, int64_t n, bool registered) {
+  return c->filter == SOM_FILTER_AUTO && direct_search_pays(c, n, registered);
+}
 
 // The dense filter runs on fp16 planes (one-level split pass or the two-level search).
 static bool uses_planes(const som_ctx *c) { return c->filter != SOM_FILTER_FP32; }
@@ -377,7 +379,6 @@ static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float 
 
 static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn,
                             bool cleared = false) {
-  if (direct_search(c, n)) return bmu_search_direct(c, X, n, W, bmus);
   c->stats_none = 0;
   int rc = ensure_candidates(c, n, true);
   if (!rc) rc = prepare_dense(c, X, n, W, have_xn, cleared);
@@ -800,12 +801,12 @@ int som_bmus_dense(som_ctx *c, const float *data, int64_t n, const float *codebo
   if (!c) return SOM_ERR_INVALID_ARG;
   if (!data || !codebook || !bmus) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
-  const bool direct = !rc && direct_search(c, n);
+  const bool reg = is_registered_dense(c, data, n);
+  const bool direct = !rc && direct_search(c, n, reg);
   if (!rc) rc = direct ? ensure_direct(c, n) : ensure_rows(c, n, true);
-  bool reg = false;
-  if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
+  if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
-  return bmu_search_dense(c, data, n, codebook, bmus, reg);
+  return direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg);
 }
 
 int som_bmus_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
@@ -897,14 +898,14 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   if (!data || !codebook || !bmus) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
-  const bool direct = !rc && direct_search(c, n);
+  const bool reg = is_registered_dense(c, data, n);
+  const bool direct = !rc && direct_search(c, n, reg);
   if (!rc && direct) rc = ensure_direct(c, n);
   if (!rc) rc = ensure_rows(c, n, true, !direct);
-  bool reg = false;
-  if (!rc && !direct && is_registered_dense(c, data, n)) { rc = registered_norms(c); reg = true; }
+  if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, !direct));
-  rc = bmu_search_dense(c, data, n, codebook, bmus, reg, true);
+  rc = direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg, true);
   if (rc) return rc;
   return update_dense(c, data, n, bmus, codebook);
 }
@@ -994,7 +995,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (!isfinite(radius0) || !isfinite(radiusN)) return fail(c, SOM_ERR_INVALID_ARG, "radius not finite");
   if (scale0 > 1.f || scaleN > 1.f) return fail(c, SOM_ERR_INVALID_ARG, "scale must be in (0, 1]");
   const bool dense = c->data_kind == 1;
-  const bool direct = dense && direct_search(c, c->d_n);
+  const bool direct = dense && direct_search(c, c->d_n, true);
   int rc = direct ? ensure_direct(c, c->d_n) : SOM_OK;
   if (!rc) rc = ensure_rows(c, c->d_n, dense, !direct);
   if (!rc && !direct) rc = registered_norms(c);
@@ -1004,7 +1005,8 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   for (int e = 0; e < n_epochs; ++e) {
     SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, !direct));
     if (dense) {
-      rc = bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true);
+      rc = direct ? bmu_search_direct(c, c->d_data, c->d_n, codebook, bmus)
+                  : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true);
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,

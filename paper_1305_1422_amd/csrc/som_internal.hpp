@@ -261,7 +261,7 @@ hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float
                                   float *out32);
 
 // bmu_direct.hip
-bool direct_search_pays(const som_ctx *c, int64_t n);
+bool direct_search_pays(const som_ctx *c, int64_t n, bool registered);
 size_t direct_record_bytes(const som_ctx *c, int64_t n);       // scratch it needs in c->direct_rec
 hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const float *W, const float *mask, int32_t *bmus);
 
