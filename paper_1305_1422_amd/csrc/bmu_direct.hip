@@ -161,7 +161,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
                                                                const float *__restrict__ W, int k, int dim,
                                                                const float *__restrict__ mask, int tiles_per_group,
                                                                int32_t *__restrict__ bmus,
-                                                               DirectBest *__restrict__ rec, double *__restrict__ xn_out) {
+                                                               DirectBest *__restrict__ rec, double *__restrict__ xn_out,
+                                                               int32_t *__restrict__ list_counts) {
   static_assert(kShare == 0 || kShare == 1 || kShare == kWaves, "a tile belongs to one wavefront or to the whole workgroup");
   constexpr bool kOwn = kShare == 1, kSplit = kShare == 0;
   constexpr int kTeams = kOwn ? kWaves : 1;      // instance tiles per workgroup
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
   const int l16 = lane & 15, g = lane >> 4;
   const int64_t j0 = ((int64_t)blockIdx.x * kTeams + team) * 16;
   if (j0 >= n) return;               // uniform over the workgroup, or (kOwn) without barriers below
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 3) list_counts[threadIdx.x] = 0;      // nothing for the exact stage
   const float *xr = X + (j0 + l16 < n ? j0 + l16 : n - 1) * dim;
   const int ntiles = (k + 16 * NT - 1) / (16 * NT);
   const int t0 = blockIdx.y * tiles_per_group;
@@ -572,7 +574,7 @@ hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const flo
   const int held = c->dim <= 64 ? (c->dim + 15) / 16 : 0;      // steps of 16 features kept in registers
 #define SOM_DIRECT(WV, SH, NTV, ST, WIDE)                                                                             \
   hipLaunchKernelGGL((k_direct_search<WV, SH, NTV, ST, WIDE>), dim3(gx, (unsigned)p.groups), dim3(64 * WV), 0, c->stream, \
-                     X, n, W, c->k, c->dim, mask, p.per_group, bmus, rec, xn)
+                     X, n, W, c->k, c->dim, mask, p.per_group, bmus, rec, xn, c->list_counts)
 #define SOM_DIRECT_HELD(WV, SH, NTV)                \
   switch (held) {                                   \
     case 0: SOM_DIRECT(WV, SH, NTV, 0, true); break; \

@@ -365,7 +365,6 @@ static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split,
 // Small search: one or two kernels, no filter pass and no per-instance preparation.
 static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus) {
   c->two_level_n = 0;
-  c->stats_none = 1;
   StageTimer t(c, 0);
   const float *mask = nullptr;
   if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) {
@@ -379,7 +378,6 @@ static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float 
 
 static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn,
                             bool cleared = false) {
-  c->stats_none = 0;
   int rc = ensure_candidates(c, n, true);
   if (!rc) rc = prepare_dense(c, X, n, W, have_xn, cleared);
   if (rc) return rc;
@@ -458,7 +456,6 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
                                  int64_t n, const float *W, int32_t *bmus, bool cleared) {
   int rc = ensure_candidates(c, n, true);
   if (rc) return rc;
-  c->stats_none = 0;
   ensure_rescan_copy(c);
   PlaneOperands swap(c);
   const bool coarse = two_level_ready(c, n);
@@ -491,7 +488,6 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus, cleared);
   int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn, cleared);
   if (rc) return rc;
-  c->stats_none = 0;
   ensure_rescan_copy(c);
   // registered rows whose frequent columns were split off: the sweeps walk the tail and start from the
   // matrix-core pass over the hot block; the exact kernels keep the caller's full rows
@@ -1204,11 +1200,6 @@ int som_debug_xcc_ids(int32_t *out, int n_blocks, void *hip_stream) {
 int som_get_stats(som_ctx *c, int64_t *out) {
   if (!c) return SOM_ERR_INVALID_ARG;
   if (!out) return fail(c, SOM_ERR_INVALID_ARG, "out is NULL");
-  if (c->stats_none) {
-    out[0] = out[1] = out[2] = 0;
-    const hipError_t e = hipStreamSynchronize(c->stream);
-    return e == hipSuccess ? SOM_OK : dev_fail(c, e, "som_get_stats");
-  }
   int32_t h[3] = {0, 0, 0};
   hipError_t e = hipMemcpyAsync(h, c->list_counts, sizeof(h), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

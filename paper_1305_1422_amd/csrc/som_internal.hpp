@@ -189,7 +189,6 @@ struct som_ctx {
   int64_t max_chunks;
   void *direct_rec;       // records of the direct search (bmu_direct.hip), direct_cap bytes
   size_t direct_cap;
-  int stats_none;         // the most recent search left nothing to the exact stage (direct search)
 
   // hot-column split of the registered sparse training set (csr_hot.hip); built on first use
   int hot_valid;          // 0: not examined yet; 1: examined (hot_on says whether the split is in use)

@@ -58,3 +58,33 @@ def test_filtered_search_beside_a_direct_epoch(oracle, filt):
         stream.synchronize()
         som.close()
     P.check_bmus_dense(oracle, X, W, want)
+
+
+def test_stats_are_those_of_the_search_that_ran_last():
+    """The counters belong to the search that the GPU ran last, whether it was called or replayed: a search without a
+    filter pass leaves zeros, a replayed filtered one its own figures."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9200)
+    rows, cols, dim, n = 20, 20, 30, 900
+    means = rng.random((10, dim))
+    W = (means[rng.integers(0, 10, rows * cols)] + 1e-7 * rng.standard_normal((rows * cols, dim))).astype(np.float32)
+    X = (means[rng.integers(0, 10, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        Xd = P.to_dev(X)
+        b = torch.empty(n, dtype=torch.int32, device="cuda")
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="split_f16")
+        som.bmus(Xd, b)
+        stats = som.stats()
+        assert stats[1] > 0
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            som.bmus(Xd, b)
+        som.set_filter("auto")
+        for _ in range(3):
+            som.bmus(Xd, b)
+            assert som.stats() == (0, 0, 0)
+            graph.replay()
+            assert som.stats() == stats
+        som.close()
