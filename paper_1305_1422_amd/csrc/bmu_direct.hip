@@ -398,10 +398,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
 // takes no more instances than two workgroups per CU leave it (per_block <= 16).  Measured, search and merge, a wavefront
 // per open instance from 1,024 instances on and 64 nodes one after the other / as it is now: 5,000 x 20 on a trained map
 // of 2,500 nodes 162 / 52 us, 1,500 x 20 on 2,500 nodes of which each has 19 exact copies 677 / 93.
+// With nothing open it is a launch of 2 to 3 us: the open ones come from one read, and 64 registers let two workgroups
+// share a CU (4,097 x 33 on 1,073 nodes, the whole search: 31.7 us with more registers and a look at each instance, 30.2).
 constexpr int kMergeWaves = 16;
 
 template <bool kWide>
-__global__ __launch_bounds__(64 * kMergeWaves) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
+__global__ __launch_bounds__(64 * kMergeWaves, kWide ? 8 : 4) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
                                                                    int groups, int nodes_per_group, int per_block,
                                                                    const float *__restrict__ X, int64_t n,
                                                                    const float *__restrict__ W, int k, int dim,
@@ -433,8 +435,9 @@ __global__ __launch_bounds__(64 * kMergeWaves) void k_direct_merge(const DirectB
     s_open[wave] = 0;
   }
   __syncthreads();
-  for (int q = 0; q < per_block; ++q) {
-    if (!s_open[q]) continue;                   // uniform
+  // (one read for all of them; uniform)
+  for (unsigned long long open = __ballot(lane < per_block && s_open[lane & (kMergeWaves - 1)]); open; open &= open - 1) {
+    const int q = __ffsll((long long)open) - 1;
     const int64_t j = j0 + q;
     const double limit = s_limit[q];
     double b = INFINITY;
