@@ -563,9 +563,12 @@ bool direct_search_pays(const som_ctx *c, int64_t n, bool registered) {
   return direct_search_us(c, n) <= 1.15 * filtered_search_us(c, n, registered);
 }
 
-size_t direct_record_bytes(const som_ctx *c, int64_t n) {
-  const DirectPlan p = direct_plan(c, n);
-  return p.groups > 1 ? (size_t)p.groups * (size_t)n * sizeof(DirectBest) + (size_t)n * sizeof(double) : 0;
+// Room for the records of any number of instances, so that no call has to grow it: groups exist for fewer than 16 cu
+// instance tiles, no more of them than (5 cu - 1) / tiles + 1 nor than tiles of 16 nodes (3.3 MB on 256 CUs).
+size_t direct_record_doubles(const som_ctx *c) {
+  const size_t cu = (size_t)c->n_cu, tiles16 = ((size_t)c->k + 15) / 16;
+  const size_t tiles = 21 * cu < 16 * cu * tiles16 ? 21 * cu : 16 * cu * tiles16;
+  return 16 * (tiles * (sizeof(DirectBest) / sizeof(double)) + 16 * cu);
 }
 
 hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const float *W, const float *mask, int32_t *bmus) {
@@ -573,7 +576,7 @@ hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const flo
   const unsigned nt16 = (unsigned)((n + 15) / 16);
   const unsigned gx = p.share == 1 ? (nt16 + 3) / 4 : nt16;
   DirectBest *rec = p.groups > 1 ? reinterpret_cast<DirectBest *>(c->direct_rec) : nullptr;
-  double *xn = p.groups > 1 ? reinterpret_cast<double *>(rec + (size_t)p.groups * (size_t)n) : nullptr;
+  double *xn = p.groups > 1 ? reinterpret_cast<double *>(rec + (size_t)p.groups * (size_t)n) : nullptr;      // behind them
   const int held = c->dim <= 64 ? (c->dim + 15) / 16 : 0;      // steps of 16 features kept in registers
 #define SOM_DIRECT(WV, SH, NTV, ST, WIDE)                                                                             \
   hipLaunchKernelGGL((k_direct_search<WV, SH, NTV, ST, WIDE>), dim3(gx, (unsigned)p.groups), dim3(64 * WV), 0, c->stream, \

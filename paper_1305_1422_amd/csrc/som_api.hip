@@ -130,20 +130,6 @@ static void free_row_scratch(som_ctx *c) {
   c->csrd_on = 0;
 }
 
-// Records of the direct search.
-static int ensure_direct(som_ctx *c, int64_t n) {
-  const size_t need = direct_record_bytes(c, n);
-  if (need <= c->direct_cap) return SOM_OK;
-  (void)hipStreamSynchronize(c->stream);
-  if (c->direct_rec) (void)hipFree(c->direct_rec);
-  c->direct_rec = nullptr;
-  c->direct_cap = 0;
-  if (hipMalloc(&c->direct_rec, need) != hipSuccess)
-    return fail(c, SOM_ERR_ALLOC, "cannot allocate the records of %lld instances", (long long)n);
-  c->direct_cap = need;
-  return SOM_OK;
-}
-
 // Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
 // will run on them (false: the direct search, or an update alone).
 static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) {
@@ -727,7 +713,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   const size_t images = grid_type == SOM_GRID_HEXAGONAL ? 2 : 1;
   bool ok = dev_alloc(&c->wn32, (K + 127) / 128 * 128) && dev_alloc(&c->wn64, K) &&
             dev_alloc(&c->counts, K + 1) && dev_alloc(&c->group_local, 2 * (K + (K + 63) / 64)) && dev_alloc(&c->seg_off, K + 1) && dev_alloc(&c->chunk_off, K + 1) &&
-            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->dist_flag, K) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
+            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->direct_rec, direct_record_doubles(c)) && dev_alloc(&c->dist_flag, K) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
             dev_alloc(&c->gy, (size_t)rows) && dev_alloc(&c->params, 1) && dev_alloc(&c->list_counts, kListWords) &&
             dev_alloc(&c->mu, (size_t)dim) && dev_alloc(&c->mu_partial, (size_t)64 * dim) &&
             dev_alloc(&c->zero16, 16) && dev_alloc(&c->mu_norm2, 1) && dev_alloc(&c->wscale, 1) &&
@@ -770,7 +756,7 @@ void som_destroy(som_ctx *c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   free_row_scratch(c);
-  if (c->direct_rec) (void)hipFree(c->direct_rec);
+  dev_free(c->direct_rec);
   dev_free(c->wn32); dev_free(c->wn64); dev_free(c->counts); dev_free(c->group_local); dev_free(c->seg_off);
   dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->dist_flag); dev_free(c->row_hash); dev_free(c->dedup_keys);
   dev_free(c->dedup_lowest); dev_free(c->cntT); dev_free(c->gx); dev_free(c->gy);
@@ -799,7 +785,7 @@ int som_bmus_dense(som_ctx *c, const float *data, int64_t n, const float *codebo
   int rc = check_rows(c, n);
   const bool reg = is_registered_dense(c, data, n);
   const bool direct = !rc && direct_search(c, n, reg);
-  if (!rc) rc = direct ? ensure_direct(c, n) : ensure_rows(c, n, true);
+  if (!rc && !direct) rc = ensure_rows(c, n, true);
   if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
   return direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg);
@@ -896,7 +882,6 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
   const bool reg = is_registered_dense(c, data, n);
   const bool direct = !rc && direct_search(c, n, reg);
-  if (!rc && direct) rc = ensure_direct(c, n);
   if (!rc) rc = ensure_rows(c, n, true, !direct);
   if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
@@ -992,8 +977,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (scale0 > 1.f || scaleN > 1.f) return fail(c, SOM_ERR_INVALID_ARG, "scale must be in (0, 1]");
   const bool dense = c->data_kind == 1;
   const bool direct = dense && direct_search(c, c->d_n, true);
-  int rc = direct ? ensure_direct(c, c->d_n) : SOM_OK;
-  if (!rc) rc = ensure_rows(c, c->d_n, dense, !direct);
+  int rc = ensure_rows(c, c->d_n, dense, !direct);
   if (!rc && !direct) rc = registered_norms(c);
   if (!rc && !dense) rc = registered_csr_dense(c);
   if (!rc && !dense && !c->csrd_on) rc = registered_hot(c);

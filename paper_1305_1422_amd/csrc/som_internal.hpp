@@ -187,8 +187,7 @@ struct som_ctx {
   int32_t *chunk_node;    // [n/kChunkRows + k]
   float *partial;         // [n/kChunkRows + k][dim]
   int64_t max_chunks;
-  void *direct_rec;       // records of the direct search (bmu_direct.hip), direct_cap bytes
-  size_t direct_cap;
+  double *direct_rec;     // records of the direct search (bmu_direct.hip), direct_record_doubles()
 
   // hot-column split of the registered sparse training set (csr_hot.hip); built on first use
   int hot_valid;          // 0: not examined yet; 1: examined (hot_on says whether the split is in use)
@@ -261,7 +260,7 @@ hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float
 
 // bmu_direct.hip
 bool direct_search_pays(const som_ctx *c, int64_t n, bool registered);
-size_t direct_record_bytes(const som_ctx *c, int64_t n);       // scratch it needs in c->direct_rec
+size_t direct_record_doubles(const som_ctx *c);       // size of c->direct_rec, for any number of instances
 hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const float *W, const float *mask, int32_t *bmus);
 
 // bmu_dense.hip

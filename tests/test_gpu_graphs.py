@@ -88,3 +88,38 @@ def test_stats_are_those_of_the_search_that_ran_last():
             graph.replay()
             assert som.stats() == stats
         som.close()
+
+
+def test_smaller_calls_need_no_more_scratch(oracle):
+    """A context that has served a large set serves any smaller one without growing: it can be recorded, which rules out
+    an allocation and a wait.  (The other context sees to it that the kernels have been loaded.)"""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9300)
+    rows, cols, dim = 50, 50, 100
+    W = rng.random((rows * cols, dim)).astype(np.float32)
+    X = rng.random((20000, dim)).astype(np.float32)
+    sizes = (1500, 4000, 700, 64, 3)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        Xd = P.to_dev(X)
+        b = torch.empty(len(X), dtype=torch.int32, device="cuda")
+        other = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        want = {}
+        for n in sizes:
+            want[n] = other.bmus(Xd[:n]).cpu().numpy()
+            assert other.stats() == (0, 0, 0)            # searched without a filter pass
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        som.bmus(Xd, b)
+        stream.synchronize()
+        for n in sizes:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                som.bmus(Xd[:n], b[:n])
+            for _ in range(3):
+                b.fill_(-1)
+                graph.replay()
+                assert np.array_equal(b[:n].cpu().numpy(), want[n]) and int(b[n]) == -1
+        stream.synchronize()
+        som.close()
+        other.close()
+    P.check_bmus_dense(oracle, X[:1500], W, want[1500])
