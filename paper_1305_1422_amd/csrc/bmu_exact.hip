@@ -826,31 +826,62 @@ __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__r
   }
 }
 
-__global__ __launch_bounds__(256) void k_mark_nodes(const int32_t *__restrict__ bmus, int64_t n, int k, int32_t mark,
-                                                    int32_t *__restrict__ flag) {
+// owner[i] = one of the instances of node i, counted from one; which one does not matter.  Zero at all others: every entry
+// is cleared by the kernel below as it takes it.
+__global__ __launch_bounds__(256) void k_mark_nodes(const int32_t *__restrict__ bmus, int64_t n, int k, int32_t *__restrict__ owner) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (j < n && (unsigned)bmus[j] < (unsigned)k) flag[bmus[j]] = mark;
+  if (j < n && (unsigned)bmus[j] < (unsigned)k) owner[bmus[j]] = (int32_t)j + 1;
 }
 
-__global__ __launch_bounds__(256) void k_marked_norms(const float *__restrict__ W, int k, int dim, int32_t mark,
-                                                      const int32_t *__restrict__ flag, double *__restrict__ wn64) {
+// Looks through the instances or through the nodes, whichever are fewer, for the owners or the owned.  A workgroup looks at a stretch of them at once, then
+// takes the norms of those found one after the other.  (A walk over all nodes whatever n, a flag at a time: 10 rows on
+// 4,000,000 nodes 529 us for the distances instead of 17.)
+__global__ __launch_bounds__(256) void k_marked_norms(const float *__restrict__ W, int64_t n, int k, int dim,
+                                                      const int32_t *__restrict__ bmus, int32_t *__restrict__ owner,
+                                                      double *__restrict__ wn64) {
   __shared__ double s_part[4];
-  for (int i = blockIdx.x; i < k; i += gridDim.x) {
-    if (flag[i] != mark) continue;               // uniform
-    const float *w = W + (int64_t)i * dim;
-    double s[4] = {0, 0, 0, 0};
-    for (int c0 = 0; c0 < dim; c0 += 8 * 256) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = w[min(c0 + 256 * u + (int)threadIdx.x, dim - 1)];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s[u & 3] += c0 + 256 * u + (int)threadIdx.x < dim ? (double)v[u] * (double)v[u] : 0.0;
+  __shared__ int s_node[256], s_found;
+  const int tid = threadIdx.x;
+  const bool by_instance = n < k;
+  const int64_t items = by_instance ? n : k;
+  const int64_t per = (items + gridDim.x - 1) / gridDim.x, first = blockIdx.x * per;
+  const int64_t last = first + per < items ? first + per : items;
+  for (int64_t t0 = first; t0 < last; t0 += 256) {
+    if (tid == 0) s_found = 0;
+    __syncthreads();
+    const int64_t t = t0 + tid;
+    int i = -1;
+    if (t < last) {
+      if (by_instance) {
+        i = bmus[t];
+        if ((unsigned)i >= (unsigned)k || owner[i] != (int32_t)t + 1) i = -1;
+      } else if (owner[t] != 0) {
+        i = (int)t;
+      }
     }
-    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = t;
+    if (i >= 0) {
+      owner[i] = 0;
+      s_node[atomicAdd(&s_found, 1)] = i;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) wn64[i] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
-    __syncthreads();
+    const int found = s_found;
+    for (int f = 0; f < found; ++f) {
+      const float *w = W + (int64_t)s_node[f] * dim;
+      double s[4] = {0, 0, 0, 0};
+      for (int c0 = 0; c0 < dim; c0 += 8 * 256) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = w[min(c0 + 256 * u + tid, dim - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u & 3] += c0 + 256 * u + tid < dim ? (double)v[u] * (double)v[u] : 0.0;
+      }
+      const double sum = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+      if ((tid & 63) == 0) s_part[tid >> 6] = sum;
+      __syncthreads();
+      if (tid == 0) wn64[s_node[f]] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
+      __syncthreads();
+    }
+    __syncthreads();                             // (nobody still reads s_found when it is cleared again)
   }
 }
 
@@ -891,10 +922,10 @@ hipError_t launch_bmu_distances(som_ctx *c, const float *X, const int64_t *indpt
                                 const float *values, int64_t n, const float *W, const int32_t *bmus, float *dist,
                                 double *qerror) {
   if (X) return launch_bmu_distances_on(c->stream, X, n, W, c->k, c->dim, bmus, dist, qerror, c->dist_partial);
-  hipLaunchKernelGGL(k_mark_nodes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, bmus, n, c->k, c->dist_call,
-                     c->dist_flag);
-  hipLaunchKernelGGL(k_marked_norms, dim3(c->k < c->n_cu * 16 ? c->k : c->n_cu * 16), dim3(256), 0, c->stream, W, c->k, c->dim,
-                     c->dist_call, c->dist_flag, c->wn64);
+  const int64_t items = n < c->k ? n : c->k;
+  hipLaunchKernelGGL(k_mark_nodes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, bmus, n, c->k, c->dist_owner);
+  hipLaunchKernelGGL(k_marked_norms, dim3((unsigned)(items < c->n_cu * 16 ? items : c->n_cu * 16)), dim3(256), 0, c->stream, W,
+                     n, c->k, c->dim, bmus, c->dist_owner, c->wn64);
   const int blocks = distance_blocks(n, kWave);
   hipLaunchKernelGGL((k_bmu_distances<true, false, kWave, 1>), dim3(blocks), dim3(kDistThreads), 0, c->stream, nullptr, indptr, indices,
                      values, W, c->wn64, n, c->k, c->dim, bmus, dist, c->dist_partial);

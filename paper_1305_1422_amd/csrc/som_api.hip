@@ -713,7 +713,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   const size_t images = grid_type == SOM_GRID_HEXAGONAL ? 2 : 1;
   bool ok = dev_alloc(&c->wn32, (K + 127) / 128 * 128) && dev_alloc(&c->wn64, K) &&
             dev_alloc(&c->counts, K + 1) && dev_alloc(&c->group_local, 2 * (K + (K + 63) / 64)) && dev_alloc(&c->seg_off, K + 1) && dev_alloc(&c->chunk_off, K + 1) &&
-            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->direct_rec, direct_record_doubles(c)) && dev_alloc(&c->dist_flag, K) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
+            dev_alloc(&c->massD, K) && dev_alloc(&c->dist_partial, kDistBlocks) && dev_alloc(&c->direct_rec, direct_record_doubles(c)) && dev_alloc(&c->dist_owner, K) && dev_alloc(&c->cntT, 2 * K) && dev_alloc(&c->gx, 2 * (size_t)cols + 1) &&
             dev_alloc(&c->gy, (size_t)rows) && dev_alloc(&c->params, 1) && dev_alloc(&c->list_counts, kListWords) &&
             dev_alloc(&c->mu, (size_t)dim) && dev_alloc(&c->mu_partial, (size_t)64 * dim) &&
             dev_alloc(&c->zero16, 16) && dev_alloc(&c->mu_norm2, 1) && dev_alloc(&c->wscale, 1) &&
@@ -735,7 +735,7 @@ int som_init(som_ctx **out, int rows, int cols, int dim, int map_type, int grid_
   c->wlost_bits = c->wmax_bits + 4;
   hipError_t e = launch_fill_zero_u32(c->stream, c->list_counts, kListWords);
   if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->zero16, 16);
-  if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->dist_flag, c->k);
+  if (e == hipSuccess) e = launch_fill_zero_u32(c->stream, c->dist_owner, c->k);
   if (e == hipSuccess && K % 128 != 0) {       // the tail of the node constants past k stays +inf for good
     float inf[128];
     for (int i = 0; i < 128; ++i) inf[i] = INFINITY;
@@ -758,7 +758,7 @@ void som_destroy(som_ctx *c) {
   free_row_scratch(c);
   dev_free(c->direct_rec);
   dev_free(c->wn32); dev_free(c->wn64); dev_free(c->counts); dev_free(c->group_local); dev_free(c->seg_off);
-  dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->dist_flag); dev_free(c->row_hash); dev_free(c->dedup_keys);
+  dev_free(c->chunk_off); dev_free(c->massD); dev_free(c->dist_partial); dev_free(c->dist_owner); dev_free(c->row_hash); dev_free(c->dedup_keys);
   dev_free(c->dedup_lowest); dev_free(c->cntT); dev_free(c->gx); dev_free(c->gy);
   dev_free(c->params); dev_free(c->list_counts); dev_free(c->unit_work); dev_free(c->vq); dev_free(c->S); dev_free(c->T); dev_free(c->Wt); dev_free(c->Wt32);
   dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial); dev_free(c->H2);
@@ -827,10 +827,6 @@ int som_bmu_distances_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (!distances && !qerror) return fail(c, SOM_ERR_INVALID_ARG, "distances and qerror are both NULL");
   const int rc = check_csr(c, indptr, indices, values, n, nnz);
   if (rc) return rc;
-  if (++c->dist_call == 0x7fffffff) {           // call numbers start over: none of the marks left may match them
-    SOM_LAUNCH(c, launch_fill_zero_u32(c->stream, c->dist_flag, c->k));
-    c->dist_call = 1;
-  }
   SOM_LAUNCH(c, launch_bmu_distances(c, nullptr, indptr, indices, values, n, codebook, bmus, distances, qerror));
   return SOM_OK;
 }

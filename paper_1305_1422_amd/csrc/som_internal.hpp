@@ -101,8 +101,7 @@ struct som_ctx {
   int32_t *seg_off;       // [k+1] exclusive scan of counts
   int32_t *chunk_off;     // [k+1] exclusive scan of chunks per node
   double *massD;          // [k] neighbourhood mass per node
-  int32_t *dist_flag;     // [k] call number of the last som_bmu_distances_csr that met the node
-  int32_t dist_call;
+  int32_t *dist_owner;    // [k] scratch of the sparse distances (bmu_exact.hip), all zero between calls
   double *dist_partial;   // [1024] per-workgroup sums of the distances to the BMUs
   uint64_t *row_hash;     // [k] hashes of the code-book rows (bubble neighbourhood only, lazily allocated)
   uint64_t *dedup_keys;   // [dedup_slots] open-addressing table of those hashes

@@ -46,3 +46,27 @@ def test_distances_of_any_row_length(n, dim):
         np.testing.assert_allclose(d.cpu().numpy(), want, rtol=2e-7)
         assert abs(float(q) - want.mean()) <= 2e-7 * want.mean()
     som.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(5, 9), (120, 130)])
+def test_sparse_distances_call_after_call(rows, cols):
+    """Calls of many and of few instances on one context, the code book changed in between: what an earlier call left
+    behind about a node is not taken for this call's."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(6300 + rows)
+    k, dim = rows * cols, 70
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(rng.random((k, dim)).astype(np.float32)))
+    for n in (3000, 20, 44, 45, 46, 3000, 1, 20000, 700):
+        W = rng.random((k, dim)).astype(np.float32)
+        som.codebook.copy_(torch.from_numpy(W))
+        X = (rng.random((n, dim)) * (rng.random((n, dim)) < 0.2)).astype(np.float32)
+        b = (rng.integers(0, k, n) // int(rng.integers(1, 4))).astype(np.int32)
+        if n > 1:
+            b[n // 2] = -1                                   # no node: a NaN of its own, nothing else changes
+        csr = torch.from_numpy(X).to_sparse_csr()
+        sparse = (csr.crow_indices().cuda(), csr.col_indices().to(torch.int32).cuda(), csr.values().cuda())
+        d, _ = som.bmu_distances(sparse, P.to_dev(b))
+        want = np.sqrt(((X.astype(np.float64) - W[b].astype(np.float64)) ** 2).sum(1))
+        want[b < 0] = np.nan
+        np.testing.assert_allclose(d.cpu().numpy(), want, rtol=2e-7)
+    som.close()
