@@ -434,13 +434,28 @@ static int group_keys_per_wave(int k, int64_t n, int waves) {
   return per;
 }
 
-int64_t group_table_entries(int k, int64_t n) {
+// The tiled form reads and writes its table three times, and from some 30 million entries on (128 MB: most of the
+// memory-side cache) that costs more than the radix sort's passes over the keys.  Counting / radix, update of four
+// columns in us: 20,164 nodes, 8,000,000 keys (20 million entries) 824 / 983; 57,600 nodes, 1,000,000 keys (28 million)
+// 356 / 403; 81,225 nodes, 1,000,000 keys (40 million) 582 / 572; 25,600 nodes, 8,000,000 keys (50 million) 1,119 / 1,004;
+// 81,225 nodes, 8,000,000 keys (317 million) 2,496 / 1,257.
+constexpr int64_t kGroupTableMax = 32 << 20;
+
+// Entries of the tiled form's table; 0: its counters do not fit LDS, or the table would be too large.
+static int64_t group_tiled_entries(int k, int64_t n) {
   const int waves = group_waves(k, 0);
-  if (!waves || k > 64 * kGroupMaxBlocks) return 1;
-  // (a shorter list may be cut finer, but then its table has at most 500,000 entries and one more tile's)
+  if (!waves || k > 64 * kGroupMaxBlocks) return 0;
   const int64_t tile = (int64_t)waves * group_keys_per_wave(k, n, waves);
-  const int64_t most = (n + tile - 1) / tile * k;
-  return most > 500000 + k ? most : 500000 + k;
+  const int64_t entries = (n + tile - 1) / tile * k;
+  return entries <= kGroupTableMax ? entries : 0;
+}
+
+int64_t group_table_entries(int k, int64_t n) {
+  if (!group_waves(k, 0) || k > 64 * kGroupMaxBlocks) return 1;
+  // (a shorter list may be cut finer, but then its table has at most 500,000 entries and one more tile's; where this one
+  // is too long for the tiled form a shorter one need not be)
+  const int64_t own = group_tiled_entries(k, n), most = own > 500000 + k ? own : 500000 + k;
+  return own ? most : kGroupTableMax;
 }
 
 // ---------------------------------------------------------------- small sets: a workgroup per node
@@ -829,7 +844,7 @@ static hipError_t launch_group_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n
     }
     return hipGetLastError();
   }
-  if (many && c->k <= 64 * kGroupMaxBlocks) {
+  if (group_tiled_entries(c->k, n) > 0) {
     const int per = group_keys_per_wave(c->k, n, many);
     const int tile = many * per;
     const unsigned tiles = (unsigned)((n + tile - 1) / tile);
