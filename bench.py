@@ -25,6 +25,7 @@ sys.path.insert(0, ROOT)
 METRIC = "epoch throughput (instance*node*dim/s)"
 PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP16_MFMA_TFLOPS = 2500.0
+PEAK_FP64_MFMA_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
 # HBM-side bytes per launch of the dominant kernel (fetched + written), from the rocprofv3 --pmc passes
 # (FETCH_SIZE, WRITE_SIZE, scaled by the copy calibration) summarised in profiles/epoch_config*.md;
@@ -194,13 +195,20 @@ def main() -> int:
     value = work / (dt / args.steps)
 
     stage_ms = {k: (v[0] / v[1] if v[1] else 0.0) for k, v in prof.items()}
+    # a search without a filter pass prepares nothing; its kernels are booked under the filter stage
+    direct = w.kind == "dense" and prof["prepare_dense"][1] == 0
     if w.kind == "dense" or planes:
         dom_ms = stage_ms["bmu_csr_filter" if planes else "bmu_dense_filter"]
         flops = 2.0 * work                               # one multiply-add per (instance, node, feature)
         fp32_equiv = flops / (dom_ms * 1e-3) / 1e12 if dom_ms > 0 else 0.0
         # achieved = the method's own work, one multiply-add per (instance, node, feature) = 2 n k dim flop,
         # over the kernel's launch time, against the dense peak of the matrix format the contraction runs in
-        if args.filter == "fp32":
+        if direct:
+            roofline = {"bound": "launch latency",
+                        "kernel": "k_direct_search (all scores in fp64 on the matrix cores, decided in the same kernel)",
+                        "achieved": fp32_equiv, "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
+                        "frac": fp32_equiv / PEAK_FP64_MFMA_TFLOPS, "traffic": None, "avg_launch_ms": dom_ms}
+        elif args.filter == "fp32":
             roofline = {"bound": "mfma", "kernel": "k_bmu_dense_dl<false> (fp32 MFMA BMU filter pass)",
                         "achieved": fp32_equiv, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                         "frac": fp32_equiv / PEAK_FP32_MFMA_TFLOPS,
@@ -212,7 +220,7 @@ def main() -> int:
             # whole filter stage (coarse pass, block selection, ordering, lists, second pass)
             products = 1.0 + 3.0 * fine_share["mean"]
             roofline = {"bound": "mfma", "kernel": "two-level BMU filter stage: k_bmu_coarse (block minima, 1 fp16 product) + "
-                                                   "k_select_blocks + radix sort + k_tile_lists + k_bmu_dense_h<fine, 3 fp16 "
+                                                   "k_select_blocks + counting sort + k_tile_lists + k_bmu_dense_h<fine, 3 fp16 "
                                                    "products on the listed pairs>",
                         "achieved": fp32_equiv, "peak": PEAK_FP16_MFMA_TFLOPS, "unit": "TFLOP/s",
                         "frac": fp32_equiv / PEAK_FP16_MFMA_TFLOPS,
@@ -260,7 +268,8 @@ def main() -> int:
         "metric": METRIC, "value": value, "unit": "instance*node*dim/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None,
-        "dtype": ("f32" if (w.kind != "dense" and not planes) or args.filter == "fp32" else
+        "dtype": ("f32 operands, f64 products and sums" if direct else
+                  "f32" if (w.kind != "dense" and not planes) or args.filter == "fp32" else
                   "f32 operands split into 2 x f16, f32 accumulation (filter); f64 (decision)"),
         "data": "synthetic",
         "config": {"workload": f"config {w.config}: {w.name}", "kind": w.kind, "n": w.n, "dim": w.dim,
@@ -271,7 +280,8 @@ def main() -> int:
                             if args.mode == "map" else
                             "som_train_epoch on the registered data set: BMU search + batch update, everything that "
                             "depends on the code book included; outside the step, once per registered data set: "
-                            + ("squared norms of the instances, their fp16 hi/lo planes, sampled column means"
+                            + ("nothing" if direct else
+                               "squared norms of the instances, their fp16 hi/lo planes, sampled column means"
                                if w.kind == "dense" else
                                "column means, squared norms and fp16 hi/lo planes of the centred rows" if planes else
                                "squared norms of the instances, hot-column split")),
