@@ -563,12 +563,14 @@ bool direct_search_pays(const som_ctx *c, int64_t n, bool registered) {
   return direct_search_us(c, n) <= 1.15 * filtered_search_us(c, n, registered);
 }
 
-// Room for the records of any number of instances, so that no call has to grow it: groups exist for fewer than 16 cu
-// instance tiles, no more of them than (5 cu - 1) / tiles + 1 nor than tiles of 16 nodes (3.3 MB on 256 CUs).
+// Room for the records of any number of instances, so that no call has to grow it: there are groups for fewer than 5 cu
+// instance tiles, no more of them than (5 cu - 1) / tiles + 1 nor than quarters of the tiles of 16 nodes (1.5 MB on 256
+// CUs at most).
 size_t direct_record_doubles(const som_ctx *c) {
-  const size_t cu = (size_t)c->n_cu, tiles16 = ((size_t)c->k + 15) / 16;
-  const size_t tiles = 21 * cu < 16 * cu * tiles16 ? 21 * cu : 16 * cu * tiles16;
-  return 16 * (tiles * (sizeof(DirectBest) / sizeof(double)) + 16 * cu);
+  const size_t cu = (size_t)c->n_cu, most = (((size_t)c->k + 15) / 16 + 3) / 4;
+  if (most < 2) return 1;
+  const size_t tiles = 10 * cu < 5 * cu * most ? 10 * cu : 5 * cu * most;
+  return 16 * (tiles * (sizeof(DirectBest) / sizeof(double)) + 5 * cu);
 }
 
 hipError_t launch_direct_search(som_ctx *c, const float *X, int64_t n, const float *W, const float *mask, int32_t *bmus) {
