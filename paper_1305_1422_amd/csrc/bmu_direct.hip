@@ -73,6 +73,18 @@ __device__ __forceinline__ void direct_row_merge(DirectBest &r) {
   direct_row_step<0x140>(r);
 }
 
+// Lanes of the set below this one.
+__device__ __forceinline__ int lanes_below(unsigned long long set) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0u));
+}
+
+// A value that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ double direct_uniform(double v) {
+  const long long u = __builtin_bit_cast(long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)u), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(u >> 32));
+  return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Scores up to this one may belong to the BMU.
 __device__ __forceinline__ double direct_limit(const DirectBest &r, double xn, int dim) {
   return r.best + 8.881784197001252e-16 * (double)(dim + 8) * (2.0 * sqrt(xn) * sqrt(r.wmax) + r.wmax);      // 2^-50
@@ -392,15 +404,17 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct_search(const float *__re
 }
 
 // Merges the groups' records.  A wavefront per instance merges them, a lane per record; the instances they leave open are
-// then decided one after the other by the whole workgroup, by plain distances: of a group's best node alone where only
+// then decided by the whole workgroup, by plain distances: of a group's best node alone where only
 // that one is inside the limit, else of all nodes of the group.  What bounds that is the latency of one load after the
-// other, so the nodes of all groups in question are shared out evenly over the sixteen wavefronts, and a workgroup
-// takes no more instances than two workgroups per CU leave it (per_block <= 16).  Measured, search and merge, a wavefront
+// other, so the nodes of all groups in question are shared out evenly over the wavefronts, and a workgroup
+// takes no more instances than two workgroups per CU leave it (per_block <= 16); where several are open, up to four at a
+// time, since sixteen wavefronts on one spend a good part on their meetings (5,000 x 256 on 400 equal nodes: 473 us one at a
+// time, 438 so).  Measured, search and merge, a wavefront
 // per open instance from 1,024 instances on and 64 nodes one after the other / as it is now: 5,000 x 20 on a trained map
-// of 2,500 nodes 162 / 52 us, 1,500 x 20 on 2,500 nodes of which each has 19 exact copies 677 / 93.
+// of 2,500 nodes 162 / 52 us, 1,500 x 20 on 2,500 nodes of which each has 19 exact copies 677 / 80.
 // With nothing open it is a launch of 2 to 3 us: the open ones come from one read, and 64 registers let two workgroups
 // share a CU (4,097 x 33 on 1,073 nodes, the whole search: 31.7 us with more registers and a look at each instance, 30.2).
-constexpr int kMergeWaves = 16;
+constexpr int kMergeWaves = 16;      // 2^4
 
 template <bool kWide>
 __global__ __launch_bounds__(64 * kMergeWaves, kWide ? 8 : 4) void k_direct_merge(const DirectBest *__restrict__ rec, const double *__restrict__ xn,
@@ -409,7 +423,7 @@ __global__ __launch_bounds__(64 * kMergeWaves, kWide ? 8 : 4) void k_direct_merg
                                                                    const float *__restrict__ W, int k, int dim,
                                                                    int32_t *__restrict__ bmus) {
   __shared__ double s_limit[kMergeWaves], s_d2[kMergeWaves];
-  __shared__ int s_open[kMergeWaves], s_id[kMergeWaves], s_one[kWave], s_first[kWave];
+  __shared__ int s_open[kMergeWaves], s_id[kMergeWaves], s_one[4][kWave], s_first[4][kWave];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t j0 = (int64_t)blockIdx.x * per_block;
@@ -436,10 +450,16 @@ __global__ __launch_bounds__(64 * kMergeWaves, kWide ? 8 : 4) void k_direct_merg
   }
   __syncthreads();
   // (one read for all of them; uniform)
-  for (unsigned long long open = __ballot(lane < per_block && s_open[lane & (kMergeWaves - 1)]); open; open &= open - 1) {
-    const int q = __ffsll((long long)open) - 1;
+  unsigned long long open = __ballot(lane < per_block && s_open[lane & (kMergeWaves - 1)]);
+  while (open) {
+    // one, two or four instances at once, the wavefronts in as many crews
+    const int left = __popcll(open), halvings = left >= 4 ? 2 : left >= 2 ? 1 : 0, hands = kMergeWaves >> halvings;
+    const int crew = wave >> (4 - halvings), hand = wave & (hands - 1);
+    int q = 0;
+    for (int t = 0; t < 1 << halvings; ++t, open &= open - 1)
+      if (t == crew) q = __ffsll((long long)open) - 1;       // (crews never outnumber the instances left)
     const int64_t j = j0 + q;
-    const double limit = s_limit[q];
+    const double limit = direct_uniform(s_limit[q]);
     double b = INFINITY;
     int a = 0x7fffffff;
     for (int v0 = 0; v0 < groups; v0 += kWave) {
@@ -447,27 +467,28 @@ __global__ __launch_bounds__(64 * kMergeWaves, kWide ? 8 : 4) void k_direct_merg
       const DirectBest r = v < groups ? rec[(int64_t)v * n + j] : direct_none();
       const bool kept = v < groups && !(r.best > limit);            // (a NaN limit keeps every group)
       const bool one = kept && r.second > limit && (unsigned)r.arg < (unsigned)k;
-      const unsigned long long ones = __ballot(one), whole = __ballot(kept && !one), below = (1ull << lane) - 1ull;
-      if (wave == 0) {
-        if (one) s_one[__popcll(ones & below)] = r.arg;
-        else if (kept) s_first[__popcll(whole & below)] = v * nodes_per_group;
+      const unsigned long long ones = __ballot(one), whole = __ballot(kept && !one);
+      int *s_ones = s_one[crew], *s_firsts = s_first[crew];
+      if (hand == 0) {
+        if (one) s_ones[lanes_below(ones)] = r.arg;
+        else if (kept) s_firsts[lanes_below(whole)] = v * nodes_per_group;
       }
       __syncthreads();
       const int singles = __popcll(ones), total = singles + __popcll(whole) * nodes_per_group;
-      const int share = (total + kMergeWaves - 1) / kMergeWaves, at = wave * share;
+      const int share = (total + hands - 1) >> (4 - halvings), at = hand * share;
       direct_plain<kWide>(X + j * dim, W, at, min(at + share, total), [&](int p) {
-        if (p < singles) return s_one[p];
+        if (p < singles) return s_ones[p];
         const int g = (p - singles) / nodes_per_group;
-        return min(s_first[g] + (p - singles) - g * nodes_per_group, k - 1);       // (the last group may be short)
+        return min(s_firsts[g] + (p - singles) - g * nodes_per_group, k - 1);      // (the last group may be short)
       }, dim, lane, b, a);
       __syncthreads();
     }
     direct_plain_merge(b, a);
     if (lane == 0) { s_d2[wave] = b; s_id[wave] = a; }
     __syncthreads();
-    if (wave == 0) {
-      b = lane < kMergeWaves ? s_d2[lane] : INFINITY;
-      a = lane < kMergeWaves ? s_id[lane] : 0x7fffffff;
+    if (hand == 0) {
+      b = lane < hands ? s_d2[wave + lane] : INFINITY;
+      a = lane < hands ? s_id[wave + lane] : 0x7fffffff;
       direct_plain_merge(b, a);
       if (lane == 0) bmus[j] = a == 0x7fffffff ? 0 : a;
     }
@@ -525,7 +546,7 @@ static DirectPlan direct_plan(const som_ctx *c, int64_t n) {
 // Direct, in (16 x 16 x 16)-steps per SIMD, by the ways of sharing out: 0.2 a step, and besides what a wavefront waits
 // for between its tiles.  Where groups are merged, 1.45 times that, for the plain distances of open instances there: a
 // trained map leaves up to a third of them open (1,500 x 100 on 2,500 nodes: unordered 39, trained 60, all rows copied
-// 263 against 124 / 167 / 164 filtered).  The second sweep of the other forms needs no such allowance, since the
+// 252 against 124 / 167 / 164 filtered).  The second sweep of the other forms needs no such allowance, since the
 // filtered search's exact stage grows by as much on such maps (12,000 x 64 on 400 nodes: 50 / 49 / 96 against
 // 62 / 92 / 123).
 static double direct_search_us(const som_ctx *c, int64_t n) {

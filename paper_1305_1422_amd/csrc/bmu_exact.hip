@@ -746,7 +746,7 @@ hipError_t launch_refine_lists_csr(som_ctx *c, const int64_t *indptr, const int3
 // ---------------------------------------------------------------- distances to the BMUs
 // Post-training output: Euclidean distance between every instance and the weight vector of
 // the node it is mapped to, in fp64, and the mean of those distances (quantisation error).
-// A wavefront per instance; a workgroup owns a contiguous block of instances and leaves one
+// A workgroup owns a contiguous block of instances and leaves one
 // partial sum, the partial sums are added in index order by k_mean_of_partials: the result
 // does not depend on the schedule.  A node index outside [0, k) yields NaN.
 

@@ -5,7 +5,8 @@
 // needs S_b = sum of the instances whose BMU is b and C_b = their number.  Dense data:
 //   1. stable counting sort of the instance ids by BMU (counters of all nodes in LDS, ballot-based ranking),
 //      so every segment lists its instances in ascending order; C_b and the segment offsets fall out of it
-//      (maps whose counters do not fit LDS: LSD radix sort, offsets by binary search in the sorted keys);
+//      (maps whose counters do not fit LDS, or whose table would be too large: LSD radix sort, offsets by binary search
+//      in the sorted keys);
 //   2. small sets skip the sort: a workgroup per node picks its instances out of the list of BMUs;
 //   3. every segment is cut into chunks of kChunkRows instances; one workgroup sums one chunk
 //      (fp64 registers, instances read as whole rows through the permutation);
