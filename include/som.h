@@ -347,7 +347,9 @@ int som_set_smoothing(som_ctx *ctx, int form);
  *                  hold the BMU by the proven bound of those scores are dropped, the instances are
  *                  ordered by the blocks they have left, and the split-fp16 pass runs over the remaining
  *                  (128 instances, block) pairs only.  Needs 6 bytes per element of extra device memory
- *                  and 4 bytes per instance and node block.
+ *                  and 4 bytes per instance and node block.  In an epoch whose radius is wide the code book
+ *                  that enters it lies in few directions: the coarse pass then runs on 32 or 64 coordinates
+ *                  (decided on the device, within the same proven bounds; 128 bytes per instance more).
  *   SOM_FILTER_AUTO (default)  small searches run without any filter pass, all distances in fp64 on the
  *                  matrix cores, wherever that is estimated to take less time than a filtered search (from
  *                  400 nodes on up to some 1e9 to 1e10 multiply-adds in all, on smaller maps of few features
@@ -389,6 +391,21 @@ int som_debug_scores_csr(som_ctx *ctx, const int64_t *indptr, const int32_t *ind
  * Errors: NULL pointers, no such preceding call with this n -> SOM_ERR_INVALID_ARG.
  */
 int som_debug_select_margins(som_ctx *ctx, int64_t n, double *margin_out);
+
+/*
+ * som_debug_subspace - test hook: the coarse pass of the two-level search in the subspace of the code book, as an
+ * epoch of a wide radius runs it.  All pointers are device pointers:
+ *   block_min [ceil(k / 128)][n]  smallest coarse score per instance and block of 128 nodes, in the order node_of;
+ *   margin_out [n]  fp64: the margins of the block selection (a score is off by half of it at most);
+ *   node_of [k]     the node at every place of that order;
+ *   mu_out [dim]    the centring vector;
+ *   used [1]        0: the code book does not lie in so few directions, the pass ran on the full rows;
+ *                   1, 2: it ran on the first 32 or on all 64 coordinates.
+ * Errors: NULL pointers, n out of range -> SOM_ERR_INVALID_ARG; no two-level search or no subspace for this n,
+ * dim and filter -> SOM_ERR_STATE.
+ */
+int som_debug_subspace(som_ctx *ctx, const float *data, int64_t n, const float *codebook, float *block_min,
+                       double *margin_out, int32_t *node_of, float *mu_out, int32_t *used);
 
 /*
  * som_debug_mfma_f16 - test hook (not an operation of the paper): `count` independent

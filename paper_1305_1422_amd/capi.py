@@ -31,7 +31,7 @@ EXPORTS = [
     "som_bmu_distances_dense", "som_bmu_distances_csr", "som_bmu_distances_dense_static",
     "som_cool_schedule", "som_umatrix", "som_get_stats", "som_two_level_stats",
     "som_profile_enable", "som_profile_read",
-    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_mfma_f16", "som_debug_xcc_ids",
+    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_subspace", "som_debug_mfma_f16", "som_debug_xcc_ids",
 ]
 PROFILE_STAGES = ("bmu_dense_filter", "bmu_csr_filter", "bmu_exact", "node_sums", "smooth_divide", "prepare_dense")
 
@@ -118,6 +118,8 @@ def load():
     L.som_set_neighborhood.argtypes = [vp, i32, i32]
     L.som_debug_select_margins.restype = i32
     L.som_debug_select_margins.argtypes = [vp, i64, vp]
+    L.som_debug_subspace.restype = i32
+    L.som_debug_subspace.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp, vp]
     L.som_debug_scores_dense.restype = i32
     L.som_debug_scores_dense.argtypes = [vp, vp, i64, vp, vp, vp, vp]
     L.som_debug_scores_csr.restype = i32
@@ -372,6 +374,18 @@ def som_debug_select_margins(ctx, margin_out) -> None:
     """Test hook: the margins of the block selection for the coarse scores of the preceding som_debug_scores_dense."""
     import torch
     _check(ctx, load().som_debug_select_margins(ctx, margin_out.shape[0], _ptr(margin_out, torch.float64, "margin_out")))
+
+
+def som_debug_subspace(ctx, data, codebook, block_min, margin_out, node_of, mu_out, used) -> None:
+    """Test hook: block minima [ceil(k / 128)][n] of the coarse pass in the code book's subspace, their margins [n]
+    (float64), the order of the nodes [k], the centring vector and which coordinates were used [1]."""
+    import torch
+    _check(ctx, load().som_debug_subspace(ctx, _ptr(data, torch.float32, "data"), data.shape[0],
+                                          _ptr(codebook, torch.float32, "codebook"),
+                                          _ptr(block_min, torch.float32, "block_min"),
+                                          _ptr(margin_out, torch.float64, "margin_out"),
+                                          _ptr(node_of, torch.int32, "node_of"), _ptr(mu_out, torch.float32, "mu_out"),
+                                          _ptr(used, torch.int32, "used")))
 
 
 def som_debug_scores_dense(ctx, data, codebook, scores, mu_out, margin_out) -> None:

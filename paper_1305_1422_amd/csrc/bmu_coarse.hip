@@ -52,15 +52,110 @@ __device__ __forceinline__ f16x8 as_halves_c(f32x4 v) { return __builtin_bit_cas
 // kDump = false: block_min[node block of 128][instance] = smallest score of the pair.
 // kDump = true (test hook): every score to dump[instance * k + node]; the rows of Wh are nodes node_of[0], node_of[1], ...
 // wc: node constants c_i, readable for i < k_const (a multiple of 128 >= k, +inf past k).
+struct CoarseOperands {
+  const float *Xh, *Wh, *xscale, *wscale;
+  int nK;                            // chunks of 64 features
+};
+// state (may be null): the device's decision to run on the coordinates in the code book's subspace.
+struct CoarseSubspace {
+  const SubspaceState *state;
+  const _Float16 *Y1, *U1;
+  const float *yscale;
+};
+
+// The pass on the subspace's coordinates (bmu_subspace.hip), 16 kKS of them: the instances' operands stay in registers, the
+// nodes' rows go through a ring of four LDS stages of 256 rows, loaded three tiles ahead.  The node constants are
+// among the coordinates (three halves per node), so an accumulator holds the score divided by a negative factor of the
+// instance, and the epilogue is a running three-way maximum in the shadow of the next matrix instructions.  Bound by the
+// matrix pipes: 1,000,000 instances x 10,000 nodes 1,754 us (64 coordinates as one chunk of the general loop below) -> 708 us (the first 32).
+template <int kKS>
+__device__ __forceinline__ void coarse_in_subspace(const CoarseSubspace &sub, float *__restrict__ lds, int64_t n, int k,
+                                                   int64_t inst0, int nb_first, int nNB, float *__restrict__ out) {
+  constexpr int kStages = 4;
+  constexpr int kRowBytes = 32 * kKS, kSlots = 2 * kKS, kTileBytes = kCTN * kRowBytes;
+  static_assert(kStages * kTileBytes <= 2 * (kCTN + kCTI) * kCRow * 4, "the ring fits the stages of the general loop");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wi = wave & 3, l32 = lane & 31, lhi = lane >> 5;
+  // 16-byte slot of a row that slot `s` is kept in: any eight consecutive rows read one slot from eight different bank groups
+  auto swizzle = [](int row) { return kKS == 4 ? (row & 7) ^ ((row >> 3) & 1) : (row >> 1) & 3; };
+
+  int row[kKS];
+  unsigned slot[kKS];
+#pragma unroll
+  for (int i = 0; i < kKS; ++i) {
+    row[i] = (wave * kKS + i) * (64 / kSlots) + lane / kSlots;
+    slot[i] = 16u * ((lane % kSlots) ^ swizzle(row[i]));
+  }
+  const unsigned lds_at = lds_address_c(lds) + wave * kKS * 1024;
+  auto issue = [&](int t) {                       // rows past the last node repeat it: they change no maximum
+    const char *base = reinterpret_cast<const char *>(sub.U1) + (int64_t)(nb_first + t) * kCTN * (kSub * 2);
+    const int last = k - 1 - (nb_first + t) * kCTN;
+#pragma unroll
+    for (int i = 0; i < kKS; ++i)
+      load16_to_lds_c(base, (unsigned)min(row[i], last) * (kSub * 2) + slot[i], lds_at + (t % kStages) * kTileBytes + i * 1024);
+  };
+  f16x8 h[2][kKS];
+  float factor[2];
+  int64_t inst[2];
+#pragma unroll
+  for (int ni = 0; ni < 2; ++ni) {
+    inst[ni] = inst0 + wi * 64 + ni * 32 + l32;
+    const int64_t j = inst[ni] < n ? inst[ni] : n - 1;
+    factor[ni] = -2.f * sub.yscale[j] * sub.state->uscale;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) h[ni][ks] = *reinterpret_cast<const f16x8 *>(sub.Y1 + j * (16 * kKS) + 16 * ks + 8 * lhi);
+  }
+  for (int t = 0; t < kStages - 1 && t < nNB; ++t) issue(t);
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float best[2] = {INFINITY, INFINITY};
+  int best_block = -1;
+  auto store = [&]() {                            // of the previous tile: its latency then passes beside a tile's products
+    if (best_block < 0 || best_block * 128 >= k || lhi != 0) return;
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+      if (inst[ni] < n) out[(int64_t)best_block * n + inst[ni]] = best[ni];
+  };
+  for (int t = 0; t < nNB; ++t) {
+    // the loads of tile t have landed when at most those of t + 1 and t + 2 are in flight (loads return in order)
+    if (t + 2 < nNB) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kKS));
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    store();
+    if (t + kStages - 1 < nNB) issue(t + kStages - 1);      // into the stage that every wavefront has left
+    const char *at = reinterpret_cast<const char *>(lds) + (t % kStages) * kTileBytes + (wm * 128 + l32) * kRowBytes;
+    float m[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+      f16x8 g[kKS];
+#pragma unroll
+      for (int ks = 0; ks < kKS; ++ks)
+        g[ks] = *reinterpret_cast<const f16x8 *>(at + mi * 32 * kRowBytes + 16 * ((2 * ks + lhi) ^ swizzle(l32)));
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni) {
+        f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(g[0], h[ni][0], zero, 0, 0, 0);
+#pragma unroll
+        for (int ks = 1; ks < kKS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(g[ks], h[ni][ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; v += 2) m[ni] = fmaxf(fmaxf(m[ni], acc[v]), acc[v + 1]);
+      }
+    }
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) best[ni] = factor[ni] * fmaxf(m[ni], __shfl_xor(m[ni], 32, 64));
+    best_block = (nb_first + t) * 2 + wm;
+  }
+  store();
+}
+
 template <bool kDump>
-__global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(const float *__restrict__ Xh, const float *__restrict__ Wh,
-                                                             const float *__restrict__ wc, int k_const,
-                                                             const float *__restrict__ xscale,
-                                                             const float *__restrict__ wscale, int64_t n, int k,
-                                                             int nK, int groups, float *__restrict__ out,
+__global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(CoarseOperands op, CoarseSubspace sub,
+                                                             const float *__restrict__ wc, int k_const, int64_t n, int k,
+                                                             int groups, float *__restrict__ out,
                                                              const int32_t *__restrict__ node_of) {
-  __shared__ __attribute__((aligned(16))) float sW[2][kCTN * kCRow];
-  __shared__ __attribute__((aligned(16))) float sX[2][kCTI * kCRow];
+  const float *__restrict__ Xh = op.Xh, *__restrict__ Wh = op.Wh, *__restrict__ xscale = op.xscale, *__restrict__ wscale = op.wscale;
+  const int nK = op.nK;
+  __shared__ __attribute__((aligned(16))) float s_stage[2 * (kCTN + kCTI) * kCRow];
+  float (*sW)[kCTN * kCRow] = reinterpret_cast<float (*)[kCTN * kCRow]>(s_stage);
+  float (*sX)[kCTI * kCRow] = reinterpret_cast<float (*)[kCTI * kCRow]>(s_stage + 2 * kCTN * kCRow);
   __shared__ float sWn[2][kCTN];     // node constants of the node tiles in flight, by parity of the tile's ordinal
 
   const int tid = threadIdx.x;
@@ -85,6 +180,11 @@ __global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(const float *__rest
   const int nNB = min(nb_per, nNB_all - nb_first);
   if (nNB <= 0) return;              // uniform over the workgroup
   const int total = nK * nNB;
+  if (!kDump && sub.state && sub.state->use) {           // the same for every workgroup
+    if (sub.state->use == 1) coarse_in_subspace<2>(sub, s_stage, n, k, inst0, nb_first, nNB, out);
+    else coarse_in_subspace<4>(sub, s_stage, n, k, inst0, nb_first, nNB, out);
+    return;
+  }
 
   // ---- loader: one instruction fills 8 tile rows; wavefront w issues W slots 4 w .. 4 w + 3 and X slots
   // 4 w .. 4 w + 3.  Rows past the end of an operand are redirected to its last row (their outputs are
@@ -275,20 +375,20 @@ static int bmu_coarse_groups(const som_ctx *c, int64_t n) {
 }
 
 // c->Xh1, c->Wh1 -> c->coarse_min [ceil(k/128)][n], or with `dump` every score [n][k] (test hook).
-hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump) {
+hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, bool sub) {
   const int groups = bmu_coarse_groups(c, n);
   const int64_t tiles = (n + kCTI - 1) / kCTI;
   const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
-  const int nK = (c->dim + 63) / 64;
   const int k_const = (c->k + kTN - 1) / kTN * kTN;      // the node constants are padded to whole blocks of 128
-  const float *Xh = reinterpret_cast<const float *>(c->Xh1);
-  const float *Wh = reinterpret_cast<const float *>(c->Wh1);
+  const CoarseOperands op{reinterpret_cast<const float *>(c->Xh1), reinterpret_cast<const float *>(c->Wh1), c->xscale, c->wscale,
+                          (c->dim + 63) / 64};
+  const CoarseSubspace cs{sub ? c->sub_state : nullptr, c->sub_Y1, c->sub_U1, c->sub_yscale};
   if (dump)
-    hipLaunchKernelGGL((k_bmu_coarse<true>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, Xh, Wh, c->wn32,
-                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, dump, c->node_of);
+    hipLaunchKernelGGL((k_bmu_coarse<true>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, cs, c->wn32,
+                       k_const, n, c->k, groups, dump, c->node_of);
   else
-    hipLaunchKernelGGL((k_bmu_coarse<false>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, Xh, Wh, c->wn32,
-                       k_const, c->xscale, c->wscale, n, c->k, nK, groups, c->coarse_min, c->node_of);
+    hipLaunchKernelGGL((k_bmu_coarse<false>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, cs, c->wn32,
+                       k_const, n, c->k, groups, c->coarse_min, c->node_of);
   return hipGetLastError();
 }
 

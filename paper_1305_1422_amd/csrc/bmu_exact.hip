@@ -625,7 +625,8 @@ static double split_roundings_for(int dim) {
 }
 
 MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool hot) {
-  MarginModel mm{2.0 * fp32_pass_roundings(c->dim) + 4.0, 0.0, nullptr, nullptr, 0, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr};
+  MarginModel mm{2.0 * fp32_pass_roundings(c->dim) + 4.0, 0.0, nullptr, nullptr, 0, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr,
+                 nullptr, nullptr};
   if (mode == kCertifyCsr) {
     mm.indptr = indptr;
     mm.row_q = c->row_q;
@@ -654,7 +655,7 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
     mm.wscale = c->wscale;
     mm.x_centered = 1;
   }
-  if (mode == kCertifySelect) {
+  if (mode == kCertifySelect || mode == kCertifySubspace) {
     // The same pass, with the norms |dx| and |dw| that these rows really have (xlost, wlost_bits) in the place of
     // their worst case: the roundings are spread evenly, so the norms are less than half of it, and the block
     // selection keeps fewer blocks.
@@ -663,6 +664,10 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
     mm.x_centered = 1;
     mm.xlost = c->xlost;
     mm.wlost_bits = c->wlost_bits;
+    if (mode == kCertifySubspace) {
+      mm.sub = c->sub_state;
+      mm.sub_err = c->sub_err;
+    }
   }
   if (mode == kCertifySplit) {
     // dot product: accumulation + 3 * 2^-22 of the split (= 12 u) ; both doubled by the factor -2;

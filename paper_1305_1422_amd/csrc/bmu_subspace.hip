@@ -1,0 +1,637 @@
+// Dense best-matching-unit search: the coarse pass in the subspace that the code book spans (paper: BMU equation;
+// batch and neighbourhood equations, which is where the subspace comes from).
+//
+// A batch update leaves every weight vector a weighted mean of the same few sums, the weights smooth over the map: while
+// the radius is wide, the k x dim code book is numerically of rank far below both k and dim (50 x 50 nodes at a radius
+// of a third of the map: its part outside 64 directions is 2e-6 of its norm).  With V [64][dim] nearly orthonormal rows
+// that span it, u_i the coordinates of node i and y = V x' those of an instance,
+//     x'.w'_i = y.u_i + x'.e_i,      e_i = w'_i - V^T u_i   (whatever u and V are),
+// so |x'| max|e_i| bounds what a score from 64 products instead of dim leaves out.  The coarse pass of the two-level
+// search (bmu_coarse.hip) only has to bound every block's best score; it takes these 64-feature operands in the
+// place of the full ones wherever the measured max|e_i| is small, and the block selection adds the bound to its margin.
+// The fine pass and the exact stage work on the full rows as before: the BMUs do not depend on any of this.
+//
+//   k_subspace_sketch   S[r] = sum of +- w'_i over the nodes i = r mod 61: 61 random combinations whose span is the
+//                       code book's as far as so many directions go (as good as dense random signs in every case
+//                       tried, and one pass over the code book); three rows in between stay zero, their coordinates
+//                       carry the node constants through the coarse pass;
+//   k_subspace_gram     S S^T in fp64;
+//   k_subspace_factor   its Cholesky factor's inverse, directions below 1e-6 of the largest dropped;
+//   k_subspace_vectors  V = L^-1 S as fp16 hi/lo planes, in the two orders that the next two kernels read;
+//   k_subspace_coords   u = V w' and |w' - V^T u| per node on the matrix cores (split fp16, three products), the maxima over the
+//                       nodes, and the decision;
+//   k_subspace_project  y = V x' for every instance, from the hi halves of its planes, and the bound on its scores.
+// Measured (MI355X, a whole epoch, without -> with): 100,000 x 1,000 on 50 x 50 nodes 860 -> 561 us (coarse pass 518 ->
+// 31, the six kernels 155), 50,000 x 256 on 200 x 200 1,541 -> 982 (1,163 -> 266 + 145), 1,000,000 x 128 on 100 x 100 4,000 ->
+// 2,009 (3,060 -> 708 + 165).
+#include "som_internal.hpp"
+
+#include <math.h>
+
+namespace som {
+
+typedef _Float16 f16x8s __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4s __attribute__((ext_vector_type(4)));
+typedef float f32x16s __attribute__((ext_vector_type(16)));
+
+constexpr double kDropPivot = 1e-12;       // (relative norm)^2 below which a sketch row adds no direction
+constexpr float kVScale = 256.f;           // V is stored times this: |V_rc| <= 1, and fp16's subnormals stay out of the way
+
+__device__ __forceinline__ float pow2_over(float m, float *inverse) {      // power of two above m (1 for 0 and non-finite m)
+  int e = 0;
+  if (m > 0.f && m < INFINITY) {
+    (void)frexpf(m, &e);
+    e = e < -100 ? -100 : (e > 126 ? 126 : e);
+  }
+  *inverse = ldexpf(1.f, -e);
+  return ldexpf(1.f, e);
+}
+
+// ---------------------------------------------------------------- basis
+// A workgroup per (bucket, 64 features); eight node subgroups.  Bound by the read of the code book out of L2.
+__global__ __launch_bounds__(512) void k_subspace_sketch(const float *__restrict__ W, int k, int dim, int dimp,
+                                                         const float *__restrict__ mu, float *__restrict__ S) {
+  __shared__ float s_part[8][64];
+  const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+  constexpr int kBuckets = kSub - 3;
+  const int r = blockIdx.x, c = blockIdx.y * 64 + lane;
+  const int first = r < kSubConst ? r : r < kSubConst + 3 ? k : r - 3;
+  const bool in = c < dim;
+  const float m = in ? mu[c] : 0.f;
+  float acc = 0.f;
+#pragma unroll 4
+  for (int64_t i = first + (int64_t)kBuckets * sub; i < k; i += kBuckets * 8) {
+    unsigned h = (unsigned)i * 2654435761u;
+    h = (h ^ (h >> 16)) * 0x85ebca6bu;
+    const float v = in ? W[i * dim + c] - m : 0.f;
+    acc += (h >> 31) ? v : -v;
+  }
+  s_part[sub][lane] = acc;
+  __syncthreads();
+  if (sub == 0) {
+#pragma unroll
+    for (int p = 1; p < 8; ++p) acc += s_part[p][lane];
+    S[(int64_t)r * dimp + c] = acc;          // zeros behind the row's end
+  }
+}
+
+// G = S S^T, a workgroup per 8 x 8 outputs; sixteen threads per output, a sixteenth of the features each (four threads:
+// 12.8 us at 1,000 features).
+__global__ __launch_bounds__(1024) void k_subspace_gram(const float *__restrict__ S, int dimp, double *__restrict__ G) {
+  constexpr int kStep = 512, kParts = 16;
+  __shared__ float s_rows[16][kStep + 1];
+  __shared__ double s_sum[kParts][64];
+  const int tid = threadIdx.x, pair = tid & 63, part = tid >> 6;
+  const int bi = blockIdx.x >> 3, bj = blockIdx.x & 7;
+  if (bj > bi) return;                        // symmetric: the other half is written with this one
+  const int i = pair >> 3, j = pair & 7;
+  double s = 0.0;
+  for (int c0 = 0; c0 < dimp; c0 += kStep) {
+    __syncthreads();
+    const int c = c0 + (tid & (kStep - 1));
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const int row = 2 * p + (tid >= kStep), r = (row < 8 ? 8 * bi : 8 * bj - 8) + row;
+      s_rows[row][tid & (kStep - 1)] = c < dimp ? S[(int64_t)r * dimp + c] : 0.f;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int c = part; c < kStep; c += kParts) s += (double)s_rows[i][c] * (double)s_rows[8 + j][c];
+  }
+  s_sum[part][pair] = s;
+  __syncthreads();
+  if (part == 0) {
+    s = 0.0;
+    for (int p = 0; p < kParts; ++p) s += s_sum[p][pair];
+    G[(8 * bi + i) * kSub + 8 * bj + j] = s;
+    G[(8 * bj + j) * kSub + 8 * bi + i] = s;
+  }
+}
+
+// Linv^T of G = L L^T by elimination on [G | I], one workgroup, both matrices in registers (4 x 4 entries of each per
+// thread); per step the pivot's column and the right half's row go round through LDS.  A pivot under the
+// floor (or NaN) gives no direction: its row of L^-1 is zero.  Bound by 64 dependent steps: the reciprocal is a Newton
+// iteration (any basis will do that is nearly orthonormal), the square roots are left for the end, and blocks of 16 rows
+// and columns that are done or still zero are left out (31 us with none of this).
+__global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, double *__restrict__ LinvT) {
+  __shared__ double s_col[2][kSub], s_row[2][kSub], s_linv[kSub][kSub + 1], s_pivot[kSub];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  double m[4][4], w[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      m[a][b] = G[(ty + 16 * a) * kSub + tx + 16 * b];
+      w[a][b] = ty + 16 * a == tx + 16 * b ? 1.0 : 0.0;
+    }
+  double top = G[(tid & 63) * (kSub + 1)];      // the largest pivot
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+  const double floor_p = top * kDropPivot;
+#pragma unroll
+  for (int tb = 0; tb < 4; ++tb) {
+#pragma unroll 1
+    for (int tt = 0; tt < 16; ++tt) {
+      const int t = 16 * tb + tt;
+      double *col = s_col[t & 1], *row = s_row[t & 1];
+      if (tx == tt) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) col[ty + 16 * a] = m[a][tb];
+      }
+      if (ty == tt) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) row[tx + 16 * b] = w[tb][b];
+      }
+      __syncthreads();
+      const double p = col[t];
+      const bool keep = p > floor_p && p < INFINITY;
+      double inv = __builtin_amdgcn_rcp(p);
+      inv = fma(fma(-p, inv, 1.0), inv, inv);
+      inv = fma(fma(-p, inv, 1.0), inv, inv);
+      if (!keep) inv = 0.0;
+      if (tid < kSub) {
+        s_linv[t][tid] = row[tid];
+        if (tid == 0) s_pivot[t] = keep ? p : 0.0;
+      }
+      double cj[4], rj[4];
+#pragma unroll
+      for (int b = tb; b < 4; ++b) cj[b] = col[tx + 16 * b];
+#pragma unroll
+      for (int b = 0; b <= tb; ++b) rj[b] = row[tx + 16 * b];
+#pragma unroll
+      for (int a = tb; a < 4; ++a) {
+        const int i = ty + 16 * a;
+        const double f = i > t ? col[i] * inv : 0.0;
+#pragma unroll
+        for (int b = tb; b < 4; ++b) m[a][b] -= f * cj[b];
+#pragma unroll
+        for (int b = 0; b <= tb; ++b) w[a][b] -= f * rj[b];
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < kSub) s_pivot[tid] = s_pivot[tid] > 0.0 ? 1.0 / sqrt(s_pivot[tid]) : 0.0;
+  __syncthreads();
+  const double norm = s_pivot[tid & 63];
+  for (int s = tid >> 6; s < kSub; s += 4) LinvT[s * kSub + (tid & 63)] = norm > 0.0 ? s_linv[tid & 63][s] * norm : 0.0;
+}
+
+// V = L^-1 S times kVScale, as hi/lo halves: Vp [chunk of 64 features][plane][64 r][64 features] and
+// Vt [feature][plane][64 r].  A workgroup per 64 features, eight rows of V per wavefront.
+__global__ __launch_bounds__(512) void k_subspace_vectors(const float *__restrict__ S, int dimp, const double *__restrict__ LinvT,
+                                                          _Float16 *__restrict__ Vp, _Float16 *__restrict__ Vt) {
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = blockIdx.x * 64 + lane;
+  double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 16
+  for (int s = 0; s < kSub; ++s) {
+    const double x = (double)S[(int64_t)s * dimp + c];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += LinvT[s * kSub + 8 * g + e] * x;
+  }
+  f16x8s hi, lo;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float f = (float)v[e] * kVScale;
+    hi[e] = (_Float16)f;
+    lo[e] = (_Float16)(f - (float)hi[e]);
+    _Float16 *at = Vp + ((int64_t)blockIdx.x * 2 * kSub + 8 * g + e) * 64 + lane;
+    at[0] = hi[e];
+    at[kSub * 64] = lo[e];
+  }
+  *reinterpret_cast<f16x8s *>(Vt + (int64_t)c * 2 * kSub + 8 * g) = hi;
+  *reinterpret_cast<f16x8s *>(Vt + (int64_t)c * 2 * kSub + kSub + 8 * g) = lo;
+}
+
+// ---------------------------------------------------------------- the nodes
+// 32 nodes per workgroup and step, the chunks of 32 features dealt to its eight wavefronts, twice: u = V w' (summed over
+// the wavefronts through LDS), then w' - V^T u, whose squares are added up.  In both products a lane holds one node.  The
+// residual is formed by the matrix cores alone: w' enters through products with 2^(8-q) times the identity.
+// Units: planes hold w'/s (s = *wscale), V times 256, u/(s 2^q) with 2^q > sqrt(dim), so that |u| <= |w'| fits.
+// Roundings of the residual: the dropped lo.lo products (2^-22 |u_r V_rc|), a chain of 16 matrix instructions
+// (2.5 * 16 + 11 roundings of 2^-24 of the terms' magnitudes), the planes' own 2^-22 |w'| and 2^-25 s per element.  Per wavefront and
+// 32 features 12 + 16 matrix instructions on 12 KB from L2: latency of those loads bounds it on small maps.
+__global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restrict__ Wh, int k, int dim, int nK,
+                                                         const _Float16 *__restrict__ Vp, const _Float16 *__restrict__ Vt,
+                                                         const float *__restrict__ wscale, const unsigned *__restrict__ wmax_bits,
+                                                         int q, const float *__restrict__ cn, _Float16 *__restrict__ U1, float *__restrict__ part,
+                                                         int32_t *__restrict__ ticket, SubspaceState *__restrict__ state) {
+  __shared__ float s_u[4][kSub][33];
+  __shared__ __attribute__((aligned(16))) _Float16 s_un[2][32][kSub + 8];     // -u as hi/lo planes
+  __shared__ float s_sum[3][8][32], s_e[2][8][32], s_v[8][2][64];
+  __shared__ float s_fin[8][5];
+  __shared__ int s_last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const float sw = *wscale;
+  const float wm = sqrtf(__uint_as_float(*wmax_bits)) * (1.f + 1e-6f);
+  const float unit = ldexpf(sw, q);                 // of the u planes
+  float cinv;                                       // the constants stay below 2^10
+  const float cscale = pow2_over(__uint_as_float(*wmax_bits), &cinv) * 0x1p-10f;
+  cinv *= 0x1p10f;
+  f16x8s ident[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ident[ks][e] = (_Float16)(l32 == 16 * ks + 8 * lhi + e ? ldexpf(1.f, 8 - q) : 0.f);
+  const f32x16s zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float top_e = 0.f, top_e32 = 0.f, top_u = 0.f, top_u1 = 0.f, top_lost = 0.f, vn = 0.f;
+  const int tiles = (k + 31) / 32;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int node = min(tile * 32 + l32, k - 1);
+    const _Float16 *w = Wh + (int64_t)node * nK * 64 + 8 * lhi;
+    f32x16s u[2] = {zero, zero};
+    float vsq[2] = {0.f, 0.f};
+    // a chunk's operands: [k-step][hi, lo] of the nodes, [k-step][block of 32 rows][hi, lo] of V; the next chunk's are
+    // in flight while one is multiplied
+    f16x8s wn[2][2], vn8[2][2][2];
+    auto load_u = [&](int t) {
+      const _Float16 *v = Vp + ((int64_t)(t >> 1) * 2 * kSub + l32) * 64 + (t & 1) * 32 + 8 * lhi;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl) {
+          wn[ks][pl] = *reinterpret_cast<const f16x8s *>(w + t * 64 + 32 * pl + 16 * ks);
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) vn8[ks][rb][pl] = *reinterpret_cast<const f16x8s *>(v + (pl * kSub + rb * 32) * 64 + 16 * ks);
+        }
+    };
+    if (wave < nK) load_u(wave);
+    for (int t = wave; t < nK; t += 8) {
+      f16x8s wc[2][2], vc[2][2][2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl) {
+          wc[ks][pl] = wn[ks][pl];
+          vc[ks][0][pl] = vn8[ks][0][pl];
+          vc[ks][1][pl] = vn8[ks][1][pl];
+        }
+      if (t + 8 < nK) load_u(t + 8);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const f16x8s vh = vc[ks][rb][0], vl = vc[ks][rb][1];
+          u[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, wc[ks][0], u[rb], 0, 0, 0);
+          u[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, wc[ks][1], u[rb], 0, 0, 0);
+          u[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, wc[ks][0], u[rb], 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float f = (float)vh[e] + (float)vl[e];
+            vsq[rb] += f * f;
+          }
+        }
+    }
+    // operands of the residual: the planes of the nodes again and V in the other order
+    f16x8s wr[2][2], vr[4][2];
+    auto load_e = [&](int t) {
+      const _Float16 *v = Vt + (int64_t)(t * 32 + l32) * 2 * kSub + 8 * lhi;
+#pragma unroll
+      for (int pl = 0; pl < 2; ++pl) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) wr[ks][pl] = *reinterpret_cast<const f16x8s *>(w + t * 64 + 32 * pl + 16 * ks);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) vr[ks][pl] = *reinterpret_cast<const f16x8s *>(v + pl * kSub + 16 * ks);
+      }
+    };
+    if (wave < nK) load_e(wave);
+    __syncthreads();                                 // the previous step's readers are done
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      if (wave >= 4) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s_u[wave - 4][rb * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)][l32] = u[rb][v];
+      }
+      s_v[wave][rb][lane] = vsq[rb];
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s_u[wave][rb * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)][l32] += u[rb][v];
+    }
+    __syncthreads();
+    if (tid < 256) {
+      const int nd = tid & 31, g = tid >> 5;         // eight coordinates of one node
+      float su = 0.f, s1 = 0.f, sl = 0.f;
+      f16x8s hi, nhi, nlo;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int r = 8 * g + e;
+        float un = 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) un += s_u[p][r][nd];
+        un *= ldexpf(1.f / kVScale, -q);
+        hi[e] = (_Float16)un;
+        const _Float16 l = (_Float16)(un - (float)hi[e]);
+        nhi[e] = -hi[e];
+        nlo[e] = -l;
+        su += un * un;
+        s1 += fabsf(un);
+        sl += (float)l * (float)l;
+      }
+      *reinterpret_cast<f16x8s *>(&s_un[0][nd][8 * g]) = nhi;
+      *reinterpret_cast<f16x8s *>(&s_un[1][nd][8 * g]) = nlo;
+      s_sum[0][g][nd] = su;
+      s_sum[1][g][nd] = s1;
+      s_sum[2][g][nd] = sl;
+      if (tile * 32 + nd < k) {
+        if (g == kSubConst / 8) {                    // c_i as the sum of three halves, to 2^-35 of the largest
+          float c = cn[tile * 32 + nd] * cinv;
+#pragma unroll
+          for (int e = kSubConst % 8; e < kSubConst % 8 + 3; ++e) { hi[e] = (_Float16)c; c -= (float)hi[e]; }
+        }
+        *reinterpret_cast<f16x8s *>(U1 + (int64_t)(tile * 32 + nd) * kSub + 8 * g) = hi;
+      }
+    }
+    {                                                // largest row norm of V: row 32 rb + l32 is spread over waves and halves
+      float f = 0.f;
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        float s = 0.f;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) s += s_v[p][rb][l32] + s_v[p][rb][32 + l32];
+        f = fmaxf(f, s);
+      }
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) f = fmaxf(f, __shfl_xor(f, o, 64));
+      vn = sqrtf(f) * (1.f + 4e-4f) / kVScale;
+    }
+    __syncthreads();
+    f16x8s uh[4], ul[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      uh[ks] = *reinterpret_cast<const f16x8s *>(&s_un[0][l32][16 * ks + 8 * lhi]);
+      ul[ks] = *reinterpret_cast<const f16x8s *>(&s_un[1][l32][16 * ks + 8 * lhi]);
+    }
+    float esq = 0.f, esq32 = 0.f;
+    for (int t = wave; t < nK; t += 8) {
+      f32x16s d = zero;
+      f16x8s vc[4][2];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { vc[ks][0] = vr[ks][0]; vc[ks][1] = vr[ks][1]; }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(ident[ks], wr[ks][0], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(ident[ks], wr[ks][1], d, 0, 0, 0);
+      }
+      if (t + 8 < nK) load_e(t + 8);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const f16x8s vh = vc[ks][0], vl = vc[ks][1];
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, uh[ks], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, uh[ks], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, ul[ks], d, 0, 0, 0);
+        if (ks == 1) {                               // what the first 32 coordinates leave
+#pragma unroll
+          for (int v2 = 0; v2 < 16; ++v2) esq32 += d[v2] * d[v2];
+        }
+      }
+#pragma unroll
+      for (int v2 = 0; v2 < 16; ++v2) esq += d[v2] * d[v2];
+    }
+    esq += __shfl_xor(esq, 32, 64);
+    esq32 += __shfl_xor(esq32, 32, 64);
+    if (lhi == 0) { s_e[0][wave][l32] = esq; s_e[1][wave][l32] = esq32; }
+    __syncthreads();
+    if (tid < 32) {
+      float su = 0.f, s1 = 0.f, sl = 0.f;
+#pragma unroll
+      for (int g = 0; g < 8; ++g) { su += s_sum[0][g][tid]; s1 += s_sum[1][g][tid]; sl += s_sum[2][g][tid]; }
+      float e2 = 0.f, e32 = 0.f;
+#pragma unroll
+      for (int p = 0; p < 8; ++p) { e2 += s_e[0][p][tid]; e32 += s_e[1][p][tid]; }
+      const float u1 = s1 * unit * (1.f + 1e-4f);
+      const float slack = 55.f * 0x1p-24f * (wm + vn * u1) + 0x1p-22f * wm + sqrtf((float)dim) * 0x1p-25f * sw;
+      e2 = (sqrtf(e2) * (1.f + 4e-4f) + 1e-15f) * ldexpf(sw, q - 8) + slack;
+      e32 = (sqrtf(e32) * (1.f + 4e-4f) + 1e-15f) * ldexpf(sw, q - 8) + slack;
+      top_e = e2 < INFINITY ? fmaxf(top_e, e2) : INFINITY;     // NaN counts as infinite
+      top_e32 = e32 < INFINITY ? fmaxf(top_e32, e32) : INFINITY;
+      top_u = fmaxf(top_u, sqrtf(su) * (1.f + 1e-4f) * unit);
+      top_u1 = fmaxf(top_u1, u1);
+      top_lost = fmaxf(top_lost, (sqrtf(sl) * (1.f + 1e-4f) + 1e-15f) * unit);
+    }
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) {
+    top_e = fmaxf(top_e, __shfl_xor(top_e, o, 64));
+    top_e32 = fmaxf(top_e32, __shfl_xor(top_e32, o, 64));
+    top_u = fmaxf(top_u, __shfl_xor(top_u, o, 64));
+    top_u1 = fmaxf(top_u1, __shfl_xor(top_u1, o, 64));
+    top_lost = fmaxf(top_lost, __shfl_xor(top_lost, o, 64));
+  }
+  // the last workgroup to get here puts the maxima together and decides
+  if (tid == 0) {
+    float *p = part + 5 * blockIdx.x;
+    __hip_atomic_store(p + 0, top_e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, top_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 2, top_u1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 3, top_lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 4, top_e32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  float f[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int b = tid; b < (int)gridDim.x; b += 512)
+#pragma unroll
+    for (int e = 0; e < 5; ++e) f[e] = fmaxf(f[e], __hip_atomic_load(part + 5 * b + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+  for (int e = 0; e < 5; ++e) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) f[e] = fmaxf(f[e], __shfl_xor(f[e], o, 64));
+    if (lane == 0) s_fin[wave][e] = f[e];
+  }
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int e = 0; e < 5; ++e)
+      for (int p = 0; p < 8; ++p) f[e] = fmaxf(f[e], s_fin[p][e]);
+    const int use = !(f[1] < INFINITY) ? 0 : f[4] <= kSubspaceLoss32 * wm ? 1 : f[0] <= kSubspaceLoss * wm ? 2 : 0;
+    state->use = use;
+    state->e = use == 1 ? f[4] : f[0];
+    state->u = f[1];
+    state->u1 = f[2] * vn;
+    state->ulost = f[3];
+    state->wm = wm;
+    state->uscale = unit;
+    state->cscale = cscale;
+  }
+}
+
+// ---------------------------------------------------------------- the instances
+// y = V hi(x') of 256 instances per workgroup, 64 per wavefront: V a chunk of 64 features at a time through LDS (16-byte slots swizzled as in
+// the coarse pass), the instances' halves straight from memory into the operand registers, one chunk ahead.  Bound by
+// the read of the hi planes (2 bytes per element).
+// A lane holds one instance; err[j] bounds |x'.w'_i - (the coarse pass's y.u_i)| for every node i.
+template <int kRB>
+__device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, int64_t n, int nK,
+                                                          const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
+                                                          const float *__restrict__ xn32, const float *__restrict__ xlost,
+                                                          const SubspaceState *__restrict__ state, _Float16 *__restrict__ Y1,
+                                                          float *__restrict__ yscale, float *__restrict__ err,
+                                                          _Float16 (&s_v)[2][2 * kSub * 64]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int64_t inst0 = (int64_t)blockIdx.x * 256 + wave * 64;
+  const _Float16 *x[2];
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib) {
+    int64_t j = inst0 + ib * 32 + l32;
+    if (j > n - 1) j = n - 1;
+    x[ib] = Xh1 + j * (int64_t)nK * 64 + 8 * lhi;
+  }
+  // loader: the chunk's 128 rows (64 hi, 64 lo) of 128 bytes, four 16-byte slots per thread
+  int st_off[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int slot = i * 256 + tid, row = slot >> 3, pos = slot & 7;
+    st_off[i] = row * 64 + 8 * (pos ^ ((row & 7) ^ ((row >> 3) & 1)));
+  }
+  const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
+  f32x16s acc[kRB][2];
+#pragma unroll
+  for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib) acc[rb][ib] = f32x16s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f16x8s v[4], xr[2][4];
+  auto load = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f16x8s *>(Vp + (int64_t)t * 2 * kSub * 64 + 8 * (i * 256 + tid));
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) xr[ib][ks] = *reinterpret_cast<const f16x8s *>(x[ib] + t * 64 + 16 * ks);
+  };
+  load(0);
+  for (int t = 0; t < nK; ++t) {
+    _Float16 *sv = s_v[t & 1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<f16x8s *>(sv + st_off[i]) = v[i];
+    f16x8s xc[2][4];
+#pragma unroll
+    for (int ib = 0; ib < 2; ++ib)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) xc[ib][ks] = xr[ib][ks];
+    if (t + 1 < nK) load(t + 1);
+    __syncthreads();           // one barrier per chunk: the other stage's readers passed the previous one
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int pl = 1; pl >= 0; --pl)
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) {
+          const int row = pl * kSub + rb * 32 + l32;
+          const f16x8s a = *reinterpret_cast<const f16x8s *>(sv + row * 64 + 8 * ((2 * ks + lhi) ^ swz));
+#pragma unroll
+          for (int ib = 0; ib < 2; ++ib) acc[rb][ib] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xc[ib][ks], acc[rb][ib], 0, 0, 0);
+        }
+  }
+  const float wm = state->wm, e = state->e, um = state->u, u1 = state->u1, ulost = state->ulost;
+  const float uscale = state->uscale, cscale = state->cscale;
+  const float chain = 2.5f * (float)(8 * nK) + 11.f;            // roundings of a chain of 8 nK matrix instructions
+#pragma unroll
+  for (int ib = 0; ib < 2; ++ib) {
+    const int64_t j = inst0 + ib * 32 + l32;
+    float top = 0.f;
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) top = fmaxf(top, fabsf(acc[rb][ib][i]));
+    top = fmaxf(top, __shfl_xor(top, 32, 64));
+    float inv;
+    float s = pow2_over(top, &inv);
+    const float xs = (j < n ? xscale[j] : 1.f) * (1.f / kVScale);
+    // the factor of the node constants, a power of two that a half holds exactly: the scale is raised where it would be
+    // too large, the bound made infinite where it would be too small (such an instance keeps every block)
+    const float over = cscale / (2.f * s * xs * uscale) * 0x1p-15f;
+    if (over > 1.f) { s *= over; inv /= over; }
+    const float cfac = -cscale / (2.f * s * xs * uscale);
+    float ysq = 0.f, lost = 0.f;
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f16x4s h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float y = acc[rb][ib][4 * g + i] * inv;
+          h[i] = (_Float16)y;
+          const float d = y - (float)h[i];
+          ysq += y * y;
+          lost += d * d;
+        }
+        if (rb == 0) {                       // coordinates kSubConst .. kSubConst + 2
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int r = 8 * g + 4 * lhi + i;
+            if (r >= kSubConst && r < kSubConst + 3) h[i] = (_Float16)cfac;
+          }
+        }
+        if (j < n) *reinterpret_cast<f16x4s *>(Y1 + j * (32 * kRB) + rb * 32 + 8 * g + 4 * lhi) = h;
+      }
+    ysq += __shfl_xor(ysq, 32, 64);
+    lost += __shfl_xor(lost, 32, 64);
+    if (j < n && lhi == 0) {
+      const float unit = s * xs;
+      const float lx = xlost[j], xn = sqrtf(xn32[j]) * (1.f + 1e-6f) + lx;
+      const float yn = (sqrtf(ysq) * (1.f + 1e-4f) + 1e-15f) * unit, yl = (sqrtf(lost) * (1.f + 4e-4f) + 1e-15f) * unit;
+      yscale[j] = unit;
+      // (x' - hi).w' + hi.e_i + (roundings of y).u + (y - hi(y)).u + hi(y).(u - hi(u)) + the coarse pass's chain of up to
+      // four instructions, over the products and over half of c_i
+      const float b = lx * wm + xn * e + chain * 0x1p-24f * xn * u1 + yl * um + (yn + yl) * (ulost + 21.f * 0x1p-24f * um) +
+                      12.f * 0x1p-24f * wm * wm;
+      err[j] = -cfac >= 0x1p-24f && -cfac <= 0x1p15f ? b * (1.f + 1e-3f) : INFINITY;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__restrict__ Xh1, int64_t n, int nK,
+                                                          const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
+                                                          const float *__restrict__ xn32, const float *__restrict__ xlost,
+                                                          const SubspaceState *__restrict__ state, _Float16 *__restrict__ Y1,
+                                                          float *__restrict__ yscale, float *__restrict__ err) {
+  __shared__ __attribute__((aligned(16))) _Float16 s_v[2][2 * kSub * 64];
+  if (state->use == 1) project_rows<1>(Xh1, n, nK, Vp, xscale, xn32, xlost, state, Y1, yscale, err, s_v);
+  else if (state->use == 2) project_rows<2>(Xh1, n, nK, Vp, xscale, xn32, xlost, state, Y1, yscale, err, s_v);
+}
+
+// ---------------------------------------------------------------- host side
+// Is the subspace worth its scratch for searches of n instances?  By default where the coarse pass would take some 150 us
+// more on the full rows (2 ns per million multiply-adds) than the basis and the coordinates take (80 us, and the read of the
+// hi planes); with the two-level search asked for by name wherever there are more features than coordinates.  Grows
+// with n, so that scratch for the largest call serves every smaller one.
+bool subspace_eligible(const som_ctx *c, int64_t n) {
+  if (c->dim <= kSub || c->dim > kPlaneMaxDim) return false;
+  return c->filter == SOM_FILTER_TWO_LEVEL || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceMinWork;
+}
+
+// Is the code book that enters an epoch of this radius likely to lie in 64 directions?  It was left by an epoch of about
+// that radius or more, and the number of directions grows with the number of radii the map is long and wide.
+bool subspace_likely(const som_ctx *c, double radius) {
+  if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
+  return (double)c->rows * (double)c->cols <= kSubspaceMaxArea * radius * radius;
+}
+
+size_t subspace_vector_halves(const som_ctx *c) { return (size_t)((c->dim + 63) / 64) * 64 * 2 * kSub; }
+
+hipError_t launch_subspace(som_ctx *c, const float *W, int64_t n) {
+  const int nK = (c->dim + 63) / 64, dimp = nK * 64;
+  hipLaunchKernelGGL(k_subspace_sketch, dim3(kSub, nK), dim3(512), 0, c->stream, W, c->k, c->dim, dimp, c->mu, c->sub_S);
+  hipLaunchKernelGGL(k_subspace_gram, dim3(64), dim3(1024), 0, c->stream, c->sub_S, dimp, c->sub_G);
+  hipLaunchKernelGGL(k_subspace_factor, dim3(1), dim3(256), 0, c->stream, c->sub_G, c->sub_G + kSub * kSub);
+  hipLaunchKernelGGL(k_subspace_vectors, dim3(nK), dim3(512), 0, c->stream, c->sub_S, dimp, c->sub_G + kSub * kSub, c->sub_Vp, c->sub_Vt);
+  int q = 0;
+  while ((1 << q) * (1 << q) < c->dim + c->dim / 8) ++q;
+  int blocks = (c->k + 31) / 32;
+  if (blocks > kSubspaceParts) blocks = kSubspaceParts;
+  hipLaunchKernelGGL(k_subspace_coords, dim3(blocks), dim3(512), 0, c->stream, c->Wh, c->k, c->dim, (c->dim + 31) / 32, c->sub_Vp,
+                     c->sub_Vt, c->wscale, c->wmax_bits, q, c->wn32, c->sub_U1, c->sub_part, c->list_counts + kSubTicketWord, c->sub_state);
+  hipLaunchKernelGGL(k_subspace_project, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->Xh1, n, nK, c->sub_Vp,
+                     c->xscale, c->xn32, c->xlost, c->sub_state, c->sub_Y1, c->sub_yscale, c->sub_err);
+  return hipGetLastError();
+}
+
+}  // namespace som

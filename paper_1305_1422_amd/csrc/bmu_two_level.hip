@@ -178,17 +178,17 @@ __global__ __launch_bounds__(256) void k_tile_lists(const uint32_t *__restrict__
   if (lane == 0) tile_cnt[tile] = count;
 }
 
-hipError_t launch_select_blocks(som_ctx *c, int64_t n) {
+hipError_t launch_select_blocks(som_ctx *c, int64_t n, bool sub) {
   const int blocks = (c->k + 127) / 128, classes = size_classes(blocks);
   // as many steps of the span as keep the keys below k: the grouping by key has room for that many
   const int spans = c->k / (classes * blocks) > blocks ? blocks : c->k / (classes * blocks) > 1 ? c->k / (classes * blocks) : 1;
   if (blocks <= 128)      // 32 blocks held per thread: all of them
     hipLaunchKernelGGL(k_select_blocks<4>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifySelect, nullptr),
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, sub ? kCertifySubspace : kCertifySelect, nullptr),
                        classes, spans, c->coarse_key, c->coarse_mask);
   else
     hipLaunchKernelGGL(k_select_blocks<8>, dim3((unsigned)((n + 63) / 64)), dim3(512), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, kCertifySelect, nullptr),
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, sub ? kCertifySubspace : kCertifySelect, nullptr),
                        classes, spans, c->coarse_key, c->coarse_mask);
   return hipGetLastError();
 }

@@ -29,6 +29,10 @@ struct MarginModel {
   // |w' - hi(w')| of the nodes; null in the other models
   const float *xlost;            // [n]
   const unsigned *wlost_bits;    // [1]
+  // ... and where the pass may have run on the coordinates in the code book's subspace: whether it did, and the bounds on
+  // the errors of an instance's dot products then, in the place of those
+  const SubspaceState *sub;      // [1] or null
+  const float *sub_err;          // [n]
 };
 
 __device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j, double xnorm2, double wmax2,
@@ -47,15 +51,19 @@ __device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j,
     // fp32 rounding: 1e-5 relative is ample), the score by twice that
     if (mm.row_q) absolute = 2.0 * 0.51 * (1.0 + 1e-5) * (double)mm.row_q[j];
   }
-  double bound = coef * xn * wm + 4.0 * wm * wm + 6.0 * mn * wm;
+  double bound = 0.0;
   if (mm.coef_hot > 0.0) {
     const double xh = sqrt((double)mm.hot_xn[j] * (1.0 + 1.2e-7));
     bound += mm.coef_hot * xh * wm + sqrt((double)kHot) * ((double)mm.hot_xscale[j] * wm + (double)*mm.hot_wscale * xh);
   }
-  if (mm.xlost) {            // x'.w' - hi(x').hi(w') = dx.w' + hi(x').dw, doubled by the score's factor -2
+  if (mm.sub && mm.sub->use) {
+    coef = 4.0 + 2.0;        // its own accumulation is part of sub_err
+    absolute += 2.0 * (double)mm.sub_err[j];
+  } else if (mm.xlost) {     // x'.w' - hi(x').hi(w') = dx.w' + hi(x').dw, doubled by the score's factor -2
     const double lx = (double)mm.xlost[j], lw = (double)__uint_as_float(*mm.wlost_bits);
     absolute += 2.0 * (lx * wm + (xn + lx) * lw);
   }
+  bound += coef * xn * wm + 4.0 * wm * wm + 6.0 * mn * wm;
   if (mm.xscale) bound += mm.coef_floor * ((double)mm.xscale[j] * wm + (double)*mm.wscale * xn);
   return 2.125 * (u * bound + absolute);          // both scores of a pair may err, plus slack for higher-order terms
 }

@@ -27,12 +27,6 @@ namespace som {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ double cooled(double v0, double vN, int n_epochs, int epoch, int kind) {
-  if (n_epochs <= 1) return v0;
-  const double t = (double)epoch / (double)(n_epochs - 1);
-  return kind == SOM_COOL_EXPONENTIAL ? v0 * pow(vN / v0, t) : v0 + (vN - v0) * t;
-}
-
 __global__ __launch_bounds__(256) void k_cool_schedule(int n_epochs, double r0, double rN, double s0, double sN,
                                                        int cooling, int scale_cooling,
                                                        double *__restrict__ radius_out,

@@ -111,6 +111,10 @@ static bool two_level_ready(const som_ctx *c, int64_t n) {
   return two_level(c, n) && c->Xh1 != nullptr && c->Wh1 != nullptr && n <= c->n_cap;
 }
 
+static bool subspace_ready(const som_ctx *c, int64_t n) {
+  return subspace_eligible(c, n) && c->sub_state != nullptr && c->sub_Y1 != nullptr;
+}
+
 static void free_row_scratch(som_ctx *c) {
   dev_free(c->xn32); dev_free(c->row_q); dev_free(c->cand_val); dev_free(c->cand_idx); dev_free(c->cand_over);
   dev_free(c->cand_n); dev_free(c->refine_list); dev_free(c->rescan_list);
@@ -120,6 +124,7 @@ static void free_row_scratch(som_ctx *c) {
   dev_free(c->Xh); dev_free(c->xscale);
   dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
   dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
+  dev_free(c->sub_Y1); dev_free(c->sub_yscale); dev_free(c->sub_err);
   c->two_level_n = 0;
   c->debug_coarse_n = 0;
   c->n_cap = 0;
@@ -130,16 +135,23 @@ static void free_row_scratch(som_ctx *c) {
   c->csrd_on = 0;
 }
 
+static void free_subspace(som_ctx *c) {
+  dev_free(c->sub_S); dev_free(c->sub_G); dev_free(c->sub_Vp); dev_free(c->sub_Vt); dev_free(c->sub_U1); dev_free(c->sub_part);
+  dev_free(c->sub_state);
+}
+
 // Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
 // will run on them (false: the direct search, or an update alone).
 static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) {
   const bool split = dense && filtered && uses_planes(c);
   // sized for the rows the scratch is (or will be) allocated for, so that it serves every n up to n_cap
   const bool coarse = split && two_level(c, n > c->n_cap ? n : c->n_cap);
+  const bool subspace = coarse && subspace_eligible(c, n > c->n_cap ? n : c->n_cap);
   const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) ||
                             (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
-                            (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr));
+                            (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr)) ||
+                            (subspace && (c->sub_Y1 == nullptr || c->sub_state == nullptr));
   if (n <= c->n_cap && !need_partial) return SOM_OK;
   if (n > c->n_cap) {
     (void)hipStreamSynchronize(c->stream);
@@ -203,6 +215,20 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
         dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
         return fail(c, SOM_ERR_ALLOC, "cannot allocate the two-level search's scratch for %lld instances", (long long)c->n_cap);
       }
+    }
+  }
+  if (subspace) {
+    const size_t v = subspace_vector_halves(c);
+    if (c->sub_state == nullptr &&
+        !(dev_alloc(&c->sub_S, v / 2) && dev_alloc(&c->sub_G, 2 * kSub * kSub) && dev_alloc(&c->sub_Vp, v) && dev_alloc(&c->sub_Vt, v) &&
+          dev_alloc(&c->sub_U1, (size_t)c->k * kSub) && dev_alloc(&c->sub_part, 5 * kSubspaceParts) && dev_alloc(&c->sub_state, 1))) {
+      free_subspace(c);
+      return fail(c, SOM_ERR_ALLOC, "cannot allocate the subspace of the code book");
+    }
+    if (c->sub_Y1 == nullptr &&
+        !(dev_alloc(&c->sub_yscale, (size_t)c->n_cap) && dev_alloc(&c->sub_err, (size_t)c->n_cap) && dev_alloc(&c->sub_Y1, (size_t)c->n_cap * kSub))) {
+      dev_free(c->sub_Y1); dev_free(c->sub_yscale); dev_free(c->sub_err);
+      return fail(c, SOM_ERR_ALLOC, "cannot allocate the coordinates of %lld instances", (long long)c->n_cap);
     }
   }
   return SOM_OK;
@@ -333,10 +359,12 @@ static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, 
 }
 
 // The filter pass over the planes (or, with the fp32 filter, over X itself): candidates per instance.
-static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split, bool coarse) {
+// W: the code book if the coarse pass may run in its subspace, else null.
+static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split, bool coarse, const float *W) {
   if (coarse) {
-    SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr));
-    SOM_LAUNCH(c, launch_select_blocks(c, n));
+    if (W) SOM_LAUNCH(c, launch_subspace(c, W, n));
+    SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, W != nullptr));
+    SOM_LAUNCH(c, launch_select_blocks(c, n, W != nullptr));
     SOM_LAUNCH(c, launch_order_by_key(c, c->coarse_key, n));
     SOM_LAUNCH(c, launch_tile_lists(c, n));
     SOM_LAUNCH(c, launch_bmu_dense_h_fine(c, n));
@@ -362,8 +390,9 @@ static int bmu_search_direct(som_ctx *c, const float *X, int64_t n, const float 
   return SOM_OK;
 }
 
+// radius: of the epoch the search belongs to, 0 for a search of its own (the code book may be anything then).
 static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *W, int32_t *bmus, bool have_xn,
-                            bool cleared = false) {
+                            bool cleared = false, double radius = 0.0) {
   int rc = ensure_candidates(c, n, true);
   if (!rc) rc = prepare_dense(c, X, n, W, have_xn, cleared);
   if (rc) return rc;
@@ -372,7 +401,8 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
   c->two_level_n = coarse ? n : 0;
   {
     StageTimer t(c, 0);
-    rc = dense_filter_stage(c, X, n, split, coarse);
+    const bool sub = coarse && radius > 0.0 && subspace_ready(c, n) && subspace_likely(c, radius);
+    rc = dense_filter_stage(c, X, n, split, coarse, sub ? W : nullptr);
     if (rc) return rc;
   }
   StageTimer t(c, 2);
@@ -436,7 +466,6 @@ struct PlaneOperands {
   ~PlaneOperands() { c->mu = mu; c->mu_norm2 = mu_norm2; c->xn32 = xn32; }
 };
 
-static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split, bool coarse);
 
 static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
                                  int64_t n, const float *W, int32_t *bmus, bool cleared) {
@@ -455,7 +484,7 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
   }
   {
     StageTimer t(c, 1);
-    rc = dense_filter_stage(c, nullptr, n, true, coarse);
+    rc = dense_filter_stage(c, nullptr, n, true, coarse, nullptr);
     if (rc) return rc;
   }
   StageTimer t(c, 2);
@@ -766,6 +795,7 @@ void som_destroy(som_ctx *c) {
   dev_free(c->mu); dev_free(c->mu_partial); dev_free(c->Wc); dev_free(c->zero16); dev_free(c->mu_norm2);
   dev_free(c->Wh); dev_free(c->Wh1); dev_free(c->node_of); dev_free(c->pos_of); dev_free(c->wscale);
   free_hot(c);
+  free_subspace(c);
   dev_free(c->csrd_mu); dev_free(c->csrd_mu_norm2); dev_free(c->csrd_xn);
   dev_free(c->hot_counts); dev_free(c->hot_rank); dev_free(c->hot_cols); dev_free(c->hot_Wc); dev_free(c->hot_Wh);
   dev_free(c->hot_wscale);
@@ -882,7 +912,7 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, !direct));
-  rc = direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg, true);
+  rc = direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg, true, radius);
   if (rc) return rc;
   return update_dense(c, data, n, bmus, codebook);
 }
@@ -982,7 +1012,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
     SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, !direct));
     if (dense) {
       rc = direct ? bmu_search_direct(c, c->d_data, c->d_n, codebook, bmus)
-                  : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true);
+                  : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true, cooled(radius0, radiusN, n_epochs, e, cooling));
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
@@ -1145,6 +1175,27 @@ int som_debug_select_margins(som_ctx *c, int64_t n, double *margin_out) {
   if (!margin_out) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   if (n < 1 || n != c->debug_coarse_n) return fail(c, SOM_ERR_INVALID_ARG, "no coarse scores of %lld instances", (long long)n);
   SOM_LAUNCH(c, launch_margins(c, n, kCertifySelect, nullptr, margin_out));
+  return SOM_OK;
+}
+
+int som_debug_subspace(som_ctx *c, const float *data, int64_t n, const float *codebook, float *block_min, double *margin_out,
+                       int32_t *node_of, float *mu_out, int32_t *used) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  if (!data || !codebook || !block_min || !margin_out || !node_of || !mu_out || !used) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  int rc = check_rows(c, n);
+  if (!rc) rc = ensure_rows(c, n, true);
+  if (rc) return rc;
+  if (!two_level_ready(c, n) || !subspace_ready(c, n)) return fail(c, SOM_ERR_STATE, "no subspace for %lld instances", (long long)n);
+  rc = prepare_dense(c, data, n, codebook, false, false);
+  if (rc) return rc;
+  SOM_LAUNCH(c, launch_subspace(c, codebook, n));
+  SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, true));
+  SOM_LAUNCH(c, launch_margins(c, n, kCertifySubspace, nullptr, margin_out));
+  const size_t blocks = ((size_t)c->k + 127) / 128;
+  SOM_LAUNCH(c, hipMemcpyAsync(block_min, c->coarse_min, blocks * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(node_of, c->node_of, (size_t)c->k * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(mu_out, c->mu, (size_t)c->dim * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(used, &c->sub_state->use, sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
   return SOM_OK;
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <stddef.h>
 
@@ -61,6 +62,13 @@ constexpr int kSmoothMfmaMin = 32;         // shortest map line whose smoothing 
 constexpr int kSmoothSplitMin = 96;        // ... and on the bf16 ones with three-part operands
 constexpr int kCsrDenseMaxDim = 4096;      // registered sparse sets up to this many columns may be searched through dense planes
 constexpr double kCsrDenseMinDensity = 0.04;   // ... if at least this share of their entries is nonzero
+constexpr int kSub = 64;                   // coordinates in the code book's subspace (bmu_subspace.hip) ...
+constexpr int kSubConst = 29;              // ... of which three, from this one on, carry the node constants
+constexpr int kSubspaceParts = 512;        // workgroups of its node pass at most
+constexpr double kSubspaceMinWork = 7e10;  // multiply-adds a search has to save for the subspace to be tried
+constexpr double kSubspaceMaxArea = 100.0; // ... and map nodes per squared radius at most
+constexpr float kSubspaceLoss = 0x1p-8f;   // share of the largest |w'| that may lie outside for it to be used
+constexpr float kSubspaceLoss32 = 0x1p-11f;    // ... outside the first 32 coordinates for those to do
 constexpr int kHot = 256;                  // columns of the dense hot block of a registered sparse training set
 constexpr double kHotMinShare = 0.3;       // share of the nonzeros those columns must hold for the split to be used
 constexpr int kProfMax = 512;              // event brackets kept per stage between two reads
@@ -75,6 +83,17 @@ struct CandView {
   float *val;      // [n][kCand]
   int32_t *idx;    // [n][kCand], -1 = empty slot
   float *over;     // [n] smallest score not kept (+inf if none)
+};
+
+// What the coarse pass needs to know of the subspace of the code book (bmu_subspace.hip), decided on the device.
+struct SubspaceState {
+  int use;                 // the coarse pass runs on the coordinates: 1 the first 32 of them, 2 all 64, 0 it does not
+  float e;                 // largest |w'_i - V^T u_i| (of the first 32, if use = 1)
+  float u, u1;             // largest |u_i|; largest sum_r |u_ir| times the largest |V_r|
+  float ulost;             // largest |u_i - hi(u_i)|
+  float wm;                // largest |w'_i|
+  float uscale;            // power of two the coordinates of the nodes were divided by
+  float cscale;            // ... and their constants c_i
 };
 
 // Epoch parameters produced on the device by the cooling kernel.
@@ -212,6 +231,15 @@ struct som_ctx {
   float *xlost;               // [n_cap] |x' - hi(x')| of the instances, with Xh1
   int64_t debug_coarse_n;     // instances of the last som_debug_scores_dense, if it ran the coarse pass
   int32_t *node_of, *pos_of;  // [k] order of the nodes in the two-level search's planes, and its inverse
+  // subspace of the code book (bmu_subspace.hip), lazily allocated with Xh1 where the searches are large enough
+  float *sub_S;               // [kSub][dim rounded up to 64] random combinations of the centred nodes
+  double *sub_G;              // [2][kSub][kSub] their Gram matrix, the transposed inverse of its Cholesky factor
+  _Float16 *sub_Vp, *sub_Vt;  // the basis as hi/lo planes in two orders
+  _Float16 *sub_U1;           // [k][kSub] hi halves of the nodes' coordinates
+  float *sub_part;            // [kSubspaceParts][5] maxima per workgroup
+  som::SubspaceState *sub_state;
+  _Float16 *sub_Y1;           // [n_cap][kSub] hi halves of the instances' coordinates
+  float *sub_yscale, *sub_err;    // [n_cap] their scales, and the bounds on their dot products' errors
   float *hot_P;           // [ceil(k/128)][n][128] dot products of the hot parts divided by the instance scale
 
   // dense planes of the registered sparse training set (som_set_sparse_dense_filter); built on first use
@@ -280,10 +308,16 @@ constexpr int64_t kTwoLevelMaxTable = 8ll << 30;
 int bmu_dense_h_groups(const som_ctx *c, int64_t n);
 hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump, bool ordered = false /* dump: rows in the order node_of */);            // Xh, Wh -> candidates (or all scores)
 int bmu_dense_h_fine_groups(const som_ctx *c, int64_t n);
-hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump);              // bmu_coarse.hip: Xh1, Wh1 -> coarse_min (or all scores)
+// bmu_coarse.hip: Xh1, Wh1 -> coarse_min (or all scores); sub: on the subspace's coordinates if sub_state says so
+hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, bool sub = false);
+// bmu_subspace.hip
+bool subspace_eligible(const som_ctx *c, int64_t n);
+bool subspace_likely(const som_ctx *c, double radius);
+size_t subspace_vector_halves(const som_ctx *c);     // size of sub_Vp and of sub_Vt
+hipError_t launch_subspace(som_ctx *c, const float *W, int64_t n);             // Wh, Xh1 -> sub_*
 hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n);                     // sort_val[0], tile_cnt, tile_list -> candidates
 // bmu_two_level.hip
-hipError_t launch_select_blocks(som_ctx *c, int64_t n);                        // coarse_min -> coarse_key, coarse_mask
+hipError_t launch_select_blocks(som_ctx *c, int64_t n, bool sub = false);      // coarse_min -> coarse_key, coarse_mask
 constexpr int kPatchRows = 12;
 hipError_t launch_patch_order(som_ctx *c);                                     // -> node_of, pos_of
 hipError_t launch_tile_lists(som_ctx *c, int64_t n);                           // coarse_mask, sort_val[0] -> tile_cnt, tile_list
@@ -317,7 +351,8 @@ constexpr int kListTicketStride = 1088;      // ... 4 KB + 256 B apart: another 
 constexpr int kListWords = kListCounts + kListTickets * kListTicketStride;
 constexpr int kUnitCounts = 4;     // first of the eight work-list lengths in it
 constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits, wlost_bits
-enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4 };      // whose rounding bound the margin uses
+constexpr int kSubTicketWord = 17; // arrivals of k_subspace_coords
+enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4, kCertifySubspace = 5 };      // whose rounding bound the margin uses
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus,
                           bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */);
 hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr, double *out,
@@ -396,6 +431,13 @@ hipError_t launch_probe_xcc(hipStream_t stream, int32_t *out, int n_blocks);
 // distance of any node gets node 0 whatever order the nodes come in).
 __device__ __forceinline__ bool nearer(double d2, int i, double best, int arg) {
   return d2 < best || (d2 == best && best < INFINITY && i < arg);
+}
+
+// Value of a cooled quantity (radius, learning rate) in an epoch of a schedule.
+__host__ __device__ inline double cooled(double v0, double vN, int n_epochs, int epoch, int kind) {
+  if (n_epochs <= 1) return v0;
+  const double t = (double)epoch / (double)(n_epochs - 1);
+  return kind == SOM_COOL_EXPONENTIAL ? v0 * pow(vN / v0, t) : v0 + (vN - v0) * t;
 }
 
 // ---------------------------------------------------------------- device helpers

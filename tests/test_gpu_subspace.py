@@ -1,0 +1,159 @@
+"""The coarse pass of the two-level search in the subspace of a smooth code book: its block minima against fp64 scores and
+the margin of the block selection, at the ranks where the device's choice of the coordinates changes and at the edges of
+its tiles; whole epochs against the oracle; what is left out of it (code books of full rank, non-finite rows)."""
+import numpy as np
+import pytest
+
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _book(rng, k, dim, rank, scale=1.0):
+    """k rows in `rank` directions (of sizes that fall off a hundredfold), plus a common row; rank 0: any rows."""
+    if rank == 0:
+        return rng.random((k, dim)).astype(np.float32) * np.float32(scale)
+    a = rng.standard_normal((k, rank)) * np.logspace(0, -2, rank)
+    b = np.linalg.qr(rng.standard_normal((dim, rank)))[0].T
+    return (scale * (rng.random(dim) + a @ b)).astype(np.float32)
+
+
+def _minima(W, X, rows, cols):
+    from paper_1305_1422_amd import Som, capi
+    k, dim = W.shape
+    n = X.shape[0]
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    m = torch.empty(((k + 127) // 128, n), dtype=torch.float32, device="cuda")
+    margin = torch.empty(n, dtype=torch.float64, device="cuda")
+    node_of = torch.empty(k, dtype=torch.int32, device="cuda")
+    mu = torch.empty(dim, dtype=torch.float32, device="cuda")
+    used = torch.empty(1, dtype=torch.int32, device="cuda")
+    capi.som_debug_subspace(som.ctx, P.to_dev(X), som.codebook, m, margin, node_of, mu, used)
+    out = m.cpu().numpy(), margin.cpu().numpy(), node_of.cpu().numpy(), mu.cpu().numpy(), int(used.item())
+    som.close()
+    return out
+
+
+@pytest.mark.parametrize("rows,cols,dim,n,rank,want", [
+    (12, 25, 65, 300, 7, 1), (1, 33, 128, 1, 28, 1), (16, 16, 255, 257, 30, 2), (37, 7, 256, 255, 60, 2), (23, 45, 1000, 520, 12, 1),
+    (40, 13, 2048, 64, 45, 2), (9, 57, 97, 1000, 90, 0), (20, 20, 300, 129, 0, 0), (5, 5, 70, 33, 3, 1)])
+@pytest.mark.parametrize("data", ["near", "offset", "sizes"])
+def test_block_minima_within_the_margin(rows, cols, dim, n, rank, want, data):
+    rng = np.random.default_rng(8000 + dim + n)
+    k = rows * cols
+    W = _book(rng, k, dim, rank)
+    X = W[rng.integers(0, k, n)] + 0.2 * rng.standard_normal((n, dim)).astype(np.float32)
+    if data == "offset":                       # data and code book far from the origin
+        W, X = W + np.float32(300), X + np.float32(300)
+    if data == "sizes":                        # instances of very different norms, one at the centre
+        X = X * np.exp2(rng.integers(-18, 18, (n, 1))).astype(np.float32)
+        X[0] = 0.0
+    m, margin, node_of, mu, used = _minima(W, X, rows, cols)
+    if data == "near":
+        assert used == want
+    assert np.array_equal(np.sort(node_of), np.arange(k))
+    xc = (X - mu).astype(np.float32).astype(np.float64)
+    wc = (W - mu).astype(np.float32).astype(np.float64)[node_of]
+    exact = (wc ** 2).sum(1)[None, :] - 2.0 * xc @ wc.T
+    want_m = np.stack([exact[:, b:b + 128].min(1) for b in range(0, k, 128)])
+    err = np.abs(m.astype(np.float64) - want_m).max(0)
+    assert np.all(err <= 0.5 * margin), (2 * err / margin).max()
+    print(f"used {used}, worst error / half the margin {(2 * err / margin).max():.3f}, margin {margin.mean():.2e}")
+
+
+@pytest.mark.parametrize("rows,cols,dim,n,map_type,grid", [(30, 36, 96, 3000, "toroid", "square"), (33, 35, 200, 1999, "planar", "hexagonal"),
+                                                           (40, 29, 1030, 700, "planar", "square")])
+def test_epochs_of_a_schedule(oracle, rows, cols, dim, n, map_type, grid):
+    """From a random code book (full rank) over wide radii (few directions) to a narrow one: registered and not."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8100 + dim)
+    means = rng.random((11, dim))
+    X = (means[rng.integers(11, size=n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    som = Som(rows, cols, dim, map_type, grid, codebook=torch.from_numpy(rng.random((rows * cols, dim)).astype(np.float32)),
+              filter="two_level")
+    Xd = P.to_dev(X)
+    capi.som_set_data_dense(som.ctx, Xd)
+    for radius in (15.0, 11.0, 7.0, 4.0, 1.0):
+        P.epoch_parity_dense(oracle, som, X, Xd, radius, P.MAP[map_type], P.GRID[grid])
+        P.epoch_parity_dense(oracle, som, X[:501], Xd[:501].clone(), radius, P.MAP[map_type], P.GRID[grid])
+    som.close()
+
+
+def test_equal_rows_and_copies(oracle):
+    """A code book of equal rows (no direction at all), and one whose instances' nearest nodes have copies in other blocks:
+    the lowest index wins."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8200)
+    rows, cols, dim, n = 40, 30, 130, 400
+    k = rows * cols
+    W = np.tile(rng.random((1, dim)).astype(np.float32), (k, 1))
+    X = rng.random((n, dim)).astype(np.float32)
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    assert np.all(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy() == 0)
+    W = _book(rng, k, dim, 9)
+    W[600:1100] = W[50:550]
+    som.codebook.copy_(P.to_dev(W))
+    X = (W[rng.integers(600, 1100, n)] + 0.001 * rng.standard_normal((n, dim))).astype(np.float32)
+    assert np.array_equal(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy(), oracle.bmu_dense(X, W))
+    som.close()
+
+
+def test_non_finite_rows_go_the_general_way(oracle):
+    """Infinities and NaN among the instances and the nodes: the same nodes as a search that does not try the subspace."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8300)
+    rows, cols, dim, n = 36, 30, 100, 600
+    k = rows * cols
+    W = _book(rng, k, dim, 8)
+    X = (W[rng.integers(0, k, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    X[5, 3] = np.inf
+    X[77, 99] = np.nan
+    X[300] = -np.inf
+    for spoil in (None, np.inf, np.nan):
+        V = W.copy()
+        if spoil is not None:
+            V[41, 7] = spoil
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(V), filter="two_level")
+        want = som.bmus(P.to_dev(X)).cpu().numpy()
+        got = som.train_epoch(P.to_dev(X), 20.0).cpu().numpy()
+        som.close()
+        assert np.array_equal(got, want)
+
+
+def test_recorded_epochs(oracle):
+    """Epochs recorded into a graph: the choice of the coordinates is made again in every replay."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8400)
+    rows, cols, dim, n = 30, 40, 150, 900
+    k = rows * cols
+    books = [_book(rng, k, dim, r) for r in (10, 50, 0)]
+    X = (books[0][rng.integers(0, k, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        Xd = P.to_dev(X)
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(books[0]), filter="two_level")
+        capi.som_set_data_dense(som.ctx, Xd)
+        start = P.to_dev(books[0])
+        b = torch.empty(n, dtype=torch.int32, device="cuda")
+
+        def epoch():
+            som.codebook.copy_(start)
+            som.train_epoch(Xd, 18.0, bmus=b)
+
+        epoch()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            epoch()
+        for W in books + books[:1]:
+            start.copy_(P.to_dev(W))
+            epoch()
+            eager = b.cpu().numpy()
+            P.check_bmus_dense(oracle, X, W, eager)
+            b.fill_(-1)
+            graph.replay()
+            assert np.array_equal(b.cpu().numpy(), eager)
+        stream.synchronize()
+        som.close()
