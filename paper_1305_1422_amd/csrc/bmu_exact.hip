@@ -311,7 +311,8 @@ __device__ __forceinline__ int nearest_listed(const float *__restrict__ x, const
 // union of the lists is compared with all 16 instances as one fp64 matrix product of rows relative to one of the nodes,
 //   d2 = |x~|^2 + |w~|^2 - 2 x~.w~,   x~ = x - w_0, w~ = w - w_0,
 // whose rounding is below (dim + 8) 2^-50 (|x~| + |w~|)^2; the nodes it cannot tell apart from the nearest - usually there are none - are compared
-// by the plain sums as before, so the decision is the same to the bit.  A union of more than kUnionCap
+// by the plain sums as before, so the decision is the same to the bit.  Bound by the fp64 matrix pipe; the product in fp32 took
+// half the time and left a dozen near-copies per instance to the plain sums (3,000 us).  A union of more than kUnionCap
 // nodes, or of more than half of what the lists hold together, is not worth it: those lists go one by one.
 constexpr int kListTileMin = 4096;
 constexpr int kUnionCap = 320, kUnionHash = 1024;
@@ -392,12 +393,13 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
       continue;
     }
     // the product: lane -> instance / node l16, features 4 quad .. 4 quad + 3 of every 16, which four instructions take one
-    // each; two tiles of 16 nodes per wavefront at a time
+    // each; a wavefront takes the 16-node tiles wave, wave + 4, ... in pairs
     const float *w0 = W + (int64_t)s_node[0] * dim;
     const float *x = X + (int64_t)(s_row[l16] < 0 ? s_row[0] : s_row[l16]) * dim;
-    for (int u0 = 32 * wave; u0 < un; u0 += 128) {
+    for (int u0 = 16 * wave; u0 < un; u0 += 128) {
+      const bool two = u0 + 64 < un;               // uniform over the wavefront
       const float *wa = W + (int64_t)s_node[min(u0 + l16, un - 1)] * dim;
-      const float *wb = W + (int64_t)s_node[min(u0 + 16 + l16, un - 1)] * dim;
+      const float *wb = W + (int64_t)s_node[min(u0 + 64 + l16, un - 1)] * dim;
       typedef double f64x4 __attribute__((ext_vector_type(4)));
       f64x4 da = {0.0, 0.0, 0.0, 0.0}, db = {0.0, 0.0, 0.0, 0.0};
       double xs = 0.0, as = 0.0, bs = 0.0;
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
           xv = row_load<kWide>(x, c + 16, dim);
           rv = row_load<kWide>(w0, c + 16, dim);
           av = row_load<kWide>(wa, c + 16, dim);
-          bv = row_load<kWide>(wb, c + 16, dim);
+          if (two) bv = row_load<kWide>(wb, c + 16, dim);
         }
         row_tail<kWide>(xc, c, dim);
         row_tail<kWide>(rc, c, dim);
@@ -418,12 +420,15 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
         row_tail<kWide>(bc, c, dim);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const double r = (double)rc[e], xd = (double)xc[e] - r, ad = (double)ac[e] - r, bd = (double)bc[e] - r;
+          const double r = (double)rc[e], xd = (double)xc[e] - r, ad = (double)ac[e] - r;
           xs = fma(xd, xd, xs);
           as = fma(ad, ad, as);
-          bs = fma(bd, bd, bs);
           da = __builtin_amdgcn_mfma_f64_16x16x4f64(xd, ad, da, 0, 0, 0);
-          db = __builtin_amdgcn_mfma_f64_16x16x4f64(xd, bd, db, 0, 0, 0);
+          if (two) {
+            const double bd = (double)bc[e] - r;
+            bs = fma(bd, bd, bs);
+            db = __builtin_amdgcn_mfma_f64_16x16x4f64(xd, bd, db, 0, 0, 0);
+          }
         }
       }
       xs += __shfl_xor(xs, 16, 64); xs += __shfl_xor(xs, 32, 64);
@@ -432,13 +437,13 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
       if (quad == 0) {
         if (u0 == 0) s_xn[l16] = xs;
         if (u0 + l16 < un) s_wn[u0 + l16] = as;
-        if (u0 + 16 + l16 < un) s_wn[u0 + 16 + l16] = bs;
+        if (u0 + 64 + l16 < un) s_wn[u0 + 64 + l16] = bs;
       }
       // column l16 = node, rows quad + 4 v = instances (the products alone: the norms are added when all are there)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         if (u0 + l16 < un) s_d2[quad + 4 * v][u0 + l16] = da[v];
-        if (u0 + 16 + l16 < un) s_d2[quad + 4 * v][u0 + 16 + l16] = db[v];
+        if (u0 + 64 + l16 < un) s_d2[quad + 4 * v][u0 + 64 + l16] = db[v];
       }
     }
     __syncthreads();
@@ -880,11 +885,12 @@ hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr
 }
 
 hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus) {
+  const int blocks = 3 * c->n_cu;          // what their LDS leaves room for
   if (c->dim >= 4)
-    hipLaunchKernelGGL(k_refine_lists_dense<true>, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, X, W,
+    hipLaunchKernelGGL(k_refine_lists_dense<true>, dim3(blocks), dim3(256), 0, c->stream, X, W,
                        c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
   else
-    hipLaunchKernelGGL(k_refine_lists_dense<false>, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, X, W,
+    hipLaunchKernelGGL(k_refine_lists_dense<false>, dim3(blocks), dim3(256), 0, c->stream, X, W,
                        c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
   return hipGetLastError();
 }
