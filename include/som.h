@@ -399,13 +399,14 @@ int som_debug_select_margins(som_ctx *ctx, int64_t n, double *margin_out);
  *   margin_out [n]  fp64: the margins of the block selection (a score is off by half of it at most);
  *   node_of [k]     the node at every place of that order;
  *   mu_out [dim]    the centring vector;
- *   used [1]        0: the code book does not lie in so few directions, the pass ran on the full rows;
- *                   1, 2: it ran on the first 32 or on all 64 coordinates.
+ *   used [2]        used[0] = 0: the code book does not lie in so few directions, the pass ran on the full rows;
+ *                   1, 2: it ran on the first 32 or on all 64 coordinates; used[1] = 1: so would the fine pass;
+ *   loss [2]        the bounds on what the first 32 and all 64 coordinates leave of the largest centred node.
  * Errors: NULL pointers, n out of range -> SOM_ERR_INVALID_ARG; no two-level search or no subspace for this n,
  * dim and filter -> SOM_ERR_STATE.
  */
 int som_debug_subspace(som_ctx *ctx, const float *data, int64_t n, const float *codebook, float *block_min,
-                       double *margin_out, int32_t *node_of, float *mu_out, int32_t *used);
+                       double *margin_out, int32_t *node_of, float *mu_out, int32_t *used, float *loss);
 
 /*
  * som_debug_mfma_f16 - test hook (not an operation of the paper): `count` independent
@@ -442,7 +443,9 @@ int som_get_stats(som_ctx *ctx, int64_t *out);
  * som_two_level_stats - how selective the coarse pass of the most recent dense BMU search on ctx was
  * (see som_set_filter, SOM_FILTER_TWO_LEVEL; synchronises the stream).  out is a HOST pointer to two
  * int64 values: the (tile of 128 instances, block of 128 nodes) pairs the second pass worked on, and all
- * such pairs.  Both are 0 when that search ran in one level (or no dense search has run yet).
+ * such pairs.  Both are 0 when that search ran in one level (or no dense search has run yet).  After a
+ * sparse epoch that tried the subspace of the code book they are those of its coordinates' search, the first 0 if
+ * the code book turned out not to lie in it.
  */
 int som_two_level_stats(som_ctx *ctx, int64_t *out);
 

@@ -119,7 +119,7 @@ def load():
     L.som_debug_select_margins.restype = i32
     L.som_debug_select_margins.argtypes = [vp, i64, vp]
     L.som_debug_subspace.restype = i32
-    L.som_debug_subspace.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp, vp]
+    L.som_debug_subspace.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     L.som_debug_scores_dense.restype = i32
     L.som_debug_scores_dense.argtypes = [vp, vp, i64, vp, vp, vp, vp]
     L.som_debug_scores_csr.restype = i32
@@ -376,16 +376,16 @@ def som_debug_select_margins(ctx, margin_out) -> None:
     _check(ctx, load().som_debug_select_margins(ctx, margin_out.shape[0], _ptr(margin_out, torch.float64, "margin_out")))
 
 
-def som_debug_subspace(ctx, data, codebook, block_min, margin_out, node_of, mu_out, used) -> None:
+def som_debug_subspace(ctx, data, codebook, block_min, margin_out, node_of, mu_out, used, loss) -> None:
     """Test hook: block minima [ceil(k / 128)][n] of the coarse pass in the code book's subspace, their margins [n]
-    (float64), the order of the nodes [k], the centring vector and which coordinates were used [1]."""
+    (float64), the order of the nodes [k], the centring vector, which coordinates were used [2] and what they leave out [2]."""
     import torch
     _check(ctx, load().som_debug_subspace(ctx, _ptr(data, torch.float32, "data"), data.shape[0],
                                           _ptr(codebook, torch.float32, "codebook"),
                                           _ptr(block_min, torch.float32, "block_min"),
                                           _ptr(margin_out, torch.float64, "margin_out"),
                                           _ptr(node_of, torch.int32, "node_of"), _ptr(mu_out, torch.float32, "mu_out"),
-                                          _ptr(used, torch.int32, "used")))
+                                          _ptr(used, torch.int32, "used"), _ptr(loss, torch.float32, "loss")))
 
 
 def som_debug_scores_dense(ctx, data, codebook, scores, mu_out, margin_out) -> None:

@@ -56,24 +56,27 @@ struct CoarseOperands {
   const float *Xh, *Wh, *xscale, *wscale;
   int nK;                            // chunks of 64 features
 };
-// state (may be null): the device's decision to run on the coordinates in the code book's subspace.
+// Coordinates in the code book's subspace, and the device's decision to run on them.
 struct CoarseSubspace {
   const SubspaceState *state;
   const _Float16 *Y1, *U1;
   const float *yscale;
 };
+constexpr int kSubRing = 64 << 10;   // bytes
 
 // The pass on the subspace's coordinates (bmu_subspace.hip), 16 kKS of them: the instances' operands stay in registers, the
-// nodes' rows go through a ring of four LDS stages of 256 rows, loaded three tiles ahead.  The node constants are
-// among the coordinates (three halves per node), so an accumulator holds the score divided by a negative factor of the
-// instance, and the epilogue is a running three-way maximum in the shadow of the next matrix instructions.  Bound by the
-// matrix pipes: 1,000,000 instances x 10,000 nodes 1,754 us (64 coordinates as one chunk of the general loop below) -> 708 us (the first 32).
+// nodes' rows go through a ring of LDS stages of 256 rows (32 coordinates: four of 16 KB, loaded three tiles ahead; 64: two of 32 KB).  The
+// node constants are among the coordinates (three halves per node), so an accumulator holds the score divided by a negative factor of
+// the instance, and the epilogue is a running three-way maximum.  A kernel of its own, because it needs half the registers and LDS of the general
+// one: two workgroups per CU, four wavefronts per SIMD, fill each other's barriers.  Bound by the matrix pipes and the maxima beside
+// them: 1,000,000 instances x 10,000 nodes 1,754 us (64 coordinates as one chunk of the general loop below) -> 708 (the first 32 in
+// a loop like this one inside that kernel) -> 633.
 template <int kKS>
 __device__ __forceinline__ void coarse_in_subspace(const CoarseSubspace &sub, float *__restrict__ lds, int64_t n, int k,
                                                    int64_t inst0, int nb_first, int nNB, float *__restrict__ out) {
-  constexpr int kStages = 4;
+  constexpr int kStages = kKS == 2 ? 4 : 2;
   constexpr int kRowBytes = 32 * kKS, kSlots = 2 * kKS, kTileBytes = kCTN * kRowBytes;
-  static_assert(kStages * kTileBytes <= 2 * (kCTN + kCTI) * kCRow * 4, "the ring fits the stages of the general loop");
+  static_assert(kStages * kTileBytes == kSubRing, "the ring");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wi = wave & 3, l32 = lane & 31, lhi = lane >> 5;
   // 16-byte slot of a row that slot `s` is kept in: any eight consecutive rows read one slot from eight different bank groups
@@ -116,8 +119,8 @@ __device__ __forceinline__ void coarse_in_subspace(const CoarseSubspace &sub, fl
       if (inst[ni] < n) out[(int64_t)best_block * n + inst[ni]] = best[ni];
   };
   for (int t = 0; t < nNB; ++t) {
-    // the loads of tile t have landed when at most those of t + 1 and t + 2 are in flight (loads return in order)
-    if (t + 2 < nNB) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kKS));
+    // the loads of tile t have landed when at most those of the tiles behind it are in flight (loads return in order)
+    if (kStages == 4 && t + 2 < nNB) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kKS));
     else __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     store();
@@ -146,11 +149,25 @@ __device__ __forceinline__ void coarse_in_subspace(const CoarseSubspace &sub, fl
   store();
 }
 
+__global__ __launch_bounds__(kCThreads, 4) void k_bmu_coarse_subspace(CoarseSubspace sub, int64_t n, int k, int groups,
+                                                                      float *__restrict__ out) {
+  __shared__ __attribute__((aligned(16))) float s_ring[kSubRing / 4];
+  const int use = sub.state->use;
+  if (!use) return;                  // the same for every workgroup
+  const int64_t slot_id = blockIdx.x >> 3, tile = (slot_id / groups) * 8 + (blockIdx.x & 7);      // as in k_bmu_coarse
+  const int group = (int)(slot_id % groups), nNB_all = (k + kCTN - 1) / kCTN, nb_per = (nNB_all + groups - 1) / groups;
+  const int nb_first = group * nb_per, nNB = min(nb_per, nNB_all - nb_first);
+  if (tile * kCTI >= n || nNB <= 0) return;
+  if (use == 1) coarse_in_subspace<2>(sub, s_ring, n, k, tile * kCTI, nb_first, nNB, out);
+  else coarse_in_subspace<4>(sub, s_ring, n, k, tile * kCTI, nb_first, nNB, out);
+}
+
 template <bool kDump>
-__global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(CoarseOperands op, CoarseSubspace sub,
+__global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(CoarseOperands op, const SubspaceState *__restrict__ off,
                                                              const float *__restrict__ wc, int k_const, int64_t n, int k,
                                                              int groups, float *__restrict__ out,
                                                              const int32_t *__restrict__ node_of) {
+  if (off && off->use) return;
   const float *__restrict__ Xh = op.Xh, *__restrict__ Wh = op.Wh, *__restrict__ xscale = op.xscale, *__restrict__ wscale = op.wscale;
   const int nK = op.nK;
   __shared__ __attribute__((aligned(16))) float s_stage[2 * (kCTN + kCTI) * kCRow];
@@ -180,11 +197,6 @@ __global__ __launch_bounds__(kCThreads, 1) void k_bmu_coarse(CoarseOperands op, 
   const int nNB = min(nb_per, nNB_all - nb_first);
   if (nNB <= 0) return;              // uniform over the workgroup
   const int total = nK * nNB;
-  if (!kDump && sub.state && sub.state->use) {           // the same for every workgroup
-    if (sub.state->use == 1) coarse_in_subspace<2>(sub, s_stage, n, k, inst0, nb_first, nNB, out);
-    else coarse_in_subspace<4>(sub, s_stage, n, k, inst0, nb_first, nNB, out);
-    return;
-  }
 
   // ---- loader: one instruction fills 8 tile rows; wavefront w issues W slots 4 w .. 4 w + 3 and X slots
   // 4 w .. 4 w + 3.  Rows past the end of an operand are redirected to its last row (their outputs are
@@ -375,20 +387,24 @@ static int bmu_coarse_groups(const som_ctx *c, int64_t n) {
 }
 
 // c->Xh1, c->Wh1 -> c->coarse_min [ceil(k/128)][n], or with `dump` every score [n][k] (test hook).
-hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, bool sub) {
+hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, SubspaceUse sub) {
   const int groups = bmu_coarse_groups(c, n);
   const int64_t tiles = (n + kCTI - 1) / kCTI;
   const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
   const int k_const = (c->k + kTN - 1) / kTN * kTN;      // the node constants are padded to whole blocks of 128
   const CoarseOperands op{reinterpret_cast<const float *>(c->Xh1), reinterpret_cast<const float *>(c->Wh1), c->xscale, c->wscale,
                           (c->dim + 63) / 64};
-  const CoarseSubspace cs{sub ? c->sub_state : nullptr, c->sub_Y1, c->sub_U1, c->sub_yscale};
+  if (sub) {
+    const CoarseSubspace cs{c->sub_state, c->sub_Y1, c->sub_U1, c->sub_yscale};
+    hipLaunchKernelGGL(k_bmu_coarse_subspace, dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, cs, n, c->k, groups, c->coarse_min);
+    if (sub == kSubOnly) return hipGetLastError();
+  }
   if (dump)
-    hipLaunchKernelGGL((k_bmu_coarse<true>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, cs, c->wn32,
+    hipLaunchKernelGGL((k_bmu_coarse<true>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, nullptr, c->wn32,
                        k_const, n, c->k, groups, dump, c->node_of);
   else
-    hipLaunchKernelGGL((k_bmu_coarse<false>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, cs, c->wn32,
-                       k_const, n, c->k, groups, c->coarse_min, c->node_of);
+    hipLaunchKernelGGL((k_bmu_coarse<false>), dim3((unsigned)blocks), dim3(kCThreads), 0, c->stream, op, sub ? c->sub_state : nullptr,
+                       c->wn32, k_const, n, c->k, groups, c->coarse_min, c->node_of);
   return hipGetLastError();
 }
 

@@ -67,7 +67,9 @@ constexpr int kCtCols = 64;
 __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__restrict__ W, const float *__restrict__ mu,
                                                               const float *__restrict__ qstep, int k, int dim,
                                                               int kpad, int cols_per_slab, int16_t *__restrict__ Wt,
-                                                              double *__restrict__ partial) {
+                                                              double *__restrict__ partial,
+                                                              const SubspaceState *__restrict__ off) {
+  if (off && off->use) return;
   // the tile turned: [column][pair of neighbouring nodes] as 32-bit words (two int16), so that a thread
   // writes one word per two entries and the columns leave through 16-byte reads; 33 words per row keep
   // the column-wise writes of a wavefront on different banks
@@ -174,7 +176,9 @@ __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__res
 
 __global__ __launch_bounds__(256) void k_finish_node_constants(const double *__restrict__ partial, int slabs, int k,
                                                                float *__restrict__ cn, double *__restrict__ wn64,
-                                                               unsigned *__restrict__ max_bits) {
+                                                               unsigned *__restrict__ max_bits,
+                                                               const SubspaceState *__restrict__ off) {
+  if (off && off->use) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   float vmax = 0.f;
   if (i < k) {
@@ -216,7 +220,9 @@ __global__ __launch_bounds__(256) void k_bmu_csr_sliced(const int64_t *__restric
                                                         const float *__restrict__ thr, int32_t *__restrict__ cnt,
                                                         int32_t *__restrict__ list, float *__restrict__ dump,
                                                         const float *__restrict__ phot,
-                                                        const float *__restrict__ hot_xscale) {
+                                                        const float *__restrict__ hot_xscale,
+                                                        const SubspaceState *__restrict__ off) {
+  if (!kCollect && off && off->use) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int slice = blockIdx.x & 7;
@@ -359,7 +365,7 @@ __global__ __launch_bounds__(256) void k_bmu_csr_sliced(const int64_t *__restric
 
 template <bool kCollect>
 static void launch_sliced(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
-                          float *dump, bool hot) {
+                          float *dump, bool hot, const SubspaceState *off) {
   const float *phot = hot ? c->hot_P : nullptr;
   int64_t groups = (n * c->csr_sweeps + 3) / 4;                   // workgroups per slice
   const int64_t cap = (int64_t)c->n_cu;                           // 8 slices x n_cu = 8 workgroups per CU
@@ -371,7 +377,7 @@ static void launch_sliced(som_ctx *c, const int64_t *indptr, const int32_t *indi
   hipLaunchKernelGGL((k_bmu_csr_sliced<A, kCollect>), grid, dim3(256), 0, c->stream, indptr, indices, values,        \
                      reinterpret_cast<const int16_t *>(c->Wt), c->kpad, c->csr_sweeps, nullptr, c->wn32, n, c->k,   \
                      c->dim, out, c->row_q, c->collect_rows, work, c->collect_thr, c->collect_cnt,    \
-                     c->collect_list, dump, phot, c->hot_xscale)
+                     c->collect_list, dump, phot, c->hot_xscale, off)
   switch (c->csr_acc) {
     case 1: SOM_SLICED(1); break;
     case 2: SOM_SLICED(2); break;
@@ -397,7 +403,9 @@ static void launch_sliced(som_ctx *c, const int64_t *indptr, const int32_t *indi
 // per node range and slice.
 __global__ __launch_bounds__(256) void k_scale_values(const int32_t *__restrict__ indices,
                                                       const float *__restrict__ values, int64_t nnz, int dim,
-                                                      const float *__restrict__ qstep, float *__restrict__ out) {
+                                                      const float *__restrict__ qstep, float *__restrict__ out,
+                                                      const SubspaceState *__restrict__ off) {
+  if (off && off->use) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < nnz; p += stride) {
     int c = indices[p];
@@ -406,13 +414,13 @@ __global__ __launch_bounds__(256) void k_scale_values(const int32_t *__restrict_
   }
 }
 
-hipError_t launch_scale_values(som_ctx *c, const int32_t *indices, const float *values, int64_t nnz) {
+hipError_t launch_scale_values(som_ctx *c, const int32_t *indices, const float *values, int64_t nnz, const SubspaceState *off) {
   if (nnz < 1) return hipSuccess;                       // every row empty: nothing to scale (and no buffer yet)
   if (!c->vq || c->vq_cap < nnz) return hipErrorInvalidValue;
   int64_t cb = (nnz + 255) / 256;
   if (cb > (int64_t)c->n_cu * 16) cb = (int64_t)c->n_cu * 16;
   hipLaunchKernelGGL(k_scale_values, dim3((unsigned)cb), dim3(256), 0, c->stream, indices, values, nnz, c->dim,
-                     c->qstep, c->vq);
+                     c->qstep, c->vq, off);
   return hipGetLastError();
 }
 
@@ -457,15 +465,15 @@ hipError_t launch_validate_csr(som_ctx *c, const int64_t *indptr, const int32_t 
 }
 
 hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
-                                 int64_t n, bool collect, float *dump, bool hot) {
-  if (collect) launch_sliced<true>(c, indptr, indices, values, n, nullptr, hot);
-  else launch_sliced<false>(c, indptr, indices, values, n, dump, hot);
+                                 int64_t n, bool collect, float *dump, bool hot, const SubspaceState *off) {
+  if (collect) launch_sliced<true>(c, indptr, indices, values, n, nullptr, hot, off);
+  else launch_sliced<false>(c, indptr, indices, values, n, dump, hot, off);
   return hipGetLastError();
 }
 
 // Centred transposed 16-bit code book, node constants (wn32 = c_i), |w_i|^2 (wn64) and the largest |w'_i|^2
 // (wmax_bits), from mu and qstep: one pass over W.
-hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W) {
+hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const SubspaceState *off) {
   const int tiles = c->kpad / kCtNodes;                       // kpad is a multiple of 512
   // enough workgroups for twelve per CU: a workgroup walks its slab one tile after the other and waits for
   // every tile's loads, so the memory system is kept busy by their number (two per CU: 2.3 TB/s)
@@ -478,9 +486,9 @@ hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W) {
   cols_per_slab = (cols_per_slab + kCtCols - 1) / kCtCols * kCtCols;
   slabs = (c->dim + cols_per_slab - 1) / cols_per_slab;
   hipLaunchKernelGGL(k_center_transpose_q16, dim3((unsigned)tiles, (unsigned)slabs), dim3(256), 0, c->stream, W, c->mu,
-                     c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial);
+                     c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial, off);
   hipLaunchKernelGGL(k_finish_node_constants, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->ct_partial, slabs,
-                     c->k, c->wn32, c->wn64, c->wmax_bits);
+                     c->k, c->wn32, c->wn64, c->wmax_bits, off);
   return hipGetLastError();
 }
 

@@ -78,23 +78,29 @@ __device__ __forceinline__ void consume_scores(f32x16 (&tot)[2][2], const float 
       }
   }
   if (kCollect) {
+    // a lane marks its 32 nodes per instance first and reserves room for all it lists at once (an atomic per node: 350 us
+    // instead of 195 where 97,000 instances list 70 nodes each)
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    for (int ni = 0; ni < 2; ++ni) {
+      unsigned hit = 0;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int nl = wm * 64 + mfma_row(mi, v, lhi);
-        const float wnv = swn[nl];
-        const int node = node0 + nl;
+      for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) {
-          const float s = fmaf(factor[ni], tot[mi][ni][v], wnv);
-          if (s <= lim[ni] && node < k) {
-            const int pos = atomicAdd(&cnt[slot_of[ni]], 1);
-            if (pos < kListCap) list[slot_of[ni] * kListCap + pos] = node_of ? node_of[node] : node;
-          }
+        for (int v = 0; v < 16; ++v) {
+          const int nl = wm * 64 + mfma_row(mi, v, lhi);
+          const float s = fmaf(factor[ni], tot[mi][ni][v], swn[nl]);
+          hit |= (s <= lim[ni] && node0 + nl < k) ? 1u << (16 * mi + v) : 0u;
           tot[mi][ni][v] = 0.f;
         }
+      if (hit) {
+        int pos = atomicAdd(&cnt[slot_of[ni]], __popc(hit));
+        for (; hit && pos < kListCap; hit &= hit - 1, ++pos) {
+          const int b = __ffs((int)hit) - 1;
+          const int node = node0 + wm * 64 + mfma_row(b >> 4, b & 15, lhi);
+          list[slot_of[ni] * kListCap + pos] = node_of ? node_of[node] : node;
+        }
       }
+    }
     return;
   }
   // Filter mode.  After the first node blocks a score rarely beats the second-best of its lane, so

@@ -366,6 +366,15 @@ __device__ __forceinline__ void bmu_dense_h_unit(const float *__restrict__ Xh, c
                         out, kFine ? rows : nullptr, kFine ? node_of : nullptr);
 }
 
+// Operands of the fine and collect modes in the code book's subspace (bmu_subspace.hip), in the place of the full rows where the
+// device decided so: 64 coordinates are two chunks.  state may be null.
+struct FineSubspace {
+  const SubspaceState *state;
+  const float *Y2, *U2, *yscale;
+  int only;                          // there are no other operands
+  const SubspaceState *off;          // the launch does nothing where the device decided for the subspace
+};
+
 // Filter, dump, partial and fine modes: one unit per workgroup.  Collect mode: the number
 // of live instance tiles is only known on the device, so a fixed grid walks the units; its size is a
 // multiple of 8, which keeps unit mod 8 = workgroup mod 8 = the XCD the decoding assumes.
@@ -381,7 +390,18 @@ __global__ __launch_bounds__(128 * kHWI, 2) void k_bmu_dense_h(const float *__re
                                                         const float *__restrict__ thr, int32_t *__restrict__ cnt,
                                                         int32_t *__restrict__ list, const int32_t *__restrict__ tcnt,
                                                         const int32_t *__restrict__ tlist,
-                                                        const int32_t *__restrict__ node_of) {
+                                                        const int32_t *__restrict__ node_of, FineSubspace sub) {
+  if ((kMode == kHCollect || kMode == kHFine) && sub.state && sub.state->fine) {      // the same for every workgroup
+    Xh = sub.Y2;
+    Wh = sub.U2;
+    xscale = sub.yscale;
+    wscale = &sub.state->uscale;
+    nK = kSub / 32;
+    flush_chunks = kSub / 32;
+  } else if ((kMode == kHCollect || kMode == kHFine) && sub.only) {
+    return;
+  }
+  if (kMode == kHPartial && sub.off && sub.off->use) return;
   if (kMode == kHCollect) {
     const int64_t ntiles = ((int64_t)*n_slots + 64 * kHWI - 1) / (64 * kHWI);
     const int64_t units = (ntiles + 7) / 8 * 8 * groups;
@@ -445,17 +465,22 @@ hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump, bool ordered) 
   if (dump)
     hipLaunchKernelGGL((k_bmu_dense_h<kHDump>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream, Xh, Wh,
                        c->wn32, c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, dump, nullptr, nullptr, nullptr,
-                       nullptr, nullptr, nullptr, nullptr, ordered ? c->node_of : nullptr);
+                       nullptr, nullptr, nullptr, nullptr, ordered ? c->node_of : nullptr, FineSubspace{nullptr, nullptr, nullptr, nullptr, 0, nullptr});
   else
     hipLaunchKernelGGL((k_bmu_dense_h<kHFilter>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream, Xh, Wh,
                        c->wn32, c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, dump, nullptr, nullptr, nullptr,
-                       nullptr, nullptr, nullptr, nullptr, nullptr);
+                       nullptr, nullptr, nullptr, nullptr, nullptr, FineSubspace{nullptr, nullptr, nullptr, nullptr, 0, nullptr});
   return hipGetLastError();
+}
+
+static FineSubspace fine_subspace(const som_ctx *c, SubspaceUse sub) {
+  return FineSubspace{sub ? c->sub_state : nullptr, reinterpret_cast<const float *>(c->sub_Y2), reinterpret_cast<const float *>(c->sub_U2),
+                      c->sub_yscale, sub == kSubOnly, nullptr};
 }
 
 // Second pass of the two-level search: the split-fp16 filter over the instance tiles of the order
 // c->sort_val[0] and the node blocks c->tile_list lists for each (c->tile_cnt of them).
-hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n) {
+hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n, SubspaceUse sub) {
   const int groups = bmu_dense_h_fine_groups(c, n);
   const int64_t tiles = (n + 64 * kHWI - 1) / (64 * kHWI);
   const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
@@ -464,13 +489,13 @@ hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n) {
   hipLaunchKernelGGL((k_bmu_dense_h<kHFine>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream,
                      reinterpret_cast<const float *>(c->Xh), reinterpret_cast<const float *>(c->Wh), c->wn32,
                      c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, nullptr, c->sort_val[0],
-                     nullptr, nullptr, nullptr, nullptr, c->tile_cnt, c->tile_list, c->node_of);
+                     nullptr, nullptr, nullptr, nullptr, c->tile_cnt, c->tile_list, c->node_of, fine_subspace(c, sub));
   return hipGetLastError();
 }
 
 // Hot-column block of the sparse search: P[node block][n][128] = (x_hot . w'_hot) / (scale of the instance), from the
 // planes c->hot_Xh [n][kHot] and c->hot_Wh [k][kHot]; the same tiling and launch shape as the filter.
-hipError_t launch_hot_partial(som_ctx *c, int64_t n) {
+hipError_t launch_hot_partial(som_ctx *c, int64_t n, const SubspaceState *off) {
   const int groups = bmu_dense_h_groups(c, n);
   const int64_t tiles = (n + 64 * kHWI - 1) / (64 * kHWI);
   const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
@@ -478,7 +503,7 @@ hipError_t launch_hot_partial(som_ctx *c, int64_t n) {
   hipLaunchKernelGGL((k_bmu_dense_h<kHPartial>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream,
                      reinterpret_cast<const float *>(c->hot_Xh), reinterpret_cast<const float *>(c->hot_Wh), nullptr,
                      nullptr, c->hot_wscale, n, c->k, kHot / 32, split_flush_chunks(kHot), groups, out, c->hot_P,
-                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, FineSubspace{nullptr, nullptr, nullptr, nullptr, 0, off});
   return hipGetLastError();
 }
 
@@ -487,7 +512,7 @@ hipError_t launch_hot_partial(som_ctx *c, int64_t n) {
 // the live units.  Usually only a few instance tiles are live, so the node blocks are shared out
 // over up to 16 workgroups.
 // lists: the node blocks of every tile of 128 collect slots are given in c->ctile_cnt / c->ctile_list.
-hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists) {
+hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists, SubspaceUse sub) {
   const int nNB = (c->k + kTN - 1) / kTN;
   const int groups = nNB < 16 ? nNB : 16;
   const int64_t tiles = (n + 64 * kHWI - 1) / (64 * kHWI);
@@ -500,7 +525,7 @@ hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists) {
                      reinterpret_cast<const float *>(c->Xh), reinterpret_cast<const float *>(c->Wh), c->wn32,
                      c->xscale, c->wscale, n, c->k, nK, split_flush_chunks(c->dim), groups, out, nullptr, c->collect_rows, c->list_counts + 1,
                      c->collect_thr, c->collect_cnt, c->collect_list, lists ? c->ctile_cnt : nullptr,
-                     lists ? c->ctile_list : nullptr, lists ? c->node_of : nullptr);
+                     lists ? c->ctile_list : nullptr, lists ? c->node_of : nullptr, fine_subspace(c, sub));
   return hipGetLastError();
 }
 

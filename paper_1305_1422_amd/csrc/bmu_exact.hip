@@ -42,7 +42,9 @@ __global__ __launch_bounds__(256) void k_certify(CandView cand, int groups, cons
                                                  float *__restrict__ collect_thr,
                                                  int32_t *__restrict__ collect_cnt,
                                                  int32_t *__restrict__ list_counts, UnitWork work,
-                                                 const int32_t *__restrict__ order) {
+                                                 const int32_t *__restrict__ order,
+                                                 const SubspaceState *__restrict__ state, int runs_if) {
+  if (state && (state->use != 0) != (runs_if != 0)) return;
   // with `order` the instances are visited in that order, so that neighbours in it are appended to the
   // lists together: the second sweep's tiles then hold instances with similar block sets (two-level
   // search).  List slots are reserved per workgroup - one atomic per list and workgroup, the positions
@@ -799,7 +801,7 @@ static double split_roundings_for(int dim) {
 
 MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool hot) {
   MarginModel mm{2.0 * fp32_pass_roundings(c->dim) + 4.0, 0.0, nullptr, nullptr, 0, nullptr, nullptr, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr,
-                 nullptr, nullptr};
+                 nullptr, nullptr, 0};
   if (mode == kCertifyCsr) {
     mm.indptr = indptr;
     mm.row_q = c->row_q;
@@ -842,7 +844,13 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
       mm.sub_err = c->sub_err;
     }
   }
-  if (mode == kCertifySplit) {
+  if (mode == kCertifySubspaceCsr || mode == kCertifySubspaceCsrSelect) {
+    // the sparse rows are not centred: terms in |mu| as in the sweep; everything else is in the coordinates' own bounds
+    mm.sub = c->sub_state;
+    mm.sub_err = mode == kCertifySubspaceCsr ? c->sub_err2 : c->sub_err;
+    mm.sub_fine = mode == kCertifySubspaceCsr;
+  }
+  if (mode == kCertifySplit || mode == kCertifySubspaceFine) {
     // dot product: accumulation + 3 * 2^-22 of the split (= 12 u) ; both doubled by the factor -2;
     // + 4 for the stored c_i, the final multiply-add and the rounding of w - mu, + 2 for the rounding
     // of x - mu (its part that does not depend on the node cancels in every comparison).  Never
@@ -853,12 +861,17 @@ MarginModel margin_model(const som_ctx *c, int mode, const int64_t *indptr, bool
     mm.xscale = c->xscale;
     mm.wscale = c->wscale;
     mm.x_centered = 1;
+    if (mode == kCertifySubspaceFine) {
+      mm.sub = c->sub_state;
+      mm.sub_err = c->sub_err2;
+      mm.sub_fine = 1;
+    }
   }
   return mm;
 }
 
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus, bool hot,
-                          const int32_t *order) {
+                          const int32_t *order, const SubspaceState *state) {
   CandView cand{c->cand_val, c->cand_idx, c->cand_over};
   const MarginModel mm = margin_model(c, mode, indptr, hot);
   UnitWork work{0, 0, nullptr, nullptr, nullptr};
@@ -866,7 +879,7 @@ hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int
     work = UnitWork{c->csr_sweeps, c->unit_cap, c->unit_work, c->list_counts + kUnitCounts, c->collect_list};
   hipLaunchKernelGGL(k_certify, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, cand, groups, c->xn32,
                      c->wmax_bits, c->mu_norm2, mm, n, c->k, bmus, c->cand_n, c->refine_list, c->collect_rows,
-                     c->collect_thr, c->collect_cnt, c->list_counts, work, order);
+                     c->collect_thr, c->collect_cnt, c->list_counts, work, order, state, mode == kCertifySubspaceCsr);
   return hipGetLastError();
 }
 

@@ -24,28 +24,12 @@
 // Measured (MI355X, a whole epoch, without -> with): 100,000 x 1,000 on 50 x 50 nodes 860 -> 561 us (coarse pass 518 ->
 // 31, the six kernels 155), 50,000 x 256 on 200 x 200 1,541 -> 982 (1,163 -> 266 + 145), 1,000,000 x 128 on 100 x 100 4,000 ->
 // 2,009 (3,060 -> 708 + 165).
-#include "som_internal.hpp"
-
-#include <math.h>
+#include "subspace.hpp"
 
 namespace som {
 
-typedef _Float16 f16x8s __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4s __attribute__((ext_vector_type(4)));
-typedef float f32x16s __attribute__((ext_vector_type(16)));
-
 constexpr double kDropPivot = 1e-12;       // (relative norm)^2 below which a sketch row adds no direction
-constexpr float kVScale = 256.f;           // V is stored times this: |V_rc| <= 1, and fp16's subnormals stay out of the way
-
-__device__ __forceinline__ float pow2_over(float m, float *inverse) {      // power of two above m (1 for 0 and non-finite m)
-  int e = 0;
-  if (m > 0.f && m < INFINITY) {
-    (void)frexpf(m, &e);
-    e = e < -100 ? -100 : (e > 126 ? 126 : e);
-  }
-  *inverse = ldexpf(1.f, -e);
-  return ldexpf(1.f, e);
-}
+constexpr int kGramCols = 256;             // features per workgroup of the Gram matrix
 
 // ---------------------------------------------------------------- basis
 // A workgroup per (bucket, 64 features); eight node subgroups.  Bound by the read of the code book out of L2.
@@ -53,18 +37,15 @@ __global__ __launch_bounds__(512) void k_subspace_sketch(const float *__restrict
                                                          const float *__restrict__ mu, float *__restrict__ S) {
   __shared__ float s_part[8][64];
   const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
-  constexpr int kBuckets = kSub - 3;
   const int r = blockIdx.x, c = blockIdx.y * 64 + lane;
   const int first = r < kSubConst ? r : r < kSubConst + 3 ? k : r - 3;
   const bool in = c < dim;
   const float m = in ? mu[c] : 0.f;
   float acc = 0.f;
 #pragma unroll 4
-  for (int64_t i = first + (int64_t)kBuckets * sub; i < k; i += kBuckets * 8) {
-    unsigned h = (unsigned)i * 2654435761u;
-    h = (h ^ (h >> 16)) * 0x85ebca6bu;
+  for (int64_t i = first + (int64_t)kSketchBuckets * sub; i < k; i += kSketchBuckets * 8) {
     const float v = in ? W[i * dim + c] - m : 0.f;
-    acc += (h >> 31) ? v : -v;
+    acc += sketch_sign((int)i) ? v : -v;
   }
   s_part[sub][lane] = acc;
   __syncthreads();
@@ -75,37 +56,43 @@ __global__ __launch_bounds__(512) void k_subspace_sketch(const float *__restrict
   }
 }
 
-// G = S S^T, a workgroup per 8 x 8 outputs; sixteen threads per output, a sixteenth of the features each (four threads:
-// 12.8 us at 1,000 features).
-__global__ __launch_bounds__(1024) void k_subspace_gram(const float *__restrict__ S, int dimp, double *__restrict__ G) {
-  constexpr int kStep = 512, kParts = 16;
-  __shared__ float s_rows[16][kStep + 1];
-  __shared__ double s_sum[kParts][64];
-  const int tid = threadIdx.x, pair = tid & 63, part = tid >> 6;
-  const int bi = blockIdx.x >> 3, bj = blockIdx.x & 7;
-  if (bj > bi) return;                        // symmetric: the other half is written with this one
-  const int i = pair >> 3, j = pair & 7;
-  double s = 0.0;
-  for (int c0 = 0; c0 < dimp; c0 += kStep) {
-    __syncthreads();
-    const int c = c0 + (tid & (kStep - 1));
+// G = S S^T in fp64 on the matrix cores, kGramCols features per workgroup and a partial matrix for each such piece (their sum: k_gram_sum,
+// or the factor itself where there are few).  A wavefront owns the 16 rows 16 wave .. of G; lane l16 holds a row, its quad four features of every 16, and
+// instruction e takes feature 4 quad + e of both operands (vector code with the rows in LDS: 48 us at 50,000 features).
+__global__ __launch_bounds__(256) void k_subspace_gram(const float *__restrict__ S, int dimp, double *__restrict__ G) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int c_end = min(dimp, ((int)blockIdx.x + 1) * kGramCols);      // (a multiple of 64)
+  f64x4 acc[4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll 4
+  for (int c = blockIdx.x * kGramCols + 4 * quad; c < c_end; c += 16) {
+    f32x4 b[4];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int row = 2 * p + (tid >= kStep), r = (row < 8 ? 8 * bi : 8 * bj - 8) + row;
-      s_rows[row][tid & (kStep - 1)] = c < dimp ? S[(int64_t)r * dimp + c] : 0.f;
-    }
-    __syncthreads();
+    for (int t = 0; t < 4; ++t) b[t] = *reinterpret_cast<const f32x4 *>(S + (int64_t)(16 * t + l16) * dimp + c);
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(S + (int64_t)(16 * wave + l16) * dimp + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[e], (double)b[t][e], acc[t], 0, 0, 0);
+  }
+  G += (int64_t)blockIdx.x * kSub * kSub;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) G[(16 * wave + 4 * v + quad) * kSub + 16 * t + l16] = acc[t][v];
+}
+
+__global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ G, int pieces) {      // into the first piece
+  __shared__ double s_part[4][64];
+  const int o = blockIdx.x * 64 + (threadIdx.x & 63), part = threadIdx.x >> 6;
+  double s = 0.0;
 #pragma unroll 8
-    for (int c = part; c < kStep; c += kParts) s += (double)s_rows[i][c] * (double)s_rows[8 + j][c];
-  }
-  s_sum[part][pair] = s;
+  for (int p = part; p < pieces; p += 4) s += G[(int64_t)p * kSub * kSub + o];
+  s_part[part][threadIdx.x & 63] = s;
   __syncthreads();
-  if (part == 0) {
-    s = 0.0;
-    for (int p = 0; p < kParts; ++p) s += s_sum[p][pair];
-    G[(8 * bi + i) * kSub + 8 * bj + j] = s;
-    G[(8 * bj + j) * kSub + 8 * bi + i] = s;
-  }
+  if (part == 0) G[o] = (s_part[0][threadIdx.x] + s_part[1][threadIdx.x]) + (s_part[2][threadIdx.x] + s_part[3][threadIdx.x]);
 }
 
 // Linv^T of G = L L^T by elimination on [G | I], one workgroup, both matrices in registers (4 x 4 entries of each per
@@ -113,7 +100,8 @@ __global__ __launch_bounds__(1024) void k_subspace_gram(const float *__restrict_
 // floor (or NaN) gives no direction: its row of L^-1 is zero.  Bound by 64 dependent steps: the reciprocal is a Newton
 // iteration (any basis will do that is nearly orthonormal), the square roots are left for the end, and blocks of 16 rows
 // and columns that are done or still zero are left out (31 us with none of this).
-__global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, double *__restrict__ LinvT) {
+__global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, int pieces, double *__restrict__ LinvT,
+                                                         SubspaceState *__restrict__ state) {
   __shared__ double s_col[2][kSub], s_row[2][kSub], s_linv[kSub][kSub + 1], s_pivot[kSub];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   double m[4][4], w[4][4];
@@ -121,12 +109,20 @@ __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restric
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      m[a][b] = G[(ty + 16 * a) * kSub + tx + 16 * b];
+      m[a][b] = 0.0;
+#pragma unroll 4
+      for (int p = 0; p < pieces; ++p) m[a][b] += G[(int64_t)p * kSub * kSub + (ty + 16 * a) * kSub + tx + 16 * b];
       w[a][b] = ty + 16 * a == tx + 16 * b ? 1.0 : 0.0;
     }
-  double top = G[(tid & 63) * (kSub + 1)];      // the largest pivot
+  if (tx == ty) {                                // the diagonal
+#pragma unroll
+    for (int a = 0; a < 4; ++a) s_pivot[ty + 16 * a] = m[a][a];
+  }
+  __syncthreads();
+  double top = s_pivot[tid & 63];               // the largest pivot
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+  __syncthreads();
   const double floor_p = top * kDropPivot;
 #pragma unroll
   for (int tb = 0; tb < 4; ++tb) {
@@ -170,6 +166,12 @@ __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restric
     }
   }
   __syncthreads();
+  if (tid == 0) {                 // the last directions still of the code book's own size: no use going on
+    double least = top;
+    for (int t = kSub - 8; t < kSub; ++t) least = fmin(least, s_pivot[t]);
+    state->use = state->fine = 0;
+    state->full = !(least <= top * (16.0 * kSubspaceLoss * kSubspaceLoss));
+  }
   if (tid < kSub) s_pivot[tid] = s_pivot[tid] > 0.0 ? 1.0 / sqrt(s_pivot[tid]) : 0.0;
   __syncthreads();
   const double norm = s_pivot[tid & 63];
@@ -179,7 +181,10 @@ __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restric
 // V = L^-1 S times kVScale, as hi/lo halves: Vp [chunk of 64 features][plane][64 r][64 features] and
 // Vt [feature][plane][64 r].  A workgroup per 64 features, eight rows of V per wavefront.
 __global__ __launch_bounds__(512) void k_subspace_vectors(const float *__restrict__ S, int dimp, const double *__restrict__ LinvT,
-                                                          _Float16 *__restrict__ Vp, _Float16 *__restrict__ Vt) {
+                                                          const SubspaceState *__restrict__ state,
+                                                          _Float16 *__restrict__ Vp, _Float16 *__restrict__ Vt,
+                                                          float *__restrict__ Vf) {
+  if (state->full) return;
   const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = blockIdx.x * 64 + lane;
   double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -199,6 +204,10 @@ __global__ __launch_bounds__(512) void k_subspace_vectors(const float *__restric
     at[0] = hi[e];
     at[kSub * 64] = lo[e];
   }
+  if (Vf) {                                     // sparse rows gather the vectors feature by feature
+#pragma unroll
+    for (int e = 0; e < 8; ++e) Vf[(int64_t)c * kSub + 8 * g + e] = ((float)hi[e] + (float)lo[e]) * (1.f / kVScale);
+  }
   *reinterpret_cast<f16x8s *>(Vt + (int64_t)c * 2 * kSub + 8 * g) = hi;
   *reinterpret_cast<f16x8s *>(Vt + (int64_t)c * 2 * kSub + kSub + 8 * g) = lo;
 }
@@ -206,34 +215,37 @@ __global__ __launch_bounds__(512) void k_subspace_vectors(const float *__restric
 // ---------------------------------------------------------------- the nodes
 // 32 nodes per workgroup and step, the chunks of 32 features dealt to its eight wavefronts, twice: u = V w' (summed over
 // the wavefronts through LDS), then w' - V^T u, whose squares are added up.  In both products a lane holds one node.  The
-// residual is formed by the matrix cores alone: w' enters through products with 2^(8-q) times the identity.
-// Units: planes hold w'/s (s = *wscale), V times 256, u/(s 2^q) with 2^q > sqrt(dim), so that |u| <= |w'| fits.
-// Roundings of the residual: the dropped lo.lo products (2^-22 |u_r V_rc|), a chain of 16 matrix instructions
-// (2.5 * 16 + 11 roundings of 2^-24 of the terms' magnitudes), the planes' own 2^-22 |w'| and 2^-25 s per element.  Per wavefront and
-// 32 features 12 + 16 matrix instructions on 12 KB from L2: latency of those loads bounds it on small maps.
+// residual is formed by the matrix cores alone: w' enters through products with 256 s over that power times the identity.
+// Units: planes hold w'/s (s = *wscale), V times 256, u divided by a power of two above the largest |w'|.
+// Roundings of the residual: w' is put together exactly; then a matrix instruction rounds by 2.5 u of the accumulator it finds and of its
+// products' magnitudes at most, and by 9 u of its largest product (the model of the filter passes; those of the four groups of 16 add up to 2 |u| |V_r| at most); accumulators are no longer
+// than what so many coordinates leave, which is measured after every 16 (plus products with a lo half, 2^-10 of |u|_1), and the
+// magnitudes add up to |u|_1 |V_r|.  The dropped lo.lo products are below 2^-23 |u|_1 |V_r|, the planes' own residual below 2^-22 |w'| and
+// 2^-25 s per element.  With all magnitudes priced in every instruction instead the bound was seven times as large, and the
+// fine pass could not have used the coordinates.  Per wavefront and 32 features 12 + 16 matrix instructions on 12 KB from
+// L2: the latency of those loads bounds it on small maps.
 __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restrict__ Wh, int k, int dim, int nK,
                                                          const _Float16 *__restrict__ Vp, const _Float16 *__restrict__ Vt,
                                                          const float *__restrict__ wscale, const unsigned *__restrict__ wmax_bits,
-                                                         int q, const float *__restrict__ cn, _Float16 *__restrict__ U1, float *__restrict__ part,
+                                                         const float *__restrict__ cn, _Float16 *__restrict__ U1, _Float16 *__restrict__ U2,
+                                                         int may_fine, float *__restrict__ part,
                                                          int32_t *__restrict__ ticket, SubspaceState *__restrict__ state) {
   __shared__ float s_u[4][kSub][33];
   __shared__ __attribute__((aligned(16))) _Float16 s_un[2][32][kSub + 8];     // -u as hi/lo planes
-  __shared__ float s_sum[3][8][32], s_e[2][8][32], s_v[8][2][64];
-  __shared__ float s_fin[8][5];
-  __shared__ int s_last;
+  __shared__ float s_sum[3][8][32], s_e[4][8][32], s_v[8][2][64];
+  if (state->full) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
   const float sw = *wscale;
   const float wm = sqrtf(__uint_as_float(*wmax_bits)) * (1.f + 1e-6f);
-  const float unit = ldexpf(sw, q);                 // of the u planes
-  float cinv;                                       // the constants stay below 2^10
-  const float cscale = pow2_over(__uint_as_float(*wmax_bits), &cinv) * 0x1p-10f;
-  cinv *= 0x1p10f;
+  float uinv, cinv;
+  const float unit = pow2_over(wm * (1.f + 1e-3f), &uinv);        // of the u planes
+  const float cscale = constant_scale(__uint_as_float(*wmax_bits), &cinv);
   f16x8s ident[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ident[ks][e] = (_Float16)(l32 == 16 * ks + 8 * lhi + e ? ldexpf(1.f, 8 - q) : 0.f);
+    for (int e = 0; e < 8; ++e) ident[ks][e] = (_Float16)(l32 == 16 * ks + 8 * lhi + e ? kVScale * (sw * uinv) : 0.f);
   const f32x16s zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float top_e = 0.f, top_e32 = 0.f, top_u = 0.f, top_u1 = 0.f, top_lost = 0.f, vn = 0.f;
   const int tiles = (k + 31) / 32;
@@ -316,21 +328,21 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
     if (tid < 256) {
       const int nd = tid & 31, g = tid >> 5;         // eight coordinates of one node
       float su = 0.f, s1 = 0.f, sl = 0.f;
-      f16x8s hi, nhi, nlo;
+      f16x8s hi, lo, nhi, nlo;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int r = 8 * g + e;
         float un = 0.f;
 #pragma unroll
         for (int p = 0; p < 4; ++p) un += s_u[p][r][nd];
-        un *= ldexpf(1.f / kVScale, -q);
+        un *= sw * uinv * (1.f / kVScale);
         hi[e] = (_Float16)un;
-        const _Float16 l = (_Float16)(un - (float)hi[e]);
+        lo[e] = (_Float16)(un - (float)hi[e]);
         nhi[e] = -hi[e];
-        nlo[e] = -l;
+        nlo[e] = -lo[e];
         su += un * un;
         s1 += fabsf(un);
-        sl += (float)l * (float)l;
+        sl += (float)lo[e] * (float)lo[e];
       }
       *reinterpret_cast<f16x8s *>(&s_un[0][nd][8 * g]) = nhi;
       *reinterpret_cast<f16x8s *>(&s_un[1][nd][8 * g]) = nlo;
@@ -338,11 +350,10 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
       s_sum[1][g][nd] = s1;
       s_sum[2][g][nd] = sl;
       if (tile * 32 + nd < k) {
-        if (g == kSubConst / 8) {                    // c_i as the sum of three halves, to 2^-35 of the largest
-          float c = cn[tile * 32 + nd] * cinv;
-#pragma unroll
-          for (int e = kSubConst % 8; e < kSubConst % 8 + 3; ++e) { hi[e] = (_Float16)c; c -= (float)hi[e]; }
-        }
+        _Float16 *u2 = U2 + (int64_t)(tile * 32 + nd) * 2 * kSub + (g >> 2) * 64 + (g & 3) * 8;
+        *reinterpret_cast<f16x8s *>(u2) = hi;
+        *reinterpret_cast<f16x8s *>(u2 + 32) = lo;
+        if (g == kSubConst / 8) put_constant(hi, cn[tile * 32 + nd] * cinv);
         *reinterpret_cast<f16x8s *>(U1 + (int64_t)(tile * 32 + nd) * kSub + 8 * g) = hi;
       }
     }
@@ -366,7 +377,7 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
       uh[ks] = *reinterpret_cast<const f16x8s *>(&s_un[0][l32][16 * ks + 8 * lhi]);
       ul[ks] = *reinterpret_cast<const f16x8s *>(&s_un[1][l32][16 * ks + 8 * lhi]);
     }
-    float esq = 0.f, esq32 = 0.f;
+    float esq[4] = {0.f, 0.f, 0.f, 0.f};
     for (int t = wave; t < nK; t += 8) {
       f32x16s d = zero;
       f16x8s vc[4][2];
@@ -384,32 +395,35 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
         d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, uh[ks], d, 0, 0, 0);
         d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl, uh[ks], d, 0, 0, 0);
         d = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh, ul[ks], d, 0, 0, 0);
-        if (ks == 1) {                               // what the first 32 coordinates leave
 #pragma unroll
-          for (int v2 = 0; v2 < 16; ++v2) esq32 += d[v2] * d[v2];
-        }
+        for (int v2 = 0; v2 < 16; ++v2) esq[ks] += d[v2] * d[v2];      // what 16, 32, 48, 64 coordinates leave
       }
-#pragma unroll
-      for (int v2 = 0; v2 < 16; ++v2) esq += d[v2] * d[v2];
     }
-    esq += __shfl_xor(esq, 32, 64);
-    esq32 += __shfl_xor(esq32, 32, 64);
-    if (lhi == 0) { s_e[0][wave][l32] = esq; s_e[1][wave][l32] = esq32; }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      esq[ks] += __shfl_xor(esq[ks], 32, 64);
+      if (lhi == 0) s_e[ks][wave][l32] = esq[ks];
+    }
     __syncthreads();
     if (tid < 32) {
       float su = 0.f, s1 = 0.f, sl = 0.f;
 #pragma unroll
       for (int g = 0; g < 8; ++g) { su += s_sum[0][g][tid]; s1 += s_sum[1][g][tid]; sl += s_sum[2][g][tid]; }
-      float e2 = 0.f, e32 = 0.f;
+      float left[4];                                 // norms
 #pragma unroll
-      for (int p = 0; p < 8; ++p) { e2 += s_e[0][p][tid]; e32 += s_e[1][p][tid]; }
+      for (int ks = 0; ks < 4; ++ks) {
+        left[ks] = 0.f;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) left[ks] += s_e[ks][p][tid];
+        left[ks] = norm_above(left[ks], unit * (1.f / kVScale));
+      }
       const float u1 = s1 * unit * (1.f + 1e-4f);
-      const float slack = 55.f * 0x1p-24f * (wm + vn * u1) + 0x1p-22f * wm + sqrtf((float)dim) * 0x1p-25f * sw;
-      e2 = (sqrtf(e2) * (1.f + 4e-4f) + 1e-15f) * ldexpf(sw, q - 8) + slack;
-      e32 = (sqrtf(e32) * (1.f + 4e-4f) + 1e-15f) * ldexpf(sw, q - 8) + slack;
+      const float un = sqrtf(su) * (1.f + 1e-4f) * unit;
+      const float slack = residual_slack(left, wm, un, u1, vn, sw, dim);
+      const float e2 = left[3] + slack, e32 = left[1] + slack;
       top_e = e2 < INFINITY ? fmaxf(top_e, e2) : INFINITY;     // NaN counts as infinite
       top_e32 = e32 < INFINITY ? fmaxf(top_e32, e32) : INFINITY;
-      top_u = fmaxf(top_u, sqrtf(su) * (1.f + 1e-4f) * unit);
+      top_u = fmaxf(top_u, un);
       top_u1 = fmaxf(top_u1, u1);
       top_lost = fmaxf(top_lost, (sqrtf(sl) * (1.f + 1e-4f) + 1e-15f) * unit);
     }
@@ -422,40 +436,19 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
     top_u1 = fmaxf(top_u1, __shfl_xor(top_u1, o, 64));
     top_lost = fmaxf(top_lost, __shfl_xor(top_lost, o, 64));
   }
-  // the last workgroup to get here puts the maxima together and decides
-  if (tid == 0) {
-    float *p = part + 5 * blockIdx.x;
-    __hip_atomic_store(p + 0, top_e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, top_u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 2, top_u1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 3, top_lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 4, top_e32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-  }
-  __syncthreads();
-  if (!s_last) return;
-  float f[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int b = tid; b < (int)gridDim.x; b += 512)
-#pragma unroll
-    for (int e = 0; e < 5; ++e) f[e] = fmaxf(f[e], __hip_atomic_load(part + 5 * b + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-#pragma unroll
-  for (int e = 0; e < 5; ++e) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) f[e] = fmaxf(f[e], __shfl_xor(f[e], o, 64));
-    if (lane == 0) s_fin[wave][e] = f[e];
-  }
-  __syncthreads();
-  if (tid == 0) {
-#pragma unroll
-    for (int e = 0; e < 5; ++e)
-      for (int p = 0; p < 8; ++p) f[e] = fmaxf(f[e], s_fin[p][e]);
+  float f[5] = {top_e, top_u, top_u1, top_lost, top_e32};
+  if (last_maxima<512>(f, part, ticket) && tid == 0) {
     const int use = !(f[1] < INFINITY) ? 0 : f[4] <= kSubspaceLoss32 * wm ? 1 : f[0] <= kSubspaceLoss * wm ? 2 : 0;
     state->use = use;
+    state->fine = may_fine && use && f[0] <= kSubspaceLossFine * wm;
     state->e = use == 1 ? f[4] : f[0];
+    state->e32 = f[4];
+    state->e64 = f[0];
     state->u = f[1];
     state->u1 = f[2] * vn;
     state->ulost = f[3];
     state->wm = wm;
+    state->cmax = __uint_as_float(*wmax_bits);
     state->uscale = unit;
     state->cscale = cscale;
   }
@@ -466,22 +459,25 @@ __global__ __launch_bounds__(512) void k_subspace_coords(const _Float16 *__restr
 // the coarse pass), the instances' halves straight from memory into the operand registers, one chunk ahead.  Bound by
 // the read of the hi planes (2 bytes per element).
 // A lane holds one instance; err[j] bounds |x'.w'_i - (the coarse pass's y.u_i)| for every node i.
-template <int kRB>
-__device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, int64_t n, int nK,
-                                                          const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
-                                                          const float *__restrict__ xn32, const float *__restrict__ xlost,
-                                                          const SubspaceState *__restrict__ state, _Float16 *__restrict__ Y1,
-                                                          float *__restrict__ yscale, float *__restrict__ err,
-                                                          _Float16 (&s_v)[2][2 * kSub * 64]) {
+template <int kRB, bool kFine>
+__device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xp, int64_t n, int dim, const _Float16 *__restrict__ Vp,
+                                             const float *__restrict__ xscale, const float *__restrict__ xn32,
+                                             const float *__restrict__ xlost, const SubspaceState *__restrict__ state,
+                                             _Float16 *__restrict__ Y1, _Float16 *__restrict__ Y2, float *__restrict__ yscale,
+                                             float *__restrict__ err, float *__restrict__ err2, _Float16 (&s_v)[2][2 * kSub * 64],
+                                             const int64_t tile) {
+  constexpr int kXPlanes = kFine ? 2 : 1, kIB = kFine ? 1 : 2;      // blocks of 32 instances per wavefront
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
-  const int64_t inst0 = (int64_t)blockIdx.x * 256 + wave * 64;
-  const _Float16 *x[2];
+  const int nK = (dim + 63) / 64, nK32 = (dim + 31) / 32;
+  const int64_t inst0 = (tile * 4 + wave) * (32 * kIB);
+  if (tile * (128 * kIB) >= n) return;     // uniform over the workgroup
+  const _Float16 *x[kIB];
 #pragma unroll
-  for (int ib = 0; ib < 2; ++ib) {
+  for (int ib = 0; ib < kIB; ++ib) {
     int64_t j = inst0 + ib * 32 + l32;
     if (j > n - 1) j = n - 1;
-    x[ib] = Xh1 + j * (int64_t)nK * 64 + 8 * lhi;
+    x[ib] = Xp + j * (int64_t)(kFine ? nK32 : nK) * 64 + 8 * lhi;
   }
   // loader: the chunk's 128 rows (64 hi, 64 lo) of 128 bytes, four 16-byte slots per thread
   int st_off[4];
@@ -491,31 +487,48 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, i
     st_off[i] = row * 64 + 8 * (pos ^ ((row & 7) ^ ((row >> 3) & 1)));
   }
   const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
-  f32x16s acc[kRB][2];
+  const f32x16s zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16s acc[kRB][kIB], tot[kFine ? kRB : 1][kIB];
 #pragma unroll
   for (int rb = 0; rb < kRB; ++rb)
 #pragma unroll
-    for (int ib = 0; ib < 2; ++ib) acc[rb][ib] = f32x16s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  f16x8s v[4], xr[2][4];
+    for (int ib = 0; ib < kIB; ++ib) {
+      acc[rb][ib] = zero;
+      if (kFine) tot[rb][ib] = zero;
+    }
+  f16x8s v[4], xr[kIB][4][kXPlanes];
   auto load = [&](int t) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const f16x8s *>(Vp + (int64_t)t * 2 * kSub * 64 + 8 * (i * 256 + tid));
 #pragma unroll
-    for (int ib = 0; ib < 2; ++ib)
+    for (int ib = 0; ib < kIB; ++ib)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) xr[ib][ks] = *reinterpret_cast<const f16x8s *>(x[ib] + t * 64 + 16 * ks);
+      for (int ks = 0; ks < 4; ++ks) {
+        if (kFine) {           // chunks of 32: [32 hi | 32 lo]; the second one of the last 64 may not be there (V is zero there)
+          const _Float16 *at = x[ib] + min(2 * t + (ks >> 1), nK32 - 1) * 64 + (ks & 1) * 16;
+          xr[ib][ks][0] = *reinterpret_cast<const f16x8s *>(at);
+          xr[ib][ks][kXPlanes - 1] = *reinterpret_cast<const f16x8s *>(at + 32);
+        } else {
+          xr[ib][ks][0] = *reinterpret_cast<const f16x8s *>(x[ib] + t * 64 + 16 * ks);
+        }
+      }
   };
-  load(0);
+  // every workgroup starts at another chunk: rows are a power of two apart where dim is one or is padded to one, and workgroups
+  // that all read the same columns would queue at the same few memory channels
+  const int turn = (int)(tile % nK);
+  load(turn);
   for (int t = 0; t < nK; ++t) {
     _Float16 *sv = s_v[t & 1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<f16x8s *>(sv + st_off[i]) = v[i];
-    f16x8s xc[2][4];
+    f16x8s xc[kIB][4][kXPlanes];
 #pragma unroll
-    for (int ib = 0; ib < 2; ++ib)
+    for (int ib = 0; ib < kIB; ++ib)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) xc[ib][ks] = xr[ib][ks];
-    if (t + 1 < nK) load(t + 1);
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int pl = 0; pl < kXPlanes; ++pl) xc[ib][ks][pl] = xr[ib][ks][pl];
+    if (t + 1 < nK) load(t + 1 + turn < nK ? t + 1 + turn : t + 1 + turn - nK);
     __syncthreads();           // one barrier per chunk: the other stage's readers passed the previous one
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
@@ -526,15 +539,33 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, i
           const int row = pl * kSub + rb * 32 + l32;
           const f16x8s a = *reinterpret_cast<const f16x8s *>(sv + row * 64 + 8 * ((2 * ks + lhi) ^ swz));
 #pragma unroll
-          for (int ib = 0; ib < 2; ++ib) acc[rb][ib] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xc[ib][ks], acc[rb][ib], 0, 0, 0);
+          for (int ib = 0; ib < kIB; ++ib) {
+            acc[rb][ib] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xc[ib][ks][0], acc[rb][ib], 0, 0, 0);
+            if (kFine && pl == 0) acc[rb][ib] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, xc[ib][ks][kXPlanes - 1], acc[rb][ib], 0, 0, 0);
+          }
         }
-  }
-  const float wm = state->wm, e = state->e, um = state->u, u1 = state->u1, ulost = state->ulost;
-  const float uscale = state->uscale, cscale = state->cscale;
-  const float chain = 2.5f * (float)(8 * nK) + 11.f;            // roundings of a chain of 8 nK matrix instructions
+    if (kFine) {               // short chains: their roundings are most of the fine pass's margin
 #pragma unroll
-  for (int ib = 0; ib < 2; ++ib) {
+      for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+        for (int ib = 0; ib < kIB; ++ib) {
+          tot[rb][ib] += acc[rb][ib];
+          acc[rb][ib] = zero;
+        }
+    }
+  }
+  const float wm = state->wm, um = state->u, u1 = state->u1, ulost = state->ulost;
+  const float uscale = state->uscale, cscale = state->cscale;
+  const bool first32 = state->use == 1;
+  // roundings of a coordinate: a chain of 8 nK matrix instructions, or (fine) chains of 12, their sum, and the dropped lo.lo products
+  const float chain = kFine ? 2.5f * 12.f + 11.f + (float)nK + 4.f : 2.5f * (float)(8 * nK) + 11.f;
+#pragma unroll
+  for (int ib = 0; ib < kIB; ++ib) {
     const int64_t j = inst0 + ib * 32 + l32;
+    if (kFine) {
+#pragma unroll
+      for (int rb = 0; rb < kRB; ++rb) acc[rb][ib] = tot[rb][ib];
+    }
     float top = 0.f;
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb)
@@ -544,24 +575,26 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, i
     float inv;
     float s = pow2_over(top, &inv);
     const float xs = (j < n ? xscale[j] : 1.f) * (1.f / kVScale);
-    // the factor of the node constants, a power of two that a half holds exactly: the scale is raised where it would be
-    // too large, the bound made infinite where it would be too small (such an instance keeps every block)
-    const float over = cscale / (2.f * s * xs * uscale) * 0x1p-15f;
-    if (over > 1.f) { s *= over; inv /= over; }
-    const float cfac = -cscale / (2.f * s * xs * uscale);
+    const float cfac = constant_factor(s, inv, xs, uscale, cscale);      // (an instance it does not fit keeps every block)
     float ysq = 0.f, lost = 0.f;
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        f16x4s h;
+        f16x4s h, l;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float y = acc[rb][ib][4 * g + i] * inv;
           h[i] = (_Float16)y;
           const float d = y - (float)h[i];
+          l[i] = (_Float16)d;
           ysq += y * y;
           lost += d * d;
+        }
+        if (kFine && j < n) {
+          _Float16 *at = Y2 + j * 2 * kSub + rb * 64 + 8 * g + 4 * lhi;
+          *reinterpret_cast<f16x4s *>(at) = h;
+          *reinterpret_cast<f16x4s *>(at + 32) = l;
         }
         if (rb == 0) {                       // coordinates kSubConst .. kSubConst + 2
 #pragma unroll
@@ -570,7 +603,7 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, i
             if (r >= kSubConst && r < kSubConst + 3) h[i] = (_Float16)cfac;
           }
         }
-        if (j < n) *reinterpret_cast<f16x4s *>(Y1 + j * (32 * kRB) + rb * 32 + 8 * g + 4 * lhi) = h;
+        if (j < n && (rb == 0 || !first32)) *reinterpret_cast<f16x4s *>(Y1 + j * (first32 ? 32 : 64) + rb * 32 + 8 * g + 4 * lhi) = h;
       }
     ysq += __shfl_xor(ysq, 32, 64);
     lost += __shfl_xor(lost, 32, 64);
@@ -579,23 +612,29 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xh1, i
       const float lx = xlost[j], xn = sqrtf(xn32[j]) * (1.f + 1e-6f) + lx;
       const float yn = (sqrtf(ysq) * (1.f + 1e-4f) + 1e-15f) * unit, yl = (sqrtf(lost) * (1.f + 4e-4f) + 1e-15f) * unit;
       yscale[j] = unit;
-      // (x' - hi).w' + hi.e_i + (roundings of y).u + (y - hi(y)).u + hi(y).(u - hi(u)) + the coarse pass's chain of up to
-      // four instructions, over the products and over half of c_i
-      const float b = lx * wm + xn * e + chain * 0x1p-24f * xn * u1 + yl * um + (yn + yl) * (ulost + 21.f * 0x1p-24f * um) +
-                      12.f * 0x1p-24f * wm * wm;
-      err[j] = -cfac >= 0x1p-24f && -cfac <= 0x1p15f ? b * (1.f + 1e-3f) : INFINITY;
+      // what the planes that were multiplied leave of x', times w', and the roundings of y, times u
+      const float left = kFine ? 0x1p-22f * xn + sqrtf((float)dim) * 0x1p-25f * xscale[j] : lx;
+      const float b = left * wm + chain * 0x1p-24f * xn * u1;
+      // coarse: hi.e_i + (y - hi(y)).u + hi(y).(u - hi(u)) + the coarse pass's chain of up to four instructions, over the
+      // products and over half of c_i
+      const float b1 = b + xn * state->e + yl * um + (yn + yl) * (ulost + 21.f * 0x1p-24f * um) + 12.f * 0x1p-24f * state->cmax;
+      err[j] = factor_fits(cfac) ? b1 * (1.f + 1e-3f) : INFINITY;
+      // fine: the residual, what hi + lo leave of y, a chain of 12 instructions, its flush and the dropped products
+      if (kFine) err2[j] = (b + xn * state->e64 + (0x1p-22f * yn + 8.f * 0x1p-25f * unit) * um + (42.f + 12.f) * 0x1p-24f * yn * um) * (1.f + 1e-3f);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__restrict__ Xh1, int64_t n, int nK,
-                                                          const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
+__global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__restrict__ Xh1, const _Float16 *__restrict__ Xh, int64_t n,
+                                                          int dim, const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
                                                           const float *__restrict__ xn32, const float *__restrict__ xlost,
                                                           const SubspaceState *__restrict__ state, _Float16 *__restrict__ Y1,
-                                                          float *__restrict__ yscale, float *__restrict__ err) {
+                                                          _Float16 *__restrict__ Y2, float *__restrict__ yscale,
+                                                          float *__restrict__ err, float *__restrict__ err2) {
   __shared__ __attribute__((aligned(16))) _Float16 s_v[2][2 * kSub * 64];
-  if (state->use == 1) project_rows<1>(Xh1, n, nK, Vp, xscale, xn32, xlost, state, Y1, yscale, err, s_v);
-  else if (state->use == 2) project_rows<2>(Xh1, n, nK, Vp, xscale, xn32, xlost, state, Y1, yscale, err, s_v);
+  if (state->fine) project_rows<2, true>(Xh, n, dim, Vp, xscale, xn32, xlost, state, Y1, Y2, yscale, err, err2, s_v, (int64_t)blockIdx.x);
+  else if (state->use == 1) project_rows<1, false>(Xh1, n, dim, Vp, xscale, xn32, xlost, state, Y1, Y2, yscale, err, err2, s_v, (int64_t)blockIdx.x);
+  else if (state->use == 2) project_rows<2, false>(Xh1, n, dim, Vp, xscale, xn32, xlost, state, Y1, Y2, yscale, err, err2, s_v, (int64_t)blockIdx.x);
 }
 
 // ---------------------------------------------------------------- host side
@@ -608,29 +647,45 @@ bool subspace_eligible(const som_ctx *c, int64_t n) {
   return c->filter == SOM_FILTER_TWO_LEVEL || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceMinWork;
 }
 
-// Is the code book that enters an epoch of this radius likely to lie in 64 directions?  It was left by an epoch of about
-// that radius or more, and the number of directions grows with the number of radii the map is long and wide.
-bool subspace_likely(const som_ctx *c, double radius) {
+// Is the code book likely to lie in 64 directions?  One that enters an epoch was left by an epoch of about its radius
+// or more, and the number of directions grows with the number of radii the map is long and wide.  A search
+// outside an epoch (radius 0) may bring any: it is tried where the work it may save is several times what a
+// failure costs (40 us, most of it the factor, which finds out).
+bool subspace_likely(const som_ctx *c, int64_t n, double radius) {
   if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
+  if (radius <= 0.0)
+    return c->filter == SOM_FILTER_TWO_LEVEL || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceAloneWork;
   return (double)c->rows * (double)c->cols <= kSubspaceMaxArea * radius * radius;
 }
 
 size_t subspace_vector_halves(const som_ctx *c) { return (size_t)((c->dim + 63) / 64) * 64 * 2 * kSub; }
 
+int subspace_gram_pieces(const som_ctx *c) { return ((c->dim + 63) / 64 * 64 + kGramCols - 1) / kGramCols; }
+
+hipError_t launch_subspace_basis(som_ctx *c, const float *W) {
+  const int nK = (c->dim + 63) / 64, dimp = nK * 64, pieces = subspace_gram_pieces(c);
+  double *linv = c->sub_G + (size_t)pieces * kSub * kSub;
+  if (W) hipLaunchKernelGGL(k_subspace_sketch, dim3(kSub, nK), dim3(512), 0, c->stream, W, c->k, c->dim, dimp, c->mu, c->sub_S);
+  hipLaunchKernelGGL(k_subspace_gram, dim3(pieces), dim3(256), 0, c->stream, c->sub_S, dimp, c->sub_G);
+  if (pieces > 8) hipLaunchKernelGGL(k_gram_sum, dim3(kSub), dim3(256), 0, c->stream, c->sub_G, pieces);
+  hipLaunchKernelGGL(k_subspace_factor, dim3(1), dim3(256), 0, c->stream, c->sub_G, pieces > 8 ? 1 : pieces, linv, c->sub_state);
+  hipLaunchKernelGGL(k_subspace_vectors, dim3(nK), dim3(512), 0, c->stream, c->sub_S, dimp, linv, c->sub_state, c->sub_Vp, c->sub_Vt,
+                     c->sub_Vf);
+  return hipGetLastError();
+}
+
 hipError_t launch_subspace(som_ctx *c, const float *W, int64_t n) {
-  const int nK = (c->dim + 63) / 64, dimp = nK * 64;
-  hipLaunchKernelGGL(k_subspace_sketch, dim3(kSub, nK), dim3(512), 0, c->stream, W, c->k, c->dim, dimp, c->mu, c->sub_S);
-  hipLaunchKernelGGL(k_subspace_gram, dim3(64), dim3(1024), 0, c->stream, c->sub_S, dimp, c->sub_G);
-  hipLaunchKernelGGL(k_subspace_factor, dim3(1), dim3(256), 0, c->stream, c->sub_G, c->sub_G + kSub * kSub);
-  hipLaunchKernelGGL(k_subspace_vectors, dim3(nK), dim3(512), 0, c->stream, c->sub_S, dimp, c->sub_G + kSub * kSub, c->sub_Vp, c->sub_Vt);
-  int q = 0;
-  while ((1 << q) * (1 << q) < c->dim + c->dim / 8) ++q;
+  const hipError_t e = launch_subspace_basis(c, W);
+  if (e != hipSuccess) return e;
   int blocks = (c->k + 31) / 32;
   if (blocks > kSubspaceParts) blocks = kSubspaceParts;
   hipLaunchKernelGGL(k_subspace_coords, dim3(blocks), dim3(512), 0, c->stream, c->Wh, c->k, c->dim, (c->dim + 31) / 32, c->sub_Vp,
-                     c->sub_Vt, c->wscale, c->wmax_bits, q, c->wn32, c->sub_U1, c->sub_part, c->list_counts + kSubTicketWord, c->sub_state);
-  hipLaunchKernelGGL(k_subspace_project, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->Xh1, n, nK, c->sub_Vp,
-                     c->xscale, c->xn32, c->xlost, c->sub_state, c->sub_Y1, c->sub_yscale, c->sub_err);
+                     c->sub_Vt, c->wscale, c->wmax_bits, c->wn32, c->sub_U1, c->sub_U2,
+                     c->sub_Y2 != nullptr, c->sub_part, c->list_counts + kSubTicketWord, c->sub_state);
+  const int64_t per = c->sub_Y2 ? 128 : 256;      // instances per workgroup (without the fine pass's planes half of 128 leave at once)
+  hipLaunchKernelGGL(k_subspace_project, dim3((unsigned)((n + per - 1) / per)), dim3(256), 0, c->stream, c->Xh1, c->Xh, n, c->dim,
+                     c->sub_Vp, c->xscale, c->xn32, c->xlost, c->sub_state, c->sub_Y1, c->sub_Y2, c->sub_yscale, c->sub_err,
+                     c->sub_err2);
   return hipGetLastError();
 }
 

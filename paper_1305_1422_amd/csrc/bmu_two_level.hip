@@ -45,7 +45,7 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
                                                               const float *__restrict__ xn32,
                                                               const unsigned *__restrict__ wmax_bits,
                                                               const float *__restrict__ mu_norm2, MarginModel mm,
-                                                              int classes, int spans, int32_t *__restrict__ key,
+                                                              int classes, int spans, int only, int32_t *__restrict__ key,
                                                               uint32_t *__restrict__ mask) {
   constexpr int kHold = 32;
   constexpr int kWordsAtOnce = 8;               // mask words combined per round: 256 blocks
@@ -54,6 +54,13 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
   const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
   const int64_t j = (int64_t)blockIdx.x * 64 + lane;
   const bool live = j < n;
+  if (only && !mm.sub->use) {                   // no scores: no blocks (the passes behind this one find nothing to do)
+    if (part == 0 && live) {
+      for (int w = 0; 32 * w < blocks; ++w) mask[(int64_t)w * n + j] = 0;
+      key[j] = 0;
+    }
+    return;
+  }
   float held[kHold];
   float best = INFINITY;
 #pragma unroll
@@ -178,18 +185,19 @@ __global__ __launch_bounds__(256) void k_tile_lists(const uint32_t *__restrict__
   if (lane == 0) tile_cnt[tile] = count;
 }
 
-hipError_t launch_select_blocks(som_ctx *c, int64_t n, bool sub) {
+hipError_t launch_select_blocks(som_ctx *c, int64_t n, SubspaceUse sub) {
   const int blocks = (c->k + 127) / 128, classes = size_classes(blocks);
+  const int mode = sub == kSubOnly ? kCertifySubspaceCsrSelect : sub == kSubMay ? kCertifySubspace : kCertifySelect;
   // as many steps of the span as keep the keys below k: the grouping by key has room for that many
   const int spans = c->k / (classes * blocks) > blocks ? blocks : c->k / (classes * blocks) > 1 ? c->k / (classes * blocks) : 1;
   if (blocks <= 128)      // 32 blocks held per thread: all of them
     hipLaunchKernelGGL(k_select_blocks<4>, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, sub ? kCertifySubspace : kCertifySelect, nullptr),
-                       classes, spans, c->coarse_key, c->coarse_mask);
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, mode, nullptr),
+                       classes, spans, sub == kSubOnly, c->coarse_key, c->coarse_mask);
   else
     hipLaunchKernelGGL(k_select_blocks<8>, dim3((unsigned)((n + 63) / 64)), dim3(512), 0, c->stream, c->coarse_min, n,
-                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, sub ? kCertifySubspace : kCertifySelect, nullptr),
-                       classes, spans, c->coarse_key, c->coarse_mask);
+                       blocks, c->xn32, c->wmax_bits, c->mu_norm2, margin_model(c, mode, nullptr),
+                       classes, spans, sub == kSubOnly, c->coarse_key, c->coarse_mask);
   return hipGetLastError();
 }
 

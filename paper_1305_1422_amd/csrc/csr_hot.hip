@@ -143,7 +143,9 @@ __global__ __launch_bounds__(256) void k_split_hot_tail(const int64_t *__restric
 // (bit pattern, atomic maximum): the operand the split kernel turns into planes.
 __global__ __launch_bounds__(256) void k_gather_hot_codebook(const float *__restrict__ W, const float *__restrict__ mu,
                                                              const int32_t *__restrict__ hot_cols, int k, int dim,
-                                                             float *__restrict__ out, unsigned *__restrict__ max_bits) {
+                                                             float *__restrict__ out, unsigned *__restrict__ max_bits,
+                                                             const SubspaceState *__restrict__ off) {
+  if (off && off->use) return;
   float amax = 0.f;
   for (int h = threadIdx.x; h < kHot; h += 256) {
     const int c = hot_cols[h];
@@ -263,10 +265,10 @@ hipError_t launch_split_hot_tail(som_ctx *c, const int64_t *indptr, const int32_
   return hipGetLastError();
 }
 
-hipError_t launch_gather_hot_codebook(som_ctx *c, const float *W) {
+hipError_t launch_gather_hot_codebook(som_ctx *c, const float *W, const SubspaceState *off) {
   const int blocks = c->k < c->n_cu * 4 ? c->k : c->n_cu * 4;
   hipLaunchKernelGGL(k_gather_hot_codebook, dim3(blocks), dim3(256), 0, c->stream, W, c->mu, c->hot_cols, c->k,
-                     c->dim, c->hot_Wc, c->hot_wmax_bits);
+                     c->dim, c->hot_Wc, c->hot_wmax_bits, off);
   return hipGetLastError();
 }
 

@@ -33,9 +33,10 @@ struct MarginModel {
   // the errors of an instance's dot products then, in the place of those
   const SubspaceState *sub;      // [1] or null
   const float *sub_err;          // [n]
+  int sub_fine;                  // the same of the fine pass
 };
 
-__device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j, double xnorm2, double wmax2,
+__device__ __forceinline__ double score_margin(MarginModel mm, int64_t j, double xnorm2, double wmax2,
                                                double munorm2) {
   const double u = 5.9604644775390625e-08;   // 2^-24
   const double xn = sqrt(xnorm2 * (1.0 + 1.2e-7));
@@ -56,9 +57,10 @@ __device__ __forceinline__ double score_margin(const MarginModel &mm, int64_t j,
     const double xh = sqrt((double)mm.hot_xn[j] * (1.0 + 1.2e-7));
     bound += mm.coef_hot * xh * wm + sqrt((double)kHot) * ((double)mm.hot_xscale[j] * wm + (double)*mm.hot_wscale * xh);
   }
-  if (mm.sub && mm.sub->use) {
+  if (mm.sub && (mm.sub_fine ? mm.sub->fine : mm.sub->use)) {
     coef = 4.0 + 2.0;        // its own accumulation is part of sub_err
     absolute += 2.0 * (double)mm.sub_err[j];
+    mm.xscale = nullptr;
   } else if (mm.xlost) {     // x'.w' - hi(x').hi(w') = dx.w' + hi(x').dw, doubled by the score's factor -2
     const double lx = (double)mm.xlost[j], lw = (double)__uint_as_float(*mm.wlost_bits);
     absolute += 2.0 * (lx * wm + (xn + lx) * lw);

@@ -303,6 +303,72 @@ hipError_t launch_codebook_means_and_steps(som_ctx *c, const float *W) {
   return hipGetLastError();
 }
 
+// The same with the sketch of the subspace search (bmu_subspace.hip) taken from the one read: a slab is the bucket of nodes
+// i = b mod 61 there, whose signed sum leaves as raw[row of the bucket][dim rounded up to 64] with the sum of its signs (50,000
+// columns, 2,500 nodes: 124 + 197 us apart).
+__global__ __launch_bounds__(kColBlock) void k_col_sums_and_sketch(const float *__restrict__ A, int k, int dim, int dimp,
+                                                                   double *__restrict__ partial, float *__restrict__ range,
+                                                                   float *__restrict__ raw, float *__restrict__ sign_sums) {
+  const int c = blockIdx.x * kColBlock + threadIdx.x, b = blockIdx.y;
+  const int row = b < kSubConst ? b : b + 3;
+  if (c >= dim) return;
+  double s = 0.0, d = 0.0;
+  float lo = INFINITY, hi = -INFINITY;
+  int signs = 0;
+  auto add = [&](int i, float a) {
+    const bool plus = sketch_sign(i);
+    s += (double)a;
+    d += plus ? (double)a : -(double)a;
+    signs += plus ? 1 : -1;
+    lo = fminf(lo, a);
+    hi = fmaxf(hi, a);
+  };
+  int i = b;
+  for (; i + 7 * kSketchBuckets < k; i += 8 * kSketchBuckets) {      // eight rows in flight per thread
+    float a[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] = A[(int64_t)(i + u * kSketchBuckets) * dim + c];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add(i + u * kSketchBuckets, a[u]);
+  }
+  for (; i < k; i += kSketchBuckets) add(i, A[(int64_t)i * dim + c]);
+  partial[(int64_t)b * dim + c] = s;
+  range[(int64_t)b * dim + c] = lo;
+  range[((int64_t)kMeanSlabs + b) * dim + c] = hi;
+  raw[(int64_t)row * dimp + c] = (float)d;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sign_sums[row] = (float)signs;
+}
+
+// Slabs behind the buckets: empty.  Then, once the means are known, the sketch of the centred nodes: its rows less sign sum x mean, the
+// three rows in between and the columns behind the last are zero.
+__global__ __launch_bounds__(256) void k_empty_slabs(int dim, double *__restrict__ partial, float *__restrict__ range) {
+  const int c = blockIdx.x * 256 + threadIdx.x, b = kSketchBuckets + blockIdx.y;
+  if (c >= dim) return;
+  partial[(int64_t)b * dim + c] = 0.0;
+  range[(int64_t)b * dim + c] = INFINITY;
+  range[((int64_t)kMeanSlabs + b) * dim + c] = -INFINITY;
+}
+__global__ __launch_bounds__(256) void k_center_sketch(float *__restrict__ S, int dim, int dimp, const float *__restrict__ mu,
+                                                       const float *__restrict__ sign_sums) {
+  const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
+  if (c >= dimp) return;
+  const bool on = c < dim && !(r >= kSubConst && r < kSubConst + 3);
+  S[(int64_t)r * dimp + c] = on ? S[(int64_t)r * dimp + c] - sign_sums[r] * mu[c] : 0.f;
+}
+
+hipError_t launch_codebook_means_steps_and_sketch(som_ctx *c, const float *W) {
+  static_assert(kSketchBuckets <= kMeanSlabs, "a slab per bucket");
+  const int dimp = (c->dim + 63) / 64 * 64;
+  hipLaunchKernelGGL(k_col_sums_and_sketch, dim3((c->dim + kColBlock - 1) / kColBlock, kSketchBuckets), dim3(kColBlock), 0, c->stream,
+                     W, c->k, c->dim, dimp, c->mu_partial, c->col_range, c->sub_S, c->sub_part);
+  hipLaunchKernelGGL(k_empty_slabs, dim3((c->dim + 255) / 256, kMeanSlabs - kSketchBuckets), dim3(256), 0, c->stream, c->dim,
+                     c->mu_partial, c->col_range);
+  hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(64), 0, c->stream, c->mu_partial,
+                     (int64_t)c->k, c->dim, c->mu, c->col_range, c->qstep, c->qstep_max_bits);
+  hipLaunchKernelGGL(k_center_sketch, dim3((dimp + 255) / 256, kSub), dim3(256), 0, c->stream, c->sub_S, c->dim, dimp, c->mu, c->sub_part);
+  return hipGetLastError();
+}
+
 hipError_t launch_vec_sqnorm(som_ctx *c, const float *v, int dim, float *out) {
   hipLaunchKernelGGL(k_vec_sqnorm, dim3(1), dim3(1024), 0, c->stream, v, dim, out);
   return hipGetLastError();

@@ -112,7 +112,7 @@ static bool two_level_ready(const som_ctx *c, int64_t n) {
 }
 
 static bool subspace_ready(const som_ctx *c, int64_t n) {
-  return subspace_eligible(c, n) && c->sub_state != nullptr && c->sub_Y1 != nullptr;
+  return subspace_eligible(c, n) && !c->sub_failed && c->sub_state != nullptr && c->sub_Y1 != nullptr;
 }
 
 static void free_row_scratch(som_ctx *c) {
@@ -124,7 +124,8 @@ static void free_row_scratch(som_ctx *c) {
   dev_free(c->Xh); dev_free(c->xscale);
   dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
   dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
-  dev_free(c->sub_Y1); dev_free(c->sub_yscale); dev_free(c->sub_err);
+  dev_free(c->sub_Y1); dev_free(c->sub_Y2); dev_free(c->sub_yscale); dev_free(c->sub_err); dev_free(c->sub_err2);
+  c->sub_failed = 0;
   c->two_level_n = 0;
   c->debug_coarse_n = 0;
   c->n_cap = 0;
@@ -136,17 +137,62 @@ static void free_row_scratch(som_ctx *c) {
 }
 
 static void free_subspace(som_ctx *c) {
-  dev_free(c->sub_S); dev_free(c->sub_G); dev_free(c->sub_Vp); dev_free(c->sub_Vt); dev_free(c->sub_U1); dev_free(c->sub_part);
-  dev_free(c->sub_state);
+  dev_free(c->sub_Y1); dev_free(c->sub_Y2); dev_free(c->sub_yscale); dev_free(c->sub_err); dev_free(c->sub_err2);
+  dev_free(c->sub_S); dev_free(c->sub_G); dev_free(c->sub_Vp); dev_free(c->sub_Vt); dev_free(c->sub_U1); dev_free(c->sub_U2); dev_free(c->sub_part);
+  dev_free(c->sub_state); dev_free(c->sub_Vf); dev_free(c->sub_cpart);
+}
+
+// Order of the nodes and tables of the two-level search, for n_cap instances.
+static int ensure_two_level_tables(som_ctx *c) {
+  const size_t blocks = (size_t)(c->k + 127) / 128, tiles = ((size_t)c->n_cap + 127) / 128;
+  if (c->node_of == nullptr) {
+    if (!(dev_alloc(&c->node_of, (size_t)c->k) && dev_alloc(&c->pos_of, (size_t)c->k))) {
+      dev_free(c->node_of); dev_free(c->pos_of);
+      return fail(c, SOM_ERR_ALLOC, "cannot allocate the order of the nodes");
+    }
+    SOM_LAUNCH(c, launch_patch_order(c));
+  }
+  if (c->coarse_min == nullptr &&
+      !(dev_alloc(&c->coarse_key, (size_t)c->n_cap) && dev_alloc(&c->coarse_mask, (blocks + 31) / 32 * (size_t)c->n_cap) &&
+        dev_alloc(&c->tile_cnt, tiles) && dev_alloc(&c->tile_list, tiles * blocks) && dev_alloc(&c->ctile_cnt, tiles) &&
+        dev_alloc(&c->ctile_list, tiles * blocks) && dev_alloc(&c->coarse_min, blocks * (size_t)c->n_cap))) {
+    dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
+    dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
+    return fail(c, SOM_ERR_ALLOC, "cannot allocate the two-level search's scratch for %lld instances", (long long)c->n_cap);
+  }
+  return SOM_OK;
+}
+
+// Basis and coordinates of the code book and, for n_cap instances, theirs.  fine: those of the fine pass; csr: the sparse search, with what its
+// passes over the code book need besides.  Where memory does not allow it, the searches run without (until n_cap changes).
+static bool allocate_subspace(som_ctx *c, bool fine, bool csr) {
+  const size_t v = subspace_vector_halves(c), N = (size_t)c->n_cap, K = (size_t)c->k;
+  if (csr && ensure_two_level_tables(c) != SOM_OK) return false;
+  if (c->sub_state == nullptr &&
+      !(dev_alloc(&c->sub_S, v / 2) && dev_alloc(&c->sub_G, (size_t)(subspace_gram_pieces(c) + 1) * kSub * kSub) && dev_alloc(&c->sub_Vp, v) &&
+        dev_alloc(&c->sub_Vt, v) && dev_alloc(&c->sub_U1, K * kSub) && dev_alloc(&c->sub_U2, K * kSub * 2) &&
+        dev_alloc(&c->sub_part, 5 * kSubspaceParts) && dev_alloc(&c->sub_state, 1)))
+    return false;
+  if (csr && c->sub_cpart == nullptr && !(dev_alloc(&c->sub_Vf, v / 2) && dev_alloc(&c->sub_cpart, subspace_csr_part_floats(c)))) return false;
+  if (c->sub_Y1 == nullptr && !(dev_alloc(&c->sub_yscale, N) && dev_alloc(&c->sub_err, N) && dev_alloc(&c->sub_Y1, N * kSub))) return false;
+  return !fine || c->sub_Y2 != nullptr || (dev_alloc(&c->sub_err2, N) && dev_alloc(&c->sub_Y2, N * kSub * 2));
+}
+
+static void ensure_subspace(som_ctx *c, bool fine, bool csr) {
+  if (c->sub_failed || allocate_subspace(c, fine, csr)) return;
+  (void)hipGetLastError();
+  free_subspace(c);
+  c->sub_failed = 1;
 }
 
 // Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
 // will run on them (false: the direct search, or an update alone).
-static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) {
+// sub: the search may run in the subspace of the code book.
+static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, bool sub = true) {
   const bool split = dense && filtered && uses_planes(c);
   // sized for the rows the scratch is (or will be) allocated for, so that it serves every n up to n_cap
   const bool coarse = split && two_level(c, n > c->n_cap ? n : c->n_cap);
-  const bool subspace = coarse && subspace_eligible(c, n > c->n_cap ? n : c->n_cap);
+  const bool subspace = sub && coarse && !c->sub_failed && subspace_eligible(c, n > c->n_cap ? n : c->n_cap);
   const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) ||
                             (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
@@ -197,40 +243,20 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true) 
   }
   if (coarse) {
     const size_t row_halves = (size_t)((c->dim + 63) / 64) * 64;
-    const size_t blocks = (size_t)(c->k + 127) / 128, tiles = ((size_t)c->n_cap + 127) / 128;
-    if (c->Wh1 == nullptr) {
-      dev_free(c->node_of); dev_free(c->pos_of);
-      if (!(dev_alloc(&c->node_of, (size_t)c->k) && dev_alloc(&c->pos_of, (size_t)c->k) && dev_alloc(&c->Wh1, (size_t)c->k * row_halves)))
-        return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of the code book");
-      SOM_LAUNCH(c, launch_patch_order(c));
-    }
+    if (c->Wh1 == nullptr && !dev_alloc(&c->Wh1, (size_t)c->k * row_halves))
+      return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of the code book");
     if (c->Xh1 == nullptr) {
       c->d_split_valid = 0;
       c->csrd_valid = 0;
-      if (!(dev_alloc(&c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc(&c->xlost, (size_t)c->n_cap) && dev_alloc(&c->coarse_min, blocks * (size_t)c->n_cap) &&
-            dev_alloc(&c->coarse_key, (size_t)c->n_cap) && dev_alloc(&c->coarse_mask, (blocks + 31) / 32 * (size_t)c->n_cap) &&
-            dev_alloc(&c->tile_cnt, tiles) && dev_alloc(&c->tile_list, tiles * blocks) &&
-            dev_alloc(&c->ctile_cnt, tiles) && dev_alloc(&c->ctile_list, tiles * blocks))) {
-        dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
-        dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
-        return fail(c, SOM_ERR_ALLOC, "cannot allocate the two-level search's scratch for %lld instances", (long long)c->n_cap);
+      if (!(dev_alloc(&c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc(&c->xlost, (size_t)c->n_cap))) {
+        dev_free(c->Xh1); dev_free(c->xlost);
+        return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of %lld instances", (long long)c->n_cap);
       }
     }
+    const int rc = ensure_two_level_tables(c);
+    if (rc) return rc;
   }
-  if (subspace) {
-    const size_t v = subspace_vector_halves(c);
-    if (c->sub_state == nullptr &&
-        !(dev_alloc(&c->sub_S, v / 2) && dev_alloc(&c->sub_G, 2 * kSub * kSub) && dev_alloc(&c->sub_Vp, v) && dev_alloc(&c->sub_Vt, v) &&
-          dev_alloc(&c->sub_U1, (size_t)c->k * kSub) && dev_alloc(&c->sub_part, 5 * kSubspaceParts) && dev_alloc(&c->sub_state, 1))) {
-      free_subspace(c);
-      return fail(c, SOM_ERR_ALLOC, "cannot allocate the subspace of the code book");
-    }
-    if (c->sub_Y1 == nullptr &&
-        !(dev_alloc(&c->sub_yscale, (size_t)c->n_cap) && dev_alloc(&c->sub_err, (size_t)c->n_cap) && dev_alloc(&c->sub_Y1, (size_t)c->n_cap * kSub))) {
-      dev_free(c->sub_Y1); dev_free(c->sub_yscale); dev_free(c->sub_err);
-      return fail(c, SOM_ERR_ALLOC, "cannot allocate the coordinates of %lld instances", (long long)c->n_cap);
-    }
-  }
+  if (subspace) ensure_subspace(c, c->dim >= kSubspaceFineDim, false);
   return SOM_OK;
 }
 
@@ -239,6 +265,7 @@ static int ensure_candidates(som_ctx *c, int64_t n, bool dense) {
   int groups_h = dense && uses_planes(c) ? bmu_dense_h_groups(c, n) : 1;
   if (dense && two_level_ready(c, n) && bmu_dense_h_fine_groups(c, n) > groups_h) groups_h = bmu_dense_h_fine_groups(c, n);
   const int groups_f = dense ? bmu_dense_groups(c, n) : 8 * c->csr_sweeps;      // sparse: one list per node range
+  if (!dense && c->sub_cpart && bmu_dense_h_fine_groups(c, n) > groups_h) groups_h = bmu_dense_h_fine_groups(c, n);
   const int64_t need = (int64_t)(groups_h > groups_f ? groups_h : groups_f) * n;
   if (!dense && n * c->csr_sweeps > c->unit_cap) {
     (void)hipStreamSynchronize(c->stream);
@@ -362,12 +389,13 @@ static int prepare_dense(som_ctx *c, const float *X, int64_t n, const float *W, 
 // W: the code book if the coarse pass may run in its subspace, else null.
 static int dense_filter_stage(som_ctx *c, const float *X, int64_t n, bool split, bool coarse, const float *W) {
   if (coarse) {
+    const SubspaceUse sub = W ? kSubMay : kSubNo;
     if (W) SOM_LAUNCH(c, launch_subspace(c, W, n));
-    SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, W != nullptr));
-    SOM_LAUNCH(c, launch_select_blocks(c, n, W != nullptr));
+    SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, sub));
+    SOM_LAUNCH(c, launch_select_blocks(c, n, sub));
     SOM_LAUNCH(c, launch_order_by_key(c, c->coarse_key, n));
     SOM_LAUNCH(c, launch_tile_lists(c, n));
-    SOM_LAUNCH(c, launch_bmu_dense_h_fine(c, n));
+    SOM_LAUNCH(c, launch_bmu_dense_h_fine(c, n, c->sub_Y2 ? sub : kSubNo));
   } else if (split) {
     SOM_LAUNCH(c, launch_bmu_dense_h(c, n, nullptr));
   } else {
@@ -398,19 +426,20 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
   if (rc) return rc;
   const bool split = uses_planes(c);
   const bool coarse = two_level_ready(c, n);
+  const bool sub = coarse && subspace_ready(c, n) && subspace_likely(c, n, radius), sub_fine = sub && c->sub_Y2;
   c->two_level_n = coarse ? n : 0;
   {
     StageTimer t(c, 0);
-    const bool sub = coarse && radius > 0.0 && subspace_ready(c, n) && subspace_likely(c, radius);
     rc = dense_filter_stage(c, X, n, split, coarse, sub ? W : nullptr);
     if (rc) return rc;
   }
   StageTimer t(c, 2);
   SOM_LAUNCH(c, launch_certify(c, n, coarse ? bmu_dense_h_fine_groups(c, n) : split ? bmu_dense_h_groups(c, n) : bmu_dense_groups(c, n),
-                               split ? kCertifySplit : kCertifyFp32, nullptr, bmus, false, coarse ? c->sort_val[0] : nullptr));
+                               sub_fine ? kCertifySubspaceFine : split ? kCertifySplit : kCertifyFp32, nullptr, bmus, false,
+                               coarse ? c->sort_val[0] : nullptr));
   SOM_LAUNCH(c, launch_refine_dense(c, X, W, bmus));
   if (coarse) SOM_LAUNCH(c, launch_collect_tile_lists(c, n));
-  if (split) SOM_LAUNCH(c, launch_bmu_dense_h_collect(c, n, coarse));
+  if (split) SOM_LAUNCH(c, launch_bmu_dense_h_collect(c, n, coarse, sub_fine ? kSubMay : kSubNo));
   else SOM_LAUNCH(c, launch_bmu_dense_collect(c, X, n));
   SOM_LAUNCH(c, launch_refine_lists_dense(c, X, W, bmus));
   SOM_LAUNCH(c, launch_rescan_dense(c, X, W, bmus));
@@ -421,7 +450,7 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
 // vector (mean of the code-book rows) with the quantisation steps, node constants, the transposed 16-bit
 // code book and the scaled values.
 static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
-                       int64_t nnz, const float *W, bool have_xn, bool cleared) {
+                       int64_t nnz, const float *W, bool have_xn, bool cleared, bool sketch = false) {
   if (nnz > c->vq_cap) {
     (void)hipStreamSynchronize(c->stream);
     dev_free(c->vq);
@@ -441,15 +470,16 @@ static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices
   if (c->data_kind == 1) { c->d_norms_valid = 0; c->d_split_valid = 0; }
   rc = begin_search(c, cleared);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_codebook_means_and_steps(c, W));
+  if (sketch) SOM_LAUNCH(c, launch_codebook_means_steps_and_sketch(c, W));
+  else SOM_LAUNCH(c, launch_codebook_means_and_steps(c, W));
   SOM_LAUNCH(c, launch_vec_sqnorm(c, c->mu, c->dim, c->mu_norm2));
   return SOM_OK;
 }
 
 // First part of the sparse filter pass: the code book read once - centred, quantised, transposed, its node
 // constants and norms taken on the way - and, under a bubble neighbourhood, its duplicate rows masked.
-static int codebook_for_sweep(som_ctx *c, const float *W) {
-  SOM_LAUNCH(c, launch_center_transpose_codebook(c, W));
+static int codebook_for_sweep(som_ctx *c, const float *W, const SubspaceState *off = nullptr) {
+  SOM_LAUNCH(c, launch_center_transpose_codebook(c, W, off));
   if (c->nb_function == SOM_NEIGHBORHOOD_BUBBLE) SOM_LAUNCH(c, launch_mask_duplicate_rows(c, W));
   return SOM_OK;
 }
@@ -498,12 +528,30 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
   return SOM_OK;
 }
 
+// radius as in bmu_search_dense.
 static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
-                          int64_t n, int64_t nnz, const float *W, int32_t *bmus, bool have_xn, bool cleared = false) {
+                          int64_t n, int64_t nnz, const float *W, int32_t *bmus, bool have_xn, bool cleared = false,
+                          double radius = 0.0) {
   if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus, cleared);
-  int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn, cleared);
+  // in the subspace of the code book if the device finds that it may, and then nothing is left for the sweep to do
+  const bool eligible = subspace_csr_eligible(c, n, nnz);
+  if (eligible) ensure_subspace(c, true, true);
+  const bool sub = eligible && !c->sub_failed && subspace_csr_likely(c, radius);
+  int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn, cleared, sub);
   if (rc) return rc;
   ensure_rescan_copy(c);
+  const SubspaceState *state = sub ? c->sub_state : nullptr;
+  c->two_level_n = sub ? n : 0;
+  if (sub) {
+    StageTimer t(c, 1);
+    SOM_LAUNCH(c, launch_csr_subspace(c, indptr, indices, values, n, W));
+    SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, kSubOnly));
+    SOM_LAUNCH(c, launch_select_blocks(c, n, kSubOnly));
+    SOM_LAUNCH(c, launch_order_by_key(c, c->coarse_key, n));
+    SOM_LAUNCH(c, launch_tile_lists(c, n));
+    SOM_LAUNCH(c, launch_bmu_dense_h_fine(c, n, kSubOnly));
+    SOM_LAUNCH(c, launch_certify(c, n, bmu_dense_h_fine_groups(c, n), kCertifySubspaceCsr, nullptr, bmus, false, c->sort_val[0], state));
+  }
   // registered rows whose frequent columns were split off: the sweeps walk the tail and start from the
   // matrix-core pass over the hot block; the exact kernels keep the caller's full rows
   const bool hot = have_xn && c->hot_on;
@@ -513,20 +561,25 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   const int64_t sw_nnz = hot ? c->tail_nnz : nnz;
   {
     StageTimer t(c, 1);
-    rc = codebook_for_sweep(c, W);
+    rc = codebook_for_sweep(c, W, state);
     if (rc) return rc;
     if (hot) {
-      SOM_LAUNCH(c, launch_gather_hot_codebook(c, W));
-      SOM_LAUNCH(c, launch_split_rows_f16(c, c->hot_Wc, c->k, c->hot_wmax_bits, nullptr, c->hot_Wh, c->hot_wscale, kHot));
-      SOM_LAUNCH(c, launch_hot_partial(c, n));
+      SOM_LAUNCH(c, launch_gather_hot_codebook(c, W, state));
+      SOM_LAUNCH(c, launch_split_rows_f16(c, c->hot_Wc, c->k, c->hot_wmax_bits, nullptr, c->hot_Wh, c->hot_wscale, kHot, nullptr, nullptr,
+                                          nullptr, nullptr, state));
+      SOM_LAUNCH(c, launch_hot_partial(c, n, state));
     }
-    SOM_LAUNCH(c, launch_scale_values(c, sw_indices, sw_values, sw_nnz));
-    SOM_LAUNCH(c, launch_bmu_csr_sliced(c, sw_indptr, sw_indices, c->vq, n, false, nullptr, hot));
+    SOM_LAUNCH(c, launch_scale_values(c, sw_indices, sw_values, sw_nnz, state));
+    SOM_LAUNCH(c, launch_bmu_csr_sliced(c, sw_indptr, sw_indices, c->vq, n, false, nullptr, hot, state));
   }
   StageTimer t(c, 2);
-  SOM_LAUNCH(c, launch_certify(c, n, 8 * c->csr_sweeps, kCertifyCsr, sw_indptr, bmus, hot));
+  SOM_LAUNCH(c, launch_certify(c, n, 8 * c->csr_sweeps, kCertifyCsr, sw_indptr, bmus, hot, nullptr, state));
   SOM_LAUNCH(c, launch_refine_csr(c, indptr, indices, values, W, bmus));
-  SOM_LAUNCH(c, launch_bmu_csr_sliced(c, sw_indptr, sw_indices, c->vq, n, true, nullptr, hot));
+  if (sub) {
+    SOM_LAUNCH(c, launch_collect_tile_lists(c, n));
+    SOM_LAUNCH(c, launch_bmu_dense_h_collect(c, n, true, kSubOnly));
+  }
+  SOM_LAUNCH(c, launch_bmu_csr_sliced(c, sw_indptr, sw_indices, c->vq, n, true, nullptr, hot));      // (its work list is empty then)
   SOM_LAUNCH(c, launch_refine_lists_csr(c, indptr, indices, values, W, bmus));
   SOM_LAUNCH(c, launch_rescan_csr(c, indptr, indices, values, W, bmus));
   return SOM_OK;
@@ -649,7 +702,7 @@ static int registered_csr_dense(som_ctx *c) {
   const int64_t n = c->d_n, nnz = c->d_nnz;
   if (!c->csrd_enabled || c->data_kind != 2 || !uses_planes(c) || c->dim > kCsrDenseMaxDim || nnz < 1) return SOM_OK;
   if ((double)nnz < kCsrDenseMinDensity * (double)n * (double)c->dim) return SOM_OK;
-  int rc = ensure_rows(c, n, true);          // planes, centred code book (may reset csrd_valid: set again below)
+  int rc = ensure_rows(c, n, true, true, false);          // planes, centred code book (may reset csrd_valid: set again below)
   if (rc) return rc;
   c->csrd_valid = 1;
   if (n > c->csrd_n_cap || !c->csrd_mu) {
@@ -933,7 +986,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
   }
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
-  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true);
+  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true, radius);
   if (rc) return rc;
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
 }
@@ -1016,7 +1069,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
-                          true);
+                          true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0 /* the first code book is the caller's */);
       if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, bmus, codebook);
     }
     if (rc) return rc;
@@ -1179,9 +1232,9 @@ int som_debug_select_margins(som_ctx *c, int64_t n, double *margin_out) {
 }
 
 int som_debug_subspace(som_ctx *c, const float *data, int64_t n, const float *codebook, float *block_min, double *margin_out,
-                       int32_t *node_of, float *mu_out, int32_t *used) {
+                       int32_t *node_of, float *mu_out, int32_t *used, float *loss) {
   if (!c) return SOM_ERR_INVALID_ARG;
-  if (!data || !codebook || !block_min || !margin_out || !node_of || !mu_out || !used) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  if (!data || !codebook || !block_min || !margin_out || !node_of || !mu_out || !used || !loss) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_rows(c, n);
   if (!rc) rc = ensure_rows(c, n, true);
   if (rc) return rc;
@@ -1189,13 +1242,14 @@ int som_debug_subspace(som_ctx *c, const float *data, int64_t n, const float *co
   rc = prepare_dense(c, data, n, codebook, false, false);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_subspace(c, codebook, n));
-  SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, true));
+  SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, kSubMay));
   SOM_LAUNCH(c, launch_margins(c, n, kCertifySubspace, nullptr, margin_out));
   const size_t blocks = ((size_t)c->k + 127) / 128;
   SOM_LAUNCH(c, hipMemcpyAsync(block_min, c->coarse_min, blocks * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
   SOM_LAUNCH(c, hipMemcpyAsync(node_of, c->node_of, (size_t)c->k * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
   SOM_LAUNCH(c, hipMemcpyAsync(mu_out, c->mu, (size_t)c->dim * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
-  SOM_LAUNCH(c, hipMemcpyAsync(used, &c->sub_state->use, sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(used, &c->sub_state->use, 2 * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(loss, &c->sub_state->e32, 2 * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
   return SOM_OK;
 }
 

@@ -64,10 +64,17 @@ constexpr int kCsrDenseMaxDim = 4096;      // registered sparse sets up to this 
 constexpr double kCsrDenseMinDensity = 0.04;   // ... if at least this share of their entries is nonzero
 constexpr int kSub = 64;                   // coordinates in the code book's subspace (bmu_subspace.hip) ...
 constexpr int kSubConst = 29;              // ... of which three, from this one on, carry the node constants
+constexpr int kSketchBuckets = kSub - 3;   // nodes i = b mod 61 share row b of its sketch (rows past kSubConst come three later)
 constexpr int kSubspaceParts = 512;        // workgroups of its node pass at most
 constexpr double kSubspaceMinWork = 7e10;  // multiply-adds a search has to save for the subspace to be tried
 constexpr double kSubspaceMaxArea = 100.0; // ... and map nodes per squared radius at most
+constexpr double kSubspaceAloneWork = 1.4e11;  // the same for a search outside an epoch, whose code book may be anything
 constexpr float kSubspaceLoss = 0x1p-8f;   // share of the largest |w'| that may lie outside for it to be used
+constexpr float kSubspaceLossFine = 0x1p-14f;  // ... outside all of them for the fine pass to use them too
+constexpr int kSubspaceFineDim = 256;      // ... which takes this many features to pay
+constexpr int kSubspaceCsrDim = 1024;      // sparse rows: fewest features ...
+constexpr double kSubspaceCsrMaxArea = 16.5;   // ... most map nodes per squared radius ...
+constexpr float kSubspaceLossCsr = 0x1p-15f;   // ... and what may lie outside
 constexpr float kSubspaceLoss32 = 0x1p-11f;    // ... outside the first 32 coordinates for those to do
 constexpr int kHot = 256;                  // columns of the dense hot block of a registered sparse training set
 constexpr double kHotMinShare = 0.3;       // share of the nonzeros those columns must hold for the split to be used
@@ -88,10 +95,14 @@ struct CandView {
 // What the coarse pass needs to know of the subspace of the code book (bmu_subspace.hip), decided on the device.
 struct SubspaceState {
   int use;                 // the coarse pass runs on the coordinates: 1 the first 32 of them, 2 all 64, 0 it does not
+  int fine;                // so do the fine and the collect pass, on all 64 of them
+  int full;                // set before the coordinates are looked at: the code book is of full rank for all one can tell
   float e;                 // largest |w'_i - V^T u_i| (of the first 32, if use = 1)
+  float e32, e64;          // ... of the first 32, of all 64
   float u, u1;             // largest |u_i|; largest sum_r |u_ir| times the largest |V_r|
   float ulost;             // largest |u_i - hi(u_i)|
   float wm;                // largest |w'_i|
+  float cmax;              // bound of the node constants
   float uscale;            // power of two the coordinates of the nodes were divided by
   float cscale;            // ... and their constants c_i
 };
@@ -233,13 +244,17 @@ struct som_ctx {
   int32_t *node_of, *pos_of;  // [k] order of the nodes in the two-level search's planes, and its inverse
   // subspace of the code book (bmu_subspace.hip), lazily allocated with Xh1 where the searches are large enough
   float *sub_S;               // [kSub][dim rounded up to 64] random combinations of the centred nodes
-  double *sub_G;              // [2][kSub][kSub] their Gram matrix, the transposed inverse of its Cholesky factor
+  double *sub_G;              // [pieces + 1][kSub][kSub] their Gram matrix in pieces, the transposed inverse of its Cholesky factor
   _Float16 *sub_Vp, *sub_Vt;  // the basis as hi/lo planes in two orders
-  _Float16 *sub_U1;           // [k][kSub] hi halves of the nodes' coordinates
+  float *sub_Vf;              // [dim rounded up to 64][kSub] the basis by feature (sparse rows only)
+  _Float16 *sub_U1, *sub_U2;  // [k][kSub] hi halves of the nodes' coordinates; [k][kSub/32][32 hi | 32 lo]
   float *sub_part;            // [kSubspaceParts][5] maxima per workgroup
   som::SubspaceState *sub_state;
-  _Float16 *sub_Y1;           // [n_cap][kSub] hi halves of the instances' coordinates
-  float *sub_yscale, *sub_err;    // [n_cap] their scales, and the bounds on their dot products' errors
+  int sub_failed;             // there was no memory for it at n_cap instances
+  float *sub_cpart;           // partial sums of the sparse search's passes over the code book, subspace_csr_part_floats
+  _Float16 *sub_Y1, *sub_Y2;  // the same of the instances, [n_cap] (sub_Y2: with enough features only)
+  float *sub_yscale;          // [n_cap] their scales ...
+  float *sub_err, *sub_err2;  // ... and the bounds on the errors of their dot products, coarse and fine
   float *hot_P;           // [ceil(k/128)][n][128] dot products of the hot parts divided by the instance scale
 
   // dense planes of the registered sparse training set (som_set_sparse_dense_filter); built on first use
@@ -276,6 +291,7 @@ namespace som {
 // norms.hip
 hipError_t launch_sample_col_means(som_ctx *c, const float *A, int64_t nrows, int dim, float *mu);
 hipError_t launch_codebook_means_and_steps(som_ctx *c, const float *W);      // -> mu, qstep, qstep_max_bits
+hipError_t launch_codebook_means_steps_and_sketch(som_ctx *c, const float *W);      // -> mu, qstep, qstep_max_bits, sub_S
 hipError_t launch_vec_sqnorm(som_ctx *c, const float *v, int dim, float *out);
 hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centered, bool want_wn64,
                                   bool x_centered,
@@ -309,25 +325,35 @@ int bmu_dense_h_groups(const som_ctx *c, int64_t n);
 hipError_t launch_bmu_dense_h(som_ctx *c, int64_t n, float *dump, bool ordered = false /* dump: rows in the order node_of */);            // Xh, Wh -> candidates (or all scores)
 int bmu_dense_h_fine_groups(const som_ctx *c, int64_t n);
 // bmu_coarse.hip: Xh1, Wh1 -> coarse_min (or all scores); sub: on the subspace's coordinates if sub_state says so
-hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, bool sub = false);
+// kSubOnly: there are no full rows, nothing happens if it says no.
+enum SubspaceUse { kSubNo = 0, kSubMay = 1, kSubOnly = 2 };
+hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, SubspaceUse sub = kSubNo);
 // bmu_subspace.hip
 bool subspace_eligible(const som_ctx *c, int64_t n);
-bool subspace_likely(const som_ctx *c, double radius);
+bool subspace_likely(const som_ctx *c, int64_t n, double radius);
 size_t subspace_vector_halves(const som_ctx *c);     // size of sub_Vp and of sub_Vt
+int subspace_gram_pieces(const som_ctx *c);
 hipError_t launch_subspace(som_ctx *c, const float *W, int64_t n);             // Wh, Xh1 -> sub_*
-hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n);                     // sort_val[0], tile_cnt, tile_list -> candidates
+// bmu_subspace_csr.hip
+bool subspace_csr_eligible(const som_ctx *c, int64_t n, int64_t nnz);
+bool subspace_csr_likely(const som_ctx *c, double radius);
+size_t subspace_csr_part_floats(const som_ctx *c);
+hipError_t launch_csr_subspace(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
+                               const float *W);                                 // mu, qstep_max_bits, xn32 -> sub_*, wn32 (in the order node_of), wn64, wmax_bits
+hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n, SubspaceUse sub = kSubNo);                   // sort_val[0], tile_cnt, tile_list -> candidates
 // bmu_two_level.hip
-hipError_t launch_select_blocks(som_ctx *c, int64_t n, bool sub = false);      // coarse_min -> coarse_key, coarse_mask
+hipError_t launch_select_blocks(som_ctx *c, int64_t n, SubspaceUse sub = kSubNo);      // coarse_min -> coarse_key, coarse_mask
 constexpr int kPatchRows = 12;
 hipError_t launch_patch_order(som_ctx *c);                                     // -> node_of, pos_of
 hipError_t launch_tile_lists(som_ctx *c, int64_t n);                           // coarse_mask, sort_val[0] -> tile_cnt, tile_list
 hipError_t launch_collect_tile_lists(som_ctx *c, int64_t n);                   // coarse_mask, collect_rows -> ctile_cnt, ctile_list
-hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists = false);   // rows of collect_rows -> collect_list
+hipError_t launch_bmu_dense_h_collect(som_ctx *c, int64_t n, bool lists = false, SubspaceUse sub = kSubNo);   // rows of collect_rows -> collect_list
 hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, const unsigned *global_max_bits,
                                  const float *mu /* subtracted first, or null */, _Float16 *out, float *scale_out,
                                  int dim = 0 /* row length; 0: the context's */,
                                  _Float16 *out_hi = nullptr /* the hi halves alone, rows padded to 64 columns */,
-                                 const int32_t *src = nullptr, float *res_out = nullptr, unsigned *res_max = nullptr);
+                                 const int32_t *src = nullptr, float *res_out = nullptr, unsigned *res_max = nullptr,
+                                 const SubspaceState *off = nullptr);
 constexpr int kPlaneMaxDim = 2048;       // rows up to this length are prepared in registers (no centred copy Wc of the code book)
 hipError_t launch_codebook_planes(som_ctx *c, const float *W, bool want_wn64, bool coarse);      // -> wn32, wmax_bits, Wh, wscale (wn64, Wh1)
 hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, const float *mu, int64_t first, bool coarse,
@@ -352,9 +378,10 @@ constexpr int kListWords = kListCounts + kListTickets * kListTicketStride;
 constexpr int kUnitCounts = 4;     // first of the eight work-list lengths in it
 constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits, wlost_bits
 constexpr int kSubTicketWord = 17; // arrivals of k_subspace_coords
-enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4, kCertifySubspace = 5 };      // whose rounding bound the margin uses
+enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4, kCertifySubspace = 5, kCertifySubspaceFine = 6, kCertifySubspaceCsrSelect = 7, kCertifySubspaceCsr = 8 };      // whose rounding bound the margin uses
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus,
-                          bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */);
+                          bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */,
+                          const SubspaceState *state = nullptr /* only if the device decided for (kCertifySubspaceCsr) or against the subspace */);
 hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr, double *out,
                           bool hot = false);   // test hook: the margin per instance
 hipError_t launch_refine_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
@@ -385,8 +412,9 @@ hipError_t launch_hot_histogram(som_ctx *c, const int32_t *indices, int64_t nnz,
 hipError_t launch_tail_lengths(som_ctx *c, const int64_t *indptr, const int32_t *indices, int64_t n, int32_t *len);
 hipError_t launch_split_hot_tail(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
                                  int64_t n);
-hipError_t launch_gather_hot_codebook(som_ctx *c, const float *W);   // -> hot_Wc, hot_wmax_bits
-hipError_t launch_hot_partial(som_ctx *c, int64_t n);                // bmu_dense_h.hip: hot_Xh, hot_Wh -> hot_P
+// `off` of the sparse sweep's launches: they do nothing where the device decided for the subspace (null: they run)
+hipError_t launch_gather_hot_codebook(som_ctx *c, const float *W, const SubspaceState *off = nullptr);   // -> hot_Wc, hot_wmax_bits
+hipError_t launch_hot_partial(som_ctx *c, int64_t n, const SubspaceState *off = nullptr);                // bmu_dense_h.hip: hot_Xh, hot_Wh -> hot_P
 hipError_t launch_scan_exclusive_i32(som_ctx *c, const int32_t *in, int32_t *out, int len);   // segsum.hip
 
 // dedup.hip
@@ -394,15 +422,15 @@ hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W, const int32_t 
 
 // bmu_csr.hip
 constexpr int kCtMaxSlabs = 64;            // column slabs of the fused centring / transpose pass
-hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W);   // mu, qstep -> Wt, wn32, wn64, wmax_bits
+hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const SubspaceState *off = nullptr);   // mu, qstep -> Wt, wn32, wn64, wmax_bits
 void csr_slice_geometry(int k, int *acc, int *sweeps, int *kpad);
-hipError_t launch_scale_values(som_ctx *c, const int32_t *indices, const float *values, int64_t nnz);   // -> vq
+hipError_t launch_scale_values(som_ctx *c, const int32_t *indices, const float *values, int64_t nnz, const SubspaceState *off = nullptr);   // -> vq
 enum { kCsrBadSorted = 1, kCsrBadIndex = 2, kCsrBadOrder = 3, kCsrBadLast = 4, kCsrBadFirst = 5 };   // k_validate_csr: the largest is reported
 hipError_t launch_validate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, int64_t n, int64_t nnz,
                                int32_t *flag);
 hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
                                  int64_t n, bool collect, float *dump = nullptr,   // dump: test hook, all scores [n][k]
-                                 bool hot = false);   // the rows are the tail of the registered set: sums start from hot_P
+                                 bool hot = false, const SubspaceState *off = nullptr);   // hot: the rows are the tail of the registered set: sums start from hot_P
 
 // segsum.hip
 int64_t group_table_entries(int k, int64_t n);       // entries of c->group_table for up to n instances
@@ -441,6 +469,13 @@ __host__ __device__ inline double cooled(double v0, double vN, int n_epochs, int
 }
 
 // ---------------------------------------------------------------- device helpers
+// Sign of node i in the sketch of the code book (bmu_subspace.hip).
+__device__ __forceinline__ bool sketch_sign(int i) {
+  unsigned h = (unsigned)i * 2654435761u;
+  h = (h ^ (h >> 16)) * 0x85ebca6bu;
+  return (h >> 31) != 0;
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);

@@ -63,7 +63,9 @@ __global__ __launch_bounds__(256) void k_split_rows_f16(const float *__restrict_
                                                         const float *__restrict__ mu,
                                                         _Float16 *__restrict__ out, float *__restrict__ scale_out,
                                                         _Float16 *__restrict__ out_hi, const int32_t *__restrict__ src,
-                                                        float *__restrict__ res_out, unsigned *__restrict__ res_max) {
+                                                        float *__restrict__ res_out, unsigned *__restrict__ res_max,
+                                                        const SubspaceState *__restrict__ off) {
+  if (off && off->use) return;
   __shared__ float smax[4];
   float worst = 0.f;
   constexpr int kTeams = 256 / kTeam;
@@ -346,7 +348,7 @@ hipError_t launch_instance_planes(som_ctx *c, const float *A, int64_t nrows, con
 
 hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, const unsigned *global_max_bits,
                                  const float *mu, _Float16 *out, float *scale_out, int dim, _Float16 *out_hi,
-                                 const int32_t *src, float *res_out, unsigned *res_max) {
+                                 const int32_t *src, float *res_out, unsigned *res_max, const SubspaceState *off) {
   if (dim <= 0) dim = c->dim;
   const int nK = (dim + 31) / 32;
   const int64_t cap = (int64_t)c->n_cu * (res_max ? 4 : 16);
@@ -354,11 +356,11 @@ hipError_t launch_split_rows_f16(som_ctx *c, const float *A, int64_t nrows, cons
     int64_t blocks = (nrows + 3) / 4;
     if (blocks > cap) blocks = cap;
     hipLaunchKernelGGL(k_split_rows_f16<64>, dim3((unsigned)blocks), dim3(256), 0, c->stream, A, nrows, dim, nK,
-                       global_max_bits, mu, out, scale_out, out_hi, src, res_out, res_max);
+                       global_max_bits, mu, out, scale_out, out_hi, src, res_out, res_max, off);
   } else {
     int64_t blocks = nrows < cap ? nrows : cap;
     hipLaunchKernelGGL(k_split_rows_f16<256>, dim3((unsigned)blocks), dim3(256), 0, c->stream, A, nrows, dim, nK,
-                       global_max_bits, mu, out, scale_out, out_hi, src, res_out, res_max);
+                       global_max_bits, mu, out, scale_out, out_hi, src, res_out, res_max, off);
   }
   return hipGetLastError();
 }

@@ -29,9 +29,10 @@ def _minima(W, X, rows, cols):
     margin = torch.empty(n, dtype=torch.float64, device="cuda")
     node_of = torch.empty(k, dtype=torch.int32, device="cuda")
     mu = torch.empty(dim, dtype=torch.float32, device="cuda")
-    used = torch.empty(1, dtype=torch.int32, device="cuda")
-    capi.som_debug_subspace(som.ctx, P.to_dev(X), som.codebook, m, margin, node_of, mu, used)
-    out = m.cpu().numpy(), margin.cpu().numpy(), node_of.cpu().numpy(), mu.cpu().numpy(), int(used.item())
+    used = torch.empty(2, dtype=torch.int32, device="cuda")
+    loss = torch.empty(2, dtype=torch.float32, device="cuda")
+    capi.som_debug_subspace(som.ctx, P.to_dev(X), som.codebook, m, margin, node_of, mu, used, loss)
+    out = m.cpu().numpy(), margin.cpu().numpy(), node_of.cpu().numpy(), mu.cpu().numpy(), int(used[0].item())
     som.close()
     return out
 
@@ -157,3 +158,26 @@ def test_recorded_epochs(oracle):
             assert np.array_equal(b.cpu().numpy(), eager)
         stream.synchronize()
         som.close()
+
+
+@pytest.mark.parametrize("dim,rank", [(256, 20), (300, 50), (1000, 12), (2048, 40)])
+@pytest.mark.parametrize("data", ["near", "sizes", "copies"])
+def test_whole_search_on_the_coordinates(oracle, dim, rank, data):
+    """Code books that lie in the coordinates to rounding: the fine and the collect pass run on them too."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8700 + dim)
+    rows, cols, n = 33, 37, 1100
+    k = rows * cols
+    W = _book(rng, k, dim, rank)
+    if data == "copies":                       # near-copies that only exact distances tell apart, and exact ones
+        W = W[np.arange(k) // 40 * 40]
+        W += (rng.integers(-1, 2, size=W.shape) * np.float32(2.0 ** -24)).astype(np.float32)
+        W[k // 2:k // 2 + 100] = W[:100]
+    X = (W[rng.integers(0, k, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    if data == "sizes":
+        X = (X * np.exp2(rng.integers(-12, 12, (n, 1)))).astype(np.float32)
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    b = som.bmus(P.to_dev(X)).cpu().numpy()
+    som.close()
+    P.check_bmus_dense(oracle, X, W, b)
+    assert np.array_equal(b, oracle.bmu_dense(X, W))

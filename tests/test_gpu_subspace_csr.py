@@ -1,0 +1,135 @@
+"""The sparse search on the coordinates of a smooth code book against the oracle: whole epochs on planar maps, at ragged sizes,
+with empty and long rows, where the coordinates do and where they do not carry the code book, recorded into a graph, and what
+goes past it."""
+import numpy as np
+import pytest
+
+from gen import sparse_zipf_csr
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _smooth_book(rng, rows, cols, dim, radius, csr):
+    """What a batch update of that radius leaves: Gaussian means of rows placed at random nodes."""
+    indptr, indices, values = csr
+    n = indptr.size - 1
+    at = rng.integers(0, rows * cols, n)
+    S = np.zeros((rows * cols, dim))
+    np.add.at(S, (np.repeat(at, np.diff(indptr)), indices), values)
+    C = np.bincount(at, minlength=rows * cols).astype(np.float64)
+    y, x = np.divmod(np.arange(rows * cols), cols)
+    H = np.exp(-((y[:, None] - y) ** 2 + (x[:, None] - x) ** 2) / (2.0 * radius * radius))
+    return ((H @ S) / (H @ C)[:, None]).astype(np.float32)
+
+
+def _edge_rows(csr, dim):
+    """The same set with an empty row, a row of one nonzero, and one of a thousand."""
+    indptr, indices, values = csr
+    n = indptr.size - 1
+    rows = [(indices[indptr[j]:indptr[j + 1]], values[indptr[j]:indptr[j + 1]]) for j in range(n)]
+    rows[3] = (np.zeros(0, np.int32), np.zeros(0, np.float32))
+    rows[5] = (np.array([dim - 1], np.int32), np.array([0.7], np.float32))
+    rows[n - 1] = (np.arange(5, 1005, dtype=np.int32), np.linspace(-0.1, 0.1, 1000).astype(np.float32))
+    ptr = np.zeros(n + 1, np.int64)
+    ptr[1:] = np.cumsum([r[0].size for r in rows])
+    return ptr, np.concatenate([r[0] for r in rows]).astype(np.int32), np.concatenate([r[1] for r in rows]).astype(np.float32)
+
+
+@pytest.mark.parametrize("rows,cols,dim,n,radius", [(30, 32, 1500, 700, 9.0), (17, 61, 2051, 333, 14.0), (40, 40, 4096, 129, 11.0), (9, 9, 1027, 65, 4.0)])
+@pytest.mark.parametrize("registered", [False, True])
+def test_epochs_on_the_coordinates(oracle, rows, cols, dim, n, radius, registered):
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8800 + dim)
+    csr = _edge_rows(sparse_zipf_csr(n, dim, 88, mean_len=40.0, max_len=200), dim)
+    W = _smooth_book(rng, rows, cols, dim, radius, csr)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    som.set_sparse_dense_filter(False)         # (short rows of a registered set would go through its planes)
+    dev = P.csr_to_dev(csr)
+    if registered:
+        capi.som_set_data_csr(som.ctx, *dev)
+    for _ in range(2):
+        mism = P.epoch_parity_csr(oracle, som, csr, dev, dim, radius, P.MAP["planar"], P.GRID["square"])
+        assert som.two_level_stats()[0] > 0, "the coordinates were not used"
+        assert mism == 0
+    P.epoch_parity_csr(oracle, som, csr, dev, dim, 1.5, P.MAP["planar"], P.GRID["square"])       # narrow: not tried
+    assert som.two_level_stats() == (0, 0)
+    som.close()
+
+
+@pytest.mark.parametrize("book", ["random", "nan", "inf", "constant"])
+def test_code_books_it_is_not_for(oracle, book):
+    """Full rank, non-finite, and equal rows: the same nodes as a search that does not try the coordinates."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8900)
+    rows, cols, dim, n = 25, 40, 1300, 300
+    csr = sparse_zipf_csr(n, dim, 89, mean_len=30.0, max_len=100)
+    W = rng.random((rows * cols, dim)).astype(np.float32) * np.float32(0.01)
+    if book == "constant":
+        W[:] = W[:1]
+    elif book != "random":
+        W = _smooth_book(rng, rows, cols, dim, 11.0, csr)
+        W[77, 5] = np.nan if book == "nan" else np.inf
+    dev = P.csr_to_dev(csr)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    want = som.bmus(dev).cpu().numpy()
+    got = som.train_epoch(dev, 11.0).cpu().numpy()
+    if book == "random":
+        assert som.two_level_stats()[0] == 0
+    som.close()
+    assert np.array_equal(got, want)
+    if book == "constant":
+        assert np.all(got == 0)
+
+
+def test_ties_and_near_copies(oracle):
+    """Copies of smooth nodes elsewhere on the map (the lowest index wins), rows that coincide with a node's weights."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9000)
+    rows, cols, dim, n = 32, 32, 1100, 400
+    csr = sparse_zipf_csr(n, dim, 90, mean_len=40.0, max_len=200)
+    W = _smooth_book(rng, rows, cols, dim, 12.0, csr)
+    W[700:1000] = W[100:400]
+    dev = P.csr_to_dev(csr)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    b = som.train_epoch(dev, 12.0).cpu().numpy()
+    assert som.two_level_stats()[0] > 0
+    som.close()
+    P.check_bmus_csr(oracle, csr, dim, W, b)
+    assert np.all((b < 700) | (b >= 1000))
+
+
+def test_recorded_epochs(oracle):
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9100)
+    rows, cols, dim, n = 30, 35, 1200, 500
+    csr = sparse_zipf_csr(n, dim, 91, mean_len=40.0, max_len=200)
+    books = [_smooth_book(rng, rows, cols, dim, 11.0, csr), (rng.random((rows * cols, dim)) * 0.01).astype(np.float32)]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        dev = P.csr_to_dev(csr)
+        som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(books[0]), filter="two_level")
+        start = P.to_dev(books[0])
+        b = torch.empty(n, dtype=torch.int32, device="cuda")
+
+        def epoch():
+            som.codebook.copy_(start)
+            som.train_epoch(dev, 11.0, bmus=b)
+
+        epoch()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            epoch()
+        for W in books + books:
+            start.copy_(P.to_dev(W))
+            epoch()
+            eager = b.cpu().numpy()
+            P.check_bmus_csr(oracle, csr, dim, W, eager)
+            b.fill_(-1)
+            graph.replay()
+            assert np.array_equal(b.cpu().numpy(), eager)
+        stream.synchronize()
+        som.close()
