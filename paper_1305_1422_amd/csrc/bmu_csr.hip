@@ -112,12 +112,16 @@ __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__res
 #pragma unroll
       for (int e = 0; e < 4; ++e) xc[jh][e] = xn[jh][e];
     if (c0 + kCtCols < c_end) load_tile(c0 + kCtCols, xn);
-    float m[4], inv[4];
+    // the quotient by the step as a product with its reciprocal: within 0.504 steps (the margin takes 0.51); steps too small
+    // for a reciprocal are scaled first
+    float m[4], inv[4], scale[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool on = c + e < c_end;
       m[e] = on ? mu[c + e] : 0.f;
-      inv[e] = on ? qstep[c + e] : 1.f;
+      const float step = on ? qstep[c + e] : 1.f;
+      scale[e] = step < 1e-30f ? 0x1p100f : 1.f;
+      inv[e] = 1.f / (step * scale[e]);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__res
             sm[2 * j + h] += (double)m[e] * (double)t;
             sw[2 * j + h] += (double)x[e] * (double)x[e];
           }
-          float q = rintf(t / inv[e]);
+          float q = rintf(t * scale[e] * inv[e]);
           q = fminf(fmaxf(q, -32767.f), 32767.f);
           word[e] |= ((uint32_t)(uint16_t)(int16_t)q) << (16 * h);
         }
@@ -174,23 +178,30 @@ __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__res
   }
 }
 
+// 32 nodes per workgroup, eight threads a node: thread q adds the slabs q, q + 8, ... and the eight sums are added in order, the same for every node.
 __global__ __launch_bounds__(256) void k_finish_node_constants(const double *__restrict__ partial, int slabs, int k,
                                                                float *__restrict__ cn, double *__restrict__ wn64,
                                                                unsigned *__restrict__ max_bits,
                                                                const SubspaceState *__restrict__ off) {
   if (off && off->use) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  float vmax = 0.f;
-  if (i < k) {
-    double s2 = 0.0, sm = 0.0, sw = 0.0;
-    for (int s = 0; s < slabs; ++s) {
+  const int i = blockIdx.x * 32 + (threadIdx.x >> 3), q = threadIdx.x & 7;
+  double s2 = 0.0, sm = 0.0, sw = 0.0;
+  if (i < k)
+    for (int s = q; s < slabs; s += 8) {
       const double *p = partial + ((int64_t)s * k + i) * 3;
       s2 += p[0]; sm += p[1]; sw += p[2];
     }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    s2 += __shfl_xor(s2, o, 64);
+    sm += __shfl_xor(sm, o, 64);
+    sw += __shfl_xor(sw, o, 64);
+  }
+  if (i < k && q == 0) {
     cn[i] = (float)(s2 + 2.0 * sm);
     wn64[i] = sw;
-    vmax = (float)s2;
   }
+  float vmax = i < k ? (float)s2 : 0.f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
   if ((threadIdx.x & 63) == 0 && vmax > 0.f) atomicMax(max_bits, __float_as_uint(vmax));
@@ -487,7 +498,7 @@ hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const Su
   slabs = (c->dim + cols_per_slab - 1) / cols_per_slab;
   hipLaunchKernelGGL(k_center_transpose_q16, dim3((unsigned)tiles, (unsigned)slabs), dim3(256), 0, c->stream, W, c->mu,
                      c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial, off);
-  hipLaunchKernelGGL(k_finish_node_constants, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->ct_partial, slabs,
+  hipLaunchKernelGGL(k_finish_node_constants, dim3((c->k + 31) / 32), dim3(256), 0, c->stream, c->ct_partial, slabs,
                      c->k, c->wn32, c->wn64, c->wmax_bits, off);
   return hipGetLastError();
 }

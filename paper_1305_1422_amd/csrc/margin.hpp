@@ -48,7 +48,7 @@ __device__ __forceinline__ double score_margin(MarginModel mm, int64_t j, double
     const double len = (double)(mm.indptr[j + 1] - mm.indptr[j]);
     coef = 2.0 * (len < 1.0 ? 1.0 : len) + 6.0;     // + 2: the product of value and column step is rounded
     // a quantised entry is within 0.51 steps of w' (0.5 from rounding, the rest from the fp32
-    // division), so the dot product moves by at most 0.51 sum |v_c| step_c (the sum itself carries
+    // quotient), so the dot product moves by at most 0.51 sum |v_c| step_c (the sum itself carries
     // fp32 rounding: 1e-5 relative is ample), the score by twice that
     if (mm.row_q) absolute = 2.0 * 0.51 * (1.0 + 1e-5) * (double)mm.row_q[j];
   }

@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kColBlock) void k_sample_col_sums(const float *__re
                                                         float *__restrict__ range) {
   const int c = blockIdx.x * kColBlock + threadIdx.x;
   if (c >= dim) return;
-  const int64_t per = (nsample + kMeanSlabs - 1) / kMeanSlabs;
+  const int64_t per = (nsample + gridDim.y - 1) / gridDim.y;
   const int64_t t0 = blockIdx.y * per;
   const int64_t t1 = t0 + per < nsample ? t0 + per : nsample;
   double s = 0.0;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kColBlock) void k_sample_col_sums(const float *__re
   partial[(int64_t)blockIdx.y * dim + c] = s;
   if (range) {
     range[(int64_t)blockIdx.y * dim + c] = lo;
-    range[((int64_t)kMeanSlabs + blockIdx.y) * dim + c] = hi;
+    range[((int64_t)gridDim.y + blockIdx.y) * dim + c] = hi;
   }
 }
 
@@ -229,23 +229,39 @@ __global__ __launch_bounds__(kColBlock) void k_sample_col_sums(const float *__re
 // every column of the centred matrix: step_c = max_i |a_ic - mu_c| / 32767 with a little slack, so
 // that a_ic - mu_c, rounded to fp32, divided by the step and rounded to an integer fits an int16;
 // and the largest step (atomic maximum on the bit pattern).
-__global__ __launch_bounds__(64) void k_finish_col_means(const double *__restrict__ partial, int64_t nsample,
-                                                         int dim, float *__restrict__ mu,
-                                                         const float *__restrict__ range, float *__restrict__ qstep,
-                                                         unsigned *__restrict__ qstep_max_bits) {
-  const int c = blockIdx.x * 64 + threadIdx.x;
+// 64 columns per workgroup, four threads each: thread q of a column adds the slabs q, q + 4, ..., and the four sums are added in order.
+__global__ __launch_bounds__(256) void k_finish_col_means(const double *__restrict__ partial, int slabs, int64_t nsample,
+                                                          int dim, float *__restrict__ mu,
+                                                          const float *__restrict__ range, float *__restrict__ qstep,
+                                                          unsigned *__restrict__ qstep_max_bits) {
+  __shared__ double s_sum[4][64];
+  __shared__ float s_lo[4][64], s_hi[4][64];
+  const int l = threadIdx.x & 63, q = threadIdx.x >> 6, c = blockIdx.x * 64 + l;
+  double s = 0.0;
+  float lo = INFINITY, hi = -INFINITY;
+  if (c < dim) {
+#pragma unroll 4
+    for (int b = q; b < slabs; b += 4) s += partial[(int64_t)b * dim + c];
+    if (range) {
+#pragma unroll 4
+      for (int b = q; b < slabs; b += 4) {
+        lo = fminf(lo, range[(int64_t)b * dim + c]);
+        hi = fmaxf(hi, range[((int64_t)slabs + b) * dim + c]);
+      }
+    }
+  }
+  s_sum[q][l] = s;
+  s_lo[q][l] = lo;
+  s_hi[q][l] = hi;
+  __syncthreads();
+  if (q) return;
   float step = 0.f;
   if (c < dim) {
-    double s = 0.0;
-    for (int b = 0; b < kMeanSlabs; ++b) s += partial[(int64_t)b * dim + c];
-    const float m = (float)(s / (double)nsample);
+    const float m = (float)((((s_sum[0][l] + s_sum[1][l]) + s_sum[2][l]) + s_sum[3][l]) / (double)nsample);
     mu[c] = m;
     if (range) {
-      float lo = INFINITY, hi = -INFINITY;
-      for (int b = 0; b < kMeanSlabs; ++b) {
-        lo = fminf(lo, range[(int64_t)b * dim + c]);
-        hi = fmaxf(hi, range[((int64_t)kMeanSlabs + b) * dim + c]);
-      }
+      lo = fminf(fminf(s_lo[0][l], s_lo[1][l]), fminf(s_lo[2][l], s_lo[3][l]));
+      hi = fmaxf(fmaxf(s_hi[0][l], s_hi[1][l]), fmaxf(s_hi[2][l], s_hi[3][l]));
       const double amax = fmax((double)hi - (double)m, (double)m - (double)lo);
       step = amax > 0.0 && amax < 1e300 ? (float)(amax * (1.0 + 1e-6) / 32767.0) : 0.f;
       if (!(step > 0.f)) step = 1e-30f;          // constant column (or no rows): every quotient is 0, and the
@@ -288,7 +304,7 @@ hipError_t launch_sample_col_means(som_ctx *c, const float *A, int64_t nrows, in
   const int64_t stride = nrows / nsample;
   hipLaunchKernelGGL(k_sample_col_sums, dim3((dim + kColBlock - 1) / kColBlock, kMeanSlabs), dim3(kColBlock), 0, c->stream, A, nsample,
                      stride, dim, c->mu_partial, (float *)nullptr);
-  hipLaunchKernelGGL(k_finish_col_means, dim3((dim + 63) / 64), dim3(64), 0, c->stream, c->mu_partial, nsample,
+  hipLaunchKernelGGL(k_finish_col_means, dim3((dim + 63) / 64), dim3(256), 0, c->stream, c->mu_partial, kMeanSlabs, nsample,
                      dim, mu, (const float *)nullptr, (float *)nullptr, (unsigned *)nullptr);
   return hipGetLastError();
 }
@@ -296,9 +312,13 @@ hipError_t launch_sample_col_means(som_ctx *c, const float *A, int64_t nrows, in
 // Means of ALL rows of the code book (at most kMeanSlabs * kMeanRowsPerSlab of them) plus the
 // quantisation steps of its centred columns: c->mu, c->qstep, c->qstep_max_bits.
 hipError_t launch_codebook_means_and_steps(som_ctx *c, const float *W) {
-  hipLaunchKernelGGL(k_sample_col_sums, dim3((c->dim + kColBlock - 1) / kColBlock, kMeanSlabs), dim3(kColBlock), 0, c->stream, W,
+  // twelve workgroups per CU keep the memory busy; every slab more is three words per column written and read again
+  const int cblocks = (c->dim + kColBlock - 1) / kColBlock;
+  int slabs = (12 * c->n_cu + cblocks - 1) / cblocks;
+  slabs = slabs < 8 ? 8 : slabs > kMeanSlabs ? kMeanSlabs : slabs;
+  hipLaunchKernelGGL(k_sample_col_sums, dim3((unsigned)cblocks, (unsigned)slabs), dim3(kColBlock), 0, c->stream, W,
                      (int64_t)c->k, (int64_t)1, c->dim, c->mu_partial, c->col_range);
-  hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(64), 0, c->stream, c->mu_partial,
+  hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(256), 0, c->stream, c->mu_partial, slabs,
                      (int64_t)c->k, c->dim, c->mu, c->col_range, c->qstep, c->qstep_max_bits);
   return hipGetLastError();
 }
@@ -334,20 +354,13 @@ __global__ __launch_bounds__(kColBlock) void k_col_sums_and_sketch(const float *
   for (; i < k; i += kSketchBuckets) add(i, A[(int64_t)i * dim + c]);
   partial[(int64_t)b * dim + c] = s;
   range[(int64_t)b * dim + c] = lo;
-  range[((int64_t)kMeanSlabs + b) * dim + c] = hi;
+  range[((int64_t)kSketchBuckets + b) * dim + c] = hi;
   raw[(int64_t)row * dimp + c] = (float)d;
   if (blockIdx.x == 0 && threadIdx.x == 0) sign_sums[row] = (float)signs;
 }
 
-// Slabs behind the buckets: empty.  Then, once the means are known, the sketch of the centred nodes: its rows less sign sum x mean, the
-// three rows in between and the columns behind the last are zero.
-__global__ __launch_bounds__(256) void k_empty_slabs(int dim, double *__restrict__ partial, float *__restrict__ range) {
-  const int c = blockIdx.x * 256 + threadIdx.x, b = kSketchBuckets + blockIdx.y;
-  if (c >= dim) return;
-  partial[(int64_t)b * dim + c] = 0.0;
-  range[(int64_t)b * dim + c] = INFINITY;
-  range[((int64_t)kMeanSlabs + b) * dim + c] = -INFINITY;
-}
+// The sketch of the centred nodes, once the means are known: its rows less sign sum x mean; the three rows in between and the
+// columns behind the last are zero.
 __global__ __launch_bounds__(256) void k_center_sketch(float *__restrict__ S, int dim, int dimp, const float *__restrict__ mu,
                                                        const float *__restrict__ sign_sums) {
   const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
@@ -361,9 +374,7 @@ hipError_t launch_codebook_means_steps_and_sketch(som_ctx *c, const float *W) {
   const int dimp = (c->dim + 63) / 64 * 64;
   hipLaunchKernelGGL(k_col_sums_and_sketch, dim3((c->dim + kColBlock - 1) / kColBlock, kSketchBuckets), dim3(kColBlock), 0, c->stream,
                      W, c->k, c->dim, dimp, c->mu_partial, c->col_range, c->sub_S, c->sub_part);
-  hipLaunchKernelGGL(k_empty_slabs, dim3((c->dim + 255) / 256, kMeanSlabs - kSketchBuckets), dim3(256), 0, c->stream, c->dim,
-                     c->mu_partial, c->col_range);
-  hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(64), 0, c->stream, c->mu_partial,
+  hipLaunchKernelGGL(k_finish_col_means, dim3((c->dim + 63) / 64), dim3(256), 0, c->stream, c->mu_partial, kSketchBuckets,
                      (int64_t)c->k, c->dim, c->mu, c->col_range, c->qstep, c->qstep_max_bits);
   hipLaunchKernelGGL(k_center_sketch, dim3((dimp + 255) / 256, kSub), dim3(256), 0, c->stream, c->sub_S, c->dim, dimp, c->mu, c->sub_part);
   return hipGetLastError();
