@@ -14,7 +14,7 @@
 // No floating-point atomics: the result is bit-reproducible.  Sparse data uses the same sort and
 // chunking, with a column tile in LDS per chunk and atomic adds (k_accumulate_csr below): the order of
 // the additions is not fixed there, so two sparse runs agree to rounding only.
-#include "som_internal.hpp"
+#include "epoch_tables.hpp"
 
 namespace som {
 
@@ -469,12 +469,18 @@ constexpr int kGatherMax = 8192;          // instances (their ids fit 16 bits of
 
 __global__ __launch_bounds__(kGatherThreads) void k_gather_sums(const float *__restrict__ X, const int32_t *__restrict__ bmus,
                                                                 int n, int k, int dim, int col_lanes,
-                                                                int32_t *__restrict__ counts, float *__restrict__ S) {
+                                                                int32_t *__restrict__ counts, float *__restrict__ S,
+                                                                EpochTables tables, EpochSchedule schedule) {
   constexpr int kWaves = kGatherThreads / 64, kPer = kGatherMax / kGatherThreads;
   __shared__ uint16_t s_list[kGatherMax];
   __shared__ int s_cnt[kWaves];
   __shared__ double s_part[kGatherThreads];
   const int b = blockIdx.x;
+  if (b >= k) {                               // what the smoothing needs of the epoch's radius (params null: it is there)
+    if (blockIdx.y == 0 && tables.params)
+      write_epoch_tables(tables, schedule, (int64_t)(b - k) * kGatherThreads + threadIdx.x, (int64_t)(gridDim.x - k) * kGatherThreads);
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // wavefront w looks through the w-th stretch of the list, 64 instances at a time; all its loads are in flight at once
   const int steps = (n + kGatherThreads - 1) / kGatherThreads;
@@ -535,7 +541,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_sums(const float *__r
 
 // The nodes' looking through the list (8e6 comparisons take about as long as a launch) and the worst case, all rows
 // on one node (2^18 values: 20 us), draw the line.
-static bool gather_pays(const som_ctx *c, int64_t n) {
+bool gather_pays(const som_ctx *c, int64_t n) {
   return n <= kGatherMax && n * (int64_t)c->k * ((c->dim + 255) / 256) <= 8000000 && n * (int64_t)c->dim <= 262144;
 }
 
@@ -886,12 +892,18 @@ hipError_t launch_scan_exclusive_i32(som_ctx *c, const int32_t *in, int32_t *out
   return hipGetLastError();
 }
 
-hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus) {
+// tables: where the epoch is in its schedule, if its tables are still to be written (then gather_pays(c, n) holds).
+hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus, const EpochSchedule *tables) {
   if (gather_pays(c, n)) {
     int col_lanes = 16;
     while (col_lanes < c->dim && col_lanes < 256) col_lanes *= 2;
-    hipLaunchKernelGGL(k_gather_sums, dim3(c->k, (c->dim + col_lanes - 1) / col_lanes), dim3(kGatherThreads), 0, c->stream, X,
-                       bmus, (int)n, c->k, c->dim, col_lanes, c->counts, c->S);
+    EpochTables t{};
+    int64_t work = 0;
+    if (tables) t = epoch_tables(c, false, &work);
+    const int64_t more = (work + kGatherThreads - 1) / kGatherThreads;
+    const int blocks = c->k + (int)(more < 4 * c->n_cu ? more : 4 * c->n_cu);
+    hipLaunchKernelGGL(k_gather_sums, dim3(blocks, (c->dim + col_lanes - 1) / col_lanes), dim3(kGatherThreads), 0, c->stream, X,
+                       bmus, (int)n, c->k, c->dim, col_lanes, c->counts, c->S, t, tables ? *tables : EpochSchedule{});
     return hipGetLastError();
   }
   const hipError_t e = launch_group_by_bmu(c, bmus, n, kChunkRows);

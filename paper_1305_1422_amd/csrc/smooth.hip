@@ -18,9 +18,7 @@
 //
 // Cooling and the two factor tables are evaluated by a one-workgroup kernel, so a whole
 // training schedule can be enqueued without the host computing anything per epoch.
-#include "som_internal.hpp"
-
-#include <math.h>
+#include "epoch_tables.hpp"
 
 namespace som {
 
@@ -37,103 +35,10 @@ __global__ __launch_bounds__(256) void k_cool_schedule(int n_epochs, double r0, 
   }
 }
 
-// twice the embedded column distance between destination column xi (row parity pi) and source
-// column xb (row parity pb)
-__device__ __forceinline__ int col_offset2(int xi, int xb, int pi, int pb, int hex, int toroid, int cols) {
-  int m = 2 * (xi - xb) + (hex ? pi - pb : 0);
-  m = m < 0 ? -m : m;
-  if (toroid && 2 * cols - m < m) m = 2 * cols - m;
-  return m;
-}
-
-__device__ __forceinline__ int row_offset(int yi, int yb, int toroid, int rows) {
-  int a = yi > yb ? yi - yb : yb - yi;
-  if (toroid && rows - a < a) a = rows - a;
-  return a;
-}
-
 // ---------------------------------------------------------------- everything an epoch prepares from its radius alone
-// One launch at the head of an epoch: the cooled radius, the two Gaussian factor tables, the coefficient matrices of
-// the smoothing passes (or the weight table of a neighbourhood with compact support; see below for their layouts), and
-// the counters that the search of this epoch starts from.  (It was four launches of 2 to 5 us with next to no work.)
-struct EpochTables {
-  EpochParams *params;
-  float *gx, *gy;             // [2 cols + 1], [rows]
-  float *GxT, *GyT;           // or null
-  int xi_pad, e_pad;
-  float *H2;                  // or null
-  int rows, cols, hex, toroid, function, compact;
-  unsigned *zero;             // words to clear, or null
-  int zero_words;
-};
-
-constexpr int kSmoothTile = 16;
-
-__device__ __forceinline__ int direct_table_width(int cols, int toroid) {
-  return (toroid ? cols : 2 * cols - 1) + kSmoothTile;
-}
-
-__global__ __launch_bounds__(256) void k_epoch_tables(EpochTables t, int epoch, int n_epochs, double r0, double rN, double s0,
-                                                      double sN, int cooling, int scale_cooling) {
-  const double radius = cooled(r0, rN, n_epochs, epoch, cooling);
-  const double inv = 1.0 / (8.0 * radius * radius);
-  const double ya = t.hex ? 3.0 : 4.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    t.params->radius = radius;
-    t.params->scale = cooled(s0, sN, n_epochs, epoch, scale_cooling);
-    t.params->inv8r2 = inv;
-  }
-  auto gx = [&](int m) { return (float)exp(-(double)m * (double)m * inv); };
-  auto gy = [&](int a) { return (float)exp(-ya * (double)a * (double)a * inv); };
-  const int rows = t.rows, cols = t.cols, par = t.hex ? 2 : 1;
-  const int64_t n_gx = 2 * (int64_t)cols + 1, n_f = n_gx + rows;
-  const int64_t n_GxT = t.GxT ? (int64_t)par * par * cols * t.xi_pad : 0, n_GyT = t.GyT ? (int64_t)par * rows * t.e_pad : 0;
-  const int width = direct_table_width(cols, t.toroid);
-  const int64_t n_H2 = t.H2 ? (int64_t)(t.hex ? 3 : 1) * rows * width : 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t o = at; o < t.zero_words; o += stride) t.zero[o] = 0u;
-  for (int64_t o = at; o < n_f; o += stride) {
-    if (o < n_gx) t.gx[o] = gx((int)o);
-    else t.gy[o - n_gx] = gy((int)(o - n_gx));
-  }
-  for (int64_t o = at; o < n_GxT + n_GyT; o += stride) {
-    if (o < n_GxT) {
-      const int xi = (int)(o % t.xi_pad);
-      const int xb = (int)((o / t.xi_pad) % cols);
-      const int ps = (int)((o / ((int64_t)t.xi_pad * cols)) % par);
-      const int img = (int)(o / ((int64_t)t.xi_pad * cols * par));
-      t.GxT[o] = xi < cols ? gx(col_offset2(xi, xb, img, ps, t.hex, t.toroid, cols)) : 0.f;
-    } else {
-      const int64_t q = o - n_GxT;
-      const int e = (int)(q % t.e_pad);
-      const int yb = (int)((q / t.e_pad) % rows);
-      const int cls = (int)(q / ((int64_t)t.e_pad * rows));
-      const int yi = par * e + cls;
-      t.GyT[q] = yi < rows ? gy(row_offset(yi, yb, t.toroid, rows)) : 0.f;
-    }
-  }
-  const double reach = 4.0 * radius * radius;     // q = 4 d^2 <= 4 r^2: inside the radius
-  for (int64_t o = at; o < n_H2; o += stride) {
-    const int c = (int)(o % width);
-    const int a_raw = (int)((o / width) % rows);
-    const int cls = (int)(o / ((int64_t)width * rows));
-    const int dpar = t.hex ? cls - 1 : 0;
-    const int dx = t.toroid ? c % cols : c - (cols - 1);
-    long long m = 2ll * dx + dpar;
-    m = m < 0 ? -m : m;
-    long long a = a_raw;
-    if (t.toroid) {
-      if (2ll * cols - m < m) m = 2ll * cols - m;
-      if (rows - a < a) a = rows - a;
-    }
-    const double q = (double)(m * m + (t.hex ? 3 : 4) * a * a);
-    const bool inside = q <= reach;
-    float h;
-    if (t.function == SOM_NEIGHBORHOOD_BUBBLE) h = inside ? 1.f : 0.f;
-    else h = (t.compact && !inside) ? 0.f : (float)exp(-q * inv);
-    t.H2[o] = h;
-  }
+// One launch at the head of an epoch.  (It was four launches of 2 to 5 us with next to no work.)
+__global__ __launch_bounds__(256) void k_epoch_tables(EpochTables t, EpochSchedule q) {
+  write_epoch_tables(t, q, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 // ---------------------------------------------------------------- count channel (fp64)
@@ -255,9 +160,11 @@ static int scale_cooling_of(const som_ctx *c, int cooling) { return c->scale_coo
 static bool direct_neighbourhood(const som_ctx *c) { return c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact; }
 static bool small_smoothing(const som_ctx *c);
 
-// `search`: a BMU search with a filter pass follows in the same call; its counters are cleared on the way.
-hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0, double sN,
-                               int cooling, bool search) {
+EpochSchedule epoch_schedule(const som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0, double sN, int cooling) {
+  return EpochSchedule{epoch, n_epochs, r0, rN, s0, sN, cooling, scale_cooling_of(c, cooling)};
+}
+
+EpochTables epoch_tables(const som_ctx *c, bool search, int64_t *most) {
   EpochTables t;
   t.params = c->params; t.gx = c->gx; t.gy = c->gy;
   const bool direct = direct_neighbourhood(c), matrices = !direct && !small_smoothing(c);
@@ -275,10 +182,16 @@ hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, d
   if (t.GxT) work += par * par * c->cols * c->xi_pad + par * c->rows * c->e_pad;
   if (t.H2) work += (int64_t)(t.hex ? 3 : 1) * c->rows * ((t.toroid ? c->cols : 2 * c->cols - 1) + kSmoothTile);
   if (t.zero_words > work) work = t.zero_words;
+  *most = work;
+  return t;
+}
+
+hipError_t launch_epoch_params(som_ctx *c, const EpochSchedule &q, bool search) {
+  int64_t work;
+  const EpochTables t = epoch_tables(c, search, &work);
   int64_t blocks = (work + 255) / 256;
   if (blocks > (int64_t)c->n_cu * 8) blocks = (int64_t)c->n_cu * 8;
-  hipLaunchKernelGGL(k_epoch_tables, dim3((unsigned)blocks), dim3(256), 0, c->stream, t, epoch, n_epochs, r0, rN, s0, sN,
-                     cooling, scale_cooling_of(c, cooling));
+  hipLaunchKernelGGL(k_epoch_tables, dim3((unsigned)blocks), dim3(256), 0, c->stream, t, q);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@
 //   for the Gaussian, one over a weight table for the others) with the division fused in.
 // The stream is synchronised only where scratch has to grow (the old buffers may still be in
 // use), by som_destroy, som_get_stats and som_profile_read.
-#include "som_internal.hpp"
+#include "epoch_tables.hpp"
 
 #include <math.h>
 #include <stdarg.h>
@@ -585,10 +585,16 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   return SOM_OK;
 }
 
-static int update_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus, float *W) {
+// Tables of an epoch: at its head, unless its search needs nothing of them and its sums are one launch, which writes them then.
+static const EpochSchedule *tables_later(som_ctx *c, int64_t n, bool filtered, const EpochSchedule &q) {
+  return !filtered && gather_pays(c, n) ? &q : nullptr;
+}
+
+// tables: the epoch whose tables are still to be written, or null.
+static int update_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus, float *W, const EpochSchedule *tables) {
   {
     StageTimer t(c, 3);
-    SOM_LAUNCH(c, launch_accumulate_dense(c, X, n, bmus));
+    SOM_LAUNCH(c, launch_accumulate_dense(c, X, n, bmus, tables));
   }
   StageTimer t(c, 4);
   SOM_LAUNCH(c, launch_smooth_and_divide(c, W));
@@ -937,8 +943,9 @@ int som_update_dense(som_ctx *c, const float *data, int64_t n, const int32_t *bm
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
   if (!rc) rc = ensure_rows(c, n, true, false);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, false));
-  return update_dense(c, data, n, bmus, codebook);
+  const EpochSchedule q = epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), *later = tables_later(c, n, false, q);
+  if (!later) SOM_LAUNCH(c, launch_epoch_params(c, q, false));
+  return update_dense(c, data, n, bmus, codebook, later);
 }
 
 int som_update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
@@ -949,7 +956,7 @@ int som_update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, co
   if (!rc) rc = check_epoch_scalars(c, radius, scale);
   if (!rc) rc = ensure_rows(c, n, false);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, false));
+  SOM_LAUNCH(c, launch_epoch_params(c, epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), false));
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
 }
 
@@ -964,10 +971,11 @@ int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codeb
   if (!rc) rc = ensure_rows(c, n, true, !direct);
   if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, !direct));
+  const EpochSchedule q = epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), *later = tables_later(c, n, !direct, q);
+  if (!later) SOM_LAUNCH(c, launch_epoch_params(c, q, !direct));
   rc = direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg, true, radius);
   if (rc) return rc;
-  return update_dense(c, data, n, bmus, codebook);
+  return update_dense(c, data, n, bmus, codebook, later);
 }
 
 int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
@@ -985,7 +993,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
     reg = true;
   }
   if (rc) return rc;
-  SOM_LAUNCH(c, launch_epoch_params(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR, true));
+  SOM_LAUNCH(c, launch_epoch_params(c, epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), true));
   rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true, radius);
   if (rc) return rc;
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
@@ -1062,11 +1070,13 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
   if (!rc && !dense && !c->csrd_on) rc = registered_hot(c);
   if (rc) return rc;
   for (int e = 0; e < n_epochs; ++e) {
-    SOM_LAUNCH(c, launch_epoch_params(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling, !direct));
+    const EpochSchedule q = epoch_schedule(c, e, n_epochs, radius0, radiusN, scale0, scaleN, cooling);
+    const EpochSchedule *later = dense ? tables_later(c, c->d_n, !direct, q) : nullptr;
+    if (!later) SOM_LAUNCH(c, launch_epoch_params(c, q, !direct));
     if (dense) {
       rc = direct ? bmu_search_direct(c, c->d_data, c->d_n, codebook, bmus)
                   : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true, cooled(radius0, radiusN, n_epochs, e, cooling));
-      if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook);
+      if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook, later);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
                           true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0 /* the first code book is the caller's */);

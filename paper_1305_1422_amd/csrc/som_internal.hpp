@@ -435,13 +435,16 @@ hipError_t launch_bmu_csr_sliced(som_ctx *c, const int64_t *indptr, const int32_
 // segsum.hip
 int64_t group_table_entries(int k, int64_t n);       // entries of c->group_table for up to n instances
 hipError_t launch_order_by_key(som_ctx *c, const int32_t *keys, int64_t n);   // -> sort_val[0]
-hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus);   // -> S, counts
+struct EpochSchedule;                                                          // epoch_tables.hpp
+EpochSchedule epoch_schedule(const som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0, double sN, int cooling);
+bool gather_pays(const som_ctx *c, int64_t n);                                 // few instances on few nodes: one launch adds them up ...
+hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus,
+                                   const EpochSchedule *tables);               // -> S, counts (... and writes the epoch's tables if asked)
 hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
                                  const float *values, int64_t n, const int32_t *bmus);   // -> S, counts
 
 // smooth.hip
-hipError_t launch_epoch_params(som_ctx *c, int epoch, int n_epochs, double r0, double rN, double s0,
-                               double sN, int cooling, bool search);
+hipError_t launch_epoch_params(som_ctx *c, const EpochSchedule &q, bool search);
 hipError_t launch_cool_schedule(som_ctx *c, int n_epochs, double r0, double rN, double s0, double sN,
                                 int cooling, double *radius_out, double *scale_out);
 hipError_t launch_smooth_and_divide(som_ctx *c, float *W);
