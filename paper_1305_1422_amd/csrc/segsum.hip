@@ -172,7 +172,7 @@ __global__ __launch_bounds__(64) void k_radix_scatter(const int32_t *__restrict_
 // prefixes over the wavefronts.  Up to 2,048 keys per wavefront of one workgroup the rest is done there too
 // (k_group_one); beyond, a workgroup counts one tile of the keys (k_group_tiles), the tables are
 // summed over the tiles and scanned within blocks of 64 nodes (k_group_prefix), and k_group_place puts the ids in place.  Measured, everything up to the chunk table (us):
-// 20,011 keys, 2,700 nodes 37 -> 20; 100,000 keys, 2,500 nodes 71 -> 24; 1,000,000 keys, 10,000 nodes 144 -> 71.
+// 20,011 keys, 2,700 nodes 37 -> 15; 100,000 keys, 2,500 nodes 71 -> 17; 1,000,000 keys, 10,000 nodes 144 -> 46.
 constexpr size_t kGroupLds = 160 * 1024 - 1024;      // the rest is for the scan's own words
 constexpr int kGroupKeysMax = 2048;                  // keys per wavefront, at most
 constexpr int kGroupOneKeys = 16384;                 // keys that one workgroup sorts faster than three launches do
@@ -214,9 +214,9 @@ __device__ __forceinline__ void group_rank_wave(const int32_t *__restrict__ keys
 }
 
 // Exclusive scans over the nodes of their counts and of their chunk counts by a workgroup of kThreads, into LDS (seg,
-// chk: k + 1 entries each).  count(b) must be readable by every thread.
-template <int kThreads, typename Count>
-__device__ __forceinline__ void group_scan(Count count, int k, int chunk_rows, int *seg, int *chk, int (*s_wave)[2]) {
+// chk: k + 1 entries each).  count(b) and chunks_of(b, count(b)) must be readable by every thread.
+template <int kThreads, typename Count, typename Chunks>
+__device__ __forceinline__ void group_scan(Count count, Chunks chunks_of, int k, int *seg, int *chk, int (*s_wave)[2]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (k + kThreads - 1) / kThreads;
   const int b0 = min(tid * per, k), b1 = min(b0 + per, k);
@@ -224,7 +224,7 @@ __device__ __forceinline__ void group_scan(Count count, int k, int chunk_rows, i
   for (int b = b0; b < b1; ++b) {
     const int v = count(b);
     sum += v;
-    chunks += (v + chunk_rows - 1) / chunk_rows;
+    chunks += chunks_of(b, v);
   }
   int inc = sum, cinc = chunks;
 #pragma unroll
@@ -241,7 +241,7 @@ __device__ __forceinline__ void group_scan(Count count, int k, int chunk_rows, i
     seg[b] = run;
     chk[b] = crun;
     run += v;
-    crun += (v + chunk_rows - 1) / chunk_rows;
+    crun += chunks_of(b, v);
   }
   if (tid == kThreads - 1) { seg[k] = run; chk[k] = crun; }
   __syncthreads();
@@ -282,17 +282,18 @@ __global__ __launch_bounds__(64 * kWaves) void k_group_one(const int32_t *__rest
   group_rank_wave(keys, lo, hi, k, bits, cnt + wave * k2, rank, lane);
   __syncthreads();
   for (int b = tid; b < k; b += kThreads) {
-    int run = 0;
+    int t[kWaves], run = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t[w] = cnt[w * k2 + b];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const int t = cnt[w * k2 + b];
       cnt[w * k2 + b] = (uint16_t)run;
-      run += t;
+      run += t[w];
     }
     counts[b] = run;
   }
   __syncthreads();                                    // (also makes counts visible to the workgroup)
-  group_scan<kThreads>([&](int b) { return counts[b]; }, k, chunk_rows, seg, chk, s_wave);
+  group_scan<kThreads>([&](int b) { return counts[b]; }, [&](int, int v) { return (v + chunk_rows - 1) / chunk_rows; }, k, seg, chk, s_wave);
   for (int b = tid; b <= k; b += kThreads) { seg_off[b] = seg[b]; chunk_off[b] = chk[b]; }
   for (int b0 = 64 * wave; b0 < k; b0 += kThreads) {
     const int b = b0 + lane;
@@ -305,10 +306,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_group_one(const int32_t *__rest
 }
 
 // table[tile][node] = keys of the tile, rank[j] = position of key j among the equal ones of its tile.  kWaves of the
-// wavefronts rank; all of them clear and sum the counters.
+// wavefronts rank; all of them clear and sum the counters.  Few workgroups at work, so the chain of one is what it takes: where a wavefront has
+// four steps of keys only (kSteps 4; 0: any number) it keeps them and their ranks in registers from the first
+// load to the last store, and a node's counters are read together before they are written (100,000 keys on 2,500 nodes 10.4 -> 9.0 us).
 constexpr int kTileThreads = 1024;
 
-template <int kWaves>
+template <int kWaves, int kSteps>
 __global__ __launch_bounds__(kTileThreads) void k_group_tiles(const int32_t *__restrict__ keys, int64_t n, int k, int bits,
                                                               int keys_per_wave, int32_t *__restrict__ table,
                                                               int32_t *__restrict__ rank) {
@@ -317,24 +320,52 @@ __global__ __launch_bounds__(kTileThreads) void k_group_tiles(const int32_t *__r
   uint16_t *cnt = reinterpret_cast<uint16_t *>(s_dyn);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int i = tid; i < kWaves * k2 / 2; i += kTileThreads) reinterpret_cast<uint32_t *>(cnt)[i] = 0u;
-  __syncthreads();
   const int64_t tile0 = (int64_t)blockIdx.x * kWaves * keys_per_wave;
   const int64_t tile1 = tile0 + kWaves * keys_per_wave < n ? tile0 + kWaves * keys_per_wave : n;
-  if (wave < kWaves) {
-    const int64_t lo = tile0 + wave * keys_per_wave;
-    if (lo < n) group_rank_wave(keys, lo, lo + keys_per_wave < n ? lo + keys_per_wave : n, k, bits, cnt + wave * k2, rank, lane);
+  const int64_t lo = tile0 + wave * keys_per_wave;
+  int key[kSteps ? kSteps : 1], pos[kSteps ? kSteps : 1];
+  if (kSteps && wave < kWaves) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) key[s] = lo + 64 * s + lane < n ? clamp_node(keys[lo + 64 * s + lane], k) : -1;
+  }
+  for (int i = tid; i < kWaves * k2 / 2; i += kTileThreads) reinterpret_cast<uint32_t *>(cnt)[i] = 0u;
+  __syncthreads();
+  if (wave < kWaves && lo < n) {
+    if (kSteps) {
+      volatile uint16_t *own = cnt + wave * k2;
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        const bool valid = key[s] >= 0;
+        const unsigned long long same = same_key_lanes(valid ? key[s] : 0, valid, bits);
+        const int earlier = __popcll(same & ((1ull << lane) - 1ull));
+        const int before = valid ? own[key[s]] : 0;
+        if (valid && earlier == 0) own[key[s]] = (uint16_t)(before + __popcll(same));
+        pos[s] = before + earlier;
+      }
+    } else {
+      group_rank_wave(keys, lo, lo + keys_per_wave < n ? lo + keys_per_wave : n, k, bits, cnt + wave * k2, rank, lane);
+    }
   }
   __syncthreads();
   for (int b = tid; b < k; b += kTileThreads) {
-    int run = 0;
+    int t[kWaves], run = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t[w] = cnt[w * k2 + b];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const int t = cnt[w * k2 + b];
       cnt[w * k2 + b] = (uint16_t)run;
-      run += t;
+      run += t[w];
     }
     table[(int64_t)blockIdx.x * k + b] = run;
+  }
+  if (kSteps) {
+    if (kWaves > 1) __syncthreads();
+    if (wave < kWaves) {
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s)
+        if (key[s] >= 0) rank[lo + 64 * s + lane] = pos[s] + (kWaves > 1 ? cnt[wave * k2 + key[s]] : 0);
+    }
+    return;
   }
   if (kWaves == 1) return;
   __syncthreads();
@@ -343,16 +374,18 @@ __global__ __launch_bounds__(kTileThreads) void k_group_tiles(const int32_t *__r
 }
 
 // Exclusive prefixes of the table over the tiles, in place, and the totals; besides, the exclusive scans of the totals
-// and of the chunk counts within the workgroup's 64 nodes (local [2][k]) and their sums (sums [2][blocks]).  The four
-// wavefronts of a workgroup share the tiles.
-__global__ __launch_bounds__(256) void k_group_prefix(int32_t *__restrict__ table, int tiles, int k, int chunk_rows,
+// and of the chunk counts within the workgroup's 64 nodes (local [2][k]) and their sums (sums [2][blocks]).  The
+// wavefronts of a workgroup share the tiles (244 tiles of 10,000 nodes: 15.5 us with four).
+constexpr int kPrefixWaves = 16;
+
+__global__ __launch_bounds__(64 * kPrefixWaves) void k_group_prefix(int32_t *__restrict__ table, int tiles, int k, int chunk_rows,
                                                       int32_t *__restrict__ counts, int32_t *__restrict__ local,
                                                       int32_t *__restrict__ sums) {
-  __shared__ int s_sum[4][64];
+  __shared__ int s_sum[kPrefixWaves][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.x * 64 + lane;
   const bool live = b < k;
-  const int per = (tiles + 3) / 4;
+  const int per = (tiles + kPrefixWaves - 1) / kPrefixWaves;
   const int t0 = min(wave * per, tiles), t1 = min(t0 + per, tiles);
   int32_t *col = table + (live ? b : 0);
   int sum = 0;
@@ -362,7 +395,7 @@ __global__ __launch_bounds__(256) void k_group_prefix(int32_t *__restrict__ tabl
   __syncthreads();
   int run = 0;
   for (int w = 0; w < wave; ++w) run += s_sum[w][lane];
-  if (wave == 3) {
+  if (wave == kPrefixWaves - 1) {
     const int total = live ? run + sum : 0, chunks = (total + chunk_rows - 1) / chunk_rows;
     int inc = total, cinc = chunks;
 #pragma unroll
@@ -397,9 +430,7 @@ __global__ __launch_bounds__(1024) void k_group_place(const int32_t *__restrict_
   __shared__ int s_wave[16][2];
   __shared__ int s_seg[kGroupMaxBlocks + 1], s_chk[kGroupMaxBlocks + 1];
   const int blocks = (k + 63) / 64;
-  group_scan<1024>([&](int b) { return sums[b]; }, blocks, 1, s_seg, s_chk, s_wave);
-  __syncthreads();
-  group_scan<1024>([&](int b) { return sums[blocks + b]; }, blocks, 1, s_chk, s_chk, s_wave);
+  group_scan<1024>([&](int b) { return sums[b]; }, [&](int b, int) { return sums[blocks + b]; }, blocks, s_seg, s_chk, s_wave);
   const int64_t at = (int64_t)blockIdx.x * 1024 + threadIdx.x, stride = (int64_t)gridDim.x * 1024;
   const int lane = threadIdx.x & 63;
   for (int64_t b0 = at - lane; b0 < k; b0 += stride) {
@@ -427,12 +458,22 @@ static int group_waves(int k, int extra) {
   return 0;
 }
 
-// Keys per wavefront of the tiled form: workgroups enough to spread over the chip, as long as the table stays at some
-// hundred thousand entries per pass.
+// Keys per wavefront of the tiled form: workgroups enough to spread over the chip, as long as the table that they write and the next launch adds up stays
+// at a few million entries (1,000,000 keys on 10,000 nodes, limit of half a million -> 2.5: tiles 42 -> 18.5 us, prefixes 7 -> 8.2; 50,000 on
+// 40,000: 28 -> 14, 5 -> 7.4).
+constexpr int64_t kGroupTableFine = 2500000;
 static int group_keys_per_wave(int k, int64_t n, int waves) {
   int per = 256;
-  while (per < kGroupKeysMax && (n + (int64_t)per * waves - 1) / ((int64_t)per * waves) * k > 500000) per *= 2;
+  while (per < kGroupKeysMax && (n + (int64_t)per * waves - 1) / ((int64_t)per * waves) * k > kGroupTableFine) per *= 2;
   return per;
+}
+
+// Wavefronts of a tile: ranking costs some 130 vector instructions per 64 keys, so four that have a SIMD each are done sooner than sixteen, as long
+// as the tiles leave CUs idle (100,000 keys on 2,500 nodes: 9.0 -> 5.6 us, their prefixes 5.0 -> 5.6).
+static int group_tile_waves(int k, int64_t n) {
+  int w = group_waves(k, 0);
+  while (w > 4 && n <= (int64_t)w * 256 * 128 && (n + 128 * w - 1) / (128 * w) * k <= kGroupTableFine) w /= 2;
+  return w;
 }
 
 // The tiled form reads and writes its table three times, and from some 30 million entries on (128 MB: most of the
@@ -444,7 +485,7 @@ constexpr int64_t kGroupTableMax = 32 << 20;
 
 // Entries of the tiled form's table; 0: its counters do not fit LDS, or the table would be too large.
 static int64_t group_tiled_entries(int k, int64_t n) {
-  const int waves = group_waves(k, 0);
+  const int waves = group_tile_waves(k, n);
   if (!waves || k > 64 * kGroupMaxBlocks) return 0;
   const int64_t tile = (int64_t)waves * group_keys_per_wave(k, n, waves);
   const int64_t entries = (n + tile - 1) / tile * k;
@@ -453,9 +494,11 @@ static int64_t group_tiled_entries(int k, int64_t n) {
 
 int64_t group_table_entries(int k, int64_t n) {
   if (!group_waves(k, 0) || k > 64 * kGroupMaxBlocks) return 1;
-  // (a shorter list may be cut finer, but then its table has at most 500,000 entries and one more tile's; where this one
-  // is too long for the tiled form a shorter one need not be)
-  const int64_t own = group_tiled_entries(k, n), most = own > 500000 + k ? own : 500000 + k;
+  // (a shorter list may be cut finer, but then its table has no more entries than the finest cut of this one and at most
+  // kGroupTableFine; where this one is too long for the tiled form a shorter one need not be)
+  const int64_t own = group_tiled_entries(k, n), least = group_waves(k, 0) < 4 ? group_waves(k, 0) : 4;
+  const int64_t finest = (n / (256 * least) + 2) * k;
+  const int64_t fine = finest < kGroupTableFine ? finest : kGroupTableFine, most = own > fine ? own : fine;
   return own ? most : kGroupTableMax;
 }
 
@@ -831,8 +874,13 @@ static void launch_group_one(som_ctx *c, const int32_t *bmus, int64_t n, int bit
 
 template <int kWaves>
 static void launch_group_tiles(som_ctx *c, const int32_t *bmus, int64_t n, int bits, int per, unsigned tiles) {
-  hipLaunchKernelGGL(k_group_tiles<kWaves>, dim3(tiles), dim3(kTileThreads), (size_t)kWaves * ((c->k + 1) & ~1) * 2, c->stream,
-                     bmus, n, c->k, bits, per, c->group_table, c->sort_key[1]);
+  const size_t lds = (size_t)kWaves * ((c->k + 1) & ~1) * 2;
+  if (per == 256)
+    hipLaunchKernelGGL((k_group_tiles<kWaves, 4>), dim3(tiles), dim3(kTileThreads), lds, c->stream, bmus, n, c->k, bits, per,
+                       c->group_table, c->sort_key[1]);
+  else
+    hipLaunchKernelGGL((k_group_tiles<kWaves, 0>), dim3(tiles), dim3(kTileThreads), lds, c->stream, bmus, n, c->k, bits, per,
+                       c->group_table, c->sort_key[1]);
 }
 
 // Stable permutation of the instance ids by BMU (c->sort_val[0]), counts, segment offsets, chunk offsets and the
@@ -840,7 +888,7 @@ static void launch_group_tiles(som_ctx *c, const int32_t *bmus, int64_t n, int b
 static hipError_t launch_group_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n, int chunk_rows) {
   int bits = 1;
   while ((1ll << bits) < (long long)c->k) ++bits;
-  const int one = group_waves(c->k, 8), many = group_waves(c->k, 0);
+  const int one = group_waves(c->k, 8), many = group_tile_waves(c->k, n);
   if (one && n <= kGroupOneKeys && n <= (int64_t)one * kGroupKeysMax) {
     switch (one) {
       case 16: launch_group_one<16>(c, bmus, n, bits, chunk_rows); break;
@@ -864,7 +912,7 @@ static hipError_t launch_group_by_bmu(som_ctx *c, const int32_t *bmus, int64_t n
     }
     const int nodeblocks = (c->k + 63) / 64;
     int32_t *local = c->group_local, *sums = c->group_local + 2 * (size_t)c->k;
-    hipLaunchKernelGGL(k_group_prefix, dim3(nodeblocks), dim3(256), 0, c->stream, c->group_table, (int)tiles, c->k, chunk_rows,
+    hipLaunchKernelGGL(k_group_prefix, dim3(nodeblocks), dim3(64 * kPrefixWaves), 0, c->stream, c->group_table, (int)tiles, c->k, chunk_rows,
                        c->counts, local, sums);
     int64_t blocks = ((n > c->k ? n : c->k) + 1023) / 1024;
     if (blocks > 2 * (int64_t)c->n_cu) blocks = 2 * (int64_t)c->n_cu;

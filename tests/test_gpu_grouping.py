@@ -17,6 +17,9 @@ torch = pytest.importorskip("torch")
     (513, 1, 70, 33, "hexagonal", "planar"), (8192, 9, 7, 32, "hexagonal", "toroid"), (8193, 9, 7, 5, "square", "toroid"),
     (4097, 37, 29, 63, "hexagonal", "planar"), (3000, 12, 11, 300, "square", "toroid"),      # a workgroup per node
     (16384, 21, 19, 40, "square", "planar"), (16385, 21, 19, 40, "hexagonal", "toroid"),      # one workgroup, tiles
+    (65536, 30, 30, 4, "square", "planar"), (131073, 50, 50, 3, "hexagonal", "toroid"),       # tiles of four, eight wavefronts ...
+    (262145, 50, 51, 2, "square", "planar"), (524289, 50, 50, 2, "square", "toroid"),          # ... sixteen, and more keys for each
+    (250000, 100, 100, 3, "square", "planar"), (300000, 200, 201, 2, "square", "planar"),      # tables at their finest and coarser
     (40001, 70, 70, 6, "square", "toroid"), (20000, 140, 150, 5, "hexagonal", "planar"),      # fewer counters per wavefront
     (9000, 230, 231, 3, "square", "planar"), (5000, 288, 282, 3, "square", "toroid"),          # one wavefront's counters (up to 81,408 nodes)
     (825000, 285, 285, 2, "square", "planar"), (850001, 285, 285, 2, "hexagonal", "toroid"),  # the largest table; radix sort beyond
