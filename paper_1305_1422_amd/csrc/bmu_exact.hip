@@ -63,27 +63,47 @@ __global__ __launch_bounds__(256) void k_certify(CandView cand, int groups, cons
   int keep[kCand] = {0, 0, 0, 0};
   int cnt = 0;
   if (live) {
-    for (int q = 0; q < groups; ++q) {
-      const float4 v = val4[(int64_t)q * n + j];
-      const int4 id = idx4[(int64_t)q * n + j];
-      if ((unsigned)id.x < (unsigned)k) smin = fminf(smin, v.x);
-      if ((unsigned)id.y < (unsigned)k) smin = fminf(smin, v.y);
-      if ((unsigned)id.z < (unsigned)k) smin = fminf(smin, v.z);
-      if ((unsigned)id.w < (unsigned)k) smin = fminf(smin, v.w);
-      omin = fminf(omin, cand.over[(int64_t)q * n + j]);
-    }
-    const double margin = score_margin(mm, j, (double)xn32[j], (double)__uint_as_float(*wmax_bits), (double)*mu_norm2);
-    thr = (double)smin + margin;
-    for (int q = 0; q < groups; ++q) {
-      const float4 v4 = val4[(int64_t)q * n + j];
-      const int4 id4 = idx4[(int64_t)q * n + j];
-      const float v[kCand] = {v4.x, v4.y, v4.z, v4.w};
-      const int id[kCand] = {id4.x, id4.y, id4.z, id4.w};
+    // the lists of kBatch groups, and what the margin is made of, in flight together: one at a time, the chain of their
+    // latencies was the kernel (1,000,000 instances of 8 groups 106 -> 77 us, 100,000 18 -> 14.7; 12,347 of 72 groups 241 -> 172); the last list is read again where fewer are left
+    constexpr int kBatch = 4;
+    float4 v4[kBatch];
+    int4 id4[kBatch];
+    float over[kBatch];
+    auto load = [&](int q0) {
 #pragma unroll
-      for (int t = 0; t < kCand; ++t) {
-        if ((unsigned)id[t] < (unsigned)k && (double)v[t] <= thr) {
-          if (cnt < kCand) keep[cnt] = id[t];
-          ++cnt;
+      for (int u = 0; u < kBatch; ++u) {
+        const int64_t at = (int64_t)min(q0 + u, groups - 1) * n + j;
+        v4[u] = val4[at];
+        id4[u] = idx4[at];
+        over[u] = cand.over[at];
+      }
+    };
+    load(0);
+    const double margin = score_margin(mm, j, (double)xn32[j], (double)__uint_as_float(*wmax_bits), (double)*mu_norm2);
+    for (int q0 = 0; q0 < groups; q0 += kBatch) {
+      if (q0) load(q0);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        if ((unsigned)id4[u].x < (unsigned)k) smin = fminf(smin, v4[u].x);
+        if ((unsigned)id4[u].y < (unsigned)k) smin = fminf(smin, v4[u].y);
+        if ((unsigned)id4[u].z < (unsigned)k) smin = fminf(smin, v4[u].z);
+        if ((unsigned)id4[u].w < (unsigned)k) smin = fminf(smin, v4[u].w);
+        omin = fminf(omin, over[u]);
+      }
+    }
+    thr = (double)smin + margin;
+    for (int q0 = 0; q0 < groups; q0 += kBatch) {
+      if (groups > kBatch) load(q0);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const float v[kCand] = {v4[u].x, v4[u].y, v4[u].z, v4[u].w};
+        const int id[kCand] = {id4[u].x, id4[u].y, id4[u].z, id4[u].w};
+#pragma unroll
+        for (int t = 0; t < kCand; ++t) {
+          if (q0 + u < groups && (unsigned)id[t] < (unsigned)k && (double)v[t] <= thr) {
+            if (cnt < kCand) keep[cnt] = id[t];
+            ++cnt;
+          }
         }
       }
     }
