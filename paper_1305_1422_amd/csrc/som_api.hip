@@ -108,7 +108,7 @@ static bool two_level(const som_ctx *c, int64_t n) {
 // ... and its scratch is there (ensure_rows sizes it for the largest row count seen, whose table may not fit
 // when that of a smaller n would: then the one-level pass serves)
 static bool two_level_ready(const som_ctx *c, int64_t n) {
-  return two_level(c, n) && c->Xh1 != nullptr && c->Wh1 != nullptr && n <= c->n_cap;
+  return two_level(c, n) && c->Xh1 != nullptr && c->Wh1 != nullptr && c->coarse_min != nullptr && c->node_of != nullptr && n <= c->n_cap;
 }
 
 static bool subspace_ready(const som_ctx *c, int64_t n) {
@@ -196,7 +196,7 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, 
   const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) ||
                             (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
-                            (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr)) ||
+                            (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr || c->coarse_min == nullptr || c->node_of == nullptr)) ||
                             (subspace && (c->sub_Y1 == nullptr || c->sub_state == nullptr));
   if (n <= c->n_cap && !need_partial) return SOM_OK;
   if (n > c->n_cap) {
