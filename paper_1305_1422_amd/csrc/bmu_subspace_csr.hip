@@ -537,7 +537,7 @@ size_t subspace_csr_part_floats(const som_ctx *c) { return (size_t)csr_pieces(c)
 // set stays outside 64 directions at any radius, so planar maps only.  Grows with n and nnz.
 bool subspace_csr_eligible(const som_ctx *c, int64_t n, int64_t nnz) {
   const int64_t blocks = (c->k + 127) / 128;
-  if (c->map_type != SOM_MAP_PLANAR || c->dim < kSubspaceCsrDim || blocks * n * 4 > kTwoLevelMaxTable) return false;
+  if (c->map_type != SOM_MAP_PLANAR || c->dim < kSubspaceCsrDim || blocks * c->n_cap * 4 > kTwoLevelMaxTable) return false;
   if (c->filter == SOM_FILTER_TWO_LEVEL) return true;
   if (c->filter != SOM_FILTER_AUTO || blocks < kTwoLevelMinBlocks) return false;
   const double own = 0.25e-3 + 3e-12 * (double)c->k * (double)c->dim + 3e-11 * (double)nnz;

@@ -115,6 +115,35 @@ static bool subspace_ready(const som_ctx *c, int64_t n) {
   return subspace_eligible(c, n) && !c->sub_failed && c->sub_state != nullptr && c->sub_Y1 != nullptr;
 }
 
+static void free_two_level_tables(som_ctx *c) {
+  dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
+  dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
+  c->two_level_n = 0;
+}
+
+static void free_subspace(som_ctx *c) {
+  dev_free(c->sub_Y1); dev_free(c->sub_Y2); dev_free(c->sub_yscale); dev_free(c->sub_err); dev_free(c->sub_err2);
+  dev_free(c->sub_S); dev_free(c->sub_G); dev_free(c->sub_Vp); dev_free(c->sub_Vt); dev_free(c->sub_U1); dev_free(c->sub_U2); dev_free(c->sub_part);
+  dev_free(c->sub_state); dev_free(c->sub_Vf); dev_free(c->sub_cpart);
+}
+
+// No memory for the subspace: the searches run without it (until n_cap changes), and tables that only it needs go too.
+static void give_up_subspace(som_ctx *c) {
+  (void)hipGetLastError();
+  free_subspace(c);
+  if (c->Xh1 == nullptr) free_two_level_tables(c);
+  c->sub_failed = 1;
+}
+
+// What a call cannot do without goes before the subspace, also where the subspace was there first.
+template <typename T>
+static bool dev_alloc_first(som_ctx *c, T **p, size_t count) {
+  if (dev_alloc(p, count)) return true;
+  if (c->sub_state == nullptr) return false;
+  give_up_subspace(c);
+  return dev_alloc(p, count);
+}
+
 static void free_row_scratch(som_ctx *c) {
   dev_free(c->xn32); dev_free(c->row_q); dev_free(c->cand_val); dev_free(c->cand_idx); dev_free(c->cand_over);
   dev_free(c->cand_n); dev_free(c->refine_list); dev_free(c->rescan_list);
@@ -122,8 +151,8 @@ static void free_row_scratch(som_ctx *c) {
   dev_free(c->sort_key[0]); dev_free(c->sort_key[1]); dev_free(c->sort_val[0]); dev_free(c->sort_val[1]);
   dev_free(c->radix_hist); dev_free(c->group_table); dev_free(c->chunk_node); dev_free(c->partial);
   dev_free(c->Xh); dev_free(c->xscale);
-  dev_free(c->Xh1); dev_free(c->xlost); dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
-  dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
+  dev_free(c->Xh1); dev_free(c->xlost);
+  free_two_level_tables(c);
   dev_free(c->sub_Y1); dev_free(c->sub_Y2); dev_free(c->sub_yscale); dev_free(c->sub_err); dev_free(c->sub_err2);
   c->sub_failed = 0;
   c->two_level_n = 0;
@@ -134,12 +163,6 @@ static void free_row_scratch(som_ctx *c) {
   c->d_split_valid = 0;
   c->csrd_valid = 0;
   c->csrd_on = 0;
-}
-
-static void free_subspace(som_ctx *c) {
-  dev_free(c->sub_Y1); dev_free(c->sub_Y2); dev_free(c->sub_yscale); dev_free(c->sub_err); dev_free(c->sub_err2);
-  dev_free(c->sub_S); dev_free(c->sub_G); dev_free(c->sub_Vp); dev_free(c->sub_Vt); dev_free(c->sub_U1); dev_free(c->sub_U2); dev_free(c->sub_part);
-  dev_free(c->sub_state); dev_free(c->sub_Vf); dev_free(c->sub_cpart);
 }
 
 // Order of the nodes and tables of the two-level search, for n_cap instances.
@@ -156,8 +179,7 @@ static int ensure_two_level_tables(som_ctx *c) {
       !(dev_alloc(&c->coarse_key, (size_t)c->n_cap) && dev_alloc(&c->coarse_mask, (blocks + 31) / 32 * (size_t)c->n_cap) &&
         dev_alloc(&c->tile_cnt, tiles) && dev_alloc(&c->tile_list, tiles * blocks) && dev_alloc(&c->ctile_cnt, tiles) &&
         dev_alloc(&c->ctile_list, tiles * blocks) && dev_alloc(&c->coarse_min, blocks * (size_t)c->n_cap))) {
-    dev_free(c->coarse_min); dev_free(c->coarse_key); dev_free(c->coarse_mask);
-    dev_free(c->tile_cnt); dev_free(c->tile_list); dev_free(c->ctile_cnt); dev_free(c->ctile_list);
+    free_two_level_tables(c);
     return fail(c, SOM_ERR_ALLOC, "cannot allocate the two-level search's scratch for %lld instances", (long long)c->n_cap);
   }
   return SOM_OK;
@@ -179,10 +201,7 @@ static bool allocate_subspace(som_ctx *c, bool fine, bool csr) {
 }
 
 static void ensure_subspace(som_ctx *c, bool fine, bool csr) {
-  if (c->sub_failed || allocate_subspace(c, fine, csr)) return;
-  (void)hipGetLastError();
-  free_subspace(c);
-  c->sub_failed = 1;
+  if (!c->sub_failed && !allocate_subspace(c, fine, csr)) give_up_subspace(c);
 }
 
 // Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
@@ -203,14 +222,14 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, 
     (void)hipStreamSynchronize(c->stream);
     free_row_scratch(c);
     const size_t N = (size_t)n;
-    bool ok = dev_alloc(&c->xn32, N) && dev_alloc(&c->row_q, N) && dev_alloc(&c->cand_val, N * kCand) && dev_alloc(&c->cand_idx, N * kCand) &&
-              dev_alloc(&c->cand_over, N) && dev_alloc(&c->cand_n, N) && dev_alloc(&c->refine_list, N) &&
-              dev_alloc(&c->rescan_list, N) && dev_alloc(&c->collect_rows, N) && dev_alloc(&c->collect_thr, N) &&
-              dev_alloc(&c->collect_cnt, N) && dev_alloc(&c->sort_key[0], N) && dev_alloc(&c->sort_key[1], N) &&
-              dev_alloc(&c->sort_val[0], N) && dev_alloc(&c->sort_val[1], N) &&
-              dev_alloc(&c->radix_hist, radix_table_entries(n));
+    bool ok = dev_alloc_first(c, &c->xn32, N) && dev_alloc_first(c, &c->row_q, N) && dev_alloc_first(c, &c->cand_val, N * kCand) && dev_alloc_first(c, &c->cand_idx, N * kCand) &&
+              dev_alloc_first(c, &c->cand_over, N) && dev_alloc_first(c, &c->cand_n, N) && dev_alloc_first(c, &c->refine_list, N) &&
+              dev_alloc_first(c, &c->rescan_list, N) && dev_alloc_first(c, &c->collect_rows, N) && dev_alloc_first(c, &c->collect_thr, N) &&
+              dev_alloc_first(c, &c->collect_cnt, N) && dev_alloc_first(c, &c->sort_key[0], N) && dev_alloc_first(c, &c->sort_key[1], N) &&
+              dev_alloc_first(c, &c->sort_val[0], N) && dev_alloc_first(c, &c->sort_val[1], N) &&
+              dev_alloc_first(c, &c->radix_hist, radix_table_entries(n));
     c->max_chunks = (int64_t)(N / kChunkRows) + c->k;
-    ok = ok && dev_alloc(&c->chunk_node, (size_t)c->max_chunks) && dev_alloc(&c->group_table, (size_t)group_table_entries(c->k, n));
+    ok = ok && dev_alloc_first(c, &c->chunk_node, (size_t)c->max_chunks) && dev_alloc_first(c, &c->group_table, (size_t)group_table_entries(c->k, n));
     if (!ok) {
       free_row_scratch(c);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate scratch for %lld instances", (long long)n);
@@ -219,36 +238,36 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, 
     c->cand_cap = n;
   }
   if (dense && c->partial == nullptr) {
-    if (!dev_alloc(&c->partial, (size_t)c->max_chunks * c->dim))
+    if (!dev_alloc_first(c, &c->partial, (size_t)c->max_chunks * c->dim))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate %lld x %d partial sums", (long long)c->max_chunks, c->dim);
   }
   if (filtered && c->collect_list == nullptr) {
-    if (!dev_alloc(&c->collect_list, (size_t)c->n_cap * kListCap))
+    if (!dev_alloc_first(c, &c->collect_list, (size_t)c->n_cap * kListCap))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate candidate lists for %lld instances", (long long)c->n_cap);
   }
   if (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) {
-    if (!dev_alloc(&c->Wc, (size_t)c->k * c->dim))
+    if (!dev_alloc_first(c, &c->Wc, (size_t)c->k * c->dim))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the centred code book (%d x %d)", c->k, c->dim);
   }
   if (split) {
     const size_t row_halves = (size_t)((c->dim + 31) / 32) * 64;
-    if (c->Wh == nullptr && !dev_alloc(&c->Wh, (size_t)c->k * row_halves))
+    if (c->Wh == nullptr && !dev_alloc_first(c, &c->Wh, (size_t)c->k * row_halves))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 planes of the code book");
     if (c->Xh == nullptr) {
       c->d_split_valid = 0;
       c->csrd_valid = 0;
-      if (!(dev_alloc(&c->Xh, (size_t)c->n_cap * row_halves) && dev_alloc(&c->xscale, (size_t)c->n_cap)))
+      if (!(dev_alloc_first(c, &c->Xh, (size_t)c->n_cap * row_halves) && dev_alloc_first(c, &c->xscale, (size_t)c->n_cap)))
         return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 planes of %lld instances", (long long)c->n_cap);
     }
   }
   if (coarse) {
     const size_t row_halves = (size_t)((c->dim + 63) / 64) * 64;
-    if (c->Wh1 == nullptr && !dev_alloc(&c->Wh1, (size_t)c->k * row_halves))
+    if (c->Wh1 == nullptr && !dev_alloc_first(c, &c->Wh1, (size_t)c->k * row_halves))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of the code book");
     if (c->Xh1 == nullptr) {
       c->d_split_valid = 0;
       c->csrd_valid = 0;
-      if (!(dev_alloc(&c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc(&c->xlost, (size_t)c->n_cap))) {
+      if (!(dev_alloc_first(c, &c->Xh1, (size_t)c->n_cap * row_halves) && dev_alloc_first(c, &c->xlost, (size_t)c->n_cap))) {
         dev_free(c->Xh1); dev_free(c->xlost);
         return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of %lld instances", (long long)c->n_cap);
       }
@@ -272,7 +291,7 @@ static int ensure_candidates(som_ctx *c, int64_t n, bool dense) {
     dev_free(c->unit_work);
     c->unit_work = nullptr;
     c->unit_cap = 0;
-    if (!dev_alloc(&c->unit_work, (size_t)8 * n * c->csr_sweeps))
+    if (!dev_alloc_first(c, &c->unit_work, (size_t)8 * n * c->csr_sweeps))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the work list of the sparse search");
     c->unit_cap = n * c->csr_sweeps;
   }
@@ -280,8 +299,8 @@ static int ensure_candidates(som_ctx *c, int64_t n, bool dense) {
   (void)hipStreamSynchronize(c->stream);
   dev_free(c->cand_val); dev_free(c->cand_idx); dev_free(c->cand_over);
   c->cand_cap = 0;
-  if (!(dev_alloc(&c->cand_val, (size_t)need * kCand) && dev_alloc(&c->cand_idx, (size_t)need * kCand) &&
-        dev_alloc(&c->cand_over, (size_t)need)))
+  if (!(dev_alloc_first(c, &c->cand_val, (size_t)need * kCand) && dev_alloc_first(c, &c->cand_idx, (size_t)need * kCand) &&
+        dev_alloc_first(c, &c->cand_over, (size_t)need)))
     return fail(c, SOM_ERR_ALLOC, "cannot allocate candidate lists for %lld slots", (long long)need);
   c->cand_cap = need;
   return SOM_OK;
@@ -290,9 +309,9 @@ static int ensure_candidates(som_ctx *c, int64_t n, bool dense) {
 static int ensure_transposed(som_ctx *c) {
   if (c->Wt) return SOM_OK;
   const size_t words = ((size_t)c->dim * c->kpad + 1) / 2;      // int16 entries
-  if (!(dev_alloc(&c->Wt, words) && dev_alloc(&c->col_range, (size_t)2 * 64 * c->dim) &&
-        dev_alloc(&c->qstep, (size_t)c->dim) &&
-        dev_alloc(&c->ct_partial, (size_t)kCtMaxSlabs * c->k * 3))) {
+  if (!(dev_alloc_first(c, &c->Wt, words) && dev_alloc_first(c, &c->col_range, (size_t)2 * 64 * c->dim) &&
+        dev_alloc_first(c, &c->qstep, (size_t)c->dim) &&
+        dev_alloc_first(c, &c->ct_partial, (size_t)kCtMaxSlabs * c->k * 3))) {
     dev_free(c->Wt); dev_free(c->col_range); dev_free(c->qstep); dev_free(c->ct_partial);
     return fail(c, SOM_ERR_ALLOC, "cannot allocate the transposed code book (%d x %d)", c->dim, c->kpad);
   }
@@ -446,21 +465,28 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
   return SOM_OK;
 }
 
-// Everything the sparse sweep needs: scratch, norms of the instances (unless registered), the centring
-// vector (mean of the code-book rows) with the quantisation steps, node constants, the transposed 16-bit
-// code book and the scaled values.
-static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
-                       int64_t nnz, const float *W, bool have_xn, bool cleared, bool sketch = false) {
+// Memory of the sparse search; the subspace (sub: it may be used) comes after what the search always needs.
+static int ensure_csr(som_ctx *c, int64_t n, int64_t nnz, bool sub) {
   if (nnz > c->vq_cap) {
     (void)hipStreamSynchronize(c->stream);
     dev_free(c->vq);
     c->vq_cap = 0;
-    if (!dev_alloc(&c->vq, (size_t)nnz)) return fail(c, SOM_ERR_ALLOC, "cannot allocate %lld scaled values", (long long)nnz);
+    if (!dev_alloc_first(c, &c->vq, (size_t)nnz)) return fail(c, SOM_ERR_ALLOC, "cannot allocate %lld scaled values", (long long)nnz);
     c->vq_cap = nnz;
   }
   int rc = ensure_transposed(c);
-  if (!rc) rc = ensure_candidates(c, n, false);
   if (rc) return rc;
+  ensure_rescan_copy(c);
+  if (sub) ensure_subspace(c, true, true);
+  return ensure_candidates(c, n, false);
+}
+
+
+// Everything the sparse sweep needs besides memory: norms of the instances (unless registered), the centring
+// vector (mean of the code-book rows) with the quantisation steps, node constants, the transposed 16-bit
+// code book and the scaled values.
+static int prepare_csr(som_ctx *c, const int64_t *indptr, const float *values, int64_t n, const float *W, bool have_xn, bool cleared,
+                       bool sketch = false) {
   if (!have_xn) {
     c->d_norms_valid = 0;
     SOM_LAUNCH(c, launch_csr_row_sqnorms(c, indptr, values, n, c->xn32));
@@ -468,7 +494,7 @@ static int prepare_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices
   // centring vector of the sparse search: the mean of the code-book rows (changes every epoch);
   // it overwrites the one a registered dense training set may have cached
   if (c->data_kind == 1) { c->d_norms_valid = 0; c->d_split_valid = 0; }
-  rc = begin_search(c, cleared);
+  const int rc = begin_search(c, cleared);
   if (rc) return rc;
   if (sketch) SOM_LAUNCH(c, launch_codebook_means_steps_and_sketch(c, W));
   else SOM_LAUNCH(c, launch_codebook_means_and_steps(c, W));
@@ -535,11 +561,11 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus, cleared);
   // in the subspace of the code book if the device finds that it may, and then nothing is left for the sweep to do
   const bool eligible = subspace_csr_eligible(c, n, nnz);
-  if (eligible) ensure_subspace(c, true, true);
-  const bool sub = eligible && !c->sub_failed && subspace_csr_likely(c, radius);
-  int rc = prepare_csr(c, indptr, indices, values, n, nnz, W, have_xn, cleared, sub);
+  int rc = ensure_csr(c, n, nnz, eligible);
   if (rc) return rc;
-  ensure_rescan_copy(c);
+  const bool sub = eligible && !c->sub_failed && subspace_csr_likely(c, radius);
+  rc = prepare_csr(c, indptr, values, n, W, have_xn, cleared, sub);
+  if (rc) return rc;
   const SubspaceState *state = sub ? c->sub_state : nullptr;
   c->two_level_n = sub ? n : 0;
   if (sub) {
@@ -652,9 +678,9 @@ static int registered_hot(som_ctx *c) {
   if (n * kP * 4 > (8ll << 30)) return SOM_OK;
   if (!c->hot_counts) {
     const size_t halves = (size_t)kHot * 2;
-    if (!(dev_alloc(&c->hot_counts, (size_t)c->dim) && dev_alloc(&c->hot_rank, (size_t)c->dim) &&
-          dev_alloc(&c->hot_cols, (size_t)kHot) && dev_alloc(&c->hot_Wc, (size_t)c->k * kHot) &&
-          dev_alloc(&c->hot_Wh, (size_t)c->k * halves) && dev_alloc(&c->hot_wscale, 1))) {
+    if (!(dev_alloc_first(c, &c->hot_counts, (size_t)c->dim) && dev_alloc_first(c, &c->hot_rank, (size_t)c->dim) &&
+          dev_alloc_first(c, &c->hot_cols, (size_t)kHot) && dev_alloc_first(c, &c->hot_Wc, (size_t)c->k * kHot) &&
+          dev_alloc_first(c, &c->hot_Wh, (size_t)c->k * halves) && dev_alloc_first(c, &c->hot_wscale, 1))) {
       dev_free(c->hot_counts); dev_free(c->hot_rank); dev_free(c->hot_cols); dev_free(c->hot_Wc); dev_free(c->hot_Wh);
       dev_free(c->hot_wscale);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the hot-column tables");
@@ -674,10 +700,10 @@ static int registered_hot(som_ctx *c) {
   const int64_t tail_cap = nnz;                            // the counters may include out-of-range indices the kernels clamp
   if (n > c->hot_n_cap || tail_cap > c->hot_nnz_cap) {
     free_hot(c);
-    if (!(dev_alloc(&c->tail_start, (size_t)n + 1) && dev_alloc(&c->tail_indptr, (size_t)n + 1) &&
-          dev_alloc(&c->tail_indices, (size_t)tail_cap) && dev_alloc(&c->tail_values, (size_t)tail_cap) &&
-          dev_alloc(&c->hot_Xh, (size_t)n * kHot * 2) && dev_alloc(&c->hot_xscale, (size_t)n) &&
-          dev_alloc(&c->hot_xn, (size_t)n) && dev_alloc(&c->hot_P, (size_t)(n * kP)))) {
+    if (!(dev_alloc_first(c, &c->tail_start, (size_t)n + 1) && dev_alloc_first(c, &c->tail_indptr, (size_t)n + 1) &&
+          dev_alloc_first(c, &c->tail_indices, (size_t)tail_cap) && dev_alloc_first(c, &c->tail_values, (size_t)tail_cap) &&
+          dev_alloc_first(c, &c->hot_Xh, (size_t)n * kHot * 2) && dev_alloc_first(c, &c->hot_xscale, (size_t)n) &&
+          dev_alloc_first(c, &c->hot_xn, (size_t)n) && dev_alloc_first(c, &c->hot_P, (size_t)(n * kP)))) {
       free_hot(c);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the hot-column split of %lld rows", (long long)n);
     }
@@ -714,7 +740,7 @@ static int registered_csr_dense(som_ctx *c) {
   if (n > c->csrd_n_cap || !c->csrd_mu) {
     dev_free(c->csrd_xn); dev_free(c->csrd_mu); dev_free(c->csrd_mu_norm2);
     c->csrd_n_cap = 0;
-    if (!(dev_alloc(&c->csrd_xn, (size_t)n) && dev_alloc(&c->csrd_mu, (size_t)c->dim) && dev_alloc(&c->csrd_mu_norm2, 1))) {
+    if (!(dev_alloc_first(c, &c->csrd_xn, (size_t)n) && dev_alloc_first(c, &c->csrd_mu, (size_t)c->dim) && dev_alloc_first(c, &c->csrd_mu_norm2, 1))) {
       dev_free(c->csrd_xn); dev_free(c->csrd_mu); dev_free(c->csrd_mu_norm2);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the norms of %lld centred rows", (long long)n);
     }
@@ -728,7 +754,7 @@ static int registered_csr_dense(som_ctx *c) {
   if (batch > n) batch = n;
   if (batch < 1) batch = 1;
   float *dense = nullptr;
-  if (!dev_alloc(&dense, (size_t)batch * c->dim)) return fail(c, SOM_ERR_ALLOC, "cannot allocate a batch of dense rows");
+  if (!dev_alloc_first(c, &dense, (size_t)batch * c->dim)) return fail(c, SOM_ERR_ALLOC, "cannot allocate a batch of dense rows");
   const bool coarse = two_level_ready(c, n);
   int rcl = SOM_OK;
   for (int64_t r0 = 0; r0 < n && rcl == SOM_OK; r0 += batch) {
@@ -1269,7 +1295,8 @@ int som_debug_scores_csr(som_ctx *c, const int64_t *indptr, const int32_t *indic
   if (!codebook || !scores || !mu_out || !margin_out) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
   int rc = check_csr(c, indptr, indices, values, n, nnz);
   if (!rc) rc = ensure_rows(c, n, false);
-  if (!rc) rc = prepare_csr(c, indptr, indices, values, n, nnz, codebook, false, false);
+  if (!rc) rc = ensure_csr(c, n, nnz, false);
+  if (!rc) rc = prepare_csr(c, indptr, values, n, codebook, false, false);
   if (rc) return rc;
   rc = codebook_for_sweep(c, codebook);
   if (rc) return rc;
