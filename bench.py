@@ -31,14 +31,14 @@ PEAK_HBM_GBS = 8000.0
 # (FETCH_SIZE, WRITE_SIZE, scaled by the copy calibration) summarised in profiles/epoch_config*.md;
 # measured once per kernel version, not during this run (the dense figures vary by some ten percent from
 # run to run: they depend on how long the workgroups that share an instance tile stay in step).
-MEASURED_TRAFFIC_BYTES = {(2, "two_level"): 1.306e9 + 0.034e9, (3, "two_level"): 2.252e9 + 0.094e9,
-                          (5, "two_level"): 2.145e9 + 0.424e9,
+MEASURED_TRAFFIC_BYTES = {(2, "two_level"): 0.461e9 + 0.035e9, (3, "two_level"): 2.082e9 + 0.094e9,
+                          (5, "two_level"): 2.059e9 + 0.425e9,
                           (6, "two_level"): 1.814e9 + 0.036e9,      # sparse rows searched through dense planes
                           # one-level split-fp16 filter and fp32 filter (earlier counter runs; those kernels are unchanged)
                           (2, "split_f16"): 3.841e9 + 0.036e9, (2, "fp32"): 8.49e9 + 0.025e9,
                           (3, "split_f16"): 14.283e9 + 0.025e9, (5, "split_f16"): 13.917e9 + 0.072e9,
                           # sparse: all kernels of the filter stage (code-book pass, hot-column block, sweep)
-                          (4, "sparse"): 16.387e9 + 1.453e9, (6, "sparse"): 0.415e9 + 0.058e9,
+                          (4, "sparse"): 11.671e9 + 1.034e9, (6, "sparse"): 0.415e9 + 0.058e9,
                           (7, "sparse"): 86.822e9 + 6.474e9}
 PEAK_FP32_VALU_TFLOPS = 157.3
 
@@ -215,18 +215,17 @@ def main() -> int:
                         "traffic": MEASURED_TRAFFIC_BYTES.get((w.config, args.filter)), "avg_launch_ms": dom_ms}
         elif fine_share is not None:
             # two-level search: one fp16 product per (instance, node, feature) in the coarse pass and three
-            # more on the share of the pairs the second pass works on: mfma_issue_frac counts those (how busy
-            # the matrix pipe is), frac counts the method's one multiply-add per triple.  avg_launch_ms is the
-            # whole filter stage (coarse pass, block selection, ordering, lists, second pass)
-            products = 1.0 + 3.0 * fine_share["mean"]
-            roofline = {"bound": "mfma", "kernel": "two-level BMU filter stage: k_bmu_coarse (block minima, 1 fp16 product) + "
-                                                   "k_select_blocks + counting sort + k_tile_lists + k_bmu_dense_h<fine, 3 fp16 "
-                                                   "products on the listed pairs>",
+            # more on the share of the pairs the second pass works on; in the epochs of a wide radius both run on 32
+            # or 64 coordinates of the code book's subspace instead of the features.  frac counts the method's one
+            # multiply-add per triple, which is more than is issued in those epochs.  avg_launch_ms is the whole
+            # filter stage (subspace, coarse pass, block selection, ordering, lists, second pass)
+            roofline = {"bound": "mfma", "kernel": "two-level BMU filter stage: k_subspace_* + k_bmu_coarse / k_bmu_coarse_subspace "
+                                                   "(block minima, 1 fp16 product) + k_select_blocks + counting sort + "
+                                                   "k_tile_lists + k_bmu_dense_h<fine, 3 fp16 products on the listed pairs>",
                         "achieved": fp32_equiv, "peak": PEAK_FP16_MFMA_TFLOPS, "unit": "TFLOP/s",
                         "frac": fp32_equiv / PEAK_FP16_MFMA_TFLOPS,
                         "traffic": MEASURED_TRAFFIC_BYTES.get((w.config, "two_level")), "avg_launch_ms": dom_ms,
                         "second_pass_share_of_pairs": fine_share,
-                        "mfma_issue_frac": products * fp32_equiv / PEAK_FP16_MFMA_TFLOPS,
                         "vs_fp32_mfma_peak": fp32_equiv / PEAK_FP32_MFMA_TFLOPS}
         else:
             # the kernel issues three fp16 matrix products per (instance, node, feature), hi*hi + hi*lo + lo*hi:
@@ -251,7 +250,8 @@ def main() -> int:
         traffic = MEASURED_TRAFFIC_BYTES.get((w.config, "sparse"))
         valu_bound_ms = 2.0 * nnz * w.k / (PEAK_FP32_VALU_TFLOPS * 1e12) * 1e3
         roofline = {"bound": "hbm", "kernel": "sparse BMU filter pass: k_center_transpose_q16 + hot-column block "
-                                              "(k_bmu_dense_h<partial>) + k_bmu_csr_sliced",
+                                              "(k_bmu_dense_h<partial>) + k_bmu_csr_sliced; epochs of a wide radius on a "
+                                              "planar map: k_subspace_* + k_csr_* + the two-level passes on 64 coordinates",
                     "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS,
                     "traffic": traffic, "avg_launch_ms": dom_ms,
                     # the three views of this kernel: (i) against the plain fp32 vector ALUs, on which 2 nnz k
