@@ -40,6 +40,10 @@ namespace som {
 // instances of a table row); thread p of an instance takes the blocks p, p + kParts, ... and keeps the first
 // 32 of them in registers, so that the table is read once for maps of up to 32 kParts blocks (beyond that the
 // rest is read again for the comparison); minima, mask words and the key are combined through LDS.
+// Bound by the read of the table, provided that the vector units keep out of its way: the block number is a scalar, so that rows are
+// addressed and left out without vector instructions, and one wavefront takes the fp64 margins for all (another one in every
+// workgroup, as wavefronts of a number share a SIMD).  1,000,000 instances x 79 blocks 132 -> 74 us (4.3 TB/s; 168 -> 60 registers), 50,000 x 313
+// 28.9 -> 23.0, 100,000 x 20 16 -> 5.9.
 template <int kParts>
 __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__restrict__ m, int64_t n, int blocks,
                                                               const float *__restrict__ xn32,
@@ -48,12 +52,16 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
                                                               int classes, int spans, int only, int32_t *__restrict__ key,
                                                               uint32_t *__restrict__ mask) {
   constexpr int kHold = 32;
-  constexpr int kWordsAtOnce = 8;               // mask words combined per round: 256 blocks
+  constexpr int kWordsAtOnce = kHold * kParts / 32;      // mask words combined per round: the first are those held
+  constexpr int kRun = 4;                       // loads between two looks at the number of blocks
   __shared__ float s_best[kParts][64];
+  __shared__ double s_margin[64];
   __shared__ uint32_t s_bits[kParts][kWordsAtOnce][64];
-  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+  const int lane = threadIdx.x & 63;
+  const int part = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + (int)blockIdx.x) & (kParts - 1);
+  const int64_t j0 = (int64_t)blockIdx.x * 64, j = j0 + lane;
   const bool live = j < n;
+  const unsigned at = (unsigned)(live ? lane : (int)(n - 1 - j0));      // lanes past the end repeat the last instance
   if (only && !mm.sub->use) {                   // no scores: no blocks (the passes behind this one find nothing to do)
     if (part == 0 && live) {
       for (int w = 0; 32 * w < blocks; ++w) mask[(int64_t)w * n + j] = 0;
@@ -65,21 +73,28 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
   float best = INFINITY;
 #pragma unroll
   for (int i = 0; i < kHold; ++i) {
-    const int b = part + i * kParts;
-    held[i] = (live && b < blocks) ? m[(int64_t)b * n + j] : INFINITY;
-    best = fminf(best, held[i]);
+    held[i] = INFINITY;
   }
-  if (live)
-    for (int b = part + kHold * kParts; b < blocks; b += kParts) best = fminf(best, m[(int64_t)b * n + j]);
+#pragma unroll
+  for (int i0 = 0; i0 < kHold; i0 += kRun)
+    if (part + i0 * kParts < blocks) {          // (blocks past the last repeat it)
+#pragma unroll
+      for (int i = i0; i < i0 + kRun; ++i) held[i] = (m + (int64_t)min(part + i * kParts, blocks - 1) * n + j0)[at];
+    }
+  // score_margin is the bound for a PAIR of scores (2 e_j and slack): exactly the window of step 2
+  if (part == 0)
+    s_margin[lane] = score_margin(mm, j0 + at, (double)xn32[j0 + at], (double)__uint_as_float(*wmax_bits), (double)*mu_norm2);
+#pragma unroll
+  for (int i = 0; i < kHold; ++i) best = fminf(best, held[i]);
+  for (int b = part + kHold * kParts; b < blocks; b += kParts) best = fminf(best, (m + (int64_t)b * n + j0)[at]);
   s_best[part][lane] = best;
   __syncthreads();
   best = s_best[0][lane];
 #pragma unroll
   for (int p = 1; p < kParts; ++p) best = fminf(best, s_best[p][lane]);
   float t32 = INFINITY;                         // no finite score at all: every block stays in
-  if (live && best < INFINITY) {
-    // score_margin is the bound for a PAIR of scores (2 e_j and slack): exactly the window of step 2
-    const double thr = (double)best + score_margin(mm, j, (double)xn32[j], (double)__uint_as_float(*wmax_bits), (double)*mu_norm2);
+  if (best < INFINITY) {
+    const double thr = (double)best + s_margin[lane];
     t32 = (float)thr;                           // rounded up: no block inside the window is lost
     if ((double)t32 < thr) t32 = nextafterf(t32, INFINITY);
   }
@@ -91,19 +106,23 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
     if (w0 == 0) {                              // the blocks held in registers: 32 kParts <= 256 of them
 #pragma unroll
       for (int i = 0; i < kHold; ++i) {
-        const int b = part + i * kParts;        // compile-time word and bit position up to `part`
-        if (b < blocks && !(held[i] > t32)) bits[(i * kParts) >> 5] |= 1u << ((part + i * kParts) & 31);   // a NaN keeps its block in
+        // compile-time word and bit position up to `part`; a NaN keeps its block in, blocks past the last go below
+        bits[(i * kParts) >> 5] |= held[i] > t32 ? 0u : 1u << ((i * kParts) & 31);
       }
     }
-    if (w0 > 0 && live) {                       // (the launcher picks kParts so that the first round is all held)
+    if (kParts > 4 && w0 > 0) {                 // (the launcher gives four parts to maps that fit the registers)
 #pragma unroll
       for (int w = 0; w < kWordsAtOnce; ++w)
+        if (w0 + 32 * w < blocks) {
+          float v[32 / kParts];
 #pragma unroll
-        for (int t = 0; t < 32 / kParts; ++t) {
-          const int b = w0 + 32 * w + part + kParts * t;
-          if (b < blocks && !(m[(int64_t)b * n + j] > t32)) bits[w] |= 1u << (part + kParts * t);
+          for (int t = 0; t < 32 / kParts; ++t) v[t] = (m + (int64_t)min(w0 + 32 * w + part + kParts * t, blocks - 1) * n + j0)[at];
+#pragma unroll
+          for (int t = 0; t < 32 / kParts; ++t) bits[w] |= v[t] > t32 ? 0u : 1u << (kParts * t);
         }
     }
+#pragma unroll
+    for (int w = 0; w < kWordsAtOnce; ++w) bits[w] <<= part;
 #pragma unroll
     for (int w = 0; w < kWordsAtOnce; ++w) s_bits[part][w][lane] = bits[w];
     __syncthreads();
@@ -114,6 +133,7 @@ __global__ __launch_bounds__(64 * kParts) void k_select_blocks(const float *__re
         uint32_t all = 0;
 #pragma unroll
         for (int p = 0; p < kParts; ++p) all |= s_bits[p][w][lane];
+        if (blocks - w0 - 32 * w < 32) all &= (1u << (blocks - w0 - 32 * w)) - 1;
         mask[(int64_t)((w0 >> 5) + w) * n + j] = all;
         if (all && lowest == 0x7fffffff) lowest = w0 + 32 * w + __ffs((int)all) - 1;
         if (all) highest = w0 + 32 * w + 31 - __clz((int)all);

@@ -219,3 +219,22 @@ def test_selection_margin_covers_the_coarse_scores(case):
     assert np.all(err <= 0.5 * margin), (err / margin).max()
     assert np.all(margin <= any_rows)
     print(f"{case}: worst error / half the margin {(2 * err / margin).max():.3f}, margin / bound for any rows {(margin / any_rows).mean():.3f}")
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 4, 5, 16, 17, 31, 32, 33, 127, 128, 129, 255, 256, 257, 300, 512, 513])
+def test_block_selection_at_every_number_of_blocks(oracle, blocks):
+    """The selection reads the block minima in runs of four per thread, keeps 128 or 256 blocks in registers and joins mask
+    words of 32: best nodes with copies in every other block, in one and in the last, ragged block and instance tile included."""
+    rng = np.random.default_rng(4400 + blocks)
+    rows = 1 if blocks <= 512 else 3                             # (a side has at most 65,535 nodes)
+    cols, dim, n = (128 * blocks - 5) // rows, 12, 65
+    k = rows * cols
+    W = rng.random((k, dim)).astype(np.float32)
+    src = rng.integers(0, 120, size=n)                           # first block
+    src[::3] = k - 1 - rng.integers(0, 120, size=len(src[::3]))  # last block
+    X = (W[src] + 1e-3 * rng.standard_normal((n, dim))).astype(np.float32)
+    for i in range(0, n, 5):
+        copies = (src[i] % 120 + 128 * np.arange(0, blocks, 1 + i % 2))
+        W[copies] = W[src[i]]                                    # exact copies: the lowest index wins
+    b, _ = _bmus(W, X, rows, cols)
+    assert np.array_equal(b, oracle.bmu_dense(X, W))
