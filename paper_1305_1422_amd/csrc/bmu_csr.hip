@@ -178,21 +178,24 @@ __global__ __launch_bounds__(256) void k_center_transpose_q16(const float *__res
   }
 }
 
-// 32 nodes per workgroup, eight threads a node: thread q adds the slabs q, q + 8, ... and the eight sums are added in order, the same for every node.
+// kQ threads a node: thread q adds the slabs q, q + kQ, ... and the kQ sums are added in order, the same for every node.  The maximum
+// is a chain of atomics on one word, some 10 ns each: one per workgroup, and only from those that raise it.
+template <int kQ>
 __global__ __launch_bounds__(256) void k_finish_node_constants(const double *__restrict__ partial, int slabs, int k,
                                                                float *__restrict__ cn, double *__restrict__ wn64,
                                                                unsigned *__restrict__ max_bits,
                                                                const SubspaceState *__restrict__ off) {
   if (off && off->use) return;
-  const int i = blockIdx.x * 32 + (threadIdx.x >> 3), q = threadIdx.x & 7;
+  __shared__ float s_max[4];
+  const int i = blockIdx.x * (256 / kQ) + (int)threadIdx.x / kQ, q = threadIdx.x % kQ;
   double s2 = 0.0, sm = 0.0, sw = 0.0;
   if (i < k)
-    for (int s = q; s < slabs; s += 8) {
+    for (int s = q; s < slabs; s += kQ) {
       const double *p = partial + ((int64_t)s * k + i) * 3;
       s2 += p[0]; sm += p[1]; sw += p[2];
     }
 #pragma unroll
-  for (int o = 1; o < 8; o <<= 1) {
+  for (int o = 1; o < kQ; o <<= 1) {
     s2 += __shfl_xor(s2, o, 64);
     sm += __shfl_xor(sm, o, 64);
     sw += __shfl_xor(sw, o, 64);
@@ -204,7 +207,13 @@ __global__ __launch_bounds__(256) void k_finish_node_constants(const double *__r
   float vmax = i < k ? (float)s2 : 0.f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
-  if ((threadIdx.x & 63) == 0 && vmax > 0.f) atomicMax(max_bits, __float_as_uint(vmax));
+  if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = vmax;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    vmax = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    if (vmax > 0.f && __float_as_uint(vmax) > __hip_atomic_load(max_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(max_bits, __float_as_uint(vmax));
+  }
 }
 
 __device__ __forceinline__ void wave_argmin(float &v, int &i) {
@@ -498,8 +507,14 @@ hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const Su
   slabs = (c->dim + cols_per_slab - 1) / cols_per_slab;
   hipLaunchKernelGGL(k_center_transpose_q16, dim3((unsigned)tiles, (unsigned)slabs), dim3(256), 0, c->stream, W, c->mu,
                      c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial, off);
-  hipLaunchKernelGGL(k_finish_node_constants, dim3((c->k + 31) / 32), dim3(256), 0, c->stream, c->ct_partial, slabs,
-                     c->k, c->wn32, c->wn64, c->wmax_bits, off);
+  // Eight threads a node where one each would leave most of the chip idle and chains of slabs to wait for (2,500 nodes 24 -> 7.8 us);
+  // with more nodes there are few slabs, and eight would only read them in shorter pieces (68,880 nodes, three slabs, 100 -> 8.5, most of it the atomics).
+  if (c->k < 65536)
+    hipLaunchKernelGGL(k_finish_node_constants<8>, dim3((c->k + 31) / 32), dim3(256), 0, c->stream, c->ct_partial, slabs, c->k, c->wn32,
+                       c->wn64, c->wmax_bits, off);
+  else
+    hipLaunchKernelGGL(k_finish_node_constants<1>, dim3((c->k + 255) / 256), dim3(256), 0, c->stream, c->ct_partial, slabs, c->k, c->wn32,
+                       c->wn64, c->wmax_bits, off);
   return hipGetLastError();
 }
 
