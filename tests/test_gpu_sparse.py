@@ -49,6 +49,21 @@ def test_many_nodes(oracle, rows, cols):
     som.close()
 
 
+@pytest.mark.parametrize("rows,cols", [(1, 65535), (256, 256), (257, 257)])
+def test_node_constants_where_their_sums_change(oracle, rows, cols):
+    """Eight threads a node below 65,536 nodes, one from there on; the node of the largest norm, which sets every margin, lies
+    in the last, ragged workgroup."""
+    from paper_1305_1422_amd import Som
+    dim, n = 70, 120
+    csr = sparse_zipf_csr(n, dim, 23, mean_len=9.0, max_len=30)
+    W = np.random.default_rng(24).random((rows * cols, dim)).astype(np.float32)
+    W[-1] *= 50.0
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
+    b = som.bmus(P.csr_to_dev(csr)).cpu().numpy()
+    P.check_bmus_csr(oracle, csr, dim, W, b)
+    som.close()
+
+
 def test_smooth_map_takes_the_second_sweep_over_listed_ranges(oracle):
     """A code book smoothed with a wide neighbourhood has neighbouring nodes closer than the 16-bit
     filter can separate: many instances go to the second sweep, which visits only the node ranges whose
