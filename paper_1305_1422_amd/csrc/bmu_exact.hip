@@ -325,17 +325,46 @@ __device__ __forceinline__ int nearest_listed(const float *__restrict__ x, const
   return arg;
 }
 
-// Exact comparison of the collected lists.  A list that overflowed its capacity sends the instance on to the full rescan.
-//
-// Few lists: a wavefront each.  From kListTileMin on, a workgroup takes 16 consecutive ones: they were appended in the
-// order of the two-level search, so they name much the same nodes, and comparing each list by itself read every node's row
-// out of L2 once per instance (14.7 GB for 100,000 x 1,000 on a trained map of 2,500 nodes: 1,900 us at 7.7 TB/s).  The
+// Exact comparison of the collected lists, a wavefront each.  A list that overflowed its capacity sends the instance on to the full
+// rescan.  This is the form for lists that come in no particular order (the one-level filters): bound by the nodes' rows out of
+// L2, with as many wavefronts as fit to wait for them.
+__device__ __forceinline__ void refine_lists_each(const float *__restrict__ X, const float *__restrict__ W, int dim, int k, int count,
+                                                  const int32_t *__restrict__ collect_rows, const int32_t *__restrict__ collect_cnt,
+                                                  const int32_t *__restrict__ collect_list, int32_t *__restrict__ rescan_list,
+                                                  int32_t *__restrict__ list_counts, int32_t *__restrict__ bmus) {
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int e = next_entry(list_counts, lane); e < count; e = next_entry(list_counts, lane)) {
+    const int64_t j = collect_rows[e];
+    const int cn = collect_cnt[e];
+    if (cn > kListCap || cn == 0) {
+      if (lane == 0) rescan_list[atomicAdd(&list_counts[2], 1)] = (int32_t)j;
+      continue;
+    }
+    const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap, cn, lane);
+    if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
+  }
+}
+
+__global__ __launch_bounds__(256) void k_refine_lists_each(const float *__restrict__ X, const float *__restrict__ W, int dim, int k,
+                                                           const int32_t *__restrict__ collect_rows,
+                                                           const int32_t *__restrict__ collect_cnt,
+                                                           const int32_t *__restrict__ collect_list,
+                                                           int32_t *__restrict__ rescan_list,
+                                                           int32_t *__restrict__ list_counts, int32_t *__restrict__ bmus) {
+  refine_lists_each(X, W, dim, k, list_counts[1], collect_rows, collect_cnt, collect_list, rescan_list, list_counts, bmus);
+}
+
+// The same for the two-level search.  Few lists: a wavefront each.  From kListTileMin on, a workgroup takes 16 consecutive ones: they
+// were appended in the order of the two-level search, so they name much the same nodes, and comparing each list by itself read every
+// node's row out of L2 once per instance (14.7 GB for 100,000 x 1,000 on a trained map of 2,500 nodes: 1,900 us at 7.7 TB/s).  The
 // union of the lists is compared with all 16 instances as one fp64 matrix product of rows relative to one of the nodes,
 //   d2 = |x~|^2 + |w~|^2 - 2 x~.w~,   x~ = x - w_0, w~ = w - w_0,
 // whose rounding is below (dim + 8) 2^-50 (|x~| + |w~|)^2; the nodes it cannot tell apart from the nearest - usually there are none - are compared
 // by the plain sums as before, so the decision is the same to the bit.  Bound by the fp64 matrix pipe; the product in fp32 took
 // half the time and left a dozen near-copies per instance to the plain sums (3,000 us).  A union of more than kUnionCap
-// nodes, or of more than half of what the lists hold together, is not worth it: those lists go one by one.
+// nodes, or of more than half of what the lists hold together, is not worth it: those lists go one by one, with the three
+// workgroups per CU that the union's LDS leaves room for.  Lists in no order nearly all do, and take twice as long then (a one-level
+// search of that size: 2,410 us by k_refine_lists_each, 4,770 here), hence the two kernels.
 constexpr int kListTileMin = 4096;
 constexpr int kUnionCap = 320, kUnionHash = 1024;
 
@@ -352,16 +381,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int count = list_counts[1];
   if (count < kListTileMin) {
-    for (int e = next_entry(list_counts, lane); e < count; e = next_entry(list_counts, lane)) {
-      const int64_t j = collect_rows[e];
-      const int cn = collect_cnt[e];
-      if (cn > kListCap || cn == 0) {
-        if (lane == 0) rescan_list[atomicAdd(&list_counts[2], 1)] = (int32_t)j;
-        continue;
-      }
-      const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap, cn, lane);
-      if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
-    }
+    refine_lists_each(X, W, dim, k, count, collect_rows, collect_cnt, collect_list, rescan_list, list_counts, bmus);
     return;
   }
   const int l16 = lane & 15, quad = lane >> 4;
@@ -917,9 +937,12 @@ hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr
   return hipGetLastError();
 }
 
-hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus) {
-  const int blocks = 3 * c->n_cu;          // what their LDS leaves room for
-  if (c->dim >= 4)
+hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus, bool ordered) {
+  const int blocks = 3 * c->n_cu;          // of the union's kernel: what their LDS leaves room for
+  if (!ordered)
+    hipLaunchKernelGGL(k_refine_lists_each, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, X, W,
+                       c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
+  else if (c->dim >= 4)
     hipLaunchKernelGGL(k_refine_lists_dense<true>, dim3(blocks), dim3(256), 0, c->stream, X, W,
                        c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
   else

@@ -385,7 +385,7 @@ hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int
 hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr, double *out,
                           bool hot = false);   // test hook: the margin per instance
 hipError_t launch_refine_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
-hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
+hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus, bool ordered /* appended in the two-level search's order */);
 hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
 hipError_t launch_refine_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
                              const float *values, const float *W, int32_t *bmus);

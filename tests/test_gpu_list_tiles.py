@@ -58,3 +58,14 @@ def test_non_finite_among_the_lists(oracle):
     X[508::1002, 5] = np.inf
     b, stats = _search(W, X, rows, cols, "split_f16")
     assert np.array_equal(b[good], clean[good]) and np.all(b[~good] == 0)
+
+
+@pytest.mark.parametrize("n,rows,cols,dim,groups,filt", [
+    (5000, 30, 30, 33, 2, "two_level"),        # the shapes above in the order that the union takes them in
+    (4500, 20, 25, 3, 25, "two_level"),
+    (6000, 16, 20, 17, 40, "two_level"),
+    (5000, 25, 30, 130, 3, "split_f16"),       # ... and a list at a time, in any order
+    (4097, 20, 30, 40, 30, "fp32"),
+])
+def test_near_copies_in_and_out_of_order(oracle, n, rows, cols, dim, groups, filt):
+    test_near_copies(oracle, n, rows, cols, dim, groups, filt)
