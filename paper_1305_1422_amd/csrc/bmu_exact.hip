@@ -298,10 +298,22 @@ __device__ inline int next_entry(int32_t *list_counts, int lane) {
   return __builtin_amdgcn_readfirstlane(t) * kListTickets + slice;
 }
 
-// One collected list compared exactly by a wavefront: the nearest of its nodes (0x7fffffff: none at a finite distance).
+// The same for a list that is usually shorter than the wavefronts are many: the first entry of each is given by its number, so that
+// nothing is drawn at all then (8,192 wavefronts that all draw from eight counters to find the list empty: 10 us).
+struct ListEntries {
+  int32_t *counters;
+  int at, drawn;             // the entry in hand; how many are given by number
+  __device__ ListEntries(int32_t *list_counts)
+      : counters(list_counts), at((int)(threadIdx.x / kWave * gridDim.x + blockIdx.x)), drawn((int)(gridDim.x * (blockDim.x / kWave))) {
+    at = __builtin_amdgcn_readfirstlane(at);
+  }
+  __device__ void next(int count, int lane) { at = count <= drawn ? count : drawn + next_entry(counters, lane); }
+};
+
+// One collected list compared exactly by a wavefront: the nearest of its nodes (0x7fffffff: none at a finite distance) and how near.
 __device__ __forceinline__ int nearest_listed(const float *__restrict__ x, const float *__restrict__ W, int dim, int k,
-                                              const int32_t *__restrict__ lst, int cn, int lane) {
-  double best = INFINITY;
+                                              const int32_t *__restrict__ lst, int cn, int lane, double &best) {
+  best = INFINITY;
   int arg = 0x7fffffff;
   // four listed nodes at a time: their rows stream together and the instance is read once for the four
   // (a list can be long, and one distance at a time left the kernel waiting on its own loads); every
@@ -328,44 +340,43 @@ __device__ __forceinline__ int nearest_listed(const float *__restrict__ x, const
 // Exact comparison of the collected lists, a wavefront each.  A list that overflowed its capacity sends the instance on to the full
 // rescan.  This is the form for lists that come in no particular order (the one-level filters): bound by the nodes' rows out of
 // L2, with as many wavefronts as fit to wait for them.
-__device__ __forceinline__ void refine_lists_each(const float *__restrict__ X, const float *__restrict__ W, int dim, int k, int count,
-                                                  const int32_t *__restrict__ collect_rows, const int32_t *__restrict__ collect_cnt,
-                                                  const int32_t *__restrict__ collect_list, int32_t *__restrict__ rescan_list,
-                                                  int32_t *__restrict__ list_counts, int32_t *__restrict__ bmus) {
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int e = next_entry(list_counts, lane); e < count; e = next_entry(list_counts, lane)) {
-    const int64_t j = collect_rows[e];
-    const int cn = collect_cnt[e];
-    if (cn > kListCap || cn == 0) {
-      if (lane == 0) rescan_list[atomicAdd(&list_counts[2], 1)] = (int32_t)j;
-      continue;
-    }
-    const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap, cn, lane);
-    if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
-  }
-}
-
 __global__ __launch_bounds__(256) void k_refine_lists_each(const float *__restrict__ X, const float *__restrict__ W, int dim, int k,
                                                            const int32_t *__restrict__ collect_rows,
                                                            const int32_t *__restrict__ collect_cnt,
                                                            const int32_t *__restrict__ collect_list,
                                                            int32_t *__restrict__ rescan_list,
                                                            int32_t *__restrict__ list_counts, int32_t *__restrict__ bmus) {
-  refine_lists_each(X, W, dim, k, list_counts[1], collect_rows, collect_cnt, collect_list, rescan_list, list_counts, bmus);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int count = list_counts[1];
+  for (ListEntries it(list_counts); it.at < count; it.next(count, lane)) {
+    const int e = it.at;
+    const int64_t j = collect_rows[e];
+    const int cn = collect_cnt[e];
+    if (cn > kListCap || cn == 0) {
+      if (lane == 0) rescan_list[atomicAdd(&list_counts[2], 1)] = (int32_t)j;
+      continue;
+    }
+    double best;
+    const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap, cn, lane, best);
+    if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
+  }
 }
 
-// The same for the two-level search.  Few lists: a wavefront each.  From kListTileMin on, a workgroup takes 16 consecutive ones: they
-// were appended in the order of the two-level search, so they name much the same nodes, and comparing each list by itself read every
-// node's row out of L2 once per instance (14.7 GB for 100,000 x 1,000 on a trained map of 2,500 nodes: 1,900 us at 7.7 TB/s).  The
-// union of the lists is compared with all 16 instances as one fp64 matrix product of rows relative to one of the nodes,
+// The same for the two-level search, whose lists were appended in its order: neighbours name much the same nodes, and comparing each
+// list by itself read every node's row out of L2 once per instance (14.7 GB for 100,000 x 1,000 on a trained map of 2,500 nodes:
+// 1,900 us at 7.7 TB/s).  From kListTileMin lists on, a workgroup takes 16 consecutive ones and compares their
+// union with all 16 instances as one fp64 matrix product of rows relative to one of the nodes,
 //   d2 = |x~|^2 + |w~|^2 - 2 x~.w~,   x~ = x - w_0, w~ = w - w_0,
 // whose rounding is below (dim + 8) 2^-50 (|x~| + |w~|)^2; the nodes it cannot tell apart from the nearest - usually there are none - are compared
 // by the plain sums as before, so the decision is the same to the bit.  Bound by the fp64 matrix pipe; the product in fp32 took
 // half the time and left a dozen near-copies per instance to the plain sums (3,000 us).  A union of more than kUnionCap
-// nodes, or of more than half of what the lists hold together, is not worth it: those lists go one by one, with the three
-// workgroups per CU that the union's LDS leaves room for.  Lists in no order nearly all do, and take twice as long then (a one-level
-// search of that size: 2,410 us by k_refine_lists_each, 4,770 here), hence the two kernels.
-constexpr int kListTileMin = 4096;
+// nodes, or of more than half of what the lists hold together, is not worth it.  Those lists, and any fewer than
+// kListTileMin, are left to the launch that also rescans (k_lists_left_and_rescan): here, with the three workgroups
+// per CU that the union's LDS leaves room for, 225 such tiles of 1,408 took as long as all the others (30,000 x 1,000 on a trained map
+// of 3,600 nodes: a search 1,933 -> 1,316 us, 1,624 with every list by itself).  kListTileMin is the wavefronts that the chip holds: with fewer lists each
+// has one or more to itself, and is done before a tile's chain of loads is (searches, tiles / one by one: 4,304 lists of 500 features
+// 829 / 741 us, 7,732 of 1,000 1,233 / 1,105, 4,860 733 / 521; but 6,962 of 300 280 / 312; 10,427 of 300 316 / 364, 11,708 of 1,000 509 / 760).
+constexpr int kListTileMin = 8192;
 constexpr int kUnionCap = 320, kUnionHash = 1024;
 
 template <bool kWide>
@@ -375,13 +386,15 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
                                                             const int32_t *__restrict__ collect_list,
                                                             int32_t *__restrict__ rescan_list,
                                                             int32_t *__restrict__ list_counts,
+                                                            int32_t *__restrict__ tiles_left,
                                                             int32_t *__restrict__ bmus) {
   __shared__ int s_hash[kUnionHash], s_node[kUnionCap], s_row[16], s_cnt[16], s_n, s_listed, s_slot;
   __shared__ double s_d2[16][kUnionCap + 1], s_xn[16], s_wn[kUnionCap];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int count = list_counts[1];
   if (count < kListTileMin) {
-    refine_lists_each(X, W, dim, k, count, collect_rows, collect_cnt, collect_list, rescan_list, list_counts, bmus);
+    for (int e = blockIdx.x * 256 + tid; e < count; e += gridDim.x * 256)
+      if (collect_cnt[e] > kListCap || collect_cnt[e] == 0) rescan_list[atomicAdd(&list_counts[2], 1)] = collect_rows[e];
     return;
   }
   const int l16 = lane & 15, quad = lane >> 4;
@@ -425,13 +438,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
     __syncthreads();
     const int un = s_n;
     if (un > kUnionCap || 2 * un > s_listed) {     // uniform: both are read after the barrier and not written before the next
-      for (int r = wave; r < 16; r += 4) {
-        const int cn = s_cnt[r];
-        if (cn == 0) continue;
-        const int64_t j = s_row[r];
-        const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)(e0 + r) * kListCap, cn, lane);
-        if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;
-      }
+      if (tid == 0) tiles_left[atomicAdd(&list_counts[kTilesLeftWord], 1)] = s_slot;
       continue;
     }
     // the product: lane -> instance / node l16, features 4 quad .. 4 quad + 3 of every 16, which four instructions take one
@@ -528,22 +535,20 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
             }
         }
       } else {
-        arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)(e0 + r) * kListCap, s_cnt[r], lane);
+        arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)(e0 + r) * kListCap, s_cnt[r], lane, best);
       }
       if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_rescan_dense(const float *__restrict__ X, const float *__restrict__ W,
-                                                      int dim, int k, const int32_t *__restrict__ rescan_list,
-                                                      const int32_t *__restrict__ list_counts,
-                                                      int32_t *__restrict__ bmus) {
+// Exact scan of all nodes for the instances of rescan_list, a workgroup each.
+__device__ __forceinline__ void rescan_rows(const float *__restrict__ X, const float *__restrict__ W, int dim, int k,
+                                            const int32_t *__restrict__ rescan_list, int count, int32_t *__restrict__ bmus) {
   __shared__ double s_best[4];
   __shared__ int s_arg[4];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
-  const int count = list_counts[2];
   for (int e = blockIdx.x; e < count; e += gridDim.x) {
     const int64_t j = rescan_list[e];
     const float *x = X + j * dim;
@@ -562,6 +567,62 @@ __global__ __launch_bounds__(256) void k_rescan_dense(const float *__restrict__ 
     }
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(256) void k_rescan_dense(const float *__restrict__ X, const float *__restrict__ W,
+                                                      int dim, int k, const int32_t *__restrict__ rescan_list,
+                                                      const int32_t *__restrict__ list_counts,
+                                                      int32_t *__restrict__ bmus) {
+  rescan_rows(X, W, dim, k, rescan_list, list_counts[2], bmus);
+}
+
+// After k_refine_lists_dense: the lists that it left, a wavefront each (the overflowed ones are on rescan_list by then), and the rescan.  Bound by the
+// longest list where there are few: two or four wavefronts share each then (3,734 lists of 1,000 features: a search 667 -> 578 us).
+__global__ __launch_bounds__(256) void k_lists_left_and_rescan(const float *__restrict__ X, const float *__restrict__ W, int dim, int k,
+                                                               const int32_t *__restrict__ collect_rows,
+                                                               const int32_t *__restrict__ collect_cnt,
+                                                               const int32_t *__restrict__ collect_list,
+                                                               const int32_t *__restrict__ tiles_left,
+                                                               const int32_t *__restrict__ rescan_list,
+                                                               int32_t *__restrict__ list_counts, int32_t *__restrict__ bmus) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int lists = list_counts[1], rescans = list_counts[2];
+  const bool tiles = lists >= kListTileMin;
+  const int count = tiles ? list_counts[kTilesLeftWord] * 16 : lists;
+  auto entry = [&](int at) { return tiles ? tiles_left[at >> 4] * 16 + (at & 15) : at; };
+  auto length = [&](int e) {
+    const int cn = e < lists ? collect_cnt[e] : 0;
+    return cn > kListCap ? 0 : cn;
+  };
+  const int wave = threadIdx.x / kWave, blocks = gridDim.x;
+  const int team = count <= blocks ? 4 : count <= 2 * blocks ? 2 : 1;
+  if (team > 1) {
+    __shared__ double s_near[4];
+    __shared__ int s_node[4];
+    const int at = (wave / team) * blocks + blockIdx.x, part = wave % team;
+    const int e = at < count ? entry(at) : 0, cn = at < count ? length(e) : 0;
+    const int per = ((cn + 3) / 4 + team - 1) / team * 4, first = min(part * per, cn);      // whole fours
+    const int64_t j = cn ? collect_rows[e] : 0;
+    double best;
+    int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap + first, min(per, cn - first), lane, best);
+    if (lane == 0) { s_near[wave] = best; s_node[wave] = arg; }
+    __syncthreads();
+    if (cn && part == 0 && lane == 0) {
+      for (int w = wave + 1; w < wave + team; ++w)
+        if (nearer(s_near[w], s_node[w], best, arg)) { best = s_near[w]; arg = s_node[w]; }
+      bmus[j] = arg == 0x7fffffff ? 0 : arg;
+    }
+  } else {
+    for (ListEntries it(list_counts + kListTickets2); it.at < count; it.next(count, lane)) {
+      const int e = entry(it.at), cn = length(e);
+      if (cn == 0) continue;
+      const int64_t j = collect_rows[e];
+      double best;
+      const int arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)e * kListCap, cn, lane, best);
+      if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;
+    }
+  }
+  rescan_rows(X, W, dim, k, rescan_list, rescans, bmus);
 }
 
 __global__ __launch_bounds__(256) void k_refine_csr(const int64_t *__restrict__ indptr,
@@ -944,10 +1005,10 @@ hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W,
                        c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
   else if (c->dim >= 4)
     hipLaunchKernelGGL(k_refine_lists_dense<true>, dim3(blocks), dim3(256), 0, c->stream, X, W,
-                       c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
+                       c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, c->refine_list, bmus);
   else
     hipLaunchKernelGGL(k_refine_lists_dense<false>, dim3(blocks), dim3(256), 0, c->stream, X, W,
-                       c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, bmus);
+                       c->dim, c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->rescan_list, c->list_counts, c->refine_list, bmus);
   return hipGetLastError();
 }
 
@@ -957,7 +1018,13 @@ hipError_t launch_refine_dense(som_ctx *c, const float *X, const float *W, int32
   return hipGetLastError();
 }
 
-hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus) {
+// ordered: as of launch_refine_lists_dense, which has left some of its lists (in tiles: refine_list, whose own entries are done).
+hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus, bool ordered) {
+  if (ordered) {
+    hipLaunchKernelGGL(k_lists_left_and_rescan, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, X, W, c->dim,
+                       c->k, c->collect_rows, c->collect_cnt, c->collect_list, c->refine_list, c->rescan_list, c->list_counts, bmus);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_rescan_dense, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, X, W, c->dim,
                      c->k, c->rescan_list, c->list_counts, bmus);
   return hipGetLastError();

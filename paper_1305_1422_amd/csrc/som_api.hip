@@ -461,7 +461,7 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
   if (split) SOM_LAUNCH(c, launch_bmu_dense_h_collect(c, n, coarse, sub_fine ? kSubMay : kSubNo));
   else SOM_LAUNCH(c, launch_bmu_dense_collect(c, X, n));
   SOM_LAUNCH(c, launch_refine_lists_dense(c, X, W, bmus, coarse));
-  SOM_LAUNCH(c, launch_rescan_dense(c, X, W, bmus));
+  SOM_LAUNCH(c, launch_rescan_dense(c, X, W, bmus, coarse));
   return SOM_OK;
 }
 

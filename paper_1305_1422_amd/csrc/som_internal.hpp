@@ -378,6 +378,8 @@ constexpr int kListWords = kListCounts + kListTickets * kListTicketStride;
 constexpr int kUnitCounts = 4;     // first of the eight work-list lengths in it
 constexpr int kMaxWords = 12;      // ... and of the maxima: wmax_bits [2], qstep_max_bits, hot_wmax_bits, wlost_bits
 constexpr int kSubTicketWord = 17; // arrivals of k_subspace_coords
+constexpr int kTilesLeftWord = 18; // tiles of collected lists that the union leaves to the launch behind it ...
+constexpr int kListTickets2 = kListTicketStride / 2;   // ... and that one's entry counters, half a stride behind the others
 enum { kCertifyFp32 = 0, kCertifySplit = 1, kCertifyCsr = 2, kCertifyCoarse = 3, kCertifySelect = 4, kCertifySubspace = 5, kCertifySubspaceFine = 6, kCertifySubspaceCsrSelect = 7, kCertifySubspaceCsr = 8 };      // whose rounding bound the margin uses
 hipError_t launch_certify(som_ctx *c, int64_t n, int groups, int mode, const int64_t *indptr, int32_t *bmus,
                           bool hot = false, const int32_t *order = nullptr /* visit the instances in this order */,
@@ -386,7 +388,7 @@ hipError_t launch_margins(som_ctx *c, int64_t n, int mode, const int64_t *indptr
                           bool hot = false);   // test hook: the margin per instance
 hipError_t launch_refine_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
 hipError_t launch_refine_lists_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus, bool ordered /* appended in the two-level search's order */);
-hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus);
+hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32_t *bmus, bool ordered);
 hipError_t launch_refine_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
                              const float *values, const float *W, int32_t *bmus);
 hipError_t launch_refine_lists_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,

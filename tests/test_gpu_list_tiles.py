@@ -69,3 +69,34 @@ def test_non_finite_among_the_lists(oracle):
 ])
 def test_near_copies_in_and_out_of_order(oracle, n, rows, cols, dim, groups, filt):
     test_near_copies(oracle, n, rows, cols, dim, groups, filt)
+
+
+@pytest.mark.parametrize("n,rows,cols,dim,groups", [
+    (8191, 20, 30, 40, 30),        # one list too few for the union
+    (8192, 20, 30, 40, 30),
+    (8209, 25, 30, 130, 3),        # 250 near-copies each: unions near their room
+    (9000, 30, 30, 33, 2),         # lists beyond their own room, all of them scanned
+    (8300, 20, 30, 50, 60),        # tiles whose lists have little in common: left, a list at a time
+    (8500, 40, 30, 7, 90),
+    (8400, 20, 25, 3, 25),         # rows of three features
+])
+def test_near_copies_by_the_union(oracle, n, rows, cols, dim, groups):
+    test_near_copies(oracle, n, rows, cols, dim, groups, "two_level")
+
+
+@pytest.mark.parametrize("groups", [20, 60])
+def test_non_finite_among_the_unions(oracle, groups):
+    """The same in the order that the union takes them in, also where tiles are left to be compared list by list."""
+    rng = np.random.default_rng(8650)
+    rows, cols, dim, n = 20, 30, 24, 9000
+    k = rows * cols
+    base = rng.random((groups, dim)).astype(np.float32)
+    W = base[np.arange(k) * groups // k] + (rng.integers(-2, 3, size=(k, dim)) * np.float32(2.0 ** -22)).astype(np.float32)
+    X = (base[rng.integers(groups, size=n)] + rng.normal(0, 0.05, size=(n, dim))).astype(np.float32)
+    good = np.ones(n, dtype=bool)
+    good[7::501] = False
+    X[7::1002] = np.nan
+    X[508::1002, 5] = np.inf
+    b, (refined, collected, rescanned) = _search(W, X, rows, cols, "two_level")
+    assert collected >= 8192
+    assert np.array_equal(b[good], oracle.bmu_dense(X[good], W)) and np.all(b[~good] == 0)
