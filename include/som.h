@@ -401,7 +401,8 @@ int som_debug_select_margins(som_ctx *ctx, int64_t n, double *margin_out);
  *   mu_out [dim]    the centring vector;
  *   used [2]        used[0] = 0: the code book does not lie in so few directions, the pass ran on the full rows;
  *                   1, 2: it ran on the first 32 or on all 64 coordinates; used[1] = 1: so would the fine pass;
- *   loss [2]        the bounds on what the first 32 and all 64 coordinates leave of the largest centred node.
+ *   loss [2]        the bounds on what the first 32 and all 64 coordinates leave of the largest centred node; -1 if the
+ *                   basis alone already said that they would leave too much.
  * Errors: NULL pointers, n out of range -> SOM_ERR_INVALID_ARG; no two-level search or no subspace for this n,
  * dim and filter -> SOM_ERR_STATE.
  */

@@ -100,7 +100,13 @@ __global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ G, int pi
 // floor (or NaN) gives no direction: its row of L^-1 is zero.  Bound by 64 dependent steps: the reciprocal is a Newton
 // iteration (any basis will do that is nearly orthonormal), the square roots are left for the end, and blocks of 16 rows
 // and columns that are done or still zero are left out; two pivots are exchanged at a time, and the pieces of G are read sixteen entries at once (30.7 -> 21 us).
-__global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, int pieces, double *__restrict__ LinvT,
+// An attempt that the nodes' losses would end anyway ends here where the pivots say so: the last eight are what the directions before
+// each leave of a random combination of the nodes, and the largest loss was 1.3 to 3.4 times their root mean square wherever it was within
+// a factor of two of kSubspaceLoss (230 trained code books, 2,500 to 40,000 nodes, dense and text-like), so half of
+// `loss` draws the line: of 105 books of 50 to 80 clusters on toroids it ended 59 of the 70 hopeless attempts and 3 of the
+// 35 others, all three at the very edge.  A last direction far below the others says that the rank ends here.  40,000 nodes of 64
+// clusters, radius a quarter of the map: an epoch without an attempt 1,637 us, with one that the losses ended 1,717, with one that ends here 1,640.
+__global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, int pieces, float loss, double *__restrict__ LinvT,
                                                          SubspaceState *__restrict__ state) {
   __shared__ double s_col[2][2][kSub], s_row[2][2][kSub], s_linv[kSub][kSub + 1], s_pivot[kSub];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
@@ -185,11 +191,16 @@ __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restric
     }
   }
   __syncthreads();
-  if (tid == 0) {                 // the last directions still of the code book's own size: no use going on
-    double least = top;
-    for (int t = kSub - 8; t < kSub; ++t) least = fmin(least, s_pivot[t]);
+  if (tid == 0) {
+    double least = top, sum = 0.0;
+    for (int t = kSub - 8; t < kSub; ++t) {
+      least = fmin(least, s_pivot[t]);
+      sum += s_pivot[t];
+    }
+    const double limit = top * ((double)loss * (double)loss);
     state->use = state->fine = 0;
-    state->full = !(least <= top * (16.0 * kSubspaceLoss * kSubspaceLoss));
+    state->full = !(sum <= 8.0 * 0.25 * limit || least <= limit / 4096.0);
+    state->e32 = state->e64 = -1.f;      // not measured
   }
   if (tid < kSub) s_pivot[tid] = s_pivot[tid] > 0.0 ? 1.0 / sqrt(s_pivot[tid]) : 0.0;
   __syncthreads();
@@ -681,20 +692,20 @@ size_t subspace_vector_halves(const som_ctx *c) { return (size_t)((c->dim + 63) 
 
 int subspace_gram_pieces(const som_ctx *c) { return ((c->dim + 63) / 64 * 64 + kGramCols - 1) / kGramCols; }
 
-hipError_t launch_subspace_basis(som_ctx *c, const float *W) {
+hipError_t launch_subspace_basis(som_ctx *c, const float *W, float loss) {
   const int nK = (c->dim + 63) / 64, dimp = nK * 64, pieces = subspace_gram_pieces(c);
   double *linv = c->sub_G + (size_t)pieces * kSub * kSub;
   if (W) hipLaunchKernelGGL(k_subspace_sketch, dim3(kSub, nK), dim3(512), 0, c->stream, W, c->k, c->dim, dimp, c->mu, c->sub_S);
   hipLaunchKernelGGL(k_subspace_gram, dim3(pieces), dim3(256), 0, c->stream, c->sub_S, dimp, c->sub_G);
   if (pieces > 8) hipLaunchKernelGGL(k_gram_sum, dim3(kSub), dim3(256), 0, c->stream, c->sub_G, pieces);
-  hipLaunchKernelGGL(k_subspace_factor, dim3(1), dim3(256), 0, c->stream, c->sub_G, pieces > 8 ? 1 : pieces, linv, c->sub_state);
+  hipLaunchKernelGGL(k_subspace_factor, dim3(1), dim3(256), 0, c->stream, c->sub_G, pieces > 8 ? 1 : pieces, loss, linv, c->sub_state);
   hipLaunchKernelGGL(k_subspace_vectors, dim3(nK), dim3(512), 0, c->stream, c->sub_S, dimp, linv, c->sub_state, c->sub_Vp, c->sub_Vt,
                      c->sub_Vf);
   return hipGetLastError();
 }
 
 hipError_t launch_subspace(som_ctx *c, const float *W, int64_t n) {
-  const hipError_t e = launch_subspace_basis(c, W);
+  const hipError_t e = launch_subspace_basis(c, W, kSubspaceLoss);
   if (e != hipSuccess) return e;
   int blocks = (c->k + 31) / 32;
   if (blocks > kSubspaceParts) blocks = kSubspaceParts;

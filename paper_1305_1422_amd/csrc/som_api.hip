@@ -1101,11 +1101,12 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
     if (!later) SOM_LAUNCH(c, launch_epoch_params(c, q, !direct));
     if (dense) {
       rc = direct ? bmu_search_direct(c, c->d_data, c->d_n, codebook, bmus)
-                  : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true, cooled(radius0, radiusN, n_epochs, e, cooling));
+                  : bmu_search_dense(c, c->d_data, c->d_n, codebook, bmus, true, true,
+                                     e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0 /* the first code book is the caller's */);
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook, later);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
-                          true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0 /* the first code book is the caller's */);
+                          true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0);
       if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, bmus, codebook);
     }
     if (rc) return rc;

@@ -96,9 +96,9 @@ struct CandView {
 struct SubspaceState {
   int use;                 // the coarse pass runs on the coordinates: 1 the first 32 of them, 2 all 64, 0 it does not
   int fine;                // so do the fine and the collect pass, on all 64 of them
-  int full;                // set before the coordinates are looked at: the code book is of full rank for all one can tell
+  int full;                // set before the coordinates are looked at: too many directions, going by the last ones of the basis
   float e;                 // largest |w'_i - V^T u_i| (of the first 32, if use = 1)
-  float e32, e64;          // ... of the first 32, of all 64
+  float e32, e64;          // ... of the first 32, of all 64 (-1: not measured, `full`)
   float u, u1;             // largest |u_i|; largest sum_r |u_ir| times the largest |V_r|
   float ulost;             // largest |u_i - hi(u_i)|
   float wm;                // largest |w'_i|

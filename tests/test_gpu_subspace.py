@@ -21,6 +21,7 @@ def _book(rng, k, dim, rank, scale=1.0):
 
 
 def _minima(W, X, rows, cols):
+    """Block minima, margins, order of the nodes, centring vector, coordinates used [2], losses [2]."""
     from paper_1305_1422_amd import Som, capi
     k, dim = W.shape
     n = X.shape[0]
@@ -32,13 +33,13 @@ def _minima(W, X, rows, cols):
     used = torch.empty(2, dtype=torch.int32, device="cuda")
     loss = torch.empty(2, dtype=torch.float32, device="cuda")
     capi.som_debug_subspace(som.ctx, P.to_dev(X), som.codebook, m, margin, node_of, mu, used, loss)
-    out = m.cpu().numpy(), margin.cpu().numpy(), node_of.cpu().numpy(), mu.cpu().numpy(), int(used[0].item())
+    out = m.cpu().numpy(), margin.cpu().numpy(), node_of.cpu().numpy(), mu.cpu().numpy(), used.cpu().numpy(), loss.cpu().numpy()
     som.close()
     return out
 
 
 @pytest.mark.parametrize("rows,cols,dim,n,rank,want", [
-    (12, 25, 65, 300, 7, 1), (1, 33, 128, 1, 28, 1), (16, 16, 255, 257, 30, 2), (37, 7, 256, 255, 60, 2), (23, 45, 1000, 520, 12, 1),
+    (12, 25, 65, 300, 7, 1), (1, 33, 128, 1, 28, 1), (16, 16, 255, 257, 30, 2), (37, 7, 256, 255, 59, 2), (37, 7, 256, 255, 60, 0), (23, 45, 1000, 520, 12, 1),
     (40, 13, 2048, 64, 45, 2), (9, 57, 97, 1000, 90, 0), (20, 20, 300, 129, 0, 0), (5, 5, 70, 33, 3, 1)])
 @pytest.mark.parametrize("data", ["near", "offset", "sizes"])
 def test_block_minima_within_the_margin(rows, cols, dim, n, rank, want, data):
@@ -51,7 +52,7 @@ def test_block_minima_within_the_margin(rows, cols, dim, n, rank, want, data):
     if data == "sizes":                        # instances of very different norms, one at the centre
         X = X * np.exp2(rng.integers(-18, 18, (n, 1))).astype(np.float32)
         X[0] = 0.0
-    m, margin, node_of, mu, used = _minima(W, X, rows, cols)
+    m, margin, node_of, mu, (used, _), _ = _minima(W, X, rows, cols)
     if data == "near":
         assert used == want
     assert np.array_equal(np.sort(node_of), np.arange(k))
@@ -62,6 +63,25 @@ def test_block_minima_within_the_margin(rows, cols, dim, n, rank, want, data):
     err = np.abs(m.astype(np.float64) - want_m).max(0)
     assert np.all(err <= 0.5 * margin), (2 * err / margin).max()
     print(f"used {used}, worst error / half the margin {(2 * err / margin).max():.3f}, margin {margin.mean():.2e}")
+
+
+@pytest.mark.parametrize("rows,cols,dim", [(30, 40, 200), (50, 50, 300)])
+@pytest.mark.parametrize("fall,want", [(0.14, 2), (0.1, 0), (0.08, 0), (0.0, 0)])
+def test_too_many_directions_end_the_attempt_early(rows, cols, dim, fall, want):
+    """150 directions of sizes exp(-fall j).  What 61 of them leave of the largest node (0.3, 2.5, 7.5 and many times what may be
+    left) shows in the last pivots already: the nodes' coordinates are not even computed where it is too much."""
+    rng = np.random.default_rng(8050)
+    k = rows * cols
+    a = rng.standard_normal((k, 150)) * np.exp(-fall * np.arange(150))
+    b = np.linalg.qr(rng.standard_normal((dim, 150)))[0].T
+    W = (rng.random(dim) + a @ b).astype(np.float32)
+    X = W[rng.integers(0, k, 100)] + np.float32(0.01) * rng.standard_normal((100, dim)).astype(np.float32)
+    _, _, _, _, (used, fine), loss = _minima(W, X, rows, cols)
+    assert used == want and fine == 0
+    if want:
+        assert 0.0 < loss[1] < loss[0]
+    else:
+        assert np.all(loss == -1.0)
 
 
 @pytest.mark.parametrize("rows,cols,dim,n,map_type,grid", [(30, 36, 96, 3000, "toroid", "square"), (33, 35, 200, 1999, "planar", "hexagonal"),
