@@ -393,6 +393,16 @@ int som_debug_scores_csr(som_ctx *ctx, const int64_t *indptr, const int32_t *ind
 int som_debug_select_margins(som_ctx *ctx, int64_t n, double *margin_out);
 
 /*
+ * som_debug_subspace_always - test hook: from now on (enable != 0) searches on ctx try the subspace of the code book whatever
+ * their size, not only where it is estimated to pay (but only under the neighbourhoods, radii and kinds of map that it is for).
+ * som_debug_subspace_used - test hook: what the most recent BMU search on ctx did (synchronises the stream).  out is a HOST
+ * pointer to three int64 values: 1 if it tried the subspace; the coordinates its coarse pass ran on, as in
+ * som_debug_subspace; 1 if its fine pass ran on them too.
+ */
+int som_debug_subspace_always(som_ctx *ctx, int enable);
+int som_debug_subspace_used(som_ctx *ctx, int64_t *out);
+
+/*
  * som_debug_subspace - test hook: the coarse pass of the two-level search in the subspace of the code book, as an
  * epoch of a wide radius runs it.  All pointers are device pointers:
  *   block_min [ceil(k / 128)][n]  smallest coarse score per instance and block of 128 nodes, in the order node_of;

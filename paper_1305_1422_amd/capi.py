@@ -31,7 +31,7 @@ EXPORTS = [
     "som_bmu_distances_dense", "som_bmu_distances_csr", "som_bmu_distances_dense_static",
     "som_cool_schedule", "som_umatrix", "som_get_stats", "som_two_level_stats",
     "som_profile_enable", "som_profile_read",
-    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_subspace", "som_debug_mfma_f16", "som_debug_xcc_ids",
+    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_subspace", "som_debug_subspace_always", "som_debug_subspace_used", "som_debug_mfma_f16", "som_debug_xcc_ids",
 ]
 PROFILE_STAGES = ("bmu_dense_filter", "bmu_csr_filter", "bmu_exact", "node_sums", "smooth_divide", "prepare_dense")
 
@@ -118,6 +118,10 @@ def load():
     L.som_set_neighborhood.argtypes = [vp, i32, i32]
     L.som_debug_select_margins.restype = i32
     L.som_debug_select_margins.argtypes = [vp, i64, vp]
+    L.som_debug_subspace_always.restype = i32
+    L.som_debug_subspace_always.argtypes = [vp, i32]
+    L.som_debug_subspace_used.restype = i32
+    L.som_debug_subspace_used.argtypes = [vp, C.POINTER(i64)]
     L.som_debug_subspace.restype = i32
     L.som_debug_subspace.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     L.som_debug_scores_dense.restype = i32
@@ -374,6 +378,18 @@ def som_debug_select_margins(ctx, margin_out) -> None:
     """Test hook: the margins of the block selection for the coarse scores of the preceding som_debug_scores_dense."""
     import torch
     _check(ctx, load().som_debug_select_margins(ctx, margin_out.shape[0], _ptr(margin_out, torch.float64, "margin_out")))
+
+
+def som_debug_subspace_always(ctx, enable: bool) -> None:
+    """Test hook: try the subspace of the code book whatever the size of the search."""
+    _check(ctx, load().som_debug_subspace_always(ctx, 1 if enable else 0))
+
+
+def som_debug_subspace_used(ctx):
+    """Test hook: (tried, coordinates of the coarse pass 0/1/2, fine pass on them) of the most recent BMU search.  Synchronises."""
+    out = (C.c_int64 * 3)()
+    _check(ctx, load().som_debug_subspace_used(ctx, out))
+    return int(out[0]), int(out[1]), int(out[2])
 
 
 def som_debug_subspace(ctx, data, codebook, block_min, margin_out, node_of, mu_out, used, loss) -> None:

@@ -670,11 +670,11 @@ __global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__rest
 // ---------------------------------------------------------------- host side
 // Is the subspace worth its scratch for searches of n instances?  By default where the coarse pass would take some 150 us
 // more on the full rows (2 ns per million multiply-adds) than the basis and the coordinates take (80 us, and the read of the
-// hi planes); with the two-level search asked for by name wherever there are more features than coordinates.  Grows
-// with n, so that scratch for the largest call serves every smaller one.
+// hi planes), by whatever name the two-level search is asked for (below that it costs: 5,000 x 100 on 400 nodes, 117 us an epoch
+// without and 161 with it, 20,000 x 200 on 1,600 nodes 197 and 226).  Grows with n, so that scratch for the largest call serves every smaller one.
 bool subspace_eligible(const som_ctx *c, int64_t n) {
   if (c->dim <= kSub || c->dim > kPlaneMaxDim) return false;
-  return c->filter == SOM_FILTER_TWO_LEVEL || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceMinWork;
+  return c->sub_always || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceMinWork;
 }
 
 // Is the code book likely to lie in 64 directions?  One that enters an epoch was left by an epoch of about its radius
@@ -684,7 +684,7 @@ bool subspace_eligible(const som_ctx *c, int64_t n) {
 bool subspace_likely(const som_ctx *c, int64_t n, double radius) {
   if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
   if (radius <= 0.0)
-    return c->filter == SOM_FILTER_TWO_LEVEL || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceAloneWork;
+    return c->sub_always || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceAloneWork;
   return (double)c->rows * (double)c->cols <= kSubspaceMaxArea * radius * radius;
 }
 

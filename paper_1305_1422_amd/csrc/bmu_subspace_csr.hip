@@ -532,16 +532,17 @@ static int csr_pieces(const som_ctx *c) {
 size_t subspace_csr_part_floats(const som_ctx *c) { return (size_t)csr_pieces(c) * c->k * (kSub + 4) + (size_t)kCtMaxSlabs * kSub + 3 * (size_t)c->k; }
 
 // Worth its scratch for n rows of nnz nonzeros?  The sweep takes 0.13 ps per nonzero and node (hot block included); this 0.25 ms, three more
-// reads of the code book and 30 ps per nonzero, all measured at 50 x 50 nodes.  It has to promise three times its own cost.  On a
-// toroid the distance across the seam has a kink that every chosen node carries over the map: 1e-2 of the code book of a text-like
+// reads of the code book and 30 ps per nonzero, all measured at 50 x 50 nodes.  It has to promise three times its own cost, and
+// half as much again where the two-level search is asked for by name (epochs, sweep / coordinates: 20,000 rows of 20,000 features on 2,500 nodes,
+// which is 1.4 times, 1,356 / 1,046 us; 2,000 of 5,000 on 900 nodes, 0.1 times, 288 / 339).  On a toroid the distance across the seam has a kink that every chosen node carries over the map: 1e-2 of the code book of a text-like
 // set stays outside 64 directions at any radius, so planar maps only.  Grows with n and nnz.
 bool subspace_csr_eligible(const som_ctx *c, int64_t n, int64_t nnz) {
   const int64_t blocks = (c->k + 127) / 128;
   if (c->map_type != SOM_MAP_PLANAR || c->dim < kSubspaceCsrDim || blocks * c->n_cap * 4 > kTwoLevelMaxTable) return false;
-  if (c->filter == SOM_FILTER_TWO_LEVEL) return true;
-  if (c->filter != SOM_FILTER_AUTO || blocks < kTwoLevelMinBlocks) return false;
+  if (c->sub_always) return true;
+  if (c->filter != SOM_FILTER_TWO_LEVEL && (c->filter != SOM_FILTER_AUTO || blocks < kTwoLevelMinBlocks)) return false;
   const double own = 0.25e-3 + 3e-12 * (double)c->k * (double)c->dim + 3e-11 * (double)nnz;
-  return 1.3e-13 * (double)nnz * (double)c->k >= 3.0 * own;
+  return 1.3e-13 * (double)nnz * (double)c->k >= (c->filter == SOM_FILTER_AUTO ? 3.0 : 1.4) * own;
 }
 
 // The code book left by an epoch of this radius or more lies in 64 directions to 3e-5 of its norm up to 16 to 17 nodes per squared

@@ -447,6 +447,7 @@ static int bmu_search_dense(som_ctx *c, const float *X, int64_t n, const float *
   const bool coarse = two_level_ready(c, n);
   const bool sub = coarse && subspace_ready(c, n) && subspace_likely(c, n, radius), sub_fine = sub && c->sub_Y2;
   c->two_level_n = coarse ? n : 0;
+  c->sub_tried = sub;
   {
     StageTimer t(c, 0);
     rc = dense_filter_stage(c, X, n, split, coarse, sub ? W : nullptr);
@@ -568,6 +569,7 @@ static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indi
   if (rc) return rc;
   const SubspaceState *state = sub ? c->sub_state : nullptr;
   c->two_level_n = sub ? n : 0;
+  c->sub_tried = sub;
   if (sub) {
     StageTimer t(c, 1);
     SOM_LAUNCH(c, launch_csr_subspace(c, indptr, indices, values, n, W));
@@ -1268,10 +1270,41 @@ int som_debug_select_margins(som_ctx *c, int64_t n, double *margin_out) {
   return SOM_OK;
 }
 
+int som_debug_subspace_always(som_ctx *c, int enable) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  c->sub_always = enable != 0;
+  return SOM_OK;
+}
+
+int som_debug_subspace_used(som_ctx *c, int64_t *out) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  if (!out) return fail(c, SOM_ERR_INVALID_ARG, "out is NULL");
+  out[0] = c->sub_tried;
+  out[1] = out[2] = 0;
+  if (!c->sub_tried || !c->sub_state) return SOM_OK;
+  SubspaceState h;
+  hipError_t e = hipMemcpyAsync(&h, c->sub_state, sizeof(h), hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) return dev_fail(c, e, "som_debug_subspace_used");
+  out[1] = h.use;
+  out[2] = h.fine;
+  return SOM_OK;
+}
+
+namespace {
+struct TryAlways {            // the hooks below look at the subspace whatever the size
+  som_ctx *c;
+  int was;
+  explicit TryAlways(som_ctx *ctx) : c(ctx), was(ctx->sub_always) { c->sub_always = 1; }
+  ~TryAlways() { c->sub_always = was; }
+};
+}  // namespace
+
 int som_debug_subspace(som_ctx *c, const float *data, int64_t n, const float *codebook, float *block_min, double *margin_out,
                        int32_t *node_of, float *mu_out, int32_t *used, float *loss) {
   if (!c) return SOM_ERR_INVALID_ARG;
   if (!data || !codebook || !block_min || !margin_out || !node_of || !mu_out || !used || !loss) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  const TryAlways always(c);
   int rc = check_rows(c, n);
   if (!rc) rc = ensure_rows(c, n, true);
   if (rc) return rc;

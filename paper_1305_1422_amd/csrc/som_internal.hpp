@@ -251,6 +251,8 @@ struct som_ctx {
   float *sub_part;            // [kSubspaceParts][5] maxima per workgroup
   som::SubspaceState *sub_state;
   int sub_failed;             // there was no memory for it at n_cap instances
+  int sub_always;             // som_debug_subspace_always
+  int sub_tried;              // the last search tried it
   float *sub_cpart;           // partial sums of the sparse search's passes over the code book, subspace_csr_part_floats
   _Float16 *sub_Y1, *sub_Y2;  // the same of the instances, [n_cap] (sub_Y2: with enough features only)
   float *sub_yscale;          // [n_cap] their scales ...

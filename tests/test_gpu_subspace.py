@@ -20,6 +20,18 @@ def _book(rng, k, dim, rank, scale=1.0):
     return (scale * (rng.random(dim) + a @ b)).astype(np.float32)
 
 
+def _always(som):
+    """These shapes are far below those that try the subspace by themselves."""
+    from paper_1305_1422_amd import capi
+    capi.som_debug_subspace_always(som.ctx, True)
+    return som
+
+
+def _used(som):
+    from paper_1305_1422_amd import capi
+    return capi.som_debug_subspace_used(som.ctx)
+
+
 def _minima(W, X, rows, cols):
     """Block minima, margins, order of the nodes, centring vector, coordinates used [2], losses [2]."""
     from paper_1305_1422_amd import Som, capi
@@ -92,12 +104,14 @@ def test_epochs_of_a_schedule(oracle, rows, cols, dim, n, map_type, grid):
     rng = np.random.default_rng(8100 + dim)
     means = rng.random((11, dim))
     X = (means[rng.integers(11, size=n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
-    som = Som(rows, cols, dim, map_type, grid, codebook=torch.from_numpy(rng.random((rows * cols, dim)).astype(np.float32)),
-              filter="two_level")
+    som = _always(Som(rows, cols, dim, map_type, grid, codebook=torch.from_numpy(rng.random((rows * cols, dim)).astype(np.float32)),
+                      filter="two_level"))
     Xd = P.to_dev(X)
     capi.som_set_data_dense(som.ctx, Xd)
-    for radius in (15.0, 11.0, 7.0, 4.0, 1.0):
+    for radius, want in ((15.0, 0), (11.0, 1), (7.0, 1), (4.0, 1), (1.0, None)):      # (the first code book is random)
         P.epoch_parity_dense(oracle, som, X, Xd, radius, P.MAP[map_type], P.GRID[grid])
+        tried, use, _ = _used(som)
+        assert not tried if want is None else tried and (use > 0) == (want > 0)
         P.epoch_parity_dense(oracle, som, X[:501], Xd[:501].clone(), radius, P.MAP[map_type], P.GRID[grid])
     som.close()
 
@@ -111,13 +125,14 @@ def test_equal_rows_and_copies(oracle):
     k = rows * cols
     W = np.tile(rng.random((1, dim)).astype(np.float32), (k, 1))
     X = rng.random((n, dim)).astype(np.float32)
-    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level"))
     assert np.all(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy() == 0)
     W = _book(rng, k, dim, 9)
     W[600:1100] = W[50:550]
     som.codebook.copy_(P.to_dev(W))
     X = (W[rng.integers(600, 1100, n)] + 0.001 * rng.standard_normal((n, dim))).astype(np.float32)
     assert np.array_equal(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy(), oracle.bmu_dense(X, W))
+    assert _used(som)[:2] == (1, 1)
     som.close()
 
 
@@ -138,9 +153,31 @@ def test_non_finite_rows_go_the_general_way(oracle):
             V[41, 7] = spoil
         som = Som(rows, cols, dim, codebook=torch.from_numpy(V), filter="two_level")
         want = som.bmus(P.to_dev(X)).cpu().numpy()
-        got = som.train_epoch(P.to_dev(X), 20.0).cpu().numpy()
+        assert _used(som)[0] == 0
+        got = _always(som).train_epoch(P.to_dev(X), 20.0).cpu().numpy()
+        assert _used(som)[:2] == (1, 0)          # (the centring vector is the mean of these instances, and not finite)
         som.close()
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("dim", [100, 300])
+def test_non_finite_instances_on_the_coordinates(oracle, dim):
+    """The same among more instances than the centring vector is a sample of, which does not hold them: the others stay on the
+    coordinates, and they themselves, at no finite distance from any node, get the first."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8350)
+    rows, cols, n = 20, 30, 16401
+    W = _book(rng, rows * cols, dim, 8)
+    X = (W[rng.integers(0, rows * cols, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    good = np.ones(n, dtype=bool)
+    good[1::1202] = False                      # (every second row is in the sample)
+    X[1::2404, 3] = np.inf
+    X[1203::2404, 99] = np.nan
+    som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level"))
+    b = som.train_epoch(P.to_dev(X), 20.0).cpu().numpy()
+    assert _used(som) == (1, 1, int(dim >= 256))
+    som.close()
+    assert np.all(b[~good] == 0) and np.array_equal(b[good], oracle.bmu_dense(X[good], W))
 
 
 def test_recorded_epochs(oracle):
@@ -154,7 +191,7 @@ def test_recorded_epochs(oracle):
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
         Xd = P.to_dev(X)
-        som = Som(rows, cols, dim, codebook=torch.from_numpy(books[0]), filter="two_level")
+        som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(books[0]), filter="two_level"))
         capi.som_set_data_dense(som.ctx, Xd)
         start = P.to_dev(books[0])
         b = torch.empty(n, dtype=torch.int32, device="cuda")
@@ -196,8 +233,25 @@ def test_whole_search_on_the_coordinates(oracle, dim, rank, data):
     X = (W[rng.integers(0, k, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
     if data == "sizes":
         X = (X * np.exp2(rng.integers(-12, 12, (n, 1)))).astype(np.float32)
-    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level"))
     b = som.bmus(P.to_dev(X)).cpu().numpy()
+    tried, use, fine = _used(som)
+    assert tried and use and fine
     som.close()
     P.check_bmus_dense(oracle, X, W, b)
     assert np.array_equal(b, oracle.bmu_dense(X, W))
+
+
+@pytest.mark.parametrize("rows,cols,dim,n", [(20, 20, 100, 5000), (40, 40, 200, 2000)])
+@pytest.mark.parametrize("filt", ["two_level", "auto"])
+def test_small_searches_do_not_try_it(oracle, rows, cols, dim, n, filt):
+    """By whatever name: the basis alone would cost a small search more than the coordinates save."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8800 + dim)
+    W = _book(rng, rows * cols, dim, 9)
+    X = (W[rng.integers(0, rows * cols, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32)
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter=filt)
+    want = oracle.bmu_dense(X, W)
+    assert np.array_equal(som.bmus(P.to_dev(X)).cpu().numpy(), want) and _used(som)[0] == 0
+    assert np.array_equal(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy(), want) and _used(som)[0] == 0
+    som.close()

@@ -12,6 +12,13 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
+def _always(som):
+    """These sets are far below those that try the coordinates by themselves."""
+    from paper_1305_1422_amd import capi
+    capi.som_debug_subspace_always(som.ctx, True)
+    return som
+
+
 def _smooth_book(rng, rows, cols, dim, radius, csr):
     """What a batch update of that radius leaves: Gaussian means of rows placed at random nodes."""
     indptr, indices, values = csr
@@ -45,7 +52,7 @@ def test_epochs_on_the_coordinates(oracle, rows, cols, dim, n, radius, registere
     rng = np.random.default_rng(8800 + dim)
     csr = _edge_rows(sparse_zipf_csr(n, dim, 88, mean_len=40.0, max_len=200), dim)
     W = _smooth_book(rng, rows, cols, dim, radius, csr)
-    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    som = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level"))
     som.set_sparse_dense_filter(False)         # (short rows of a registered set would go through its planes)
     dev = P.csr_to_dev(csr)
     if registered:
@@ -75,7 +82,10 @@ def test_code_books_it_is_not_for(oracle, book):
     dev = P.csr_to_dev(csr)
     som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
     want = som.bmus(dev).cpu().numpy()
-    got = som.train_epoch(dev, 11.0).cpu().numpy()
+    got = som.train_epoch(dev, 11.0).cpu().numpy()           # a small set: not tried by itself
+    assert som.two_level_stats() == (0, 0) and np.array_equal(got, want)
+    som.codebook.copy_(torch.from_numpy(W))
+    got = _always(som).train_epoch(dev, 11.0).cpu().numpy()
     if book == "random":
         assert som.two_level_stats()[0] == 0
     som.close()
@@ -93,7 +103,7 @@ def test_ties_and_near_copies(oracle):
     W = _smooth_book(rng, rows, cols, dim, 12.0, csr)
     W[700:1000] = W[100:400]
     dev = P.csr_to_dev(csr)
-    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    som = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level"))
     b = som.train_epoch(dev, 12.0).cpu().numpy()
     assert som.two_level_stats()[0] > 0
     som.close()
@@ -110,7 +120,7 @@ def test_recorded_epochs(oracle):
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
         dev = P.csr_to_dev(csr)
-        som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(books[0]), filter="two_level")
+        som = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(books[0]), filter="two_level"))
         start = P.to_dev(books[0])
         b = torch.empty(n, dtype=torch.int32, device="cuda")
 
