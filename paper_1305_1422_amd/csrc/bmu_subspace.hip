@@ -672,9 +672,10 @@ __global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__rest
 // more on the full rows (2 ns per million multiply-adds) than the basis and the coordinates take (80 us, and the read of the
 // hi planes), by whatever name the two-level search is asked for (below that it costs: 5,000 x 100 on 400 nodes, 117 us an epoch
 // without and 161 with it, 20,000 x 200 on 1,600 nodes 197 and 226).  Grows with n, so that scratch for the largest call serves every smaller one.
-bool subspace_eligible(const som_ctx *c, int64_t n) {
-  if (c->dim <= kSub || c->dim > kPlaneMaxDim) return false;
-  return c->sub_always || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceMinWork;
+// alone: for a search outside an epoch.  Under the other neighbourhoods a code book has as many directions as nodes.
+bool subspace_eligible(const som_ctx *c, int64_t n, bool alone) {
+  if (c->dim <= kSub || c->dim > kPlaneMaxDim || c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
+  return c->sub_always || (double)n * (double)c->k * (double)(c->dim - kSub) >= (alone ? kSubspaceAloneWork : kSubspaceMinWork);
 }
 
 // Is the code book likely to lie in 64 directions?  One that enters an epoch was left by an epoch of about its radius
@@ -682,9 +683,7 @@ bool subspace_eligible(const som_ctx *c, int64_t n) {
 // outside an epoch (radius 0) may bring any: it is tried where the work it may save is several times what a
 // failure costs (40 us, most of it the factor, which finds out).
 bool subspace_likely(const som_ctx *c, int64_t n, double radius) {
-  if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
-  if (radius <= 0.0)
-    return c->sub_always || (double)n * (double)c->k * (double)(c->dim - kSub) >= kSubspaceAloneWork;
+  if (radius <= 0.0) return subspace_eligible(c, n, true);
   return (double)c->rows * (double)c->cols <= kSubspaceMaxArea * radius * radius;
 }
 

@@ -538,6 +538,7 @@ size_t subspace_csr_part_floats(const som_ctx *c) { return (size_t)csr_pieces(c)
 // set stays outside 64 directions at any radius, so planar maps only.  Grows with n and nnz.
 bool subspace_csr_eligible(const som_ctx *c, int64_t n, int64_t nnz) {
   const int64_t blocks = (c->k + 127) / 128;
+  if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact) return false;
   if (c->map_type != SOM_MAP_PLANAR || c->dim < kSubspaceCsrDim || blocks * c->n_cap * 4 > kTwoLevelMaxTable) return false;
   if (c->sub_always) return true;
   if (c->filter != SOM_FILTER_TWO_LEVEL && (c->filter != SOM_FILTER_AUTO || blocks < kTwoLevelMinBlocks)) return false;
@@ -548,8 +549,7 @@ bool subspace_csr_eligible(const som_ctx *c, int64_t n, int64_t nnz) {
 // The code book left by an epoch of this radius or more lies in 64 directions to 3e-5 of its norm up to 16 to 17 nodes per squared
 // radius on planar maps (text-like rows, square and hexagonal, 400 to 10,000 nodes: 1e-5 at 15, 8e-5 at 21).
 bool subspace_csr_likely(const som_ctx *c, double radius) {
-  if (c->nb_function != SOM_NEIGHBORHOOD_GAUSSIAN || c->nb_compact || radius <= 0.0) return false;
-  return (double)c->rows * (double)c->cols <= kSubspaceCsrMaxArea * radius * radius;
+  return radius > 0.0 && (double)c->rows * (double)c->cols <= kSubspaceCsrMaxArea * radius * radius;
 }
 
 hipError_t launch_csr_subspace(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n, const float *W) {

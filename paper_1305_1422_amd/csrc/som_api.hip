@@ -112,7 +112,7 @@ static bool two_level_ready(const som_ctx *c, int64_t n) {
 }
 
 static bool subspace_ready(const som_ctx *c, int64_t n) {
-  return subspace_eligible(c, n) && !c->sub_failed && c->sub_state != nullptr && c->sub_Y1 != nullptr;
+  return subspace_eligible(c, n, false) && !c->sub_failed && c->sub_state != nullptr && c->sub_Y1 != nullptr;
 }
 
 static void free_two_level_tables(som_ctx *c) {
@@ -200,23 +200,37 @@ static bool allocate_subspace(som_ctx *c, bool fine, bool csr) {
   return !fine || c->sub_Y2 != nullptr || (dev_alloc(&c->sub_err2, N) && dev_alloc(&c->sub_Y2, N * kSub * 2));
 }
 
-static void ensure_subspace(som_ctx *c, bool fine, bool csr) {
-  if (!c->sub_failed && !allocate_subspace(c, fine, csr)) give_up_subspace(c);
+static bool has_subspace(const som_ctx *c, bool fine, bool csr) {
+  return c->sub_state && c->sub_Y1 && (!fine || c->sub_Y2) && (!csr || (c->sub_cpart && c->node_of && c->coarse_min));
 }
+
+// A call that is being recorded does without it if it is not there: what the search needs came with any call of this size
+// before, the subspace only with those that may use it.
+static void ensure_subspace(som_ctx *c, bool fine, bool csr) {
+  if (c->sub_failed || has_subspace(c, fine, csr)) return;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (!allocate_subspace(c, fine, csr)) give_up_subspace(c);
+}
+
+// What a search may do with the subspace of the code book: the calls that never try it hold no memory for it.
+enum SearchKind { kSearchPlain, kSearchAlone, kSearchEpoch };      // never; a search of its own; one of an epoch
 
 // Scratch that scales with the number of instances; grown (never shrunk) on demand.  `filtered`: a filter pass
 // will run on them (false: the direct search, or an update alone).
-// sub: the search may run in the subspace of the code book.
-static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, bool sub = true) {
+static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, SearchKind kind = kSearchEpoch) {
   const bool split = dense && filtered && uses_planes(c);
   // sized for the rows the scratch is (or will be) allocated for, so that it serves every n up to n_cap
   const bool coarse = split && two_level(c, n > c->n_cap ? n : c->n_cap);
-  const bool subspace = sub && coarse && !c->sub_failed && subspace_eligible(c, n > c->n_cap ? n : c->n_cap);
+  const bool subspace = kind != kSearchPlain && coarse && !c->sub_failed && subspace_eligible(c, n > c->n_cap ? n : c->n_cap, kind == kSearchAlone);
   const bool need_partial = (dense && c->partial == nullptr) || (dense && filtered && needs_centred_copy(c) && c->Wc == nullptr) ||
                             (filtered && c->collect_list == nullptr) ||
                             (split && (c->Xh == nullptr || c->Wh == nullptr)) ||
                             (coarse && (c->Xh1 == nullptr || c->Wh1 == nullptr || c->coarse_min == nullptr || c->node_of == nullptr)) ||
-                            (subspace && (c->sub_Y1 == nullptr || c->sub_state == nullptr));
+                            (subspace && !has_subspace(c, c->dim >= kSubspaceFineDim, false));
   if (n <= c->n_cap && !need_partial) return SOM_OK;
   if (n > c->n_cap) {
     (void)hipStreamSynchronize(c->stream);
@@ -272,7 +286,11 @@ static int ensure_rows(som_ctx *c, int64_t n, bool dense, bool filtered = true, 
         return fail(c, SOM_ERR_ALLOC, "cannot allocate the fp16 plane of %lld instances", (long long)c->n_cap);
       }
     }
-    const int rc = ensure_two_level_tables(c);
+    int rc = ensure_two_level_tables(c);
+    if (rc && c->sub_state) {
+      give_up_subspace(c);
+      rc = ensure_two_level_tables(c);
+    }
     if (rc) return rc;
   }
   if (subspace) ensure_subspace(c, c->dim >= kSubspaceFineDim, false);
@@ -555,16 +573,16 @@ static int bmu_search_csr_planes(som_ctx *c, const int64_t *indptr, const int32_
   return SOM_OK;
 }
 
-// radius as in bmu_search_dense.
+// radius as in bmu_search_dense (a search of its own is not tried; epoch: it belongs to one all the same).
 static int bmu_search_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
                           int64_t n, int64_t nnz, const float *W, int32_t *bmus, bool have_xn, bool cleared = false,
-                          double radius = 0.0) {
+                          bool epoch = false, double radius = 0.0) {
   if (have_xn && c->csrd_valid && c->csrd_on) return bmu_search_csr_planes(c, indptr, indices, values, n, W, bmus, cleared);
   // in the subspace of the code book if the device finds that it may, and then nothing is left for the sweep to do
-  const bool eligible = subspace_csr_eligible(c, n, nnz);
+  const bool eligible = epoch && subspace_csr_eligible(c, n, nnz);
   int rc = ensure_csr(c, n, nnz, eligible);
   if (rc) return rc;
-  const bool sub = eligible && !c->sub_failed && subspace_csr_likely(c, radius);
+  const bool sub = eligible && !c->sub_failed && has_subspace(c, true, true) && subspace_csr_likely(c, radius);
   rc = prepare_csr(c, indptr, values, n, W, have_xn, cleared, sub);
   if (rc) return rc;
   const SubspaceState *state = sub ? c->sub_state : nullptr;
@@ -736,7 +754,7 @@ static int registered_csr_dense(som_ctx *c) {
   const int64_t n = c->d_n, nnz = c->d_nnz;
   if (!c->csrd_enabled || c->data_kind != 2 || !uses_planes(c) || c->dim > kCsrDenseMaxDim || nnz < 1) return SOM_OK;
   if ((double)nnz < kCsrDenseMinDensity * (double)n * (double)c->dim) return SOM_OK;
-  int rc = ensure_rows(c, n, true, true, false);          // planes, centred code book (may reset csrd_valid: set again below)
+  int rc = ensure_rows(c, n, true, true, kSearchPlain);          // planes, centred code book (may reset csrd_valid: set again below)
   if (rc) return rc;
   c->csrd_valid = 1;
   if (n > c->csrd_n_cap || !c->csrd_mu) {
@@ -902,7 +920,7 @@ int som_bmus_dense(som_ctx *c, const float *data, int64_t n, const float *codebo
   int rc = check_rows(c, n);
   const bool reg = is_registered_dense(c, data, n);
   const bool direct = !rc && direct_search(c, n, reg);
-  if (!rc && !direct) rc = ensure_rows(c, n, true);
+  if (!rc && !direct) rc = ensure_rows(c, n, true, true, kSearchAlone);
   if (!rc && !direct && reg) rc = registered_norms(c);
   if (rc) return rc;
   return direct ? bmu_search_direct(c, data, n, codebook, bmus) : bmu_search_dense(c, data, n, codebook, bmus, reg);
@@ -1022,7 +1040,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
   }
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), true));
-  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true, radius);
+  rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true, true, radius);
   if (rc) return rc;
   return update_csr(c, indptr, indices, values, n, bmus, codebook);
 }
@@ -1108,7 +1126,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
       if (!rc) rc = update_dense(c, c->d_data, c->d_n, bmus, codebook, later);
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
-                          true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0);
+                          true, true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0);
       if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, bmus, codebook);
     }
     if (rc) return rc;
@@ -1150,15 +1168,15 @@ int som_set_neighborhood(som_ctx *c, int function, int compact_support) {
   if (direct && !c->H2) {
     const size_t width = (size_t)(c->map_type == SOM_MAP_TOROID ? c->cols : 2 * c->cols - 1) + 16;
     const size_t classes = c->grid_type == SOM_GRID_HEXAGONAL ? 3 : 1;
-    if (!dev_alloc(&c->H2, classes * c->rows * width))
+    if (!dev_alloc_first(c, &c->H2, classes * c->rows * width))
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the neighbourhood table");
   }
   if (function == SOM_NEIGHBORHOOD_BUBBLE && !c->row_hash) {
     // a bubble makes whole classes of nodes bit-identical: the searches take the duplicates out first
     int slots = 64;
     while (slots < 2 * c->k) slots *= 2;
-    if (!(dev_alloc(&c->row_hash, (size_t)c->k) && dev_alloc(&c->dedup_keys, (size_t)slots) &&
-          dev_alloc(&c->dedup_lowest, (size_t)slots))) {
+    if (!(dev_alloc_first(c, &c->row_hash, (size_t)c->k) && dev_alloc_first(c, &c->dedup_keys, (size_t)slots) &&
+          dev_alloc_first(c, &c->dedup_lowest, (size_t)slots))) {
       dev_free(c->row_hash); dev_free(c->dedup_keys); dev_free(c->dedup_lowest);
       return fail(c, SOM_ERR_ALLOC, "cannot allocate the duplicate-row table");
     }

@@ -331,7 +331,7 @@ int bmu_dense_h_fine_groups(const som_ctx *c, int64_t n);
 enum SubspaceUse { kSubNo = 0, kSubMay = 1, kSubOnly = 2 };
 hipError_t launch_bmu_coarse(som_ctx *c, int64_t n, float *dump, SubspaceUse sub = kSubNo);
 // bmu_subspace.hip
-bool subspace_eligible(const som_ctx *c, int64_t n);
+bool subspace_eligible(const som_ctx *c, int64_t n, bool alone);
 bool subspace_likely(const som_ctx *c, int64_t n, double radius);
 size_t subspace_vector_halves(const som_ctx *c);     // size of sub_Vp and of sub_Vt
 int subspace_gram_pieces(const som_ctx *c);

@@ -255,3 +255,26 @@ def test_small_searches_do_not_try_it(oracle, rows, cols, dim, n, filt):
     assert np.array_equal(som.bmus(P.to_dev(X)).cpu().numpy(), want) and _used(som)[0] == 0
     assert np.array_equal(som.train_epoch(P.to_dev(X), 20.0).cpu().numpy(), want) and _used(som)[0] == 0
     som.close()
+
+
+def test_only_the_gaussian_neighbourhood_holds_memory_for_it():
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8900)
+    rows, cols, dim, n = 20, 25, 260, 60_000
+    W = _book(rng, rows * cols, dim, 9)
+    Xd = P.to_dev((W[rng.integers(0, rows * cols, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32))
+    b = torch.empty(n, dtype=torch.int32, device="cuda")
+    held = {}
+    for function, compact in (("gaussian", False), ("gaussian", True), ("bubble", False)):
+        som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level"))
+        som.set_neighborhood(function, compact)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        som.train_epoch(Xd, 8.0, bmus=b)
+        torch.cuda.synchronize()
+        held[function, compact] = before - torch.cuda.mem_get_info()[0]
+        assert _used(som)[0] == int((function, compact) == ("gaussian", False))
+        som.close()
+    room = n * 396
+    assert held["gaussian", False] >= held["gaussian", True] + 3 * room // 4
+    assert held["gaussian", False] >= held["bubble", False] + 3 * room // 4

@@ -143,3 +143,79 @@ def test_recorded_epochs(oracle):
             assert np.array_equal(b.cpu().numpy(), eager)
         stream.synchronize()
         som.close()
+
+
+def _held(call):
+    """Device memory that the call leaves allocated, besides torch's."""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved()
+    call()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0] - torch.cuda.memory_reserved()
+
+
+def test_only_epochs_hold_memory_for_it(oracle):
+    """Searches of their own and the other neighbourhoods never try the coordinates: 396 bytes an instance that they do not hold."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(9200)
+    rows, cols, dim, n = 20, 20, 1100, 60_000
+    csr = sparse_zipf_csr(n, dim, 92, mean_len=5.0, max_len=20)
+    W = _smooth_book(rng, rows, cols, dim, 8.0, csr)
+    dev = P.csr_to_dev(csr)
+    b = torch.empty(n, dtype=torch.int32, device="cuda")
+    room = n * 396
+
+    def context(function="gaussian", compact=False):
+        som = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level"))
+        som.set_neighborhood(function, compact)
+        return som
+
+    som = context()
+    own = _held(lambda: som.bmus(dev, b))
+    want = b.cpu().numpy()
+    epoch = _held(lambda: som.train_epoch(dev, 8.0, bmus=b))
+    assert capi.som_debug_subspace_used(som.ctx)[1] > 0 and np.array_equal(b.cpu().numpy(), want)
+    assert epoch >= room
+    som.close()
+    for kind in (("bubble", False), ("gaussian", True)):
+        som = context(*kind)
+        held = _held(lambda: som.train_epoch(dev, 8.0, bmus=b))
+        assert capi.som_debug_subspace_used(som.ctx)[0] == 0
+        assert held <= own + room // 4, (held, own, room)
+        som.close()
+
+
+def test_an_epoch_recorded_before_any_other(oracle):
+    """What a search needs came with a search of its own; the coordinates did not, and nothing can be allocated while recording:
+    the epoch is recorded without them."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(9300)
+    rows, cols, dim, n = 20, 30, 1100, 900
+    csr = sparse_zipf_csr(n, dim, 93, mean_len=30.0, max_len=100)
+    W = _smooth_book(rng, rows, cols, dim, 9.0, csr)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        dev = P.csr_to_dev(csr)
+        other = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level"))
+        eager = other.train_epoch(dev, 9.0).cpu().numpy()          # (loads the kernels)
+        assert capi.som_debug_subspace_used(other.ctx)[1] > 0
+        som = _always(Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level"))
+        start = P.to_dev(W)
+        b = torch.empty(n, dtype=torch.int32, device="cuda")
+        som.bmus(dev, b)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            som.codebook.copy_(start)
+            som.train_epoch(dev, 9.0, bmus=b)
+        for _ in range(3):
+            b.fill_(-1)
+            graph.replay()
+            assert np.array_equal(b.cpu().numpy(), eager)
+            np.testing.assert_allclose(som.codebook.cpu().numpy(), other.codebook.cpu().numpy(), rtol=0, atol=1e-5 * np.abs(W).max())
+            other.codebook.copy_(start)
+            assert np.array_equal(other.train_epoch(dev, 9.0).cpu().numpy(), eager)
+        assert capi.som_debug_subspace_used(som.ctx)[0] == 0
+        stream.synchronize()
+        som.close()
+        other.close()
