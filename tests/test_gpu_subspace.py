@@ -265,7 +265,8 @@ def test_only_the_gaussian_neighbourhood_holds_memory_for_it():
     Xd = P.to_dev((W[rng.integers(0, rows * cols, n)] + 0.05 * rng.standard_normal((n, dim))).astype(np.float32))
     b = torch.empty(n, dtype=torch.int32, device="cuda")
     held = {}
-    for function, compact in (("gaussian", False), ("gaussian", True), ("bubble", False)):
+    kinds = (("gaussian", False), ("gaussian", True), ("bubble", False))
+    for function, compact in kinds + kinds:    # (the second time nothing is left to load)
         som = _always(Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level"))
         som.set_neighborhood(function, compact)
         torch.cuda.synchronize()
