@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ G, int pi
 // each leave of a random combination of the nodes, and the largest loss was 1.3 to 3.4 times their root mean square wherever it was within
 // a factor of two of kSubspaceLoss (230 trained code books, 2,500 to 40,000 nodes, dense and text-like), so half of
 // `loss` draws the line: of 105 books of 50 to 80 clusters on toroids it ended 59 of the 70 hopeless attempts and 3 of the
-// 35 others, all three at the very edge.  A last direction far below the others says that the rank ends here.  40,000 nodes of 64
+// 35 others, all three at the very edge.  A last direction of a sixteenth of the limit says that the rank ends here.  40,000 nodes of 64
 // clusters, radius a quarter of the map: an epoch without an attempt 1,637 us, with one that the losses ended 1,717, with one that ends here 1,640.
 __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restrict__ G, int pieces, float loss, double *__restrict__ LinvT,
                                                          SubspaceState *__restrict__ state) {
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void k_subspace_factor(const double *__restric
     }
     const double limit = top * ((double)loss * (double)loss);
     state->use = state->fine = 0;
-    state->full = !(sum <= 8.0 * 0.25 * limit || least <= limit / 4096.0);
+    state->full = !(sum <= 8.0 * 0.25 * limit || least <= limit / 256.0);
     state->e32 = state->e64 = -1.f;      // not measured
   }
   if (tid < kSub) s_pivot[tid] = s_pivot[tid] > 0.0 ? 1.0 / sqrt(s_pivot[tid]) : 0.0;

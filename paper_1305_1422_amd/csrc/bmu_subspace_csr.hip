@@ -553,7 +553,7 @@ bool subspace_csr_likely(const som_ctx *c, double radius) {
 }
 
 hipError_t launch_csr_subspace(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n, const float *W) {
-  const hipError_t e = launch_subspace_basis(c, nullptr, kSubspaceLossCsr);
+  const hipError_t e = launch_subspace_basis(c, nullptr, 2.f * kSubspaceLossCsr);      // (an attempt costs a ninth of what it may save)
   if (e != hipSuccess) return e;
   const int nK = (c->dim + 31) / 32, pieces = csr_pieces(c), per = (nK + pieces - 1) / pieces;
   const int tiles = (c->k + kCsrNodes - 1) / kCsrNodes;

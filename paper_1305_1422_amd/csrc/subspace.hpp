@@ -89,7 +89,7 @@ __device__ __forceinline__ bool last_maxima(float (&f)[5], float *__restrict__ p
 }
 
 // The basis, up to its vectors (bmu_subspace.hip): W, mu -> sub_Vp, sub_Vt (sub_Vf).  W null: the sketch sub_S is there.  loss: the
-// share of the largest |w'| that may lie outside.
+// share of the largest |w'| that may lie outside, for the end of an attempt.
 hipError_t launch_subspace_basis(som_ctx *c, const float *W, float loss);
 
 }  // namespace som
