@@ -420,6 +420,21 @@ int som_debug_subspace(som_ctx *ctx, const float *data, int64_t n, const float *
                        double *margin_out, int32_t *node_of, float *mu_out, int32_t *used, float *loss);
 
 /*
+ * som_debug_subspace_fine, som_debug_subspace_csr - test hooks: the passes of som_debug_subspace's kind that it leaves out, on the
+ * same data whatever the device decides (what it decided is in used [2], as there; nothing holds where used[0], for the
+ * fine pass used[1], is 0).  The fine pass of a dense search: scores [n][k], mu_out [dim], margin_out [n] as som_debug_scores_dense
+ * has them.  Both passes of a sparse search (rows are not centred, only the nodes): block_min, node_of and, as the
+ * margins of the block selection, select_margin_out [n] as som_debug_subspace has them; scores, mu_out and
+ * margin_out of the fine pass.
+ * Errors: as som_debug_subspace; fewer features than the fine pass takes -> SOM_ERR_STATE.
+ */
+int som_debug_subspace_fine(som_ctx *ctx, const float *data, int64_t n, const float *codebook, float *scores, float *mu_out,
+                            double *margin_out, int32_t *used);
+int som_debug_subspace_csr(som_ctx *ctx, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
+                           int64_t nnz, const float *codebook, float *block_min, double *select_margin_out, int32_t *node_of,
+                           float *scores, double *margin_out, float *mu_out, int32_t *used);
+
+/*
  * som_debug_mfma_f16 - test hook (not an operation of the paper): `count` independent
  * executions of the 32x32x16 fp16 matrix instruction, D = A B^T + C with A [32][16] and
  * B [32][16] given as fp16 bit patterns, C and D [32][32] fp32, problem t at offsets 512 t

@@ -31,7 +31,7 @@ EXPORTS = [
     "som_bmu_distances_dense", "som_bmu_distances_csr", "som_bmu_distances_dense_static",
     "som_cool_schedule", "som_umatrix", "som_get_stats", "som_two_level_stats",
     "som_profile_enable", "som_profile_read",
-    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_subspace", "som_debug_subspace_always", "som_debug_subspace_used", "som_debug_mfma_f16", "som_debug_xcc_ids",
+    "som_set_filter", "som_set_smoothing", "som_set_sparse_hot_block", "som_sparse_hot_block_active", "som_set_sparse_dense_filter", "som_sparse_dense_filter_active", "som_set_neighborhood", "som_set_scale_cooling", "som_validate_csr", "som_debug_scores_dense", "som_debug_scores_csr", "som_debug_select_margins", "som_debug_subspace", "som_debug_subspace_always", "som_debug_subspace_used", "som_debug_subspace_fine", "som_debug_subspace_csr", "som_debug_mfma_f16", "som_debug_xcc_ids",
 ]
 PROFILE_STAGES = ("bmu_dense_filter", "bmu_csr_filter", "bmu_exact", "node_sums", "smooth_divide", "prepare_dense")
 
@@ -122,6 +122,10 @@ def load():
     L.som_debug_subspace_always.argtypes = [vp, i32]
     L.som_debug_subspace_used.restype = i32
     L.som_debug_subspace_used.argtypes = [vp, C.POINTER(i64)]
+    L.som_debug_subspace_fine.restype = i32
+    L.som_debug_subspace_fine.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp]
+    L.som_debug_subspace_csr.restype = i32
+    L.som_debug_subspace_csr.argtypes = [vp, vp, vp, vp, i64, i64, vp, vp, vp, vp, vp, vp, vp, vp]
     L.som_debug_subspace.restype = i32
     L.som_debug_subspace.argtypes = [vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     L.som_debug_scores_dense.restype = i32
@@ -402,6 +406,28 @@ def som_debug_subspace(ctx, data, codebook, block_min, margin_out, node_of, mu_o
                                           _ptr(margin_out, torch.float64, "margin_out"),
                                           _ptr(node_of, torch.int32, "node_of"), _ptr(mu_out, torch.float32, "mu_out"),
                                           _ptr(used, torch.int32, "used"), _ptr(loss, torch.float32, "loss")))
+
+
+def som_debug_subspace_fine(ctx, data, codebook, scores, mu_out, margin_out, used) -> None:
+    """Test hook: scores [n][k] of the fine pass in the code book's subspace and its margins [n] (float64)."""
+    import torch
+    _check(ctx, load().som_debug_subspace_fine(ctx, _ptr(data, torch.float32, "data"), data.shape[0],
+                                               _ptr(codebook, torch.float32, "codebook"), _ptr(scores, torch.float32, "scores"),
+                                               _ptr(mu_out, torch.float32, "mu_out"), _ptr(margin_out, torch.float64, "margin_out"),
+                                               _ptr(used, torch.int32, "used")))
+
+
+def som_debug_subspace_csr(ctx, indptr, indices, values, codebook, block_min, select_margin_out, node_of, scores, margin_out, mu_out,
+                           used) -> None:
+    """Test hook: block minima and scores of the sparse search in the code book's subspace, with their margins."""
+    import torch
+    _check(ctx, load().som_debug_subspace_csr(ctx, _ptr(indptr, torch.int64, "indptr"), _ptr(indices, torch.int32, "indices"),
+                                              _ptr(values, torch.float32, "values"), indptr.shape[0] - 1, indices.shape[0],
+                                              _ptr(codebook, torch.float32, "codebook"), _ptr(block_min, torch.float32, "block_min"),
+                                              _ptr(select_margin_out, torch.float64, "select_margin_out"),
+                                              _ptr(node_of, torch.int32, "node_of"), _ptr(scores, torch.float32, "scores"),
+                                              _ptr(margin_out, torch.float64, "margin_out"), _ptr(mu_out, torch.float32, "mu_out"),
+                                              _ptr(used, torch.int32, "used")))
 
 
 def som_debug_scores_dense(ctx, data, codebook, scores, mu_out, margin_out) -> None:

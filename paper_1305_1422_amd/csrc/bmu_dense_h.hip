@@ -478,6 +478,19 @@ static FineSubspace fine_subspace(const som_ctx *c, SubspaceUse sub) {
                       c->sub_yscale, sub == kSubOnly, nullptr};
 }
 
+// Every score of the fine pass on the coordinates in the code book's subspace, dump [n][k] (test hook): U2 and Y2 are there whatever was decided.
+hipError_t launch_subspace_scores(som_ctx *c, int64_t n, float *dump) {
+  const int groups = bmu_dense_h_groups(c, n);
+  const int64_t tiles = (n + 64 * kHWI - 1) / (64 * kHWI);
+  const int64_t blocks = (tiles + 7) / 8 * 8 * groups;
+  hipLaunchKernelGGL((k_bmu_dense_h<kHDump>), dim3((unsigned)blocks), dim3(128 * kHWI), 0, c->stream,
+                     reinterpret_cast<const float *>(c->sub_Y2), reinterpret_cast<const float *>(c->sub_U2), c->wn32, c->sub_yscale,
+                     &c->sub_state->uscale, n, c->k, kSub / 32, kSub / 32, groups, CandView{c->cand_val, c->cand_idx, c->cand_over}, dump,
+                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, c->node_of,
+                     FineSubspace{nullptr, nullptr, nullptr, nullptr, 0, nullptr});
+  return hipGetLastError();
+}
+
 // Second pass of the two-level search: the split-fp16 filter over the instance tiles of the order
 // c->sort_val[0] and the node blocks c->tile_list lists for each (c->tile_cnt of them).
 hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n, SubspaceUse sub) {

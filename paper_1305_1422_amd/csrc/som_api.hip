@@ -1341,6 +1341,55 @@ int som_debug_subspace(som_ctx *c, const float *data, int64_t n, const float *co
   return SOM_OK;
 }
 
+int som_debug_subspace_fine(som_ctx *c, const float *data, int64_t n, const float *codebook, float *scores, float *mu_out,
+                            double *margin_out, int32_t *used) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  if (!data || !codebook || !scores || !mu_out || !margin_out || !used) return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  const TryAlways always(c);
+  int rc = check_rows(c, n);
+  if (!rc) rc = ensure_rows(c, n, true);
+  if (!rc) rc = ensure_candidates(c, n, true);
+  if (rc) return rc;
+  if (!two_level_ready(c, n) || !subspace_ready(c, n) || !c->sub_Y2) return fail(c, SOM_ERR_STATE, "no fine pass in the subspace for %lld instances", (long long)n);
+  rc = prepare_dense(c, data, n, codebook, false, false);
+  if (rc) return rc;
+  SOM_LAUNCH(c, launch_subspace(c, codebook, n));
+  SOM_LAUNCH(c, launch_subspace_scores(c, n, scores));
+  SOM_LAUNCH(c, launch_margins(c, n, kCertifySubspaceFine, nullptr, margin_out));
+  SOM_LAUNCH(c, hipMemcpyAsync(mu_out, c->mu, (size_t)c->dim * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(used, &c->sub_state->use, 2 * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  return SOM_OK;
+}
+
+int som_debug_subspace_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n, int64_t nnz,
+                           const float *codebook, float *block_min, double *select_margin_out, int32_t *node_of, float *scores,
+                           double *margin_out, float *mu_out, int32_t *used) {
+  if (!c) return SOM_ERR_INVALID_ARG;
+  if (!codebook || !block_min || !select_margin_out || !node_of || !scores || !margin_out || !mu_out || !used)
+    return fail(c, SOM_ERR_INVALID_ARG, "NULL pointer argument");
+  const TryAlways always(c);
+  int rc = check_csr(c, indptr, indices, values, n, nnz);
+  if (!rc) rc = ensure_rows(c, n, false);
+  if (rc) return rc;
+  const bool eligible = subspace_csr_eligible(c, n, nnz);
+  rc = ensure_csr(c, n, nnz, eligible);
+  if (rc) return rc;
+  if (!eligible || !has_subspace(c, true, true)) return fail(c, SOM_ERR_STATE, "no subspace for %lld sparse instances", (long long)n);
+  rc = prepare_csr(c, indptr, values, n, codebook, false, false, true);
+  if (rc) return rc;
+  SOM_LAUNCH(c, launch_csr_subspace(c, indptr, indices, values, n, codebook));
+  SOM_LAUNCH(c, launch_bmu_coarse(c, n, nullptr, kSubOnly));
+  SOM_LAUNCH(c, launch_margins(c, n, kCertifySubspaceCsrSelect, nullptr, select_margin_out));
+  SOM_LAUNCH(c, launch_subspace_scores(c, n, scores));
+  SOM_LAUNCH(c, launch_margins(c, n, kCertifySubspaceCsr, nullptr, margin_out));
+  const size_t blocks = ((size_t)c->k + 127) / 128;
+  SOM_LAUNCH(c, hipMemcpyAsync(block_min, c->coarse_min, blocks * (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(node_of, c->node_of, (size_t)c->k * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(mu_out, c->mu, (size_t)c->dim * sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+  SOM_LAUNCH(c, hipMemcpyAsync(used, &c->sub_state->use, 2 * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
+  return SOM_OK;
+}
+
 int som_debug_scores_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
                          int64_t nnz, const float *codebook, float *scores, float *mu_out, double *margin_out) {
   if (!c) return SOM_ERR_INVALID_ARG;

@@ -342,6 +342,7 @@ bool subspace_csr_likely(const som_ctx *c, double radius);
 size_t subspace_csr_part_floats(const som_ctx *c);
 hipError_t launch_csr_subspace(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
                                const float *W);                                 // mu, qstep_max_bits, xn32 -> sub_*, wn32 (in the order node_of), wn64, wmax_bits
+hipError_t launch_subspace_scores(som_ctx *c, int64_t n, float *dump);          // sub_Y2, sub_U2 -> all scores
 hipError_t launch_bmu_dense_h_fine(som_ctx *c, int64_t n, SubspaceUse sub = kSubNo);                   // sort_val[0], tile_cnt, tile_list -> candidates
 // bmu_two_level.hip
 hipError_t launch_select_blocks(som_ctx *c, int64_t n, SubspaceUse sub = kSubNo);      // coarse_min -> coarse_key, coarse_mask

@@ -96,6 +96,59 @@ def test_too_many_directions_end_the_attempt_early(rows, cols, dim, fall, want):
         assert np.all(loss == -1.0)
 
 
+@pytest.mark.parametrize("rows,cols,dim,n,rank", [(12, 25, 256, 300, 7), (16, 16, 257, 257, 30), (37, 7, 320, 255, 55), (23, 45, 1000, 520, 12),
+                                                  (40, 13, 2048, 64, 45), (1, 33, 1001, 129, 20)])
+@pytest.mark.parametrize("data", ["near", "offset", "sizes", "rest"])
+def test_fine_scores_within_the_margin(rows, cols, dim, n, rank, data):
+    """Every score of the fine pass on the coordinates against fp64.  "rest": nodes that lie outside by an eighth of what the fine pass
+    may leave (2^-14 of the largest), and by several times that once the basis has been disturbed by it."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8060 + dim + n)
+    k = rows * cols
+    W = _book(rng, k, dim, rank)
+    if data == "rest":
+        e = rng.standard_normal((k, dim))
+        W = (W + e * (2.0 ** -17 * np.linalg.norm(W - W.mean(0), axis=1).max() / np.linalg.norm(e, axis=1))[:, None]).astype(np.float32)
+    X = W[rng.integers(0, k, n)] + 0.2 * rng.standard_normal((n, dim)).astype(np.float32)
+    if data == "offset":
+        W, X = W + np.float32(3), X + np.float32(3)
+    if data == "sizes":
+        X = X * np.exp2(rng.integers(-18, 18, (n, 1))).astype(np.float32)
+        X[0] = 0.0
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W), filter="two_level")
+    scores = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    margin = torch.empty(n, dtype=torch.float64, device="cuda")
+    mu = torch.empty(dim, dtype=torch.float32, device="cuda")
+    used = torch.empty(2, dtype=torch.int32, device="cuda")
+    capi.som_debug_subspace_fine(som.ctx, P.to_dev(X), som.codebook, scores, mu, margin, used)
+    s, margin, mu, used = scores.cpu().numpy(), margin.cpu().numpy(), mu.cpu().numpy(), used.cpu().numpy()
+    som.close()
+    if data != "sizes":
+        assert used[1] == 1
+    if not used[1]:                            # (a centring vector far from the nodes: the largest |w'| is its length then)
+        return
+    xc = (X - mu).astype(np.float32).astype(np.float64)
+    wc = (W - mu).astype(np.float32).astype(np.float64)
+    err = np.abs(s.astype(np.float64) - ((wc ** 2).sum(1)[None, :] - 2.0 * xc @ wc.T)).max(1)
+    assert np.all(err <= 0.5 * margin), (2 * err / margin).max()
+    print(f"used {used}, worst error / half the margin {(2 * err / margin).max():.3f}, margin {margin.mean():.2e}")
+
+
+def test_what_the_fine_pass_may_leave():
+    """A remainder between what the coarse and what the fine pass may leave: the coarse pass alone runs on the coordinates."""
+    rng = np.random.default_rng(8070)
+    rows, cols, dim = 30, 40, 300
+    k = rows * cols
+    base = _book(rng, k, dim, 20)
+    e = rng.standard_normal((k, dim))
+    e *= np.linalg.norm(base - base.mean(0), axis=1).max() / np.linalg.norm(e, axis=1)[:, None]
+    for share, coarse, fine in ((2.0 ** -17, True, 1), (2.0 ** -13, True, 0), (2.0 ** -11, True, 0), (2.0 ** -6, False, 0)):
+        W = (base + share * e).astype(np.float32)
+        X = W[rng.integers(0, k, 200)]
+        _, _, _, _, used, loss = _minima(W, X, rows, cols)
+        assert (used[0] > 0) == coarse and used[1] == fine, (share, used, loss)
+
+
 @pytest.mark.parametrize("rows,cols,dim,n,map_type,grid", [(30, 36, 96, 3000, "toroid", "square"), (33, 35, 200, 1999, "planar", "hexagonal"),
                                                            (40, 29, 1030, 700, "planar", "square")])
 def test_epochs_of_a_schedule(oracle, rows, cols, dim, n, map_type, grid):
@@ -279,3 +332,24 @@ def test_only_the_gaussian_neighbourhood_holds_memory_for_it():
     room = n * 396
     assert held["gaussian", False] >= held["gaussian", True] + 3 * room // 4
     assert held["gaussian", False] >= held["bubble", False] + 3 * room // 4
+
+
+def test_a_search_by_default(oracle):
+    """Large enough to try the subspace by itself: an epoch, and a search of its own, which takes twice the work."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(8950)
+    rows, cols, dim, n = 40, 50, 320, 280_000
+    k = rows * cols
+    W = _book(rng, k, dim, 9)
+    Xd = torch.from_numpy(W).cuda()[torch.from_numpy(rng.integers(0, k, n)).cuda()] + 0.05 * torch.randn((n, dim), device="cuda")
+    som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+    b = som.bmus(Xd).cpu().numpy()
+    assert _used(som) == (1, 1, 1)
+    few = slice(0, 20_011)
+    assert np.array_equal(b[few], oracle.bmu_dense(Xd[few].cpu().numpy(), W))
+    assert np.array_equal(som.train_epoch(Xd, 20.0).cpu().numpy(), b) and _used(som) == (1, 1, 1)
+    som.codebook.copy_(torch.from_numpy(W))
+    half = Xd[: n // 2].contiguous()
+    assert np.array_equal(som.bmus(half).cpu().numpy(), b[: n // 2]) and _used(som)[0] == 0
+    assert np.array_equal(som.train_epoch(half, 20.0).cpu().numpy(), b[: n // 2]) and _used(som) == (1, 1, 1)
+    som.close()

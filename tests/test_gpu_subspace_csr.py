@@ -66,6 +66,75 @@ def test_epochs_on_the_coordinates(oracle, rows, cols, dim, n, radius, registere
     som.close()
 
 
+def _dense(csr, dim):
+    indptr, indices, values = csr
+    X = np.zeros((indptr.size - 1, dim))
+    X[np.repeat(np.arange(indptr.size - 1), np.diff(indptr)), indices] = values
+    return X
+
+
+@pytest.mark.parametrize("rows,cols,dim,n,radius", [(30, 32, 1500, 300, 9.0), (17, 61, 2051, 333, 14.0), (9, 9, 1027, 65, 4.0),
+                                                    (16, 16, 40000, 40, 5.0)])
+@pytest.mark.parametrize("data", ["near", "sizes", "rest"])
+def test_scores_within_the_margins(rows, cols, dim, n, radius, data):
+    """Block minima of the coarse and every score of the fine pass against fp64; among the rows an empty one, one of a thousand
+    nonzeros and one that is full.  "rest": nodes that lie outside by a share of what may be left, and by several
+    times that once the basis has been disturbed by it."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8850 + dim)
+    k = rows * cols
+    csr = _edge_rows(sparse_zipf_csr(n, dim, 88, mean_len=40.0, max_len=200), dim)
+    W = _smooth_book(rng, rows, cols, dim, radius, csr)
+    indptr, indices, values = csr
+    full = rng.standard_normal(dim).astype(np.float32) / np.float32(np.sqrt(dim))
+    indptr = np.append(indptr, indptr[-1] + dim)
+    indices, values = np.concatenate([indices, np.arange(dim, dtype=np.int32)]), np.concatenate([values, full])
+    n += 1
+    if data == "rest":
+        e = rng.standard_normal((k, dim))
+        W = (W + e * (2.0 ** -21 * np.linalg.norm(W - W.mean(0), axis=1).max() / np.linalg.norm(e, axis=1))[:, None]).astype(np.float32)
+    if data == "sizes":
+        values = values * np.repeat(np.exp2(rng.integers(-18, 18, n)), np.diff(indptr)).astype(np.float32)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W), filter="two_level")
+    dev = P.csr_to_dev((indptr, indices, values))
+    m = torch.empty(((k + 127) // 128, n), dtype=torch.float32, device="cuda")
+    scores = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    select, margin = (torch.empty(n, dtype=torch.float64, device="cuda") for _ in range(2))
+    node_of = torch.empty(k, dtype=torch.int32, device="cuda")
+    mu = torch.empty(dim, dtype=torch.float32, device="cuda")
+    used = torch.empty(2, dtype=torch.int32, device="cuda")
+    capi.som_debug_subspace_csr(som.ctx, *dev, som.codebook, m, select, node_of, scores, margin, mu, used)
+    m, scores, select, margin, node_of, mu, used = (t.cpu().numpy() for t in (m, scores, select, margin, node_of, mu, used))
+    som.close()
+    assert used[0] > 0 and used[1] == 1
+    X = _dense((indptr, indices, values), dim)
+    wc = (W - mu).astype(np.float32).astype(np.float64)
+    c = (wc ** 2).sum(1) + 2.0 * wc @ mu.astype(np.float64)
+    exact = c[None, :] - 2.0 * X @ wc.T
+    err = np.abs(scores.astype(np.float64) - exact).max(1)
+    assert np.all(err <= 0.5 * margin), (2 * err / margin).max()
+    ordered = exact[:, node_of]
+    want_m = np.stack([ordered[:, b:b + 128].min(1) for b in range(0, k, 128)])
+    err_m = np.abs(m.astype(np.float64) - want_m).max(0)
+    assert np.all(err_m <= 0.5 * select), (2 * err_m / select).max()
+    print(f"used {used}, worst error / half the margin: fine {(2 * err / margin).max():.3f}, coarse {(2 * err_m / select).max():.3f}")
+
+
+def test_an_epoch_by_default(oracle):
+    """Large enough to try the coordinates by itself."""
+    from paper_1305_1422_amd import Som, capi
+    rng = np.random.default_rng(8860)
+    rows, cols, dim, n = 45, 45, 1100, 120_000
+    csr = sparse_zipf_csr(n, dim, 86, mean_len=60.0, max_len=120)
+    few = (csr[0][:4001], csr[1][:csr[0][4000]], csr[2][:csr[0][4000]])
+    W = _smooth_book(rng, rows, cols, dim, 14.0, few)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
+    b = som.train_epoch(P.csr_to_dev(csr), 14.0).cpu().numpy()
+    assert capi.som_debug_subspace_used(som.ctx)[0::2] == (1, 1)
+    som.close()
+    P.check_bmus_csr(oracle, few, dim, W, b[:4000])
+
+
 @pytest.mark.parametrize("book", ["random", "nan", "inf", "constant"])
 def test_code_books_it_is_not_for(oracle, book):
     """Full rank, non-finite, and equal rows: the same nodes as a search that does not try the coordinates."""
