@@ -508,8 +508,9 @@ __global__ __launch_bounds__(256) void k_csr_project(const int64_t *__restrict__
     if (lane == 0) {
       const float xn = sqrtf(xn32[j]) * (1.f + 1e-6f), yn = norm_above(ysq, s), yl = norm_above(lost, s);
       yscale[j] = s;
-      // as in the dense projection; y itself is off by its rounding to fp32 (and 1e-13 of |x|) only
-      const float b = 0x1p-23f * (yn + xn * 0x1p-18f) * um;
+      // as in the dense projection; y itself is off by its rounding to fp32 and by that of its chain, len 2^-53 |x| |V_r| a coordinate
+      // and eight times that (|V_r| is 1 to a few 1e-3, so sixteen) over the 64
+      const float b = (0x1p-23f * yn + (float)len * 0x1p-49f * xn) * um;
       err[j] = factor_fits(cfac)
                    ? (b + xn * e1 + yl * um + (yn + yl) * (ulost + 21.f * 0x1p-24f * um) + 12.f * 0x1p-24f * state->cmax) * (1.f + 1e-3f)
                    : INFINITY;
