@@ -507,9 +507,10 @@ hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const Su
   slabs = (c->dim + cols_per_slab - 1) / cols_per_slab;
   hipLaunchKernelGGL(k_center_transpose_q16, dim3((unsigned)tiles, (unsigned)slabs), dim3(256), 0, c->stream, W, c->mu,
                      c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial, off);
-  // Eight threads a node where one each would leave most of the chip idle and chains of slabs to wait for (2,500 nodes 24 -> 7.8 us);
-  // with more nodes there are few slabs, and eight would only read them in shorter pieces (68,880 nodes, three slabs, 100 -> 8.5, most of it the atomics).
-  if (c->k < 65536)
+  // A node's slabs are a chain of loads to one thread, an eighth of it to eight; where there are few of them, eight times as many workgroups
+  // read them in shorter pieces for nothing.  One / eight threads, us: 61 slabs of 2,500 nodes 24.8 / 7.4, 32 of 4,900 10.6 / 5.2, 20 of 10,000
+  // 11.4 / 8.7, 16 of 10,000 6.5 / 6.7, 10 of 19,600 8.3 / 8.0, 8 of 19,600 5.3 / 8.3, 5 of 40,000 6.6 / 10.4, 3 of 67,600 6.6 / 12.9.
+  if (slabs >= 16)
     hipLaunchKernelGGL(k_finish_node_constants<8>, dim3((c->k + 31) / 32), dim3(256), 0, c->stream, c->ct_partial, slabs, c->k, c->wn32,
                        c->wn64, c->wmax_bits, off);
   else

@@ -49,12 +49,13 @@ def test_many_nodes(oracle, rows, cols):
     som.close()
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 65535), (256, 256), (257, 257)])
-def test_node_constants_where_their_sums_change(oracle, rows, cols):
-    """Eight threads a node below 65,536 nodes, one from there on; the node of the largest norm, which sets every margin, lies
+@pytest.mark.parametrize("rows,cols,dim", [(1, 65535, 70), (256, 256, 70), (257, 257, 70), (13, 37, 960), (13, 37, 961),
+                                           (7, 5, 5000), (100, 100, 2000)])
+def test_node_constants_where_their_sums_change(oracle, rows, cols, dim):
+    """Eight threads a node from sixteen slabs of columns on, one below; the node of the largest norm, which sets every margin, lies
     in the last, ragged workgroup."""
     from paper_1305_1422_amd import Som
-    dim, n = 70, 120
+    n = 120
     csr = sparse_zipf_csr(n, dim, 23, mean_len=9.0, max_len=30)
     W = np.random.default_rng(24).random((rows * cols, dim)).astype(np.float32)
     W[-1] *= 50.0
