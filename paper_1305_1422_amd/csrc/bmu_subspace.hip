@@ -681,7 +681,7 @@ bool subspace_eligible(const som_ctx *c, int64_t n, bool alone) {
 // Is the code book likely to lie in 64 directions?  One that enters an epoch was left by an epoch of about its radius
 // or more, and the number of directions grows with the number of radii the map is long and wide.  A search
 // outside an epoch (radius 0) may bring any: it is tried where the work it may save is several times what a
-// failure costs (40 us, most of it the factor, which finds out).
+// failure costs (13 us for 2,500 nodes and 22 for 40,000 where the factor finds out, 75 to 110 where the nodes' losses do).
 bool subspace_likely(const som_ctx *c, int64_t n, double radius) {
   if (radius <= 0.0) return subspace_eligible(c, n, true);
   return (double)c->rows * (double)c->cols <= kSubspaceMaxArea * radius * radius;

@@ -69,13 +69,20 @@ constexpr int kSubspaceParts = 512;        // workgroups of its node pass at mos
 constexpr double kSubspaceMinWork = 7e10;  // multiply-adds a search has to save for the subspace to be tried
 constexpr double kSubspaceMaxArea = 100.0; // ... and map nodes per squared radius at most
 constexpr double kSubspaceAloneWork = 1.4e11;  // the same for a search outside an epoch, whose code book may be anything
-constexpr float kSubspaceLoss = 0x1p-8f;   // share of the largest |w'| that may lie outside for it to be used
-constexpr float kSubspaceLossFine = 0x1p-14f;  // ... outside all of them for the fine pass to use them too
+// Share of the largest |w'| that may lie outside of the coordinates for the coarse pass to use them, outside of all of them for the fine
+// pass to do so too, outside of the first 32 for those to do.  How much a loss widens the margins depends on how far the instances are from
+// the nodes, so a line is where clusters begin to gain and data without structure do not yet lose; epochs of 50,000 to
+// 600,000 instances, lines two to eight times higher and lower, relative times where they changed:
+//   2^-8: with 2^-7 clusters 0.63 - 0.83, uniform data 1.17 - 1.6; with 2^-9 clusters 1.37 - 1.73;
+//   2^-14: with 2^-12 clusters 1.03 - 1.18, uniform data 1.2 - 5.8; with 2^-17 clusters 1.04 - 1.14;
+//   2^-11: with 2^-9 clusters 0.81 - 0.95, uniform and very noisy data 1.03 - 1.2; with 2^-13 clusters 1.08 - 1.27.
+constexpr float kSubspaceLoss = 0x1p-8f;
+constexpr float kSubspaceLossFine = 0x1p-14f;
+constexpr float kSubspaceLoss32 = 0x1p-11f;
 constexpr int kSubspaceFineDim = 256;      // ... which takes this many features to pay
 constexpr int kSubspaceCsrDim = 1024;      // sparse rows: fewest features ...
 constexpr double kSubspaceCsrMaxArea = 16.5;   // ... most map nodes per squared radius ...
 constexpr float kSubspaceLossCsr = 0x1p-15f;   // ... and what may lie outside
-constexpr float kSubspaceLoss32 = 0x1p-11f;    // ... outside the first 32 coordinates for those to do
 constexpr int kHot = 256;                  // columns of the dense hot block of a registered sparse training set
 constexpr double kHotMinShare = 0.3;       // share of the nonzeros those columns must hold for the split to be used
 constexpr int kProfMax = 512;              // event brackets kept per stage between two reads
