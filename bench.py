@@ -27,19 +27,19 @@ PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP16_MFMA_TFLOPS = 2500.0
 PEAK_FP64_MFMA_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
-# HBM-side bytes per launch of the dominant kernel (fetched + written), from the rocprofv3 --pmc passes
+# HBM-side bytes per epoch of the filter stage (fetched + written), from the rocprofv3 --pmc passes
 # (FETCH_SIZE, WRITE_SIZE, scaled by the copy calibration) summarised in profiles/epoch_config*.md;
 # measured once per kernel version, not during this run (the dense figures vary by some ten percent from
 # run to run: they depend on how long the workgroups that share an instance tile stay in step).
-MEASURED_TRAFFIC_BYTES = {(2, "two_level"): 0.461e9 + 0.035e9, (3, "two_level"): 2.082e9 + 0.094e9,
-                          (5, "two_level"): 2.059e9 + 0.425e9,
-                          (6, "two_level"): 1.814e9 + 0.036e9,      # sparse rows searched through dense planes
+MEASURED_TRAFFIC_BYTES = {(2, "two_level"): 0.767e9 + 0.063e9, (3, "two_level"): 2.100e9 + 0.117e9,
+                          (5, "two_level"): 2.187e9 + 0.520e9,
+                          (6, "two_level"): 1.813e9 + 0.039e9,      # sparse rows searched through dense planes
                           # one-level split-fp16 filter and fp32 filter (earlier counter runs; those kernels are unchanged)
                           (2, "split_f16"): 3.841e9 + 0.036e9, (2, "fp32"): 8.49e9 + 0.025e9,
                           (3, "split_f16"): 14.283e9 + 0.025e9, (5, "split_f16"): 13.917e9 + 0.072e9,
                           # sparse: all kernels of the filter stage (code-book pass, hot-column block, sweep)
-                          (4, "sparse"): 11.671e9 + 1.034e9, (6, "sparse"): 0.415e9 + 0.058e9,
-                          (7, "sparse"): 86.822e9 + 6.474e9}
+                          (4, "sparse"): 11.653e9 + 1.031e9, (6, "sparse"): 0.415e9 + 0.058e9,
+                          (7, "sparse"): 81.380e9 + 6.454e9}
 PEAK_FP32_VALU_TFLOPS = 157.3
 
 

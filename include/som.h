@@ -347,9 +347,14 @@ int som_set_smoothing(som_ctx *ctx, int form);
  *                  hold the BMU by the proven bound of those scores are dropped, the instances are
  *                  ordered by the blocks they have left, and the split-fp16 pass runs over the remaining
  *                  (128 instances, block) pairs only.  Needs 6 bytes per element of extra device memory
- *                  and 4 bytes per instance and node block.  In an epoch whose radius is wide the code book
- *                  that enters it lies in few directions: the coarse pass then runs on 32 or 64 coordinates
- *                  (decided on the device, within the same proven bounds; 128 bytes per instance more).
+ *                  and 4 bytes per instance and node block.  While the radius is wide the code book lies in few
+ *                  directions: large epochs, and larger searches of their own, under the Gaussian neighbourhood then
+ *                  run the coarse pass on 32 or 64 coordinates, and with 256 features or more, where next to
+ *                  nothing lies outside of them, the second pass too (decided on the device, within the same
+ *                  proven bounds).  Contexts of such calls hold 136 bytes per instance more, from 256 features on 396,
+ *                  and for the basis some 400 bytes per node and 1 KB per feature.  Large sparse epochs on planar maps are
+ *                  searched on the coordinates altogether; they hold the same, 4 bytes per instance and node block, and up
+ *                  to 17 KB per node.
  *   SOM_FILTER_AUTO (default)  small searches run without any filter pass, all distances in fp64 on the
  *                  matrix cores, wherever that is estimated to take less time than a filtered search (from
  *                  400 nodes on up to some 1e9 to 1e10 multiply-adds in all, on smaller maps of few features
