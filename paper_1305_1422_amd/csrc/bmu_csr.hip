@@ -507,10 +507,11 @@ hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const Su
   slabs = (c->dim + cols_per_slab - 1) / cols_per_slab;
   hipLaunchKernelGGL(k_center_transpose_q16, dim3((unsigned)tiles, (unsigned)slabs), dim3(256), 0, c->stream, W, c->mu,
                      c->qstep, c->k, c->dim, c->kpad, cols_per_slab, reinterpret_cast<int16_t *>(c->Wt), c->ct_partial, off);
-  // A node's slabs are a chain of loads to one thread, an eighth of it to eight; where there are few of them, eight times as many workgroups
-  // read them in shorter pieces for nothing.  One / eight threads, us: 61 slabs of 2,500 nodes 24.8 / 7.4, 32 of 4,900 10.6 / 5.2, 20 of 10,000
-  // 11.4 / 8.7, 16 of 10,000 6.5 / 6.7, 10 of 19,600 8.3 / 8.0, 8 of 19,600 5.3 / 8.3, 5 of 40,000 6.6 / 10.4, 3 of 67,600 6.6 / 12.9.
-  if (slabs >= 16)
+  // A node's slabs are a chain of loads to one thread, an eighth of it to eight (0.3 us less per slab); eight times as many workgroups take some
+  // 0.3 us more per thousand nodes, and have nothing to share out where there are fewer than four slabs.  One / eight threads, us: 61 slabs
+  // of 2,500 nodes 24.8 / 7.4, 20 of 10,000 11.4 / 8.7, 15 of 10,000 6.5 / 5.9, 12 of 10,000 5.7 / 6.2, 8 of 2,500 4.4 / 3.6, 8 of 7,225 4.4 / 4.4,
+  // 8 of 19,600 5.3 / 9.1, 4 of 1,600 3.5 / 3.4, 2 of 1,600 2.8 / 3.4, 5 of 40,000 6.6 / 10.4, 3 of 67,600 6.6 / 12.9 (150 sizes).
+  if (slabs >= 4 && 800 * slabs >= c->k)
     hipLaunchKernelGGL(k_finish_node_constants<8>, dim3((c->k + 31) / 32), dim3(256), 0, c->stream, c->ct_partial, slabs, c->k, c->wn32,
                        c->wn64, c->wmax_bits, off);
   else

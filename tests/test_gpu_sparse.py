@@ -49,11 +49,11 @@ def test_many_nodes(oracle, rows, cols):
     som.close()
 
 
-@pytest.mark.parametrize("rows,cols,dim", [(1, 65535, 70), (256, 256, 70), (257, 257, 70), (13, 37, 960), (13, 37, 961),
-                                           (7, 5, 5000), (100, 100, 2000)])
+@pytest.mark.parametrize("rows,cols,dim", [(1, 65535, 70), (256, 256, 70), (257, 257, 70), (40, 80, 250), (27, 120, 250),
+                                           (13, 37, 192), (7, 5, 5000), (100, 100, 2000)])
 def test_node_constants_where_their_sums_change(oracle, rows, cols, dim):
-    """Eight threads a node from sixteen slabs of columns on, one below; the node of the largest norm, which sets every margin, lies
-    in the last, ragged workgroup."""
+    """Eight threads a node from four slabs of columns on and up to 800 nodes a slab, else one; the node of the largest norm, which sets
+    every margin, lies in the last, ragged workgroup."""
     from paper_1305_1422_amd import Som
     n = 120
     csr = sparse_zipf_csr(n, dim, 23, mean_len=9.0, max_len=30)
