@@ -693,21 +693,26 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // ---------------------------------------------------------------- sparse rows
 // S_b for CSR data.
 //
-// Rows of up to kCsrTile columns: the instances are sorted by BMU as in the dense path and cut into
-// chunks of kCsrChunkRows; a workgroup adds the nonzeros of its chunk into a copy of the node's row
-// in LDS (LDS atomics: the rows of a node share their frequent columns).  A node with a single chunk
-// is then written with plain stores, zeros included, so its row needs no clearing beforehand; the
-// chunks of a larger node add their nonzero entries to a row cleared by k_zero_rows_if.
+// The instances are sorted by BMU as in the dense path and cut into chunks of kCsrChunkRows; a workgroup adds the nonzeros of its
+// chunk into a copy of the node's row in LDS (LDS atomics: the rows of a node share their frequent columns), one tile of columns
+// after the other.  A node with a single chunk is then written with plain stores, zeros included, so its row needs no clearing
+// beforehand; the chunks of a larger node add their nonzero entries to a row cleared by k_zero_rows_if.
 //
-// Longer rows: every chosen row is cleared and every nonzero goes straight into S with a global
-// atomic, in instance order.  Measured alternatives on configuration 4 (rows of 50,000 columns, 1e7
-// nonzeros, 0.64 ms + 0.1 ms of clearing this way): the sorted chunks with one LDS tile of columns
-// after the other 0.71 ms (walking a chunk is a chain of dependent loads - permutation, row pointer,
-// entries - and is repeated per tile); the sorted chunks with global atomics 0.79 ms (the sort costs
-// what the locality gains).  On configuration 6 (rows of 1,000 columns, 5e6 nonzeros colliding on
-// 10 MB) the LDS copy took the stage from 0.51 to 0.14 ms.
-constexpr int kCsrChunkRows = 256;
-constexpr int kCsrTile = 16384;           // columns of a row copy in LDS (64 KB: two workgroups per CU)
+// Bound by the chain of loads that leads to a chunk's entries (chunk, node, ids, row bounds, entries) and, with long rows, by writing
+// S.  So the chain is walked once per chunk: it has as many rows as the wavefronts keep in registers, eight each, and
+// the tiles take their entries from there (a tile as a workgroup of its own, chunks of 256 rows: 302 us on 100,000 rows of 50,000 columns
+// and 100 nonzeros, 2,500 nodes; chunks of 256 / 128 / 64 rows with the first ones kept: 223 / 208 / 192, 1.0 GB moved; clearing S and
+// one global atomic for each nonzero outside the 256 most frequent columns, as before: 451).  5e6 nonzeros in rows of 1,000
+// columns: 82 -> 46 us.
+//
+// Long rows with fewer than kTileFrom instances per node: every chosen row is cleared and every nonzero goes straight into S with a global atomic,
+// in instance order; the sort costs more than the atomics there (20,000 columns, 2,500 nodes, the whole update, atomics / tiles, us: one
+// instance per node 241 / 248, two 266 / 273 evenly spread and 265 / 255 skewed, eight 334 / 303 and 400 / 293).
+constexpr int kCsrThreads = 512, kCsrWaves = kCsrThreads / kWave;
+constexpr int kCsrRowsPerWave = 8;
+constexpr int kCsrChunkRows = kCsrWaves * kCsrRowsPerWave;
+constexpr int kCsrTile = 13056;           // columns of a row copy in LDS (51 KB: three workgroups per CU)
+constexpr int64_t kTileFrom = 2;
 static_assert(kCsrChunkRows % kChunkRows == 0, "the chunk tables are sized for kChunkRows");
 
 // Clears the rows of S whose node has more than `lo` instances.
@@ -719,15 +724,18 @@ __global__ __launch_bounds__(256) void k_zero_rows_if(const int32_t *__restrict_
   for (int c = blockIdx.y * 256 + threadIdx.x; c < dim; c += gridDim.y * 256) dst[c] = 0.f;
 }
 
-__global__ __launch_bounds__(256) void k_accumulate_csr(const int64_t *__restrict__ indptr,
-                                                        const int32_t *__restrict__ indices,
-                                                        const float *__restrict__ values, int dim,
-                                                        const int32_t *__restrict__ perm,
-                                                        const int32_t *__restrict__ seg_off,
-                                                        const int32_t *__restrict__ chunk_off,
-                                                        const int32_t *__restrict__ chunk_node, int k,
-                                                        float *__restrict__ S) {
-  extern __shared__ float s_row[];           // dim floats
+// The rows of a chunk are dealt to the wavefronts, whose first lanes hold their bounds; a lane keeps entries lane and lane + 64 of every
+// row, what lies beyond is read again for every tile.
+__global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *__restrict__ indptr,
+                                                                const int32_t *__restrict__ indices,
+                                                                const float *__restrict__ values, int dim, int tile,
+                                                                const int32_t *__restrict__ perm,
+                                                                const int32_t *__restrict__ seg_off,
+                                                                const int32_t *__restrict__ chunk_off,
+                                                                const int32_t *__restrict__ chunk_node, int k,
+                                                                float *__restrict__ S) {
+  extern __shared__ float4 s_row4[];         // tile floats
+  float *s_row = reinterpret_cast<float *>(s_row4);
   const int chunk = blockIdx.x;
   if (chunk >= chunk_off[k]) return;          // uniform over the workgroup
   const int b = chunk_node[chunk];
@@ -735,69 +743,67 @@ __global__ __launch_bounds__(256) void k_accumulate_csr(const int64_t *__restric
   const int lo = seg_off[b] + (chunk - first_chunk) * kCsrChunkRows;
   const int hi = min(lo + kCsrChunkRows, seg_off[b + 1]);
   const bool single = (chunk_off[b + 1] - first_chunk) == 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float *dst = S + (int64_t)b * dim;
-  for (int c = threadIdx.x; c < dim; c += 256) s_row[c] = 0.f;
-  __syncthreads();
-  for (int r = lo + wave; r < hi; r += 4) {
-    const int64_t j = perm[r];
-    for (int64_t p = indptr[j] + lane; p < indptr[j + 1]; p += 64) {
-      int c = indices[p];
-      c = c < 0 ? 0 : (c >= dim ? dim - 1 : c);
-      atomicAdd(&s_row[c], values[p]);
-    }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t from = 0;
+  int length = 0;
+  if (lane < kCsrRowsPerWave && lo + wave + lane * kCsrWaves < hi) {
+    const int64_t j = perm[lo + wave + lane * kCsrWaves];
+    from = indptr[j];
+    length = (int)(indptr[j + 1] - from);
   }
-  __syncthreads();
-  if (single) {
-    for (int c = threadIdx.x; c < dim; c += 256) dst[c] = s_row[c];
-  } else {
-    for (int c = threadIdx.x; c < dim; c += 256) {
-      const float v = s_row[c];
-      if (v != 0.f) unsafeAtomicAdd(dst + c, v);
-    }
+  int ec[kCsrRowsPerWave][2];
+  float ev[kCsrRowsPerWave][2];
+  auto start = [&](int t) {                   // scalars: the address of a load is one pair of them and the lane
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, t) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)from >> 32), t) << 32);
+  };
+#pragma unroll
+  for (int t = 0; t < kCsrRowsPerWave; ++t) {
+    const int len = __builtin_amdgcn_readlane(length, t);
+    const int32_t *ip = indices + start(t);
+    const float *vp = values + start(t);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (lane + 64 * u < len) {
+        ec[t][u] = ip[lane + 64 * u];
+        ev[t][u] = vp[lane + 64 * u];
+      }
   }
-}
-
-// Long rows of a context that holds a split into frequent columns and the rest (csr_hot.hip; the tables
-// describe the registered set, but any table gives correct sums): the instances are sorted by BMU and cut
-// into chunks as above, the nonzeros of the kHot frequent columns - about half of all, and the ones whose
-// atomics collide - are added up in LDS per chunk and leave as at most kHot atomics, the others go straight
-// into S.  The rows of the chosen nodes are cleared beforehand.
-__global__ __launch_bounds__(256) void k_accumulate_csr_hot(const int64_t *__restrict__ indptr,
-                                                            const int32_t *__restrict__ indices,
-                                                            const float *__restrict__ values, int dim,
-                                                            const int32_t *__restrict__ perm,
-                                                            const int32_t *__restrict__ seg_off,
-                                                            const int32_t *__restrict__ chunk_off,
-                                                            const int32_t *__restrict__ chunk_node, int k,
-                                                            const int32_t *__restrict__ rank,
-                                                            const int32_t *__restrict__ hot_cols,
-                                                            float *__restrict__ S) {
-  __shared__ float s_hot[kHot];
-  const int chunk = blockIdx.x;
-  if (chunk >= chunk_off[k]) return;          // uniform over the workgroup
-  const int b = chunk_node[chunk];
-  const int first_chunk = chunk_off[b];
-  const int lo = seg_off[b] + (chunk - first_chunk) * kCsrChunkRows;
-  const int hi = min(lo + kCsrChunkRows, seg_off[b + 1]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float *dst = S + (int64_t)b * dim;
-  for (int h = threadIdx.x; h < kHot; h += 256) s_hot[h] = 0.f;
-  __syncthreads();
-  for (int r = lo + wave; r < hi; r += 4) {
-    const int64_t j = perm[r];
-    for (int64_t p = indptr[j] + lane; p < indptr[j + 1]; p += 64) {
-      int c = indices[p];
-      c = c < 0 ? 0 : (c >= dim ? dim - 1 : c);
-      const int h = rank[c];
-      if (h >= 0) atomicAdd(&s_hot[h], values[p]);
-      else unsafeAtomicAdd(dst + c, values[p]);
+  for (int c0 = 0; c0 < dim; c0 += tile) {
+    const int width = min(tile, dim - c0);
+    for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+    auto add = [&](int c, float v) {
+      const unsigned at = (unsigned)(min(max(c, 0), dim - 1) - c0);
+      if (at < (unsigned)width) atomicAdd(&s_row[at], v);
+    };
+#pragma unroll
+    for (int t = 0; t < kCsrRowsPerWave; ++t) {
+      const int len = __builtin_amdgcn_readlane(length, t);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (lane + 64 * u < len) add(ec[t][u], ev[t][u]);
+      if (len > 128) {
+        const int32_t *ip = indices + start(t);
+        const float *vp = values + start(t);
+        for (int x = 128 + lane; x < len; x += 64) add(ip[x], vp[x]);
+      }
     }
-  }
-  __syncthreads();
-  for (int h = threadIdx.x; h < kHot; h += 256) {
-    const float v = s_hot[h];
-    if (v != 0.f) unsafeAtomicAdd(dst + hot_cols[h], v);
+    __syncthreads();
+    float *dst = S + (int64_t)b * dim + c0;
+    if (single) {
+      if ((dim & 3) == 0) {                   // tiles are whole fours, so are the rows: 16 bytes a lane
+        for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
+      } else {
+        for (int c = threadIdx.x; c < width; c += kCsrThreads) dst[c] = s_row[c];
+      }
+    } else {
+      for (int c = threadIdx.x; c < width; c += kCsrThreads) {
+        const float v = s_row[c];
+        if (v != 0.f) unsafeAtomicAdd(dst + c, v);
+      }
+    }
+    if (c0 + tile < dim) __syncthreads();     // other threads clear the tile for the next one
   }
 }
 
@@ -984,7 +990,8 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
                                  const float *values, int64_t n, const int32_t *bmus) {
   int ysplit = (c->dim + 4095) / 4096;
   if (ysplit > 64) ysplit = 64;
-  if (c->dim <= kCsrTile) {
+  if (c->dim <= kCsrTile || n >= kTileFrom * (int64_t)c->k) {
+    const int tiles = (c->dim + kCsrTile - 1) / kCsrTile, tile = ((c->dim + tiles - 1) / tiles + 3) & ~3;
     hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
     if (e != hipSuccess) return e;
     if (c->GxT) {          // matrix smoothing only reads the rows of chosen nodes
@@ -996,27 +1003,9 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
     }
     int64_t max_chunks = n / kCsrChunkRows + (n < c->k ? n : c->k);
     if (max_chunks < 1) max_chunks = 1;
-    hipLaunchKernelGGL(k_accumulate_csr, dim3((unsigned)max_chunks), dim3(256), (size_t)c->dim * sizeof(float),
-                       c->stream, indptr, indices, values, c->dim, c->sort_val[0], c->seg_off, c->chunk_off,
+    hipLaunchKernelGGL(k_accumulate_csr, dim3((unsigned)max_chunks), dim3(kCsrThreads), (size_t)tile * sizeof(float),
+                       c->stream, indptr, indices, values, c->dim, tile, c->sort_val[0], c->seg_off, c->chunk_off,
                        c->chunk_node, c->k, c->S);
-    return hipGetLastError();
-  }
-  // (worth the sort only with several instances per node: with 12,347 instances on 68,880 nodes it cost 0.09 ms
-  // more than the plain scatter, with 100,000 on 2,500 it saves 0.14)
-  if (c->hot_valid && c->hot_on && n >= 8 * (int64_t)c->k) {
-    hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
-    if (e != hipSuccess) return e;
-    if (c->GxT) {
-      hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, 0, c->dim, c->S);
-    } else {
-      e = launch_fill_zero_u32(c->stream, c->S, (int64_t)c->k * c->dim);
-      if (e != hipSuccess) return e;
-    }
-    int64_t max_chunks = n / kCsrChunkRows + (n < c->k ? n : c->k);
-    if (max_chunks < 1) max_chunks = 1;
-    hipLaunchKernelGGL(k_accumulate_csr_hot, dim3((unsigned)max_chunks), dim3(256), 0, c->stream, indptr, indices,
-                       values, c->dim, c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->hot_rank,
-                       c->hot_cols, c->S);
     return hipGetLastError();
   }
   hipError_t e = launch_fill_zero_u32(c->stream, c->counts, c->k);

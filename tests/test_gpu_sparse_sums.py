@@ -1,0 +1,42 @@
+"""Per-node sums of sparse rows at the edges of their tiles and chunks (gpu tests, through the C ABI)."""
+import numpy as np
+import pytest
+
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("dim", [5, 1000, 13055, 13056, 13057, 26112, 26113, 40004])
+@pytest.mark.parametrize("per_node", [2, 3])
+def test_sums_at_the_edges_of_tiles_and_chunks(oracle, dim, per_node):
+    """One tile of columns, its largest, one column more, several; rows of no, one, 64, 128, 129 and 300 entries; nodes with none, one,
+    64 (a chunk), 65 and 130 instances; on both sides of the line where long rows leave the atomics.  The sums are exact: small whole
+    numbers, so any order of the additions gives the same."""
+    from paper_1305_1422_amd import Som
+    rows, cols = 10, 12
+    k, n = rows * cols, rows * cols * per_node - (per_node == 2)
+    rng = np.random.default_rng(dim + per_node)
+    bmus = np.full(n, 7, dtype=np.int32)
+    bmus[:64], bmus[64:129], bmus[129:130] = 3, k - 1, 11
+    if per_node == 3:
+        bmus[130:260] = 0
+    rng.shuffle(bmus)
+    lengths = np.minimum(rng.choice([0, 1, 64, 65, 128, 129, 300], size=n), dim)
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    indptr[1:] = np.cumsum(lengths)
+    indices = np.concatenate([np.sort(rng.choice(dim, size=m, replace=False)) for m in lengths]).astype(np.int32)
+    values = rng.integers(1, 9, size=indptr[-1]).astype(np.float32)
+    W = rng.random((k, dim)).astype(np.float32)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
+    som.set_neighborhood("bubble")                       # radius below 1: every node is the mean of its own instances
+    som.update(P.csr_to_dev((indptr, indices, values)), P.to_dev(bmus), 0.5)
+    torch.cuda.synchronize()
+    S, C = np.zeros((k, dim)), np.bincount(bmus, minlength=k)
+    np.add.at(S, (np.repeat(bmus, lengths), indices), values)
+    want = np.where(C[:, None] > 0, S / np.maximum(C, 1)[:, None], W)
+    got = som.codebook.cpu().numpy()
+    assert np.abs(got - want).max() <= 2.0 ** -22 * np.abs(want).max()      # one division, its operands exact: an ulp or two
+    som.close()
