@@ -206,19 +206,46 @@ __device__ __forceinline__ void sqdist_dense_wave4(const float *__restrict__ x, 
 // visited: |w|^2 + sum_nz ((v - w_c)^2 - w_c^2).  Equal to the plain sum in exact arithmetic; in fp64
 // its absolute error is about (dim + len) 2^-53 (|w|^2 + |x|^2), which is harmless unless the
 // distance itself is that small (sqdist_csr_wave below).
-__device__ __forceinline__ double sqdist_csr_regrouped_wave(const int32_t *__restrict__ idx,
-                                                            const float *__restrict__ val, int len,
-                                                            const float *__restrict__ w, double wn, int dim,
-                                                            int lane) {
-  double s = 0.0;
-  for (int p = lane; p < len; p += kWave) {
-    int c = idx[p];
-    c = c < 0 ? 0 : (c >= dim ? dim - 1 : c);
-    const double wc = (double)w[c];
-    const double d = (double)val[p] - wc;
-    s += d * d - wc * wc;
+// kN nodes at a time: the gathers of their weights are what it waits for, so they go together, 128 nonzeros of each.
+// The term is rounded the same for any kN (lists of 100,000 rows of 100 nonzeros on 2,500 nodes: 190 -> 163 us; lists of two to four, which
+// many wavefronts wait for side by side, 106 -> 105).
+__device__ __forceinline__ double regrouped_term(double v, double wc) {
+#pragma clang fp contract(off)
+  const double d = v - wc;
+  return __builtin_fma(d, d, -(wc * wc));
+}
+
+template <int kN>
+__device__ __forceinline__ void sqdist_csr_regrouped_wave(const int32_t *__restrict__ idx,
+                                                          const float *__restrict__ val, int len,
+                                                          const float *__restrict__ W, const int (&node)[kN],
+                                                          const double *__restrict__ wn64, int dim, int lane, double (&out)[kN]) {
+  double s[kN] = {};
+  for (int p0 = 0; p0 < len; p0 += 2 * kWave) {
+    int c[2];
+    float v[2], w[2][kN];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = min(p0 + u * kWave + lane, len - 1);
+      c[u] = idx[p];
+      v[u] = val[p];
+      c[u] = c[u] < 0 ? 0 : (c[u] >= dim ? dim - 1 : c[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (p0 + u * kWave + lane < len) {
+#pragma unroll
+        for (int t = 0; t < kN; ++t) w[u][t] = W[(int64_t)node[t] * dim + c[u]];
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (p0 + u * kWave + lane < len) {
+#pragma unroll
+        for (int t = 0; t < kN; ++t) s[t] += regrouped_term((double)v[u], (double)w[u][t]);
+      }
   }
-  return wn + wave_sum(s);
+#pragma unroll
+  for (int t = 0; t < kN; ++t) out[t] = wn64[node[t]] + wave_sum(s[t]);
 }
 
 // The BMU equation's sum as it is printed: every coordinate once, an unlisted one as zero, all
@@ -251,13 +278,46 @@ __device__ __forceinline__ double csr_row_sqnorm_wave(const float *__restrict__ 
 // decision), the plain sum otherwise.  wn = |w|^2, xn = |x|^2.  Every lane holds the same bits of
 // the regrouped value, so the branch is uniform over the wavefront; bit-identical weight vectors
 // take the same branch and get the same bits.
-__device__ __forceinline__ double sqdist_csr_wave(const int32_t *__restrict__ idx, const float *__restrict__ val,
-                                                  int len, const float *__restrict__ w, double wn, double xn,
-                                                  int dim, int lane) {
-  const double d2 = sqdist_csr_regrouped_wave(idx, val, len, w, wn, dim, lane);
-  const double noise = ((double)dim + (double)len + 2.0) * 1.862645149230957e-09 * (wn + xn);   // 2^-29 = 2^-52 * 2^23
-  if (d2 < noise) return sqdist_csr_plain_wave(idx, val, len, w, dim, lane);
-  return d2;
+template <int kN>
+__device__ __forceinline__ void sqdist_csr_wave(const int32_t *__restrict__ idx, const float *__restrict__ val,
+                                                int len, const float *__restrict__ W, const int (&node)[kN],
+                                                const double *__restrict__ wn64, double xn, int dim, int lane, double (&d2)[kN]) {
+  sqdist_csr_regrouped_wave<kN>(idx, val, len, W, node, wn64, dim, lane, d2);
+#pragma unroll
+  for (int t = 0; t < kN; ++t) {
+    const double noise = ((double)dim + (double)len + 2.0) * 1.862645149230957e-09 * (wn64[node[t]] + xn);   // 2^-29 = 2^-52 * 2^23
+    if (d2[t] < noise) d2[t] = sqdist_csr_plain_wave(idx, val, len, W + (int64_t)node[t] * dim, dim, lane);
+  }
+}
+
+// The nearest of some nodes to a sparse row, by a wavefront: four at a time, then two, then one.
+template <int kN>
+__device__ __forceinline__ void nearest_csr_step(const int32_t *__restrict__ idx, const float *__restrict__ val, int len,
+                                                 const float *__restrict__ W, const int32_t *__restrict__ lst,
+                                                 const double *__restrict__ wn64, double xn, int dim, int k, int lane, double &best, int &arg) {
+  int node[kN];
+  double d2[kN];
+#pragma unroll
+  for (int t = 0; t < kN; ++t) node[t] = min(max(lst[t], 0), k - 1);      // lists only ever hold valid nodes; never trust memory
+  sqdist_csr_wave<kN>(idx, val, len, W, node, wn64, xn, dim, lane, d2);
+#pragma unroll
+  for (int t = 0; t < kN; ++t)
+    if (nearer(d2[t], node[t], best, arg)) { best = d2[t]; arg = node[t]; }
+}
+
+__device__ __forceinline__ int nearest_csr(const int32_t *__restrict__ idx, const float *__restrict__ val, int len,
+                                           const float *__restrict__ W, const int32_t *__restrict__ lst, int cn,
+                                           const double *__restrict__ wn64, int dim, int k, int lane) {
+  const double xn = csr_row_sqnorm_wave(val, len, lane);
+  double best = INFINITY;
+  int arg = 0x7fffffff, t = 0;
+  for (; t + 4 <= cn; t += 4) nearest_csr_step<4>(idx, val, len, W, lst + t, wn64, xn, dim, k, lane, best, arg);
+  if (t + 2 <= cn) {
+    nearest_csr_step<2>(idx, val, len, W, lst + t, wn64, xn, dim, k, lane, best, arg);
+    t += 2;
+  }
+  if (t < cn) nearest_csr_step<1>(idx, val, len, W, lst + t, wn64, xn, dim, k, lane, best, arg);
+  return arg;
 }
 
 __global__ __launch_bounds__(256) void k_refine_dense(const float *__restrict__ X, const float *__restrict__ W,
@@ -294,6 +354,9 @@ __global__ __launch_bounds__(256) void k_refine_dense(const float *__restrict__ 
 __device__ inline int next_entry(int32_t *list_counts, int lane) {
   const int slice = blockIdx.x & (kListTickets - 1);
   int t = 0;
+  // (opaque: where a loop ends in another "lane 0 only", the compiler may join the two and take the other lanes to the
+  // broadcast below without lane 0, whose entry they would never get)
+  asm volatile("" : "+v"(lane));
   if (lane == 0) t = atomicAdd(list_counts + kListCounts + slice * kListTicketStride, 1);
   return __builtin_amdgcn_readfirstlane(t) * kListTickets + slice;
 }
@@ -329,7 +392,16 @@ __device__ __forceinline__ int nearest_listed(const float *__restrict__ x, const
     for (int u = 0; u < 4; ++u)
       if (nearer(d2[u], id[u], best, arg)) { best = d2[u]; arg = id[u]; }
   }
-  for (; t < cn; ++t) {
+  if (cn - t > 1) {                                // two or three left: as four, the last one again
+    int id[4];
+    double d2[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) id[u] = min(max(lst[min(t + u, cn - 1)], 0), k - 1);
+    sqdist_dense_wave4(x, W, id, dim, lane, d2);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (nearer(d2[u], id[u], best, arg)) { best = d2[u]; arg = id[u]; }
+  } else if (t < cn) {
     const int i = min(max(lst[t], 0), k - 1);
     const double d2 = sqdist_dense_wave(x, W + (int64_t)i * dim, dim, lane);
     if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
@@ -524,15 +596,18 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
             ++under;
             arg = s_node[u0 + __ffsll((long long)m) - 1];
           }
-        if (under != 1) {                          // the plain sums decide
-          arg = 0x7fffffff;
-          for (int u0 = 0; u0 < un; u0 += kWave)
-            for (unsigned long long m = __ballot(u0 + lane < un && !(xn + s_wn[min(u0 + lane, un - 1)] - 2.0 * s_d2[r][min(u0 + lane, un - 1)] > limit));
-                 m; m &= m - 1) {
-              const int i = s_node[u0 + __ffsll((long long)m) - 1];
-              const double d2 = sqdist_dense_wave(X + j * dim, W + (int64_t)i * dim, dim, lane);
-              if (nearer(d2, i, nearest, arg)) { nearest = d2; arg = i; }
-            }
+        if (under != 1) {                          // the plain sums decide, in the place of the products no longer needed
+          int *open = reinterpret_cast<int *>(s_d2[r]);
+          int at = 0;
+          for (int u0 = 0; u0 < un; u0 += kWave) {
+            const int u = min(u0 + lane, un - 1);
+            const bool in = u0 + lane < un && !(xn + s_wn[u] - 2.0 * s_d2[r][u] > limit);
+            const unsigned long long m = __ballot(in);
+            // (a word of the list lies at or before the product its lane has read, and every product before that has been read)
+            if (in) open[at + __popcll(m & ((1ull << lane) - 1))] = s_node[u];
+            at += __popcll(m);
+          }
+          arg = nearest_listed(X + j * dim, W, dim, k, open, at, lane, nearest);
         }
       } else {
         arg = nearest_listed(X + j * dim, W, dim, k, collect_list + (int64_t)(e0 + r) * kListCap, s_cnt[r], lane, best);
@@ -629,7 +704,7 @@ __global__ __launch_bounds__(256) void k_refine_csr(const int64_t *__restrict__ 
                                                     const int32_t *__restrict__ indices,
                                                     const float *__restrict__ values,
                                                     const float *__restrict__ W, const double *__restrict__ wn64,
-                                                    int dim, const int32_t *__restrict__ cand_idx,
+                                                    int dim, int k, const int32_t *__restrict__ cand_idx,
                                                     const int32_t *__restrict__ cand_n,
                                                     const int32_t *__restrict__ refine_list,
                                                     const int32_t *__restrict__ list_counts,
@@ -643,14 +718,7 @@ __global__ __launch_bounds__(256) void k_refine_csr(const int64_t *__restrict__ 
     const int64_t s = indptr[j];
     const int len = (int)(indptr[j + 1] - s);
     const int cn = cand_n[j];
-    const double xn = csr_row_sqnorm_wave(values + s, len, lane);
-    double best = INFINITY;
-    int arg = 0x7fffffff;
-    for (int t = 0; t < cn; ++t) {
-      const int i = cand_idx[j * kCand + t];
-      const double d2 = sqdist_csr_wave(indices + s, values + s, len, W + (int64_t)i * dim, wn64[i], xn, dim, lane);
-      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
-    }
+    const int arg = nearest_csr(indices + s, values + s, len, W, cand_idx + j * kCand, cn, wn64, dim, k, lane);
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;      // no finite distance (non-finite input): node 0, as a plain scan gives
   }
 }
@@ -679,15 +747,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_csr(const int64_t *__restr
       continue;
     }
     const int cn = min(collect_cnt[e], kListCap);
-    const int32_t *lst = collect_list + (int64_t)e * kListCap;
-    const double xn = csr_row_sqnorm_wave(values + s, len, lane);
-    double best = INFINITY;
-    int arg = 0x7fffffff;
-    for (int t = 0; t < cn; ++t) {
-      const int i = min(max(lst[t], 0), k - 1);
-      const double d2 = sqdist_csr_wave(indices + s, values + s, len, W + (int64_t)i * dim, wn64[i], xn, dim, lane);
-      if (nearer(d2, i, best, arg)) { best = d2; arg = i; }
-    }
+    const int arg = nearest_csr(indices + s, values + s, len, W, collect_list + (int64_t)e * kListCap, cn, wn64, dim, k, lane);
     if (lane == 0) bmus[j] = arg == 0x7fffffff ? 0 : arg;
   }
 }
@@ -701,8 +761,10 @@ __device__ __forceinline__ void rescan_row_major(const int32_t *__restrict__ idx
   best = INFINITY;
   arg = 0x7fffffff;
   for (int i = wave; i < k; i += 4) {             // ascending within a wave: strict < keeps the lowest index
-    const double d2 = sqdist_csr_wave(idx, val, len, W + (int64_t)i * dim, wn64[i], xn, dim, lane);
-    if (d2 < best) { best = d2; arg = i; }
+    const int node[1] = {i};
+    double d2[1];
+    sqdist_csr_wave<1>(idx, val, len, W, node, wn64, xn, dim, lane, d2);
+    if (d2[0] < best) { best = d2[0]; arg = i; }
   }
 }
 
@@ -1033,7 +1095,7 @@ hipError_t launch_rescan_dense(som_ctx *c, const float *X, const float *W, int32
 hipError_t launch_refine_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values,
                              const float *W, int32_t *bmus) {
   hipLaunchKernelGGL(k_refine_csr, dim3(persistent_blocks(c, 1 << 20)), dim3(256), 0, c->stream, indptr, indices,
-                     values, W, c->wn64, c->dim, c->cand_idx, c->cand_n, c->refine_list, c->list_counts, bmus);
+                     values, W, c->wn64, c->dim, c->k, c->cand_idx, c->cand_n, c->refine_list, c->list_counts, bmus);
   return hipGetLastError();
 }
 
@@ -1090,8 +1152,10 @@ __global__ __launch_bounds__(kDistThreads) void k_bmu_distances(const float *__r
       if (kCsr) {
         const int64_t rs = indptr[j];
         const int len = (int)(indptr[j + 1] - rs);
-        d2 = sqdist_csr_wave(indices + rs, values + rs, len, w, wn64[b], csr_row_sqnorm_wave(values + rs, len, lane), dim,
-                             lane);
+        const int node[1] = {b};
+        double one[1];
+        sqdist_csr_wave<1>(indices + rs, values + rs, len, W, node, wn64, csr_row_sqnorm_wave(values + rs, len, lane), dim, lane, one);
+        d2 = one[0];
       } else {
         const float *x = X + j * dim;
         double s = 0.0;
