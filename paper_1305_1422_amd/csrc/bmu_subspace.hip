@@ -655,7 +655,7 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xp, in
   }
 }
 
-__global__ __launch_bounds__(256) void k_subspace_project(const _Float16 *__restrict__ Xh1, const _Float16 *__restrict__ Xh, int64_t n,
+__global__ __launch_bounds__(256, 3) void k_subspace_project(const _Float16 *__restrict__ Xh1, const _Float16 *__restrict__ Xh, int64_t n,
                                                           int dim, const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
                                                           const float *__restrict__ xn32, const float *__restrict__ xlost,
                                                           const SubspaceState *__restrict__ state, _Float16 *__restrict__ Y1,
