@@ -164,9 +164,11 @@ __global__ __launch_bounds__(1024) void k_vec_sqnorm(const float *__restrict__ v
   }
 }
 
+// With `met` the columns of the nonzeros are marked too: met[column] = stamp, which no earlier call has used.
 __global__ __launch_bounds__(256) void k_csr_row_sqnorms(const int64_t *__restrict__ indptr,
                                                          const float *__restrict__ values, int64_t n,
-                                                         float *__restrict__ out32) {
+                                                         float *__restrict__ out32, const int32_t *__restrict__ indices, int dim,
+                                                         unsigned *__restrict__ met, unsigned stamp) {
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / kWave);
@@ -175,6 +177,7 @@ __global__ __launch_bounds__(256) void k_csr_row_sqnorms(const int64_t *__restri
     for (int64_t p = indptr[r] + lane; p < indptr[r + 1]; p += kWave) {
       double v = (double)values[p];
       s += v * v;
+      if (met) met[min(max(indices[p], 0), dim - 1)] = stamp;
     }
     s = wave_sum(s);
     if (lane == 0) out32[r] = (float)s;
@@ -415,9 +418,9 @@ hipError_t launch_row_sqnorms(som_ctx *c, const float *A, int64_t nrows, int dim
 }
 
 hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n,
-                                  float *out32) {
+                                  float *out32, const int32_t *indices, unsigned *met, unsigned stamp) {
   hipLaunchKernelGGL(k_csr_row_sqnorms, dim3(grid_for_waves(c, n)), dim3(256), 0, c->stream, indptr,
-                     values, n, out32);
+                     values, n, out32, indices, c->dim, met, stamp);
   return hipGetLastError();
 }
 

@@ -169,6 +169,8 @@ struct som_ctx {
   int Wt32_tried;
   int csr_acc, csr_sweeps;    // sparse BMU kernel: scores per lane and sweep, sweeps per node slice
   float *col_range;       // [2][64][dim] slab minima and maxima of the code-book columns (with Wt)
+  unsigned *met;          // [dim] columns that a search's nonzeros lie in: those that hold its stamp (with Wt)
+  unsigned met_stamp;     // the most recent search's that marked them (0: none, nothing holds it)
   float *qstep;           // [dim] quantisation step of every column of Wt (with Wt)
   double *ct_partial;     // [kCtMaxSlabs][k][3] row sums per column slab of the fused centring / transpose pass (with Wt)
   unsigned *qstep_max_bits;   // [1] (word of list_counts) bit pattern of the largest step
@@ -307,8 +309,8 @@ hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centere
                                   const int32_t *pos_of = nullptr);   // -> Wc, wn32 (= c_i; without the 2 mu.w' term if the instances are centred too), wmax_bits, wn64
 hipError_t launch_row_sqnorms(som_ctx *c, const float *A, int64_t nrows, int dim, const float *mu,
                               float *out32, double *out64, unsigned *max_bits);
-hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n,
-                                  float *out32);
+hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n, float *out32,
+                                  const int32_t *indices = nullptr, unsigned *met = nullptr, unsigned stamp = 0);      // met: marks the columns;
 
 // bmu_direct.hip
 bool direct_search_pays(const som_ctx *c, int64_t n, bool registered);
@@ -434,7 +436,8 @@ hipError_t launch_mask_duplicate_rows(som_ctx *c, const float *W, const int32_t 
 
 // bmu_csr.hip
 constexpr int kCtMaxSlabs = 64;            // column slabs of the fused centring / transpose pass
-hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const SubspaceState *off = nullptr);   // mu, qstep -> Wt, wn32, wn64, wmax_bits
+hipError_t launch_center_transpose_codebook(som_ctx *c, const float *W, const SubspaceState *off = nullptr,
+                                            bool met_only = false /* Wt: only the columns marked by the stamp of now */);   // mu, qstep -> Wt, wn32, wn64, wmax_bits
 void csr_slice_geometry(int k, int *acc, int *sweeps, int *kpad);
 hipError_t launch_scale_values(som_ctx *c, const int32_t *indices, const float *values, int64_t nnz, const SubspaceState *off = nullptr);   // -> vq
 enum { kCsrBadSorted = 1, kCsrBadIndex = 2, kCsrBadOrder = 3, kCsrBadLast = 4, kCsrBadFirst = 5 };   // k_validate_csr: the largest is reported
