@@ -441,7 +441,7 @@ __global__ __launch_bounds__(256) void k_refine_lists_each(const float *__restri
 //   d2 = |x~|^2 + |w~|^2 - 2 x~.w~,   x~ = x - w_0, w~ = w - w_0,
 // whose rounding is below (dim + 8) 2^-50 (|x~| + |w~|)^2; the nodes it cannot tell apart from the nearest - usually there are none - are compared
 // by the plain sums as before, so the decision is the same to the bit.  Bound by the fp64 matrix pipe; the product in fp32 took
-// half the time and left a dozen near-copies per instance to the plain sums (3,000 us).  A union of more than kUnionCap
+// half the time and left a dozen near-copies per instance to the plain sums (3,000 us).  The nodes left go four at a time: 1,000 -> 935 us.  A union of more than kUnionCap
 // nodes, or of more than half of what the lists hold together, is not worth it.  Those lists, and any fewer than
 // kListTileMin, are left to the launch that also rescans (k_lists_left_and_rescan): here, with the three workgroups
 // per CU that the union's LDS leaves room for, 225 such tiles of 1,408 took as long as all the others (30,000 x 1,000 on a trained map

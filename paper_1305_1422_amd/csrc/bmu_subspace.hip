@@ -655,6 +655,8 @@ __device__ __forceinline__ void project_rows(const _Float16 *__restrict__ Xp, in
   }
 }
 
+// (three workgroups per CU: 168 registers, 20 bytes spilled once, against 204 and two; 100,000 x 1,000 with the fine pass's planes 123 -> 116 us,
+// 1,000,000 x 128 93 -> 82)
 __global__ __launch_bounds__(256, 3) void k_subspace_project(const _Float16 *__restrict__ Xh1, const _Float16 *__restrict__ Xh, int64_t n,
                                                           int dim, const _Float16 *__restrict__ Vp, const float *__restrict__ xscale,
                                                           const float *__restrict__ xn32, const float *__restrict__ xlost,
