@@ -702,17 +702,23 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // S.  So the chain is walked once per chunk: it has as many rows as the wavefronts keep in registers, eight each, and
 // the tiles take their entries from there (a tile as a workgroup of its own, chunks of 256 rows: 302 us on 100,000 rows of 50,000 columns
 // and 100 nonzeros, 2,500 nodes; chunks of 256 / 128 / 64 rows with the first ones kept: 223 / 208 / 192, 1.0 GB moved; clearing S and
-// one global atomic for each nonzero outside the 256 most frequent columns, as before: 451).  5e6 nonzeros in rows of 1,000
-// columns: 82 -> 46 us.
+// one global atomic for each nonzero outside the 256 most frequent columns: 451).  5e6 nonzeros in rows of 1,000
+// columns: 82 -> 46 us.  Few chunks of many tiles leave the chip idle, so their tiles are shared out until there are kCsrFill workgroups per CU
+// (whole update, us, atomics / a chunk's tiles by one workgroup / shared out: 16 nodes of 200,000 columns, 32 instances of 100 nonzeros
+// 59 / 76 / 53, 3,200 of 2,000 355 / 1,359 / 185; 100 nodes of 50,000, 4,000 of 4,000 534 / 721 / 246).
 //
-// Long rows with fewer than kTileFrom instances per node: every chosen row is cleared and every nonzero goes straight into S with a global atomic,
-// in instance order; the sort costs more than the atomics there (20,000 columns, 2,500 nodes, the whole update, atomics / tiles, us: one
-// instance per node 241 / 248, two 266 / 273 evenly spread and 265 / 255 skewed, eight 334 / 303 and 400 / 293).
+// Everything goes straight into S instead, the chosen rows cleared and a global atomic for every nonzero in instance order, where that is less:
+// long rows with fewer than kTileFrom instances per node, where the sort costs more (the whole update, atomics / tiles, us: 2,500 nodes of
+// 20,000 columns, one instance per node 241 / 248, two 266 / 273 evenly spread and 265 / 255 skewed, eight 334 / 303 and 400 / 293; two of
+// 13,100 columns 214 / 208, of 16,000 242 / 226); and rows of more than kTilesMax tiles, where going through the tiles costs more than
+// the atomics save (100 nodes, 10,000 instances of 20 / 500 / 2,000 nonzeros: 300,000 columns 218 / 242, 449 / 410, 1,127 / 795; 400,000 274 /
+// 310, 506 / 539, 1,192 / 1,061; 600,000 402 / 451, 621 / 727, 1,319 / 1,486; 1,000,000 637 / 719, 857 / 1,164, 1,556 / 2,263).
 constexpr int kCsrThreads = 512, kCsrWaves = kCsrThreads / kWave;
 constexpr int kCsrRowsPerWave = 8;
 constexpr int kCsrChunkRows = kCsrWaves * kCsrRowsPerWave;
 constexpr int kCsrTile = 13056;           // columns of a row copy in LDS (51 KB: three workgroups per CU)
-constexpr int64_t kTileFrom = 2;
+constexpr int64_t kTileFrom = 2, kTilesMax = 32, kCsrFill = 6;
+static_assert(kCsrChunkRows == kWave, "a lane for every row of a chunk");
 static_assert(kCsrChunkRows % kChunkRows == 0, "the chunk tables are sized for kChunkRows");
 
 // Clears the rows of S whose node has more than `lo` instances.
@@ -724,8 +730,8 @@ __global__ __launch_bounds__(256) void k_zero_rows_if(const int32_t *__restrict_
   for (int c = blockIdx.y * 256 + threadIdx.x; c < dim; c += gridDim.y * 256) dst[c] = 0.f;
 }
 
-// The rows of a chunk are dealt to the wavefronts, whose first lanes hold their bounds; a lane keeps entries lane and lane + 64 of every
-// row, what lies beyond is read again for every tile.
+// A lane holds the bounds of one of the chunk's rows, eight rows to a wavefront, which keeps entries lane and lane + 64 of its own; what lies
+// beyond is dealt to the wavefronts in pieces of 256 entries and read again for every tile.  grid.y: the tiles of a chunk are shared out.
 __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *__restrict__ indptr,
                                                                 const int32_t *__restrict__ indices,
                                                                 const float *__restrict__ values, int dim, int tile,
@@ -734,7 +740,7 @@ __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *_
                                                                 const int32_t *__restrict__ chunk_off,
                                                                 const int32_t *__restrict__ chunk_node, int k,
                                                                 float *__restrict__ S) {
-  extern __shared__ float4 s_row4[];         // tile floats
+  extern __shared__ float4 s_row4[];          // tile floats
   float *s_row = reinterpret_cast<float *>(s_row4);
   const int chunk = blockIdx.x;
   if (chunk >= chunk_off[k]) return;          // uniform over the workgroup
@@ -746,22 +752,22 @@ __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *_
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t from = 0;
   int length = 0;
-  if (lane < kCsrRowsPerWave && lo + wave + lane * kCsrWaves < hi) {
-    const int64_t j = perm[lo + wave + lane * kCsrWaves];
+  int ec[kCsrRowsPerWave][2];
+  float ev[kCsrRowsPerWave][2];
+  auto start = [&](int r) {                   // scalars: the address of a load is one pair of them and the lane
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, r) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)from >> 32), r) << 32);
+  };
+  if (lo + lane < hi) {
+    const int64_t j = perm[lo + lane];
     from = indptr[j];
     length = (int)(indptr[j + 1] - from);
   }
-  int ec[kCsrRowsPerWave][2];
-  float ev[kCsrRowsPerWave][2];
-  auto start = [&](int t) {                   // scalars: the address of a load is one pair of them and the lane
-    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, t) |
-                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)from >> 32), t) << 32);
-  };
 #pragma unroll
   for (int t = 0; t < kCsrRowsPerWave; ++t) {
-    const int len = __builtin_amdgcn_readlane(length, t);
-    const int32_t *ip = indices + start(t);
-    const float *vp = values + start(t);
+    const int r = wave + kCsrWaves * t, len = __builtin_amdgcn_readlane(length, r);
+    const int32_t *ip = indices + start(r);
+    const float *vp = values + start(r);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
       if (lane + 64 * u < len) {
@@ -769,7 +775,9 @@ __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *_
         ev[t][u] = vp[lane + 64 * u];
       }
   }
-  for (int c0 = 0; c0 < dim; c0 += tile) {
+  const int tiles = (dim + tile - 1) / tile, per = (tiles + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int c_end = min(((int)blockIdx.y + 1) * per * tile, dim);      // (few tiles: no overflow)
+  for (int c0 = (int)blockIdx.y * per * tile; c0 < c_end; c0 += tile) {
     const int width = min(tile, dim - c0);
     for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
@@ -779,31 +787,43 @@ __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *_
     };
 #pragma unroll
     for (int t = 0; t < kCsrRowsPerWave; ++t) {
-      const int len = __builtin_amdgcn_readlane(length, t);
+      const int len = __builtin_amdgcn_readlane(length, wave + kCsrWaves * t);
 #pragma unroll
       for (int u = 0; u < 2; ++u)
         if (lane + 64 * u < len) add(ec[t][u], ev[t][u]);
-      if (len > 128) {
-        const int32_t *ip = indices + start(t);
-        const float *vp = values + start(t);
-        for (int x = 128 + lane; x < len; x += 64) add(ip[x], vp[x]);
+    }
+    int before = 0;                         // pieces of the long rows before this one
+    for (unsigned long long m = __ballot(length > 128); m; m &= m - 1) {
+      const int r = __ffsll((long long)m) - 1, len = __builtin_amdgcn_readlane(length, r), pieces = (len - 128 + 255) / 256;
+      const int32_t *ip = indices + start(r);
+      const float *vp = values + start(r);
+      for (int q = (wave - before) & (kCsrWaves - 1); q < pieces; q += kCsrWaves) {
+        const int x = 128 + 256 * q + lane;
+        int xc[4];
+        float xv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {       // (no branch: all in flight)
+          xc[u] = ip[min(x + 64 * u, len - 1)];
+          xv[u] = vp[min(x + 64 * u, len - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (x + 64 * u < len) add(xc[u], xv[u]);
       }
+      before += pieces;
     }
     __syncthreads();
     float *dst = S + (int64_t)b * dim + c0;
-    if (single) {
-      if ((dim & 3) == 0) {                   // tiles are whole fours, so are the rows: 16 bytes a lane
-        for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
-      } else {
-        for (int c = threadIdx.x; c < width; c += kCsrThreads) dst[c] = s_row[c];
-      }
+    if (single && (dim & 3) == 0) {           // tiles are whole fours, so are the rows: 16 bytes a lane
+      for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
     } else {
       for (int c = threadIdx.x; c < width; c += kCsrThreads) {
         const float v = s_row[c];
-        if (v != 0.f) unsafeAtomicAdd(dst + c, v);
+        if (single) dst[c] = v;
+        else if (v != 0.f) unsafeAtomicAdd(dst + c, v);
       }
     }
-    if (c0 + tile < dim) __syncthreads();     // other threads clear the tile for the next one
+    if (c0 + tile < c_end) __syncthreads();      // other threads clear the tile for the next one
   }
 }
 
@@ -990,8 +1010,9 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
                                  const float *values, int64_t n, const int32_t *bmus) {
   int ysplit = (c->dim + 4095) / 4096;
   if (ysplit > 64) ysplit = 64;
-  if (c->dim <= kCsrTile || n >= kTileFrom * (int64_t)c->k) {
-    const int tiles = (c->dim + kCsrTile - 1) / kCsrTile, tile = ((c->dim + tiles - 1) / tiles + 3) & ~3;
+  const int64_t tiles = ((int64_t)c->dim + kCsrTile - 1) / kCsrTile;
+  if (tiles == 1 || (tiles <= kTilesMax && n >= kTileFrom * c->k)) {
+    const int tile = (int)((c->dim + tiles - 1) / tiles + 3) & ~3;
     hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
     if (e != hipSuccess) return e;
     if (c->GxT) {          // matrix smoothing only reads the rows of chosen nodes
@@ -1001,11 +1022,11 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
       e = launch_fill_zero_u32(c->stream, c->S, (int64_t)c->k * c->dim);
       if (e != hipSuccess) return e;
     }
-    int64_t max_chunks = n / kCsrChunkRows + (n < c->k ? n : c->k);
-    if (max_chunks < 1) max_chunks = 1;
-    hipLaunchKernelGGL(k_accumulate_csr, dim3((unsigned)max_chunks), dim3(kCsrThreads), (size_t)tile * sizeof(float),
-                       c->stream, indptr, indices, values, c->dim, tile, c->sort_val[0], c->seg_off, c->chunk_off,
-                       c->chunk_node, c->k, c->S);
+    const int64_t max_chunks = n / kCsrChunkRows + (n < c->k ? n : c->k);
+    int64_t ways = (kCsrFill * (int64_t)c->n_cu + max_chunks - 1) / max_chunks;
+    if (ways > tiles) ways = tiles;
+    hipLaunchKernelGGL(k_accumulate_csr, dim3((unsigned)max_chunks, (unsigned)ways), dim3(kCsrThreads), (size_t)tile * sizeof(float), c->stream,
+                       indptr, indices, values, c->dim, tile, c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
     return hipGetLastError();
   }
   hipError_t e = launch_fill_zero_u32(c->stream, c->counts, c->k);

@@ -40,3 +40,34 @@ def test_sums_at_the_edges_of_tiles_and_chunks(oracle, dim, per_node):
     got = som.codebook.cpu().numpy()
     assert np.abs(got - want).max() <= 2.0 ** -22 * np.abs(want).max()      # one division, its operands exact: an ulp or two
     som.close()
+
+
+@pytest.mark.parametrize("dim", [26113, 104448, 417792, 417793])
+@pytest.mark.parametrize("n", [12, 200])
+def test_sums_of_long_rows_and_many_tiles(dim, n):
+    """Three, eight and 32 tiles of columns shared out to several workgroups, and the first row length that goes by atomics; rows at the
+    edges of what a lane keeps (128 entries) and of the pieces of 256 beyond it, one of thousands among short ones; nodes of one chunk and of
+    several.  Small whole numbers: any order of the additions gives the same."""
+    from paper_1305_1422_amd import Som
+    k = 6
+    rng = np.random.default_rng(dim + n)
+    bmus = rng.integers(0, k - 1, size=n).astype(np.int32)      # (the last node has none)
+    bmus[n // 3:] = 2
+    lengths = rng.choice([0, 1, 127, 128, 129, 384, 385, 2176, 2177, 6000], size=n)
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    indptr[1:] = np.cumsum(lengths)
+    indices = np.concatenate([np.sort(rng.choice(dim, size=m, replace=False)) for m in lengths]).astype(np.int32)
+    if lengths[-1]:
+        indices[-1] = dim - 1                            # the last column of the last tile
+    values = rng.integers(1, 9, size=indptr[-1]).astype(np.float32)
+    W = rng.random((k, dim)).astype(np.float32)
+    som = Som(2, 3, dim, "planar", "square", codebook=torch.from_numpy(W))
+    som.set_neighborhood("bubble")
+    csr = P.csr_to_dev((indptr, indices, values))
+    som.update(csr, P.to_dev(bmus), 0.5)
+    torch.cuda.synchronize()
+    S, C = np.zeros((k, dim)), np.bincount(bmus, minlength=k)
+    np.add.at(S, (np.repeat(bmus, lengths), indices), values)
+    want = np.where(C[:, None] > 0, S / np.maximum(C, 1)[:, None], W)
+    assert np.abs(som.codebook.cpu().numpy() - want).max() <= 2.0 ** -22 * np.abs(want).max()      # as above
+    som.close()
