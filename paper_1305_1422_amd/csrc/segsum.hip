@@ -699,7 +699,7 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // beforehand; the chunks of a larger node add their nonzero entries to a row cleared by k_zero_rows_if.
 //
 // Bound by the chain of loads that leads to a chunk's entries (chunk, node, ids, row bounds, entries) and, with long rows, by writing
-// S.  So the chain is walked once per chunk: it has as many rows as the wavefronts keep in registers, eight each, and
+// S.  So the chain is walked once per chunk: it has as many rows as eight wavefronts keep in registers, eight each, and
 // the tiles take their entries from there (a tile as a workgroup of its own, chunks of 256 rows: 302 us on 100,000 rows of 50,000 columns
 // and 100 nonzeros, 2,500 nodes; chunks of 256 / 128 / 64 rows with the first ones kept: 223 / 208 / 192, 1.0 GB moved; clearing S and
 // one global atomic for each nonzero outside the 256 most frequent columns: 451).  5e6 nonzeros in rows of 1,000
@@ -713,12 +713,14 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // 13,100 columns 214 / 208, of 16,000 242 / 226); and rows of more than kTilesMax tiles, where going through the tiles costs more than
 // the atomics save (100 nodes, 10,000 instances of 20 / 500 / 2,000 nonzeros: 300,000 columns 218 / 242, 449 / 410, 1,127 / 795; 400,000 274 /
 // 310, 506 / 539, 1,192 / 1,061; 600,000 402 / 451, 621 / 727, 1,319 / 1,486; 1,000,000 637 / 719, 857 / 1,164, 1,556 / 2,263).
-constexpr int kCsrThreads = 512, kCsrWaves = kCsrThreads / kWave;
-constexpr int kCsrRowsPerWave = 8;
-constexpr int kCsrChunkRows = kCsrWaves * kCsrRowsPerWave;
+//
+// Where a node has few entries the wavefronts of a chunk have nothing to do and many workgroups to start: two of them then, four rows
+// each at a time (whole update, us, eight wavefronts / two: 10,000 nodes, rows of 200 columns and 20 nonzeros, 1 / 4 / 10 instances per
+// node 101 / 83, 118 / 90, 123 / 100; 500 and 40 104 / 89, 123 / 96, 126 / 111; 1,000 and 100 122 / 107, 144 / 131, 164 / 163; 40,000 nodes, 2,000 and
+// 100, 2 per node 785 / 697; but 2,500 nodes, 1,000 and 100, 10 per node 73 / 76, 20 86 / 89, 13,056 and 100, 5 per node 227 / 235).
+constexpr int kCsrChunkRows = 64;
 constexpr int kCsrTile = 13056;           // columns of a row copy in LDS (51 KB: three workgroups per CU)
-constexpr int64_t kTileFrom = 2, kTilesMax = 32, kCsrFill = 6;
-static_assert(kCsrChunkRows == kWave, "a lane for every row of a chunk");
+constexpr int64_t kTileFrom = 2, kTilesMax = 32, kCsrFill = 6, kCsrFewEntries = 768;
 static_assert(kCsrChunkRows % kChunkRows == 0, "the chunk tables are sized for kChunkRows");
 
 // Clears the rows of S whose node has more than `lo` instances.
@@ -730,9 +732,11 @@ __global__ __launch_bounds__(256) void k_zero_rows_if(const int32_t *__restrict_
   for (int c = blockIdx.y * 256 + threadIdx.x; c < dim; c += gridDim.y * 256) dst[c] = 0.f;
 }
 
-// A lane holds the bounds of one of the chunk's rows, eight rows to a wavefront, which keeps entries lane and lane + 64 of its own; what lies
-// beyond is dealt to the wavefronts in pieces of 256 entries and read again for every tile.  grid.y: the tiles of a chunk are shared out.
-__global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *__restrict__ indptr,
+// A lane holds the bounds of one row of the batch at hand, kEach rows to a wavefront, which keeps entries lane and lane + 64 of its own; what lies
+// beyond is dealt to the wavefronts in pieces of 256 entries and read again for every tile.  With more than one batch to a chunk there
+// is one tile.  grid.y: the tiles of a chunk are shared out.
+template <int kWaves, int kEach>
+__global__ __launch_bounds__(64 * kWaves) void k_accumulate_csr(const int64_t *__restrict__ indptr,
                                                                 const int32_t *__restrict__ indices,
                                                                 const float *__restrict__ values, int dim, int tile,
                                                                 const int32_t *__restrict__ perm,
@@ -740,84 +744,96 @@ __global__ __launch_bounds__(kCsrThreads) void k_accumulate_csr(const int64_t *_
                                                                 const int32_t *__restrict__ chunk_off,
                                                                 const int32_t *__restrict__ chunk_node, int k,
                                                                 float *__restrict__ S) {
+  constexpr int kThreads = 64 * kWaves, kBatch = kWaves * kEach;
+  static_assert(kBatch <= kWave && kCsrChunkRows % kBatch == 0, "a lane for every row of a batch");
   extern __shared__ float4 s_row4[];          // tile floats
   float *s_row = reinterpret_cast<float *>(s_row4);
   const int chunk = blockIdx.x;
   if (chunk >= chunk_off[k]) return;          // uniform over the workgroup
   const int b = chunk_node[chunk];
   const int first_chunk = chunk_off[b];
-  const int lo = seg_off[b] + (chunk - first_chunk) * kCsrChunkRows;
+  int lo = seg_off[b] + (chunk - first_chunk) * kCsrChunkRows;
   const int hi = min(lo + kCsrChunkRows, seg_off[b + 1]);
   const bool single = (chunk_off[b + 1] - first_chunk) == 1;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int64_t from = 0;
-  int length = 0;
-  int ec[kCsrRowsPerWave][2];
-  float ev[kCsrRowsPerWave][2];
+  int64_t from;
+  int length;
+  int ec[kEach][2];
+  float ev[kEach][2];
   auto start = [&](int r) {                   // scalars: the address of a load is one pair of them and the lane
     return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, r) |
                      (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)from >> 32), r) << 32);
   };
-  if (lo + lane < hi) {
-    const int64_t j = perm[lo + lane];
-    from = indptr[j];
-    length = (int)(indptr[j + 1] - from);
-  }
+  auto load = [&] {
+    from = 0;
+    length = 0;
+    if (lane < kBatch && lo + lane < hi) {
+      const int64_t j = perm[lo + lane];
+      from = indptr[j];
+      length = (int)(indptr[j + 1] - from);
+    }
 #pragma unroll
-  for (int t = 0; t < kCsrRowsPerWave; ++t) {
-    const int r = wave + kCsrWaves * t, len = __builtin_amdgcn_readlane(length, r);
-    const int32_t *ip = indices + start(r);
-    const float *vp = values + start(r);
+    for (int t = 0; t < kEach; ++t) {
+      const int r = wave + kWaves * t, len = __builtin_amdgcn_readlane(length, r);
+      const int32_t *ip = indices + start(r);
+      const float *vp = values + start(r);
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (lane + 64 * u < len) {
-        ec[t][u] = ip[lane + 64 * u];
-        ev[t][u] = vp[lane + 64 * u];
-      }
-  }
+      for (int u = 0; u < 2; ++u)
+        if (lane + 64 * u < len) {
+          ec[t][u] = ip[lane + 64 * u];
+          ev[t][u] = vp[lane + 64 * u];
+        }
+    }
+  };
   const int tiles = (dim + tile - 1) / tile, per = (tiles + (int)gridDim.y - 1) / (int)gridDim.y;
   const int c_end = min(((int)blockIdx.y + 1) * per * tile, dim);      // (few tiles: no overflow)
+  load();
   for (int c0 = (int)blockIdx.y * per * tile; c0 < c_end; c0 += tile) {
     const int width = min(tile, dim - c0);
-    for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c = threadIdx.x; 4 * c < width; c += kThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     auto add = [&](int c, float v) {
       const unsigned at = (unsigned)(min(max(c, 0), dim - 1) - c0);
       if (at < (unsigned)width) atomicAdd(&s_row[at], v);
     };
+    for (;;) {
 #pragma unroll
-    for (int t = 0; t < kCsrRowsPerWave; ++t) {
-      const int len = __builtin_amdgcn_readlane(length, wave + kCsrWaves * t);
+      for (int t = 0; t < kEach; ++t) {
+        const int len = __builtin_amdgcn_readlane(length, wave + kWaves * t);
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        if (lane + 64 * u < len) add(ec[t][u], ev[t][u]);
-    }
-    int before = 0;                         // pieces of the long rows before this one
-    for (unsigned long long m = __ballot(length > 128); m; m &= m - 1) {
-      const int r = __ffsll((long long)m) - 1, len = __builtin_amdgcn_readlane(length, r), pieces = (len - 128 + 255) / 256;
-      const int32_t *ip = indices + start(r);
-      const float *vp = values + start(r);
-      for (int q = (wave - before) & (kCsrWaves - 1); q < pieces; q += kCsrWaves) {
-        const int x = 128 + 256 * q + lane;
-        int xc[4];
-        float xv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {       // (no branch: all in flight)
-          xc[u] = ip[min(x + 64 * u, len - 1)];
-          xv[u] = vp[min(x + 64 * u, len - 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (x + 64 * u < len) add(xc[u], xv[u]);
+        for (int u = 0; u < 2; ++u)
+          if (lane + 64 * u < len) add(ec[t][u], ev[t][u]);
       }
-      before += pieces;
+      int before = 0;                         // pieces of the long rows before this one
+      for (unsigned long long m = __ballot(length > 128); m; m &= m - 1) {
+        const int r = __ffsll((long long)m) - 1, len = __builtin_amdgcn_readlane(length, r), pieces = (len - 128 + 255) / 256;
+        const int32_t *ip = indices + start(r);
+        const float *vp = values + start(r);
+        for (int q = (wave - before) & (kWaves - 1); q < pieces; q += kWaves) {
+          const int x = 128 + 256 * q + lane;
+          int xc[4];
+          float xv[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {       // (no branch: all in flight)
+            xc[u] = ip[min(x + 64 * u, len - 1)];
+            xv[u] = vp[min(x + 64 * u, len - 1)];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (x + 64 * u < len) add(xc[u], xv[u]);
+        }
+        before += pieces;
+      }
+      if (lo + kBatch >= hi) break;           // uniform over the workgroup
+      lo += kBatch;
+      load();
     }
     __syncthreads();
     float *dst = S + (int64_t)b * dim + c0;
     if (single && (dim & 3) == 0) {           // tiles are whole fours, so are the rows: 16 bytes a lane
-      for (int c = threadIdx.x; 4 * c < width; c += kCsrThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
+      for (int c = threadIdx.x; 4 * c < width; c += kThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
     } else {
-      for (int c = threadIdx.x; c < width; c += kCsrThreads) {
+      for (int c = threadIdx.x; c < width; c += kThreads) {
         const float v = s_row[c];
         if (single) dst[c] = v;
         else if (v != 0.f) unsafeAtomicAdd(dst + c, v);
@@ -1007,26 +1023,32 @@ hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const 
 }
 
 hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
-                                 const float *values, int64_t n, const int32_t *bmus) {
+                                 const float *values, int64_t n, int64_t nnz, const int32_t *bmus) {
   int ysplit = (c->dim + 4095) / 4096;
   if (ysplit > 64) ysplit = 64;
-  const int64_t tiles = ((int64_t)c->dim + kCsrTile - 1) / kCsrTile;
-  if (tiles == 1 || (tiles <= kTilesMax && n >= kTileFrom * c->k)) {
+  const int64_t k = c->k, tiles = ((int64_t)c->dim + kCsrTile - 1) / kCsrTile;
+  if (tiles == 1 || (tiles <= kTilesMax && n >= kTileFrom * k)) {
     const int tile = (int)((c->dim + tiles - 1) / tiles + 3) & ~3;
+    const bool few = tiles == 1 && nnz < kCsrFewEntries * k;
     hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
     if (e != hipSuccess) return e;
     if (c->GxT) {          // matrix smoothing only reads the rows of chosen nodes
-      hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, kCsrChunkRows, c->dim,
-                         c->S);
+      hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, kCsrChunkRows, c->dim, c->S);
     } else {               // the stencil smoothing reads every row: those of nodes nobody chose must be zero
-      e = launch_fill_zero_u32(c->stream, c->S, (int64_t)c->k * c->dim);
+      e = launch_fill_zero_u32(c->stream, c->S, k * c->dim);
       if (e != hipSuccess) return e;
     }
-    const int64_t max_chunks = n / kCsrChunkRows + (n < c->k ? n : c->k);
+    const int64_t max_chunks = n / kCsrChunkRows + (n < k ? n : k);
     int64_t ways = (kCsrFill * (int64_t)c->n_cu + max_chunks - 1) / max_chunks;
     if (ways > tiles) ways = tiles;
-    hipLaunchKernelGGL(k_accumulate_csr, dim3((unsigned)max_chunks, (unsigned)ways), dim3(kCsrThreads), (size_t)tile * sizeof(float), c->stream,
-                       indptr, indices, values, c->dim, tile, c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
+    const dim3 grid((unsigned)max_chunks, (unsigned)ways);
+    const size_t lds = (size_t)tile * sizeof(float);
+    if (few)
+      hipLaunchKernelGGL((k_accumulate_csr<2, 4>), grid, dim3(128), lds, c->stream, indptr, indices, values, c->dim, tile,
+                         c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
+    else
+      hipLaunchKernelGGL((k_accumulate_csr<8, 8>), grid, dim3(512), lds, c->stream, indptr, indices, values, c->dim, tile,
+                         c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
     return hipGetLastError();
   }
   hipError_t e = launch_fill_zero_u32(c->stream, c->counts, c->k);

@@ -655,11 +655,11 @@ static int update_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bm
   return SOM_OK;
 }
 
-static int update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n,
+static int update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, const float *values, int64_t n, int64_t nnz,
                       const int32_t *bmus, float *W) {
   {
     StageTimer t(c, 3);
-    SOM_LAUNCH(c, launch_accumulate_csr(c, indptr, indices, values, n, bmus));
+    SOM_LAUNCH(c, launch_accumulate_csr(c, indptr, indices, values, n, nnz, bmus));
   }
   StageTimer t(c, 4);
   SOM_LAUNCH(c, launch_smooth_and_divide(c, W));
@@ -1011,7 +1011,7 @@ int som_update_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices, co
   if (!rc) rc = ensure_rows(c, n, false);
   if (rc) return rc;
   SOM_LAUNCH(c, launch_epoch_params(c, epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), false));
-  return update_csr(c, indptr, indices, values, n, bmus, codebook);
+  return update_csr(c, indptr, indices, values, n, nnz, bmus, codebook);
 }
 
 int som_train_epoch_dense(som_ctx *c, const float *data, int64_t n, float *codebook, float radius, float scale,
@@ -1050,7 +1050,7 @@ int som_train_epoch_csr(som_ctx *c, const int64_t *indptr, const int32_t *indice
   SOM_LAUNCH(c, launch_epoch_params(c, epoch_schedule(c, 0, 1, radius, radius, scale, scale, SOM_COOL_LINEAR), true));
   rc = bmu_search_csr(c, indptr, indices, values, n, nnz, codebook, bmus, reg, true, true, radius);
   if (rc) return rc;
-  return update_csr(c, indptr, indices, values, n, bmus, codebook);
+  return update_csr(c, indptr, indices, values, n, nnz, bmus, codebook);
 }
 
 int som_set_data_dense(som_ctx *c, const float *data, int64_t n) {
@@ -1135,7 +1135,7 @@ int som_train_snapshots(som_ctx *c, int n_epochs, float radius0, float radiusN, 
     } else {
       rc = bmu_search_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, codebook, bmus, true,
                           true, true, e > 0 ? cooled(radius0, radiusN, n_epochs, e, cooling) : 0.0);
-      if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, bmus, codebook);
+      if (!rc) rc = update_csr(c, c->d_indptr, c->d_indices, c->d_values, c->d_n, c->d_nnz, bmus, codebook);
     }
     if (rc) return rc;
     if (snapshots >= 1) SOM_LAUNCH(c, launch_umatrix(c, codebook, umatrices + (size_t)e * c->k));

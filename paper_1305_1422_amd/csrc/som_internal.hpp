@@ -456,7 +456,7 @@ bool gather_pays(const som_ctx *c, int64_t n);                                 /
 hipError_t launch_accumulate_dense(som_ctx *c, const float *X, int64_t n, const int32_t *bmus,
                                    const EpochSchedule *tables);               // -> S, counts (... and writes the epoch's tables if asked)
 hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_t *indices,
-                                 const float *values, int64_t n, const int32_t *bmus);   // -> S, counts
+                                 const float *values, int64_t n, int64_t nnz, const int32_t *bmus);   // -> S, counts
 
 // smooth.hip
 hipError_t launch_epoch_params(som_ctx *c, const EpochSchedule &q, bool search);

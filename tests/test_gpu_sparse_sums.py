@@ -71,3 +71,44 @@ def test_sums_of_long_rows_and_many_tiles(dim, n):
     want = np.where(C[:, None] > 0, S / np.maximum(C, 1)[:, None], W)
     assert np.abs(som.codebook.cpu().numpy() - want).max() <= 2.0 ** -22 * np.abs(want).max()      # as above
     som.close()
+
+
+def _check_sums(rows, cols, dim, bmus, lengths, rng):
+    """Bubble below radius 1: every node the mean of its own instances, whose entries are small whole numbers (any order adds up the same)."""
+    from paper_1305_1422_amd import Som
+    k, n = rows * cols, len(bmus)
+    indptr = np.zeros(n + 1, dtype=np.int64)
+    indptr[1:] = np.cumsum(lengths)
+    first = rng.integers(0, dim, size=n)
+    step = np.arange(indptr[-1]) - np.repeat(indptr[:-1], lengths)
+    column = (np.repeat(first, lengths) + step) % dim    # consecutive columns, wrapped: put in order row by row
+    row = np.repeat(np.arange(n), lengths)
+    indices = column[np.lexsort((column, row))].astype(np.int32)
+    values = rng.integers(1, 9, size=indptr[-1]).astype(np.float32)
+    W = rng.random((k, dim)).astype(np.float32)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
+    som.set_neighborhood("bubble")
+    som.update(P.csr_to_dev((indptr, indices, values)), P.to_dev(bmus.astype(np.int32)), 0.5)
+    torch.cuda.synchronize()
+    C = np.bincount(bmus, minlength=k)
+    S = np.bincount(bmus[row].astype(np.int64) * dim + indices, weights=values, minlength=k * dim).reshape(k, dim)
+    want = np.where(C[:, None] > 0, S / np.maximum(C, 1)[:, None], W)
+    assert np.abs(som.codebook.cpu().numpy() - want).max() <= 2.0 ** -22 * np.abs(want).max()      # one division, as above
+    som.close()
+
+
+@pytest.mark.parametrize("dim,more", [(7, 0), (500, 0), (500, 1), (501, 0), (13056, 0), (13056, 1), (13053, 0)])
+def test_sums_of_nodes_with_few_entries(dim, more):
+    """Both sides of 768 entries per node (rows of seven columns never reach it): nodes of 0, 1, 8, 9, 16, 63, 64, 65 and 130 instances."""
+    rng = np.random.default_rng(dim + more)
+    rows, cols = 10, 12
+    k = rows * cols
+    sizes = np.array([0, 1, 8, 9, 16, 63, 64, 65, 130, 0] + [2] * (k - 10))
+    bmus = np.repeat(np.arange(k), sizes)
+    rng.shuffle(bmus)
+    n, nnz = len(bmus), 768 * k - 1 + more
+    lengths = np.minimum(np.full(n, nnz // n), dim)
+    if lengths[0] < dim:
+        lengths[:nnz - lengths.sum()] += 1
+        assert lengths.sum() == nnz
+    _check_sums(rows, cols, dim, bmus, lengths, rng)
