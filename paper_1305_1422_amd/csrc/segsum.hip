@@ -718,7 +718,13 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // each at a time (whole update, us, eight wavefronts / two: 10,000 nodes, rows of 200 columns and 20 nonzeros, 1 / 4 / 10 instances per
 // node 101 / 83, 118 / 90, 123 / 100; 500 and 40 104 / 89, 123 / 96, 126 / 111; 1,000 and 100 122 / 107, 144 / 131, 164 / 163; 40,000 nodes, 2,000 and
 // 100, 2 per node 785 / 697; but 2,500 nodes, 1,000 and 100, 10 per node 73 / 76, 20 86 / 89, 13,056 and 100, 5 per node 227 / 235).
-constexpr int kCsrChunkRows = 64;
+//
+// Up to about a hundred instances of short rows per node: chunks of 128, which most nodes fit, so that a node is still written once. Each half
+// of the wavefronts adds its 64 rows to a copy of its own, so no sum is longer than in a chunk of 64 (whole update, us, chunks of 64 / of
+// 128: 900 nodes of 4,000 columns, 100 nonzeros, 60 instances per node 107 / 103, 90 138 / 118, 104 129 / 128; 256 of 1,000, 40 57 / 58, 64 78 / 69,
+// 90 66 / 63, 104 74 / 77; with 100 nodes, which don't fill the chip, 100 per node 54 / 59; beyond, the second chunk of a node is nearly empty:
+// 130 145 / 153).
+constexpr int kCsrChunkRows = 64;         // (or twice as many, in two copies of the row)
 constexpr int kCsrTile = 13056;           // columns of a row copy in LDS (51 KB: three workgroups per CU)
 constexpr int64_t kTileFrom = 2, kTilesMax = 32, kCsrFill = 6, kCsrFewEntries = 768;
 static_assert(kCsrChunkRows % kChunkRows == 0, "the chunk tables are sized for kChunkRows");
@@ -734,8 +740,8 @@ __global__ __launch_bounds__(256) void k_zero_rows_if(const int32_t *__restrict_
 
 // A lane holds the bounds of one row of the batch at hand, kEach rows to a wavefront, which keeps entries lane and lane + 64 of its own; what lies
 // beyond is dealt to the wavefronts in pieces of 256 entries and read again for every tile.  With more than one batch to a chunk there
-// is one tile.  grid.y: the tiles of a chunk are shared out.
-template <int kWaves, int kEach>
+// is one tile.  grid.y: the tiles of a chunk are shared out.  kCopies = 2: the wavefronts' halves have a copy of the row each.
+template <int kWaves, int kEach, int kCopies>
 __global__ __launch_bounds__(64 * kWaves) void k_accumulate_csr(const int64_t *__restrict__ indptr,
                                                                 const int32_t *__restrict__ indices,
                                                                 const float *__restrict__ values, int dim, int tile,
@@ -744,18 +750,19 @@ __global__ __launch_bounds__(64 * kWaves) void k_accumulate_csr(const int64_t *_
                                                                 const int32_t *__restrict__ chunk_off,
                                                                 const int32_t *__restrict__ chunk_node, int k,
                                                                 float *__restrict__ S) {
-  constexpr int kThreads = 64 * kWaves, kBatch = kWaves * kEach;
-  static_assert(kBatch <= kWave && kCsrChunkRows % kBatch == 0, "a lane for every row of a batch");
-  extern __shared__ float4 s_row4[];          // tile floats
+  constexpr int kThreads = 64 * kWaves, kBatch = kWaves * kEach, kRows = kCsrChunkRows * kCopies;
+  static_assert(kBatch <= kWave && kRows % kBatch == 0, "a lane for every row of a batch");
+  extern __shared__ float4 s_row4[];          // kCopies x tile floats
   float *s_row = reinterpret_cast<float *>(s_row4);
   const int chunk = blockIdx.x;
   if (chunk >= chunk_off[k]) return;          // uniform over the workgroup
   const int b = chunk_node[chunk];
   const int first_chunk = chunk_off[b];
-  int lo = seg_off[b] + (chunk - first_chunk) * kCsrChunkRows;
-  const int hi = min(lo + kCsrChunkRows, seg_off[b + 1]);
+  int lo = seg_off[b] + (chunk - first_chunk) * kRows;
+  const int hi = min(lo + kRows, seg_off[b + 1]);
   const bool single = (chunk_off[b + 1] - first_chunk) == 1;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float *own = kCopies > 1 ? s_row + (2 * wave / kWaves) * tile : s_row;
   int64_t from;
   int length;
   int ec[kEach][2];
@@ -790,11 +797,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_accumulate_csr(const int64_t *_
   load();
   for (int c0 = (int)blockIdx.y * per * tile; c0 < c_end; c0 += tile) {
     const int width = min(tile, dim - c0);
-    for (int c = threadIdx.x; 4 * c < width; c += kThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c = threadIdx.x; 4 * c < kCopies * tile; c += kThreads) s_row4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     auto add = [&](int c, float v) {
       const unsigned at = (unsigned)(min(max(c, 0), dim - 1) - c0);
-      if (at < (unsigned)width) atomicAdd(&s_row[at], v);
+      if (at < (unsigned)width) atomicAdd(&own[at], v);
     };
     for (;;) {
 #pragma unroll
@@ -831,10 +838,17 @@ __global__ __launch_bounds__(64 * kWaves) void k_accumulate_csr(const int64_t *_
     __syncthreads();
     float *dst = S + (int64_t)b * dim + c0;
     if (single && (dim & 3) == 0) {           // tiles are whole fours, so are the rows: 16 bytes a lane
-      for (int c = threadIdx.x; 4 * c < width; c += kThreads) reinterpret_cast<float4 *>(dst)[c] = s_row4[c];
+      for (int c = threadIdx.x; 4 * c < width; c += kThreads) {
+        float4 v = s_row4[c];
+        if (kCopies > 1) {
+          const float4 w = s_row4[tile / 4 + c];
+          v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+        }
+        reinterpret_cast<float4 *>(dst)[c] = v;
+      }
     } else {
       for (int c = threadIdx.x; c < width; c += kThreads) {
-        const float v = s_row[c];
+        const float v = kCopies > 1 ? s_row[c] + s_row[tile + c] : s_row[c];
         if (single) dst[c] = v;
         else if (v != 0.f) unsafeAtomicAdd(dst + c, v);
       }
@@ -1030,24 +1044,29 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
   if (tiles == 1 || (tiles <= kTilesMax && n >= kTileFrom * k)) {
     const int tile = (int)((c->dim + tiles - 1) / tiles + 3) & ~3;
     const bool few = tiles == 1 && nnz < kCsrFewEntries * k;
-    hipError_t e = launch_group_by_bmu(c, bmus, n, kCsrChunkRows);
+    const bool twice = !few && tiles == 1 && 2 * tile <= kCsrTile && k >= c->n_cu && n >= 48 * k && n <= 100 * k;
+    const int rows = twice ? 2 * kCsrChunkRows : kCsrChunkRows;
+    hipError_t e = launch_group_by_bmu(c, bmus, n, rows);
     if (e != hipSuccess) return e;
     if (c->GxT) {          // matrix smoothing only reads the rows of chosen nodes
-      hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, kCsrChunkRows, c->dim, c->S);
+      hipLaunchKernelGGL(k_zero_rows_if, dim3(c->k, ysplit), dim3(256), 0, c->stream, c->counts, rows, c->dim, c->S);
     } else {               // the stencil smoothing reads every row: those of nodes nobody chose must be zero
       e = launch_fill_zero_u32(c->stream, c->S, k * c->dim);
       if (e != hipSuccess) return e;
     }
-    const int64_t max_chunks = n / kCsrChunkRows + (n < k ? n : k);
+    const int64_t max_chunks = n / rows + (n < k ? n : k);
     int64_t ways = (kCsrFill * (int64_t)c->n_cu + max_chunks - 1) / max_chunks;
     if (ways > tiles) ways = tiles;
     const dim3 grid((unsigned)max_chunks, (unsigned)ways);
     const size_t lds = (size_t)tile * sizeof(float);
     if (few)
-      hipLaunchKernelGGL((k_accumulate_csr<2, 4>), grid, dim3(128), lds, c->stream, indptr, indices, values, c->dim, tile,
+      hipLaunchKernelGGL((k_accumulate_csr<2, 4, 1>), grid, dim3(128), lds, c->stream, indptr, indices, values, c->dim, tile,
+                         c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
+    else if (twice)
+      hipLaunchKernelGGL((k_accumulate_csr<8, 8, 2>), grid, dim3(512), 2 * lds, c->stream, indptr, indices, values, c->dim, tile,
                          c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
     else
-      hipLaunchKernelGGL((k_accumulate_csr<8, 8>), grid, dim3(512), lds, c->stream, indptr, indices, values, c->dim, tile,
+      hipLaunchKernelGGL((k_accumulate_csr<8, 8, 1>), grid, dim3(512), lds, c->stream, indptr, indices, values, c->dim, tile,
                          c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
     return hipGetLastError();
   }

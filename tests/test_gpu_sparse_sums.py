@@ -112,3 +112,18 @@ def test_sums_of_nodes_with_few_entries(dim, more):
         lengths[:nnz - lengths.sum()] += 1
         assert lengths.sum() == nnz
     _check_sums(rows, cols, dim, bmus, lengths, rng)
+
+
+@pytest.mark.parametrize("dim", [30, 31, 6528, 6529])
+@pytest.mark.parametrize("n", [48 * 256 - 1, 48 * 256, 100 * 256, 100 * 256 + 1])
+def test_sums_of_about_a_hundred_instances_a_node(dim, n):
+    """Chunks of 128 rows in two copies of the row, and the sizes on both sides of them: a node of none, of 1, 31 .. 33, 63 .. 65, 127 .. 129, 256 and 257
+    instances, the others share the rest."""
+    rng = np.random.default_rng(dim + n)
+    sizes = np.zeros(256, dtype=np.int64)
+    sizes[:14] = [0, 1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 256, 257, 8]
+    sizes[14:] = (n - sizes.sum()) // 242
+    sizes[255] += n - sizes.sum()
+    bmus = np.repeat(np.arange(256), sizes)
+    rng.shuffle(bmus)
+    _check_sums(16, 16, dim, bmus, rng.choice([20, 25, 30], size=n), rng)
