@@ -170,17 +170,17 @@ def test_non_finite_values_do_not_leave_the_index_range(oracle):
     som.close()
 
 
-@pytest.mark.parametrize("dim", [16384, 16385])
-def test_update_csr_at_the_row_length_where_the_accumulation_changes(oracle, dim):
-    """Rows of up to 16,384 columns are summed in LDS per node, longer ones with global atomics; both sides
-    of the switch, with one node that holds more instances than one chunk."""
+@pytest.mark.parametrize("dim,n", [(16384, 700), (16385, 700), (13056, 23), (13057, 23), (13057, 24)])
+def test_update_csr_at_the_row_length_where_the_accumulation_changes(oracle, dim, n):
+    """Rows of more than 13,056 columns are summed with global atomics where there are fewer than two instances per node (12 nodes), in
+    tiles in LDS otherwise: both sides of both lines, and rows of two tiles with a node that holds more instances than one chunk."""
     from paper_1305_1422_amd import Som
-    n, rows, cols = 700, 3, 4
+    rows, cols = 3, 4
     csr = sparse_zipf_csr(n, dim, 43, mean_len=12.0, max_len=40)
     rng = np.random.default_rng(44)
     W = rng.random((rows * cols, dim)).astype(np.float32)
     bmus = rng.integers(0, rows * cols, size=n).astype(np.int32)
-    bmus[:400] = 5
+    bmus[:n * 4 // 7] = 5
     bmus[bmus == 9] = 2                                    # node 9 is chosen by nobody
     som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
     som.update(P.csr_to_dev(csr), P.to_dev(bmus), 1.0)
@@ -201,6 +201,28 @@ def test_sparse_update_on_a_map_side_above_the_coefficient_matrix_limit(oracle):
     csr_d = P.csr_to_dev(csr)
     for radius in (25.0, 2.0):
         P.epoch_parity_csr(oracle, som, csr, csr_d, dim, radius, oracle.TOROID, oracle.SQUARE)
+    som.close()
+
+
+@pytest.mark.parametrize("dim,n", [(13057, 30), (13057, 4160), (40, 2000)])
+def test_sparse_sums_for_the_stencils(oracle, dim, n):
+    """The same with sums by global atomics, in two tiles of columns, and by two wavefronts a node: S comes from another call's values
+    and has to be cleared where nobody's row is."""
+    from paper_1305_1422_amd import Som
+    rows, cols = 2, 1040
+    csr = sparse_zipf_csr(n, dim, 145, mean_len=8.0, max_len=25)
+    rng = np.random.default_rng(146)
+    W = rng.random((rows * cols, dim)).astype(np.float32)
+    som = Som(rows, cols, dim, "planar", "square", codebook=torch.from_numpy(W))
+    csr_d = P.csr_to_dev(csr)
+    nodes = np.concatenate([np.arange(0, 60), np.arange(1000, 1060), np.arange(2060, 2080)]).astype(np.int32)
+    for chosen in (rows * cols, 40):                       # the first leaves sums in nearly every row, or in n of them
+        bmus = rng.integers(0, chosen, size=n).astype(np.int32)
+        som.codebook.copy_(torch.from_numpy(W))
+        som.update(csr_d, P.to_dev(bmus), 2.0)
+        torch.cuda.synchronize()
+        S, C = oracle.accumulate_csr(csr, dim, bmus, rows * cols)
+        P.check_codebook(oracle, S, C, W, som.codebook.cpu().numpy(), rows, cols, oracle.PLANAR, oracle.SQUARE, 2.0, nodes=nodes)
     som.close()
 
 
@@ -470,9 +492,8 @@ def test_dense_planes_are_declined_or_dropped(oracle):
 
 
 def test_long_rows_with_hot_column_tables_whole_epochs(oracle):
-    """Rows longer than an LDS tile of columns (17,000 > 16,384) on a context that holds the hot-column tables, with
-    more than eight instances per node: the per-node sums go through the BMU-sorted chunks with the frequent
-    columns in LDS.  Whole epochs against the oracle, registered and - same tables, other rows - unregistered data;
+    """Rows longer than an LDS tile of columns (17,000 > 13,056) on a context that holds the hot-column tables, which the
+    search uses.  Whole epochs against the oracle, registered and - same tables, other rows - unregistered data;
     one node takes half of the instances (many chunks), most nodes none."""
     from paper_1305_1422_amd import Som, capi
     n, dim, rows, cols = 1500, 17000, 5, 6
