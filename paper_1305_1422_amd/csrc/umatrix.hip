@@ -119,9 +119,13 @@ static void launch_umatrix_form(som_ctx *c, const float *W, float *U) {
 
 hipError_t launch_umatrix(som_ctx *c, const float *W, float *U) {
   // Square map, us: short rows, one by one / sixteen bytes a lane: 2,500 nodes of 300 features 9.9 / 10.3, of 500 11.3 / 10.4.  Where several
-  // nodes wait for every wavefront, one neighbour at a time has the fewer instructions: 40,000 of 30 65 against 76 four at a time.  Four
-  // wavefronts a node / one: 100 nodes of 50,000 27 / 81, 400 of 20,000 25 / 38, 2,500 of 5,000 40 / 32, 400 of 1,000 9.3 / 8.7.
-  if (c->dim <= 384 && c->k > 24 * c->n_cu) launch_umatrix_form<1, 1, true>(c, W, U);
+  // nodes wait for every wavefront, one neighbour at a time has the fewer instructions: 40,000 of 30 65 against 76 four at a time; the
+  // line, one / four neighbours at a time, square planar and hexagonal toroid: 3,600 of 30 9.7 / 9.6, 14.2 / 14.0, of 200 11.1 / 10.2, 16.6 / 15.3;
+  // 4,356 of 30 10.8 / 11.0, 16.0 / 16.7, of 64 10.8 / 10.9, 15.7 / 16.4, of 200 12.0 / 11.1, 18.3 / 17.6; 6,084 of 30 11.9 / 12.0, 17.9 / 19.1, of 200
+  // 13.8 / 13.2, 20.2 / 20.1.  Four wavefronts a node / one: 100 nodes of 50,000 27 / 81, 400 of 20,000 25 / 38, 2,500 of 5,000 40 / 32, 400 of
+  // 1,000 9.3 / 8.7.  (Hexagonal toroids of 385 features and more, one neighbour and 64 features / this: 2,500 nodes of 385 16 / 14, of 1,000
+  // 38 / 17, of 20,000 613 / 176; 40,000 of 400 128 / 113; 100 of 50,000 1,350 / 47.)
+  if (c->dim <= 384 && c->k > (c->dim <= 128 ? 16 : 24) * c->n_cu) launch_umatrix_form<1, 1, true>(c, W, U);
   else if (c->dim <= 384) launch_umatrix_form<1, 4, true>(c, W, U);
   else if (c->k <= 4 * c->n_cu && c->dim >= 4096) launch_umatrix_form<4, 4, false>(c, W, U);
   else launch_umatrix_form<1, 4, false>(c, W, U);

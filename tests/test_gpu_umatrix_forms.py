@@ -15,6 +15,7 @@ torch = pytest.importorskip("torch")
     (3, 5, 767), (3, 5, 4095), (3, 5, 4096), (3, 5, 4099),  # ... and a node by four wavefronts
     (32, 32, 4097), (25, 41, 4098),                         # ... up to 1,024 nodes
     (80, 77, 5), (72, 85, 6),                              # one neighbour at a time from there on
+    (64, 64, 128), (64, 65, 128), (64, 65, 129), (96, 64, 129), (96, 65, 129),      # ... with rows of up to 128, and of more
     (1, 1, 4100), (1, 2, 400), (2, 2, 4100), (3, 3, 390),   # few or aliased neighbours
 ])
 def test_forms(oracle, map_type, grid, rows, cols, dim):
