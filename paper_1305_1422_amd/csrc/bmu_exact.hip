@@ -597,7 +597,8 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
             arg = s_node[u0 + __ffsll((long long)m) - 1];
           }
         if (under != 1) {                          // the plain sums decide, in the place of the products no longer needed
-          int *open = reinterpret_cast<int *>(s_d2[r]);
+          typedef int __attribute__((may_alias)) word;
+          word *open = reinterpret_cast<word *>(s_d2[r]);
           int at = 0;
           for (int u0 = 0; u0 < un; u0 += kWave) {
             const int u = min(u0 + lane, un - 1);
@@ -607,6 +608,8 @@ __global__ __launch_bounds__(256) void k_refine_lists_dense(const float *__restr
             if (in) open[at + __popcll(m & ((1ull << lane) - 1))] = s_node[u];
             at += __popcll(m);
           }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // a lane reads what others have written
+          __builtin_amdgcn_wave_barrier();
           arg = nearest_listed(X + j * dim, W, dim, k, open, at, lane, nearest);
         }
       } else {
