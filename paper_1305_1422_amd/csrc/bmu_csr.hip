@@ -61,8 +61,8 @@ void csr_slice_geometry(int k, int *acc, int *sweeps, int *kpad) {
 // a thread reads four nodes (two pairs of neighbours) x four columns per tile (16-byte loads along the
 // rows), the quantised tile turns in LDS, and every column leaves as 128 contiguous bytes.  The row sums of a slab go to
 // `partial` [slab][node][3]; k_finish_node_constants adds the slabs in order.  With `met` only the columns that some instance has
-// a nonzero in are written, a third of the traffic where they are few (1,000 rows of 100 nonzeros and 50,000 Zipf columns, 2,500 nodes:
-// 185 -> 172 us).
+// a nonzero in are written (in a replay also those of earlier replays), which saves most of the writes where they are few (1,000 rows of 100
+// nonzeros and 50,000 Zipf columns, 2,500 nodes: 185 -> 172 us).
 constexpr int kCtNodes = 64;
 constexpr int kCtCols = 64;
 

@@ -164,7 +164,8 @@ __global__ __launch_bounds__(1024) void k_vec_sqnorm(const float *__restrict__ v
   }
 }
 
-// With `met` the columns of the nonzeros are marked too: met[column] = stamp, which no earlier call has used.
+// With `met` the columns of the nonzeros are marked too: met[column] = stamp, not zero and not one that another call has used (a replay of a
+// recorded call marks with its own again).
 __global__ __launch_bounds__(256) void k_csr_row_sqnorms(const int64_t *__restrict__ indptr,
                                                          const float *__restrict__ values, int64_t n,
                                                          float *__restrict__ out32, const int32_t *__restrict__ indices, int dim,

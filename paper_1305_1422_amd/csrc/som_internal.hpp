@@ -169,8 +169,9 @@ struct som_ctx {
   int Wt32_tried;
   int csr_acc, csr_sweeps;    // sparse BMU kernel: scores per lane and sweep, sweeps per node slice
   float *col_range;       // [2][64][dim] slab minima and maxima of the code-book columns (with Wt)
-  unsigned *met;          // [dim] columns that a search's nonzeros lie in: those that hold its stamp (with Wt)
-  unsigned met_stamp;     // the most recent search's that marked them (0: none, nothing holds it)
+  unsigned *met;          // [dim] columns that a search's nonzeros lie in: those that hold its stamp (with Wt); zeros at first
+  unsigned met_stamp;     // the most recent search's that marked them (0: none did).  A recorded search keeps the stamp it was recorded with, so
+                          // what its earlier replays marked stays marked: the columns that hold a stamp are at least those met, not just those
   float *qstep;           // [dim] quantisation step of every column of Wt (with Wt)
   double *ct_partial;     // [kCtMaxSlabs][k][3] row sums per column slab of the fused centring / transpose pass (with Wt)
   unsigned *qstep_max_bits;   // [1] (word of list_counts) bit pattern of the largest step
@@ -310,7 +311,7 @@ hipError_t launch_center_codebook(som_ctx *c, const float *W, bool store_centere
 hipError_t launch_row_sqnorms(som_ctx *c, const float *A, int64_t nrows, int dim, const float *mu,
                               float *out32, double *out64, unsigned *max_bits);
 hipError_t launch_csr_row_sqnorms(som_ctx *c, const int64_t *indptr, const float *values, int64_t n, float *out32,
-                                  const int32_t *indices = nullptr, unsigned *met = nullptr, unsigned stamp = 0);      // met: marks the columns;
+                                  const int32_t *indices = nullptr, unsigned *met = nullptr, unsigned stamp = 0);      // met: marks the columns of the nonzeros too
 
 // bmu_direct.hip
 bool direct_search_pays(const som_ctx *c, int64_t n, bool registered);

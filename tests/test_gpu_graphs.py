@@ -123,3 +123,82 @@ def test_smaller_calls_need_no_more_scratch(oracle):
         som.close()
         other.close()
     P.check_bmus_dense(oracle, X[:1500], W, want[1500])
+
+
+def test_recorded_searches_of_changing_sparse_rows(oracle):
+    """A search of few unregistered rows writes only the columns they meet and marks them with a number of its own, which a
+    replay uses again: its rows and the code book change in place, and plain searches of other rows come between."""
+    from gen import sparse_zipf_csr
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9400)
+    rows, cols, dim, n, m = 24, 26, 1500, 60, 40          # 2,400 nonzeros on 1,500 columns
+    stream = torch.cuda.Stream()
+
+    def draw(low):                                         # columns of one half, or anywhere
+        columns = [np.sort(rng.choice(dim // 2, size=m, replace=False)) + low for _ in range(n)]
+        return (np.arange(n + 1, dtype=np.int64) * m, np.concatenate(columns).astype(np.int32),
+                (rng.random(n * m) + 0.1).astype(np.float32))
+
+    with torch.cuda.stream(stream):
+        csr = draw(0)
+        csr_d = P.csr_to_dev(csr)
+        W = rng.random((rows * cols, dim)).astype(np.float32)
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        b = torch.empty(n, dtype=torch.int32, device="cuda")
+        som.bmus(csr_d, b)                                 # allocates what the recorded call needs
+        other = sparse_zipf_csr(30, dim, 9401, mean_len=20.0, max_len=60)
+        other_d = P.csr_to_dev(other)
+        b_other = torch.empty(30, dtype=torch.int32, device="cuda")
+        som.bmus(other_d, b_other)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            som.bmus(csr_d, b)
+        for low in (0, dim // 2, dim // 4, 0, dim // 2):
+            csr = draw(low)
+            for dst, src in zip(csr_d, csr):
+                dst.copy_(torch.from_numpy(src))
+            W = rng.random((rows * cols, dim)).astype(np.float32)
+            som.codebook.copy_(torch.from_numpy(W))
+            som.bmus(other_d, b_other)
+            b.fill_(-1)
+            graph.replay()
+            P.check_bmus_csr(oracle, csr, dim, W, b.cpu().numpy())
+            P.check_bmus_csr(oracle, other, dim, W, b_other.cpu().numpy())
+        stream.synchronize()
+        som.close()
+
+
+@pytest.mark.parametrize("dim,n", [(300, 90), (300, 3000), (300, 18000), (30000, 900)])
+def test_recorded_updates_of_changing_sparse_rows(oracle, dim, n):
+    """The sums of sparse rows by two and by eight wavefronts a node, in two copies and in several tiles, recorded once; the rows and their nodes
+    change in place between the replays."""
+    from paper_1305_1422_amd import Som
+    rng = np.random.default_rng(9500 + n)
+    rows, cols, m = 16, 18, 20
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        csr_d = (torch.arange(n + 1, dtype=torch.int64, device="cuda") * m, torch.zeros(n * m, dtype=torch.int32, device="cuda"),
+                 torch.zeros(n * m, dtype=torch.float32, device="cuda"))
+        b = torch.zeros(n, dtype=torch.int32, device="cuda")
+        W = rng.random((rows * cols, dim)).astype(np.float32)
+        som = Som(rows, cols, dim, codebook=torch.from_numpy(W))
+        som.update(csr_d, b, 1.5)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            som.update(csr_d, b, 1.5)
+        for turn in range(4):
+            start = rng.integers(dim - m, size=(n, 1))
+            csr = (csr_d[0].cpu().numpy(), (start + np.arange(m)).reshape(-1).astype(np.int32), rng.random(n * m).astype(np.float32))
+            bmus = (rng.random(n) ** (1 + turn) * rows * cols).astype(np.int32)
+            csr_d[1].copy_(torch.from_numpy(csr[1]))
+            csr_d[2].copy_(torch.from_numpy(csr[2]))
+            b.copy_(torch.from_numpy(bmus))
+            som.codebook.copy_(torch.from_numpy(W))
+            graph.replay()
+            got = som.codebook.cpu().numpy()
+            S, C = oracle.accumulate_csr(csr, dim, bmus, rows * cols)
+            P.check_codebook(oracle, S, C, W, got, rows, cols, oracle.PLANAR, oracle.SQUARE, 1.5)
+        stream.synchronize()
+        som.close()
