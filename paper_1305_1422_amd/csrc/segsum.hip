@@ -714,10 +714,12 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // the atomics save (100 nodes, 10,000 instances of 20 / 500 / 2,000 nonzeros: 300,000 columns 218 / 242, 449 / 410, 1,127 / 795; 400,000 274 /
 // 310, 506 / 539, 1,192 / 1,061; 600,000 402 / 451, 621 / 727, 1,319 / 1,486; 1,000,000 637 / 719, 857 / 1,164, 1,556 / 2,263).
 //
-// Where a node has few entries the wavefronts of a chunk have nothing to do and many workgroups to start: two of them then, four rows
-// each at a time (whole update, us, eight wavefronts / two: 10,000 nodes, rows of 200 columns and 20 nonzeros, 1 / 4 / 10 instances per
-// node 101 / 83, 118 / 90, 123 / 100; 500 and 40 104 / 89, 123 / 96, 126 / 111; 1,000 and 100 122 / 107, 144 / 131, 164 / 163; 40,000 nodes, 2,000 and
-// 100, 2 per node 785 / 697; but 2,500 nodes, 1,000 and 100, 10 per node 73 / 76, 20 86 / 89, 13,056 and 100, 5 per node 227 / 235).
+// Where a node has few entries most of eight wavefronts have nothing to do and take their time to start: four then, four rows each at a time
+// (whole update, us, eight wavefronts / four / two: 10,000 nodes, rows of 200 columns and 20 nonzeros, 1 / 4 / 10 evenly spread instances per node
+// 101 / 88 / 83, 118 / 96 / 90, 123 / 100 / 100; 1,000 and 100 122 / 110 / 107, 144 / 130 / 131, 164 / 159 / 163; 40,000 nodes, 2,000 and 100, 2 per node
+// 785 / 721 / 697; 2,500 nodes, 1,000 and 100, 10 per node 73 / 76 / 76, 20 86 / 90 / 89; but instances as an epoch's search leaves them, in
+// epochs, four / two: 7 rows a node of 12,857 columns and 100 nonzeros 3,141 / 3,160, 2,592 instances of 392 and 25 on 800 nodes 127 / 133).
+// Not with fewer nodes than CUs, where the chain of a chunk's batches is what it takes (1,270 instances of 307 and 12 on 108 nodes 87 / 89 / 92).
 //
 // Up to about a hundred instances of short rows per node: chunks of 128, which most nodes fit, so that a node is still written once. Each half
 // of the wavefronts adds its 64 rows to a copy of its own, so no sum is longer than in a chunk of 64 (whole update, us, chunks of 64 / of
@@ -1043,7 +1045,7 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
   const int64_t k = c->k, tiles = ((int64_t)c->dim + kCsrTile - 1) / kCsrTile;
   if (tiles == 1 || (tiles <= kTilesMax && n >= kTileFrom * k)) {
     const int tile = (int)((c->dim + tiles - 1) / tiles + 3) & ~3;
-    const bool few = tiles == 1 && nnz < kCsrFewEntries * k;
+    const bool few = tiles == 1 && k >= c->n_cu && nnz < kCsrFewEntries * k;
     const bool twice = !few && tiles == 1 && 2 * tile <= kCsrTile && k >= c->n_cu && n >= 48 * k && n <= 100 * k;
     const int rows = twice ? 2 * kCsrChunkRows : kCsrChunkRows;
     hipError_t e = launch_group_by_bmu(c, bmus, n, rows);
@@ -1060,7 +1062,7 @@ hipError_t launch_accumulate_csr(som_ctx *c, const int64_t *indptr, const int32_
     const dim3 grid((unsigned)max_chunks, (unsigned)ways);
     const size_t lds = (size_t)tile * sizeof(float);
     if (few)
-      hipLaunchKernelGGL((k_accumulate_csr<2, 4, 1>), grid, dim3(128), lds, c->stream, indptr, indices, values, c->dim, tile,
+      hipLaunchKernelGGL((k_accumulate_csr<4, 4, 1>), grid, dim3(256), lds, c->stream, indptr, indices, values, c->dim, tile,
                          c->sort_val[0], c->seg_off, c->chunk_off, c->chunk_node, c->k, c->S);
     else if (twice)
       hipLaunchKernelGGL((k_accumulate_csr<8, 8, 2>), grid, dim3(512), 2 * lds, c->stream, indptr, indices, values, c->dim, tile,

@@ -171,7 +171,7 @@ def test_recorded_searches_of_changing_sparse_rows(oracle):
 
 @pytest.mark.parametrize("dim,n", [(300, 90), (300, 3000), (300, 18000), (30000, 900)])
 def test_recorded_updates_of_changing_sparse_rows(oracle, dim, n):
-    """The sums of sparse rows by two and by eight wavefronts a node, in two copies and in several tiles, recorded once; the rows and their nodes
+    """The sums of sparse rows by four and by eight wavefronts a node, in two copies and in several tiles, recorded once; the rows and their nodes
     change in place between the replays."""
     from paper_1305_1422_amd import Som
     rng = np.random.default_rng(9500 + n)

@@ -206,7 +206,7 @@ def test_sparse_update_on_a_map_side_above_the_coefficient_matrix_limit(oracle):
 
 @pytest.mark.parametrize("dim,n", [(13057, 30), (13057, 4160), (40, 2000)])
 def test_sparse_sums_for_the_stencils(oracle, dim, n):
-    """The same with sums by global atomics, in two tiles of columns, and by two wavefronts a node: S comes from another call's values
+    """The same with sums by global atomics, in two tiles of columns, and by four wavefronts a node: S comes from another call's values
     and has to be cleared where nobody's row is."""
     from paper_1305_1422_amd import Som
     rows, cols = 2, 1040

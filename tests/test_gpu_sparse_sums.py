@@ -98,12 +98,13 @@ def _check_sums(rows, cols, dim, bmus, lengths, rng):
 
 
 @pytest.mark.parametrize("dim,more", [(7, 0), (500, 0), (500, 1), (501, 0), (13056, 0), (13056, 1), (13053, 0)])
-def test_sums_of_nodes_with_few_entries(dim, more):
-    """Both sides of 768 entries per node (rows of seven columns never reach it): nodes of 0, 1, 8, 9, 16, 63, 64, 65 and 130 instances."""
+@pytest.mark.parametrize("rows,cols", [(10, 12), (16, 17)])
+def test_sums_of_nodes_with_few_entries(rows, cols, dim, more):
+    """Both sides of 768 entries per node (rows of seven columns never reach it), on maps of fewer nodes than the chip has CUs and of more: nodes of
+    0, 1, 15, 16, 17, 63, 64, 65 and 130 instances."""
     rng = np.random.default_rng(dim + more)
-    rows, cols = 10, 12
     k = rows * cols
-    sizes = np.array([0, 1, 8, 9, 16, 63, 64, 65, 130, 0] + [2] * (k - 10))
+    sizes = np.array([0, 1, 15, 16, 17, 63, 64, 65, 130, 0] + [2] * (k - 10))
     bmus = np.repeat(np.arange(k), sizes)
     rng.shuffle(bmus)
     n, nnz = len(bmus), 768 * k - 1 + more
