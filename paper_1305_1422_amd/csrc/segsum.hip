@@ -702,8 +702,8 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // S.  So the chain is walked once per chunk: it has as many rows as eight wavefronts keep in registers, eight each, and
 // the tiles take their entries from there (a tile as a workgroup of its own, chunks of 256 rows: 302 us on 100,000 rows of 50,000 columns
 // and 100 nonzeros, 2,500 nodes; chunks of 256 / 128 / 64 rows with the first ones kept: 223 / 208 / 192, 1.0 GB moved; clearing S and
-// one global atomic for each nonzero outside the 256 most frequent columns: 451).  5e6 nonzeros in rows of 1,000
-// columns: 82 -> 46 us.  Few chunks of many tiles leave the chip idle, so their tiles are shared out until there are kCsrFill workgroups per CU
+// one global atomic for each nonzero outside the 256 most frequent columns: 451; what is beyond 128 entries dealt out: 177).  5e6 nonzeros in
+// rows of 1,000 columns: 82 -> 42 us.  Few chunks of many tiles leave the chip idle, so their tiles are shared out until there are kCsrFill workgroups per CU
 // (whole update, us, atomics / a chunk's tiles by one workgroup / shared out: 16 nodes of 200,000 columns, 32 instances of 100 nonzeros
 // 59 / 76 / 53, 3,200 of 2,000 355 / 1,359 / 185; 100 nodes of 50,000, 4,000 of 4,000 534 / 721 / 246).
 //
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(256) void k_combine_chunks(const int32_t *__restric
 // (whole update, us, eight wavefronts / four / two: 10,000 nodes, rows of 200 columns and 20 nonzeros, 1 / 4 / 10 evenly spread instances per node
 // 101 / 88 / 83, 118 / 96 / 90, 123 / 100 / 100; 1,000 and 100 122 / 110 / 107, 144 / 130 / 131, 164 / 159 / 163; 40,000 nodes, 2,000 and 100, 2 per node
 // 785 / 721 / 697; 2,500 nodes, 1,000 and 100, 10 per node 73 / 76 / 76, 20 86 / 90 / 89; but instances as an epoch's search leaves them, in
-// epochs, four / two: 7 rows a node of 12,857 columns and 100 nonzeros 3,141 / 3,160, 2,592 instances of 392 and 25 on 800 nodes 127 / 133).
+// epochs, four / two: 14,733 instances of 12,857 columns and 100 nonzeros on 8,816 nodes 3,141 / 3,160, 2,592 of 392 and 25 on 800 127 / 133).
 // Not with fewer nodes than CUs, where the chain of a chunk's batches is what it takes (1,270 instances of 307 and 12 on 108 nodes 87 / 89 / 92).
 //
 // Up to about a hundred instances of short rows per node: chunks of 128, which most nodes fit, so that a node is still written once. Each half
